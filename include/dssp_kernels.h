@@ -53,6 +53,16 @@ int dsspk_gemm_splitk_layers(int M, int N, int K);
 int dsspk_gemm_splitk(void* stream, const float* A_dev, long a_rs, long a_cs, const float* B_dev, long b_rs, long b_cs,
                       float* C_dev, long ldc, int M, int N, int K, const float* bias_dev, int relu,
                       float* scratch_dev, int layers);
+/* Backward pass of a fully connected layer y = x W + b in one launch: dw[n_in][n_out] = x^T dy, db[n_out] = column sums of
+ * dy and, if dx_dev is not NULL, dx[m][n_in] = dy W^T (times [x > 0] if mask_dx: x is then a post-ReLU activation and dx
+ * the gradient in front of its ReLU).  w_dev may be NULL without dx.  loss_dev (may be NULL) receives the mean of
+ * row_loss_dev[m]. */
+int dsspk_fc_bwd(void* stream, const float* x_dev, const float* dy_dev, const float* w_dev, float* dw_dev, float* db_dev,
+                 float* dx_dev, int mask_dx, const float* row_loss_dev, float* loss_dev, int m, int n_in, int n_out);
+/* Last layer and loss in one launch, at most 128 classes (-1 beyond): z[m][C] = x W + b, dz = (softmax(z) - onehot(y)) / m,
+ * row_loss[i] = logsumexp(z_i) - z_i[y_i] (its mean: dsspk_fc_bwd). */
+int dsspk_fc_softmax_xent(void* stream, const float* x_dev, const float* w_dev, const float* bias_dev, const int32_t* y_dev,
+                          float* z_dev, float* dz_dev, float* row_loss_dev, int m, int n_in, int C);
 /* out[j] = sum_i X[i][j], X is [M][N] row-major.  Fixed summation order (row slabs, then the slabs). */
 int dsspk_colsum(void* stream, const float* X_dev, float* out_dev, float* scratch_dev, long M, int N);
 /* Floats of scratch_dev dsspk_colsum needs for an [M][N] matrix (0 for short matrices: scratch_dev may be NULL). */

@@ -75,6 +75,8 @@ _SIGNATURES = {
     "dsspk_gemm_splitk_layers": (c_int, [c_int, c_int, c_int]),
     "dsspk_gemm_splitk": (c_int, [c_void_p, c_void_p, c_long, c_long, c_void_p, c_long, c_long, c_void_p, c_long,
                                   c_int, c_int, c_int, c_void_p, c_int, c_void_p, c_int]),
+    "dsspk_fc_bwd": (c_int, [c_void_p] * 7 + [c_int, c_void_p, c_void_p, c_int, c_int, c_int]),
+    "dsspk_fc_softmax_xent": (c_int, [c_void_p] * 8 + [c_int] * 3),
     "dsspk_colsum": (c_int, [c_void_p, c_void_p, c_void_p, c_void_p, c_long, c_int]),
     "dsspk_colsum_scratch_floats": (c_size_t, [c_long, c_int]),
     "dsspk_colsum_noalloc": (c_int, [c_void_p, c_void_p, c_void_p, c_long, c_int]),

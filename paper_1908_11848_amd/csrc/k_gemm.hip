@@ -1,7 +1,14 @@
 // Fully connected layers: C = op(A) * op(B) (+ bias) (ReLU), fp32 on the matrix cores.
-// One workgroup (4 wavefronts) owns a 64 x 64 tile of C; wavefront w owns the 32 x 32
-// quadrant (w / 2, w % 2).  Operands come in through generic strides, so the same kernel
-// serves y = x W (+b), dx = dy W^T and dW = x^T dy of Alg. 1's worker gradient.
+// Operands come in through generic strides, so the same product serves y = x W (+b), dx = dy W^T and
+// dW = x^T dy of Alg. 1's worker gradient.
+//
+// These products are small (0.005 to 1 GFLOP) and bound by latency, not by the matrix cores or by memory: what counts is
+// how many loads are in flight.  So there is no LDS staging and no barrier in the product: a wavefront fetches its MFMA
+// operands straight from memory into registers, G k-chunks of 16 at a time, the next G already in flight while the matrix
+// cores work on the present ones, and the wavefronts of a workgroup split the reduction index of one output tile (their
+// partial tiles are summed through LDS once, in a fixed order).  Measured, kernel time: 32 x 256 with K = 3072 17 us (93 us
+// when workgroups of 64x64 tiles walked the reduction one 16-wide LDS stage and barrier after the other, on four compute
+// units); 128 x 384 with K = 3136 17 us in one kernel (22 us with 22 layers of K and a second kernel that sums them).
 #include <mutex>
 
 #include "mma.hpp"
@@ -9,87 +16,215 @@
 
 namespace {
 
-constexpr int BM = 64, BN = 64, THREADS = 256;
+struct Operand {
+    const float* p;     // element (i, k) at p[i * s + k * ks], i = row of op(A) / column of op(B)
+    long s, ks;
+};
 
-// A_FAST_K: op(A) is k-contiguous in memory (a_cs == 1); otherwise row-contiguous (a_rs == 1).
-// B_FAST_N: op(B) is column-contiguous (b_cs == 1); otherwise k-contiguous (b_rs == 1).
-// The flags only select which index runs across neighbouring lanes so that loads coalesce.
-template <bool A_FAST_K, bool B_FAST_N>
-__global__ __launch_bounds__(THREADS) void gemm_kernel(const float* __restrict__ A, long a_rs, long a_cs,
-                                                       const float* __restrict__ B, long b_rs, long b_cs,
-                                                       float* __restrict__ C, long ldc, int M, int N, int K,
-                                                       const float* __restrict__ bias, int relu, int k_per_layer) {
-    __shared__ __attribute__((aligned(16))) float As[2][BM * mma::LDK];
-    __shared__ __attribute__((aligned(16))) float Bs[2][BN * mma::LDK];      // stored [col][k]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    // split-K: layer z of the grid takes the reduction indices [z * k_per_layer, (z + 1) * k_per_layer) and writes its
-    // partial product to the z-th [M][N] slab of C (the caller passes scratch, no bias, no ReLU)
-    const int k_lo = blockIdx.z * k_per_layer;
-    K = min(K, k_lo + k_per_layer);
-    C += (long)blockIdx.z * M * N;
-    floatx4 acc[2][2];
-    mma::zero(acc);
-    float ra[4], rb[4];
-    auto load = [&](int k0) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + e * THREADS;                     // 0 .. 1023
-            const int i = A_FAST_K ? idx / 16 : idx % 64, k = A_FAST_K ? idx % 16 : idx / 64;
-            ra[e] = (m0 + i < M && k0 + k < K) ? A[(long)(m0 + i) * a_rs + (long)(k0 + k) * a_cs] : 0.f;
-            const int j = B_FAST_N ? idx % 64 : idx / 16, kb = B_FAST_N ? idx / 64 : idx % 16;
-            rb[e] = (n0 + j < N && k0 + kb < K) ? B[(long)(k0 + kb) * b_rs + (long)(n0 + j) * b_cs] : 0.f;
-        }
-    };
-    auto store = [&](int buf) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + e * THREADS;
-            const int i = A_FAST_K ? idx / 16 : idx % 64, k = A_FAST_K ? idx % 16 : idx / 64;
-            As[buf][i * mma::LDK + k] = ra[e];
-            const int j = B_FAST_N ? idx % 64 : idx / 16, kb = B_FAST_N ? idx / 64 : idx % 16;
-            Bs[buf][j * mma::LDK + kb] = rb[e];
-        }
-    };
-    const int nk = (K - k_lo + mma::KC - 1) / mma::KC;
-    load(k_lo);
-    for (int kc = 0; kc < nk; ++kc) {
-        const int buf = kc & 1;
-        store(buf);
-        __syncthreads();
-        if (kc + 1 < nk) load(k_lo + (kc + 1) * mma::KC);
-        mma::chunk16<2, 2, false, true>(As[buf], mma::LDK, Bs[buf], mma::LDK, 32 * (wave >> 1), 32 * (wave & 1), acc, lane);
-    }
-    mma::drain();
+// acc += (rows row0 .. of a) * (columns col0 .. of b) over the k-chunks first, first + every, ... of [0, K).
+//   AV / BV: the operand is contiguous along k, 16-byte aligned with a stride and K that are multiples of 4 (one 16-byte
+//   load per lane and chunk); otherwise four scalar loads, which coalesce across the lanes when i is the contiguous index.
+// Rows and columns beyond M / N are clamped (the caller drops those results), k beyond K reads as zero.
+template <int WM, int WN, int G, bool AV, bool BV>
+__device__ __forceinline__ void wave_product(const Operand& a, const Operand& b, int M, int N, int row0, int col0, int K, int first,
+                                             int every, floatx4 (&acc)[WM][WN], int lane) {
     const int l16 = lane & 15, q = lane >> 4;
+    const float *pa[WM], *pb[WN];
 #pragma unroll
-    for (int wm = 0; wm < 2; ++wm)
+    for (int w = 0; w < WM; ++w) pa[w] = a.p + (long)min(row0 + 16 * w + l16, M - 1) * a.s;
 #pragma unroll
-        for (int wn = 0; wn < 2; ++wn) {
-            const int col = n0 + 32 * (wave & 1) + 16 * wn + l16;
-            if (col >= N) continue;
-            const float bv = bias ? bias[col] : 0.f;
+    for (int w = 0; w < WN; ++w) pb[w] = b.p + (long)min(col0 + 16 * w + l16, N - 1) * b.s;
+    const int chunks = (K + mma::KC - 1) / mma::KC;
+    float fa[2][G][WM][4], fb[2][G][WN][4];
+    auto fetch = [&](int buf, int c0) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = m0 + 32 * (wave >> 1) + 16 * wm + 4 * q + v;
-                if (row >= M) continue;
-                float x = acc[wm][wn][v] + bv;
-                if (relu) x = fmaxf(x, 0.f);
-                C[(long)row * ldc + col] = x;
+        for (int u = 0; u < G; ++u) {
+            const int c = c0 + u * every;
+            if (c >= chunks) {                          // uniform over the wavefront
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+#pragma unroll
+                    for (int w = 0; w < WM; ++w) fa[buf][u][w][s] = 0.f;
+#pragma unroll
+                    for (int w = 0; w < WN; ++w) fb[buf][u][w][s] = 0.f;
+                }
+                continue;
+            }
+            const int k = c * mma::KC + 4 * q;
+            if (AV && BV ? true : c * mma::KC + mma::KC <= K) {
+                // with K a multiple of 4 a lane's four k are all inside or all outside
+                const bool in = !(AV && BV) || k < K;
+                const int kc = in ? k : 0;
+#pragma unroll
+                for (int w = 0; w < WM; ++w) {
+                    if constexpr (AV) {
+                        const float4 v = *reinterpret_cast<const float4*>(pa[w] + kc);
+                        fa[buf][u][w][0] = in ? v.x : 0.f; fa[buf][u][w][1] = in ? v.y : 0.f;
+                        fa[buf][u][w][2] = in ? v.z : 0.f; fa[buf][u][w][3] = in ? v.w : 0.f;
+                    } else {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) fa[buf][u][w][s] = pa[w][(long)(kc + s) * a.ks];
+                    }
+                }
+#pragma unroll
+                for (int w = 0; w < WN; ++w) {
+                    if constexpr (BV) {
+                        const float4 v = *reinterpret_cast<const float4*>(pb[w] + kc);
+                        fb[buf][u][w][0] = in ? v.x : 0.f; fb[buf][u][w][1] = in ? v.y : 0.f;
+                        fb[buf][u][w][2] = in ? v.z : 0.f; fb[buf][u][w][3] = in ? v.w : 0.f;
+                    } else {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) fb[buf][u][w][s] = pb[w][(long)(kc + s) * b.ks];
+                    }
+                }
+            } else {                                    // the partial last chunk
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const bool in = k + s < K;
+                    const long kk = in ? k + s : 0;
+#pragma unroll
+                    for (int w = 0; w < WM; ++w) { const float v = pa[w][kk * a.ks]; fa[buf][u][w][s] = in ? v : 0.f; }
+#pragma unroll
+                    for (int w = 0; w < WN; ++w) { const float v = pb[w][kk * b.ks]; fb[buf][u][w][s] = in ? v : 0.f; }
+                }
             }
         }
+    };
+    auto multiply = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < G; ++u)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[buf][u][i][s], fb[buf][u][j][s], acc[i][j], 0, 0, 0);
+    };
+    if (first >= chunks) return;
+    fetch(0, first);
+    for (int c = first; c < chunks; c += 2 * G * every) {
+        if (c + G * every < chunks) fetch(1, c + G * every);
+        multiply(0);
+        if (c + G * every >= chunks) break;
+        if (c + 2 * G * every < chunks) fetch(0, c + 2 * G * every);
+        multiply(1);
+    }
+}
+
+struct Epilogue {
+    float* C;                   // element (i, j) at C[i * ldc + j]
+    long ldc;
+    const float* bias;          // [N] or null
+    int relu;
+    const float* mask;          // laid out as C, or null: the result is 0 where mask <= 0
+};
+
+__device__ __forceinline__ void store_result(const Epilogue& e, int row, int col, float x) {
+    if (e.bias) x += e.bias[col];
+    if (e.relu) x = fmaxf(x, 0.f);
+    if (e.mask) x = e.mask[(long)row * e.ldc + col] > 0.f ? x : 0.f;
+    e.C[(long)row * e.ldc + col] = x;
+}
+
+// One output tile by a workgroup of GM x GN x KW wavefronts, each 16 WM x 16 WN outputs of it; the KW wavefronts of an
+// output sub-tile take its k-chunks in turn.  lds: KW * GM * GN * 256 * WM * WN floats if KW > 1.
+template <int WM, int WN, int GM, int GN, int G, bool AV, bool BV>
+__device__ __forceinline__ void tile_product(const Operand& a, const Operand& b, int M, int N, int K, int tile_m, int tile_n,
+                                             const Epilogue& e, float* lds) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int kw = blockDim.x / (64 * GM * GN), sub = wave % (GM * GN), part = wave / (GM * GN);
+    const int row0 = (tile_m * GM + sub / GN) * 16 * WM, col0 = (tile_n * GN + sub % GN) * 16 * WN;
+    floatx4 acc[WM][WN];
+    mma::zero(acc);
+    wave_product<WM, WN, G, AV, BV>(a, b, M, N, row0, col0, K, part, kw, acc, lane);
+    mma::drain();
+    const int l16 = lane & 15, q = lane >> 4;
+    if (kw == 1) {
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int row = row0 + 16 * i + 4 * q + v, col = col0 + 16 * j + l16;
+                    if (row < M && col < N) store_result(e, row, col, acc[i][j][v]);
+                }
+        return;
+    }
+    constexpr int TILE = 256 * WM * WN, ALL = TILE * GM * GN;
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                lds[part * ALL + sub * TILE + (16 * i + 4 * q + v) * 16 * WN + 16 * j + l16] = acc[i][j][v];
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < ALL; idx += blockDim.x) {
+        float s = 0.f;
+        for (int p = 0; p < kw; ++p) s += lds[p * ALL + idx];
+        const int t = idx / TILE, r = idx % TILE;
+        const int row = (tile_m * GM + t / GN) * 16 * WM + r / (16 * WN), col = (tile_n * GN + t % GN) * 16 * WN + r % (16 * WN);
+        if (row < M && col < N) store_result(e, row, col, s);
+    }
+}
+
+// Tile shapes: BIG 64x64 by 2x2 wavefronts of 32x32; MID 32x32 and SMALL 16x16 by one output sub-tile, the wavefronts
+// splitting k.  Rule: the largest tile that still gives half a chip of workgroups (128): the products here have few output
+// tiles and the time of one is the time of its slowest workgroup, while a smaller tile reads its operands more often.
+enum { BIG, MID, SMALL };
+inline int tile_shape(int M, int N) {
+    if ((long)ceil_div(M, 64) * ceil_div(N, 64) >= 128) return BIG;
+    return (long)ceil_div(M, 32) * ceil_div(N, 32) >= 128 ? MID : SMALL;
+}
+inline int tile_edge(int shape) { return shape == BIG ? 64 : shape == MID ? 32 : 16; }
+
+template <int SHAPE, bool AV, bool BV>
+__device__ __forceinline__ void shaped_tile(const Operand& a, const Operand& b, int M, int N, int K, int tile_m, int tile_n,
+                                            const Epilogue& e, float* lds) {
+    if constexpr (SHAPE == BIG) tile_product<2, 2, 2, 2, 1, AV, BV>(a, b, M, N, K, tile_m, tile_n, e, lds);
+    else if constexpr (SHAPE == MID) tile_product<2, 2, 1, 1, 1, AV, BV>(a, b, M, N, K, tile_m, tile_n, e, lds);
+    else tile_product<1, 1, 1, 1, 4, AV, BV>(a, b, M, N, K, tile_m, tile_n, e, lds);
+}
+
+// LDS (bytes) of a tile whose reduction is split over the wavefronts of `threads`
+inline size_t tile_lds(int shape, int threads) {
+    const int waves = threads / 64, kw = shape == BIG ? waves / 4 : waves;
+    return kw > 1 ? sizeof(float) * waves * (shape == SMALL ? 256 : 1024) : 0;
+}
+
+// Layer z of the grid takes the reduction indices [z * k_per_layer, (z + 1) * k_per_layer) and writes its product to the
+// z-th [M][N] slab of C (split-K with a second kernel; one layer otherwise).
+template <int SHAPE, bool AV, bool BV>
+__global__ __launch_bounds__(1024) void gemm_kernel(Operand a, Operand b, Epilogue e, int M, int N, int K, int k_per_layer) {
+    extern __shared__ float lds[];
+    const int k_lo = blockIdx.z * k_per_layer;
+    a.p += (long)k_lo * a.ks; b.p += (long)k_lo * b.ks;
+    e.C += (long)blockIdx.z * M * N;
+    shaped_tile<SHAPE, AV, BV>(a, b, M, N, min(K - k_lo, k_per_layer), blockIdx.y, blockIdx.x, e, lds);
+}
+
+// Threads of a workgroup: a wavefront is worth having for two k-chunks; up to 16 of them for the one-sub-tile shapes.
+inline int tile_threads(int shape, int K) {
+    const int chunks = ceil_div(K, mma::KC);
+    if (shape == BIG) return 256;
+    const int waves = chunks / 2 < 1 ? 1 : chunks / 2 > 16 ? 16 : chunks / 2;
+    return 64 * waves;
+}
+
+inline bool vector_k(const Operand& o, int K) {
+    return o.ks == 1 && o.s % 4 == 0 && K % 4 == 0 && (reinterpret_cast<uintptr_t>(o.p) & 15) == 0;
 }
 
 // out[slab][j] = sum over the rows i of the slab of X[i][j]: a workgroup owns 64 columns and one slab of rows
 // (blockIdx.y), four row lanes each adding every fourth row of the slab in ascending order, eight loads in flight.
 // Tall matrices take two passes (slab sums into scratch, then the sum of the slabs), short ones a single slab.
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ X, float* __restrict__ out, long M, int N,
-                                                     long rows_per_slab) {
-    __shared__ float part[4][64];
+__device__ __forceinline__ void colsum_block(const float* __restrict__ X, float* __restrict__ out, long r0, long r1, int N, int col_block,
+                                             float* lds) {
+    float(*part)[64] = reinterpret_cast<float(*)[64]>(lds);       // [4][64]
     const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int col = blockIdx.x * 64 + c;
-    const long r0 = (long)blockIdx.y * rows_per_slab;
-    const long r1 = r0 + rows_per_slab < M ? r0 + rows_per_slab : M;
+    const int col = col_block * 64 + c;
     float s = 0.f;
     if (col < N) {
         long i = r0 + g;
@@ -104,7 +239,14 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ X
     }
     part[g][c] = s;
     __syncthreads();
-    if (g == 0 && col < N) out[(long)blockIdx.y * N + col] = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
+    if (g == 0 && col < N) out[col] = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
+}
+
+__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ X, float* __restrict__ out, long M, int N,
+                                                     long rows_per_slab) {
+    __shared__ float lds[256];
+    const long r0 = (long)blockIdx.y * rows_per_slab;
+    colsum_block(X, out + (long)blockIdx.y * N, r0, r0 + rows_per_slab < M ? r0 + rows_per_slab : M, N, blockIdx.x, lds);
 }
 
 constexpr int COLSUM_SLABS = 256;
@@ -122,19 +264,116 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float* __restrict
     C[(e / N) * ldc + col] = s;
 }
 
-int launch_gemm(hipStream_t s, const float* A, long a_rs, long a_cs, const float* B, long b_rs, long b_cs, float* C, long ldc,
-                int M, int N, int K, const float* bias, int relu, int layers) {
+int launch_gemm(hipStream_t s, const Operand& a, const Operand& b, const Epilogue& e, int M, int N, int K, int layers) {
     const int chunks = ceil_div(K, mma::KC);
     const int k_per_layer = ceil_div(chunks, layers) * mma::KC;
-    dim3 grid(ceil_div(N, BN), ceil_div(M, BM), ceil_div(K, k_per_layer));
-    const bool ak = a_cs == 1, bn = b_cs == 1;
-#define GO(AK, BNF) hipLaunchKernelGGL((gemm_kernel<AK, BNF>), grid, dim3(THREADS), 0, s, A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, M, N, K, bias, relu, k_per_layer)
-    if (ak && bn) GO(true, true);
-    else if (ak) GO(true, false);
-    else if (bn) GO(false, true);
-    else GO(false, false);
+    const int shape = tile_shape(M, N), edge = tile_edge(shape), threads = tile_threads(shape, k_per_layer < K ? k_per_layer : K);
+    const dim3 grid(ceil_div(N, edge), ceil_div(M, edge), ceil_div(K, k_per_layer));
+    const bool av = vector_k(a, K), bv = vector_k(b, K);
+    const size_t lds = tile_lds(shape, threads);
+#define GO(S, AV, BV) hipLaunchKernelGGL((gemm_kernel<S, AV, BV>), grid, dim3(threads), lds, s, a, b, e, M, N, K, k_per_layer)
+#define GO_V(S) do { if (av && bv) GO(S, true, true); else if (av) GO(S, true, false); else if (bv) GO(S, false, true); else GO(S, false, false); } while (0)
+    if (shape == BIG) GO_V(BIG); else if (shape == MID) GO_V(MID); else GO_V(SMALL);
+#undef GO_V
 #undef GO
     return (int)grid.z;
+}
+
+// Backward pass of a fully connected layer y = x W + b in one launch: dW = x^T dy, db = column sums of dy, and (dx wanted)
+// dx = dy W^T, masked by x > 0 if x is a post-ReLU activation; optionally also the mean of the mini-batch's losses.  The
+// products do not depend on each other, so their tiles are workgroups of one grid; as kernels of their own (with the bias
+// sums and the ReLU mask two more) each of them cost a dependent launch of 4 to 6 us.
+struct FcBwd {
+    Operand xt, dy_n;           // dW = xt * dy_n
+    Operand dy_k, wt;           // dx = dy_k * wt
+    Epilogue edw, edx;
+    const float* dy; float* db;
+    const float* row_loss; float* loss;
+    int m, n_in, n_out;
+    int tiles_n_w, tiles_n_x;   // output tiles side by side
+    int blocks_w, blocks_x, blocks_b;
+};
+
+constexpr int FC_THREADS = 256;
+
+template <int SHW, int SHX, bool V>
+__global__ __launch_bounds__(FC_THREADS) void fc_bwd_kernel(FcBwd f) {
+    extern __shared__ float lds[];
+    int b = blockIdx.x;
+    if (b < f.blocks_x) {
+        shaped_tile<SHX, V, V>(f.dy_k, f.wt, f.m, f.n_in, f.n_out, b / f.tiles_n_x, b % f.tiles_n_x, f.edx, lds);
+        return;
+    }
+    b -= f.blocks_x;
+    if (b < f.blocks_w) {
+        shaped_tile<SHW, false, false>(f.xt, f.dy_n, f.n_in, f.n_out, f.m, b / f.tiles_n_w, b % f.tiles_n_w, f.edw, lds);
+        return;
+    }
+    b -= f.blocks_w;
+    if (b < f.blocks_b) {
+        colsum_block(f.dy, f.db, 0, f.m, f.n_out, b, lds);
+        return;
+    }
+    float s = 0.f;              // mean loss: a lane adds its samples in order, lanes by a tree
+    for (int i = threadIdx.x; i < f.m; i += FC_THREADS) s += f.row_loss[i];
+    lds[threadIdx.x] = s;
+    __syncthreads();
+    for (int h = FC_THREADS / 2; h >= 1; h >>= 1) {
+        if ((int)threadIdx.x < h) lds[threadIdx.x] += lds[threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *f.loss = lds[0] / (float)f.m;
+}
+
+// Last layer and loss in one kernel: logits z = x W + b for 16 samples per workgroup (every class, at most 128), then the
+// softmax of those rows from LDS: dz = (softmax(z) - onehot(y)) / m, row_loss[i] = logsumexp(z_i) - z_i[y_i].
+// Eight wavefronts: class tiles side by side, the rest of them split the inputs.
+constexpr int SX_WAVES = 8, SX_MAX_C = 128;
+template <bool AV>
+__global__ __launch_bounds__(64 * SX_WAVES) void fc_softmax_kernel(Operand x, Operand w, const float* __restrict__ bias,
+                                                                   const int32_t* __restrict__ label, float* __restrict__ z,
+                                                                   float* __restrict__ dz, float* __restrict__ row_loss, int m,
+                                                                   int n_in, int C) {
+    __shared__ float part[SX_WAVES][16][17];
+    __shared__ float Z[16][SX_MAX_C + 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l16 = lane & 15, q = lane >> 4;
+    const int tiles = (C + 15) / 16, kw = SX_WAVES / tiles;        // tiles <= 8
+    const int row0 = blockIdx.x * 16;
+    if (wave < tiles * kw) {
+        floatx4 acc[1][1];
+        mma::zero(acc);
+        wave_product<1, 1, 4, AV, false>(x, w, m, C, row0, 16 * (wave % tiles), n_in, wave / tiles, kw, acc, lane);
+        mma::drain();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[wave][4 * q + v][l16] = acc[0][0][v];
+    }
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < 16 * C; idx += 64 * SX_WAVES) {
+        const int r = idx / C, c = idx - r * C;
+        float s = 0.f;
+        for (int p = 0; p < kw; ++p) s += part[p * tiles + c / 16][r][c % 16];
+        s += bias[c];
+        Z[r][c] = s;
+        if (row0 + r < m) z[(long)(row0 + r) * C + c] = s;
+    }
+    __syncthreads();
+    const float invm = 1.0f / (float)m;
+    for (int r = wave; r < 16 && row0 + r < m; r += SX_WAVES) {
+        const long i = row0 + r;
+        float mx = -INFINITY;
+        for (int j = lane; j < C; j += 64) mx = fmaxf(mx, Z[r][j]);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        float se = 0.f;
+        for (int j = lane; j < C; j += 64) se += expf(Z[r][j] - mx);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) se += __shfl_xor(se, o);
+        const int y = label[i];
+        if (lane == 0) row_loss[i] = logf(se) + mx - Z[r][y];
+        const float inv = 1.0f / se;
+        for (int j = lane; j < C; j += 64) dz[i * C + j] = (expf(Z[r][j] - mx) * inv - (j == y ? 1.f : 0.f)) * invm;
+    }
 }
 
 }  // namespace
@@ -142,15 +381,15 @@ int launch_gemm(hipStream_t s, const float* A, long a_rs, long a_cs, const float
 extern "C" int dsspk_gemm(void* stream, const float* A, long a_rs, long a_cs, const float* B, long b_rs, long b_cs,
                           float* C, long ldc, int M, int N, int K, const float* bias, int relu) {
     if (!A || !B || !C || M < 1 || N < 1 || K < 1) return -1;
-    launch_gemm((hipStream_t)stream, A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, M, N, K, bias, relu, 1);
+    launch_gemm((hipStream_t)stream, Operand{A, a_rs, a_cs}, Operand{B, b_cs, b_rs}, Epilogue{C, ldc, bias, relu, nullptr}, M, N, K, 1);
     return DSSPK_LAUNCH_RC();
 }
 
-// Layers worth splitting K into (K of 1024 and more, fewer than 128 output tiles): enough workgroups to cover the
-// chip, at least 8 k-chunks of work per layer.
+// Layers worth splitting K into (K of 1024 and more, fewer than 128 output tiles of 64 x 64): enough workgroups to cover
+// the chip, at least 8 k-chunks of work per layer.
 extern "C" int dsspk_gemm_splitk_layers(int M, int N, int K) {
     if (M < 1 || N < 1 || K < 1) return 0;
-    const int tiles = ceil_div(N, BN) * ceil_div(M, BM), chunks = ceil_div(K, mma::KC);
+    const int tiles = ceil_div(N, 64) * ceil_div(M, 64), chunks = ceil_div(K, mma::KC);
     if (tiles >= 128 || chunks < 64) return 1;
     const int want = ceil_div(384, tiles), most = chunks / 8;
     const int layers = want < most ? want : most;
@@ -164,9 +403,49 @@ extern "C" int dsspk_gemm_splitk(void* stream, const float* A, long a_rs, long a
     if (layers == 1) return dsspk_gemm(stream, A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, M, N, K, bias, relu);
     if (!scratch) return -1;
     hipStream_t s = (hipStream_t)stream;
-    const int launched = launch_gemm(s, A, a_rs, a_cs, B, b_rs, b_cs, scratch, N, M, N, K, nullptr, 0, layers);
+    const int launched = launch_gemm(s, Operand{A, a_rs, a_cs}, Operand{B, b_cs, b_rs}, Epilogue{scratch, N, nullptr, 0, nullptr}, M, N, K, layers);
     const long n = (long)M * N;
     hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)ceil_div(n, 256L)), dim3(256), 0, s, scratch, C, ldc, M, N, launched, bias, relu);
+    return DSSPK_LAUNCH_RC();
+}
+
+extern "C" int dsspk_fc_bwd(void* stream, const float* x, const float* dy, const float* w, float* dw, float* db, float* dx, int mask_dx,
+                            const float* row_loss, float* loss, int m, int n_in, int n_out) {
+    if (!x || !dy || !dw || !db || (dx && !w) || (loss && !row_loss) || m < 1 || n_in < 1 || n_out < 1) return -1;
+    FcBwd f;
+    f.xt = Operand{x, 1, n_in}; f.dy_n = Operand{dy, 1, n_out};
+    f.dy_k = Operand{dy, n_out, 1}; f.wt = Operand{w, n_out, 1};
+    f.edw = Epilogue{dw, n_out, nullptr, 0, nullptr};
+    f.edx = Epilogue{dx, n_in, nullptr, 0, mask_dx ? x : nullptr};
+    f.dy = dy; f.db = db; f.row_loss = row_loss; f.loss = loss; f.m = m; f.n_in = n_in; f.n_out = n_out;
+    const int shw = tile_shape(n_in, n_out), shx = tile_shape(m, n_in), ew = tile_edge(shw), ex = tile_edge(shx);
+    f.tiles_n_w = ceil_div(n_out, ew); f.tiles_n_x = ceil_div(n_in, ex);
+    f.blocks_w = f.tiles_n_w * ceil_div(n_in, ew);
+    f.blocks_x = dx ? f.tiles_n_x * ceil_div(m, ex) : 0;
+    f.blocks_b = ceil_div(n_out, 64);
+    const int grid = f.blocks_x + f.blocks_w + f.blocks_b + (loss ? 1 : 0);
+    const bool v = dx && vector_k(f.dy_k, n_out) && vector_k(f.wt, n_out);
+    size_t lds = tile_lds(shw, FC_THREADS), ldx = tile_lds(shx, FC_THREADS);
+    if (lds < ldx) lds = ldx;
+    if (lds < sizeof(float) * FC_THREADS) lds = sizeof(float) * FC_THREADS;
+#define GO(W, X) do { if (v) hipLaunchKernelGGL((fc_bwd_kernel<W, X, true>), dim3(grid), dim3(FC_THREADS), lds, (hipStream_t)stream, f); \
+                      else hipLaunchKernelGGL((fc_bwd_kernel<W, X, false>), dim3(grid), dim3(FC_THREADS), lds, (hipStream_t)stream, f); } while (0)
+#define GO_X(W) do { if (shx == BIG) GO(W, BIG); else if (shx == MID) GO(W, MID); else GO(W, SMALL); } while (0)
+    if (shw == BIG) GO_X(BIG); else if (shw == MID) GO_X(MID); else GO_X(SMALL);
+#undef GO_X
+#undef GO
+    return DSSPK_LAUNCH_RC();
+}
+
+extern "C" int dsspk_fc_softmax_xent(void* stream, const float* x, const float* w, const float* bias, const int32_t* y, float* z,
+                                     float* dz, float* row_loss, int m, int n_in, int C) {
+    if (!x || !w || !bias || !y || !z || !dz || !row_loss || m < 1 || n_in < 1 || C < 1 || C > SX_MAX_C) return -1;
+    const Operand a{x, n_in, 1}, b{w, 1, C};
+    const dim3 grid(ceil_div(m, 16)), threads(64 * SX_WAVES);
+    if (vector_k(a, n_in))
+        hipLaunchKernelGGL((fc_softmax_kernel<true>), grid, threads, 0, (hipStream_t)stream, a, b, bias, y, z, dz, row_loss, m, n_in, C);
+    else
+        hipLaunchKernelGGL((fc_softmax_kernel<false>), grid, threads, 0, (hipStream_t)stream, a, b, bias, y, z, dz, row_loss, m, n_in, C);
     return DSSPK_LAUNCH_RC();
 }
 

@@ -43,7 +43,7 @@ struct Plan {
     std::vector<Tens> tens;
 
     // common tail
-    size_t logits = 0, dlogits = 0, fc_scratch = 0, colsum_scratch = 0, wg_scratch = 0, wg_scratch2 = 0, bn_scratch = 0, bn_scratch2 = 0, tot_a = 0, tot_b = 0;
+    size_t logits = 0, dlogits = 0, row_loss = 0, colsum_scratch = 0, wg_scratch = 0, wg_scratch2 = 0, bn_scratch = 0, bn_scratch2 = 0, tot_a = 0, tot_b = 0;
     // MLP
     size_t mlp_a1 = 0, mlp_da1 = 0;
     // AlexNet-style
@@ -162,9 +162,7 @@ struct Plan {
         logits = a.floats((size_t)m * classes);
         dlogits = a.floats((size_t)m * classes);
         tens.push_back({2, logits, (int64_t)m * classes});
-        // split-K scratch of the wide fully connected forward product (3136 -> 384)
-        fc_scratch = a.floats(id == DSSP_MODEL_ALEXNET_DS ? (size_t)dsspk_gemm_splitk_layers(m, 384, 3136) * m * 384
-                              : id == DSSP_MODEL_ALEXNET_3C ? (size_t)dsspk_gemm_splitk_layers(m, 384, 3136) * m * 384 : 1);
+        row_loss = a.floats((size_t)m);
         {
             size_t cs = 1;
             if (id == DSSP_MODEL_ALEXNET_DS || id == DSSP_MODEL_ALEXNET_3C) cs = dsspk_colsum_scratch_floats((long)m * 32 * 32, 64) + 1;
@@ -188,20 +186,31 @@ namespace {
         if (rc_) { err = #call; return rc_; }                            \
     } while (0)
 
+// Last fully connected layer (input a [m][n_in], weights at w + fw, biases at w + fb), softmax cross-entropy and the
+// backward pass of that layer: logits, dlogits, gradients of fw / fb, the mini-batch's loss, and d_in (masked by a > 0 if
+// mask), the gradient in front of a.
+int last_layer(Plan* P, char* ws, void* s, const float* a, int n_in, const int32_t* y, const float* w, float* g, int64_t fw, int64_t fb,
+               float* d_in, int mask, float* loss, std::string& err) {
+    const int m = P->m, C = P->n_classes;
+    float* z = (float*)(ws + P->logits); float* dz = (float*)(ws + P->dlogits); float* rl = (float*)(ws + P->row_loss);
+    if (C <= 128) {
+        RUN(dsspk_fc_softmax_xent(s, a, w + fw, w + fb, y, z, dz, rl, m, n_in, C));
+        RUN(dsspk_fc_bwd(s, a, dz, w + fw, g + fw, g + fb, d_in, mask, rl, loss, m, n_in, C));
+    } else {                    // more classes than the fused kernel holds
+        RUN(dsspk_gemm(s, a, n_in, 1, w + fw, C, 1, z, C, m, C, n_in, w + fb, 0));
+        RUN(dsspk_softmax_xent(s, z, y, dz, loss, m, C));
+        RUN(dsspk_fc_bwd(s, a, dz, w + fw, g + fw, g + fb, d_in, mask, nullptr, nullptr, m, n_in, C));
+    }
+    return 0;
+}
+
 int step_mlp(Plan* P, char* ws, void* s, const float* x, const int32_t* y, const float* w, float* g, float* loss, std::string& err) {
     const int m = P->m, C = P->n_classes;
     float* a1 = (float*)(ws + P->mlp_a1); float* da1 = (float*)(ws + P->mlp_da1);
-    float* z = (float*)(ws + P->logits); float* dz = (float*)(ws + P->dlogits);
     const int64_t w1 = 0, b1 = 3072 * 256, w2 = b1 + 256, b2 = w2 + 256 * (int64_t)C;
-    RUN(dsspk_gemm(s, x, 3072, 1, w + w1, 256, 1, a1, 256, m, 256, 3072, w + b1, 1));   // (split-K: one more launch, and this net is bound by launches)
-    RUN(dsspk_gemm(s, a1, 256, 1, w + w2, C, 1, z, C, m, C, 256, w + b2, 0));
-    RUN(dsspk_softmax_xent(s, z, y, dz, loss, m, C));
-    RUN(dsspk_gemm(s, a1, 1, 256, dz, C, 1, g + w2, C, 256, C, m, nullptr, 0));          // dW2 = a1^T dz
-    RUN(dsspk_colsum(s, dz, g + b2, nullptr, m, C));
-    RUN(dsspk_gemm(s, dz, C, 1, w + w2, 1, C, da1, 256, m, 256, C, nullptr, 0));         // da1 = dz W2^T
-    RUN(dsspk_relu_bwd(s, da1, a1, (long)m * 256));
-    RUN(dsspk_gemm(s, x, 1, 3072, da1, 256, 1, g + w1, 256, 3072, 256, m, nullptr, 0));  // dW1 = x^T dz1
-    RUN(dsspk_colsum(s, da1, g + b1, nullptr, m, 256));
+    RUN(dsspk_gemm(s, x, 3072, 1, w + w1, 256, 1, a1, 256, m, 256, 3072, w + b1, 1));
+    if (int rc = last_layer(P, ws, s, a1, 256, y, w, g, w2, b2, da1, 1, loss, err)) return rc;
+    RUN(dsspk_fc_bwd(s, x, da1, nullptr, g + w1, g + b1, nullptr, 0, nullptr, nullptr, m, 3072, 256));
     return 0;
 }
 
@@ -210,7 +219,7 @@ int step_alexnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, c
     auto F = [&](size_t off) { return (float*)(ws + off); };
     float *a1 = F(P->ax_a1), *p1 = F(P->ax_p1), *a2 = F(P->ax_a2), *p2 = F(P->ax_p2), *a3 = F(P->ax_a3), *a4 = F(P->ax_a4);
     uint8_t *arg1 = (uint8_t*)(ws + P->ax_arg1), *arg2 = (uint8_t*)(ws + P->ax_arg2);
-    float *z = F(P->logits), *dz = F(P->dlogits), *da4 = F(P->ax_da4), *da3 = F(P->ax_da3), *dp2 = F(P->ax_dp2);
+    float *da4 = F(P->ax_da4), *da3 = F(P->ax_da3), *dp2 = F(P->ax_dp2);
     float *da2 = F(P->ax_da2), *dp1 = F(P->ax_dp1), *da1 = F(P->ax_da1), *scr = F(P->wg_scratch);
     const int64_t cw1 = 0, cb1 = 4800, cw2 = cb1 + 64, cb2 = cw2 + 102400, fw1 = cb2 + 64, fb1 = fw1 + 3136 * 384,
                   fw2 = fb1 + 384, fb2 = fw2 + 384 * 192, fw3 = fb2 + 192, fb3 = fw3 + 192 * (int64_t)C;
@@ -219,23 +228,12 @@ int step_alexnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, c
     RUN(dsspk_maxpool_fwd(s, a1, p1, arg1, m, 32, 32, 64));
     RUN(dsspk_conv_fwd(s, p1, w + cw2, w + cb2, a2, m, 15, 15, 64, 64, 5, 5, 1, 2, 1, nullptr));
     RUN(dsspk_maxpool_fwd(s, a2, p2, arg2, m, 15, 15, 64));
-    RUN(dsspk_gemm_splitk(s, p2, 3136, 1, w + fw1, 384, 1, a3, 384, m, 384, 3136, w + fb1, 1, F(P->fc_scratch),
-                          dsspk_gemm_splitk_layers(m, 384, 3136)));
+    RUN(dsspk_gemm(s, p2, 3136, 1, w + fw1, 384, 1, a3, 384, m, 384, 3136, w + fb1, 1));
     RUN(dsspk_gemm(s, a3, 384, 1, w + fw2, 192, 1, a4, 192, m, 192, 384, w + fb2, 1));
-    RUN(dsspk_gemm(s, a4, 192, 1, w + fw3, C, 1, z, C, m, C, 192, w + fb3, 0));
-    RUN(dsspk_softmax_xent(s, z, y, dz, loss, m, C));
+    if (int rc = last_layer(P, ws, s, a4, 192, y, w, g, fw3, fb3, da4, 1, loss, err)) return rc;
     // backward
-    RUN(dsspk_gemm(s, a4, 1, 192, dz, C, 1, g + fw3, C, 192, C, m, nullptr, 0));
-    RUN(dsspk_colsum(s, dz, g + fb3, nullptr, m, C));
-    RUN(dsspk_gemm(s, dz, C, 1, w + fw3, 1, C, da4, 192, m, 192, C, nullptr, 0));
-    RUN(dsspk_relu_bwd(s, da4, a4, (long)m * 192));
-    RUN(dsspk_gemm(s, a3, 1, 384, da4, 192, 1, g + fw2, 192, 384, 192, m, nullptr, 0));
-    RUN(dsspk_colsum(s, da4, g + fb2, nullptr, m, 192));
-    RUN(dsspk_gemm(s, da4, 192, 1, w + fw2, 1, 192, da3, 384, m, 384, 192, nullptr, 0));
-    RUN(dsspk_relu_bwd(s, da3, a3, (long)m * 384));
-    RUN(dsspk_gemm(s, p2, 1, 3136, da3, 384, 1, g + fw1, 384, 3136, 384, m, nullptr, 0));
-    RUN(dsspk_colsum(s, da3, g + fb1, nullptr, m, 384));
-    RUN(dsspk_gemm(s, da3, 384, 1, w + fw1, 1, 384, dp2, 3136, m, 3136, 384, nullptr, 0));
+    RUN(dsspk_fc_bwd(s, a3, da4, w + fw2, g + fw2, g + fb2, da3, 1, nullptr, nullptr, m, 384, 192));
+    RUN(dsspk_fc_bwd(s, p2, da3, w + fw1, g + fw1, g + fb1, dp2, 0, nullptr, nullptr, m, 3136, 384));
     RUN(dsspk_maxpool_bwd_relu(s, dp2, arg2, a2, da2, m, 15, 15, 64));
     RUN(dsspk_conv_bwd_weight(s, p1, da2, g + cw2, scr, m, 15, 15, 64, 64, 5, 5, 1, 2));
     RUN(dsspk_colsum(s, da2, g + cb2, F(P->colsum_scratch), (long)m * 15 * 15, 64));
@@ -253,7 +251,7 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
     auto F = [&](size_t off) { return (float*)(ws + off); };
     float *a1 = F(P->ax_a1), *p1 = F(P->ax_p1), *a2 = F(P->ax_a2), *p2 = F(P->ax_p2), *c3 = F(P->ax_c3), *a3 = F(P->ax_a3);
     uint8_t *arg1 = (uint8_t*)(ws + P->ax_arg1), *arg2 = (uint8_t*)(ws + P->ax_arg2);
-    float *z = F(P->logits), *dz = F(P->dlogits), *da3 = F(P->ax_da3), *dc3 = F(P->ax_dc3), *dp2 = F(P->ax_dp2);
+    float *da3 = F(P->ax_da3), *dc3 = F(P->ax_dc3), *dp2 = F(P->ax_dp2);
     float *da2 = F(P->ax_da2), *dp1 = F(P->ax_dp1), *da1 = F(P->ax_da1), *scr = F(P->wg_scratch), *cscr = F(P->colsum_scratch);
     const int64_t cw1 = 0, cb1 = 4800, cw2 = cb1 + 64, cb2 = cw2 + 102400, cw3 = cb2 + 64, cb3 = cw3 + 36864,
                   fw1 = cb3 + 64, fb1 = fw1 + 3136 * 384, fw2 = fb1 + 384, fb2 = fw2 + 384 * (int64_t)C;
@@ -263,19 +261,10 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
     RUN(dsspk_conv_fwd(s, p1, w + cw2, w + cb2, a2, m, 15, 15, 64, 64, 5, 5, 1, 2, 1, nullptr));
     RUN(dsspk_maxpool_fwd(s, a2, p2, arg2, m, 15, 15, 64));
     RUN(dsspk_conv_fwd(s, p2, w + cw3, w + cb3, c3, m, 7, 7, 64, 64, 3, 3, 1, 1, 1, nullptr));
-    RUN(dsspk_gemm_splitk(s, c3, 3136, 1, w + fw1, 384, 1, a3, 384, m, 384, 3136, w + fb1, 1, F(P->fc_scratch),
-                          dsspk_gemm_splitk_layers(m, 384, 3136)));
-    RUN(dsspk_gemm(s, a3, 384, 1, w + fw2, C, 1, z, C, m, C, 384, w + fb2, 0));
-    RUN(dsspk_softmax_xent(s, z, y, dz, loss, m, C));
+    RUN(dsspk_gemm(s, c3, 3136, 1, w + fw1, 384, 1, a3, 384, m, 384, 3136, w + fb1, 1));
+    if (int rc = last_layer(P, ws, s, a3, 384, y, w, g, fw2, fb2, da3, 1, loss, err)) return rc;
     // backward
-    RUN(dsspk_gemm(s, a3, 1, 384, dz, C, 1, g + fw2, C, 384, C, m, nullptr, 0));
-    RUN(dsspk_colsum(s, dz, g + fb2, nullptr, m, C));
-    RUN(dsspk_gemm(s, dz, C, 1, w + fw2, 1, C, da3, 384, m, 384, C, nullptr, 0));
-    RUN(dsspk_relu_bwd(s, da3, a3, (long)m * 384));
-    RUN(dsspk_gemm(s, c3, 1, 3136, da3, 384, 1, g + fw1, 384, 3136, 384, m, nullptr, 0));
-    RUN(dsspk_colsum(s, da3, g + fb1, nullptr, m, 384));
-    RUN(dsspk_gemm(s, da3, 384, 1, w + fw1, 1, 384, dc3, 3136, m, 3136, 384, nullptr, 0));
-    RUN(dsspk_relu_bwd(s, dc3, c3, (long)m * 3136));
+    RUN(dsspk_fc_bwd(s, c3, da3, w + fw1, g + fw1, g + fb1, dc3, 1, nullptr, nullptr, m, 3136, 384));
     RUN(dsspk_conv_bwd_weight(s, p2, dc3, g + cw3, scr, m, 7, 7, 64, 64, 3, 3, 1, 1));
     RUN(dsspk_colsum(s, dc3, g + cb3, cscr, (long)m * 7 * 7, 64));
     RUN(dsspk_conv_bwd_data(s, dc3, w + cw3, nullptr, dp2, m, 7, 7, 64, 64, 3, 3, 1, 1));
@@ -340,12 +329,8 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         cur = F(B.out);
     }
     RUN(dsspk_gap_fwd(s, cur, F(P->pooled), m, 64, 64));
-    RUN(dsspk_gemm(s, F(P->pooled), 64, 1, w + P->fc_w, C, 1, F(P->logits), C, m, C, 64, w + P->fc_b, 0));
-    RUN(dsspk_softmax_xent(s, F(P->logits), y, F(P->dlogits), loss, m, C));
+    if (int rc = last_layer(P, ws, s, F(P->pooled), 64, y, w, g, P->fc_w, P->fc_b, F(P->dpooled), 0, loss, err)) return rc;
     // ---- backward
-    RUN(dsspk_gemm(s, F(P->pooled), 1, 64, F(P->dlogits), C, 1, g + P->fc_w, C, 64, C, m, nullptr, 0));
-    RUN(dsspk_colsum(s, F(P->dlogits), g + P->fc_b, nullptr, m, C));
-    RUN(dsspk_gemm(s, F(P->dlogits), C, 1, w + P->fc_w, 1, C, F(P->dpooled), 64, m, 64, C, nullptr, 0));
     float *g0 = F(P->G[0]), *g1 = F(P->G[1]), *g2 = F(P->G[2]);     // g0: gradient w.r.t. the current block output
     RUN(dsspk_gap_bwd(s, F(P->dpooled), g0, m, 64, 64));
     // Per convolution layer the backward pass is  BN backward -> d-input convolution -> d-filter convolution.

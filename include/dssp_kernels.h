@@ -158,6 +158,25 @@ int dsspk_conv_bwd_weight_parts(void* stream, const float* x_dev, const float* d
 int dsspk_wgrad_reduce(void* stream, const float* partial_dev, float* dw_dev, int E, int chunks);
 size_t dsspk_conv_wgrad_scratch_floats(int N, int H, int W, int Cin, int Cout, int KH, int KW, int stride, int pad);
 
+/* Stride-1 convolutions of wide layers (Cin and Cout multiples of 64, k x k filters with k = 3 or 5, pad < k) with fp32
+ * arithmetic on the bf16 matrix cores: every operand is split into three bf16 terms (24 significant bits in all), six of the
+ * nine products of terms are accumulated in fp32; at least as accurate as dsspk_conv_*.  dsspk_conv_split_covers: 1 if the
+ * shape is one of these and its tiles fit (the launchers return -1 otherwise).
+ * The filter is converted once per set of weights: dsspk_conv_split_filters writes the planes of the forward and / or of the
+ * d-input pass (either may be NULL), dsspk_conv_split_filter_bytes(...) bytes each, 16-byte aligned. */
+int dsspk_conv_split_covers(int N, int H, int W, int Cin, int Cout, int k, int pad);
+size_t dsspk_conv_split_filter_bytes(int Cin, int Cout, int k);
+int dsspk_conv_split_filters(void* stream, const float* w_dev, void* planes_fwd_dev, void* planes_bwd_dev, int Cin, int Cout, int k);
+int dsspk_conv_split_fwd(void* stream, const float* x_dev, const void* planes_fwd_dev, const float* bias_dev, float* y_dev, int N,
+                         int H, int W, int Cin, int Cout, int k, int pad, int relu);
+int dsspk_conv_split_bwd_data(void* stream, const float* dy_dev, const void* planes_bwd_dev, const float* add_dev, float* dx_dev, int N,
+                              int H, int W, int Cin, int Cout, int k, int pad);
+/* Gradient w.r.t. the filter and, with_bias, w.r.t. the bias (column sums of dy), which is stored right behind it:
+ * dw_dev[k k Cin Cout (+ Cout)].  scratch_dev: dsspk_conv_split_wgrad_scratch_floats(...) floats. */
+size_t dsspk_conv_split_wgrad_scratch_floats(int N, int H, int W, int Cin, int Cout, int k, int pad);
+int dsspk_conv_split_bwd_weight(void* stream, const float* x_dev, const float* dy_dev, float* dw_dev, int with_bias, float* scratch_dev,
+                                int N, int H, int W, int Cin, int Cout, int k, int pad);
+
 /* dy[i] = a[i] > 0 ? dy[i] : 0 (in place). */
 int dsspk_relu_bwd(void* stream, float* dy_dev, const float* a_dev, long n);
 /* out[i] += in[i]. */

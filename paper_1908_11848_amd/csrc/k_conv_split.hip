@@ -1,0 +1,516 @@
+// Stride-1 convolutions of wide layers (channels multiples of 64, 3x3 or 5x5
+// filters) with fp32 arithmetic on the bf16 matrix cores (split.hpp): forward, gradient w.r.t. the input (the same kernel on
+// a transposed, reversed filter) and gradient w.r.t. the filter and bias.
+#include "jobs.hpp"
+#include "split.hpp"
+#include "../../include/dssp_kernels.h"
+
+namespace {
+
+constexpr int THREADS = 256;
+constexpr size_t LDS_MAX = 160 * 1024;
+
+// Workgroups go to the 8 XCDs round-robin; consecutive tiles (shared halo rows) go to one XCD and its L2.
+__device__ __forceinline__ int xcd_tile(int block, int n_blocks) {
+    constexpr int XCDS = 8;
+    return n_blocks % XCDS ? block : (block % XCDS) * (n_blocks / XCDS) + block / XCDS;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Filter planes in operand order: [step][16 result channels][plane][lane] of 16 bytes, step = (tap, 32 reduction channels),
+// lane (l16, q) holding the reduction channels 8 q .. 8 q + 7 of result channel l16.  A wavefront then fetches an operand
+// as one contiguous KiB.  Written once per step, read by every workgroup of the layer's convolutions.
+//   TR = false: result channel = output channel;  true (d-input): result = input channel, taps reversed
+struct Frag {
+    const float* w;
+    uint4* out;
+    int taps, IC, OC;       // of the layer
+};
+
+__device__ __forceinline__ void filter_frag(const Frag& f, bool tr, long idx) {
+    const int RC = tr ? f.OC : f.IC, RS = tr ? f.IC : f.OC;      // reduction / result channels
+    const int lane = (int)(idx & 63);
+    const long r = idx >> 6;
+    const int tiles = RS / 16, tile = (int)(r % tiles), step = (int)(r / tiles);
+    const int c32 = step % (RC / 32), tap = step / (RC / 32);
+    const int rs = 16 * tile + (lane & 15), rc = 32 * c32 + 8 * (lane >> 4);
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        v[j] = tr ? f.w[((long)(f.taps - 1 - tap) * f.IC + rs) * f.OC + rc + j] : f.w[((long)tap * f.IC + rc + j) * f.OC + rs];
+#pragma unroll
+    for (int p = 0; p < split::PLANES; ++p) {
+        uint4 u;
+        u.x = split::take(v[0], v[1]); u.y = split::take(v[2], v[3]);
+        u.z = split::take(v[4], v[5]); u.w = split::take(v[6], v[7]);
+        f.out[(r * split::PLANES + p) * 64 + lane] = u;
+    }
+}
+
+__global__ __launch_bounds__(THREADS) void filter_planes_kernel(Frag fwd, Frag bwd, long n) {
+    const long i = (long)blockIdx.x * THREADS + threadIdx.x;
+    if (i < n) {
+        if (fwd.out) filter_frag(fwd, false, i);
+    } else if (i < 2 * n) {
+        if (bwd.out) filter_frag(bwd, true, i - n);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// forward / d-input.  A workgroup owns 64 result channels of up to 16 MT pixels: R whole output rows of one image, or G whole
+// images.  The input tile with its halo goes to LDS once, already split into its three planes (every element is converted
+// once, not once per tap), and serves all taps from there; a pixel's 32 channels of one plane are a 16-byte read per lane.
+// The filter planes come straight from L2 into registers, two steps ahead.  The matrix-core tile is 16 channels (rows) x
+// 16 pixels (columns), so a lane ends up with four consecutive channels of a pixel.
+// Bound by the matrix cores: 64 -> 64 at 5x5 on 15x15, batch 128, is 2.46 M MFMAs = 20 us of them.
+struct Geom {
+    int N, H, W, OH, OW, pad;      // input / output pixel grid of this pass
+    int IC, OC;                    // reduction / result channels of this pass
+    int R, G, bands;               // output rows per tile, images per tile (G > 1: whole images), tiles per image
+};
+
+// MT pixel tiles per workgroup; wavefronts: WP over the pixels, 4 / WP over the 4 channel tiles
+template <int MT> struct Waves { static constexpr int WP = MT >= 4 ? 2 : 1, WC = 4 / WP, TP = MT / WP, TC = 4 / WC; };
+
+constexpr int ICB = 64;            // reduction channels staged at a time
+constexpr int pitch(int channels) { return channels * 2 * split::PLANES + 16; }      // bytes of a pixel in LDS: 4 words (mod 32) apart
+
+template <int MT, int KS>
+__global__ __launch_bounds__(THREADS) void conv_split_kernel(const float* __restrict__ src, const uint4* __restrict__ wf,
+                                                             const float* __restrict__ bias, const float* __restrict__ add,
+                                                             float* __restrict__ dst, Geom g, int relu) {
+    using W = Waves<MT>;
+    constexpr int PITCH = pitch(ICB), PLANE = 2 * ICB, CS = ICB / 32;      // CS: steps per tap and block of channels
+    constexpr int STEPS = KS * KS * CS, WD = MT == 2 ? 8 : 4;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, q = lane >> 4;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int n0 = tile / g.bands * g.G, r0 = tile % g.bands * g.R;
+    const int TH = g.R + KS - 1, TW = g.OW + KS - 1;
+    const int wp = wave % W::WP, wc = wave / W::WP;
+    const int ct0 = blockIdx.y * 4 + wc * W::TC;           // first 16-channel tile of this wavefront
+
+    // this lane's pixels: where their patch starts in LDS, and where they go
+    int base[W::TP];
+    long out[W::TP];
+#pragma unroll
+    for (int t = 0; t < W::TP; ++t) {
+        const int p = (wp * W::TP + t) * 16 + l16;
+        const int per = g.R * g.OW, gi = p / per, rest = p - gi * per, r = rest / g.OW, c = rest - r * g.OW;
+        const bool ok = gi < g.G && n0 + gi < g.N && r0 + r < g.OH;
+        base[t] = ok ? ((gi * TH + r) * TW + c) * PITCH + 16 * q : 16 * q;
+        out[t] = ok ? (((long)(n0 + gi) * g.OH + r0 + r) * g.OW + c) * g.OC : -1;
+    }
+    floatx4 acc[W::TC][W::TP];
+#pragma unroll
+    for (int i = 0; i < W::TC; ++i)
+#pragma unroll
+        for (int t = 0; t < W::TP; ++t) acc[i][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    const int tiles_c = g.OC / 16, steps_c = g.IC / 32;
+    const split::Buffer images = split::buffer(src + (long)n0 * g.H * g.W * g.IC, 4u * (unsigned)(min(g.G, g.N - n0) * g.H * g.W * g.IC));
+    for (int c0 = 0; c0 < g.IC; c0 += ICB) {
+        if (c0) __syncthreads();
+        // LOADS 16-byte loads in flight per thread (one at a time, their latencies add up to half the kernel)
+        constexpr int LOADS = 8;
+        const int total = g.G * TH * TW * (ICB / 4);
+        for (int i0 = tid; i0 < total; i0 += LOADS * THREADS) {
+            float4 v[LOADS];
+#pragma unroll
+            for (int e = 0; e < LOADS; ++e) {
+                const int idx = i0 + e * THREADS, px = idx / (ICB / 4), c4 = idx % (ICB / 4);
+                const int gi = px / (TH * TW), rest = px - gi * (TH * TW), ty = rest / TW, tx = rest - ty * TW;
+                const int h = r0 + ty - g.pad, w = tx - g.pad;
+                const bool in = idx < total && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;      // images past the last: beyond the buffer
+                v[e] = split::load4(images, in ? 4u * (unsigned)(((gi * g.H + h) * g.W + w) * g.IC + c0 + 4 * c4) : split::OUTSIDE);
+            }
+#pragma unroll
+            for (int e = 0; e < LOADS; ++e) {
+                const int idx = i0 + e * THREADS;
+                if (idx >= total) break;
+                uint2 pl[split::PLANES];
+                split::split4(v[e], pl);
+#pragma unroll
+                for (int p = 0; p < split::PLANES; ++p)
+                    *reinterpret_cast<uint2*>(lds + idx / (ICB / 4) * PITCH + p * PLANE + 8 * (idx % (ICB / 4))) = pl[p];
+            }
+        }
+        // Filter planes are fetched WD steps before their use (they come from L2: one step, 0.3 us, does not cover that),
+        // pixel operands one step.
+        uint4 wv[WD][W::TC][split::PLANES], pv[2][W::TP][split::PLANES];
+        auto load_w = [&](int buf, int s) {
+            s = s < STEPS ? s : STEPS - 1;
+            const uint4* p = wf + ((((long)(s / CS) * steps_c + c0 / 32 + s % CS) * tiles_c + ct0) * split::PLANES) * 64 + lane;
+#pragma unroll
+            for (int i = 0; i < W::TC; ++i)
+#pragma unroll
+                for (int k = 0; k < split::PLANES; ++k) wv[buf][i][k] = p[(i * split::PLANES + k) * 64];
+        };
+        auto load_p = [&](int buf, int s) {
+            s = s < STEPS ? s : STEPS - 1;
+            const int tap = s / CS, off = (tap / KS * TW + tap % KS) * PITCH + s % CS * 64;
+#pragma unroll
+            for (int t = 0; t < W::TP; ++t)
+#pragma unroll
+                for (int k = 0; k < split::PLANES; ++k) pv[buf][t][k] = *reinterpret_cast<const uint4*>(lds + base[t] + off + k * PLANE);
+        };
+#pragma unroll
+        for (int u = 0; u < WD; ++u) load_w(u, u);
+        __syncthreads();
+        load_p(0, 0);
+        for (int s = 0; s < STEPS; s += WD) {
+#pragma unroll
+            for (int u = 0; u < WD; ++u) {
+                if (s + u >= STEPS) break;
+                load_p((u + 1) & 1, s + u + 1);
+                __builtin_amdgcn_sched_barrier(0);      // or the compiler moves the reads down to their use, behind the products
+                split::product(wv[u], pv[u & 1], acc);
+                __builtin_amdgcn_sched_barrier(0);
+                load_w(u, s + u + WD);
+            }
+        }
+    }
+
+#pragma unroll
+    for (int i = 0; i < W::TC; ++i) {
+        const int co = 16 * (ct0 + i) + 4 * q;
+        const float4 b = bias ? *reinterpret_cast<const float4*>(bias + co) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int t = 0; t < W::TP; ++t) {
+            if (out[t] < 0) continue;
+            float4 v = make_float4(acc[i][t][0] + b.x, acc[i][t][1] + b.y, acc[i][t][2] + b.z, acc[i][t][3] + b.w);
+            if (add) {
+                const float4 a = *reinterpret_cast<const float4*>(add + out[t] + co);
+                v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+            }
+            if (relu) { v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f); v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f); }
+            *reinterpret_cast<float4*>(dst + out[t] + co) = v;
+        }
+    }
+}
+
+// Tile of one launch: the number of 16-pixel tiles per workgroup, its rows and images.
+struct Tiling { int mt, R, G, bands, blocks; size_t lds; };
+
+size_t tile_bytes(int G, int R, int OW, int ks) { return (size_t)G * (R + ks - 1) * (OW + ks - 1) * pitch(ICB); }
+
+bool tiling_for(Tiling& t, int mt, int N, int OH, int OW, int ks) {
+    const int px = 16 * mt;
+    if (OW > px) return false;
+    t.mt = mt;
+    t.R = px / OW < OH ? px / OW : OH;
+    t.bands = ceil_div(OH, t.R);
+    t.R = ceil_div(OH, t.bands);                          // even bands
+    t.G = t.bands == 1 ? px / (OH * OW) : 1;
+    if (t.G > N) t.G = N;
+    while (t.G > 1 && tile_bytes(t.G, t.R, OW, ks) > LDS_MAX) --t.G;
+    t.lds = tile_bytes(t.G, t.R, OW, ks);
+    t.blocks = ceil_div(N, t.G) * t.bands;
+    return t.lds <= LDS_MAX;
+}
+
+// The largest tile (fewest halo rows and filter reads per pixel) that still gives most compute units a workgroup.
+bool choose_tiling(Tiling& t, int N, int OH, int OW, int OC, int ks) {
+    bool have = false;
+    for (int mt = 8; mt >= 2; mt /= 2) {
+        Tiling c;
+        if (!tiling_for(c, mt, N, OH, OW, ks)) continue;
+        if (!have || (long)t.blocks * (OC / 64) < 192) t = c;
+        have = true;
+    }
+    return have;
+}
+
+template <int MT, int KS>
+int launch_tile(hipStream_t s, const float* src, const uint4* wf, const float* bias, const float* add, float* dst, const Geom& g, int relu,
+                const Tiling& t) {
+    auto kern = conv_split_kernel<MT, KS>;
+    static bool attr_set = false;       // raise the dynamic-LDS limit once per instantiation
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX) != hipSuccess) return -1;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(t.blocks, g.OC / 64), dim3(THREADS), t.lds, s, src, wf, bias, add, dst, g, relu);
+    return DSSPK_LAUNCH_RC();
+}
+
+int launch_conv(hipStream_t s, const float* src, const uint4* wf, const float* bias, const float* add, float* dst, Geom g, int ks, int relu) {
+    Tiling t;
+    if (!choose_tiling(t, g.N, g.OH, g.OW, g.OC, ks)) return -1;
+    g.R = t.R; g.G = t.G; g.bands = t.bands;
+#define GO(MT) return ks == 5 ? launch_tile<MT, 5>(s, src, wf, bias, add, dst, g, relu, t) : launch_tile<MT, 3>(s, src, wf, bias, add, dst, g, relu, t)
+    if (t.mt == 8) GO(8);
+    if (t.mt == 4) GO(4);
+    GO(2);
+#undef GO
+}
+
+// ---------------------------------------------------------------------------------------------
+// d-filter (and bias gradient), stage 1 of 2.  Workgroup (chunk, filter row kh and 32 input channels, 64 output channels)
+// walks its chunk's pixel tiles (R whole output rows of one image, at most 64 pixels): the x rows that filter row kh meets
+// and the dy rows go to LDS as planes, and dw[kh][kw][ci][co] += x[pixel + kw][ci] dy[pixel][co] is accumulated for all KS
+// taps of the row with the pixels as reduction index, 32 to an MFMA.  Both operands need a lane's pixels side by side while
+// LDS has the channels side by side: the transposing LDS reads turn them.  The next tile's loads are in flight while the
+// matrix cores work.  Wavefront w: input channels 16 (w mod 2) .., output channels 32 (w / 2) ..
+// Output: partial[chunk][KS KS IC OC (+ OC bias sums, added up by the workgroups of filter row 0 and the first channels)].
+constexpr int WG_PX = 64, WG_XPX = 96;
+constexpr int XPITCH = 32 * 6 + 32, DPITCH = 64 * 6 + 32;      // 24 and 8 words (mod 32): four rows cover all banks once
+
+template <int KS>
+__global__ __launch_bounds__(THREADS) void wgrad_split_kernel(const float* __restrict__ x, const float* __restrict__ dy,
+                                                              float* __restrict__ partial, Geom g, int items_per_chunk, int with_bias) {
+    constexpr int NX = WG_XPX * 8 / THREADS, ND = WG_PX * 16 / THREADS;      // 16-byte loads per thread and tile
+    constexpr int XBYTES = WG_XPX * XPITCH, BUF = XBYTES + WG_PX * DPITCH;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, q = lane >> 4;
+    const int kh = blockIdx.y % KS, ci0 = blockIdx.y / KS * 32, co0 = blockIdx.z * 64;
+    const int TW = g.OW + KS - 1, P = g.R * g.OW;
+    const int items = g.N * g.bands, i0 = blockIdx.x * items_per_chunk, i1 = min(items, i0 + items_per_chunk);
+    const bool bias_role = with_bias && blockIdx.y == 0;
+
+    // transposing reads: this lane names row 8 q + l16 / 4 (and the one four further) of each run of 32 pixels
+    int xa[WG_PX / 32][2], da[WG_PX / 32][2];
+#pragma unroll
+    for (int k = 0; k < WG_PX / 32; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int p = 32 * k + 8 * q + 4 * h + (l16 >> 2);
+            const int r = p / g.OW, c = p - r * g.OW;
+            xa[k][h] = (p < P ? (r * TW + c) * XPITCH : 0) + 8 * (l16 & 3) + 32 * (wave & 1);      // beyond P dy is zero
+            da[k][h] = p * DPITCH + 8 * (l16 & 3) + 64 * (wave >> 1);
+        }
+    floatx4 acc[KS][2][1];
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[k][i][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float4 sb = make_float4(0.f, 0.f, 0.f, 0.f);
+
+    // The thread's staged elements: NX of x, then ND of dy.  One tile is in LDS and worked on, the next one is in registers
+    // and converted and written to the other LDS buffer element by element between the products (a vector instruction beside
+    // an MFMA costs nothing), and the registers it frees take the loads of the tile after that.
+    constexpr int NE = NX + ND;
+    float4 rv[NE];
+    unsigned off[NE];              // byte offset from the tile's first row; rows above or below the image fall outside its buffer
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        const bool is_x = e < NX;
+        const int idx = tid + (is_x ? e : e - NX) * THREADS, px = is_x ? idx >> 3 : idx >> 4, c4 = is_x ? idx & 7 : idx & 15;
+        const int width = is_x ? TW : g.OW, r = px / width, c = px - r * width - (is_x ? g.pad : 0);
+        const bool in = is_x ? r < g.R && c >= 0 && c < g.W : px < P;
+        off[e] = !in ? split::OUTSIDE : is_x ? 4u * (unsigned)(((r + kh - g.pad) * g.W + c) * g.IC + ci0 + 4 * c4)
+                                             : 4u * (unsigned)((r * g.OW + c) * g.OC + co0 + 4 * c4);
+    }
+    int fn = i0 / g.bands, fr = i0 % g.bands * g.R;            // tile of the next fetch: image, first row
+    split::Buffer xb, db;
+    auto image = [&]() {
+        xb = split::buffer(x + (long)fn * g.H * g.W * g.IC, 4u * (unsigned)(g.H * g.W * g.IC));
+        db = split::buffer(dy + (long)fn * g.OH * g.OW * g.OC, 4u * (unsigned)(g.OH * g.OW * g.OC));
+    };
+    auto fetch = [&](int e) {
+        rv[e] = e < NX ? split::load4(xb, off[e] + 4u * (unsigned)(fr * g.W * g.IC)) : split::load4(db, off[e] + 4u * (unsigned)(fr * g.OW * g.OC));
+    };
+    int fetched = 1;                                           // tiles fetched so far
+    auto advance = [&]() {                                     // past the chunk's end the last tile is fetched again (never used)
+        if (i0 + fetched < i1) {
+            fr += g.R;
+            if (fr >= g.bands * g.R) { fr = 0; ++fn; }
+        }
+        image();
+        ++fetched;
+    };
+    auto stage = [&](int e, char* buf, float count) {          // count: 1, or 0 if the tile is not to enter the bias sums
+        const float4 v = rv[e];
+        if (e >= NX) { sb.x = fmaf(v.x, count, sb.x); sb.y = fmaf(v.y, count, sb.y); sb.z = fmaf(v.z, count, sb.z); sb.w = fmaf(v.w, count, sb.w); }
+        uint2 pl[split::PLANES];
+        split::split4(v, pl);
+        const int idx = tid + (e < NX ? e : e - NX) * THREADS;
+        char* to = e < NX ? buf + (idx >> 3) * XPITCH + 8 * (idx & 7) : buf + XBYTES + (idx >> 4) * DPITCH + 8 * (idx & 15);
+#pragma unroll
+        for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(to + p * (e < NX ? 64 : 128)) = pl[p];
+    };
+    uint4 dv[2][2][split::PLANES], xv[2][1][split::PLANES];
+    auto load_d = [&](int b, int k, const char* buf) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int p = 0; p < split::PLANES; ++p) {
+                const uint2 lo = split::read_tr(buf + XBYTES + da[k][0] + 32 * i + 128 * p), hi = split::read_tr(buf + XBYTES + da[k][1] + 32 * i + 128 * p);
+                dv[b][i][p] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
+    };
+    auto load_x = [&](int b, int k, int kw, const char* buf) {
+#pragma unroll
+        for (int p = 0; p < split::PLANES; ++p) {
+            const uint2 lo = split::read_tr(buf + xa[k][0] + kw * XPITCH + 64 * p), hi = split::read_tr(buf + xa[k][1] + kw * XPITCH + 64 * p);
+            xv[b][0][p] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        }
+    };
+    constexpr int RUNS = WG_PX / 32, STEPS = RUNS * KS;
+    if (i0 < i1) {
+        image();
+#pragma unroll
+        for (int e = 0; e < NE; ++e) fetch(e);
+        advance();
+#pragma unroll
+        for (int e = 0; e < NE; ++e) stage(e, lds, 1.f);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) fetch(e);
+        advance();
+    }
+    for (int item = i0; item < i1; ++item) {
+        const char* cur = lds + ((item - i0) & 1) * BUF;
+        char* nxt = lds + ((item - i0 + 1) & 1) * BUF;
+        const float count = item + 1 < i1 ? 1.f : 0.f;
+        __syncthreads();                                       // this tile is complete, the other buffer is consumed
+        load_d(0, 0, cur);
+        load_x(0, 0, 0, cur);
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {                      // (run, tap) steps, operands read one step ahead
+            const int k = t / KS, kw = t % KS;
+            if (t + 1 < STEPS) load_x((t + 1) & 1, (t + 1) / KS, (t + 1) % KS, cur);
+            if (kw == KS - 2 && k + 1 < RUNS) load_d((k + 1) & 1, k + 1, cur);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = t * NE / STEPS; e < (t + 1) * NE / STEPS; ++e)
+                stage(e, nxt, count);
+            split::product(dv[k & 1], xv[t & 1], acc[kw]);
+#pragma unroll
+            for (int m = 0; m < 12; ++m) {                     // one MFMA, a few vector instructions, ...
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = t * NE / STEPS; e < (t + 1) * NE / STEPS; ++e) fetch(e);
+        }
+        advance();
+    }
+    const long E = (long)KS * KS * g.IC * g.OC;
+    float* outp = partial + blockIdx.x * (E + (with_bias ? g.OC : 0));
+#pragma unroll
+    for (int kw = 0; kw < KS; ++kw)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            *reinterpret_cast<floatx4*>(outp + ((long)(kh * KS + kw) * g.IC + ci0 + 16 * (wave & 1) + l16) * g.OC + co0 + 32 * (wave >> 1) + 16 * i + 4 * q) =
+                acc[kw][i][0];
+    if (bias_role) {                                           // lanes of one channel group, in order
+        __syncthreads();
+        float4* red = reinterpret_cast<float4*>(lds);
+        red[tid] = sb;
+        __syncthreads();
+        if (tid < 16) {
+            float4 s = red[tid];
+            for (int j = 1; j < THREADS / 16; ++j) { const float4 v = red[tid + 16 * j]; s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w; }
+            *reinterpret_cast<float4*>(outp + E + co0 + 4 * tid) = s;
+        }
+    }
+}
+
+template <int KS>
+int launch_wgrad(hipStream_t s, dim3 grid, const float* x, const float* dy, float* partial, const Geom& g, int items_per_chunk, int with_bias) {
+    constexpr int bytes = 2 * (WG_XPX * XPITCH + WG_PX * DPITCH);
+    auto kern = wgrad_split_kernel<KS>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return -1;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(THREADS), bytes, s, x, dy, partial, g, items_per_chunk, with_bias);
+    return DSSPK_LAUNCH_RC();
+}
+
+bool wgrad_rows(Geom& g, int ks) {
+    if (g.OW > WG_PX || g.OW + ks - 1 > WG_XPX) return false;
+    int R = WG_PX / g.OW;
+    if (R > WG_XPX / (g.OW + ks - 1)) R = WG_XPX / (g.OW + ks - 1);
+    if (R > g.OH) R = g.OH;
+    g.bands = ceil_div(g.OH, R);
+    g.R = ceil_div(g.OH, g.bands);
+    g.G = 1;
+    return true;
+}
+
+// Chunks: at most one workgroup per compute unit (its LDS allows no second one, so one more workgroup than that doubles the
+// kernel's time); the partial results (chunks times the filter) stay small beside the activations.
+int wgrad_items(const Geom& g, int ks) {
+    const int roles = ks * (g.IC / 32) * (g.OC / 64);
+    int chunks = 256 / roles;
+    if (chunks < 1) chunks = 1;
+    const int items = g.N * g.bands;
+    if (chunks > items) chunks = items;
+    return ceil_div(items, chunks);
+}
+
+bool shape_ok(int H, int W, int Cin, int Cout, int k, int pad) {
+    return (k == 3 || k == 5) && Cin % 64 == 0 && Cout % 64 == 0 && pad >= 0 && pad < k && H + 2 * pad >= k && W + 2 * pad >= k;
+}
+
+Geom forward_geom(int N, int H, int W, int Cin, int Cout, int k, int pad) {
+    Geom g = {};
+    g.N = N; g.H = H; g.W = W; g.OH = H + 2 * pad - k + 1; g.OW = W + 2 * pad - k + 1; g.pad = pad; g.IC = Cin; g.OC = Cout;
+    return g;
+}
+
+Geom backward_geom(int N, int H, int W, int Cin, int Cout, int k, int pad) {
+    const Geom f = forward_geom(N, H, W, Cin, Cout, k, pad);
+    Geom g = {};
+    g.N = N; g.H = f.OH; g.W = f.OW; g.OH = H; g.OW = W; g.pad = k - 1 - pad; g.IC = Cout; g.OC = Cin;
+    return g;
+}
+
+}  // namespace
+
+extern "C" int dsspk_conv_split_covers(int N, int H, int W, int Cin, int Cout, int k, int pad) {
+    if (N < 1 || !shape_ok(H, W, Cin, Cout, k, pad)) return 0;
+    Geom f = forward_geom(N, H, W, Cin, Cout, k, pad), b = backward_geom(N, H, W, Cin, Cout, k, pad);
+    // byte offsets within a group of images are 32-bit and below 2^31 (a group of several has at most 128 pixels each way)
+    if ((long)H * W * Cin >= 1L << 29 || (long)f.OH * f.OW * Cout >= 1L << 29) return 0;
+    if ((long)N * H * W >= 1L << 31 || (long)N * f.OH * f.OW >= 1L << 31) return 0;
+    Tiling t;
+    return choose_tiling(t, N, f.OH, f.OW, f.OC, k) && choose_tiling(t, N, b.OH, b.OW, b.OC, k) && wgrad_rows(f, k);
+}
+
+extern "C" size_t dsspk_conv_split_filter_bytes(int Cin, int Cout, int k) { return (size_t)k * k * Cin * Cout * 2 * split::PLANES; }
+
+extern "C" int dsspk_conv_split_filters(void* stream, const float* w, void* planes_fwd, void* planes_bwd, int Cin, int Cout, int k) {
+    if (!w || (!planes_fwd && !planes_bwd) || (k != 3 && k != 5) || Cin < 64 || Cin % 64 || Cout < 64 || Cout % 64) return -1;
+    const Frag f{w, (uint4*)planes_fwd, k * k, Cin, Cout}, b{w, (uint4*)planes_bwd, k * k, Cin, Cout};
+    const long n = (long)k * k * Cin * Cout / 8;
+    hipLaunchKernelGGL(filter_planes_kernel, dim3(ceil_div(2 * n, THREADS)), dim3(THREADS), 0, (hipStream_t)stream, f, b, n);
+    return DSSPK_LAUNCH_RC();
+}
+
+extern "C" int dsspk_conv_split_fwd(void* stream, const float* x, const void* planes_fwd, const float* bias, float* y, int N, int H, int W,
+                                    int Cin, int Cout, int k, int pad, int relu) {
+    if (!x || !planes_fwd || !y || !dsspk_conv_split_covers(N, H, W, Cin, Cout, k, pad)) return -1;
+    return launch_conv((hipStream_t)stream, x, (const uint4*)planes_fwd, bias, nullptr, y, forward_geom(N, H, W, Cin, Cout, k, pad), k, relu);
+}
+
+extern "C" int dsspk_conv_split_bwd_data(void* stream, const float* dy, const void* planes_bwd, const float* add, float* dx, int N, int H,
+                                         int W, int Cin, int Cout, int k, int pad) {
+    if (!dy || !planes_bwd || !dx || !dsspk_conv_split_covers(N, H, W, Cin, Cout, k, pad)) return -1;
+    return launch_conv((hipStream_t)stream, dy, (const uint4*)planes_bwd, nullptr, add, dx, backward_geom(N, H, W, Cin, Cout, k, pad), k, 0);
+}
+
+extern "C" size_t dsspk_conv_split_wgrad_scratch_floats(int N, int H, int W, int Cin, int Cout, int k, int pad) {
+    if (!dsspk_conv_split_covers(N, H, W, Cin, Cout, k, pad)) return 0;
+    Geom g = forward_geom(N, H, W, Cin, Cout, k, pad);
+    wgrad_rows(g, k);
+    return (size_t)ceil_div(g.N * g.bands, wgrad_items(g, k)) * ((size_t)k * k * Cin * Cout + Cout);
+}
+
+extern "C" int dsspk_conv_split_bwd_weight(void* stream, const float* x, const float* dy, float* dw, int with_bias, float* scratch, int N,
+                                           int H, int W, int Cin, int Cout, int k, int pad) {
+    if (!x || !dy || !dw || !scratch || !dsspk_conv_split_covers(N, H, W, Cin, Cout, k, pad)) return -1;
+    Geom g = forward_geom(N, H, W, Cin, Cout, k, pad);
+    wgrad_rows(g, k);
+    const int per = wgrad_items(g, k), chunks = ceil_div(g.N * g.bands, per);
+    const dim3 grid(chunks, k * (Cin / 32), Cout / 64);
+    hipStream_t s = (hipStream_t)stream;
+    const int rc1 = k == 5 ? launch_wgrad<5>(s, grid, x, dy, scratch, g, per, with_bias) : launch_wgrad<3>(s, grid, x, dy, scratch, g, per, with_bias);
+    if (rc1) return rc1;
+    return dsspk_wgrad_reduce(stream, scratch, dw, k * k * Cin * Cout + (with_bias ? Cout : 0), chunks);
+}

@@ -50,6 +50,7 @@ struct Plan {
     size_t ax_a1 = 0, ax_p1 = 0, ax_arg1 = 0, ax_a2 = 0, ax_p2 = 0, ax_arg2 = 0, ax_a3 = 0, ax_a4 = 0;
     size_t ax_da4 = 0, ax_da3 = 0, ax_dp2 = 0, ax_da2 = 0, ax_dp1 = 0, ax_da1 = 0;
     size_t ax_c3 = 0, ax_dc3 = 0;     // three-convolution variant: conv3 output (post-ReLU) and its gradient
+    struct WideConv { size_t fwd = 0, bwd = 0; } wide2, wide3;      // filter planes of the convolutions behind the first one
     // ResNet
     std::vector<ResBlock> blocks;
     int64_t stem_w = 0, stem_g = 0, stem_b = 0, fc_w = 0, fc_b = 0;
@@ -83,6 +84,13 @@ struct Plan {
             const size_t f = dsspk_conv_wgrad_scratch_floats(N, H, H, Cin, Cout, k, k, s, p);
             if (f > wg) wg = f;
         };
+        // wide stride-1 layer (dsspk_conv_split_*): room for its filter planes and the partial sums of its d-filter pass
+        auto wide_conv = [&](WideConv& c, int H, int k, int p) {
+            const size_t f = dsspk_conv_split_wgrad_scratch_floats(m, H, H, 64, 64, k, p);
+            if (f > wg) wg = f;
+            c.fwd = a.take(dsspk_conv_split_filter_bytes(64, 64, k));
+            c.bwd = a.take(dsspk_conv_split_filter_bytes(64, 64, k));
+        };
         auto bn_need = [&](long M, int C) { const size_t f = dsspk_bn_scratch_floats(M, C); if (f > bn) bn = f; };
         if (id == DSSP_MODEL_MLP) {
             fc_seg(3072, 256);
@@ -103,7 +111,7 @@ struct Plan {
             ax_da4 = a.floats((size_t)m * 192); ax_da3 = a.floats((size_t)m * 384); ax_dp2 = a.floats(s7);
             ax_da2 = a.floats(s15); ax_dp1 = a.floats(s15); ax_da1 = a.floats(s32);
             wg_need(m, 32, 3, 64, 5, 1, 2);
-            wg_need(m, 15, 64, 64, 5, 1, 2);
+            wide_conv(wide2, 15, 5, 2);
             tens.push_back({0, ax_a1, (int64_t)s32}); tens.push_back({0, ax_a2, (int64_t)s15});
             tens.push_back({0, ax_a3, (int64_t)m * 384}); tens.push_back({0, ax_a4, (int64_t)m * 192});
             tens.push_back({1, ax_arg1, (int64_t)s15}); tens.push_back({1, ax_arg2, (int64_t)s7});
@@ -120,8 +128,8 @@ struct Plan {
             ax_da3 = a.floats((size_t)m * 384); ax_dc3 = a.floats(s7c); ax_dp2 = a.floats(s7);
             ax_da2 = a.floats(s15); ax_dp1 = a.floats(s15); ax_da1 = a.floats(s32);
             wg_need(m, 32, 3, 64, 5, 1, 2);
-            wg_need(m, 15, 64, 64, 5, 1, 2);
-            wg_need(m, 7, 64, 64, 3, 1, 1);
+            wide_conv(wide2, 15, 5, 2);
+            wide_conv(wide3, 7, 3, 1);
             tens.push_back({0, ax_a1, (int64_t)s32}); tens.push_back({0, ax_a2, (int64_t)s15});
             tens.push_back({0, ax_c3, (int64_t)s7c}); tens.push_back({0, ax_a3, (int64_t)m * 384});
             tens.push_back({1, ax_arg1, (int64_t)s15}); tens.push_back({1, ax_arg2, (int64_t)s7});
@@ -226,7 +234,8 @@ int step_alexnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, c
     // forward
     RUN(dsspk_conv_fwd(s, x, w + cw1, w + cb1, a1, m, 32, 32, 3, 64, 5, 5, 1, 2, 1, nullptr));
     RUN(dsspk_maxpool_fwd(s, a1, p1, arg1, m, 32, 32, 64));
-    RUN(dsspk_conv_fwd(s, p1, w + cw2, w + cb2, a2, m, 15, 15, 64, 64, 5, 5, 1, 2, 1, nullptr));
+    RUN(dsspk_conv_split_filters(s, w + cw2, ws + P->wide2.fwd, ws + P->wide2.bwd, 64, 64, 5));
+    RUN(dsspk_conv_split_fwd(s, p1, ws + P->wide2.fwd, w + cb2, a2, m, 15, 15, 64, 64, 5, 2, 1));
     RUN(dsspk_maxpool_fwd(s, a2, p2, arg2, m, 15, 15, 64));
     RUN(dsspk_gemm(s, p2, 3136, 1, w + fw1, 384, 1, a3, 384, m, 384, 3136, w + fb1, 1));
     RUN(dsspk_gemm(s, a3, 384, 1, w + fw2, 192, 1, a4, 192, m, 192, 384, w + fb2, 1));
@@ -235,9 +244,8 @@ int step_alexnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, c
     RUN(dsspk_fc_bwd(s, a3, da4, w + fw2, g + fw2, g + fb2, da3, 1, nullptr, nullptr, m, 384, 192));
     RUN(dsspk_fc_bwd(s, p2, da3, w + fw1, g + fw1, g + fb1, dp2, 0, nullptr, nullptr, m, 3136, 384));
     RUN(dsspk_maxpool_bwd_relu(s, dp2, arg2, a2, da2, m, 15, 15, 64));
-    RUN(dsspk_conv_bwd_weight(s, p1, da2, g + cw2, scr, m, 15, 15, 64, 64, 5, 5, 1, 2));
-    RUN(dsspk_colsum(s, da2, g + cb2, F(P->colsum_scratch), (long)m * 15 * 15, 64));
-    RUN(dsspk_conv_bwd_data(s, da2, w + cw2, nullptr, dp1, m, 15, 15, 64, 64, 5, 5, 1, 2));
+    RUN(dsspk_conv_split_bwd_weight(s, p1, da2, g + cw2, 1, scr, m, 15, 15, 64, 64, 5, 2));      // and the biases behind the filter
+    RUN(dsspk_conv_split_bwd_data(s, da2, ws + P->wide2.bwd, nullptr, dp1, m, 15, 15, 64, 64, 5, 2));
     RUN(dsspk_maxpool_bwd_relu(s, dp1, arg1, a1, da1, m, 32, 32, 64));
     RUN(dsspk_conv_bwd_weight(s, x, da1, g + cw1, scr, m, 32, 32, 3, 64, 5, 5, 1, 2));
     RUN(dsspk_colsum(s, da1, g + cb1, F(P->colsum_scratch), (long)m * 32 * 32, 64));
@@ -258,20 +266,20 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
     // forward
     RUN(dsspk_conv_fwd(s, x, w + cw1, w + cb1, a1, m, 32, 32, 3, 64, 5, 5, 1, 2, 1, nullptr));
     RUN(dsspk_maxpool_fwd(s, a1, p1, arg1, m, 32, 32, 64));
-    RUN(dsspk_conv_fwd(s, p1, w + cw2, w + cb2, a2, m, 15, 15, 64, 64, 5, 5, 1, 2, 1, nullptr));
+    RUN(dsspk_conv_split_filters(s, w + cw2, ws + P->wide2.fwd, ws + P->wide2.bwd, 64, 64, 5));
+    RUN(dsspk_conv_split_fwd(s, p1, ws + P->wide2.fwd, w + cb2, a2, m, 15, 15, 64, 64, 5, 2, 1));
     RUN(dsspk_maxpool_fwd(s, a2, p2, arg2, m, 15, 15, 64));
-    RUN(dsspk_conv_fwd(s, p2, w + cw3, w + cb3, c3, m, 7, 7, 64, 64, 3, 3, 1, 1, 1, nullptr));
+    RUN(dsspk_conv_split_filters(s, w + cw3, ws + P->wide3.fwd, ws + P->wide3.bwd, 64, 64, 3));
+    RUN(dsspk_conv_split_fwd(s, p2, ws + P->wide3.fwd, w + cb3, c3, m, 7, 7, 64, 64, 3, 1, 1));
     RUN(dsspk_gemm(s, c3, 3136, 1, w + fw1, 384, 1, a3, 384, m, 384, 3136, w + fb1, 1));
     if (int rc = last_layer(P, ws, s, a3, 384, y, w, g, fw2, fb2, da3, 1, loss, err)) return rc;
     // backward
     RUN(dsspk_fc_bwd(s, c3, da3, w + fw1, g + fw1, g + fb1, dc3, 1, nullptr, nullptr, m, 3136, 384));
-    RUN(dsspk_conv_bwd_weight(s, p2, dc3, g + cw3, scr, m, 7, 7, 64, 64, 3, 3, 1, 1));
-    RUN(dsspk_colsum(s, dc3, g + cb3, cscr, (long)m * 7 * 7, 64));
-    RUN(dsspk_conv_bwd_data(s, dc3, w + cw3, nullptr, dp2, m, 7, 7, 64, 64, 3, 3, 1, 1));
+    RUN(dsspk_conv_split_bwd_weight(s, p2, dc3, g + cw3, 1, scr, m, 7, 7, 64, 64, 3, 1));
+    RUN(dsspk_conv_split_bwd_data(s, dc3, ws + P->wide3.bwd, nullptr, dp2, m, 7, 7, 64, 64, 3, 1));
     RUN(dsspk_maxpool_bwd_relu(s, dp2, arg2, a2, da2, m, 15, 15, 64));
-    RUN(dsspk_conv_bwd_weight(s, p1, da2, g + cw2, scr, m, 15, 15, 64, 64, 5, 5, 1, 2));
-    RUN(dsspk_colsum(s, da2, g + cb2, cscr, (long)m * 15 * 15, 64));
-    RUN(dsspk_conv_bwd_data(s, da2, w + cw2, nullptr, dp1, m, 15, 15, 64, 64, 5, 5, 1, 2));
+    RUN(dsspk_conv_split_bwd_weight(s, p1, da2, g + cw2, 1, scr, m, 15, 15, 64, 64, 5, 2));      // and the biases behind the filter
+    RUN(dsspk_conv_split_bwd_data(s, da2, ws + P->wide2.bwd, nullptr, dp1, m, 15, 15, 64, 64, 5, 2));
     RUN(dsspk_maxpool_bwd_relu(s, dp1, arg1, a1, da1, m, 32, 32, 64));
     RUN(dsspk_conv_bwd_weight(s, x, da1, g + cw1, scr, m, 32, 32, 3, 64, 5, 5, 1, 2));
     RUN(dsspk_colsum(s, da1, g + cb1, cscr, (long)m * 32 * 32, 64));
@@ -279,7 +287,7 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
 }
 
 int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, const float* w, float* g, float* loss, std::string& err) {
-    const int m = P->m, C = P->n_classes;
+    const int m = P->m;
     const float eps = 1e-5f;
     auto F = [&](size_t off) { return (float*)(ws + off); };
     float *scr = F(P->wg_scratch), *bscr = F(P->bn_scratch);

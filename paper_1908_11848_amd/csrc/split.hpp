@@ -1,0 +1,85 @@
+// fp32 products on the bf16 matrix cores (internal).
+//
+// A float is split into three bf16 numbers, x = x0 + x1 + x2: x0 is x rounded to bf16, x1 the rounded remainder, x2 the
+// remainder of that.  Each step leaves at most half a unit of the 8-bit significand, so |x1| <= 2^-8 |x|, |x2| <= 2^-16 |x|
+// and three of them hold all 24 bits of x.  A product of two such numbers is the sum of nine bf16 products, each exact in
+// the fp32 accumulator's arithmetic; the six with i + j <= 2 are taken, the three dropped ones add up to less than
+// 2^-23 of the product and, their signs being random, to about 2^-27 of it on average: less than the rounding of one fp32
+// multiplication.  (The decomposition and the six-product form are the known "three bf16 terms" emulation of single
+// precision.)
+//
+// Why: v_mfma_f32_16x16x4_f32 keeps the vector ALU of its SIMD idle, v_mfma_f32_16x16x32_bf16 does not, and six of the latter
+// do the work of eight of the former.  Measured on this chip, per SIMD: 14.5 ns against 8.3 ns an instruction (116 against
+// 50 ns for a 16x16x32 product), a vector instruction adds 3 ns to the first and nothing (up to two per MFMA) to the second.
+// Accuracy, against float64 on random data: relative error 1.6e-7 at K = 160 (fp32 MFMA 2.4e-7), 5.5e-7 at K = 1600
+// (6.8e-7); with all nine products the same to two digits.
+//
+// Range: as fp32 down to about 1e-33 (below that x2, then x1, leave bf16's subnormal range and the product keeps fewer
+// bits); an infinite value or one above 3.39e38 yields NaN.
+#pragma once
+#include "common.hpp"
+
+namespace split {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+constexpr int PLANES = 3;
+
+// two floats -> packed bf16 (round to nearest even), and what is left of them
+__device__ __forceinline__ unsigned take(float& a, float& b) {
+    const bf16x2 h = __builtin_convertvector(floatx2{a, b}, bf16x2);
+    const unsigned u = __builtin_bit_cast(unsigned, h);
+    a -= __uint_as_float(u << 16);
+    b -= __uint_as_float(u & 0xffff0000u);
+    return u;
+}
+
+// four consecutive values -> their three planes, 8 bytes each
+__device__ __forceinline__ void split4(float4 v, uint2 (&p)[PLANES]) {
+#pragma unroll
+    for (int i = 0; i < PLANES; ++i) p[i] = make_uint2(take(v.x, v.y), take(v.z, v.w));
+}
+
+// acc[.] += a . b over 32 reduction indices; a[plane], b[plane]: a lane's 8 values (k = 8 (lane / 16) ..)
+__device__ __forceinline__ floatx4 mfma(const uint4& a, const uint4& b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// The six products for TA x TB tiles, small ones first, each over all tiles before the next (independent accumulators
+// follow each other).  acc[i][j] is 16x16: rows from a, columns from b.
+template <int TA, int TB>
+__device__ __forceinline__ void product(const uint4 (&a)[TA][PLANES], const uint4 (&b)[TB][PLANES], floatx4 (&acc)[TA][TB]) {
+    constexpr int PA[6] = {0, 2, 1, 0, 1, 0}, PB[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+    for (int p = 0; p < 6; ++p)
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int j = 0; j < TB; ++j) acc[i][j] = mfma(a[i][PA[p]], b[j][PB[p]], acc[i][j]);
+}
+
+// Transposing LDS read: the 16 lanes of a quarter wavefront name four rows of 16 two-byte elements (lane j: row j / 4,
+// elements 4 (j mod 4) ..), lane j receives element j of each row.  Two of them give a lane eight consecutive reduction
+// indices of its row or column out of a tile that is stored with the reduction index outermost.
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint2 read_tr(const char* lds) {
+    typedef __attribute__((address_space(3))) shortx4 lds_t;
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t*)lds));
+}
+
+// Buffer loads check their offset against the buffer's size and return zero beyond it: zero padding without a branch and
+// without a select.  Offsets are unsigned bytes below 2^32; OUTSIDE lies beyond any buffer of less than 2^31 bytes, also after
+// another such offset is added to it.
+constexpr unsigned OUTSIDE = 0x80000000u;
+typedef __amdgpu_buffer_rsrc_t Buffer;
+__device__ __forceinline__ Buffer buffer(const float* p, unsigned bytes) {
+    constexpr int RAW_DWORDS = 0x00027000;          // untyped 32-bit data, no swizzle
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)bytes, RAW_DWORDS);
+}
+__device__ __forceinline__ float4 load4(Buffer b, unsigned offset) {
+    return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)offset, 0, 0));
+}
+
+}  // namespace split

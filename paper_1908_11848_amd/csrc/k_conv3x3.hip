@@ -10,18 +10,17 @@
 // while the halo tile is still in flight).  LDS therefore holds the halo tile only (about
 // 27 KB in every stage), which lets workgroups of several kernels share a compute unit.
 //
-// The arithmetic is Winograd's minimal filtering F(2x2, 3x3) (Lavin & Gray, "Fast Algorithms for
-// Convolutional Neural Networks"): per 2x2 output tile and channel pair 16 multiplications instead of 36,
-// Y = A^T [ (G g G^T) .* (B^T d B) ] A with the element-wise products summed over the input channels - which
-// is a matrix product per position of the transformed 4x4 patch, M_xi[tile][co] = sum_k V_xi[tile][k] U_xi[k][co].
-// Those 16 products run on the matrix cores: v_mfma_f32_16x16x4_f32, 16 tiles x 16 output channels per wavefront,
-// with the k-permutation of mma.hpp (both operands k-contiguous per lane: one float4 feeds four MFMAs).  Patch and
-// filter transforms are float4 additions in registers (no multiplications but the halvings of G), so the matrix
-// cores do 4/9 of the direct form's work; in fp32 the result differs from the direct form by a few ulps.
+// The arithmetic is fp32 on the bf16 matrix cores (split.hpp): the loader leaves every element in LDS as three bf16 terms
+// (each converted once, not once per tap), the filter values are split in registers while the input is on its way, and six
+// of the nine products are taken.  The matrix-core tile is 16 output channels (rows) x 16 pixels (columns); a wavefront owns
+// one channel tile and four pixel tiles that lie below each other, so a pixel operand fetched for one filter row serves
+// the tiles above it too, and a lane ends up with four consecutive channels of a pixel (16-byte loads and stores in the
+// epilogue).
 //
 // Gradient w.r.t. the input of such a convolution is the same operation on dy with the filter
 // taps reversed and its two channel indices swapped; only the filter fetch differs.
 #include "mma.hpp"
+#include "split.hpp"
 #include "bn_merge.hpp"
 #include "jobs.hpp"
 #include "../../include/dssp_kernels.h"
@@ -109,28 +108,27 @@ __device__ __forceinline__ void dfilter_finish(const floatx4 (&M)[16], floatx4 (
 template <int C, int HW, int R, int NSPLIT>
 struct Cfg {
     static constexpr int CN = C / NSPLIT;          // output channels per workgroup
-    static constexpr int LDC = C + 4;              // pitch of one pixel in LDS (floats)
+    static constexpr int PLANE = 2 * C;            // bytes between the three bf16 terms of a pixel in LDS
+    // pitch of a pixel: 26 words (C = 16, 8-byte reads), 20 and 4 words (mod 32) for 16-byte reads, so that 16 pixels
+    // side by side meet all banks equally
+    static constexpr int PITCH = 3 * PLANE + (C == 16 ? 8 : 16);
     static constexpr int TW = HW + 2;              // halo tile width
-    static constexpr int XS = (R + 2) * TW * LDC;  // floats
-    static constexpr int RUNS = R * HW / 16;       // output pixels of the band / 16
+    static constexpr int XB = (R + 2) * TW * PITCH;            // bytes
     static constexpr int WAVES_N = CN / 16;        // wavefronts side by side over the output channels
-    static constexpr int WAVES_M = 4 / WAVES_N;    // ... and over the runs
-    static constexpr int WM = RUNS / WAVES_M;      // accumulator tiles (16 pixels x 16 channels) a wavefront finishes
-    static constexpr int KC = C / 16;              // 16-wide chunks of the reduction channel
-    static constexpr int SS = 8 * CN;              // per-wavefront column sums (batch-norm records, two components)
-    static constexpr int PS = THREADS + 2 * C;     // merge of the input's batch-norm records: tree + (mean, invstd)
-    // A run is 16 tiles of 2x2 outputs; every wavefront works on one run.  If the band has fewer runs than
-    // WAVES_M (last stage: 16 tiles per image), KS wavefronts share a run and split the input channels; they swap
-    // halves of their partial results through LDS and each finishes its half.
-    static constexpr int WRUNS = (R / 2) * (HW / 2) / 16;      // runs per band
-    static constexpr int KS = WAVES_M / WRUNS;                 // wavefronts per run, each with 1/KS of the channels
-    static constexpr int KCW = KC / KS;                        // k-chunks per wavefront
-    static constexpr size_t LDS_BYTES = (size_t)(XS + SS + PS) * sizeof(float);
-    static constexpr size_t LDS_BYTES_WG = LDS_BYTES + (size_t)XS * sizeof(float);   // + the x halo tile of the fused d-filter
-    static_assert(WAVES_N == 1 || WAVES_N == 2 || WAVES_N == 4, "one 16-channel tile per wavefront");
-    static_assert(RUNS % WAVES_M == 0 && WM >= 1, "band must give every wavefront at least one run");
-    static_assert(WRUNS * KS == WAVES_M && (KS == 1 || KS == 2) && WM * KS == 4 && KCW * KS == KC,
-                  "one run of 16 tiles per wavefront, 16 / KS outputs per lane");
+    static constexpr int WAVES_M = 4 / WAVES_N;    // ... and over the pixels or, in the last stage, the input channels
+    // A wavefront works on four pixel tiles, each one (HW >= 16) or two (HW = 8) image rows below the one before.
+    static constexpr int TROWS = HW >= 16 ? 1 : 2;
+    static constexpr int TX = HW >= 16 ? HW / 16 : 1;          // tiles side by side
+    static constexpr int WPX = R / (4 * TROWS) * TX;           // wavefronts over the band's pixels
+    static constexpr int KS = WAVES_M / WPX;       // wavefronts that share pixels and split the input channels; they swap
+                                                   // halves of their sums through LDS and each finishes its half
+    static constexpr int WM = 4 / KS;              // pixel tiles a wavefront finishes
+    static constexpr int SS = 8 * CN;              // floats: per-wavefront column sums (batch-norm records, two components)
+    static constexpr int PS = 5 * C;               // floats: per-channel vectors of the loader
+    static constexpr size_t LDS_BYTES = XB + (size_t)(SS + PS) * sizeof(float);
+    static constexpr size_t LDS_BYTES_WG = LDS_BYTES + XB;     // + the x halo tile of the fused d-filter
+    static_assert(WPX * KS == WAVES_M && (KS == 1 || KS == 2) && (C == 16 || C == 32 * KS), "roles of the four wavefronts");
+    static_assert(XB % 16 == 0 && KS * 4 * 4 * 64 * 16 / 2 <= XB, "alignment; room for the exchange");
 };
 
 // Normalisation applied to the input while it is loaded (PRE != 0): the kernel then computes
@@ -189,24 +187,92 @@ struct WgradFused {
 
 // add and dst may be the same buffer (every element is read and written by the same lane); with PRE == 3
 // dst must differ from src, whose halo rows other workgroups still read.
-// Registers: with the Winograd form the compiler would keep all 16 accumulator tiles in flight and the kernel
-// at 2-3 wavefronts per SIMD; told how many should fit, it orders the work row by row instead (no spills).
-template <int C, bool TRANSPOSED, bool WG>
-constexpr int min_waves() { return C == 16 ? (WG ? 2 : TRANSPOSED ? 3 : 4) : C == 32 ? 2 : 1; }
+template <int C, bool WG>
+constexpr int min_waves() { return C == 16 && !WG ? 4 : 2; }
+
+// Sum over the 16 lanes of a quarter wavefront, in all of them.
+__device__ __forceinline__ float sum16(float v) {
+#define ROR(n) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + n, 0xf, 0xf, true))
+    v += ROR(8); v += ROR(4); v += ROR(2); v += ROR(1);
+#undef ROR
+    return v;
+}
+__device__ __forceinline__ float4 sum16(float4 v) { return make_float4(sum16(v.x), sum16(v.y), sum16(v.z), sum16(v.w)); }
+
+// One matrix-core operand of fp32 values.  32 reduction channels: the three planes, a lane's eight channels each.
+// 16 reduction channels (C = 16): an instruction's 32 indices take two planes of them, a lane's four channels each, and
+// three instructions instead of six do the six products: (y2, y0) . (x0, x2), (y0, y1) . (x1, x0), (y0, y1) . (x0, x1).
+template <int C> struct Filt { uint4 v[C == 16 ? 2 : 3]; };
+template <int C> struct Pix { uint4 v[3]; };
+
+template <int C> __device__ __forceinline__ Filt<C> filter_operand(const float4 (&r)[C == 16 ? 1 : 2]) {
+    Filt<C> f;
+    uint2 lo[split::PLANES];
+    split::split4(r[0], lo);
+    if constexpr (C == 16) {
+        f.v[0] = make_uint4(lo[2].x, lo[2].y, lo[0].x, lo[0].y);
+        f.v[1] = make_uint4(lo[0].x, lo[0].y, lo[1].x, lo[1].y);
+    } else {
+        uint2 hi[split::PLANES];
+        split::split4(r[1], hi);
+#pragma unroll
+        for (int p = 0; p < split::PLANES; ++p) f.v[p] = make_uint4(lo[p].x, lo[p].y, hi[p].x, hi[p].y);
+    }
+    return f;
+}
+
+template <int C, int PLANE> __device__ __forceinline__ Pix<C> pixel_operand(const char* at) {
+    Pix<C> x;
+    if constexpr (C == 16) {
+        const uint2 x0 = *reinterpret_cast<const uint2*>(at), x1 = *reinterpret_cast<const uint2*>(at + PLANE),
+                    x2 = *reinterpret_cast<const uint2*>(at + 2 * PLANE);
+        x.v[0] = make_uint4(x0.x, x0.y, x2.x, x2.y);
+        x.v[1] = make_uint4(x1.x, x1.y, x0.x, x0.y);
+        x.v[2] = make_uint4(x0.x, x0.y, x1.x, x1.y);
+    } else {
+#pragma unroll
+        for (int p = 0; p < split::PLANES; ++p) x.v[p] = *reinterpret_cast<const uint4*>(at + p * PLANE);
+    }
+    return x;
+}
+
+// the same for the transposing reads of the d-filter step: lane l16 of quarter q receives channel l16 of pixels 8 q ..
+template <int PLANE> __device__ __forceinline__ void transposed_operand(uint4 (&x)[split::PLANES], const char* lo_at, const char* hi_at) {
+#pragma unroll
+    for (int p = 0; p < split::PLANES; ++p) {
+        const uint2 lo = split::read_tr(lo_at + p * PLANE), hi = split::read_tr(hi_at + p * PLANE);
+        x[p] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    }
+}
+
+template <int C> constexpr int products() { return C == 16 ? 3 : 6; }
+// product p of the sum, small ones first
+template <int C> __device__ __forceinline__ floatx4 product(int p, const Filt<C>& f, const Pix<C>& x, floatx4 acc) {
+    if constexpr (C == 16) {
+        return split::mfma(f.v[p ? 1 : 0], x.v[p], acc);
+    } else {
+        constexpr int PF[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
+        return split::mfma(f.v[PF[p]], x.v[PX[p]], acc);
+    }
+}
 
 template <int C, int HW, int R, int NSPLIT, bool TRANSPOSED, int PRE, bool POST = false, bool WG = false>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_waves<C, TRANSPOSED, WG>()))) void conv3x3_kernel(const float* __restrict__ src, const float* __restrict__ wgt,
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_waves<C, WG>()))) void conv3x3_kernel(const float* __restrict__ src, const float* __restrict__ wgt,
                                                           const float* add, float* dst,
                                                           float* __restrict__ bn_partial, PreBn pre, PostBn post, BwdBn bwd,
                                                           int conv_blocks, jobs::ReduceJob rj, WgradFused wg) {
     using K = Cfg<C, HW, R, NSPLIT>;
     static_assert(!WG || (PRE == 3 && NSPLIT == 1 && TRANSPOSED && (C == 16 || C == 32)), "fused d-filter: d-input form, whole channel range");
-    extern __shared__ __attribute__((aligned(16))) float lds[];
+    extern __shared__ __attribute__((aligned(16))) char lds_bytes[];
+    char* lds = lds_bytes;
     if ((int)blockIdx.x >= conv_blocks) {           // workgroups behind the convolution's own carry the reduction job
-        jobs::wgrad_reduce(rj, blockIdx.x - conv_blocks, lds);
+        jobs::wgrad_reduce(rj, blockIdx.x - conv_blocks, reinterpret_cast<float*>(lds));
         return;
     }
-    float* Xs = lds;
+    char* Xs = lds;
+    float* Ss = reinterpret_cast<float*>(lds + K::XB);          // column sums
+    float* Sh = Ss + K::SS;                                     // per-channel vectors of the loader
+    char* Xs2 = lds + K::LDS_BYTES;                             // x halo tile (WG)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, q = lane >> 4;
     const int wave_n = wave % K::WAVES_N, wave_m = wave / K::WAVES_N;
@@ -216,17 +282,33 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
     const int band = (tile / NSPLIT) % BANDS;
     const int n = tile / (NSPLIT * BANDS);
     const int r_base = band * R;                    // first output row of the band
-    const int co_base = split * K::CN;
-    const int co = co_base + 16 * wave_n + l16;     // this lane's output channel (column of the MFMA tile)
+    const int co_w = split * K::CN + 16 * wave_n;   // first output channel of this wavefront
+    const int wpx = wave_m / K::KS, ks = wave_m % K::KS;       // its pixels, its share of the input channels
+    const int row0 = wpx / K::TX * 4 * K::TROWS + (K::TROWS == 2 ? l16 >> 3 : 0);      // this lane's pixel in the first tile
+    const int col = K::TROWS == 2 ? l16 & 7 : 16 * (wpx % K::TX) + l16;
 
-    // ---- input halo tile, zero outside the image.  The raw loads are issued first; with PRE the merge of
-    //      the statistics records (a latency chain of its own) then runs while they are in flight.
+    // ---- filter values of this lane, result channel co_w + l16 (row of the MFMA tile) and reduction channels k0 ..:
+    //      forward : w[tap][k][co]           (C floats apart)
+    //      d-input : w[8 - tap][co][k]       (16-byte loads, taps reversed)
+    constexpr int FV = C == 16 ? 1 : 2;
+    const int k0 = C == 16 ? 4 * q : 32 * ks + 8 * q;
+    float4 fr[9][FV];
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+        for (int e = 0; e < FV; ++e) {
+            if constexpr (TRANSPOSED) {
+                fr[tap][e] = *reinterpret_cast<const float4*>(wgt + ((long)(8 - tap) * C + co_w + l16) * C + k0 + 4 * e);
+            } else {
+                const float* wp = wgt + ((long)tap * C + k0 + 4 * e) * C + co_w + l16;
+                fr[tap][e] = make_float4(wp[0], wp[C], wp[2 * C], wp[3 * C]);
+            }
+        }
+    // ---- input halo tile, zero outside the image.  The raw loads are issued first; the filter is split while they are
+    //      in flight.
     constexpr int V = C / 4;
     constexpr int NL = ((R + 2) * K::TW * V + THREADS - 1) / THREADS;
-    float* Sh = PRE == 3 ? lds + K::XS + K::SS                  // five per-channel vectors (PRE == 3)
-                         : lds + K::XS + K::SS + THREADS;       // mean[C], invstd[C] of the input (PRE == 1, 2)
     float4 val[NL], scv[PRE >= 2 ? NL : 1], xin[WG ? NL : 1];
-    float* Xs2 = lds + K::XS + K::SS + K::PS;                   // x halo tile (WG)
 #pragma unroll
     for (int e = 0; e < NL; ++e) {
         const int idx = tid + e * THREADS;
@@ -246,6 +328,9 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
                 xin[e] = *reinterpret_cast<const float4*>(wg.x_in + (((long)n * HW + h) * HW + w) * C + 4 * v);
         }
     }
+    Filt<C> filt[9];
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) filt[tap] = filter_operand<C>(fr[tap]);
     if constexpr (PRE == 1 || PRE == 2) {   // mean / invstd of the input, merged from its records by records_merge_kernel
         if (tid < 2 * C) Sh[tid] = pre.stats_out[tid];
         __syncthreads();
@@ -261,6 +346,12 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
         }
         __syncthreads();
     }
+    auto stage = [&](char* to, float4 v) {  // 4 channels of a pixel as their three terms
+        uint2 pl[split::PLANES];
+        split::split4(v, pl);
+#pragma unroll
+        for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(to + p * K::PLANE) = pl[p];
+    };
 #pragma unroll
     for (int e = 0; e < NL; ++e) {
         const int idx = tid + e * THREADS;
@@ -285,7 +376,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
                     *reinterpret_cast<float4*>(bwd.dx_out + (((long)n * HW + h) * HW + w) * C + 4 * v) = o;
             }
         }
-        if constexpr (WG) *reinterpret_cast<float4*>(&Xs2[(pr * K::TW + pc) * K::LDC + 4 * v]) = xin[e];
+        if constexpr (WG) stage(Xs2 + (pr * K::TW + pc) * K::PITCH + 8 * v, xin[e]);
         if constexpr (PRE == 1 || PRE == 2) {
             if (h >= 0 && h < HW && w >= 0 && w < HW) {
                 const float4 mu = *reinterpret_cast<const float4*>(Sh + 4 * v);
@@ -305,225 +396,197 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
                     *reinterpret_cast<float4*>(pre.act_out + (((long)n * HW + h) * HW + w) * C + 4 * v) = o;
             }
         }
-        *reinterpret_cast<float4*>(&Xs[(pr * K::TW + pc) * K::LDC + 4 * v]) = val[e];
+        stage(Xs + (pr * K::TW + pc) * K::PITCH + 8 * v, val[e]);
     }
-    // ---- filter values of this wavefront's 16 output channels, B[k][co] with k = 16 kc + 4 q + {0..3}:
-    //      forward : w[tap][k][co]           (four loads, C floats apart)
-    //      d-input : w[8 - tap][co][k]       (one 16-byte load, taps reversed)
-    const int wrun = wave_m / K::KS, ks = wave_m % K::KS;      // this wavefront's run and share of the channels
-    const int k0 = 16 * K::KCW * ks + 4 * q;                   // its first reduction channel
-    float4 bf[9][K::KCW];
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-        for (int kc = 0; kc < K::KCW; ++kc) {
-            if constexpr (TRANSPOSED) {
-                bf[tap][kc] = *reinterpret_cast<const float4*>(wgt + ((long)(8 - tap) * C + co) * C + k0 + 16 * kc);
-            } else {
-                const float* wp = wgt + ((long)tap * C + k0 + 16 * kc) * C + co;
-                bf[tap][kc] = make_float4(wp[0], wp[C], wp[2 * C], wp[3 * C]);
-            }
-        }
     __syncthreads();
 
+    // ---- products.  Pixel operand (st, kx): the tile that starts st rows below the wavefront's first one, kx to the right
+    //      (halo coordinates); it meets filter row ky in the tile t with TROWS t + ky = st.
     floatx4 acc[K::WM];
-    // band-local pixel (row-major) of accumulator element (wm, v)
-    auto pixel = [&](int wm, int v) {   // tile 4q + v of the wavefront's run, output (e / 2, e % 2) of its 2x2
-        const int g = wrun * 16 + 4 * q + v, e = ks * K::WM + wm;
-        return (2 * (g / (HW / 2)) + (e >> 1)) * HW + 2 * (g % (HW / 2)) + (e & 1);
-    };
     {
-        // ---- Winograd F(2x2, 3x3), Y = A^T [ (G g G^T) .* (B^T d B) ] A per tile and channel pair, the products
-        //      summed over the input channels by the matrix cores: for each of the 16 positions of the transformed
-        //      4x4 patch, M[tile][co] += V[tile][k] U[k][co].  A lane transforms the patch of tile l16 (channels
-        //      16 kc + 4q ..) and the filter of output channel `co` (same channels), both element-wise on float4.
-        constexpr int TXN = HW / 2;
-        const int g = wrun * 16 + l16;
-        const int base = (2 * (g / TXN) * K::TW + 2 * (g % TXN)) * K::LDC + k0;
-        // Row a of the transformed patch at a time (4 of the 16 positions), so that only its four accumulators,
-        // its four U and V values and the running A^T M sums are live: s0 = M0 + M1 + M2, s1 = M1 - M2 - M3.
-        floatx4 s0[4], s1[4];
+        constexpr int ST = 3 * K::TROWS + 3;
+        const char* base = Xs + (row0 * K::TW + col) * K::PITCH + (C == 16 ? 8 : 16) * q + 64 * ks;
+        // Two accumulators: the leading products, and the small ones (2^-8 and less of them), so that most of the roundings are
+        // those of the small sum.
+        floatx4 a[4], lo[4];
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            floatx4 m[4];
+        for (int t = 0; t < 4; ++t) a[t] = lo[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        Pix<C> x[2];
+        x[0] = pixel_operand<C, K::PLANE>(base);
 #pragma unroll
-            for (int b = 0; b < 4; ++b) m[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < 3 * ST; ++i) {
+            const int st = i / 3, kx = i % 3;
+            if (i + 1 < 3 * ST) x[(i + 1) & 1] = pixel_operand<C, K::PLANE>(base + ((i + 1) / 3 * K::TW + (i + 1) % 3) * K::PITCH);
+            __builtin_amdgcn_sched_barrier(0);      // or the compiler moves the reads down to their use, behind the products
 #pragma unroll
-            for (int kc = 0; kc < K::KCW; ++kc) {
-                float4 U[4];           // row a of G g G^T, G = [1 0 0; .5 .5 .5; .5 -.5 .5; 0 0 1]
-                {
-                    float4 u[3];
+            for (int p = 0; p < products<C>(); ++p)
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        const float4 g0 = bf[j][kc], g1 = bf[3 + j][kc], g2 = bf[6 + j][kc];
-                        u[j] = a == 0 ? g0 : a == 3 ? g2 : a == 1 ? (g0 + g2) * 0.5f + g1 * 0.5f : (g0 + g2) * 0.5f - g1 * 0.5f;
-                    }
-                    const float4 e = (u[0] + u[2]) * 0.5f, o = u[1] * 0.5f;
-                    U[0] = u[0]; U[1] = e + o; U[2] = e - o; U[3] = u[2];
+                for (int t = 0; t < 4; ++t) {
+                    const int ky = st - K::TROWS * t;
+                    if (ky < 0 || ky > 2) continue;
+                    floatx4& to = p + 1 < products<C>() ? lo[t] : a[t];
+                    to = product<C>(p, filt[3 * ky + kx], x[i & 1], to);
                 }
-                float4 V[4];           // row a of B^T d B, B^T = [1 0 -1 0; 0 1 1 0; 0 -1 1 0; 0 1 0 -1]
-                {
-                    constexpr int RA[4] = {0, 1, 2, 1}, RB[4] = {2, 2, 1, 3};      // t[a] = +-d[RA] +- d[RB]
-                    float4 t[4];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const float4 da = *reinterpret_cast<const float4*>(&Xs[base + (RA[a] * K::TW + c) * K::LDC + 16 * kc]);
-                        const float4 db = *reinterpret_cast<const float4*>(&Xs[base + (RB[a] * K::TW + c) * K::LDC + 16 * kc]);
-                        t[c] = a == 1 ? da + db : da - db;
-                    }
-                    V[0] = t[0] - t[2]; V[1] = t[1] + t[2]; V[2] = t[2] - t[1]; V[3] = t[1] - t[3];
-                }
-#pragma unroll
-                for (int b = 0; b < 4; ++b) m[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(V[b].x, U[b].x, m[b], 0, 0, 0);
-#pragma unroll
-                for (int b = 0; b < 4; ++b) m[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(V[b].y, U[b].y, m[b], 0, 0, 0);
-#pragma unroll
-                for (int b = 0; b < 4; ++b) m[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(V[b].z, U[b].z, m[b], 0, 0, 0);
-#pragma unroll
-                for (int b = 0; b < 4; ++b) m[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(V[b].w, U[b].w, m[b], 0, 0, 0);
-            }
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                if (a == 0) s0[b] = m[b];
-                if (a == 1) { s0[b] += m[b]; s1[b] = m[b]; }
-                if (a == 2) { s0[b] += m[b]; s1[b] -= m[b]; }
-                if (a == 3) s1[b] -= m[b];
-            }
+            __builtin_amdgcn_sched_barrier(0);
         }
         mma::drain();
-        // (A^T M) A, A^T = [1 1 1 0; 0 1 -1 -1]: element v of every accumulator belongs to tile 4q + v
-        floatx4 y[4];
-        y[0] = s0[0] + s0[1] + s0[2]; y[1] = s0[1] - s0[2] - s0[3];
-        y[2] = s1[0] + s1[1] + s1[2]; y[3] = s1[1] - s1[2] - s1[3];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[t] += lo[t];
         if constexpr (K::KS == 1) {
 #pragma unroll
-            for (int wm = 0; wm < 4; ++wm) acc[wm] = y[wm];
+            for (int t = 0; t < 4; ++t) acc[t] = a[t];
         } else {
-            // the two wavefronts of a run hold partial sums over their halves of the input channels: each hands
-            // the other the two accumulators it will not finish and adds what it receives (first half + second half)
+            // the two wavefronts of a group of pixels hold partial sums over their halves of the input channels: each
+            // hands the other the two tiles it will not finish and adds what it receives (first half + second half)
             __syncthreads();                               // every wavefront has read the tile for the last time
-            float* Ex = lds;                               // [wavefront][2][4][64]
+            float* Ex = reinterpret_cast<float*>(lds);             // [wavefront][2][64][4]
 #pragma unroll
             for (int wm = 0; wm < 2; ++wm)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) Ex[((wave * 2 + wm) * 4 + v) * 64 + lane] = ks == 0 ? y[2 + wm][v] : y[wm][v];
+                for (int v = 0; v < 4; ++v) {
+                    const float give = ks == 0 ? a[2 + wm][v] : a[wm][v];
+                    acc[wm][v] = ks == 0 ? a[wm][v] : a[2 + wm][v];
+                    Ex[((wave * 2 + wm) * 64 + lane) * 4 + v] = give;
+                }
             __syncthreads();
             const int partner = (wave_m ^ 1) * K::WAVES_N + wave_n;
 #pragma unroll
             for (int wm = 0; wm < 2; ++wm)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float other = Ex[((partner * 2 + wm) * 4 + v) * 64 + lane];
-                    const float own = ks == 0 ? y[wm][v] : y[2 + wm][v];
-                    acc[wm][v] = ks == 0 ? own + other : other + own;
-                }
+                for (int v = 0; v < 4; ++v) acc[wm][v] += Ex[((partner * 2 + wm) * 64 + lane) * 4 + v];
         }
     }
 
-    mma::drain();
-    // ---- store: lane holds the elements acc[wm][v] of pixels pixel(wm, v), all of output channel co
-    float sum_dz = 0.f, sum_dzx = 0.f, mu_c = 0.f, is_c = 0.f;
+    // ---- store: a lane holds channels co .. co + 3 of its pixel of every tile
+    const int co = co_w + 4 * q;
+    float4 mu_c = make_float4(0.f, 0.f, 0.f, 0.f), is_c = mu_c;
     if constexpr (POST) {
-        mu_c = post.stats[co];
-        is_c = post.stats[C + co];
+        mu_c = *reinterpret_cast<const float4*>(post.stats + co);
+        is_c = *reinterpret_cast<const float4*>(post.stats + C + co);
     }
     // all loads of the epilogue first (dst may alias add, so the compiler cannot move them across the stores itself)
-    float addv[K::WM][4], maskv[POST ? K::WM : 1][4], xcv[POST ? K::WM : 1][4];
-    auto out_off = [&](int wm, int v) {
-        const int p = pixel(wm, v);
-        return (((long)n * HW + r_base + p / HW) * HW + p % HW) * C + co;
-    };
+    float4 addv[K::WM], maskv[POST ? K::WM : 1], xcv[POST ? K::WM : 1];
+    auto row_of = [&](int wm) { return row0 + K::TROWS * (ks * K::WM + wm); };
+    auto out_off = [&](int wm) { return (((long)n * HW + r_base + row_of(wm)) * HW + col) * C + co; };
 #pragma unroll
-    for (int wm = 0; wm < K::WM; ++wm)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const long off = out_off(wm, v);
-            addv[wm][v] = add ? add[off] : 0.f;
-            if constexpr (POST) {
-                if constexpr (WG) {     // the mask source is the convolution's input, whose tile is in LDS
-                    const int p = pixel(wm, v);
-                    maskv[wm][v] = Xs2[((p / HW + 1) * K::TW + (p % HW + 1)) * K::LDC + co];
-                } else {
-                    maskv[wm][v] = post.mask_src[off];
-                }
-                xcv[wm][v] = post.xc[off];
+    for (int wm = 0; wm < K::WM; ++wm) {
+        const long off = out_off(wm);
+        addv[wm] = add ? *reinterpret_cast<const float4*>(add + off) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (POST) {
+            if constexpr (WG) {     // the mask source is the convolution's input, whose leading terms are in LDS
+                const uint2 m = *reinterpret_cast<const uint2*>(Xs2 + ((row_of(wm) + 1) * K::TW + col + 1) * K::PITCH + 2 * co);
+                maskv[wm] = make_float4(__uint_as_float(m.x << 16), __uint_as_float(m.x & 0xffff0000u),
+                                        __uint_as_float(m.y << 16), __uint_as_float(m.y & 0xffff0000u));
+            } else {
+                maskv[wm] = *reinterpret_cast<const float4*>(post.mask_src + off);
             }
+            xcv[wm] = *reinterpret_cast<const float4*>(post.xc + off);
         }
+    }
     if constexpr (WG) {
-        // ---- d-filter of the same layer from the two LDS tiles, while the epilogue's operands are in flight (see
-        //      dfilter_run): x patches from Xs2, dx tiles from the interior of Xs.
-        //      C = 16: one 16x16 tile of (ci, co), the four wavefronts take one run each and are summed in a fixed
-        //      order; C = 32: wavefront w owns tile (w / 2, w % 2) and walks both runs.
+        // ---- d-filter of the same layer from the two LDS tiles, while the epilogue's operands are in flight:
+        //      dw[tap][ci][co] += x[pixel + tap][ci] dx[pixel][co], pixels as reduction index, 32 to an MFMA, both operands
+        //      by transposing reads.  A run of 32 pixels is one image row (C = 16) or two (C = 32); an x operand fetched
+        //      for one filter row serves the run above it too.  Rows of the matrix-core tile: co, columns: ci.
+        //      C = 16: one 16x16 tile of (ci, co); a wavefront takes two of the band's eight runs, the four are summed
+        //      in a fixed order.  C = 32: wavefront w owns tile (w / 2, w % 2) and takes all four runs.
         constexpr bool SPLIT_K = (C == 16);
-        constexpr int TXN = HW / 2;
+        constexpr int RROWS = 32 / HW, RUNS = SPLIT_K ? 2 : 4;     // image rows per run, runs per wavefront
         const int cit = SPLIT_K ? 0 : wave >> 1, cot = SPLIT_K ? 0 : wave & 1;
-        floatx4 M[16];
+        const int first = SPLIT_K ? RUNS * wave : 0;               // first image row of the wavefront's runs
+        const char *xa[2], *da[2];                                 // of pixels 8 q + 4 h + l16 / 4 of the first run
 #pragma unroll
-        for (int xi = 0; xi < 16; ++xi) M[xi] = floatx4{0.f, 0.f, 0.f, 0.f};
-        for (int run = SPLIT_K ? wave : 0; run < K::WRUNS; run += SPLIT_K ? 4 : 1) {
-            dfilter_run(M, q,
-                        [&](int tile) {                 // the patch's corner in both halo tiles
-                            const int g = run * 16 + tile;
-                            return (2 * (g / TXN) * K::TW + 2 * (g % TXN)) * K::LDC;
-                        },
-                        [&](int o, int r, int c) { return Xs2[o + (r * K::TW + c) * K::LDC + 16 * cit + l16]; },
-                        [&](int o, int i, int j) { return Xs[o + ((i + 1) * K::TW + j + 1) * K::LDC + 16 * cot + l16]; });
+        for (int h = 0; h < 2; ++h) {
+            const int p = 8 * q + 4 * h + (l16 >> 2);
+            const int o = ((first + p / HW) * K::TW + p % HW) * K::PITCH + 8 * (l16 & 3);
+            xa[h] = Xs2 + o + 32 * cit;
+            da[h] = Xs + o + (K::TW + 1) * K::PITCH + 32 * cot;
+        }
+        floatx4 dw[9];
+#pragma unroll
+        for (int t = 0; t < 9; ++t) dw[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        uint4 d[RUNS][split::PLANES], x[2][split::PLANES];
+        auto load_d = [&](int run) { transposed_operand<K::PLANE>(d[run], da[0] + run * RROWS * K::TW * K::PITCH, da[1] + run * RROWS * K::TW * K::PITCH); };
+        auto load_x = [&](int b, int i) {
+            const int off = (i / 3 * K::TW + i % 3) * K::PITCH;
+            transposed_operand<K::PLANE>(x[b], xa[0] + off, xa[1] + off);
+        };
+        constexpr int ST = RROWS * (RUNS - 1) + 3;
+        load_d(0);
+        load_x(0, 0);
+#pragma unroll
+        for (int i = 0; i < 3 * ST; ++i) {
+            const int st = i / 3, kx = i % 3;
+            if (i + 1 < 3 * ST) load_x((i + 1) & 1, i + 1);
+            if (i % 3 == 0 && st % RROWS == 0 && st / RROWS + 1 < RUNS) load_d(st / RROWS + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int PD[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+            for (int p = 0; p < 6; ++p)
+#pragma unroll
+                for (int run = 0; run < RUNS; ++run) {
+                    const int ky = st - RROWS * run;
+                    if (ky >= 0 && ky < 3) dw[3 * ky + kx] = split::mfma(d[run][PD[p]], x[i & 1][PX[p]], dw[3 * ky + kx]);
+                }
+            __builtin_amdgcn_sched_barrier(0);
         }
         mma::drain();
-        floatx4 dwa[9];
-        dfilter_finish(M, dwa);
         float* pout = wg.partial + (long)tile * 9 * C * C;
         if constexpr (SPLIT_K) {
-            static_assert(!SPLIT_K || 4 * 9 * C * C <= 2 * K::XS + K::SS + K::PS, "room for the four partial sums");
+            static_assert(!SPLIT_K || 4 * 9 * C * C * sizeof(float) <= K::LDS_BYTES_WG, "room for the four partial sums");
             __syncthreads();                              // both tiles are no longer needed: reuse LDS for the 4 partial sums
-            float* Red = lds;
+            floatx4* Red = reinterpret_cast<floatx4*>(lds);       // [wavefront][tap][ci][co / 4]
+            constexpr int E4 = 9 * C * C / 4;
 #pragma unroll
-            for (int t = 0; t < 9; ++t)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) Red[wave * 9 * C * C + (t * C + 4 * q + v) * C + l16] = dwa[t][v];
+            for (int t = 0; t < 9; ++t) Red[wave * E4 + (t * C + l16) * 4 + q] = dw[t];
             __syncthreads();
-            for (int idx = tid; idx < 9 * C * C; idx += THREADS)
-                pout[idx] = (Red[idx] + Red[9 * C * C + idx]) + (Red[2 * 9 * C * C + idx] + Red[3 * 9 * C * C + idx]);
+            for (int idx = tid; idx < E4; idx += THREADS)
+                reinterpret_cast<floatx4*>(pout)[idx] = (Red[idx] + Red[E4 + idx]) + (Red[2 * E4 + idx] + Red[3 * E4 + idx]);
             __syncthreads();                              // before the epilogue's sums use LDS again
         } else {
 #pragma unroll
             for (int t = 0; t < 9; ++t)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) pout[(t * C + 16 * cit + 4 * q + v) * C + 16 * cot + l16] = dwa[t][v];
+                *reinterpret_cast<floatx4*>(pout + (t * C + 16 * cit + l16) * C + 16 * cot + 4 * q) = dw[t];
         }
     }
+    float4 sum_dz = make_float4(0.f, 0.f, 0.f, 0.f), sum_dzx = sum_dz;
 #pragma unroll
-    for (int wm = 0; wm < K::WM; ++wm)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            float r = acc[wm][v] + addv[wm][v];
-            if constexpr (POST) {
-                r = maskv[wm][v] > 0.f ? r : 0.f;
-                const float xh = (xcv[wm][v] - mu_c) * is_c;
-                sum_dz += r;
-                sum_dzx = fmaf(r, xh, sum_dzx);
-            }
-            dst[out_off(wm, v)] = r;
+    for (int wm = 0; wm < K::WM; ++wm) {
+        float4 r = make_float4(acc[wm][0] + addv[wm].x, acc[wm][1] + addv[wm].y, acc[wm][2] + addv[wm].z, acc[wm][3] + addv[wm].w);
+        if constexpr (POST) {
+            r.x = maskv[wm].x > 0.f ? r.x : 0.f; r.y = maskv[wm].y > 0.f ? r.y : 0.f;
+            r.z = maskv[wm].z > 0.f ? r.z : 0.f; r.w = maskv[wm].w > 0.f ? r.w : 0.f;
+            sum_dz.x += r.x; sum_dz.y += r.y; sum_dz.z += r.z; sum_dz.w += r.w;
+            sum_dzx.x = fmaf(r.x, (xcv[wm].x - mu_c.x) * is_c.x, sum_dzx.x);
+            sum_dzx.y = fmaf(r.y, (xcv[wm].y - mu_c.y) * is_c.y, sum_dzx.y);
+            sum_dzx.z = fmaf(r.z, (xcv[wm].z - mu_c.z) * is_c.z, sum_dzx.z);
+            sum_dzx.w = fmaf(r.w, (xcv[wm].w - mu_c.w) * is_c.w, sum_dzx.w);
         }
-    // per-channel totals over the workgroup's tile: lanes of a wavefront by shuffles, then the WAVES_M
+        *reinterpret_cast<float4*>(dst + out_off(wm)) = r;
+    }
+    // per-channel totals over the workgroup's tile: lanes of a wavefront by lane rotations, then the WAVES_M
     // wavefronts that share the channel tile through LDS, in a fixed order
-    float* Ss = lds + K::XS;
-    const int cl = 16 * wave_n + l16;                // channel inside the workgroup's CN
+    const int cl = 16 * wave_n + 4 * q;              // first channel inside the workgroup's CN
+    auto put = [&](float* S, float4 v) { if (l16 == 0) *reinterpret_cast<float4*>(S + wave_m * K::CN + cl) = v; };
     auto tile_total = [&](const float* S) {
-        float t = S[cl];
+        float4 t = *reinterpret_cast<const float4*>(S + cl);
 #pragma unroll
-        for (int m = 1; m < K::WAVES_M; ++m) t += S[m * K::CN + cl];
+        for (int m = 1; m < K::WAVES_M; ++m) {
+            const float4 o = *reinterpret_cast<const float4*>(S + m * K::CN + cl);
+            t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+        }
         return t;
     };
+    auto put_records = [&](float* records, float4 a_, float4 b_) {      // pairs per channel
+        float4* to = reinterpret_cast<float4*>(records + ((long)(n * BANDS + band) * C + co) * 2);
+        to[0] = make_float4(a_.x, b_.x, a_.y, b_.y);
+        to[1] = make_float4(a_.z, b_.z, a_.w, b_.w);
+    };
     if constexpr (POST) {
-        float a_ = sum_dz, b_ = sum_dzx;
-        a_ += __shfl_xor(a_, 16); a_ += __shfl_xor(a_, 32);
-        b_ += __shfl_xor(b_, 16); b_ += __shfl_xor(b_, 32);
-        if (q == 0) { Ss[wave_m * K::CN + cl] = a_; Ss[4 * K::CN + wave_m * K::CN + cl] = b_; }
+        put(Ss, sum16(sum_dz));
+        put(Ss + 4 * K::CN, sum16(sum_dzx));
         __syncthreads();
-        if (wave_m == 0 && q == 0)
-            *reinterpret_cast<float2*>(post.records + ((long)(n * BANDS + band) * C + co) * 2) =
-                make_float2(tile_total(Ss), tile_total(Ss + 4 * K::CN));
+        if (wave_m == 0 && l16 == 0) put_records(post.records, tile_total(Ss), tile_total(Ss + 4 * K::CN));
     }
 
     // ---- optional: batch-norm statistics of this workgroup's output tile, per channel:
@@ -531,27 +594,22 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
     //      (bn_partial[(g*C + c)*2 + {0,1}], g = image * bands + band), merged later like row slabs.
     if (bn_partial) {
         constexpr float inv_n = 1.0f / (float)(R * HW);
-        float mean_t = 0.f;
+        float4 mean = make_float4(0.f, 0.f, 0.f, 0.f), s_ = mean;
 #pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            float s_ = 0.f;
+        for (int wm = 0; wm < K::WM; ++wm) { s_.x += acc[wm][0]; s_.y += acc[wm][1]; s_.z += acc[wm][2]; s_.w += acc[wm][3]; }
+        put(Ss, sum16(s_));
+        __syncthreads();
+        mean = tile_total(Ss);
+        mean.x *= inv_n; mean.y *= inv_n; mean.z *= inv_n; mean.w *= inv_n;
+        s_ = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-            for (int wm = 0; wm < K::WM; ++wm)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float d = pass == 0 ? acc[wm][v] : acc[wm][v] - mean_t;
-                    s_ += pass == 0 ? d : d * d;
-                }
-            s_ += __shfl_xor(s_, 16);
-            s_ += __shfl_xor(s_, 32);
-            if (q == 0) Ss[wave_m * K::CN + cl] = s_;
-            __syncthreads();
-            const float tot = tile_total(Ss);
-            if (pass == 0) mean_t = tot * inv_n;
-            else if (wave_m == 0 && q == 0)
-                *reinterpret_cast<float2*>(bn_partial + ((long)(n * BANDS + band) * C + co) * 2) = make_float2(mean_t, tot);
-            __syncthreads();
+        for (int wm = 0; wm < K::WM; ++wm) {
+            const float dx = acc[wm][0] - mean.x, dy = acc[wm][1] - mean.y, dz = acc[wm][2] - mean.z, dw = acc[wm][3] - mean.w;
+            s_.x += dx * dx; s_.y += dy * dy; s_.z += dz * dz; s_.w += dw * dw;
         }
+        put(Ss + 4 * K::CN, sum16(s_));
+        __syncthreads();
+        if (wave_m == 0 && l16 == 0) put_records(bn_partial, mean, tile_total(Ss + 4 * K::CN));
     }
 }
 

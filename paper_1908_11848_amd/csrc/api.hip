@@ -15,6 +15,15 @@
 #include "../../include/dssp_kernels.h"
 #include "model.hpp"
 
+// The integers the server keeps (Alg. 1 preamble, table A of Alg. 2) plus the bookkeeping of pending snapshots.
+struct HostState {
+    std::vector<int64_t> t;
+    std::vector<int32_t> r;
+    std::vector<std::array<int64_t, 2>> A;
+    std::vector<uint8_t> blocked, has_ok, pull_pending;
+    uint64_t version = 0;
+};
+
 struct dssp_ctx {
     int K = 0, s_L = 0, r_max = 0;
     float lr = 0.f, scale = 0.f;
@@ -35,6 +44,7 @@ struct dssp_ctx {
     std::vector<hipStream_t> wstream;
     std::vector<uint8_t> own_wstream;
     hipEvent_t ev_apply = nullptr;                // last apply finished
+    hipStream_t apply_stream = nullptr;           // where it was enqueued (what follows on that stream needs no wait); null: not known
     std::vector<hipEvent_t> ev_grad;              // worker's gradient is complete
     std::vector<hipEvent_t> ev_pull;              // worker's snapshot copy finished reading w
     std::vector<uint8_t> pull_pending;            // a pull was enqueued since the last apply
@@ -54,11 +64,16 @@ struct dssp_ctx {
     // A worker step is a fixed chain of several hundred kernels whose arguments depend only on the
     // five buffers it is called with.  The first call with a set of buffers runs eagerly, the second
     // is captured into a HIP graph, later ones replay the graph (one submission instead of hundreds).
-    struct StepGraph { int calls = 0; hipGraph_t graph = nullptr; hipGraphExec_t exec = nullptr; };
+    // Steps of at most MAX_LAUNCHES_DIRECT kernels stay launches: submitting a graph takes the host 19 us and 0.6 us a kernel
+    // (22 us for the perceptron's four, 87 us for the 110 of a 20-layer network), a launch 2.6 us, so the lines cross
+    // between 9 and 10.
+    static constexpr size_t MAX_LAUNCHES_DIRECT = 8;
+    struct StepGraph { int calls = 0; bool direct = false; hipGraph_t graph = nullptr; hipGraphExec_t exec = nullptr; };
     typedef std::tuple<int, const void*, const void*, const void*, const void*, const void*> StepKey;
     std::map<StepKey, StepGraph> step_graphs;
     bool use_graphs = true;
 
+    HostState saved;                              // of the push being worked on
     std::string err;
 };
 
@@ -199,6 +214,7 @@ extern "C" int dssp_set_stream(dssp_ctx* c, int worker, void* hip_stream) {
     if (!c) return DSSP_EINVAL;
     if (worker < -1 || worker >= c->K) return fail(c, DSSP_EINVAL, "worker index out of range");
     if (c->host_only) return DSSP_OK;
+    c->apply_stream = nullptr;
     if (worker < 0) { c->server_stream = (hipStream_t)hip_stream; return DSSP_OK; }
     hipStream_t& s = c->wstream[worker];
     if (c->own_wstream[worker] && s) { HIP_TRY(c, hipStreamSynchronize(s)); HIP_TRY(c, hipStreamDestroy(s)); }
@@ -238,7 +254,7 @@ extern "C" int dssp_pull(dssp_ctx* c, int worker, float* dst_dev, uint64_t* vers
     if (!dst_dev) return fail(c, DSSP_EINVAL, "dst_dev is null");
     if (int rc = ensure_stream(c, worker)) return rc;
     hipStream_t s = c->wstream[worker];
-    if (c->version > 0) HIP_TRY(c, hipStreamWaitEvent(s, c->ev_apply, 0));
+    if (c->version > 0 && c->apply_stream != s) HIP_TRY(c, hipStreamWaitEvent(s, c->ev_apply, 0));
     if (int rc = dsspk_pull(s, dst_dev, c->params, c->n_params, c->stamps_dev + 1 + worker, c->stamps_dev))
         return fail(c, DSSP_EHIP, "pull kernel launch failed (rc " + std::to_string(rc) + ")");
     HIP_TRY(c, hipEventRecord(c->ev_pull[worker], s));
@@ -262,7 +278,7 @@ extern "C" int dssp_worker_step(dssp_ctx* c, int worker, const float* x_dev, con
             return DSSP_OK;
         }
     }
-    const bool capture = sg && sg->calls >= 1;
+    const bool capture = sg && sg->calls >= 1 && !sg->direct;
     if (capture) HIP_TRY(c, hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
     const int rc = dssp_model::step(c->plan, worker, s, x_dev, y_dev, w_local_dev, grad_dev, loss_dev, err);
     if (capture) {
@@ -271,6 +287,13 @@ extern "C" int dssp_worker_step(dssp_ctx* c, int worker, const float* x_dev, con
         if (rc || e != hipSuccess) {
             if (graph) (void)hipGraphDestroy(graph);
             return fail(c, DSSP_EHIP, "worker_step (capture): " + err + " rc " + std::to_string(rc) + " " + hipGetErrorString(e));
+        }
+        size_t n_nodes = 0;
+        if (hipGraphGetNodes(graph, nullptr, &n_nodes) == hipSuccess && n_nodes <= dssp_ctx::MAX_LAUNCHES_DIRECT) {
+            sg->direct = true;
+            (void)hipGraphDestroy(graph);
+            const int rd = dssp_model::step(c->plan, worker, s, x_dev, y_dev, w_local_dev, grad_dev, loss_dev, err);
+            return rd ? fail(c, DSSP_EHIP, "worker_step: " + err + " (rc " + std::to_string(rd) + ")") : DSSP_OK;
         }
         const hipError_t ei = hipGraphInstantiate(&sg->exec, graph, nullptr, nullptr, 0);
         if (ei != hipSuccess) {             // the next call with these buffers captures again
@@ -283,24 +306,21 @@ extern "C" int dssp_worker_step(dssp_ctx* c, int worker, const float* x_dev, con
         return DSSP_OK;
     }
     if (rc) return fail(c, DSSP_EHIP, "worker_step: " + err + " (rc " + std::to_string(rc) + ")");
-    if (sg) sg->calls += 1;
+    if (sg && sg->calls == 0) sg->calls = 1;
     return DSSP_OK;
 }
 
 namespace {
 
-// The integers the server keeps (Alg. 1 preamble, table A of Alg. 2) plus the bookkeeping of pending snapshots: saved
-// before a push is decided and put back if any device call of that push fails, so that a failed push leaves the
-// context as it was (the clocks never say "applied" for a gradient that was not).
-struct HostState {
-    std::vector<int64_t> t;
-    std::vector<int32_t> r;
-    std::vector<std::array<int64_t, 2>> A;
-    std::vector<uint8_t> blocked, has_ok, pull_pending;
-    uint64_t version;
-};
-
-HostState save_state(const dssp_ctx* c) { return HostState{c->t, c->r, c->A, c->blocked, c->has_ok, c->pull_pending, c->version}; }
+// Saved before a push is decided and put back if any device call of that push fails, so that a failed push leaves the
+// context as it was (the clocks never say "applied" for a gradient that was not).  The copy is the context's own: no
+// allocation per push.
+const HostState& save_state(dssp_ctx* c) {
+    HostState& h = c->saved;
+    h.t = c->t; h.r = c->r; h.A = c->A; h.blocked = c->blocked; h.has_ok = c->has_ok; h.pull_pending = c->pull_pending;
+    h.version = c->version;
+    return h;
+}
 
 void restore_state(dssp_ctx* c, const HostState& h) {
     c->t = h.t; c->r = h.r; c->A = h.A; c->blocked = h.blocked; c->has_ok = h.has_ok; c->pull_pending = h.pull_pending;
@@ -350,14 +370,20 @@ Decision decide(dssp_ctx* c, int p, int64_t t_push, int* released) {
     return d;
 }
 
-// Stream `as` waits for the apply before it and for every snapshot copy still reading w.
+// Stream `as` waits for the apply before it and for every snapshot copy still reading w.  A wait costs the host 2 to 4 us, so
+// none is enqueued for what the stream order, or another of these waits, guarantees: the apply before it on the same
+// stream, and one that a snapshot copy waited for here followed on its stream.
 int wait_for_w(dssp_ctx* c, hipStream_t as, uint64_t applies_before) {
-    if (applies_before > 0) HIP_TRY(c, hipStreamWaitEvent(as, c->ev_apply, 0));
+    bool behind_apply = applies_before == 0 || c->apply_stream == as;
     for (int q = 0; q < c->K; ++q)
         if (c->pull_pending[q]) {
-            if (c->wstream[q] != as) HIP_TRY(c, hipStreamWaitEvent(as, c->ev_pull[q], 0));
+            if (c->wstream[q] != as) {
+                HIP_TRY(c, hipStreamWaitEvent(as, c->ev_pull[q], 0));
+                if (c->wstream[q] == c->apply_stream) behind_apply = true;
+            }
             c->pull_pending[q] = 0;
         }
+    if (!behind_apply) HIP_TRY(c, hipStreamWaitEvent(as, c->ev_apply, 0));
     return DSSP_OK;
 }
 
@@ -381,6 +407,7 @@ int enqueue_apply(dssp_ctx* c, int p, const float* grad_dev, float* pull_dst_dev
         rc = dsspk_apply(as, c->params, grad_dev, c->n_params, c->scale, c->stamps_dev, c->version);
     if (rc) return fail(c, DSSP_EHIP, "apply kernel launch failed (rc " + std::to_string(rc) + ")");
     HIP_TRY(c, hipEventRecord(c->ev_apply, as));
+    c->apply_stream = as;
     if (fused && !own) HIP_TRY(c, hipStreamWaitEvent(c->wstream[p], c->ev_apply, 0));
     return DSSP_OK;
 }
@@ -400,7 +427,7 @@ int push_impl(dssp_ctx* c, int worker, const float* grad_dev, int64_t t_push, fl
         if (!grad_dev) return fail(c, DSSP_EINVAL, "grad_dev is null");
         if (int rc = ensure_stream(c, p)) return rc;
     }
-    const HostState before = save_state(c);
+    const HostState& before = save_state(c);
     const Decision d = decide(c, p, t_push, released_out);
     const bool fused = d.ok && pull_dst_dev != nullptr;
     if (!c->host_only)
@@ -456,7 +483,7 @@ extern "C" int dssp_push_many(dssp_ctx* c, int m, const int* workers, const floa
             if (int rc = ensure_stream(c, workers[j])) return rc;
         }
     }
-    const HostState before = save_state(c);
+    const HostState& before = save_state(c);
     // snapshots in the order they are taken: after push j its pusher (if it may go on), then the workers it releases
     int snap_worker[DSSPK_APPLY_MANY_MAX_DST], snap_after[DSSPK_APPLY_MANY_MAX_DST], n_snap = 0, n_rel = 0;
     for (int q = 0; q < c->K; ++q) pulled_version_out[q] = 0;
@@ -503,6 +530,7 @@ extern "C" int dssp_push_many(dssp_ctx* c, int m, const int* workers, const floa
                                   before.version + 1))
         return undo(fail(c, DSSP_EHIP, "aggregated apply kernel launch failed (rc " + std::to_string(rc) + ")"));
     HIP_TRY(c, hipEventRecord(c->ev_apply, as));
+    c->apply_stream = as;
     for (int e = 0; e < n_snap; ++e)        // whoever got a snapshot goes on behind the kernel that wrote it
         if (c->wstream[snap_worker[e]] != as) HIP_TRY(c, hipStreamWaitEvent(c->wstream[snap_worker[e]], c->ev_apply, 0));
     return DSSP_OK;

@@ -177,6 +177,17 @@ size_t dsspk_conv_split_wgrad_scratch_floats(int N, int H, int W, int Cin, int C
 int dsspk_conv_split_bwd_weight(void* stream, const float* x_dev, const float* dy_dev, float* dw_dev, int with_bias, float* scratch_dev,
                                 int N, int H, int W, int Cin, int Cout, int k, int pad);
 
+/* First layer of the AlexNet-style networks in the same arithmetic: 5x5 (pad 2), 3 -> 64 channels on [N][32][32][3] images, bias,
+ * ReLU and the 3x3 / stride 2 max-pool behind it in one pass.  a_dev[N][32][32][64]; pooled_dev[N][15][15][64] and arg_dev as
+ * dsspk_maxpool_fwd gives them. */
+int dsspk_conv_first_pool_fwd(void* stream, const float* x_dev, const float* w_dev, const float* bias_dev, float* a_dev,
+                              float* pooled_dev, uint8_t* arg_dev, int N);
+/* Its gradients w.r.t. filter and biases (stored behind the filter: dw_dev[4800 + 64]) from the gradient w.r.t. the pooled output,
+ * i.e. through pooling and ReLU.  scratch_dev: dsspk_conv_first_scratch_floats(N) floats. */
+size_t dsspk_conv_first_scratch_floats(int N);
+int dsspk_conv_first_pool_bwd_weight(void* stream, const float* x_dev, const float* dpooled_dev, const float* pooled_dev,
+                                     const uint8_t* arg_dev, float* dw_dev, float* scratch_dev, int N);
+
 /* dy[i] = a[i] > 0 ? dy[i] : 0 (in place). */
 int dsspk_relu_bwd(void* stream, float* dy_dev, const float* a_dev, long n);
 /* out[i] += in[i]. */

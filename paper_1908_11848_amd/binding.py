@@ -93,6 +93,9 @@ _SIGNATURES = {
     "dsspk_conv_split_fwd": (c_int, [c_void_p] * 5 + [c_int] * 8),
     "dsspk_conv_split_bwd_data": (c_int, [c_void_p] * 5 + [c_int] * 7),
     "dsspk_conv_split_wgrad_scratch_floats": (c_size_t, [c_int] * 7),
+    "dsspk_conv_first_pool_fwd": (c_int, [c_void_p] * 7 + [c_int]),
+    "dsspk_conv_first_scratch_floats": (c_size_t, [c_int]),
+    "dsspk_conv_first_pool_bwd_weight": (c_int, [c_void_p] * 7 + [c_int]),
     "dsspk_conv_split_bwd_weight": (c_int, [c_void_p] * 4 + [c_int, c_void_p] + [c_int] * 7),
     "dsspk_relu_bwd": (c_int, [c_void_p, c_void_p, c_void_p, c_long]),
     "dsspk_add": (c_int, [c_void_p, c_void_p, c_void_p, c_long]),

@@ -199,63 +199,6 @@ __device__ __forceinline__ float sum16(float v) {
 }
 __device__ __forceinline__ float4 sum16(float4 v) { return make_float4(sum16(v.x), sum16(v.y), sum16(v.z), sum16(v.w)); }
 
-// One matrix-core operand of fp32 values.  32 reduction channels: the three planes, a lane's eight channels each.
-// 16 reduction channels (C = 16): an instruction's 32 indices take two planes of them, a lane's four channels each, and
-// three instructions instead of six do the six products: (y2, y0) . (x0, x2), (y0, y1) . (x1, x0), (y0, y1) . (x0, x1).
-template <int C> struct Filt { uint4 v[C == 16 ? 2 : 3]; };
-template <int C> struct Pix { uint4 v[3]; };
-
-template <int C> __device__ __forceinline__ Filt<C> filter_operand(const float4 (&r)[C == 16 ? 1 : 2]) {
-    Filt<C> f;
-    uint2 lo[split::PLANES];
-    split::split4(r[0], lo);
-    if constexpr (C == 16) {
-        f.v[0] = make_uint4(lo[2].x, lo[2].y, lo[0].x, lo[0].y);
-        f.v[1] = make_uint4(lo[0].x, lo[0].y, lo[1].x, lo[1].y);
-    } else {
-        uint2 hi[split::PLANES];
-        split::split4(r[1], hi);
-#pragma unroll
-        for (int p = 0; p < split::PLANES; ++p) f.v[p] = make_uint4(lo[p].x, lo[p].y, hi[p].x, hi[p].y);
-    }
-    return f;
-}
-
-template <int C, int PLANE> __device__ __forceinline__ Pix<C> pixel_operand(const char* at) {
-    Pix<C> x;
-    if constexpr (C == 16) {
-        const uint2 x0 = *reinterpret_cast<const uint2*>(at), x1 = *reinterpret_cast<const uint2*>(at + PLANE),
-                    x2 = *reinterpret_cast<const uint2*>(at + 2 * PLANE);
-        x.v[0] = make_uint4(x0.x, x0.y, x2.x, x2.y);
-        x.v[1] = make_uint4(x1.x, x1.y, x0.x, x0.y);
-        x.v[2] = make_uint4(x0.x, x0.y, x1.x, x1.y);
-    } else {
-#pragma unroll
-        for (int p = 0; p < split::PLANES; ++p) x.v[p] = *reinterpret_cast<const uint4*>(at + p * PLANE);
-    }
-    return x;
-}
-
-// the same for the transposing reads of the d-filter step: lane l16 of quarter q receives channel l16 of pixels 8 q ..
-template <int PLANE> __device__ __forceinline__ void transposed_operand(uint4 (&x)[split::PLANES], const char* lo_at, const char* hi_at) {
-#pragma unroll
-    for (int p = 0; p < split::PLANES; ++p) {
-        const uint2 lo = split::read_tr(lo_at + p * PLANE), hi = split::read_tr(hi_at + p * PLANE);
-        x[p] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-    }
-}
-
-template <int C> constexpr int products() { return C == 16 ? 3 : 6; }
-// product p of the sum, small ones first
-template <int C> __device__ __forceinline__ floatx4 product(int p, const Filt<C>& f, const Pix<C>& x, floatx4 acc) {
-    if constexpr (C == 16) {
-        return split::mfma(f.v[p ? 1 : 0], x.v[p], acc);
-    } else {
-        constexpr int PF[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
-        return split::mfma(f.v[PF[p]], x.v[PX[p]], acc);
-    }
-}
-
 template <int C, int HW, int R, int NSPLIT, bool TRANSPOSED, int PRE, bool POST = false, bool WG = false>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_waves<C, WG>()))) void conv3x3_kernel(const float* __restrict__ src, const float* __restrict__ wgt,
                                                           const float* add, float* dst,
@@ -278,11 +221,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
     const int wave_n = wave % K::WAVES_N, wave_m = wave / K::WAVES_N;
     constexpr int BANDS = HW / R;
     const int tile = xcd_tile(blockIdx.x, conv_blocks);
-    const int split = tile % NSPLIT;
+    const int part = tile % NSPLIT;
     const int band = (tile / NSPLIT) % BANDS;
     const int n = tile / (NSPLIT * BANDS);
     const int r_base = band * R;                    // first output row of the band
-    const int co_w = split * K::CN + 16 * wave_n;   // first output channel of this wavefront
+    const int co_w = part * K::CN + 16 * wave_n;   // first output channel of this wavefront
     const int wpx = wave_m / K::KS, ks = wave_m % K::KS;       // its pixels, its share of the input channels
     const int row0 = wpx / K::TX * 4 * K::TROWS + (K::TROWS == 2 ? l16 >> 3 : 0);      // this lane's pixel in the first tile
     const int col = K::TROWS == 2 ? l16 & 7 : 16 * (wpx % K::TX) + l16;
@@ -328,9 +271,9 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
                 xin[e] = *reinterpret_cast<const float4*>(wg.x_in + (((long)n * HW + h) * HW + w) * C + 4 * v);
         }
     }
-    Filt<C> filt[9];
+    split::Filt<C> filt[9];
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) filt[tap] = filter_operand<C>(fr[tap]);
+    for (int tap = 0; tap < 9; ++tap) filt[tap] = split::filter_operand<C>(fr[tap]);
     if constexpr (PRE == 1 || PRE == 2) {   // mean / invstd of the input, merged from its records by records_merge_kernel
         if (tid < 2 * C) Sh[tid] = pre.stats_out[tid];
         __syncthreads();
@@ -372,7 +315,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
                 o.z = gi.z * (val[e].z - db.z - (scv[e].z - mu.z) * is.z * dg.z);
                 o.w = gi.w * (val[e].w - db.w - (scv[e].w - mu.w) * is.w * dg.w);
                 val[e] = o;
-                if (!WG && split == 0 && pr >= 1 && pr <= R)
+                if (!WG && part == 0 && pr >= 1 && pr <= R)
                     *reinterpret_cast<float4*>(bwd.dx_out + (((long)n * HW + h) * HW + w) * C + 4 * v) = o;
             }
         }
@@ -392,7 +335,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
                 o.x = fmaxf(o.x, 0.f); o.y = fmaxf(o.y, 0.f); o.z = fmaxf(o.z, 0.f); o.w = fmaxf(o.w, 0.f);
                 val[e] = o;
                 // the band's own rows (not the halo rows) are this workgroup's part of `a`
-                if (split == 0 && pr >= 1 && pr <= R)
+                if (part == 0 && pr >= 1 && pr <= R)
                     *reinterpret_cast<float4*>(pre.act_out + (((long)n * HW + h) * HW + w) * C + 4 * v) = o;
             }
         }
@@ -411,21 +354,21 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
         floatx4 a[4], lo[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) a[t] = lo[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-        Pix<C> x[2];
-        x[0] = pixel_operand<C, K::PLANE>(base);
+        split::Pix<C> x[2];
+        x[0] = split::pixel_operand<C, K::PLANE>(base);
 #pragma unroll
         for (int i = 0; i < 3 * ST; ++i) {
             const int st = i / 3, kx = i % 3;
-            if (i + 1 < 3 * ST) x[(i + 1) & 1] = pixel_operand<C, K::PLANE>(base + ((i + 1) / 3 * K::TW + (i + 1) % 3) * K::PITCH);
+            if (i + 1 < 3 * ST) x[(i + 1) & 1] = split::pixel_operand<C, K::PLANE>(base + ((i + 1) / 3 * K::TW + (i + 1) % 3) * K::PITCH);
             __builtin_amdgcn_sched_barrier(0);      // or the compiler moves the reads down to their use, behind the products
 #pragma unroll
-            for (int p = 0; p < products<C>(); ++p)
+            for (int p = 0; p < split::products<C>(); ++p)
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int ky = st - K::TROWS * t;
                     if (ky < 0 || ky > 2) continue;
-                    floatx4& to = p + 1 < products<C>() ? lo[t] : a[t];
-                    to = product<C>(p, filt[3 * ky + kx], x[i & 1], to);
+                    floatx4& to = p + 1 < split::products<C>() ? lo[t] : a[t];
+                    to = split::product<C>(p, filt[3 * ky + kx], x[i & 1], to);
                 }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -506,10 +449,10 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
 #pragma unroll
         for (int t = 0; t < 9; ++t) dw[t] = floatx4{0.f, 0.f, 0.f, 0.f};
         uint4 d[RUNS][split::PLANES], x[2][split::PLANES];
-        auto load_d = [&](int run) { transposed_operand<K::PLANE>(d[run], da[0] + run * RROWS * K::TW * K::PITCH, da[1] + run * RROWS * K::TW * K::PITCH); };
+        auto load_d = [&](int run) { split::transposed_operand<K::PLANE>(d[run], da[0] + run * RROWS * K::TW * K::PITCH, da[1] + run * RROWS * K::TW * K::PITCH); };
         auto load_x = [&](int b, int i) {
             const int off = (i / 3 * K::TW + i % 3) * K::PITCH;
-            transposed_operand<K::PLANE>(x[b], xa[0] + off, xa[1] + off);
+            split::transposed_operand<K::PLANE>(x[b], xa[0] + off, xa[1] + off);
         };
         constexpr int ST = RROWS * (RUNS - 1) + 3;
         load_d(0);

@@ -43,12 +43,12 @@ struct Plan {
     std::vector<Tens> tens;
 
     // common tail
-    size_t logits = 0, dlogits = 0, row_loss = 0, colsum_scratch = 0, wg_scratch = 0, wg_scratch2 = 0, bn_scratch = 0, bn_scratch2 = 0, tot_a = 0, tot_b = 0;
+    size_t logits = 0, dlogits = 0, row_loss = 0, wg_scratch = 0, wg_scratch2 = 0, bn_scratch = 0, bn_scratch2 = 0, tot_a = 0, tot_b = 0;
     // MLP
     size_t mlp_a1 = 0, mlp_da1 = 0;
     // AlexNet-style
     size_t ax_a1 = 0, ax_p1 = 0, ax_arg1 = 0, ax_a2 = 0, ax_p2 = 0, ax_arg2 = 0, ax_a3 = 0, ax_a4 = 0;
-    size_t ax_da4 = 0, ax_da3 = 0, ax_dp2 = 0, ax_da2 = 0, ax_dp1 = 0, ax_da1 = 0;
+    size_t ax_da4 = 0, ax_da3 = 0, ax_dp2 = 0, ax_da2 = 0, ax_dp1 = 0;
     size_t ax_c3 = 0, ax_dc3 = 0;     // three-convolution variant: conv3 output (post-ReLU) and its gradient
     struct WideConv { size_t fwd = 0, bwd = 0; } wide2, wide3;      // filter planes of the convolutions behind the first one
     // ResNet
@@ -109,8 +109,8 @@ struct Plan {
             ax_a2 = a.floats(s15); ax_p2 = a.floats(s7); ax_arg2 = a.take(s7);
             ax_a3 = a.floats((size_t)m * 384); ax_a4 = a.floats((size_t)m * 192);
             ax_da4 = a.floats((size_t)m * 192); ax_da3 = a.floats((size_t)m * 384); ax_dp2 = a.floats(s7);
-            ax_da2 = a.floats(s15); ax_dp1 = a.floats(s15); ax_da1 = a.floats(s32);
-            wg_need(m, 32, 3, 64, 5, 1, 2);
+            ax_da2 = a.floats(s15); ax_dp1 = a.floats(s15);
+            wg = std::max(wg, dsspk_conv_first_scratch_floats(m));
             wide_conv(wide2, 15, 5, 2);
             tens.push_back({0, ax_a1, (int64_t)s32}); tens.push_back({0, ax_a2, (int64_t)s15});
             tens.push_back({0, ax_a3, (int64_t)m * 384}); tens.push_back({0, ax_a4, (int64_t)m * 192});
@@ -126,8 +126,8 @@ struct Plan {
             ax_a2 = a.floats(s15); ax_p2 = a.floats(s7); ax_arg2 = a.take(s7);
             ax_c3 = a.floats(s7c); ax_a3 = a.floats((size_t)m * 384);
             ax_da3 = a.floats((size_t)m * 384); ax_dc3 = a.floats(s7c); ax_dp2 = a.floats(s7);
-            ax_da2 = a.floats(s15); ax_dp1 = a.floats(s15); ax_da1 = a.floats(s32);
-            wg_need(m, 32, 3, 64, 5, 1, 2);
+            ax_da2 = a.floats(s15); ax_dp1 = a.floats(s15);
+            wg = std::max(wg, dsspk_conv_first_scratch_floats(m));
             wide_conv(wide2, 15, 5, 2);
             wide_conv(wide3, 7, 3, 1);
             tens.push_back({0, ax_a1, (int64_t)s32}); tens.push_back({0, ax_a2, (int64_t)s15});
@@ -171,11 +171,6 @@ struct Plan {
         dlogits = a.floats((size_t)m * classes);
         tens.push_back({2, logits, (int64_t)m * classes});
         row_loss = a.floats((size_t)m);
-        {
-            size_t cs = 1;
-            if (id == DSSP_MODEL_ALEXNET_DS || id == DSSP_MODEL_ALEXNET_3C) cs = dsspk_colsum_scratch_floats((long)m * 32 * 32, 64) + 1;
-            colsum_scratch = a.floats(cs);
-        }
         wg_scratch = a.floats(wg ? wg : 1);
         wg_scratch2 = a.floats(is_resnet(id) && wg ? wg : 1);   // d-filter partial sums alternate between the two
         bn_scratch = a.floats(bn ? bn : 1);
@@ -228,12 +223,11 @@ int step_alexnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, c
     float *a1 = F(P->ax_a1), *p1 = F(P->ax_p1), *a2 = F(P->ax_a2), *p2 = F(P->ax_p2), *a3 = F(P->ax_a3), *a4 = F(P->ax_a4);
     uint8_t *arg1 = (uint8_t*)(ws + P->ax_arg1), *arg2 = (uint8_t*)(ws + P->ax_arg2);
     float *da4 = F(P->ax_da4), *da3 = F(P->ax_da3), *dp2 = F(P->ax_dp2);
-    float *da2 = F(P->ax_da2), *dp1 = F(P->ax_dp1), *da1 = F(P->ax_da1), *scr = F(P->wg_scratch);
+    float *da2 = F(P->ax_da2), *dp1 = F(P->ax_dp1), *scr = F(P->wg_scratch);
     const int64_t cw1 = 0, cb1 = 4800, cw2 = cb1 + 64, cb2 = cw2 + 102400, fw1 = cb2 + 64, fb1 = fw1 + 3136 * 384,
                   fw2 = fb1 + 384, fb2 = fw2 + 384 * 192, fw3 = fb2 + 192, fb3 = fw3 + 192 * (int64_t)C;
     // forward
-    RUN(dsspk_conv_fwd(s, x, w + cw1, w + cb1, a1, m, 32, 32, 3, 64, 5, 5, 1, 2, 1, nullptr));
-    RUN(dsspk_maxpool_fwd(s, a1, p1, arg1, m, 32, 32, 64));
+    RUN(dsspk_conv_first_pool_fwd(s, x, w + cw1, w + cb1, a1, p1, arg1, m));
     RUN(dsspk_conv_split_filters(s, w + cw2, ws + P->wide2.fwd, ws + P->wide2.bwd, 64, 64, 5));
     RUN(dsspk_conv_split_fwd(s, p1, ws + P->wide2.fwd, w + cb2, a2, m, 15, 15, 64, 64, 5, 2, 1));
     RUN(dsspk_maxpool_fwd(s, a2, p2, arg2, m, 15, 15, 64));
@@ -246,9 +240,7 @@ int step_alexnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, c
     RUN(dsspk_maxpool_bwd_relu(s, dp2, arg2, a2, da2, m, 15, 15, 64));
     RUN(dsspk_conv_split_bwd_weight(s, p1, da2, g + cw2, 1, scr, m, 15, 15, 64, 64, 5, 2));      // and the biases behind the filter
     RUN(dsspk_conv_split_bwd_data(s, da2, ws + P->wide2.bwd, nullptr, dp1, m, 15, 15, 64, 64, 5, 2));
-    RUN(dsspk_maxpool_bwd_relu(s, dp1, arg1, a1, da1, m, 32, 32, 64));
-    RUN(dsspk_conv_bwd_weight(s, x, da1, g + cw1, scr, m, 32, 32, 3, 64, 5, 5, 1, 2));
-    RUN(dsspk_colsum(s, da1, g + cb1, F(P->colsum_scratch), (long)m * 32 * 32, 64));
+    RUN(dsspk_conv_first_pool_bwd_weight(s, x, dp1, p1, arg1, g + cw1, scr, m));      // and the biases behind the filter
     return 0;
 }
 
@@ -260,12 +252,11 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
     float *a1 = F(P->ax_a1), *p1 = F(P->ax_p1), *a2 = F(P->ax_a2), *p2 = F(P->ax_p2), *c3 = F(P->ax_c3), *a3 = F(P->ax_a3);
     uint8_t *arg1 = (uint8_t*)(ws + P->ax_arg1), *arg2 = (uint8_t*)(ws + P->ax_arg2);
     float *da3 = F(P->ax_da3), *dc3 = F(P->ax_dc3), *dp2 = F(P->ax_dp2);
-    float *da2 = F(P->ax_da2), *dp1 = F(P->ax_dp1), *da1 = F(P->ax_da1), *scr = F(P->wg_scratch), *cscr = F(P->colsum_scratch);
+    float *da2 = F(P->ax_da2), *dp1 = F(P->ax_dp1), *scr = F(P->wg_scratch);
     const int64_t cw1 = 0, cb1 = 4800, cw2 = cb1 + 64, cb2 = cw2 + 102400, cw3 = cb2 + 64, cb3 = cw3 + 36864,
                   fw1 = cb3 + 64, fb1 = fw1 + 3136 * 384, fw2 = fb1 + 384, fb2 = fw2 + 384 * (int64_t)C;
     // forward
-    RUN(dsspk_conv_fwd(s, x, w + cw1, w + cb1, a1, m, 32, 32, 3, 64, 5, 5, 1, 2, 1, nullptr));
-    RUN(dsspk_maxpool_fwd(s, a1, p1, arg1, m, 32, 32, 64));
+    RUN(dsspk_conv_first_pool_fwd(s, x, w + cw1, w + cb1, a1, p1, arg1, m));
     RUN(dsspk_conv_split_filters(s, w + cw2, ws + P->wide2.fwd, ws + P->wide2.bwd, 64, 64, 5));
     RUN(dsspk_conv_split_fwd(s, p1, ws + P->wide2.fwd, w + cb2, a2, m, 15, 15, 64, 64, 5, 2, 1));
     RUN(dsspk_maxpool_fwd(s, a2, p2, arg2, m, 15, 15, 64));
@@ -280,9 +271,7 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
     RUN(dsspk_maxpool_bwd_relu(s, dp2, arg2, a2, da2, m, 15, 15, 64));
     RUN(dsspk_conv_split_bwd_weight(s, p1, da2, g + cw2, 1, scr, m, 15, 15, 64, 64, 5, 2));      // and the biases behind the filter
     RUN(dsspk_conv_split_bwd_data(s, da2, ws + P->wide2.bwd, nullptr, dp1, m, 15, 15, 64, 64, 5, 2));
-    RUN(dsspk_maxpool_bwd_relu(s, dp1, arg1, a1, da1, m, 32, 32, 64));
-    RUN(dsspk_conv_bwd_weight(s, x, da1, g + cw1, scr, m, 32, 32, 3, 64, 5, 5, 1, 2));
-    RUN(dsspk_colsum(s, da1, g + cb1, cscr, (long)m * 32 * 32, 64));
+    RUN(dsspk_conv_first_pool_bwd_weight(s, x, dp1, p1, arg1, g + cw1, scr, m));      // and the biases behind the filter
     return 0;
 }
 

@@ -69,17 +69,75 @@ __device__ __forceinline__ uint2 read_tr(const char* lds) {
     return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t*)lds));
 }
 
+// One matrix-core operand of fp32 values.  32 reduction channels: the three planes, a lane's eight channels each.
+// 16 reduction channels (C = 16): an instruction's 32 indices take two planes of them, a lane's four channels each, and
+// three instructions instead of six do the six products: (y2, y0) . (x0, x2), (y0, y1) . (x1, x0), (y0, y1) . (x0, x1).
+template <int C> struct Filt { uint4 v[C == 16 ? 2 : 3]; };
+template <int C> struct Pix { uint4 v[3]; };
+
+template <int C> __device__ __forceinline__ Filt<C> filter_operand(const float4 (&r)[C == 16 ? 1 : 2]) {
+    Filt<C> f;
+    uint2 lo[PLANES];
+    split4(r[0], lo);
+    if constexpr (C == 16) {
+        f.v[0] = make_uint4(lo[2].x, lo[2].y, lo[0].x, lo[0].y);
+        f.v[1] = make_uint4(lo[0].x, lo[0].y, lo[1].x, lo[1].y);
+    } else {
+        uint2 hi[PLANES];
+        split4(r[1], hi);
+#pragma unroll
+        for (int p = 0; p < PLANES; ++p) f.v[p] = make_uint4(lo[p].x, lo[p].y, hi[p].x, hi[p].y);
+    }
+    return f;
+}
+
+template <int C, int PLANE> __device__ __forceinline__ Pix<C> pixel_operand(const char* at) {
+    Pix<C> x;
+    if constexpr (C == 16) {
+        const uint2 x0 = *reinterpret_cast<const uint2*>(at), x1 = *reinterpret_cast<const uint2*>(at + PLANE),
+                    x2 = *reinterpret_cast<const uint2*>(at + 2 * PLANE);
+        x.v[0] = make_uint4(x0.x, x0.y, x2.x, x2.y);
+        x.v[1] = make_uint4(x1.x, x1.y, x0.x, x0.y);
+        x.v[2] = make_uint4(x0.x, x0.y, x1.x, x1.y);
+    } else {
+#pragma unroll
+        for (int p = 0; p < PLANES; ++p) x.v[p] = *reinterpret_cast<const uint4*>(at + p * PLANE);
+    }
+    return x;
+}
+
+// the same for the transposing reads of the d-filter step: lane l16 of quarter q receives channel l16 of pixels 8 q ..
+template <int PLANE> __device__ __forceinline__ void transposed_operand(uint4 (&x)[PLANES], const char* lo_at, const char* hi_at) {
+#pragma unroll
+    for (int p = 0; p < PLANES; ++p) {
+        const uint2 lo = read_tr(lo_at + p * PLANE), hi = read_tr(hi_at + p * PLANE);
+        x[p] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    }
+}
+
+template <int C> constexpr int products() { return C == 16 ? 3 : 6; }
+// product p of the sum, small ones first
+template <int C> __device__ __forceinline__ floatx4 product(int p, const Filt<C>& f, const Pix<C>& x, floatx4 acc) {
+    if constexpr (C == 16) {
+        return mfma(f.v[p ? 1 : 0], x.v[p], acc);
+    } else {
+        constexpr int PF[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
+        return mfma(f.v[PF[p]], x.v[PX[p]], acc);
+    }
+}
+
 // Buffer loads check their offset against the buffer's size and return zero beyond it: zero padding without a branch and
 // without a select.  Offsets are unsigned bytes below 2^32; OUTSIDE lies beyond any buffer of less than 2^31 bytes, also after
 // another such offset is added to it.
 constexpr unsigned OUTSIDE = 0x80000000u;
 typedef __amdgpu_buffer_rsrc_t Buffer;
-__device__ __forceinline__ Buffer buffer(const float* p, unsigned bytes) {
+__device__ __forceinline__ Buffer buffer(const void* p, unsigned bytes) {
     constexpr int RAW_DWORDS = 0x00027000;          // untyped 32-bit data, no swizzle
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)bytes, RAW_DWORDS);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, RAW_DWORDS);
 }
 __device__ __forceinline__ float4 load4(Buffer b, unsigned offset) {
     return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)offset, 0, 0));
 }
+__device__ __forceinline__ unsigned load1(Buffer b, unsigned offset) { return __builtin_amdgcn_raw_buffer_load_b32(b, (int)offset, 0, 0); }
 
 }  // namespace split

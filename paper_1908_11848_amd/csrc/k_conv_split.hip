@@ -61,34 +61,39 @@ __global__ __launch_bounds__(THREADS) void filter_planes_kernel(Frag fwd, Frag b
 // images.  The input tile with its halo goes to LDS once, already split into its three planes (every element is converted
 // once, not once per tap), and serves all taps from there; a pixel's 32 channels of one plane are a 16-byte read per lane.
 // The filter planes come straight from L2 into registers, two steps ahead.  The matrix-core tile is 16 channels (rows) x
-// 16 pixels (columns), so a lane ends up with four consecutive channels of a pixel.
-// Bound by the matrix cores: 64 -> 64 at 5x5 on 15x15, batch 128, is 2.46 M MFMAs = 20 us of them.
+// 16 pixels (columns), so a lane ends up with four consecutive channels of a pixel.  Four wavefronts share out the tile.  The
+// largest tile, one workgroup to a compute unit, has eight, two to a SIMD, so that one multiplies while the other fetches: the
+// other four do the same with the other half of the staged reduction channels (the traffic per product stays that of the large
+// tile), and the two halves of a sum meet in LDS at the end.  The smaller tiles gain nothing from that: several of their
+// workgroups share a compute unit, and with more than one stream eight wavefronts cost 4 % of a step at batch 37.
+// Bound by the matrix cores: 64 -> 64 at 5x5 on 15x15, batch 128, is 2.46 M MFMAs = 17 us of them at 2.4 GHz (the chip runs
+// them at 1.9).  Measured at batch 37 / 128 / 512: 19 / 33 / 140 us (largest tile with four wavefronts: 38 / 150 us).
 struct Geom {
     int N, H, W, OH, OW, pad;      // input / output pixel grid of this pass
     int IC, OC;                    // reduction / result channels of this pass
     int R, G, bands;               // output rows per tile, images per tile (G > 1: whole images), tiles per image
 };
 
-// MT pixel tiles per workgroup; wavefronts: WP over the pixels, 4 / WP over the 4 channel tiles
-template <int MT> struct Waves { static constexpr int WP = MT >= 4 ? 2 : 1, WC = 4 / WP, TP = MT / WP, TC = 4 / WC; };
+// MT pixel tiles per workgroup; four wavefronts: WP over the pixels, 4 / WP over the 4 channel tiles; HALVES such groups
+template <int MT> struct Waves { static constexpr int WP = MT >= 4 ? 2 : 1, WC = 4 / WP, TP = MT / WP, TC = 4 / WC, HALVES = MT == 8 ? 2 : 1; };
 
 constexpr int ICB = 64;            // reduction channels staged at a time
 constexpr int pitch(int channels) { return channels * 2 * split::PLANES + 16; }      // bytes of a pixel in LDS: 4 words (mod 32) apart
 
 template <int MT, int KS>
-__global__ __launch_bounds__(THREADS) void conv_split_kernel(const float* __restrict__ src, const uint4* __restrict__ wf,
+__global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_waves_per_eu(2))) void conv_split_kernel(const float* __restrict__ src, const uint4* __restrict__ wf,
                                                              const float* __restrict__ bias, const float* __restrict__ add,
                                                              float* __restrict__ dst, Geom g, int relu) {
     using W = Waves<MT>;
-    constexpr int PITCH = pitch(ICB), PLANE = 2 * ICB, CS = ICB / 32;      // CS: steps per tap and block of channels
-    constexpr int STEPS = KS * KS * CS, WD = MT == 2 ? 8 : 4;
+    constexpr int PITCH = pitch(ICB), PLANE = 2 * ICB, CS = ICB / 32 / W::HALVES;      // CS: steps per tap and block of channels
+    constexpr int STEPS = KS * KS * CS, WD = MT == 2 ? 8 : MT == 4 ? 4 : 2, NT = THREADS * W::HALVES;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l16 = lane & 15, q = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, q = lane >> 4, half = W::HALVES == 2 ? wave >> 2 : 0;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int n0 = tile / g.bands * g.G, r0 = tile % g.bands * g.R;
     const int TH = g.R + KS - 1, TW = g.OW + KS - 1;
-    const int wp = wave % W::WP, wc = wave / W::WP;
+    const int wp = (wave & 3) % W::WP, wc = (wave & 3) / W::WP;
     const int ct0 = blockIdx.y * 4 + wc * W::TC;           // first 16-channel tile of this wavefront
 
     // this lane's pixels: where their patch starts in LDS, and where they go
@@ -99,7 +104,7 @@ __global__ __launch_bounds__(THREADS) void conv_split_kernel(const float* __rest
         const int p = (wp * W::TP + t) * 16 + l16;
         const int per = g.R * g.OW, gi = p / per, rest = p - gi * per, r = rest / g.OW, c = rest - r * g.OW;
         const bool ok = gi < g.G && n0 + gi < g.N && r0 + r < g.OH;
-        base[t] = ok ? ((gi * TH + r) * TW + c) * PITCH + 16 * q : 16 * q;
+        base[t] = (ok ? ((gi * TH + r) * TW + c) * PITCH : 0) + 16 * q + 64 * half;
         out[t] = ok ? (((long)(n0 + gi) * g.OH + r0 + r) * g.OW + c) * g.OC : -1;
     }
     floatx4 acc[W::TC][W::TP];
@@ -112,14 +117,27 @@ __global__ __launch_bounds__(THREADS) void conv_split_kernel(const float* __rest
     const split::Buffer images = split::buffer(src + (long)n0 * g.H * g.W * g.IC, 4u * (unsigned)(min(g.G, g.N - n0) * g.H * g.W * g.IC));
     for (int c0 = 0; c0 < g.IC; c0 += ICB) {
         if (c0) __syncthreads();
+        // Filter planes are fetched WD steps before their use (they come from L2: one step, 0.3 us, does not cover that),
+        // pixel operands one step.
+        uint4 wv[WD][W::TC][split::PLANES];
+        auto load_w = [&](int buf, int s) {
+            s = s < STEPS ? s : STEPS - 1;
+            const uint4* p = wf + ((s / CS * steps_c + c0 / 32 + half + s % CS) * tiles_c + ct0) * (split::PLANES * 64) + lane;
+#pragma unroll
+            for (int i = 0; i < W::TC; ++i)
+#pragma unroll
+                for (int k = 0; k < split::PLANES; ++k) wv[buf][i][k] = p[(i * split::PLANES + k) * 64];
+        };
+#pragma unroll
+        for (int u = 0; u < WD; ++u) load_w(u, u);
         // LOADS 16-byte loads in flight per thread (one at a time, their latencies add up to half the kernel)
         constexpr int LOADS = 8;
         const int total = g.G * TH * TW * (ICB / 4);
-        for (int i0 = tid; i0 < total; i0 += LOADS * THREADS) {
+        for (int i0 = tid; i0 < total; i0 += LOADS * NT) {
             float4 v[LOADS];
 #pragma unroll
             for (int e = 0; e < LOADS; ++e) {
-                const int idx = i0 + e * THREADS, px = idx / (ICB / 4), c4 = idx % (ICB / 4);
+                const int idx = i0 + e * NT, px = idx / (ICB / 4), c4 = idx % (ICB / 4);
                 const int gi = px / (TH * TW), rest = px - gi * (TH * TW), ty = rest / TW, tx = rest - ty * TW;
                 const int h = r0 + ty - g.pad, w = tx - g.pad;
                 const bool in = idx < total && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;      // images past the last: beyond the buffer
@@ -127,7 +145,7 @@ __global__ __launch_bounds__(THREADS) void conv_split_kernel(const float* __rest
             }
 #pragma unroll
             for (int e = 0; e < LOADS; ++e) {
-                const int idx = i0 + e * THREADS;
+                const int idx = i0 + e * NT;
                 if (idx >= total) break;
                 uint2 pl[split::PLANES];
                 split::split4(v[e], pl);
@@ -136,17 +154,7 @@ __global__ __launch_bounds__(THREADS) void conv_split_kernel(const float* __rest
                     *reinterpret_cast<uint2*>(lds + idx / (ICB / 4) * PITCH + p * PLANE + 8 * (idx % (ICB / 4))) = pl[p];
             }
         }
-        // Filter planes are fetched WD steps before their use (they come from L2: one step, 0.3 us, does not cover that),
-        // pixel operands one step.
-        uint4 wv[WD][W::TC][split::PLANES], pv[2][W::TP][split::PLANES];
-        auto load_w = [&](int buf, int s) {
-            s = s < STEPS ? s : STEPS - 1;
-            const uint4* p = wf + ((((long)(s / CS) * steps_c + c0 / 32 + s % CS) * tiles_c + ct0) * split::PLANES) * 64 + lane;
-#pragma unroll
-            for (int i = 0; i < W::TC; ++i)
-#pragma unroll
-                for (int k = 0; k < split::PLANES; ++k) wv[buf][i][k] = p[(i * split::PLANES + k) * 64];
-        };
+        uint4 pv[2][W::TP][split::PLANES];
         auto load_p = [&](int buf, int s) {
             s = s < STEPS ? s : STEPS - 1;
             const int tap = s / CS, off = (tap / KS * TW + tap % KS) * PITCH + s % CS * 64;
@@ -155,8 +163,6 @@ __global__ __launch_bounds__(THREADS) void conv_split_kernel(const float* __rest
 #pragma unroll
                 for (int k = 0; k < split::PLANES; ++k) pv[buf][t][k] = *reinterpret_cast<const uint4*>(lds + base[t] + off + k * PLANE);
         };
-#pragma unroll
-        for (int u = 0; u < WD; ++u) load_w(u, u);
         __syncthreads();
         load_p(0, 0);
         for (int s = 0; s < STEPS; s += WD) {
@@ -172,21 +178,36 @@ __global__ __launch_bounds__(THREADS) void conv_split_kernel(const float* __rest
         }
     }
 
-#pragma unroll
-    for (int i = 0; i < W::TC; ++i) {
-        const int co = 16 * (ct0 + i) + 4 * q;
+    auto finish = [&](const floatx4& sum, int ct, long at) {
+        if (at < 0) return;
+        const int co = 16 * ct + 4 * q;
         const float4 b = bias ? *reinterpret_cast<const float4*>(bias + co) : make_float4(0.f, 0.f, 0.f, 0.f);
+        float4 v = make_float4(sum[0] + b.x, sum[1] + b.y, sum[2] + b.z, sum[3] + b.w);
+        if (add) {
+            const float4 a = *reinterpret_cast<const float4*>(add + at + co);
+            v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+        }
+        if (relu) { v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f); v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f); }
+        *reinterpret_cast<float4*>(dst + at + co) = v;
+    };
+    if constexpr (W::HALVES == 1) {
+#pragma unroll
+        for (int i = 0; i < W::TC; ++i)
+#pragma unroll
+            for (int t = 0; t < W::TP; ++t) finish(acc[i][t], ct0 + i, out[t]);
+    } else {        // the other half's share of the channel tile this wavefront finishes, against its own share of the other one
+        static_assert(W::HALVES == 1 || W::TC == 2, "a channel tile each");
+        __syncthreads();
+        floatx4* ex = reinterpret_cast<floatx4*>(lds);             // [wavefront][TP][64]
 #pragma unroll
         for (int t = 0; t < W::TP; ++t) {
-            if (out[t] < 0) continue;
-            float4 v = make_float4(acc[i][t][0] + b.x, acc[i][t][1] + b.y, acc[i][t][2] + b.z, acc[i][t][3] + b.w);
-            if (add) {
-                const float4 a = *reinterpret_cast<const float4*>(add + out[t] + co);
-                v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
-            }
-            if (relu) { v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f); v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f); }
-            *reinterpret_cast<float4*>(dst + out[t] + co) = v;
+            const floatx4 u = acc[0][t], v = acc[W::TC - 1][t];
+            ex[(wave * W::TP + t) * 64 + lane] = half ? u : v;
+            acc[0][t] = half ? v : u;
         }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < W::TP; ++t) finish(acc[0][t] + ex[((wave ^ 4) * W::TP + t) * 64 + lane], ct0 + half, out[t]);
     }
 }
 
@@ -206,6 +227,7 @@ bool tiling_for(Tiling& t, int mt, int N, int OH, int OW, int ks) {
     if (t.G > N) t.G = N;
     while (t.G > 1 && tile_bytes(t.G, t.R, OW, ks) > LDS_MAX) --t.G;
     t.lds = tile_bytes(t.G, t.R, OW, ks);
+    if (mt == 8 && t.lds < 32 * 1024) t.lds = 32 * 1024;  // exchange of sums: four matrix-core tiles of each of the eight wavefronts
     t.blocks = ceil_div(N, t.G) * t.bands;
     return t.lds <= LDS_MAX;
 }
@@ -231,7 +253,7 @@ int launch_tile(hipStream_t s, const float* src, const uint4* wf, const float* b
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX) != hipSuccess) return -1;
         attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3(t.blocks, g.OC / 64), dim3(THREADS), t.lds, s, src, wf, bias, add, dst, g, relu);
+    hipLaunchKernelGGL(kern, dim3(t.blocks, g.OC / 64), dim3(THREADS * Waves<MT>::HALVES), t.lds, s, src, wf, bias, add, dst, g, relu);
     return DSSPK_LAUNCH_RC();
 }
 
@@ -252,35 +274,37 @@ int launch_conv(hipStream_t s, const float* src, const uint4* wf, const float* b
 // and the dy rows go to LDS as planes, and dw[kh][kw][ci][co] += x[pixel + kw][ci] dy[pixel][co] is accumulated for all KS
 // taps of the row with the pixels as reduction index, 32 to an MFMA.  Both operands need a lane's pixels side by side while
 // LDS has the channels side by side: the transposing LDS reads turn them.  The next tile's loads are in flight while the
-// matrix cores work.  Wavefront w: input channels 16 (w mod 2) .., output channels 32 (w / 2) ..
+// matrix cores work.  Wavefront w: input channels 16 (w mod 2) .., output channels 32 (w / 2 mod 2) .., the first or second 32
+// pixels of the tile (w / 4: two wavefronts to a SIMD, one multiplies while the other fetches); their sums meet in LDS at the end.
+// Measured with the reduction at batch 37 / 128 / 512: 23 / 51 / 146 us (four wavefronts, reads behind the barrier: 24 / 53 / 159).
 // Output: partial[chunk][KS KS IC OC (+ OC bias sums, added up by the workgroups of filter row 0 and the first channels)].
-constexpr int WG_PX = 64, WG_XPX = 96;
+constexpr int WG_PX = 64, WG_XPX = 96, CTHREADS = 512;
 constexpr int XPITCH = 32 * 6 + 32, DPITCH = 64 * 6 + 32;      // 24 and 8 words (mod 32): four rows cover all banks once
 
 template <int KS>
-__global__ __launch_bounds__(THREADS) void wgrad_split_kernel(const float* __restrict__ x, const float* __restrict__ dy,
+__global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void wgrad_split_kernel(const float* __restrict__ x, const float* __restrict__ dy,
                                                               float* __restrict__ partial, Geom g, int items_per_chunk, int with_bias) {
-    constexpr int NX = WG_XPX * 8 / THREADS, ND = WG_PX * 16 / THREADS;      // 16-byte loads per thread and tile
+    constexpr int NX = (WG_XPX * 8 + CTHREADS - 1) / CTHREADS, ND = WG_PX * 16 / CTHREADS;      // 16-byte loads per thread and tile
+    static_assert(WG_PX == 64 && WG_PX * 16 % CTHREADS == 0, "one run of 32 pixels per wavefront");
     constexpr int XBYTES = WG_XPX * XPITCH, BUF = XBYTES + WG_PX * DPITCH;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l16 = lane & 15, q = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, q = lane >> 4, run = wave >> 2;
+    const int ci_w = 16 * (wave & 1), co_w = 32 * (wave >> 1 & 1);         // this wavefront's first channels within the workgroup's
     const int kh = blockIdx.y % KS, ci0 = blockIdx.y / KS * 32, co0 = blockIdx.z * 64;
     const int TW = g.OW + KS - 1, P = g.R * g.OW;
     const int items = g.N * g.bands, i0 = blockIdx.x * items_per_chunk, i1 = min(items, i0 + items_per_chunk);
     const bool bias_role = with_bias && blockIdx.y == 0;
 
-    // transposing reads: this lane names row 8 q + l16 / 4 (and the one four further) of each run of 32 pixels
-    int xa[WG_PX / 32][2], da[WG_PX / 32][2];
+    // transposing reads: this lane names row 8 q + l16 / 4 (and the one four further) of its run of 32 pixels
+    int xa[2], da[2];
 #pragma unroll
-    for (int k = 0; k < WG_PX / 32; ++k)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int p = 32 * k + 8 * q + 4 * h + (l16 >> 2);
-            const int r = p / g.OW, c = p - r * g.OW;
-            xa[k][h] = (p < P ? (r * TW + c) * XPITCH : 0) + 8 * (l16 & 3) + 32 * (wave & 1);      // beyond P dy is zero
-            da[k][h] = p * DPITCH + 8 * (l16 & 3) + 64 * (wave >> 1);
-        }
+    for (int h = 0; h < 2; ++h) {
+        const int p = 32 * run + 8 * q + 4 * h + (l16 >> 2);
+        const int r = p / g.OW, c = p - r * g.OW;
+        xa[h] = (p < P ? (r * TW + c) * XPITCH : 0) + 8 * (l16 & 3) + 2 * ci_w;      // beyond P dy is zero
+        da[h] = p * DPITCH + 8 * (l16 & 3) + 2 * co_w;
+    }
     floatx4 acc[KS][2][1];
 #pragma unroll
     for (int k = 0; k < KS; ++k)
@@ -297,9 +321,9 @@ __global__ __launch_bounds__(THREADS) void wgrad_split_kernel(const float* __res
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
         const bool is_x = e < NX;
-        const int idx = tid + (is_x ? e : e - NX) * THREADS, px = is_x ? idx >> 3 : idx >> 4, c4 = is_x ? idx & 7 : idx & 15;
+        const int idx = tid + (is_x ? e : e - NX) * CTHREADS, px = is_x ? idx >> 3 : idx >> 4, c4 = is_x ? idx & 7 : idx & 15;
         const int width = is_x ? TW : g.OW, r = px / width, c = px - r * width - (is_x ? g.pad : 0);
-        const bool in = is_x ? r < g.R && c >= 0 && c < g.W : px < P;
+        const bool in = is_x ? px < WG_XPX && r < g.R && c >= 0 && c < g.W : px < P;
         off[e] = !in ? split::OUTSIDE : is_x ? 4u * (unsigned)(((r + kh - g.pad) * g.W + c) * g.IC + ci0 + 4 * c4)
                                              : 4u * (unsigned)((r * g.OW + c) * g.OC + co0 + 4 * c4);
     }
@@ -326,29 +350,18 @@ __global__ __launch_bounds__(THREADS) void wgrad_split_kernel(const float* __res
         if (e >= NX) { sb.x = fmaf(v.x, count, sb.x); sb.y = fmaf(v.y, count, sb.y); sb.z = fmaf(v.z, count, sb.z); sb.w = fmaf(v.w, count, sb.w); }
         uint2 pl[split::PLANES];
         split::split4(v, pl);
-        const int idx = tid + (e < NX ? e : e - NX) * THREADS;
+        const int idx = tid + (e < NX ? e : e - NX) * CTHREADS;
+        if (e < NX && idx >= WG_XPX * 8) return;
         char* to = e < NX ? buf + (idx >> 3) * XPITCH + 8 * (idx & 7) : buf + XBYTES + (idx >> 4) * DPITCH + 8 * (idx & 15);
 #pragma unroll
         for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(to + p * (e < NX ? 64 : 128)) = pl[p];
     };
-    uint4 dv[2][2][split::PLANES], xv[2][1][split::PLANES];
-    auto load_d = [&](int b, int k, const char* buf) {
+    uint4 dv[2][split::PLANES], dn[2][split::PLANES], xv[2][1][split::PLANES], xn[1][split::PLANES];
+    auto load_d = [&](uint4 (&to)[2][split::PLANES], const char* buf) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int p = 0; p < split::PLANES; ++p) {
-                const uint2 lo = split::read_tr(buf + XBYTES + da[k][0] + 32 * i + 128 * p), hi = split::read_tr(buf + XBYTES + da[k][1] + 32 * i + 128 * p);
-                dv[b][i][p] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-            }
+        for (int i = 0; i < 2; ++i) split::transposed_operand<128>(to[i], buf + XBYTES + da[0] + 32 * i, buf + XBYTES + da[1] + 32 * i);
     };
-    auto load_x = [&](int b, int k, int kw, const char* buf) {
-#pragma unroll
-        for (int p = 0; p < split::PLANES; ++p) {
-            const uint2 lo = split::read_tr(buf + xa[k][0] + kw * XPITCH + 64 * p), hi = split::read_tr(buf + xa[k][1] + kw * XPITCH + 64 * p);
-            xv[b][0][p] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-        }
-    };
-    constexpr int RUNS = WG_PX / 32, STEPS = RUNS * KS;
+    auto load_x = [&](uint4 (&to)[1][split::PLANES], int kw, const char* buf) { split::transposed_operand<64>(to[0], buf + xa[0] + kw * XPITCH, buf + xa[1] + kw * XPITCH); };
     if (i0 < i1) {
         image();
 #pragma unroll
@@ -359,43 +372,62 @@ __global__ __launch_bounds__(THREADS) void wgrad_split_kernel(const float* __res
 #pragma unroll
         for (int e = 0; e < NE; ++e) fetch(e);
         advance();
+        __syncthreads();
+        load_d(dn, lds);
+        load_x(xn, 0, lds);
     }
     for (int item = i0; item < i1; ++item) {
         const char* cur = lds + ((item - i0) & 1) * BUF;
         char* nxt = lds + ((item - i0 + 1) & 1) * BUF;
         const float count = item + 1 < i1 ? 1.f : 0.f;
-        __syncthreads();                                       // this tile is complete, the other buffer is consumed
-        load_d(0, 0, cur);
-        load_x(0, 0, 0, cur);
 #pragma unroll
-        for (int t = 0; t < STEPS; ++t) {                      // (run, tap) steps, operands read one step ahead
-            const int k = t / KS, kw = t % KS;
-            if (t + 1 < STEPS) load_x((t + 1) & 1, (t + 1) / KS, (t + 1) % KS, cur);
-            if (kw == KS - 2 && k + 1 < RUNS) load_d((k + 1) & 1, k + 1, cur);
+        for (int p = 0; p < split::PLANES; ++p) { dv[0][p] = dn[0][p]; dv[1][p] = dn[1][p]; xv[0][0][p] = xn[0][p]; }
+#pragma unroll
+        for (int kw = 0; kw < KS; ++kw) {
+            // Operands are read one step ahead.  In the last step the next tile is complete and this one consumed (its last
+            // operands are in registers): the barrier goes here, so that its wait and the next tile's first reads hide behind products.
+            if (kw + 1 < KS) {
+                load_x(xv[(kw + 1) & 1], kw + 1, cur);
+            } else {
+                __syncthreads();
+                load_d(dn, nxt);
+                load_x(xn, 0, nxt);
+            }
             __builtin_amdgcn_sched_barrier(0);
+            constexpr int SS = KS - 1;                         // steps that stage the next tile
+            if (kw < SS) {
 #pragma unroll
-            for (int e = t * NE / STEPS; e < (t + 1) * NE / STEPS; ++e)
-                stage(e, nxt, count);
-            split::product(dv[k & 1], xv[t & 1], acc[kw]);
+                for (int e = kw * NE / SS; e < (kw + 1) * NE / SS; ++e) stage(e, nxt, count);
+            }
+            split::product(dv, xv[kw & 1], acc[kw]);
 #pragma unroll
             for (int m = 0; m < 12; ++m) {                     // one MFMA, a few vector instructions, ...
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
+            if (kw < SS) {
 #pragma unroll
-            for (int e = t * NE / STEPS; e < (t + 1) * NE / STEPS; ++e) fetch(e);
+                for (int e = kw * NE / SS; e < (kw + 1) * NE / SS; ++e) fetch(e);
+            }
         }
         advance();
     }
     const long E = (long)KS * KS * g.IC * g.OC;
     float* outp = partial + blockIdx.x * (E + (with_bias ? g.OC : 0));
+    // the sums over the other run: this wavefront finishes its output channel tile `run` and gives the other one away
+    static_assert(8 * KS * 1024 <= 2 * BUF, "room for the exchange");
+    __syncthreads();
+    floatx4* ex = reinterpret_cast<floatx4*>(lds);             // [wavefront][tap][64]
 #pragma unroll
-    for (int kw = 0; kw < KS; ++kw)
+    for (int kw = 0; kw < KS; ++kw) ex[(wave * KS + kw) * 64 + lane] = run ? acc[kw][0][0] : acc[kw][1][0];
+    __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            *reinterpret_cast<floatx4*>(outp + ((long)(kh * KS + kw) * g.IC + ci0 + 16 * (wave & 1) + l16) * g.OC + co0 + 32 * (wave >> 1) + 16 * i + 4 * q) =
-                acc[kw][i][0];
+    for (int kw = 0; kw < KS; ++kw) {
+        const floatx4 own = run ? acc[kw][1][0] : acc[kw][0][0];
+        *reinterpret_cast<floatx4*>(outp + ((long)(kh * KS + kw) * g.IC + ci0 + ci_w + l16) * g.OC + co0 + co_w + 16 * run + 4 * q) =
+            own + ex[((wave ^ 4) * KS + kw) * 64 + lane];
+    }
     if (bias_role) {                                           // lanes of one channel group, in order
         __syncthreads();
         float4* red = reinterpret_cast<float4*>(lds);
@@ -403,7 +435,7 @@ __global__ __launch_bounds__(THREADS) void wgrad_split_kernel(const float* __res
         __syncthreads();
         if (tid < 16) {
             float4 s = red[tid];
-            for (int j = 1; j < THREADS / 16; ++j) { const float4 v = red[tid + 16 * j]; s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w; }
+            for (int j = 1; j < CTHREADS / 16; ++j) { const float4 v = red[tid + 16 * j]; s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w; }
             *reinterpret_cast<float4*>(outp + E + co0 + 4 * tid) = s;
         }
     }
@@ -418,7 +450,7 @@ int launch_wgrad(hipStream_t s, dim3 grid, const float* x, const float* dy, floa
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return -1;
         attr_set = true;
     }
-    hipLaunchKernelGGL(kern, grid, dim3(THREADS), bytes, s, x, dy, partial, g, items_per_chunk, with_bias);
+    hipLaunchKernelGGL(kern, grid, dim3(CTHREADS), bytes, s, x, dy, partial, g, items_per_chunk, with_bias);
     return DSSPK_LAUNCH_RC();
 }
 

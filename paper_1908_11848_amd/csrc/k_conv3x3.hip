@@ -5,10 +5,11 @@
 // stage) and CN of the C output channels.  It loads the (R+2) x (HW+2) x C input halo tile
 // (zero borders) into LDS once; everything else is served from LDS, so every input element
 // is read from memory once per band instead of nine times.  The filter never passes through
-// LDS: a wavefront owns ONE tile of 16 output channels and keeps that tile's 9 x C filter
-// values in registers (9 * C / 16 float4 per lane, fetched straight from the cached filter
-// while the halo tile is still in flight).  LDS therefore holds the halo tile only (about
-// 27 KB in every stage), which lets workgroups of several kernels share a compute unit.
+// LDS: a wavefront owns ONE tile of 16 output channels and holds one column of that tile's filter
+// (three taps) in registers, the next one being on its way.  LDS therefore holds the halo tile only (36 to
+// 42 KB), registers stay below 128 (C = 16) or 170, and the workgroups of three or four kernels share a compute
+// unit: one stream's transfers run beside another's products (with the whole filter in registers and two tiles in
+// LDS for the fused d-filter, two: ResNet-110 at batch 128, 8 workers, 2.31 ms per push against 2.15).
 //
 // The arithmetic is fp32 on the bf16 matrix cores (split.hpp): the loader leaves every element in LDS as three bf16 terms
 // (each converted once, not once per tap), the filter values are split in registers while the input is on its way, and six
@@ -126,7 +127,9 @@ struct Cfg {
     static constexpr int SS = 8 * CN;              // floats: per-wavefront column sums (batch-norm records, two components)
     static constexpr int PS = 5 * C;               // floats: per-channel vectors of the loader
     static constexpr size_t LDS_BYTES = XB + (size_t)(SS + PS) * sizeof(float);
-    static constexpr size_t LDS_BYTES_WG = LDS_BYTES + XB;     // + the x halo tile of the fused d-filter
+    // fused d-filter: the x halo tile takes the place of the first one; C = 16: four partial sums at the end
+    static constexpr size_t RED = C == 16 ? 4 * 9 * C * C * sizeof(float) : 0;
+    static constexpr size_t LDS_BYTES_WG = LDS_BYTES > RED ? LDS_BYTES : RED;
     static_assert(WPX * KS == WAVES_M && (KS == 1 || KS == 2) && (C == 16 || C == 32 * KS), "roles of the four wavefronts");
     static_assert(XB % 16 == 0 && KS * 4 * 4 * 64 * 16 / 2 <= XB, "alignment; room for the exchange");
 };
@@ -188,7 +191,7 @@ struct WgradFused {
 // add and dst may be the same buffer (every element is read and written by the same lane); with PRE == 3
 // dst must differ from src, whose halo rows other workgroups still read.
 template <int C, bool WG>
-constexpr int min_waves() { return C == 16 && !WG ? 4 : 2; }
+constexpr int min_waves() { return C == 16 && !WG ? 4 : 3; }
 
 // Sum over the 16 lanes of a quarter wavefront, in all of them.
 __device__ __forceinline__ float sum16(float v) {
@@ -215,7 +218,6 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
     char* Xs = lds;
     float* Ss = reinterpret_cast<float*>(lds + K::XB);          // column sums
     float* Sh = Ss + K::SS;                                     // per-channel vectors of the loader
-    char* Xs2 = lds + K::LDS_BYTES;                             // x halo tile (WG)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, q = lane >> 4;
     const int wave_n = wave % K::WAVES_N, wave_m = wave / K::WAVES_N;
@@ -233,25 +235,31 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
     // ---- filter values of this lane, result channel co_w + l16 (row of the MFMA tile) and reduction channels k0 ..:
     //      forward : w[tap][k][co]           (C floats apart)
     //      d-input : w[8 - tap][co][k]       (16-byte loads, taps reversed)
+    //      One filter column at a time (three taps): the product loop walks the columns, and the next one is on its way while it works
+    //      on the present one.
     constexpr int FV = C == 16 ? 1 : 2;
     const int k0 = C == 16 ? 4 * q : 32 * ks + 8 * q;
-    float4 fr[9][FV];
+    float4 fr[3][FV];
+    auto load_filter = [&](int kx) {
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap)
+        for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
-        for (int e = 0; e < FV; ++e) {
-            if constexpr (TRANSPOSED) {
-                fr[tap][e] = *reinterpret_cast<const float4*>(wgt + ((long)(8 - tap) * C + co_w + l16) * C + k0 + 4 * e);
-            } else {
-                const float* wp = wgt + ((long)tap * C + k0 + 4 * e) * C + co_w + l16;
-                fr[tap][e] = make_float4(wp[0], wp[C], wp[2 * C], wp[3 * C]);
+            for (int e = 0; e < FV; ++e) {
+                const int tap = 3 * ky + kx;
+                if constexpr (TRANSPOSED) {
+                    fr[ky][e] = *reinterpret_cast<const float4*>(wgt + ((long)(8 - tap) * C + co_w + l16) * C + k0 + 4 * e);
+                } else {
+                    const float* wp = wgt + ((long)tap * C + k0 + 4 * e) * C + co_w + l16;
+                    fr[ky][e] = make_float4(wp[0], wp[C], wp[2 * C], wp[3 * C]);
+                }
             }
-        }
-    // ---- input halo tile, zero outside the image.  The raw loads are issued first; the filter is split while they are
-    //      in flight.
+    };
+    load_filter(0);
+    // ---- input halo tile, zero outside the image.  The raw loads are issued first; the first filter column is split while
+    //      they are in flight.
     constexpr int V = C / 4;
     constexpr int NL = ((R + 2) * K::TW * V + THREADS - 1) / THREADS;
-    float4 val[NL], scv[PRE >= 2 ? NL : 1], xin[WG ? NL : 1];
+    float4 val[NL], scv[PRE >= 2 ? NL : 1];
 #pragma unroll
     for (int e = 0; e < NL; ++e) {
         const int idx = tid + e * THREADS;
@@ -265,15 +273,13 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
             if constexpr (PRE == 2) scv[e] = *reinterpret_cast<const float4*>(pre.shortcut + off);
             if constexpr (PRE == 3) scv[e] = *reinterpret_cast<const float4*>(bwd.xc + off);
         }
-        if constexpr (WG) {
-            xin[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (pr < R + 2 && h >= 0 && h < HW && w >= 0 && w < HW)
-                xin[e] = *reinterpret_cast<const float4*>(wg.x_in + (((long)n * HW + h) * HW + w) * C + 4 * v);
-        }
     }
-    split::Filt<C> filt[9];
+    split::Filt<C> filt[3];
+    auto split_filter = [&]() {
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) filt[tap] = split::filter_operand<C>(fr[tap]);
+        for (int ky = 0; ky < 3; ++ky) filt[ky] = split::filter_operand<C>(fr[ky]);
+    };
+    split_filter();
     if constexpr (PRE == 1 || PRE == 2) {   // mean / invstd of the input, merged from its records by records_merge_kernel
         if (tid < 2 * C) Sh[tid] = pre.stats_out[tid];
         __syncthreads();
@@ -319,7 +325,6 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
                     *reinterpret_cast<float4*>(bwd.dx_out + (((long)n * HW + h) * HW + w) * C + 4 * v) = o;
             }
         }
-        if constexpr (WG) stage(Xs2 + (pr * K::TW + pc) * K::PITCH + 8 * v, xin[e]);
         if constexpr (PRE == 1 || PRE == 2) {
             if (h >= 0 && h < HW && w >= 0 && w < HW) {
                 const float4 mu = *reinterpret_cast<const float4*>(Sh + 4 * v);
@@ -341,6 +346,18 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
         }
         stage(Xs + (pr * K::TW + pc) * K::PITCH + 8 * v, val[e]);
     }
+    load_filter(1);
+    // x halo tile of the fused d-filter: on its way during the product loop (pixels outside the image: some other pixel, zeroed later)
+    float4 xin[WG ? NL : 1];
+    if constexpr (WG) {
+#pragma unroll
+        for (int e = 0; e < NL; ++e) {
+            const int idx = tid + e * THREADS;
+            const int v = idx % V, pc = (idx / V) % K::TW, pr = idx / (V * K::TW);
+            const int h = min(max(r_base + pr - 1, 0), HW - 1), w = min(max(pc - 1, 0), HW - 1);
+            xin[e] = *reinterpret_cast<const float4*>(wg.x_in + (((long)n * HW + h) * HW + w) * C + 4 * v);
+        }
+    }
     __syncthreads();
 
     // ---- products.  Pixel operand (st, kx): the tile that starts st rows below the wavefront's first one, kx to the right
@@ -355,11 +372,16 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
 #pragma unroll
         for (int t = 0; t < 4; ++t) a[t] = lo[t] = floatx4{0.f, 0.f, 0.f, 0.f};
         split::Pix<C> x[2];
-        x[0] = split::pixel_operand<C, K::PLANE>(base);
+        auto pixels = [&](int i) { return split::pixel_operand<C, K::PLANE>(base + (i % ST * K::TW + i / ST) * K::PITCH); };
+        x[0] = pixels(0);
 #pragma unroll
         for (int i = 0; i < 3 * ST; ++i) {
-            const int st = i / 3, kx = i % 3;
-            if (i + 1 < 3 * ST) x[(i + 1) & 1] = split::pixel_operand<C, K::PLANE>(base + ((i + 1) / 3 * K::TW + (i + 1) % 3) * K::PITCH);
+            const int st = i % ST, kx = i / ST;
+            if (kx > 0 && st == 0) {
+                split_filter();
+                if (kx == 1) load_filter(2);
+            }
+            if (i + 1 < 3 * ST) x[(i + 1) & 1] = pixels(i + 1);
             __builtin_amdgcn_sched_barrier(0);      // or the compiler moves the reads down to their use, behind the products
 #pragma unroll
             for (int p = 0; p < split::products<C>(); ++p)
@@ -368,7 +390,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
                     const int ky = st - K::TROWS * t;
                     if (ky < 0 || ky > 2) continue;
                     floatx4& to = p + 1 < split::products<C>() ? lo[t] : a[t];
-                    to = split::product<C>(p, filt[3 * ky + kx], x[i & 1], to);
+                    to = split::product<C>(p, filt[ky], x[i & 1], to);
                 }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -403,33 +425,33 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
     // ---- store: a lane holds channels co .. co + 3 of its pixel of every tile
     const int co = co_w + 4 * q;
     float4 mu_c = make_float4(0.f, 0.f, 0.f, 0.f), is_c = mu_c;
-    if constexpr (POST) {
-        mu_c = *reinterpret_cast<const float4*>(post.stats + co);
-        is_c = *reinterpret_cast<const float4*>(post.stats + C + co);
-    }
-    // all loads of the epilogue first (dst may alias add, so the compiler cannot move them across the stores itself)
-    float4 addv[K::WM], maskv[POST ? K::WM : 1], xcv[POST ? K::WM : 1];
     auto row_of = [&](int wm) { return row0 + K::TROWS * (ks * K::WM + wm); };
     auto out_off = [&](int wm) { return (((long)n * HW + r_base + row_of(wm)) * HW + col) * C + co; };
-#pragma unroll
-    for (int wm = 0; wm < K::WM; ++wm) {
-        const long off = out_off(wm);
-        addv[wm] = add ? *reinterpret_cast<const float4*>(add + off) : make_float4(0.f, 0.f, 0.f, 0.f);
+    // all loads of the epilogue together (dst may alias add, so the compiler cannot move them across the stores itself)
+    float4 addv[K::WM], maskv[POST ? K::WM : 1], xcv[POST ? K::WM : 1];
+    unsigned mask_bits = 0;         // WG: bit 4 wm + channel
+    auto epilogue_loads = [&]() {
         if constexpr (POST) {
-            if constexpr (WG) {     // the mask source is the convolution's input, whose leading terms are in LDS
-                const uint2 m = *reinterpret_cast<const uint2*>(Xs2 + ((row_of(wm) + 1) * K::TW + col + 1) * K::PITCH + 2 * co);
-                maskv[wm] = make_float4(__uint_as_float(m.x << 16), __uint_as_float(m.x & 0xffff0000u),
-                                        __uint_as_float(m.y << 16), __uint_as_float(m.y & 0xffff0000u));
-            } else {
-                maskv[wm] = *reinterpret_cast<const float4*>(post.mask_src + off);
-            }
-            xcv[wm] = *reinterpret_cast<const float4*>(post.xc + off);
+            mu_c = *reinterpret_cast<const float4*>(post.stats + co);
+            is_c = *reinterpret_cast<const float4*>(post.stats + C + co);
         }
-    }
+#pragma unroll
+        for (int wm = 0; wm < K::WM; ++wm) {
+            const long off = out_off(wm);
+            addv[wm] = add ? *reinterpret_cast<const float4*>(add + off) : make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (POST) {
+                if constexpr (!WG) maskv[wm] = *reinterpret_cast<const float4*>(post.mask_src + off);
+                xcv[wm] = *reinterpret_cast<const float4*>(post.xc + off);
+            }
+        }
+    };
+    if constexpr (!WG) epilogue_loads();
     if constexpr (WG) {
-        // ---- d-filter of the same layer from the two LDS tiles, while the epilogue's operands are in flight:
+        // ---- d-filter of the same layer:
         //      dw[tap][ci][co] += x[pixel + tap][ci] dx[pixel][co], pixels as reduction index, 32 to an MFMA, both operands
-        //      by transposing reads.  A run of 32 pixels is one image row (C = 16) or two (C = 32); an x operand fetched
+        //      by transposing reads.  The dx operands go to registers (the product loop is through with the tile), the x tile
+        //      takes the place of the dx tile: half the LDS, so that workgroups of two more kernels fit beside this one's.
+        //      A run of 32 pixels is one image row (C = 16) or two (C = 32); an x operand fetched
         //      for one filter row serves the run above it too.  Rows of the matrix-core tile: co, columns: ci.
         //      C = 16: one 16x16 tile of (ci, co); a wavefront takes two of the band's eight runs, the four are summed
         //      in a fixed order.  C = 32: wavefront w owns tile (w / 2, w % 2) and takes all four runs.
@@ -437,31 +459,53 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
         constexpr int RROWS = 32 / HW, RUNS = SPLIT_K ? 2 : 4;     // image rows per run, runs per wavefront
         const int cit = SPLIT_K ? 0 : wave >> 1, cot = SPLIT_K ? 0 : wave & 1;
         const int first = SPLIT_K ? RUNS * wave : 0;               // first image row of the wavefront's runs
-        const char *xa[2], *da[2];                                 // of pixels 8 q + 4 h + l16 / 4 of the first run
+        const char* xa[2];                                         // of pixels 8 q + 4 h + l16 / 4 of the first run
+        uint4 d[RUNS][split::PLANES], x[2][split::PLANES];
+        {
+            const char* da[2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int p = 8 * q + 4 * h + (l16 >> 2);
-            const int o = ((first + p / HW) * K::TW + p % HW) * K::PITCH + 8 * (l16 & 3);
-            xa[h] = Xs2 + o + 32 * cit;
-            da[h] = Xs + o + (K::TW + 1) * K::PITCH + 32 * cot;
+            for (int h = 0; h < 2; ++h) {
+                const int p = 8 * q + 4 * h + (l16 >> 2);
+                const int o = ((first + p / HW) * K::TW + p % HW) * K::PITCH + 8 * (l16 & 3);
+                xa[h] = Xs + o + 32 * cit;
+                da[h] = Xs + o + (K::TW + 1) * K::PITCH + 32 * cot;
+            }
+#pragma unroll
+            for (int run = 0; run < RUNS; ++run)
+                split::transposed_operand<K::PLANE>(d[run], da[0] + run * RROWS * K::TW * K::PITCH, da[1] + run * RROWS * K::TW * K::PITCH);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < NL; ++e) {
+            const int idx = tid + e * THREADS;
+            const int v = idx % V, pc = (idx / V) % K::TW, pr = idx / (V * K::TW);
+            const int h = r_base + pr - 1, w = pc - 1;
+            if (pr >= R + 2) continue;
+            const bool in = h >= 0 && h < HW && w >= 0 && w < HW;
+            stage(Xs + (pr * K::TW + pc) * K::PITCH + 8 * v,
+                  make_float4(in ? xin[e].x : 0.f, in ? xin[e].y : 0.f, in ? xin[e].z : 0.f, in ? xin[e].w : 0.f));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int wm = 0; wm < K::WM; ++wm) {        // the mask source is the convolution's input, whose leading terms are in LDS
+            const uint2 m = *reinterpret_cast<const uint2*>(Xs + ((row_of(wm) + 1) * K::TW + col + 1) * K::PITCH + 2 * co);
+            const float f[4] = {__uint_as_float(m.x << 16), __uint_as_float(m.x & 0xffff0000u), __uint_as_float(m.y << 16), __uint_as_float(m.y & 0xffff0000u)};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) mask_bits |= f[v] > 0.f ? 1u << (4 * wm + v) : 0u;
         }
         floatx4 dw[9];
 #pragma unroll
         for (int t = 0; t < 9; ++t) dw[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-        uint4 d[RUNS][split::PLANES], x[2][split::PLANES];
-        auto load_d = [&](int run) { split::transposed_operand<K::PLANE>(d[run], da[0] + run * RROWS * K::TW * K::PITCH, da[1] + run * RROWS * K::TW * K::PITCH); };
         auto load_x = [&](int b, int i) {
             const int off = (i / 3 * K::TW + i % 3) * K::PITCH;
             split::transposed_operand<K::PLANE>(x[b], xa[0] + off, xa[1] + off);
         };
         constexpr int ST = RROWS * (RUNS - 1) + 3;
-        load_d(0);
         load_x(0, 0);
 #pragma unroll
         for (int i = 0; i < 3 * ST; ++i) {
             const int st = i / 3, kx = i % 3;
             if (i + 1 < 3 * ST) load_x((i + 1) & 1, i + 1);
-            if (i % 3 == 0 && st % RROWS == 0 && st / RROWS + 1 < RUNS) load_d(st / RROWS + 1);
             __builtin_amdgcn_sched_barrier(0);
             constexpr int PD[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
@@ -474,6 +518,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
             __builtin_amdgcn_sched_barrier(0);
         }
         mma::drain();
+        epilogue_loads();
         float* pout = wg.partial + (long)tile * 9 * C * C;
         if constexpr (SPLIT_K) {
             static_assert(!SPLIT_K || 4 * 9 * C * C * sizeof(float) <= K::LDS_BYTES_WG, "room for the four partial sums");
@@ -497,8 +542,9 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
     for (int wm = 0; wm < K::WM; ++wm) {
         float4 r = make_float4(acc[wm][0] + addv[wm].x, acc[wm][1] + addv[wm].y, acc[wm][2] + addv[wm].z, acc[wm][3] + addv[wm].w);
         if constexpr (POST) {
-            r.x = maskv[wm].x > 0.f ? r.x : 0.f; r.y = maskv[wm].y > 0.f ? r.y : 0.f;
-            r.z = maskv[wm].z > 0.f ? r.z : 0.f; r.w = maskv[wm].w > 0.f ? r.w : 0.f;
+            auto on = [&](int v, float m) { return WG ? (mask_bits >> (4 * wm + v) & 1u) != 0 : m > 0.f; };
+            r.x = on(0, maskv[wm].x) ? r.x : 0.f; r.y = on(1, maskv[wm].y) ? r.y : 0.f;
+            r.z = on(2, maskv[wm].z) ? r.z : 0.f; r.w = on(3, maskv[wm].w) ? r.w : 0.f;
             sum_dz.x += r.x; sum_dz.y += r.y; sum_dz.z += r.z; sum_dz.w += r.w;
             sum_dzx.x = fmaf(r.x, (xcv[wm].x - mu_c.x) * is_c.x, sum_dzx.x);
             sum_dzx.y = fmaf(r.y, (xcv[wm].y - mu_c.y) * is_c.y, sum_dzx.y);

@@ -860,101 +860,139 @@ __global__ __launch_bounds__(THREADS) void wgrad3x3_kernel(const float* __restri
     }
 }
 
-// The same for the last stage (64 channels, 8x8 images), where one image is only four pixel chunks and the
-// result is as large as 9 x 64 x 64: a workgroup owns 16 of the input channels (wavefront w: output channels
-// 16w..16w+15, the 16 accumulator tiles of the transformed domain) and IMGS whole images, one after the other; the next image's
-// x halo tile (its 16 channels only) and dy tile are fetched into registers while the matrix cores work on the
-// current one (two LDS buffers, one barrier per image).  Output: partial[image group][tap][ci][co], the
-// workgroup's 16 ci rows of it.
-template <int IMGS>
-__global__ __launch_bounds__(THREADS) void wgrad3x3_wide_kernel(const float* __restrict__ x, const float* __restrict__ dy,
-                                                                float* __restrict__ partial, int N, int own_blocks,
-                                                                jobs::TotalsJob tj) {
-    constexpr int C = 64, HW = 8, TW = HW + 2, CIW = 16, LDA = CIW + 4, LDB = C + 4;
-    constexpr int XS = TW * TW * LDA, DS = HW * HW * LDB, BUF = XS + DS;
-    constexpr int XV = (TW * TW * (CIW / 4) + THREADS - 1) / THREADS, DV = HW * HW * (C / 4) / THREADS;
-    extern __shared__ __attribute__((aligned(16))) float lds[];
+// The same for the last stage (64 channels, 8x8 images), on the bf16 matrix cores (split.hpp).  The result is as large as
+// 9 x 64 x 64, so a workgroup owns 16 input and 32 output channels of it and four images, one per wavefront, which needs no
+// barrier until the four sums meet in LDS: pixels are the reduction index, four image rows to an MFMA.  The wavefront leaves its
+// slice of x (with a zero border) in LDS as three bf16 terms and takes it from there once per tap by transposing reads, the dy
+// operands come straight from memory, eight pixels of a channel to a lane (through LDS too, 95 KB, two more kernels' workgroups
+// would not fit beside: 10.2 us alone and 2 % of a ResNet step lost).  32 output channels (and not 16 of them and eight
+// images) so that an x operand serves two products; rows of the matrix-core tile: co, columns: ci.  Output: partial[image group][tap][ci][co], 4.7 MB at batch 128 (as minimal filtering on the
+// fp32 matrix cores, two images to a workgroup, 9.4 MB, each written and read once).
+namespace wide {
+constexpr int C = 64, HW = 8, TW = HW + 2, IMGS = 4, CI = 16, CO = 32;
+constexpr int XPLANE = 2 * CI, XPITCH = 3 * XPLANE + 8;
+constexpr int XB = TW * TW * XPITCH, RED = 2 * 9 * CI * CO * 4, LDS = 4 * XB > RED ? 4 * XB : RED;
+static_assert(XB % 16 == 0, "alignment");
+}  // namespace wide
+
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) void wgrad3x3_wide_kernel(
+    const float* __restrict__ x, const float* __restrict__ dy, float* __restrict__ partial, int N, int own_blocks, jobs::TotalsJob tj) {
+    using namespace wide;
+    extern __shared__ __attribute__((aligned(16))) char lds_bytes[];
+    char* lds = lds_bytes;
     if ((int)blockIdx.x >= own_blocks) {
-        jobs::bn_totals(tj, blockIdx.x - own_blocks, lds);
+        jobs::bn_totals(tj, blockIdx.x - own_blocks, reinterpret_cast<float*>(lds));
         return;
     }
-    const int tid = threadIdx.x, lane = tid & 63, cot = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, q = lane >> 4;
     const int tile = xcd_tile(blockIdx.x, own_blocks);
-    const int cit = tile % (C / CIW), grp = tile / (C / CIW);
-    const int n0 = grp * IMGS;
-    const int nimg = min(IMGS, N - n0);
-    float4 rx[XV], rd[DV];
+    constexpr int ROLES = (C / CI) * (C / CO);
+    const int role = tile % ROLES, grp = tile / ROLES, ci0 = CI * (role % (C / CI)), co0 = CO * (role / (C / CI));
+    const int n = grp * IMGS + wave;
+    char* X = lds + wave * XB;
+    floatx4 acc[9][2];
 #pragma unroll
-    for (int e = 0; e < XV; ++e) rx[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int t = 0; t < 9; ++t) acc[t][0] = acc[t][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (n < N) {
+        constexpr int NX = HW * HW * CI / 4 / 64;
+        float4 rx[NX], rd[2][2][2];            // rd[run][co tile]: pixels 8 q .. 8 q + 7 of the run
 #pragma unroll
-    for (int e = 0; e < DV; ++e) rd[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-    // written out as macros: with lambdas that capture the two arrays the compiler kept rd in scratch memory
-#define WIDE_FETCH(n)                                                                                                      \
-    _Pragma("unroll") for (int e = 0; e < XV; ++e) {                                                                       \
-        const int idx = tid + e * THREADS;                                                                                 \
-        const int v = idx % (CIW / 4), pix = idx / (CIW / 4);                                                              \
-        const int h = pix / TW - 1, w = pix % TW - 1;                                                                      \
-        rx[e] = make_float4(0.f, 0.f, 0.f, 0.f);                                                                           \
-        if (pix < TW * TW && h >= 0 && h < HW && w >= 0 && w < HW)                                                         \
-            rx[e] = *reinterpret_cast<const float4*>(x + (((long)(n) * HW + h) * HW + w) * C + CIW * cit + 4 * v);         \
-    }                                                                                                                      \
-    _Pragma("unroll") for (int e = 0; e < DV; ++e)                                                                         \
-        rd[e] = *reinterpret_cast<const float4*>(dy + (long)(n) * HW * HW * C + 4 * (long)(tid + e * THREADS));
-#define WIDE_STAGE(buf)                                                                                                    \
-    {                                                                                                                      \
-        float* Xw = lds + (buf) * BUF;                                                                                     \
-        float* Dw = Xw + XS;                                                                                               \
-        _Pragma("unroll") for (int e = 0; e < XV; ++e) {                                                                   \
-            const int idx = tid + e * THREADS;                                                                             \
-            if (idx < TW * TW * (CIW / 4)) *reinterpret_cast<float4*>(&Xw[(idx / (CIW / 4)) * LDA + 4 * (idx % (CIW / 4))]) = rx[e]; \
-        }                                                                                                                  \
-        _Pragma("unroll") for (int e = 0; e < DV; ++e) {                                                                   \
-            const int idx = tid + e * THREADS;                                                                             \
-            *reinterpret_cast<float4*>(&Dw[(idx / (C / 4)) * LDB + 4 * (idx % (C / 4))]) = rd[e];                          \
-        }                                                                                                                  \
+        for (int e = 0; e < NX; ++e) {
+            const int idx = lane + 64 * e;
+            rx[e] = *reinterpret_cast<const float4*>(x + ((long)n * HW * HW + idx / (CI / 4)) * C + ci0 + 4 * (idx % (CI / 4)));
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const float* dp = dy + ((long)n * HW * HW + 32 * r + 8 * q + 4 * e) * C + co0 + 16 * j + l16;
+                    rd[r][j][e] = make_float4(dp[0], dp[C], dp[2 * C], dp[3 * C]);
+                }
+        for (int i = lane; i < 4 * (TW - 1) * (XPITCH / 8); i += 64) {          // zero border
+            const int h = i / (XPITCH / 8);
+            const int r = h < TW ? 0 : h < 2 * TW ? TW - 1 : (h - 2 * TW) / 2 + 1;
+            const int c = h < 2 * TW ? h % TW : (h & 1) * (TW - 1);
+            *reinterpret_cast<uint2*>(X + (r * TW + c) * XPITCH + 8 * (i % (XPITCH / 8))) = make_uint2(0u, 0u);
+        }
+        uint2 pl[split::PLANES];
+#pragma unroll
+        for (int e = 0; e < NX; ++e) {
+            const int idx = lane + 64 * e, px = idx / (CI / 4);
+            split::split4(rx[e], pl);
+#pragma unroll
+            for (int p = 0; p < split::PLANES; ++p)
+                *reinterpret_cast<uint2*>(X + ((px / HW + 1) * TW + px % HW + 1) * XPITCH + p * XPLANE + 8 * (idx % (CI / 4))) = pl[p];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const char* xa[2];                          // of pixels 8 q + 4 h + l16 / 4 of the first run (four rows)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int p = 8 * q + 4 * h + (l16 >> 2);
+            xa[h] = X + (p / HW * TW + p % HW) * XPITCH + 8 * (l16 & 3);
+        }
+        split::Filt<32> d[2];
+        uint4 xv[2][1][split::PLANES];
+        auto load_x = [&](int i) {                  // run i / 9, tap i % 9
+            const int off = ((4 * (i / 9) + i % 9 / 3) * TW + i % 3) * XPITCH;
+            split::transposed_operand<XPLANE>(xv[i & 1][0], xa[0] + off, xa[1] + off);
+        };
+        load_x(0);
+#pragma unroll
+        for (int i = 0; i < 18; ++i) {
+            if (i % 9 == 0)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) d[j] = split::filter_operand<32>(rd[i / 9][j]);
+            if (i + 1 < 18) load_x(i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int PD[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+            for (int p = 0; p < 6; ++p)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i % 9][j] = split::mfma(d[j].v[PD[p]], xv[i & 1][0][PX[p]], acc[i % 9][j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        mma::drain();
     }
-    floatx4 M[16];
+    // the four sums, in a fixed order: wavefronts 2 and 3 hand theirs to 0 and 1, those two meet in LDS
+    floatx4* Red = reinterpret_cast<floatx4*>(lds); // [2][tap][ci][co / 4]
+    constexpr int E4 = 9 * CI * CO / 4;
+    floatx4* mine = Red + (wave & 1) * E4 + l16 * (CO / 4) + q;
 #pragma unroll
-    for (int xi = 0; xi < 16; ++xi) M[xi] = floatx4{0.f, 0.f, 0.f, 0.f};
-    WIDE_FETCH(n0)
-    for (int i = 0; i < nimg; ++i) {
-        WIDE_STAGE(i & 1)
+    for (int round = 0; round < 2; ++round) {
         __syncthreads();
-        if (i + 1 < nimg) { WIDE_FETCH(n0 + i + 1) }
-        const float* Xs = lds + (i & 1) * BUF;
-        const float* Ds = Xs + XS;
-        // the image is one run: 4 x 4 tiles of 2x2 pixels
-        dfilter_run(M, q,
-                    [&](int tile) { return make_int2(2 * (tile / 4), 2 * (tile % 4)); },
-                    [&](int2 o, int r, int c) { return Xs[((o.x + r) * TW + o.y + c) * LDA + l16]; },
-                    [&](int2 o, int i_, int j) { return Ds[((o.x + i_) * HW + o.y + j) * LDB + 16 * cot + l16]; });
+        if (wave >> 1 == 1 - round)
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) mine[t * CI * (CO / 4) + 4 * j] = acc[t][j];
+        __syncthreads();
+        if (round == 0 && wave < 2)
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[t][j] += mine[t * CI * (CO / 4) + 4 * j];
     }
-#undef WIDE_FETCH
-#undef WIDE_STAGE
-    mma::drain();
-    floatx4 acc[9];
-    dfilter_finish(M, acc);
     float* out = partial + (long)grp * 9 * C * C;
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) out[(t * C + CIW * cit + 4 * q + v) * C + 16 * cot + l16] = acc[t][v];
+    for (int idx = tid; idx < E4; idx += THREADS) {
+        const int c4 = idx % (CO / 4), ci = idx / (CO / 4) % CI, t = idx / (CO / 4) / CI;
+        *reinterpret_cast<floatx4*>(out + (t * C + ci0 + ci) * C + co0 + 4 * c4) = Red[idx] + Red[E4 + idx];
+    }
 }
 
-template <int IMGS>
 int launch_wgrad_wide(hipStream_t s, const float* x, const float* dy, float* partial, int N, const jobs::TotalsJob& tj) {
-    constexpr size_t bytes = (size_t)2 * (10 * 10 * 20 + 8 * 8 * 68) * sizeof(float);
-    static_assert(bytes >= jobs::LDS_FLOATS * sizeof(float), "room for a carried job");
+    static_assert(wide::LDS >= jobs::LDS_FLOATS * sizeof(float), "room for a carried job");
     static bool attr_set = false;
-    auto kern = wgrad3x3_wide_kernel<IMGS>;
     if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad3x3_wide_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, wide::LDS) !=
+            hipSuccess)
             return -1;
         attr_set = true;
     }
-    const int own = (N + IMGS - 1) / IMGS * 4;
-    hipLaunchKernelGGL(kern, dim3(own + tj.blocks), dim3(THREADS), bytes, s, x, dy, partial, N, own, tj);
+    const int own = (N + wide::IMGS - 1) / wide::IMGS * (wide::C / wide::CI) * (wide::C / wide::CO);
+    hipLaunchKernelGGL(wgrad3x3_wide_kernel, dim3(own + tj.blocks), dim3(THREADS), wide::LDS, s, x, dy, partial, N, own, tj);
     return DSSPK_LAUNCH_RC();
 }
 
@@ -977,19 +1015,17 @@ int launch_wgrad(hipStream_t s, const float* x, const float* dy, float* partial,
 
 }  // namespace
 
-constexpr int WIDE_IMGS = 2;          // images per workgroup of the last stage's d-filter kernel
-
 // Number of partial results the specialised d-filter kernel writes, 0 if the shape is not covered.
 int wgrad3x3_tiled_parts(int N, int HW, int C) {
     if (C == 16 && HW == 32) return N * 4;
     if (C == 32 && HW == 16) return N * 2;
-    if (C == 64 && HW == 8) return (N + WIDE_IMGS - 1) / WIDE_IMGS;
+    if (C == 64 && HW == 8) return (N + wide::IMGS - 1) / wide::IMGS;
     return 0;
 }
 
 int wgrad3x3_tiled(hipStream_t s, const float* x, const float* dy, float* partial, int N, int HW, int C, const jobs::TotalsJob& tj) {
     if (C == 16 && HW == 32) return launch_wgrad<16, 32, 8>(s, x, dy, partial, N, tj);
     if (C == 32 && HW == 16) return launch_wgrad<32, 16, 8>(s, x, dy, partial, N, tj);
-    if (C == 64 && HW == 8) return launch_wgrad_wide<WIDE_IMGS>(s, x, dy, partial, N, tj);
+    if (C == 64 && HW == 8) return launch_wgrad_wide(s, x, dy, partial, N, tj);
     return -2;
 }

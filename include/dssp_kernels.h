@@ -143,6 +143,23 @@ int dsspk_conv_bwd_data_bn_wgrad(void* stream, const float* dz_dev, const float*
                                  const float* x_in_dev, float* partial_dev, const float* red_partial_dev,
                                  float* red_dw_dev, int red_E, int red_chunks, int N, int H, int C);
 int dsspk_conv_bwd_fused_chunks(int N, int H, int C);
+/* The two with the sums of their batch norm added up by the kernel itself: totals_dev NULL and in_parts records in
+ * in_records_dev (what dsspk_bn_bwd_totals would be given; not the buffer records_dev points to); dgamma_dev[C] and dbeta_dev[C]
+ * are stored as that call would.  Only where dsspk_conv_records_inline(in_parts, C) says 1 (few records; -1 otherwise).
+ * dsspk_conv_fwd_prebn merges such records in the same way, without a kernel of its own. */
+int dsspk_conv_records_inline(int parts, int C);
+int dsspk_conv_bwd_data_bn_records(void* stream, const float* dz_dev, const float* xc_dev, const float* stats_dev,
+                                   const float* gamma_dev, const float* totals_dev, const float* in_records_dev, int in_parts,
+                                   float* dgamma_dev, float* dbeta_dev, float* dx_dev, const float* w_dev,
+                                   const float* add_dev, float* out_dev, const float* mask_src_dev, const float* xc_post_dev,
+                                   const float* stats_post_dev, float* records_dev, const float* red_partial_dev,
+                                   float* red_dw_dev, int red_E, int red_chunks, int N, int H, int C);
+int dsspk_conv_bwd_data_bn_wgrad_records(void* stream, const float* dz_dev, const float* xc_dev, const float* stats_dev,
+                                         const float* gamma_dev, const float* totals_dev, const float* in_records_dev, int in_parts,
+                                         float* dgamma_dev, float* dbeta_dev, const float* w_dev, const float* add_dev,
+                                         float* out_dev, const float* xc_post_dev, const float* stats_post_dev,
+                                         float* records_dev, const float* x_in_dev, float* partial_dev,
+                                         const float* red_partial_dev, float* red_dw_dev, int red_E, int red_chunks, int N, int H, int C);
 /* dw[kh][kw][ci][co] = sum over batch and output pixels of x * dy.  Two stages (partial sums per
  * pixel chunk, then a fixed-order reduction).  scratch_dev: dsspk_conv_wgrad_scratch_floats(...) floats. */
 int dsspk_conv_bwd_weight(void* stream, const float* x_dev, const float* dy_dev, float* dw_dev, float* scratch_dev,

@@ -25,12 +25,16 @@ int conv3x3_tiled_prebn(hipStream_t s, const float* src, const float* records, i
                          const float* w, float* dst, float* bn_partial, int N, int HW, int C);
 int wgrad3x3_tiled_parts(int N, int HW, int C);
 int wgrad3x3_tiled(hipStream_t s, const float* x, const float* dy, float* partial, int N, int HW, int C, const jobs::TotalsJob& tj);
+// The batch norm's sums: totals, or (totals null) parts records to add up, dgamma and dbeta stored from them.
+bool conv3x3_records_inline(int parts, int C);
 int conv3x3_tiled_dgrad_bn(hipStream_t s, const float* dz, const float* xc, const float* stats, const float* gamma,
-                            const float* totals, float* dx_out, const float* w, const float* add, float* out,
+                            const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta, float* dx_out,
+                            const float* w, const float* add, float* out,
                             const float* mask_src, const float* xc_post, const float* stats_post, float* records,
                             const float* red_partial, float* red_dw, int red_E, int red_chunks, int N, int HW, int C);
 int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc, const float* stats, const float* gamma,
-                                  const float* totals, const float* w, const float* add, float* out,
+                                  const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta,
+                                  const float* w, const float* add, float* out,
                                   const float* xc_post, const float* stats_post, float* records,
                                   const float* x_in, float* partial, const float* red_partial, float* red_dw, int red_E,
                                   int red_chunks, int N, int HW, int C);
@@ -899,17 +903,29 @@ extern "C" int dsspk_bn_bwd_totals(void* stream, const float* records, int G, in
     return DSSPK_LAUNCH_RC();
 }
 
+extern "C" int dsspk_conv_records_inline(int parts, int C) { return conv3x3_records_inline(parts, C) ? 1 : 0; }
+
+extern "C" int dsspk_conv_bwd_data_bn_records(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,
+                                              const float* totals, const float* in_records, int in_parts, float* dgamma, float* dbeta,
+                                              float* dx, const float* w, const float* add, float* out,
+                                              const float* mask_src, const float* xc_post, const float* stats_post, float* records,
+                                              const float* red_partial, float* red_dw, int red_E, int red_chunks, int N, int H, int C) {
+    if (!dz || !xc || !stats || !gamma || !dx || !w || !out || !mask_src || !xc_post || !stats_post || !records || N < 1) return -1;
+    if (!totals && (!in_records || in_records == records || !dgamma || !dbeta || in_parts < 1)) return -1;
+    if (out == dz || dx == dz || dx == out) return -1;
+    if (red_partial && (!red_dw || red_E < 4 || red_E % 4 || red_chunks < 1)) return -1;
+    const int rc = conv3x3_tiled_dgrad_bn((hipStream_t)stream, dz, xc, stats, gamma, totals, in_records, in_parts, dgamma, dbeta, dx, w, add, out,
+                                           mask_src, xc_post, stats_post, records, red_partial, red_dw, red_E, red_chunks, N, H, C);
+    return rc == -2 ? -1 : rc;
+}
+
 extern "C" int dsspk_conv_bwd_data_bn(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,
                                       const float* totals, float* dx, const float* w, const float* add, float* out,
                                       const float* mask_src, const float* xc_post, const float* stats_post, float* records,
                                       const float* red_partial, float* red_dw, int red_E, int red_chunks, int N, int H, int C) {
-    if (!dz || !xc || !stats || !gamma || !totals || !dx || !w || !out || !mask_src || !xc_post || !stats_post || !records || N < 1)
-        return -1;
-    if (out == dz || dx == dz || dx == out) return -1;
-    if (red_partial && (!red_dw || red_E < 4 || red_E % 4 || red_chunks < 1)) return -1;
-    const int rc = conv3x3_tiled_dgrad_bn((hipStream_t)stream, dz, xc, stats, gamma, totals, dx, w, add, out, mask_src, xc_post,
-                                           stats_post, records, red_partial, red_dw, red_E, red_chunks, N, H, C);
-    return rc == -2 ? -1 : rc;
+    if (!totals) return -1;
+    return dsspk_conv_bwd_data_bn_records(stream, dz, xc, stats, gamma, totals, nullptr, 0, nullptr, nullptr, dx, w, add, out, mask_src, xc_post,
+                                          stats_post, records, red_partial, red_dw, red_E, red_chunks, N, H, C);
 }
 
 extern "C" int dsspk_conv_bwd_fused_chunks(int N, int H, int C) {
@@ -917,18 +933,29 @@ extern "C" int dsspk_conv_bwd_fused_chunks(int N, int H, int C) {
     return 0;
 }
 
+extern "C" int dsspk_conv_bwd_data_bn_wgrad_records(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,
+                                                    const float* totals, const float* in_records, int in_parts, float* dgamma, float* dbeta,
+                                                    const float* w, const float* add, float* out,
+                                                    const float* xc_post, const float* stats_post, float* records,
+                                                    const float* x_in, float* partial, const float* red_partial, float* red_dw,
+                                                    int red_E, int red_chunks, int N, int H, int C) {
+    if (!dz || !xc || !stats || !gamma || !w || !out || !xc_post || !stats_post || !records || !x_in || !partial || N < 1) return -1;
+    if (!totals && (!in_records || in_records == records || !dgamma || !dbeta || in_parts < 1)) return -1;
+    if (out == dz || partial == red_partial) return -1;
+    if (red_partial && (!red_dw || red_E < 4 || red_E % 4 || red_chunks < 1)) return -1;
+    if (dsspk_conv_bwd_fused_chunks(N, H, C) == 0) return -1;
+    const int rc = conv3x3_tiled_dgrad_bn_wgrad((hipStream_t)stream, dz, xc, stats, gamma, totals, in_records, in_parts, dgamma, dbeta, w, add,
+                                                 out, xc_post, stats_post, records, x_in, partial, red_partial, red_dw, red_E, red_chunks, N,
+                                                 H, C);
+    return rc == -2 ? -1 : rc;
+}
+
 extern "C" int dsspk_conv_bwd_data_bn_wgrad(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,
                                             const float* totals, const float* w, const float* add, float* out,
                                             const float* xc_post, const float* stats_post, float* records,
                                             const float* x_in, float* partial, const float* red_partial, float* red_dw,
                                             int red_E, int red_chunks, int N, int H, int C) {
-    if (!dz || !xc || !stats || !gamma || !totals || !w || !out || !xc_post || !stats_post || !records || !x_in ||
-        !partial || N < 1)
-        return -1;
-    if (out == dz || partial == red_partial) return -1;
-    if (red_partial && (!red_dw || red_E < 4 || red_E % 4 || red_chunks < 1)) return -1;
-    if (dsspk_conv_bwd_fused_chunks(N, H, C) == 0) return -1;
-    const int rc = conv3x3_tiled_dgrad_bn_wgrad((hipStream_t)stream, dz, xc, stats, gamma, totals, w, add, out, xc_post,
-                                                 stats_post, records, x_in, partial, red_partial, red_dw, red_E, red_chunks, N, H, C);
-    return rc == -2 ? -1 : rc;
+    if (!totals) return -1;
+    return dsspk_conv_bwd_data_bn_wgrad_records(stream, dz, xc, stats, gamma, totals, nullptr, 0, nullptr, nullptr, w, add, out, xc_post, stats_post,
+                                                records, x_in, partial, red_partial, red_dw, red_E, red_chunks, N, H, C);
 }

@@ -137,8 +137,8 @@ struct Cfg {
 // Normalisation applied to the input while it is loaded (PRE != 0): the kernel then computes
 //   a = ReLU(gamma * (src - mean) * invstd + beta (+ shortcut))   and   dst = conv(a),
 // i.e. the batch norm + ReLU that separates two convolutions never runs as a pass of its own.
-// mean / invstd come from the statistics records of src, merged by a one-workgroup kernel launched just
-// before (they are also what the backward pass needs); the workgroups write `a` (their own rows).
+// mean / invstd come from the statistics records of src, merged by a small kernel launched just before or, if they are few
+// (records_inline), by every workgroup itself; they are also what the backward pass needs.  The workgroups write `a` (their own rows).
 struct PreBn {
     const float* records;      // statistics records of src
     bnm::BnLayout L;           // their layout
@@ -149,6 +149,7 @@ struct PreBn {
     const float* shortcut;     // PRE == 2: added before the ReLU, same shape as src
     float* act_out;            // a
     float* stats_out;          // mean[C], invstd[C]
+    bool merge;                // every workgroup merges the records, the first one stores stats_out
 };
 
 // Backward of the ReLU + batch norm that FOLLOWS in the backward direction, started in the epilogue (POST):
@@ -166,12 +167,16 @@ struct PostBn {
 // masked gradient at the batch norm's output, and the convolution runs on
 //   dx = gamma * invstd * (dz - sum(dz) / M - xhat * sum(dz * xhat) / M),   xhat = (xc - mean) * invstd,
 // the gradient w.r.t. the batch norm's input xc; the workgroups also write dx (their own rows) for the
-// d-filter kernel.  The two sums come from the records of the epilogue that produced dz (TotalsJob).
+// d-filter kernel.  The two sums come from the records of the epilogue that produced dz: added up before (TotalsJob) or, if
+// they are few, by every workgroup itself.
 struct BwdBn {
     const float* xc;           // the batch norm's input
     const float* stats;        // its mean[C], invstd[C]
     const float* gamma;
-    const float* totals;       // sum dz [C], sum dz * xhat [C]
+    const float* totals;       // sum dz [C], sum dz * xhat [C]; null: add up `records`
+    const float* records;      // [parts][C][2]
+    int parts;
+    float *dgamma, *dbeta;     // with records: sum dz * xhat and sum dz, stored by the first workgroup
     float inv_m;               // 1 / (N * HW * HW)
     float* dx_out;
 };
@@ -201,6 +206,34 @@ __device__ __forceinline__ float sum16(float v) {
     return v;
 }
 __device__ __forceinline__ float4 sum16(float4 v) { return make_float4(sum16(v.x), sum16(v.y), sum16(v.z), sum16(v.w)); }
+
+// Records of a tensor small enough for every workgroup of its consumer to merge them itself, INLINE_RECORDS / C of them at most.  A
+// kernel of its own for that takes 4 us of a stream's time; reading the records takes every workgroup 0.5 us at 16 KB and
+// as long as that kernel at the 64 KB of batch 128 (where 512 workgroups doing so lost 2 % of a step).
+constexpr int INLINE_RECORDS = 2048, RECORDS_PER_THREAD = INLINE_RECORDS / THREADS;
+constexpr bool records_inline(int parts, int C) { return parts * C <= INLINE_RECORDS; }
+
+// Thread (channel tid % C, lane tid / C) holds records lane, lane + 256 / C, ... of its channel; all loads in flight together.
+template <int C>
+__device__ __forceinline__ void load_records(float2 (&v)[RECORDS_PER_THREAD], const float* __restrict__ records, int parts, int tid) {
+#pragma unroll
+    for (int u = 0; u < RECORDS_PER_THREAD; ++u) {
+        const int g = tid / C + u * (THREADS / C);
+        v[u] = *reinterpret_cast<const float2*>(records + ((long)min(g, parts - 1) * C + tid % C) * 2);
+        if (g >= parts) v[u] = make_float2(0.f, 0.f);
+    }
+}
+
+// Sum of every lane's s of this thread's channel, in lane order; red: THREADS floats nobody else uses between the barriers.
+template <int C>
+__device__ __forceinline__ float channel_sum(float s, float* red, int tid) {
+    red[tid] = s;
+    __syncthreads();
+    float t = red[tid % C];
+#pragma unroll
+    for (int j = 1; j < THREADS / C; ++j) t += red[j * C + tid % C];
+    return t;
+}
 
 template <int C, int HW, int R, int NSPLIT, bool TRANSPOSED, int PRE, bool POST = false, bool WG = false>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_waves<C, WG>()))) void conv3x3_kernel(const float* __restrict__ src, const float* __restrict__ wgt,
@@ -254,6 +287,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
                 }
             }
     };
+    float2 rec[PRE ? RECORDS_PER_THREAD : 1];
+    if constexpr (PRE == 1 || PRE == 2)
+        if (pre.merge) load_records<C>(rec, pre.records, pre.L.G, tid);
+    if constexpr (PRE == 3)
+        if (!bwd.totals) load_records<C>(rec, bwd.records, bwd.parts, tid);
     load_filter(0);
     // ---- input halo tile, zero outside the image.  The raw loads are issued first; the first filter column is split while
     //      they are in flight.
@@ -280,18 +318,49 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
         for (int ky = 0; ky < 3; ++ky) filt[ky] = split::filter_operand<C>(fr[ky]);
     };
     split_filter();
-    if constexpr (PRE == 1 || PRE == 2) {   // mean / invstd of the input, merged from its records by records_merge_kernel
-        if (tid < 2 * C) Sh[tid] = pre.stats_out[tid];
+    float* red = reinterpret_cast<float*>(lds);         // the tile is not there yet
+    if constexpr (PRE == 1 || PRE == 2) {               // mean / invstd of the input
+        if (pre.merge) {                                // mean = sum n mean_g / M, M2 = sum (M2_g + n (mean_g - mean)^2)
+            const float nn = (float)pre.L.rows_per_block, M = (float)pre.M;
+            float s_ = 0.f, m2 = 0.f;
+#pragma unroll
+            for (int u = 0; u < RECORDS_PER_THREAD; ++u) s_ = fmaf(nn, rec[u].x, s_);
+            const float mean = channel_sum<C>(s_, red, tid) / M;
+#pragma unroll
+            for (int u = 0; u < RECORDS_PER_THREAD; ++u) {
+                const float d = rec[u].x - mean;
+                m2 += tid / C + u * (THREADS / C) < pre.L.G ? rec[u].y + nn * d * d : 0.f;
+            }
+            const float invstd = 1.0f / sqrtf(channel_sum<C>(m2, red + THREADS, tid) / M + pre.eps);
+            if (tid < C) {
+                Sh[tid] = mean;
+                Sh[C + tid] = invstd;
+                if (blockIdx.x == 0) { pre.stats_out[tid] = mean; pre.stats_out[C + tid] = invstd; }
+            }
+        } else if (tid < 2 * C) {
+            Sh[tid] = pre.stats_out[tid];
+        }
         __syncthreads();
     }
     if constexpr (PRE == 3) {               // mean, invstd, gamma * invstd, sum(dz) / M, sum(dz * xhat) / M
+        float sum_b = 0.f, sum_g = 0.f;
+        if (!bwd.totals) {
+#pragma unroll
+            for (int u = 0; u < RECORDS_PER_THREAD; ++u) { sum_b += rec[u].x; sum_g += rec[u].y; }
+            sum_b = channel_sum<C>(sum_b, red, tid);
+            sum_g = channel_sum<C>(sum_g, red + THREADS, tid);
+        } else if (tid < C) {
+            sum_b = bwd.totals[tid];
+            sum_g = bwd.totals[C + tid];
+        }
         if (tid < C) {
             const float is = bwd.stats[C + tid];
             Sh[tid] = bwd.stats[tid];
             Sh[C + tid] = is;
             Sh[2 * C + tid] = bwd.gamma[tid] * is;
-            Sh[3 * C + tid] = bwd.totals[tid] * bwd.inv_m;
-            Sh[4 * C + tid] = bwd.totals[C + tid] * bwd.inv_m;
+            Sh[3 * C + tid] = sum_b * bwd.inv_m;
+            Sh[4 * C + tid] = sum_g * bwd.inv_m;
+            if (!bwd.totals && blockIdx.x == 0) { bwd.dbeta[tid] = sum_b; bwd.dgamma[tid] = sum_g; }
         }
         __syncthreads();
     }
@@ -641,7 +710,7 @@ __global__ __launch_bounds__(THREADS) void records_merge_kernel(const float* __r
 
 template <int C, int HW, int R, int NSPLIT, bool T, int PRE = 0, bool POST = false, bool WG = false>
 int launch(hipStream_t s, const float* src, const float* w, const float* add, float* dst, float* bn_partial, int N,
-           const PreBn& pre = PreBn(), const PostBn& post = PostBn(), const BwdBn& bwd = BwdBn(),
+           const PreBn& pre = PreBn{}, const PostBn& post = PostBn(), const BwdBn& bwd = BwdBn(),
            const jobs::ReduceJob& rj = jobs::ReduceJob(), const WgradFused& wg = WgradFused()) {
     using K = Cfg<C, HW, R, NSPLIT>;
     constexpr size_t LDS_BYTES = WG ? K::LDS_BYTES_WG : K::LDS_BYTES;
@@ -688,7 +757,9 @@ int conv3x3_tiled_prebn(hipStream_t s, const float* src, const float* records, i
     pre.shortcut = shortcut; pre.act_out = act_out; pre.stats_out = stats_out;
     if (C != 16 && C != 32 && C != 64) return -2;
     if (in_parts > 8 * (THREADS / 4)) return -1;
-    hipLaunchKernelGGL(records_merge_kernel, dim3(C / 4), dim3(THREADS), 0, s, records, in_parts, pre.L.rows_per_block, pre.M, C, eps, stats_out);
+    pre.merge = records_inline(in_parts, C);
+    if (!pre.merge)
+        hipLaunchKernelGGL(records_merge_kernel, dim3(C / 4), dim3(THREADS), 0, s, records, in_parts, pre.L.rows_per_block, pre.M, C, eps, stats_out);
     if (C == 16 && HW == 32)
         return shortcut ? launch<16, 32, 8, 1, false, 2>(s, src, w, nullptr, dst, bn_partial, N, pre)
                         : launch<16, 32, 8, 1, false, 1>(s, src, w, nullptr, dst, bn_partial, N, pre);
@@ -716,11 +787,14 @@ int conv3x3_tiled_dgrad_post(hipStream_t s, const float* dy, const float* w, con
 // d-input convolution of dx = batch-norm backward of dz (see BwdBn), with the epilogue of conv3x3_tiled_dgrad_post;
 // optionally carries the second stage of an earlier d-filter convolution (red_partial != NULL).
 int conv3x3_tiled_dgrad_bn(hipStream_t s, const float* dz, const float* xc, const float* stats, const float* gamma,
-                            const float* totals, float* dx_out, const float* w, const float* add, float* out,
+                            const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta, float* dx_out,
+                            const float* w, const float* add, float* out,
                             const float* mask_src, const float* xc_post, const float* stats_post, float* records,
                             const float* red_partial, float* red_dw, int red_E, int red_chunks, int N, int HW, int C) {
+    if (!totals && !records_inline(parts, C)) return -1;
     BwdBn bwd;
     bwd.xc = xc; bwd.stats = stats; bwd.gamma = gamma; bwd.totals = totals; bwd.dx_out = dx_out;
+    bwd.records = in_records; bwd.parts = parts; bwd.dgamma = dgamma; bwd.dbeta = dbeta;
     bwd.inv_m = 1.0f / (float)((long)N * HW * HW);
     PostBn post;
     post.mask_src = mask_src; post.xc = xc_post; post.stats = stats_post; post.records = records;
@@ -739,12 +813,15 @@ int conv3x3_tiled_dgrad_bn(hipStream_t s, const float* dz, const float* xc, cons
 // conv3x3_tiled_dgrad_bn with the d-filter convolution of the same layer in the same kernel (see WgradFused);
 // dx is not stored.  Returns -2 for shapes the fused form does not cover (then the two-kernel form applies).
 int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc, const float* stats, const float* gamma,
-                                  const float* totals, const float* w, const float* add, float* out,
+                                  const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta,
+                                  const float* w, const float* add, float* out,
                                   const float* xc_post, const float* stats_post, float* records,
                                   const float* x_in, float* partial, const float* red_partial, float* red_dw, int red_E,
                                   int red_chunks, int N, int HW, int C) {
+    if (!totals && !records_inline(parts, C)) return -1;
     BwdBn bwd;
     bwd.xc = xc; bwd.stats = stats; bwd.gamma = gamma; bwd.totals = totals; bwd.dx_out = nullptr;
+    bwd.records = in_records; bwd.parts = parts; bwd.dgamma = dgamma; bwd.dbeta = dbeta;
     bwd.inv_m = 1.0f / (float)((long)N * HW * HW);
     PostBn post;
     post.mask_src = x_in; post.xc = xc_post; post.stats = stats_post; post.records = records;
@@ -760,6 +837,8 @@ int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc
     if (C == 32 && HW == 16) return launch<32, 16, 8, 1, true, 3, true, true>(s, dz, w, add, out, nullptr, N, PreBn(), post, bwd, rj, wg);
     return -2;
 }
+
+bool conv3x3_records_inline(int parts, int C) { return parts >= 1 && records_inline(parts, C); }
 
 // Number of per-workgroup statistics records (tiles of equal size) the forward kernel emits, 0 if the
 // shape is not covered by it.

@@ -355,21 +355,28 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     };
     // dz (masked, records summed into tot) -> through BN (xc, st, gamma) -> dx -> d-input (+ add) with the mask / records
     // epilogue (mask_src = x_in, xc_post, st_post -> records) into out, and d-filter (x_in, dx) into dw (pending).
-    // nrec != NULL: the records just written are summed into ntot / ndgamma / ndbeta for the next layer.
-    auto regular_layer = [&](const float* dz, const float* xc, const float* st, const float* gamma, const float* tot,
+    // The sums of dz: in_rec / in_parts / in_dgamma / in_dbeta, added up by the kernel itself where they are few, else already in
+    // tot (ready) or by a launch here.  sum_next: the records just written are summed into ntot / ndgamma / ndbeta for the
+    // next layer (not where that layer does it itself).
+    auto regular_layer = [&](const float* in_rec, int in_parts, float* in_dgamma, float* in_dbeta, bool ready,
+                             const float* dz, const float* xc, const float* st, const float* gamma, float* tot,
                              const float* wt, const float* add, float* out, const float* x_in, const float* xc_post,
                              const float* st_post, float* records, float* dw, int H, int Cc, bool sum_next, int nparts,
                              float* ntot, float* ndgamma, float* ndbeta) -> int {
         float* out_scr = (pend.on && pend.partial == scrs[0]) ? scrs[1] : scrs[0];
         const float* rp = pend.on ? pend.partial : nullptr;
+        const bool own_sums = dsspk_conv_records_inline(in_parts, Cc) != 0;
+        if (!own_sums && !ready) RUN(dsspk_bn_bwd_totals(s, in_rec, in_parts, Cc, tot, in_dgamma, in_dbeta));
+        const float* totals = own_sums ? nullptr : tot;
+        sum_next = sum_next && !dsspk_conv_records_inline(nparts, Cc);
         int chunks = dsspk_conv_bwd_fused_chunks(m, H, Cc);
         if (chunks > 0) {
-            RUN(dsspk_conv_bwd_data_bn_wgrad(s, dz, xc, st, gamma, tot, wt, add, out, xc_post, st_post, records, x_in,
-                                             out_scr, rp, pend.dw, pend.E, pend.chunks, m, H, Cc));
+            RUN(dsspk_conv_bwd_data_bn_wgrad_records(s, dz, xc, st, gamma, totals, in_rec, in_parts, in_dgamma, in_dbeta, wt, add, out, xc_post,
+                                                     st_post, records, x_in, out_scr, rp, pend.dw, pend.E, pend.chunks, m, H, Cc));
             if (sum_next) RUN(dsspk_bn_bwd_totals(s, records, nparts, Cc, ntot, ndgamma, ndbeta));
         } else {
-            RUN(dsspk_conv_bwd_data_bn(s, dz, xc, st, gamma, tot, g1, wt, add, out, x_in, xc_post, st_post, records,
-                                       rp, pend.dw, pend.E, pend.chunks, m, H, Cc));
+            RUN(dsspk_conv_bwd_data_bn_records(s, dz, xc, st, gamma, totals, in_rec, in_parts, in_dgamma, in_dbeta, g1, wt, add, out, x_in,
+                                               xc_post, st_post, records, rp, pend.dw, pend.E, pend.chunks, m, H, Cc));
             RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, sum_next ? records : nullptr,
                                             nparts, Cc, ntot, ndgamma, ndbeta, &chunks));
         }
@@ -388,8 +395,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         bool tot1 = false;                                   // sums of BN1's records are in totA
         // ---- BN2 + conv2: g0 = dz2 -> g1 = d conv2 output, g2 = dz1 = d a1 * [a1 > 0] (+ BN1's records in bscr)
         if (parts0 > 0 && parts1 > 0) {
-            if (!tot0) RUN(dsspk_bn_bwd_totals(s, recB0, parts0, B.cout, totB, g + B.g2, g + B.b2));
-            RUN(regular_layer(g0, F(B.c2), F(B.st2), w + B.g2, totB, w + B.w2, nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr,
+            RUN(regular_layer(recB0, parts0, g + B.g2, g + B.b2, tot0, g0, F(B.c2), F(B.st2), w + B.g2, totB, w + B.w2, nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr,
                               g + B.w2, Ho, B.cout, fused1, parts1, totA, g + B.g1, g + B.b1));
             tot1 = fused1;
         } else {
@@ -410,10 +416,9 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         if (fused1) {
             const float* pc = bi ? F(P->blocks[bi - 1].c2) : F(P->stem_c);
             const float* pst = bi ? F(P->blocks[bi - 1].st2) : F(P->stem_st);
-            if (!tot1) RUN(dsspk_bn_bwd_totals(s, bscr, parts1, B.cout, totA, g + B.g1, g + B.b1));
             // output in place over the shortcut's gradient g0; g0 stays the gradient w.r.t. the previous block's output
             const bool next_fused = bi > 0;                  // the previous block's conv2 has this convolution's shape
-            RUN(regular_layer(g2, F(B.c1), F(B.st1), w + B.g1, totA, w + B.w1, g0, g0, xin, pc, pst, recB0, g + B.w1, B.H, B.cin,
+            RUN(regular_layer(bscr, parts1, g + B.g1, g + B.b1, tot1, g2, F(B.c1), F(B.st1), w + B.g1, totA, w + B.w1, g0, g0, xin, pc, pst, recB0, g + B.w1, B.H, B.cin,
                               next_fused, partsp, totB, next_fused ? g + P->blocks[bi - 1].g2 : nullptr,
                               next_fused ? g + P->blocks[bi - 1].b2 : nullptr));
             parts0 = partsp;

@@ -30,3 +30,45 @@ def test_error_of_forward_and_input_gradient(oracle_nn, N, H, C, offset):
     dxo, _, _ = oracle_nn.conv2d_bwd(x64, w64, dy64, 1, 1, True)
     assert rel_l2(host(y), yo) < 2e-7 and max_abs(host(y), yo) < 2e-6
     assert rel_l2(host(dx), dxo) < 2e-7 and max_abs(host(dx), dxo) < 2e-6
+
+
+# one image; the largest batch whose records every workgroup adds up itself (2048 / C of them), and one more
+@pytest.mark.parametrize("N,H,C", [(1, 32, 16), (5, 32, 16), (32, 32, 16), (33, 32, 16), (1, 16, 32), (32, 16, 32), (33, 16, 32), (1, 8, 64),
+                                   (32, 8, 64), (33, 8, 64)])
+def test_batchnorm_sums_taken_from_records(N, H, C):
+    """The backward kernels with their batch norm's sums added up inside against the same kernels behind dsspk_bn_bwd_totals.  The sums
+    are over the same records in another order: 1e-6 of the scale of their terms; outputs depend on them linearly."""
+    import torch
+    g = np.random.default_rng(N + C)
+    L, s = B.lib(), stream_ptr()
+    parts = L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1)
+    assert L.dsspk_conv_records_inline(parts, C) == (1 if N <= 32 else 0)
+    f = lambda *sh: dev(g.standard_normal(sh).astype(np.float32))
+    dz, xc, xp, xin, add, w = f(N, H, H, C), f(N, H, H, C), f(N, H, H, C), torch.relu(f(N, H, H, C)), f(N, H, H, C), f(3, 3, C, C)
+    stats, statsp = torch.cat([f(C), f(C).abs() + 0.5]), torch.cat([f(C), f(C).abs() + 0.5])
+    gamma, rin = f(C), f(parts, C, 2)
+    tot, dgam, dbet = empty(2 * C), empty(C), empty(C)
+    assert L.dsspk_bn_bwd_totals(s, rin.data_ptr(), parts, C, tot.data_ptr(), dgam.data_ptr(), dbet.data_ptr()) == 0
+    fused = L.dsspk_conv_bwd_fused_chunks(N, H, C)
+    res = []
+    for totals in (tot, None):
+        out, dx, rout, part = empty((N, H, H, C)), empty((N, H, H, C)), empty((parts, C, 2)), empty(max(1, fused) * 9 * C * C)
+        dg, db = empty(C), empty(C)
+        common = (s, dz.data_ptr(), xc.data_ptr(), stats.data_ptr(), gamma.data_ptr(), totals.data_ptr() if totals is not None else None,
+                  rin.data_ptr(), parts, dg.data_ptr(), db.data_ptr())
+        if fused:
+            rc = L.dsspk_conv_bwd_data_bn_wgrad_records(*common, w.data_ptr(), add.data_ptr(), out.data_ptr(), xp.data_ptr(), statsp.data_ptr(),
+                                                        rout.data_ptr(), xin.data_ptr(), part.data_ptr(), None, None, 0, 0, N, H, C)
+        else:
+            rc = L.dsspk_conv_bwd_data_bn_records(*common, dx.data_ptr(), w.data_ptr(), add.data_ptr(), out.data_ptr(), xin.data_ptr(),
+                                                  xp.data_ptr(), statsp.data_ptr(), rout.data_ptr(), None, None, 0, 0, N, H, C)
+        if totals is None and N > 32:
+            assert rc == -1
+            return
+        assert rc == 0
+        if totals is None:
+            scale = np.sqrt(parts)
+            assert np.max(np.abs(host(dg) - host(dgam))) < 1e-6 * scale and np.max(np.abs(host(db) - host(dbet))) < 1e-6 * scale
+        res.append([host(t) for t in ((out, rout, part) if fused else (out, rout, dx))])
+    for a, b in zip(*res):
+        assert rel_l2(b, a) < 2e-6 and max_abs(b, a) < 2e-5

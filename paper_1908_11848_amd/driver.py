@@ -69,10 +69,16 @@ class Schedule:
             if self.aggregate:
                 group = self._same_time_group(n_pushes - done)
                 if group is not None:
-                    done += self._push_group(*group)
+                    n = self._push_group(*group)
+                    self.aggregated += n
+                    done += n
                     continue
             T, p = heapq.heappop(self.heap)
             self.T_end = T
+            if self._may_release(p):
+                self._push_group(T, [p])
+                done += 1
+                continue
             pulled_version = None
             if self.fused_pull and not (self.quota is not None and self.count[p] + 1 >= self.quota):
                 ok, released, rstar, grant, pulled, v_now = B.dssp_push_pull(self.ctx, p, self.gp(p), T, K, self.pd(p))
@@ -102,6 +108,17 @@ class Schedule:
 
     MAX_GROUP = 16                      # DSSPK_APPLY_MANY_MAX
 
+    MAX_SNAPSHOTS = 32                  # DSSPK_APPLY_MANY_MAX_DST
+
+    def _may_release(self, p):
+        """fused_pull: whether worker p's push can release waiting workers (somebody waits, and p alone is slowest).  Such a push goes
+        through dssp_push_many, whose kernel writes the snapshots of all who go on: 4 bytes a parameter each instead of the
+        8 of a pull of their own (25 M parameters, 16 workers: 1224 -> 1140 us for 16 pushes)."""
+        if not self.fused_pull or self.quota is not None or len(self.heap) + 1 >= self.K or self.K > self.MAX_SNAPSHOTS:
+            return False
+        t_min = min(self.count)
+        return self.count[p] == t_min and self.count.count(t_min) == 1
+
     def _same_time_group(self, room):
         """The pushes at the head of the heap that share its smallest timestamp, if there are at least two (at most
         `room`, at most MAX_GROUP; the rest of a larger group follows in the next call)."""
@@ -119,7 +136,6 @@ class Schedule:
         ok, released, rstar, grant, pv = B.dssp_push_many(self.ctx, workers, [self.gp(p) for p in workers], T, K,
                                                           [self.pd(q) for q in range(K)])
         self.T_end = T
-        self.aggregated += len(workers)
         t, r, _, v_end = B.dssp_clock(self.ctx, K) if log is not None else (None, None, None, None)
         for j, p in enumerate(workers):
             self.version += 1

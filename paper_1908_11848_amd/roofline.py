@@ -12,8 +12,8 @@ what the hardware-counter passes are taken on:
         -- python3 -m paper_1908_11848_amd.roofline
 
 Algorithmic work per launch, with T = 4 * N * H * H * C bytes (one activation tensor of the stage) and
-W = (4/9) * 2 * N * H * H * C * 9 * C FLOP, the matrix-core work of one 3x3 convolution by minimal filtering
-(16 instead of 36 multiplications per 2x2 tile and channel pair; the direct form would be 9/4 W):
+W = 6 * 2 * N * H * H * C * 9 * C FLOP, what the bf16 matrix cores execute for one 3x3 convolution with fp32 operands (three bf16
+terms each, six products of terms per product):
     conv_fwd       plain forward convolution + statistics records            W,  2 T  (read x, write y)
     conv_fwd_bn    records merge + forward convolution with BN + shortcut    W,  4 T  (read z, shortcut; write a, y)
                    + ReLU folded into its loader (2 kernels)
@@ -28,9 +28,8 @@ W = (4/9) * 2 * N * H * H * C * 9 * C FLOP, the matrix-core work of one 3x3 conv
     apply / pull   server update and snapshot copy                               12 / 8 bytes per parameter
     apply_pull     update + the pusher's snapshot in one pass                    16 bytes per parameter
     apply_many4    four simultaneous pushes + one snapshot in one pass           28 bytes per parameter (56 one by one)
-A case is bound by whichever of its two floors is higher: its FLOP at 157.3 TFLOP/s (fp32 matrix cores: 256 CUs
-x 4 SIMDs x 64 FLOP/cycle x 2.4 GHz) or its bytes at 8 TB/s (HBM); with minimal filtering that is HBM for every
-3x3 case.  HBM traffic per launch (`traffic`)
+A case is bound by whichever of its two floors is higher: its FLOP at 2517 TFLOP/s (bf16 matrix cores: 256 CUs
+x 4 SIMDs x 1024 FLOP/cycle x 2.4 GHz) or its bytes at 8 TB/s (HBM).  HBM traffic per launch (`traffic`)
 comes from profiles/traffic_counters.json (counter values scaled by what the same counter reads
 for the snapshot-copy kernel of known size) and is reported as null as soon as the kernel's
 source file differs from the one the counters were taken on.
@@ -40,7 +39,7 @@ import hashlib
 import json
 import os
 
-PEAK_MFMA_F32 = 157.3e12
+PEAK_MFMA = 2516.6e12
 PEAK_HBM = 8.0e12
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _COUNTERS = os.path.join(os.path.dirname(_HERE), "profiles", "traffic_counters.json")
@@ -48,7 +47,7 @@ _COUNTERS = os.path.join(os.path.dirname(_HERE), "profiles", "traffic_counters.j
 STAGES = ((32, 16), (16, 32), (8, 64))      # (height = width, channels) of the three ResNet stages
 BATCH = 128
 N_PARAMS = 1_733_812                         # ResNet-110, 10 classes
-SOURCES = ("k_conv3x3.hip", "k_conv.hip", "k_elem.hip", "k_server.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp")
+SOURCES = ("k_conv3x3.hip", "k_conv.hip", "k_elem.hip", "k_server.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp")
 
 
 def case_list(n_params=N_PARAMS):
@@ -99,7 +98,7 @@ def _traffic(key, srcs):
     return int(e["fetch_bytes"] + e["write_bytes"])
 
 
-_CONV_SRCS = ("k_conv3x3.hip", "k_conv.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp")
+_CONV_SRCS = ("k_conv3x3.hip", "k_conv.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp")
 
 
 def _conv_cases(H, C, dev):
@@ -127,7 +126,7 @@ def _conv_cases(H, C, dev):
     E = 9 * C * C
     ch = ctypes.c_int(0)
     T = 4.0 * M * C
-    F = 2.0 * M * C * 9 * C * 4.0 / 9.0          # executed on the matrix cores (minimal filtering)
+    F = 6 * 2.0 * M * C * 9 * C                  # executed on the matrix cores (six products of bf16 terms)
     fwd = lambda s: L.dsspk_conv_fwd(s, x.data_ptr(), w.data_ptr(), None, z.data_ptr(), N, H, H, C, C, 3, 3, 1, 1, 0, recA.data_ptr())
     fwd_bn = lambda s: L.dsspk_conv_fwd_prebn(s, z.data_ptr(), recA.data_ptr(), parts, gamma.data_ptr(), beta.data_ptr(), 1e-5,
                                               sc.data_ptr(), a.data_ptr(), stats_o.data_ptr(), w.data_ptr(), y.data_ptr(),
@@ -147,6 +146,7 @@ def _conv_cases(H, C, dev):
                                                      E, chunks, N, H, C)
     keep = (x, z, sc, a, y, dz, xc, add, act, xcp, dx, w, gamma, beta, stats, stats_o, tot, dgam, dbet, recA, recB, rec, scr, scr2, dw, ch)
     part_bytes = 4.0 * chunks * E
+    own_bytes = 4.0 * ((N + 3) // 4) * E if C == 64 else part_bytes      # partial sums the d-filter kernel of the last stage writes
     desc = "%d->%d @%dx%d, batch %d" % (C, C, H, H, N)
     head = [
         ("conv_fwd_%dx%dx%d" % (H, H, C), "conv 3x3 forward + statistics records " + desc, F, 2 * T, fwd, None, keep),
@@ -160,7 +160,7 @@ def _conv_cases(H, C, dev):
     return head + [
         ("conv_dgrad_bn_%dx%dx%d" % (H, H, C), "conv 3x3 d-input with BN backward in its loader, shortcut gradient, ReLU mask + "
          "sum records in its epilogue, carrying a d-filter reduction " + desc, F, 7 * T + part_bytes + 4.0 * E, dgrad_bn, wgrad, keep),
-        ("conv_wgrad_%dx%dx%d" % (H, H, C), "conv 3x3 d-filter stage 1, carrying the BN sums " + desc, F, 2 * T + part_bytes, wgrad, None, keep),
+        ("conv_wgrad_%dx%dx%d" % (H, H, C), "conv 3x3 d-filter stage 1, carrying the BN sums " + desc, F, 2 * T + own_bytes, wgrad, None, keep),
     ]
 
 
@@ -232,9 +232,9 @@ def cases(dev, n_params=N_PARAMS):
 
 def _entry(case, t):
     key, desc, flops, nbytes, fn, prep, srcs, keep = case
-    t_mfma, t_hbm = flops / PEAK_MFMA_F32, nbytes / PEAK_HBM
+    t_mfma, t_hbm = flops / PEAK_MFMA, nbytes / PEAK_HBM
     if t_mfma > t_hbm:
-        bound, achieved, peak, unit = "mfma", flops / t / 1e12, PEAK_MFMA_F32 / 1e12, "TFLOP/s"
+        bound, achieved, peak, unit = "mfma", flops / t / 1e12, PEAK_MFMA / 1e12, "TFLOP/s"
     else:
         bound, achieved, peak, unit = "hbm", nbytes / t / 1e9, PEAK_HBM / 1e9, "GB/s"
     return {"kernel": desc, "bound": bound, "achieved": round(achieved, 3), "peak": peak, "unit": unit,
@@ -261,10 +261,12 @@ def _alexnet_conv2_case(dev):
     w = torch.randn(5, 5, C, C, device=dev) * 0.05
     b = torch.zeros(C, device=dev)
     y = torch.empty(N, H, H, C, device=dev)
-    fn = lambda s: L.dsspk_conv_fwd(s, x.data_ptr(), w.data_ptr(), b.data_ptr(), y.data_ptr(), N, H, H, C, C, 5, 5, 1, 2, 1, None)
-    flops = 2.0 * N * H * H * C * 25 * C
-    return ("alexnet_conv2_fwd", "conv 5x5 forward + bias + ReLU 64->64 @15x15, batch %d (implicit GEMM)" % N, flops,
-            2 * 4.0 * N * H * H * C, fn, None, ("k_conv.hip", "mma.hpp"), (x, w, b, y))
+    planes = torch.empty(L.dsspk_conv_split_filter_bytes(C, C, 5), dtype=torch.uint8, device=dev)
+    prep = lambda s: L.dsspk_conv_split_filters(s, w.data_ptr(), planes.data_ptr(), None, C, C, 5)
+    fn = lambda s: L.dsspk_conv_split_fwd(s, x.data_ptr(), planes.data_ptr(), b.data_ptr(), y.data_ptr(), N, H, H, C, C, 5, 2, 1)
+    flops = 6 * 2.0 * N * H * H * C * 25 * C
+    return ("alexnet_conv2_fwd", "conv 5x5 forward + bias + ReLU 64->64 @15x15, batch %d (three bf16 terms)" % N, flops,
+            2 * 4.0 * N * H * H * C, fn, prep, ("k_conv_split.hip", "split.hpp"), (x, w, b, y, planes))
 
 
 def measure(workload, em):
@@ -276,6 +278,8 @@ def measure(workload, em):
     elif workload.startswith("alexnet"):
         case = _alexnet_conv2_case(em.dev)
         top = case[0]
+        case[5](em.streams[0].cuda_stream)
+        em.streams[0].synchronize()
         allm[top] = _entry(case, _time(case[4], em.streams[0]))
     else:
         top = "apply_%d" % em.n

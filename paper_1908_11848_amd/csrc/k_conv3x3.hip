@@ -195,6 +195,8 @@ struct WgradFused {
 
 // add and dst may be the same buffer (every element is read and written by the same lane); with PRE == 3
 // dst must differ from src, whose halo rows other workgroups still read.
+// Wavefronts per SIMD the register allocation aims at: 4 (128 registers) fit the 16-channel kernels, 3 (168) the others; with 4 there
+// the compiler spills up to 20.
 template <int C, bool WG>
 constexpr int min_waves() { return C == 16 && !WG ? 4 : 3; }
 
@@ -207,9 +209,10 @@ __device__ __forceinline__ float sum16(float v) {
 }
 __device__ __forceinline__ float4 sum16(float4 v) { return make_float4(sum16(v.x), sum16(v.y), sum16(v.z), sum16(v.w)); }
 
-// Records of a tensor small enough for every workgroup of its consumer to merge them itself, INLINE_RECORDS / C of them at most.  A
-// kernel of its own for that takes 4 us of a stream's time; reading the records takes every workgroup 0.5 us at 16 KB and
-// as long as that kernel at the 64 KB of batch 128 (where 512 workgroups doing so lost 2 % of a step).
+// Records of a tensor small enough for every workgroup of its consumer to merge them itself, INLINE_RECORDS / C of them at most, so
+// up to batch 32.  A kernel of its own for that takes 4 us of a stream's time.  20-layer network, four workers, a round with such
+// kernels and without: batch 16 876 -> 821 us, batch 32 945 -> 894 us.  Twice as many would still win at batch 64 (1135 -> 1103 us),
+// but their loads cost the smaller batches 2 % and, at four wavefronts a SIMD, spilled registers of the 16-channel kernels at every batch.
 constexpr int INLINE_RECORDS = 2048, RECORDS_PER_THREAD = INLINE_RECORDS / THREADS;
 constexpr bool records_inline(int parts, int C) { return parts * C <= INLINE_RECORDS; }
 

@@ -2,6 +2,7 @@
 // filters) with fp32 arithmetic on the bf16 matrix cores (split.hpp): forward, gradient w.r.t. the input (the same kernel on
 // a transposed, reversed filter) and gradient w.r.t. the filter and bias.
 #include "jobs.hpp"
+#include "mma.hpp"
 #include "split.hpp"
 #include "../../include/dssp_kernels.h"
 
@@ -20,7 +21,11 @@ __device__ __forceinline__ int xcd_tile(int block, int n_blocks) {
 // Filter planes in operand order: [step][16 result channels][plane][lane] of 16 bytes, step = (tap, 32 reduction channels),
 // lane (l16, q) holding the reduction channels 8 q .. 8 q + 7 of result channel l16.  A wavefront then fetches an operand
 // as one contiguous KiB.  Written once per step, read by every workgroup of the layer's convolutions.
+// A value that the terms cannot hold (2^103 or more, infinite, NaN) has NaN as its leading term, which spoils every sum it enters, and
+// its two halves in the place of the others, where the computation in fp32 finds it.
 //   TR = false: result channel = output channel;  true (d-input): result = input channel, taps reversed
+constexpr float WIDE = 0x1p103f;
+constexpr unsigned BF16_NAN = 0x7fc0u;
 struct Frag {
     const float* w;
     uint4* out;
@@ -38,13 +43,28 @@ __device__ __forceinline__ void filter_frag(const Frag& f, bool tr, long idx) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
         v[j] = tr ? f.w[((long)(f.taps - 1 - tap) * f.IC + rs) * f.OC + rc + j] : f.w[((long)tap * f.IC + rc + j) * f.OC + rs];
+    float t[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t[j] = v[j] * split::SCALE;
 #pragma unroll
     for (int p = 0; p < split::PLANES; ++p) {
-        uint4 u;
-        u.x = split::take(v[0], v[1]); u.y = split::take(v[2], v[3]);
-        u.z = split::take(v[4], v[5]); u.w = split::take(v[6], v[7]);
-        f.out[(r * split::PLANES + p) * 64 + lane] = u;
+        unsigned u[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[j] = split::take(t[2 * j], t[2 * j + 1]);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (fabsf(v[j]) < WIDE) continue;               // (not so for NaN)
+            const unsigned bits = __float_as_uint(v[j]), part = p == 0 ? BF16_NAN : p == 1 ? bits >> 16 : bits & 0xffffu;
+            u[j / 2] = j % 2 ? (u[j / 2] & 0xffffu) | part << 16 : (u[j / 2] & 0xffff0000u) | part;
+        }
+        f.out[(r * split::PLANES + p) * 64 + lane] = make_uint4(u[0], u[1], u[2], u[3]);
     }
+}
+
+// the value again from its terms (16 bits each)
+__device__ __forceinline__ float filter_value(unsigned t0, unsigned t1, unsigned t2) {
+    if ((t0 & 0x7fffu) == BF16_NAN) return __uint_as_float(t1 << 16 | t2);
+    return (__uint_as_float(t0 << 16) + (__uint_as_float(t1 << 16) + __uint_as_float(t2 << 16))) * (1.f / split::SCALE);
 }
 
 __global__ __launch_bounds__(THREADS) void filter_planes_kernel(Frag fwd, Frag bwd, long n) {
@@ -101,7 +121,8 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
     long out[W::TP];
 #pragma unroll
     for (int t = 0; t < W::TP; ++t) {
-        const int p = (wp * W::TP + t) * 16 + l16;
+        int p = (wp * W::TP + t) * 16 + l16;
+        asm("" : "+v"(p));              // or the compiler keeps what it worked out above for every tile in registers through the product loop
         const int per = g.R * g.OW, gi = p / per, rest = p - gi * per, r = rest / g.OW, c = rest - r * g.OW;
         const bool ok = gi < g.G && n0 + gi < g.N && r0 + r < g.OH;
         base[t] = (ok ? ((gi * TH + r) * TW + c) * PITCH : 0) + 16 * q + 64 * half;
@@ -148,7 +169,7 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
                 const int idx = i0 + e * NT;
                 if (idx >= total) break;
                 uint2 pl[split::PLANES];
-                split::split4(v[e], pl);
+                split::split4(split::scaled(v[e]), pl);
 #pragma unroll
                 for (int p = 0; p < split::PLANES; ++p)
                     *reinterpret_cast<uint2*>(lds + idx / (ICB / 4) * PITCH + p * PLANE + 8 * (idx % (ICB / 4))) = pl[p];
@@ -190,11 +211,50 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
         if (relu) { v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f); v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f); }
         *reinterpret_cast<float4*>(dst + at + co) = v;
     };
+    // Sums beyond the range of the scaled terms: the tile from the operands in memory.  A step takes 32 channels of a tap, a lane the
+    // eight of its filter fragment.
+    auto direct = [&](int ct, int t) {
+        int p = (wp * W::TP + t) * 16 + l16;
+        asm("" : "+v"(p));              // or the compiler keeps what it worked out above for every tile in registers through the product loop
+        const int per = g.R * g.OW, gi = p / per, rest = p - gi * per, r = rest / g.OW, c = rest - r * g.OW;
+        const bool ok = gi < g.G && n0 + gi < g.N && r0 + r < g.OH;
+        floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+        for (int tap = 0; tap < KS * KS; ++tap) {
+            const int h = r0 + r + tap / KS - g.pad, w = c + tap % KS - g.pad;
+            const bool in = ok && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
+            const float* px = src + (((long)(n0 + gi) * g.H + h) * g.W + w) * g.IC + 8 * q;
+            for (int c32 = 0; c32 < steps_c; ++c32) {
+                float a[8], b[8];
+                unsigned u[split::PLANES][4];
+#pragma unroll
+                for (int k = 0; k < split::PLANES; ++k)
+                    *reinterpret_cast<uint4*>(u[k]) = wf[((tap * steps_c + c32) * tiles_c + ct) * (split::PLANES * 64) + k * 64 + lane];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    a[j] = filter_value(u[0][j / 2] >> 16 * (j & 1) & 0xffffu, u[1][j / 2] >> 16 * (j & 1) & 0xffffu, u[2][j / 2] >> 16 * (j & 1) & 0xffffu);
+                    b[j] = in ? px[32 * c32 + j] : 0.f;
+                }
+                sum = split::product32(a, b, sum);
+            }
+        }
+        mma::drain();
+        finish(sum, ct, ok ? (((long)(n0 + gi) * g.OH + r0 + r) * g.OW + c) * g.OC : -1);
+    };
+    float bad = 0.f;
     if constexpr (W::HALVES == 1) {
 #pragma unroll
         for (int i = 0; i < W::TC; ++i)
 #pragma unroll
-            for (int t = 0; t < W::TP; ++t) finish(acc[i][t], ct0 + i, out[t]);
+            for (int t = 0; t < W::TP; ++t) bad = split::spoil(acc[i][t], bad);
+        if (split::spoiled(bad)) {
+#pragma unroll 1
+            for (int i = 0; i < W::TC * W::TP; ++i) direct(ct0 + i / W::TP, i % W::TP);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < W::TC; ++i)
+#pragma unroll
+            for (int t = 0; t < W::TP; ++t) finish(acc[i][t] * split::UNSCALE, ct0 + i, out[t]);
     } else {        // the other half's share of the channel tile this wavefront finishes, against its own share of the other one
         static_assert(W::HALVES == 1 || W::TC == 2, "a channel tile each");
         __syncthreads();
@@ -207,7 +267,17 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
         }
         __syncthreads();
 #pragma unroll
-        for (int t = 0; t < W::TP; ++t) finish(acc[0][t] + ex[((wave ^ 4) * W::TP + t) * 64 + lane], ct0 + half, out[t]);
+        for (int t = 0; t < W::TP; ++t) {
+            acc[0][t] += ex[((wave ^ 4) * W::TP + t) * 64 + lane];
+            bad = split::spoil(acc[0][t], bad);
+        }
+        if (split::spoiled(bad)) {
+#pragma unroll 1
+            for (int t = 0; t < W::TP; ++t) direct(ct0 + half, t);
+            return;
+        }
+#pragma unroll
+        for (int t = 0; t < W::TP; ++t) finish(acc[0][t] * split::UNSCALE, ct0 + half, out[t]);
     }
 }
 
@@ -337,19 +407,21 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         rv[e] = e < NX ? split::load4(xb, off[e] + 4u * (unsigned)(fr * g.W * g.IC)) : split::load4(db, off[e] + 4u * (unsigned)(fr * g.OW * g.OC));
     };
     int fetched = 1;                                           // tiles fetched so far
-    auto advance = [&]() {                                     // past the chunk's end the last tile is fetched again (never used)
+    auto advance = [&]() {                                     // past the chunk's end: zeros, which change no bias sum
         if (i0 + fetched < i1) {
             fr += g.R;
             if (fr >= g.bands * g.R) { fr = 0; ++fn; }
+            image();
+        } else {
+            xb = split::buffer(x, 0); db = split::buffer(dy, 0);
         }
-        image();
         ++fetched;
     };
-    auto stage = [&](int e, char* buf, float count) {          // count: 1, or 0 if the tile is not to enter the bias sums
+    auto stage = [&](int e, char* buf) {
         const float4 v = rv[e];
-        if (e >= NX) { sb.x = fmaf(v.x, count, sb.x); sb.y = fmaf(v.y, count, sb.y); sb.z = fmaf(v.z, count, sb.z); sb.w = fmaf(v.w, count, sb.w); }
+        if (e >= NX) { sb.x += v.x; sb.y += v.y; sb.z += v.z; sb.w += v.w; }
         uint2 pl[split::PLANES];
-        split::split4(v, pl);
+        split::split4(split::scaled(v), pl);
         const int idx = tid + (e < NX ? e : e - NX) * CTHREADS;
         if (e < NX && idx >= WG_XPX * 8) return;
         char* to = e < NX ? buf + (idx >> 3) * XPITCH + 8 * (idx & 7) : buf + XBYTES + (idx >> 4) * DPITCH + 8 * (idx & 15);
@@ -368,7 +440,7 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         for (int e = 0; e < NE; ++e) fetch(e);
         advance();
 #pragma unroll
-        for (int e = 0; e < NE; ++e) stage(e, lds, 1.f);
+        for (int e = 0; e < NE; ++e) stage(e, lds);
 #pragma unroll
         for (int e = 0; e < NE; ++e) fetch(e);
         advance();
@@ -379,7 +451,6 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     for (int item = i0; item < i1; ++item) {
         const char* cur = lds + ((item - i0) & 1) * BUF;
         char* nxt = lds + ((item - i0 + 1) & 1) * BUF;
-        const float count = item + 1 < i1 ? 1.f : 0.f;
 #pragma unroll
         for (int p = 0; p < split::PLANES; ++p) { dv[0][p] = dn[0][p]; dv[1][p] = dn[1][p]; xv[0][0][p] = xn[0][p]; }
 #pragma unroll
@@ -397,7 +468,7 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
             constexpr int SS = KS - 1;                         // steps that stage the next tile
             if (kw < SS) {
 #pragma unroll
-                for (int e = kw * NE / SS; e < (kw + 1) * NE / SS; ++e) stage(e, nxt, count);
+                for (int e = kw * NE / SS; e < (kw + 1) * NE / SS; ++e) stage(e, nxt);
             }
             split::product(dv, xv[kw & 1], acc[kw]);
 #pragma unroll
@@ -412,6 +483,36 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
             }
         }
         advance();
+    }
+    float bad = 0.f;
+#pragma unroll
+    for (int kw = 0; kw < KS; ++kw)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) bad = split::spoil(acc[kw][i][0], bad);
+    if (split::spoiled(bad)) {      // beyond the range of the scaled terms: this wavefront's sums from the operands in memory, four pixels a step
+#pragma unroll
+        for (int kw = 0; kw < KS; ++kw) acc[kw][0][0] = acc[kw][1][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int item = i0; item < i1; ++item) {
+            const int n = item / g.bands, row0 = item % g.bands * g.R;
+            for (int p = 32 * run + q; p < 32 * run + 32; p += 4) {
+                const int r = p / g.OW, c = p - r * g.OW;
+                const bool ok = p < P && row0 + r < g.OH;
+                const float* dp = dy + (((long)n * g.OH + row0 + r) * g.OW + c) * g.OC + co0 + co_w + l16;
+                const float d0[1] = {ok ? dp[0] : 0.f}, d1[1] = {ok ? dp[16] : 0.f};
+#pragma unroll
+                for (int kw = 0; kw < KS; ++kw) {
+                    const int h = row0 + r + kh - g.pad, w = c + kw - g.pad;
+                    const bool in = ok && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
+                    const float xs[1] = {in ? x[(((long)n * g.H + h) * g.W + w) * g.IC + ci0 + ci_w + l16] : 0.f};
+                    acc[kw][0][0] = split::product32(d0, xs, acc[kw][0][0]);
+                    acc[kw][1][0] = split::product32(d1, xs, acc[kw][1][0]);
+                }
+            }
+        }
+        mma::drain();
+    } else {
+#pragma unroll
+        for (int kw = 0; kw < KS; ++kw) { acc[kw][0][0] *= split::UNSCALE; acc[kw][1][0] *= split::UNSCALE; }
     }
     const long E = (long)KS * KS * g.IC * g.OC;
     float* outp = partial + blockIdx.x * (E + (with_bias ? g.OC : 0));

@@ -14,8 +14,13 @@
 // Accuracy, against float64 on random data: relative error 1.6e-7 at K = 160 (fp32 MFMA 2.4e-7), 5.5e-7 at K = 1600
 // (6.8e-7); with all nine products the same to two digits.
 //
-// Range: as fp32 down to about 1e-33 (below that x2, then x1, leave bf16's subnormal range and the product keeps fewer
-// bits); an infinite value or one above 3.39e38 yields NaN.
+// Range: all of fp32's.  bf16 has fp32's exponents, so the small terms of a value below 1e-33 would be subnormal or lost.  Therefore
+// the terms are those of 2^24 x: every fp32 value, subnormal ones included, is a multiple of 2^-149, its terms are multiples of 2^-125
+// and none of them is subnormal.  A sum of products then carries 2^48, which comes off at the end; powers of two commute with every
+// rounding, so ordinary results are the same bits as without them.  At the upper end an operand of 2^103 (1e31) or more, a result
+// above 2^79 (6e23), an infinity or a NaN makes the scaled sum infinite or NaN (nothing added to such a sum makes it finite
+// again).  A wavefront that finds one among its sums computes its tiles again from the unscaled operands on the fp32 matrix
+// cores (product32): slower, but such values belong to networks that have diverged.
 #pragma once
 #include "common.hpp"
 
@@ -36,7 +41,26 @@ __device__ __forceinline__ unsigned take(float& a, float& b) {
     return u;
 }
 
-// four consecutive values -> their three planes, 8 bytes each
+constexpr float SCALE = 0x1p24f, UNSCALE = 0x1p-48f;
+__device__ __forceinline__ float4 scaled(float4 v) { return make_float4(v.x * SCALE, v.y * SCALE, v.z * SCALE, v.w * SCALE); }
+
+// Sums that are infinite or NaN: `spoil` gathers them (0 or NaN), `spoiled` says whether any lane of the wavefront has one.
+__device__ __forceinline__ float spoil(const floatx4& sum, float so_far) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) so_far = fmaf(sum[v], 0.f, so_far);
+    return so_far;
+}
+__device__ __forceinline__ bool spoiled(float gathered) { return __builtin_expect(__any(gathered != 0.f) != 0, 0); }
+
+// acc += a . b on the fp32 matrix cores; a[j], b[j]: the lane's value at the same reduction index.  All lanes take part.
+template <int N>
+__device__ __forceinline__ floatx4 product32(const float (&a)[N], const float (&b)[N], floatx4 acc) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+    return acc;
+}
+
+// four consecutive values (scaled) -> their three planes, 8 bytes each
 __device__ __forceinline__ void split4(float4 v, uint2 (&p)[PLANES]) {
 #pragma unroll
     for (int i = 0; i < PLANES; ++i) p[i] = make_uint2(take(v.x, v.y), take(v.z, v.w));

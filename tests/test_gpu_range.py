@@ -1,0 +1,115 @@
+"""The convolutions that do fp32 arithmetic on the bf16 matrix cores, at the ends of fp32's range, against the oracle's direct loops in
+float64: operands near and below the smallest normal number (three bf16 terms of the value itself would hold 1e-36 in 14 bits), products
+beyond 1e35, single values above the largest bf16 number, infinities and NaN.
+
+Tolerance: as for ordinary operands, 2e-6 of the result (fp32 accumulation of up to 1600 products); a result that is not finite in fp32
+arithmetic has to be that infinity or NaN.  Padding is a zero operand: times an infinity it is NaN."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_1908_11848_amd import binding as B               # noqa: E402
+from gpu_util import dev, empty, host, stream_ptr           # noqa: E402
+import torch                                                 # noqa: E402
+
+ABOVE_BF16 = np.float32(3.395e38)       # a finite fp32 value that rounds to an infinite bf16 one
+
+
+def check(got, want, tol=2e-6):
+    got, want = np.asarray(got, dtype=np.float64).ravel(), np.asarray(want, dtype=np.float64).ravel()
+    with np.errstate(over="ignore"):
+        want32 = want.astype(np.float32)
+    assert np.array_equal(np.isnan(got), np.isnan(want32))
+    inf = np.isinf(want32)
+    assert np.array_equal(got[inf], want32[inf].astype(np.float64)) and not np.isinf(got[~inf]).any()
+    fin = np.isfinite(want32)
+    scale = np.max(np.abs(want[fin]), initial=1e-300)           # norms of values near 1e38 in float64: no overflow
+    d, w = (got[fin] - want[fin]) / scale, want[fin] / scale
+    assert np.linalg.norm(d) <= tol * max(np.linalg.norm(w), 1e-300), np.linalg.norm(d) / np.linalg.norm(w)
+    assert np.max(np.abs(d), initial=0.0) <= 10 * tol
+
+
+def operands(kind, g, a_shape, b_shape):
+    """Two operands of a product whose results are ordinary or large numbers; `kind` says what is special about the first or second."""
+    a, b = g.standard_normal(a_shape), 0.05 * g.standard_normal(b_shape)
+    scale = {"tiny-first": (1e-37, 1e6), "tiny-second": (1e6, 1e-36), "huge": (1e20, 1e15)}.get(kind, (1.0, 1.0))
+    a, b = (scale[0] * a).astype(np.float32), (scale[1] * b).astype(np.float32)
+    if kind == "special":               # in the middle of an image, far apart where there is room
+        h, w = a_shape[1] // 2, a_shape[2] // 2
+        a[0, h, w, 1] = np.inf
+        a[-1, h, w, 2] = -np.inf
+        a[0, -1, -1, 0] = ABOVE_BF16
+        if a_shape[0] > 2:
+            a[1, h, w, 0] = np.nan
+    return a, b
+
+
+KINDS = ["tiny-first", "tiny-second", "huge", "special"]
+
+
+def f64(*arrays):
+    return [x.astype(np.float64) for x in arrays]
+
+
+# every tile size of the dispatch, ragged groups of images, bands, several blocks of channels, no padding
+@pytest.mark.parametrize("case", [(1, 7, 7, 64, 64, 3, 1), (5, 15, 15, 64, 64, 5, 2), (37, 15, 15, 64, 64, 5, 2), (128, 15, 15, 64, 64, 5, 2),
+                                  (200, 7, 7, 64, 64, 3, 1), (2, 6, 9, 128, 64, 3, 1), (2, 5, 5, 64, 128, 5, 2), (3, 12, 17, 64, 64, 3, 0)],
+                         ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("kind", KINDS)
+def test_wide_convolutions(oracle_nn, case, kind):
+    N, H, W, Cin, Cout, k, pad = case
+    g = np.random.default_rng(N + H + k)
+    OH, OW = H + 2 * pad - k + 1, W + 2 * pad - k + 1
+    L, s = B.lib(), stream_ptr()
+    n_planes = L.dsspk_conv_split_filter_bytes(Cin, Cout, k) // 4
+    pf, pb = empty(n_planes), empty(n_planes)
+
+    def planes(w):
+        assert L.dsspk_conv_split_filters(s, dev(w).data_ptr(), pf.data_ptr(), pb.data_ptr(), Cin, Cout, k) == 0
+        torch.cuda.synchronize()
+
+    with np.errstate(all="ignore"):
+        x, w = operands(kind, g, (N, H, W, Cin), (k, k, Cin, Cout))
+        planes(w)
+        y = empty((N, OH, OW, Cout))
+        X = dev(x)
+        assert L.dsspk_conv_split_fwd(s, X.data_ptr(), pf.data_ptr(), None, y.data_ptr(), N, H, W, Cin, Cout, k, pad, 0) == 0
+        want = oracle_nn.conv2d_fwd(*f64(x, w), None, 1, pad)
+        check(host(y), want)
+        assert L.dsspk_conv_split_fwd(s, X.data_ptr(), pf.data_ptr(), None, y.data_ptr(), N, H, W, Cin, Cout, k, pad, 1) == 0
+        check(host(y), np.fmax(want, 0))                        # the ReLU of a NaN is 0
+        dy, w = operands(kind, g, (N, OH, OW, Cout), (k, k, Cin, Cout))
+        planes(w)
+        DY, dx = dev(dy), empty((N, H, W, Cin))
+        assert L.dsspk_conv_split_bwd_data(s, DY.data_ptr(), pb.data_ptr(), None, dx.data_ptr(), N, H, W, Cin, Cout, k, pad) == 0
+        check(host(dx), oracle_nn.conv2d_bwd(np.zeros((N, H, W, Cin)), *f64(w, dy), 1, pad, True)[0])
+        x, dy = operands(kind, g, (N, H, W, Cin), (N, OH, OW, Cout))
+        E = k * k * Cin * Cout
+        dw, scr = empty(E + Cout), empty(L.dsspk_conv_split_wgrad_scratch_floats(N, H, W, Cin, Cout, k, pad))
+        X, DY = dev(x), dev(dy)
+        assert L.dsspk_conv_split_bwd_weight(s, X.data_ptr(), DY.data_ptr(), dw.data_ptr(), 1, scr.data_ptr(), N, H, W, Cin, Cout, k, pad) == 0
+        _, dwo, dbo = oracle_nn.conv2d_bwd(*f64(x, w, dy), 1, pad, True)
+        check(host(dw)[:E], dwo)
+        check(host(dw)[E:], dbo, 2e-5)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float(ABOVE_BF16), float("nan")])
+def test_wide_convolutions_special_weight(oracle_nn, value):
+    """One weight that three terms cannot hold, in the filter planes of both passes."""
+    N, H, W, C, k, pad = 3, 15, 15, 64, 5, 2
+    g = np.random.default_rng(7)
+    x, w = (0.1 * g.standard_normal((N, H, W, C))).astype(np.float32), (0.05 * g.standard_normal((k, k, C, C))).astype(np.float32)
+    w[1, 3, 5, 40] = value
+    L, s = B.lib(), stream_ptr()
+    n_planes = L.dsspk_conv_split_filter_bytes(C, C, k) // 4
+    pf, pb, X, Wd, y, dx = empty(n_planes), empty(n_planes), dev(x), dev(w), empty(x.shape), empty(x.shape)
+    assert L.dsspk_conv_split_filters(s, Wd.data_ptr(), pf.data_ptr(), pb.data_ptr(), C, C, k) == 0
+    assert L.dsspk_conv_split_fwd(s, X.data_ptr(), pf.data_ptr(), None, y.data_ptr(), N, H, W, C, C, k, pad, 0) == 0
+    assert L.dsspk_conv_split_bwd_data(s, X.data_ptr(), pb.data_ptr(), None, dx.data_ptr(), N, H, W, C, C, k, pad) == 0
+    xp = np.pad(x, ((0, 0), (pad, pad), (pad, pad), (0, 0)))
+    with np.errstate(all="ignore"):
+        check(host(y), oracle_nn.conv2d_fwd(*f64(xp, w), None, 1, 0))
+        # the input gradient is a convolution of the padded dy with the transposed, reversed filter
+        wt = np.ascontiguousarray(w[::-1, ::-1].transpose(0, 1, 3, 2))
+        check(host(dx), oracle_nn.conv2d_fwd(*f64(xp, wt), None, 1, 0))

@@ -8,8 +8,8 @@
 // three bf16 terms.  The reduction over a filter row is then 16 wide, and both operands of both directions are plain 8-byte
 // or transposing LDS reads.
 //
-// Measured alone, batch 37 / 128 / 512: forward and pooling 10.6 / 15.9 / 57.6 us (as implicit GEMM on the fp32 matrix cores and a
-// pooling kernel 17.8 / 37.0 / 122), gradients with their reduction 13.9 / 21.8 / 52.4 us (pooling backward, d-filter and column
+// Measured alone, batch 37 / 128 / 512: forward and pooling 10.8 / 16.3 / 58.3 us (as implicit GEMM on the fp32 matrix cores and a
+// pooling kernel 17.8 / 37.0 / 122), gradients with their reduction 14.3 / 22.4 / 53.7 us (pooling backward, d-filter and column
 // sums as kernels of their own 49 / 78 / 246).  Forward at batch 128 writes 41 MB: 2.6 TB/s; the rest is the patches'
 // construction, then 4 us of matrix instructions, one after the other within a workgroup (two fit a compute unit).
 #include "jobs.hpp"
@@ -54,7 +54,7 @@ __device__ __forceinline__ void build_patches(const float* __restrict__ x, int n
         const int idx = tid + e * THREADS;
         if (idx >= TASKS) break;
         uint2 pl[split::PLANES];
-        split::split4(v[e], pl);
+        split::split4(split::scaled(v[e]), pl);
 #pragma unroll
         for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(T + (idx >> 2) * TPITCH + p * TPLANE + 8 * (idx & 3)) = pl[p];
     }
@@ -82,17 +82,19 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) vo
     float4 fr[F][1];
 #pragma unroll
     for (int k = 0; k < F; ++k) {
-        float f[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) f[i] = 4 * q + i < ROWF ? w[(k * ROWF + 4 * q + i) * CO + 16 * wave + l16] : 0.f;
-        fr[k][0] = make_float4(f[0], f[1], f[2], f[3]);
+        const float* wp = w + (k * ROWF + 4 * q) * CO + 16 * wave + l16;
+        fr[k][0] = make_float4(wp[0], wp[CO], wp[2 * CO], wp[q < 3 ? 3 * CO : 2 * CO]);         // all of them in flight together
     }
     const int co = 16 * wave + 4 * q;
     const float4 b = *reinterpret_cast<const float4*>(bias + co);
     build_patches<ROWS_F + F - 1>(x, n, r0 - PAD, T, tid);
     split::Filt<16> filt[F];
 #pragma unroll
-    for (int k = 0; k < F; ++k) filt[k] = split::filter_operand<16>(fr[k]);
+    for (int k = 0; k < F; ++k) {
+        if (q == 3) fr[k][0].w = 0.f;               // a filter row has 15 values
+        fr[k][0] = split::scaled(fr[k][0]);
+        filt[k] = split::filter_operand<16>(fr[k]);
+    }
     __syncthreads();
 
     floatx4 hi[ROWS_F][2], lo[ROWS_F][2];
@@ -107,6 +109,36 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) vo
         for (int h = 0; h < 2; ++h) op[t & 1][h] = split::pixel_operand<16, TPLANE>(base + (t * HW + 16 * h) * TPITCH);
     };
     const int rows = band == BANDS - 1 ? R : ROWS_F;
+    auto store = [&](int r, int h, const floatx4& sum, float factor) {
+        const float4 v = make_float4(fmaxf(fmaf(sum[0], factor, b.x), 0.f), fmaxf(fmaf(sum[1], factor, b.y), 0.f),
+                                     fmaxf(fmaf(sum[2], factor, b.z), 0.f), fmaxf(fmaf(sum[3], factor, b.w), 0.f));
+        const int px = 16 * h + l16;
+        if (r < R) *reinterpret_cast<float4*>(a + (((long)n * HW + r0 + r) * HW + px) * CO + co) = v;
+        *reinterpret_cast<float4*>(ring + r % 3 * RING_ROW + px * RING_PITCH + 16 * q) = v;
+    };
+    auto pool = [&](int r) {
+        if (r < 2 || r % 2) return;
+        // window row (r0 + r) / 2 - 1: the ring's three rows.  Lane (l16, q): window column l16 (15 of them), channels co ..
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (l16 < PW) {
+            float4 best = make_float4(0.f, 0.f, 0.f, 0.f);
+            uchar4 bi = make_uchar4(0, 0, 0, 0);
+#pragma unroll
+            for (int k = 0; k < 9; ++k) {        // first maximum in scan order, per channel
+                const float4 v = *reinterpret_cast<const float4*>(ring + (r - 2 + k / 3) % 3 * RING_ROW + (2 * l16 + k % 3) * RING_PITCH + 16 * q);
+                if (k == 0) { best = v; continue; }
+                if (v.x > best.x) { best.x = v.x; bi.x = (unsigned char)k; }
+                if (v.y > best.y) { best.y = v.y; bi.y = (unsigned char)k; }
+                if (v.z > best.z) { best.z = v.z; bi.z = (unsigned char)k; }
+                if (v.w > best.w) { best.w = v.w; bi.w = (unsigned char)k; }
+            }
+            const long o = (((long)n * PW + (r0 + r) / 2 - 1) * PW + l16) * (CO / 4) + co / 4;
+            pooled[o] = best;
+            arg[o] = bi;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    float bad = 0.f;
     load(0);
 #pragma unroll
     for (int t = 0; t < ROWS_F + F - 1; ++t) {
@@ -129,32 +161,57 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (r < 0 || r >= rows) continue;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const floatx4 s = hi[r][h] + lo[r][h];
-            const float4 v = make_float4(fmaxf(s[0] + b.x, 0.f), fmaxf(s[1] + b.y, 0.f), fmaxf(s[2] + b.z, 0.f), fmaxf(s[3] + b.w, 0.f));
-            const int px = 16 * h + l16;
-            if (r < R) *reinterpret_cast<float4*>(a + (((long)n * HW + r0 + r) * HW + px) * CO + co) = v;
-            *reinterpret_cast<float4*>(ring + r % 3 * RING_ROW + px * RING_PITCH + 16 * q) = v;
+            const floatx4 sum = hi[r][h] + lo[r][h];
+            bad = split::spoil(sum, bad);
+            store(r, h, sum, split::UNSCALE);
         }
-        if (r < 2 || r % 2) continue;
-        // window row (r0 + r) / 2 - 1: the ring's three rows.  Lane (l16, q): window column l16 (15 of them), channels co ..
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (l16 < PW) {
-            float4 best = make_float4(0.f, 0.f, 0.f, 0.f);
-            uchar4 bi = make_uchar4(0, 0, 0, 0);
+        pool(r);
+    }
+    if (!split::spoiled(bad)) return;
+    // Some sum is beyond the range of the scaled terms: the wavefront's rows once more, those with such a sum from the operands in memory
+    // (a lane with four of a filter row's values at its pixel, as in the patches), the others as above, so that a row that two
+    // bands compute is the same in both.
+#pragma unroll 1
+    for (int r = 0; r < rows; ++r) {
+        floatx4 sum[2], small[2];
 #pragma unroll
-            for (int k = 0; k < 9; ++k) {        // first maximum in scan order, per channel
-                const float4 v = *reinterpret_cast<const float4*>(ring + (r - 2 + k / 3) % 3 * RING_ROW + (2 * l16 + k % 3) * RING_PITCH + 16 * q);
-                if (k == 0) { best = v; continue; }
-                if (v.x > best.x) { best.x = v.x; bi.x = (unsigned char)k; }
-                if (v.y > best.y) { best.y = v.y; bi.y = (unsigned char)k; }
-                if (v.z > best.z) { best.z = v.z; bi.z = (unsigned char)k; }
-                if (v.w > best.w) { best.w = v.w; bi.w = (unsigned char)k; }
+        for (int h = 0; h < 2; ++h) sum[h] = small[h] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < F; ++k)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const split::Pix<16> o = split::pixel_operand<16, TPLANE>(base + ((r + k) * HW + 16 * h) * TPITCH);
+                small[h] = split::product<16>(0, filt[k], o, small[h]);
+                small[h] = split::product<16>(1, filt[k], o, small[h]);
+                sum[h] = split::product<16>(2, filt[k], o, sum[h]);
             }
-            const long o = (((long)n * PW + (r0 + r) / 2 - 1) * PW + l16) * (CO / 4) + co / 4;
-            pooled[o] = best;
-            arg[o] = bi;
+        mma::drain();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) sum[h] += small[h];
+        float factor = split::UNSCALE;
+        if (split::spoiled(split::spoil(sum[1], split::spoil(sum[0], 0.f)))) {
+            factor = 1.f;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                sum[h] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (int k = 0; k < F; ++k) {
+                    const int row = r0 + r + k - PAD, at = CI * (16 * h + l16 - PAD) + 4 * q;
+                    float wv[4], xv[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const bool e = 4 * q + i < ROWF;
+                        wv[i] = e ? w[(k * ROWF + 4 * q + i) * CO + 16 * wave + l16] : 0.f;
+                        xv[i] = e && (unsigned)row < (unsigned)HW && (unsigned)(at + i) < (unsigned)(HW * CI) ? x[((long)n * HW + row) * HW * CI + at + i] : 0.f;
+                    }
+                    sum[h] = split::product32(wv, xv, sum[h]);
+                }
+            }
+            mma::drain();
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int h = 0; h < 2; ++h) store(r, h, sum[h], factor);
+        pool(r);
     }
 }
 
@@ -221,7 +278,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) vo
                 }
                 sb.x += v.x; sb.y += v.y; sb.z += v.z; sb.w += v.w;
                 uint2 pl[split::PLANES];
-                split::split4(v, pl);
+                split::split4(split::scaled(v), pl);
 #pragma unroll
                 for (int p = 0; p < split::PLANES; ++p)
                     *reinterpret_cast<uint2*>(D + (dr * HW + 2 * bj + dc) * DPITCH + p * DPLANE + 8 * c4) = pl[p];
@@ -267,10 +324,43 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
     }
     mma::drain();
+    float bad = 0.f;
+#pragma unroll
+    for (int k = 0; k < F; ++k) {
+        hi[k] += lo[k];
+        bad = split::spoil(hi[k], bad);
+    }
+    if (split::spoiled(bad)) {      // beyond the range of the scaled terms: this wavefront's sums from the operands in memory, four pixels a step
+#pragma unroll
+        for (int k = 0; k < F; ++k) hi[k] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int px = i0 * R * HW + q; px < i1 * R * HW; px += 4) {
+            const int n = px / (HW * HW), h = px / HW % HW, c = px % HW, co = 16 * wave + l16, at = CI * (c - PAD) + l16;
+            float d = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {       // the (up to) four windows of the pixel, in the order of stage()
+                const int i = h / 2 - 1 + (k >> 1), j = c / 2 - 1 + (k & 1), wr = h - 2 * i, wc = c - 2 * j;
+                if ((unsigned)i >= (unsigned)PW || (unsigned)j >= (unsigned)PW || wr > 2 || wc > 2) continue;
+                const long o = (((long)n * PW + i) * PW + j) * CO + co;
+                if (arg[o] == 3 * wr + wc && pooled[o] > 0.f) d += dpool[o];
+            }
+            const float dv[1] = {d};
+#pragma unroll
+            for (int k = 0; k < F; ++k) {
+                const int row = h + k - PAD;
+                const bool in = l16 < ROWF && (unsigned)row < (unsigned)HW && (unsigned)at < (unsigned)(HW * CI);
+                const float xv[1] = {in ? x[((long)n * HW + row) * HW * CI + at] : 0.f};
+                hi[k] = split::product32(dv, xv, hi[k]);
+            }
+        }
+        mma::drain();
+    } else {
+#pragma unroll
+        for (int k = 0; k < F; ++k) hi[k] *= split::UNSCALE;
+    }
     float* out = partial + (long)blockIdx.x * (E + CO);
     if (l16 < ROWF)
 #pragma unroll
-        for (int k = 0; k < F; ++k) *reinterpret_cast<floatx4*>(out + (k * ROWF + l16) * CO + 16 * wave + 4 * q) = hi[k] + lo[k];
+        for (int k = 0; k < F; ++k) *reinterpret_cast<floatx4*>(out + (k * ROWF + l16) * CO + 16 * wave + 4 * q) = hi[k];
     float4* red = reinterpret_cast<float4*>(lds_bytes);             // bias: the 16 threads of one channel group, in order
     red[tid] = sb;
     __syncthreads();

@@ -44,12 +44,9 @@ __device__ __forceinline__ unsigned take(float& a, float& b) {
 constexpr float SCALE = 0x1p24f, UNSCALE = 0x1p-48f;
 __device__ __forceinline__ float4 scaled(float4 v) { return make_float4(v.x * SCALE, v.y * SCALE, v.z * SCALE, v.w * SCALE); }
 
-// Sums that are infinite or NaN: `spoil` gathers them (0 or NaN), `spoiled` says whether any lane of the wavefront has one.
-__device__ __forceinline__ float spoil(const floatx4& sum, float so_far) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) so_far = fmaf(sum[v], 0.f, so_far);
-    return so_far;
-}
+// Sums that are infinite or NaN: `spoil` gathers them (0 or NaN; a group of four large ones may overflow as well, at no harm),
+// `spoiled` says whether any lane of the wavefront has one.
+__device__ __forceinline__ float spoil(const floatx4& sum, float so_far) { return fmaf((sum[0] + sum[1]) + (sum[2] + sum[3]), 0.f, so_far); }
 __device__ __forceinline__ bool spoiled(float gathered) { return __builtin_expect(__any(gathered != 0.f) != 0, 0); }
 
 // acc += a . b on the fp32 matrix cores; a[j], b[j]: the lane's value at the same reduction index.  All lanes take part.
@@ -93,7 +90,7 @@ __device__ __forceinline__ uint2 read_tr(const char* lds) {
     return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t*)lds));
 }
 
-// One matrix-core operand of fp32 values.  32 reduction channels: the three planes, a lane's eight channels each.
+// One matrix-core operand of (scaled) fp32 values.  32 reduction channels: the three planes, a lane's eight channels each.
 // 16 reduction channels (C = 16): an instruction's 32 indices take two planes of them, a lane's four channels each, and
 // three instructions instead of six do the six products: (y2, y0) . (x0, x2), (y0, y1) . (x1, x0), (y0, y1) . (x0, x1).
 template <int C> struct Filt { uint4 v[C == 16 ? 2 : 3]; };

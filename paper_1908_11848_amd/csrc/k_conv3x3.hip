@@ -318,7 +318,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
     split::Filt<C> filt[3];
     auto split_filter = [&]() {
 #pragma unroll
-        for (int ky = 0; ky < 3; ++ky) filt[ky] = split::filter_operand<C>(fr[ky]);
+        for (int ky = 0; ky < 3; ++ky) {
+#pragma unroll
+            for (int e = 0; e < FV; ++e) fr[ky][e] = split::scaled(fr[ky][e]);
+            filt[ky] = split::filter_operand<C>(fr[ky]);
+        }
     };
     split_filter();
     float* red = reinterpret_cast<float*>(lds);         // the tile is not there yet
@@ -369,9 +373,44 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
     }
     auto stage = [&](char* to, float4 v) {  // 4 channels of a pixel as their three terms
         uint2 pl[split::PLANES];
-        split::split4(v, pl);
+        split::split4(split::scaled(v), pl);
 #pragma unroll
         for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(to + p * K::PLANE) = pl[p];
+    };
+    // what the convolution runs on, four channels of a pixel of src (and of the shortcut or xc)
+    auto transformed = [&](float4 o, float4 sc, int c) {
+        if constexpr (PRE == 3) {
+            const float4 mu = *reinterpret_cast<const float4*>(Sh + c);
+            const float4 is = *reinterpret_cast<const float4*>(Sh + C + c);
+            const float4 gi = *reinterpret_cast<const float4*>(Sh + 2 * C + c);
+            const float4 db = *reinterpret_cast<const float4*>(Sh + 3 * C + c);
+            const float4 dg = *reinterpret_cast<const float4*>(Sh + 4 * C + c);
+            o.x = gi.x * (o.x - db.x - (sc.x - mu.x) * is.x * dg.x);
+            o.y = gi.y * (o.y - db.y - (sc.y - mu.y) * is.y * dg.y);
+            o.z = gi.z * (o.z - db.z - (sc.z - mu.z) * is.z * dg.z);
+            o.w = gi.w * (o.w - db.w - (sc.w - mu.w) * is.w * dg.w);
+        }
+        if constexpr (PRE == 1 || PRE == 2) {
+            const float4 mu = *reinterpret_cast<const float4*>(Sh + c);
+            const float4 is = *reinterpret_cast<const float4*>(Sh + C + c);
+            const float4 ga = *reinterpret_cast<const float4*>(pre.gamma + c);
+            const float4 be = *reinterpret_cast<const float4*>(pre.beta + c);
+            o.x = fmaf((o.x - mu.x) * is.x, ga.x, be.x);
+            o.y = fmaf((o.y - mu.y) * is.y, ga.y, be.y);
+            o.z = fmaf((o.z - mu.z) * is.z, ga.z, be.z);
+            o.w = fmaf((o.w - mu.w) * is.w, ga.w, be.w);
+            if constexpr (PRE == 2) { o.x += sc.x; o.y += sc.y; o.z += sc.z; o.w += sc.w; }
+            o.x = fmaxf(o.x, 0.f); o.y = fmaxf(o.y, 0.f); o.z = fmaxf(o.z, 0.f); o.w = fmaxf(o.w, 0.f);
+        }
+        return o;
+    };
+    auto input = [&](int h, int w, int c) {  // the same from memory, zero outside the image
+        if (h < 0 || h >= HW || w < 0 || w >= HW) return make_float4(0.f, 0.f, 0.f, 0.f);
+        const long off = (((long)n * HW + h) * HW + w) * C + c;
+        float4 sc = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (PRE == 2) sc = *reinterpret_cast<const float4*>(pre.shortcut + off);
+        if constexpr (PRE == 3) sc = *reinterpret_cast<const float4*>(bwd.xc + off);
+        return transformed(*reinterpret_cast<const float4*>(src + off), sc, c);
     };
 #pragma unroll
     for (int e = 0; e < NL; ++e) {
@@ -380,40 +419,12 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
         const int pc = (idx / V) % K::TW, pr = idx / (V * K::TW);
         const int h = r_base + pr - 1, w = pc - 1;
         if (pr >= R + 2) continue;
-        if constexpr (PRE == 3) {
+        if constexpr (PRE != 0) {
             if (h >= 0 && h < HW && w >= 0 && w < HW) {
-                const float4 mu = *reinterpret_cast<const float4*>(Sh + 4 * v);
-                const float4 is = *reinterpret_cast<const float4*>(Sh + C + 4 * v);
-                const float4 gi = *reinterpret_cast<const float4*>(Sh + 2 * C + 4 * v);
-                const float4 db = *reinterpret_cast<const float4*>(Sh + 3 * C + 4 * v);
-                const float4 dg = *reinterpret_cast<const float4*>(Sh + 4 * C + 4 * v);
-                float4 o;
-                o.x = gi.x * (val[e].x - db.x - (scv[e].x - mu.x) * is.x * dg.x);
-                o.y = gi.y * (val[e].y - db.y - (scv[e].y - mu.y) * is.y * dg.y);
-                o.z = gi.z * (val[e].z - db.z - (scv[e].z - mu.z) * is.z * dg.z);
-                o.w = gi.w * (val[e].w - db.w - (scv[e].w - mu.w) * is.w * dg.w);
-                val[e] = o;
+                val[e] = transformed(val[e], scv[PRE >= 2 ? e : 0], 4 * v);
+                // the band's own rows (not the halo rows) are this workgroup's part of `a` or dx
                 if (!WG && part == 0 && pr >= 1 && pr <= R)
-                    *reinterpret_cast<float4*>(bwd.dx_out + (((long)n * HW + h) * HW + w) * C + 4 * v) = o;
-            }
-        }
-        if constexpr (PRE == 1 || PRE == 2) {
-            if (h >= 0 && h < HW && w >= 0 && w < HW) {
-                const float4 mu = *reinterpret_cast<const float4*>(Sh + 4 * v);
-                const float4 is = *reinterpret_cast<const float4*>(Sh + C + 4 * v);
-                const float4 ga = *reinterpret_cast<const float4*>(pre.gamma + 4 * v);
-                const float4 be = *reinterpret_cast<const float4*>(pre.beta + 4 * v);
-                float4 o = val[e];
-                o.x = fmaf((o.x - mu.x) * is.x, ga.x, be.x);
-                o.y = fmaf((o.y - mu.y) * is.y, ga.y, be.y);
-                o.z = fmaf((o.z - mu.z) * is.z, ga.z, be.z);
-                o.w = fmaf((o.w - mu.w) * is.w, ga.w, be.w);
-                if constexpr (PRE == 2) { o.x += scv[e].x; o.y += scv[e].y; o.z += scv[e].z; o.w += scv[e].w; }
-                o.x = fmaxf(o.x, 0.f); o.y = fmaxf(o.y, 0.f); o.z = fmaxf(o.z, 0.f); o.w = fmaxf(o.w, 0.f);
-                val[e] = o;
-                // the band's own rows (not the halo rows) are this workgroup's part of `a`
-                if (part == 0 && pr >= 1 && pr <= R)
-                    *reinterpret_cast<float4*>(pre.act_out + (((long)n * HW + h) * HW + w) * C + 4 * v) = o;
+                    *reinterpret_cast<float4*>((PRE == 3 ? bwd.dx_out : pre.act_out) + (((long)n * HW + h) * HW + w) * C + 4 * v) = val[e];
             }
         }
         stage(Xs + (pr * K::TW + pc) * K::PITCH + 8 * v, val[e]);
@@ -492,6 +503,36 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[wm][v] += Ex[((partner * 2 + wm) * 64 + lane) * 4 + v];
         }
+    }
+
+    float bad = 0.f;
+#pragma unroll
+    for (int wm = 0; wm < K::WM; ++wm) bad = split::spoil(acc[wm], bad);
+    if (split::spoiled(bad)) {      // beyond the range of the scaled terms: the wavefront's tiles from the operands in memory
+#pragma unroll
+        for (int wm = 0; wm < K::WM; ++wm) {
+            acc[wm] = floatx4{0.f, 0.f, 0.f, 0.f};
+            const int h0 = r_base + row0 + K::TROWS * (ks * K::WM + wm) - 1;
+#pragma unroll 1
+            for (int tap = 0; tap < 9; ++tap)
+#pragma unroll 1
+                for (int c = 4 * q; c < C; c += 16) {
+                    const float4 x = input(h0 + tap / 3, col + tap % 3 - 1, c);
+                    float4 y;
+                    if constexpr (TRANSPOSED) {
+                        y = *reinterpret_cast<const float4*>(wgt + ((long)(8 - tap) * C + co_w + l16) * C + c);
+                    } else {
+                        const float* wp = wgt + ((long)tap * C + c) * C + co_w + l16;
+                        y = make_float4(wp[0], wp[C], wp[2 * C], wp[3 * C]);
+                    }
+                    const float a[4] = {y.x, y.y, y.z, y.w}, b[4] = {x.x, x.y, x.z, x.w};
+                    acc[wm] = split::product32(a, b, acc[wm]);
+                }
+        }
+        mma::drain();
+    } else {
+#pragma unroll
+        for (int wm = 0; wm < K::WM; ++wm) acc[wm] *= split::UNSCALE;
     }
 
     // ---- store: a lane holds channels co .. co + 3 of its pixel of every tile
@@ -590,6 +631,30 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(min_wav
             __builtin_amdgcn_sched_barrier(0);
         }
         mma::drain();
+        float worst = 0.f;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) worst = split::spoil(dw[t], worst);
+        if (split::spoiled(worst)) {        // the wavefront's runs from the operands in memory, four pixels of a row a step
+#pragma unroll
+            for (int t = 0; t < 9; ++t) dw[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int p = first * HW + q; p < (first + RUNS * RROWS) * HW; p += 4) {
+                const int h = r_base + p / HW, w = p % HW, c = 16 * cot + l16;
+                const float4 dx = input(h, w, c & ~3);
+                const float d[1] = {c & 2 ? (c & 1 ? dx.w : dx.z) : (c & 1 ? dx.y : dx.x)};
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    const int xh = h + t / 3 - 1, xw = w + t % 3 - 1;
+                    const bool in = (unsigned)xh < (unsigned)HW && (unsigned)xw < (unsigned)HW;
+                    const float xv[1] = {in ? wg.x_in[(((long)n * HW + xh) * HW + xw) * C + 16 * cit + l16] : 0.f};
+                    dw[t] = split::product32(d, xv, dw[t]);
+                }
+            }
+            mma::drain();
+        } else {
+#pragma unroll
+            for (int t = 0; t < 9; ++t) dw[t] *= split::UNSCALE;
+        }
         epilogue_loads();
         float* pout = wg.partial + (long)tile * 9 * C * C;
         if constexpr (SPLIT_K) {
@@ -1003,7 +1068,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
         for (int e = 0; e < NX; ++e) {
             const int idx = lane + 64 * e, px = idx / (CI / 4);
-            split::split4(rx[e], pl);
+            split::split4(split::scaled(rx[e]), pl);
 #pragma unroll
             for (int p = 0; p < split::PLANES; ++p)
                 *reinterpret_cast<uint2*>(X + ((px / HW + 1) * TW + px % HW + 1) * XPITCH + p * XPLANE + 8 * (idx % (CI / 4))) = pl[p];
@@ -1026,7 +1091,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) vo
         for (int i = 0; i < 18; ++i) {
             if (i % 9 == 0)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) d[j] = split::filter_operand<32>(rd[i / 9][j]);
+                for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) rd[i / 9][j][e] = split::scaled(rd[i / 9][j][e]);
+                    d[j] = split::filter_operand<32>(rd[i / 9][j]);
+                }
             if (i + 1 < 18) load_x(i + 1);
             __builtin_amdgcn_sched_barrier(0);
             constexpr int PD[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
@@ -1037,6 +1106,32 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) vo
             __builtin_amdgcn_sched_barrier(0);
         }
         mma::drain();
+        float bad = 0.f;
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) bad = split::spoil(acc[t][j], bad);
+        if (split::spoiled(bad)) {                  // beyond the range of the scaled terms: from the operands in memory, four pixels a step
+#pragma unroll
+            for (int t = 0; t < 9; ++t) acc[t][0] = acc[t][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int p = q; p < HW * HW; p += 4) {
+                const float* dp = dy + ((long)n * HW * HW + p) * C + co0 + l16;
+                const float d0[1] = {dp[0]}, d1[1] = {dp[16]};
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    const int xh = p / HW + t / 3 - 1, xw = p % HW + t % 3 - 1;
+                    const bool in = (unsigned)xh < (unsigned)HW && (unsigned)xw < (unsigned)HW;
+                    const float xs[1] = {in ? x[(((long)n * HW + xh) * HW + xw) * C + ci0 + l16] : 0.f};
+                    acc[t][0] = split::product32(d0, xs, acc[t][0]);
+                    acc[t][1] = split::product32(d1, xs, acc[t][1]);
+                }
+            }
+            mma::drain();
+        } else {
+#pragma unroll
+            for (int t = 0; t < 9; ++t) { acc[t][0] *= split::UNSCALE; acc[t][1] *= split::UNSCALE; }
+        }
     }
     // the four sums, in a fixed order: wavefronts 2 and 3 hand theirs to 0 and 1, those two meet in LDS
     floatx4* Red = reinterpret_cast<floatx4*>(lds); // [2][tap][ci][co / 4]

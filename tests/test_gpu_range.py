@@ -155,3 +155,103 @@ def test_first_layer(oracle_nn, N, kind):
         out = host(dw)
         check(out[:4800], dwo)
         check(out[4800:], dz.sum(axis=(0, 1, 2)), 2e-5)
+
+
+SHAPES3 = [(1, 32, 16), (3, 32, 16), (3, 16, 32), (1, 8, 64), (6, 8, 64)]
+
+
+def dfilter(x, d):
+    """Filter gradient of a 3x3, pad 1 convolution as the matrix cores sum it: padding and masked-out elements take part as zeros."""
+    H = x.shape[1]
+    xp = np.pad(x, ((0, 0), (1, 1), (1, 1), (0, 0)))
+    return np.stack([np.einsum("nhwc,nhwo->co", xp[:, kh:kh + H, kw:kw + H], d) for kh in range(3) for kw in range(3)])
+
+
+@pytest.mark.parametrize("N,H,C", SHAPES3)
+@pytest.mark.parametrize("kind", KINDS)
+def test_residual_convolutions(oracle_nn, N, H, C, kind):
+    g = np.random.default_rng(N + C)
+    L, s = B.lib(), stream_ptr()
+    with np.errstate(all="ignore"):
+        x, w = operands(kind, g, (N, H, H, C), (3, 3, C, C))
+        X, W, y, dx = dev(x), dev(w), empty(x.shape), empty(x.shape)
+        assert L.dsspk_conv_fwd(s, X.data_ptr(), W.data_ptr(), None, y.data_ptr(), N, H, H, C, C, 3, 3, 1, 1, 0, None) == 0
+        check(host(y), oracle_nn.conv2d_fwd(*f64(x, w), None, 1, 1))
+        assert L.dsspk_conv_bwd_data(s, X.data_ptr(), W.data_ptr(), None, dx.data_ptr(), N, H, H, C, C, 3, 3, 1, 1) == 0
+        check(host(dx), oracle_nn.conv2d_bwd(np.zeros(x.shape), *f64(w, x), 1, 1, True)[0])
+        if C == 64:
+            x, dy = operands(kind, g, (N, H, H, C), (N, H, H, C))
+            X, DY, dw = dev(x), dev(dy), empty(9 * C * C)
+            scr = empty(L.dsspk_conv_wgrad_scratch_floats(N, H, H, C, C, 3, 3, 1, 1))
+            assert L.dsspk_conv_bwd_weight(s, X.data_ptr(), DY.data_ptr(), dw.data_ptr(), scr.data_ptr(), N, H, H, C, C, 3, 3, 1, 1) == 0
+            check(host(dw), dfilter(*f64(x, dy)))
+
+
+@pytest.mark.parametrize("N,H,C", SHAPES3 + [(33, 16, 32)])      # the last: sums merged by a kernel of their own
+@pytest.mark.parametrize("with_shortcut", [False, True])
+@pytest.mark.parametrize("kind", KINDS)
+def test_residual_convolution_behind_batchnorm(oracle_nn, N, H, C, with_shortcut, kind):
+    g = np.random.default_rng(N + C)
+    L, s = B.lib(), stream_ptr()
+    parts = L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1)
+    shape = (N, H, H, C)
+    first, second = {"tiny-first": (1e-37, 1e6), "tiny-second": (1e6, 1e-36), "huge": (1e20, 1e15)}.get(kind, (1.0, 1.0))
+    x, w0 = g.standard_normal(shape), 0.1 * g.standard_normal((3, 3, C, C))
+    gamma, beta = first * (1 + 0.2 * g.standard_normal(C)), first * 0.3 * g.standard_normal(C)
+    w1, sc = second * 0.05 * g.standard_normal((3, 3, C, C)), first * g.standard_normal(shape)
+    if kind == "special":
+        gamma[3], sc[0, H // 2, H // 2, 5], sc[0, H // 2, H // 2, 6] = np.inf, np.nan, ABOVE_BF16
+    X, W0, W1, Ga, Be, SC = dev(x), dev(w0), dev(w1), dev(gamma), dev(beta), dev(sc)
+    c, a, y, stats = empty(shape), empty(shape), empty(shape), empty(2 * C)
+    rec, rec1 = empty(L.dsspk_bn_scratch_floats(N * H * H, C)), empty(L.dsspk_bn_scratch_floats(N * H * H, C))
+    assert L.dsspk_conv_fwd(s, X.data_ptr(), W0.data_ptr(), None, c.data_ptr(), N, H, H, C, C, 3, 3, 1, 1, 0, rec.data_ptr()) == 0
+    assert L.dsspk_conv_fwd_prebn(s, c.data_ptr(), rec.data_ptr(), parts, Ga.data_ptr(), Be.data_ptr(), 1e-5, SC.data_ptr() if with_shortcut else None,
+                                  a.data_ptr(), stats.data_ptr(), W1.data_ptr(), y.data_ptr(), rec1.data_ptr(), N, H, C) == 0
+    with np.errstate(all="ignore"):
+        st = host(stats).astype(np.float64)
+        ao = (host(c).astype(np.float64) - st[:C]) * st[C:] * host(Ga) + host(Be) + (host(SC) if with_shortcut else 0)
+        check(host(a), np.fmax(ao, 0), 1e-6)
+        check(host(y), oracle_nn.conv2d_fwd(host(a).astype(np.float64), host(W1).astype(np.float64), None, 1, 1))
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("N,H,C", SHAPES3)
+@pytest.mark.parametrize("kind", KINDS)
+def test_residual_backward(oracle_nn, N, H, C, kind, fused):
+    """Batch-norm backward, input gradient, ReLU mask and (fused) filter gradient.  The mask is that of the activation, subnormal ones
+    included."""
+    g = np.random.default_rng(N + C)
+    L, s = B.lib(), stream_ptr()
+    if fused and L.dsspk_conv_bwd_fused_chunks(N, H, C) == 0:
+        pytest.skip("no fused form for this shape")
+    shape, M = (N, H, H, C), N * H * H
+    dz, w = operands(kind, g, shape, (3, 3, C, C))
+    scale = {"tiny-first": (1e-37, 1e6), "tiny-second": (1e6, 1e-36), "huge": (1e20, 1e15)}.get(kind, (1.0, 1.0))
+    x_in = np.maximum(scale[1] * g.standard_normal(shape), 0)
+    x_in[g.random(shape) < 0.1] = 1e-44
+    xc, xp, add = g.standard_normal(shape), g.standard_normal(shape), scale[0] * scale[1] * g.standard_normal(shape)
+    stats = np.concatenate([0.1 * g.standard_normal(C), 1 + 0.1 * g.random(C)])
+    gamma, totals = 1 + 0.1 * g.standard_normal(C), scale[0] * 0.1 * M * g.standard_normal(2 * C)
+    DZ, W, XI, XC, XP, ADD, ST, GA, TOT = (dev(np.asarray(t, dtype=np.float32)) for t in (dz, w, x_in, xc, xp, add, stats, gamma, totals))
+    out, dx, rec = empty(shape), empty(shape), empty(2 * C * L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1))
+    front = (s, DZ.data_ptr(), XC.data_ptr(), ST.data_ptr(), GA.data_ptr(), TOT.data_ptr())
+    if fused:
+        chunks = L.dsspk_conv_bwd_fused_chunks(N, H, C)
+        partial = empty((chunks, 9 * C * C))
+        rc = L.dsspk_conv_bwd_data_bn_wgrad(*front, W.data_ptr(), ADD.data_ptr(), out.data_ptr(), XP.data_ptr(), ST.data_ptr(), rec.data_ptr(),
+                                            XI.data_ptr(), partial.data_ptr(), None, None, 0, 0, N, H, C)
+    else:
+        rc = L.dsspk_conv_bwd_data_bn(*front, dx.data_ptr(), W.data_ptr(), ADD.data_ptr(), out.data_ptr(), XI.data_ptr(), XP.data_ptr(), ST.data_ptr(),
+                                      rec.data_ptr(), None, None, 0, 0, N, H, C)
+    assert rc == 0
+    with np.errstate(all="ignore"):
+        z, xi, cc, st, ga, tot = f64(*(host(t) for t in (DZ, XI, XC, ST, GA, TOT)))
+        d = ga * st[C:] * (z - tot[:C] / M - (cc - st[:C]) * st[C:] * tot[C:] / M)
+        d = d.astype(np.float32).astype(np.float64)         # overflows where the kernel's does
+        if not fused:
+            check(host(dx), d)
+            d = host(dx).astype(np.float64)
+        want = oracle_nn.conv2d_bwd(np.zeros(shape), w.astype(np.float64), d, 1, 1, True)[0] + host(ADD)
+        check(host(out), np.where(xi > 0, want, 0))
+        if fused:
+            check(host(partial).astype(np.float64).sum(axis=0), dfilter(xi, d))

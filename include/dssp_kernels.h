@@ -178,7 +178,7 @@ size_t dsspk_conv_wgrad_scratch_floats(int N, int H, int W, int Cin, int Cout, i
 /* Stride-1 convolutions of wide layers (Cin and Cout multiples of 64, k x k filters with k = 3 or 5, pad < k) with fp32
  * arithmetic on the bf16 matrix cores: every operand is split into three bf16 terms (24 significant bits in all), six of the
  * nine products of terms are accumulated in fp32; at least as accurate as dsspk_conv_*.  dsspk_conv_split_covers: 1 if the
- * shape is one of these and its tiles fit (the launchers return -1 otherwise).
+ * shape is one of these, its tiles fit and its filter has at most 2^30 elements (the launchers return -1 otherwise).
  * The filter is converted once per set of weights: dsspk_conv_split_filters writes the planes of the forward and / or of the
  * d-input pass (either may be NULL), dsspk_conv_split_filter_bytes(...) bytes each, 16-byte aligned. */
 int dsspk_conv_split_covers(int N, int H, int W, int Cin, int Cout, int k, int pad);

@@ -581,6 +581,9 @@ bool shape_ok(int H, int W, int Cin, int Cout, int k, int pad) {
     return (k == 3 || k == 5) && Cin % 64 == 0 && Cout % 64 == 0 && pad >= 0 && pad < k && H + 2 * pad >= k && W + 2 * pad >= k;
 }
 
+// Filter elements (and the bias behind them) are counted in int, by the reduction with a stride of as many more.
+bool filter_ok(int Cin, int Cout, int k) { return (long)k * k * Cin * Cout + Cout <= 1L << 30; }
+
 Geom forward_geom(int N, int H, int W, int Cin, int Cout, int k, int pad) {
     Geom g = {};
     g.N = N; g.H = H; g.W = W; g.OH = H + 2 * pad - k + 1; g.OW = W + 2 * pad - k + 1; g.pad = pad; g.IC = Cin; g.OC = Cout;
@@ -599,17 +602,19 @@ Geom backward_geom(int N, int H, int W, int Cin, int Cout, int k, int pad) {
 extern "C" int dsspk_conv_split_covers(int N, int H, int W, int Cin, int Cout, int k, int pad) {
     if (N < 1 || !shape_ok(H, W, Cin, Cout, k, pad)) return 0;
     Geom f = forward_geom(N, H, W, Cin, Cout, k, pad), b = backward_geom(N, H, W, Cin, Cout, k, pad);
-    // byte offsets within a group of images are 32-bit and below 2^31 (a group of several has at most 128 pixels each way)
+    if (!filter_ok(Cin, Cout, k)) return 0;
     if ((long)H * W * Cin >= 1L << 29 || (long)f.OH * f.OW * Cout >= 1L << 29) return 0;
     if ((long)N * H * W >= 1L << 31 || (long)N * f.OH * f.OW >= 1L << 31) return 0;
-    Tiling t;
-    return choose_tiling(t, N, f.OH, f.OW, f.OC, k) && choose_tiling(t, N, b.OH, b.OW, b.OC, k) && wgrad_rows(f, k);
+    // byte offsets within a group of images stay below split::OUTSIDE
+    auto fits = [&](const Geom& g) { Tiling t; return choose_tiling(t, N, g.OH, g.OW, g.OC, k) && (long)t.G * g.H * g.W * g.IC < 1L << 29; };
+    return fits(f) && fits(b) && wgrad_rows(f, k);
 }
 
 extern "C" size_t dsspk_conv_split_filter_bytes(int Cin, int Cout, int k) { return (size_t)k * k * Cin * Cout * 2 * split::PLANES; }
 
 extern "C" int dsspk_conv_split_filters(void* stream, const float* w, void* planes_fwd, void* planes_bwd, int Cin, int Cout, int k) {
-    if (!w || (!planes_fwd && !planes_bwd) || (k != 3 && k != 5) || Cin < 64 || Cin % 64 || Cout < 64 || Cout % 64) return -1;
+    if (!w || (!planes_fwd && !planes_bwd) || (k != 3 && k != 5) || Cin < 64 || Cin % 64 || Cout < 64 || Cout % 64 || !filter_ok(Cin, Cout, k))
+        return -1;
     const Frag f{w, (uint4*)planes_fwd, k * k, Cin, Cout}, b{w, (uint4*)planes_bwd, k * k, Cin, Cout};
     const long n = (long)k * k * Cin * Cout / 8;
     hipLaunchKernelGGL(filter_planes_kernel, dim3(ceil_div(2 * n, THREADS)), dim3(THREADS), 0, (hipStream_t)stream, f, b, n);

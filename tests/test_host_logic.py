@@ -261,3 +261,16 @@ def test_workers_are_dealt_onto_streams_by_their_rates():
     assert deal(rates, 4) == lane_of                                          # deterministic
     assert deal([1.0] * 8, 4) == [0, 1, 2, 3, 0, 1, 2, 3]                     # equal workers: round-robin
     assert deal([3.0, 1.0], 4) == [0, 1] and deal([1.0, 2.0, 3.0], 1) == [0, 0, 0]
+
+
+def test_wide_convolutions_beyond_32_bit_indices_are_refused():
+    """dsspk_conv_split_*: filter elements, and byte offsets within a workgroup's group of images, are 32-bit in the kernels."""
+    lib = B.lib()
+    assert lib.dsspk_conv_split_covers(1, 8, 8, 8192, 8192, 3, 1) == 1               # 2.4 GB of filter
+    assert lib.dsspk_conv_split_covers(1, 8, 8, 16384, 8192, 3, 1) == 0              # more than 2^30 elements
+    assert lib.dsspk_conv_split_covers(1, 8, 8, 32768, 32768, 3, 1) == 0             # more than 2^32
+    assert lib.dsspk_conv_split_wgrad_scratch_floats(1, 8, 8, 32768, 32768, 3, 1) == 0
+    assert lib.dsspk_conv_split_covers(8640, 3, 3, 65536, 64, 3, 0) == 1
+    assert lib.dsspk_conv_split_covers(8640, 3, 3, 1572864, 64, 3, 0) == 0           # 45 images of 57 MB to a workgroup
+    one = 256                                                                        # never dereferenced
+    assert lib.dsspk_conv_split_filters(None, one, one, one, 32768, 32768, 3) == -1

@@ -578,7 +578,8 @@ int wgrad_items(const Geom& g, int ks) {
 }
 
 bool shape_ok(int H, int W, int Cin, int Cout, int k, int pad) {
-    return (k == 3 || k == 5) && Cin % 64 == 0 && Cout % 64 == 0 && pad >= 0 && pad < k && H + 2 * pad >= k && W + 2 * pad >= k;
+    return (k == 3 || k == 5) && Cin >= 64 && Cin % 64 == 0 && Cout >= 64 && Cout % 64 == 0 && pad >= 0 && pad < k && H >= 1 && W >= 1 &&
+           H + 2 * pad >= k && W + 2 * pad >= k;
 }
 
 // Filter elements (and the bias behind them) are counted in int, by the reduction with a stride of as many more.

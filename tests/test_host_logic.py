@@ -274,3 +274,12 @@ def test_wide_convolutions_beyond_32_bit_indices_are_refused():
     assert lib.dsspk_conv_split_covers(8640, 3, 3, 1572864, 64, 3, 0) == 0           # 45 images of 57 MB to a workgroup
     one = 256                                                                        # never dereferenced
     assert lib.dsspk_conv_split_filters(None, one, one, one, 32768, 32768, 3) == -1
+
+
+def test_wide_convolutions_without_channels_are_refused():
+    lib = B.lib()
+    for Cin, Cout in ((0, 64), (64, 0), (0, 0), (-64, 64), (64, -64)):
+        assert lib.dsspk_conv_split_covers(1, 8, 8, Cin, Cout, 3, 1) == 0
+        assert lib.dsspk_conv_split_wgrad_scratch_floats(1, 8, 8, Cin, Cout, 3, 1) == 0
+    assert lib.dsspk_conv_split_covers(1, -3, 8, 64, 64, 5, 4) == 0
+    assert lib.dsspk_conv_split_covers(1, 8, 0, 64, 64, 5, 4) == 0

@@ -214,7 +214,7 @@ __device__ __forceinline__ float4 sum16(float4 v) { return make_float4(sum16(v.x
 // kernels and without: batch 16 876 -> 821 us, batch 32 945 -> 894 us.  Twice as many would still win at batch 64 (1135 -> 1103 us),
 // but their loads cost the smaller batches 2 % and, at four wavefronts a SIMD, spilled registers of the 16-channel kernels at every batch.
 constexpr int INLINE_RECORDS = 2048, RECORDS_PER_THREAD = INLINE_RECORDS / THREADS;
-constexpr bool records_inline(int parts, int C) { return parts * C <= INLINE_RECORDS; }
+constexpr bool records_inline(int parts, int C) { return (C == 16 || C == 32 || C == 64) && parts >= 1 && (long)parts * C <= INLINE_RECORDS; }
 
 // Thread (channel tid % C, lane tid / C) holds records lane, lane + 256 / C, ... of its channel; all loads in flight together.
 template <int C>
@@ -906,7 +906,7 @@ int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc
     return -2;
 }
 
-bool conv3x3_records_inline(int parts, int C) { return parts >= 1 && records_inline(parts, C); }
+bool conv3x3_records_inline(int parts, int C) { return records_inline(parts, C); }
 
 // Number of per-workgroup statistics records (tiles of equal size) the forward kernel emits, 0 if the
 // shape is not covered by it.

@@ -283,3 +283,16 @@ def test_wide_convolutions_without_channels_are_refused():
         assert lib.dsspk_conv_split_wgrad_scratch_floats(1, 8, 8, Cin, Cout, 3, 1) == 0
     assert lib.dsspk_conv_split_covers(1, -3, 8, 64, 64, 5, 4) == 0
     assert lib.dsspk_conv_split_covers(1, 8, 0, 64, 64, 5, 4) == 0
+
+
+def test_records_are_inline_only_where_the_kernels_merge_them():
+    """dsspk_conv_records_inline says 1 for the channel counts of the kernels that add up records, at most 2048 / C of them."""
+    lib = B.lib()
+    for C in (16, 32, 64):
+        assert lib.dsspk_conv_records_inline(2048 // C, C) == 1
+        assert lib.dsspk_conv_records_inline(2048 // C + 1, C) == 0
+        assert lib.dsspk_conv_records_inline(0, C) == 0
+        assert lib.dsspk_conv_records_inline(2**32 // C - 2**31 // C, C) == 0        # parts * C does not fit 32 bits
+        assert lib.dsspk_conv_records_inline(2**28, C) == 0
+    for C in (0, -16, 4, 8, 24, 128):
+        assert lib.dsspk_conv_records_inline(1, C) == 0

@@ -128,11 +128,11 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
         base[t] = (ok ? ((gi * TH + r) * TW + c) * PITCH : 0) + 16 * q + 64 * half;
         out[t] = ok ? (((long)(n0 + gi) * g.OH + r0 + r) * g.OW + c) * g.OC : -1;
     }
-    floatx4 acc[W::TC][W::TP];
+    floatx4 acc[W::TC][W::TP], small[W::TC][W::TP];
 #pragma unroll
     for (int i = 0; i < W::TC; ++i)
 #pragma unroll
-        for (int t = 0; t < W::TP; ++t) acc[i][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < W::TP; ++t) acc[i][t] = small[i][t] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     const int tiles_c = g.OC / 16, steps_c = g.IC / 32;
     const split::Buffer images = split::buffer(src + (long)n0 * g.H * g.W * g.IC, 4u * (unsigned)(min(g.G, g.N - n0) * g.H * g.W * g.IC));
@@ -192,13 +192,17 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
                 if (s + u >= STEPS) break;
                 load_p((u + 1) & 1, s + u + 1);
                 __builtin_amdgcn_sched_barrier(0);      // or the compiler moves the reads down to their use, behind the products
-                split::product(wv[u], pv[u & 1], acc);
+                split::product(wv[u], pv[u & 1], acc, small);
                 __builtin_amdgcn_sched_barrier(0);
                 load_w(u, s + u + WD);
             }
         }
     }
 
+#pragma unroll
+    for (int i = 0; i < W::TC; ++i)
+#pragma unroll
+        for (int t = 0; t < W::TP; ++t) acc[i][t] += small[i][t];
     auto finish = [&](const floatx4& sum, int ct, long at) {
         if (at < 0) return;
         const int co = 16 * ct + 4 * q;
@@ -375,11 +379,11 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         xa[h] = (p < P ? (r * TW + c) * XPITCH : 0) + 8 * (l16 & 3) + 2 * ci_w;      // beyond P dy is zero
         da[h] = p * DPITCH + 8 * (l16 & 3) + 2 * co_w;
     }
-    floatx4 acc[KS][2][1];
+    floatx4 acc[KS][2][1], small[KS][2][1];
 #pragma unroll
     for (int k = 0; k < KS; ++k)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) acc[k][i][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < 2; ++i) acc[k][i][0] = small[k][i][0] = floatx4{0.f, 0.f, 0.f, 0.f};
     float4 sb = make_float4(0.f, 0.f, 0.f, 0.f);
 
     // The thread's staged elements: NX of x, then ND of dy.  One tile is in LDS and worked on, the next one is in registers
@@ -470,7 +474,7 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
                 for (int e = kw * NE / SS; e < (kw + 1) * NE / SS; ++e) stage(e, nxt);
             }
-            split::product(dv, xv[kw & 1], acc[kw]);
+            split::product(dv, xv[kw & 1], acc[kw], small[kw]);
 #pragma unroll
             for (int m = 0; m < 12; ++m) {                     // one MFMA, a few vector instructions, ...
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -488,7 +492,10 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
     for (int kw = 0; kw < KS; ++kw)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) bad = split::spoil(acc[kw][i][0], bad);
+        for (int i = 0; i < 2; ++i) {
+            acc[kw][i][0] += small[kw][i][0];
+            bad = split::spoil(acc[kw][i][0], bad);
+        }
     if (split::spoiled(bad)) {      // beyond the range of the scaled terms: this wavefront's sums from the operands in memory, four pixels a step
 #pragma unroll
         for (int kw = 0; kw < KS; ++kw) acc[kw][0][0] = acc[kw][1][0] = floatx4{0.f, 0.f, 0.f, 0.f};

@@ -69,16 +69,21 @@ __device__ __forceinline__ floatx4 mfma(const uint4& a, const uint4& b, floatx4 
 }
 
 // The six products for TA x TB tiles, small ones first, each over all tiles before the next (independent accumulators
-// follow each other).  acc[i][j] is 16x16: rows from a, columns from b.
+// follow each other).  sum[i][j] is 16x16: rows from a, columns from b.  The five small products (2^-8 and less of the leading one) have
+// an accumulator of their own: what a matrix-core instruction rounds, it rounds to the size of its accumulator, so the leading sum
+// is then rounded once per 32 reduction indices and not six times.
 template <int TA, int TB>
-__device__ __forceinline__ void product(const uint4 (&a)[TA][PLANES], const uint4 (&b)[TB][PLANES], floatx4 (&acc)[TA][TB]) {
+__device__ __forceinline__ void product(const uint4 (&a)[TA][PLANES], const uint4 (&b)[TB][PLANES], floatx4 (&sum)[TA][TB], floatx4 (&small)[TA][TB]) {
     constexpr int PA[6] = {0, 2, 1, 0, 1, 0}, PB[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
     for (int p = 0; p < 6; ++p)
 #pragma unroll
         for (int i = 0; i < TA; ++i)
 #pragma unroll
-            for (int j = 0; j < TB; ++j) acc[i][j] = mfma(a[i][PA[p]], b[j][PB[p]], acc[i][j]);
+            for (int j = 0; j < TB; ++j) {
+                floatx4& to = p < 5 ? small[i][j] : sum[i][j];
+                to = mfma(a[i][PA[p]], b[j][PB[p]], to);
+            }
 }
 
 // Transposing LDS read: the 16 lanes of a quarter wavefront name four rows of 16 two-byte elements (lane j: row j / 4,

@@ -70,3 +70,37 @@ def test_conv_split_refuses_other_shapes():
     for case in [(1, 8, 8, 32, 64, 3, 1), (1, 8, 8, 64, 48, 3, 1), (1, 8, 8, 64, 64, 4, 1), (1, 8, 8, 64, 64, 3, 3), (1, 2, 2, 64, 64, 5, 0),
                  (1, 4, 200, 64, 64, 3, 1)]:
         assert L.dsspk_conv_split_covers(*case) == 0
+
+
+# the networks' operands: post-ReLU activations and gradients behind a ReLU's mask, half of them zero (a sum on the fp32 cores is not
+# rounded where it adds a zero)
+@pytest.mark.parametrize("case", [(1, 15, 15, 64, 64, 5, 2), (37, 15, 15, 64, 64, 5, 2), (128, 15, 15, 64, 64, 5, 2), (300, 15, 15, 64, 64, 5, 2),
+                                  (3, 7, 7, 64, 64, 3, 1), (200, 7, 7, 64, 64, 3, 1), (512, 7, 7, 64, 64, 3, 1), (5, 9, 9, 128, 64, 3, 1),
+                                  (5, 9, 9, 64, 128, 5, 2)], ids=lambda c: "x".join(map(str, c)))
+def test_error_no_larger_than_the_fp32_matrix_cores(oracle_nn, case):
+    N, H, W, Cin, Cout, k, pad = case
+    g = np.random.default_rng(N + H)
+    x = np.maximum(g.standard_normal((N, H, W, Cin)), 0).astype(np.float32)
+    dy = (g.standard_normal((N, H, W, Cout)) * (g.random((N, H, W, Cout)) < 0.5)).astype(np.float32)
+    w = (np.sqrt(2.0 / (k * k * Cin)) * g.standard_normal((k, k, Cin, Cout))).astype(np.float32)
+    L, s = B.lib(), stream_ptr()
+    X, Wd, DY = dev(x), dev(w), dev(dy)
+    n_planes = L.dsspk_conv_split_filter_bytes(Cin, Cout, k) // 4
+    pf, pb = empty(n_planes), empty(n_planes)
+    assert L.dsspk_conv_split_filters(s, Wd.data_ptr(), pf.data_ptr(), pb.data_ptr(), Cin, Cout, k) == 0
+    y, dx, dw = [empty((N, H, W, Cout)) for _ in "ab"], [empty((N, H, W, Cin)) for _ in "ab"], [empty(k * k * Cin * Cout) for _ in "ab"]
+    shape = (N, H, W, Cin, Cout, k, pad)
+    assert L.dsspk_conv_split_fwd(s, X.data_ptr(), pf.data_ptr(), None, y[0].data_ptr(), *shape, 0) == 0
+    assert L.dsspk_conv_split_bwd_data(s, DY.data_ptr(), pb.data_ptr(), None, dx[0].data_ptr(), *shape) == 0
+    scr = empty(L.dsspk_conv_split_wgrad_scratch_floats(*shape))
+    assert L.dsspk_conv_split_bwd_weight(s, X.data_ptr(), DY.data_ptr(), dw[0].data_ptr(), 0, scr.data_ptr(), *shape) == 0
+    general = (N, H, W, Cin, Cout, k, k, 1, pad)
+    assert L.dsspk_conv_fwd(s, X.data_ptr(), Wd.data_ptr(), None, y[1].data_ptr(), *general, 0, None) == 0
+    assert L.dsspk_conv_bwd_data(s, DY.data_ptr(), Wd.data_ptr(), None, dx[1].data_ptr(), *general) == 0
+    scr1 = empty(L.dsspk_conv_wgrad_scratch_floats(*general))
+    assert L.dsspk_conv_bwd_weight(s, X.data_ptr(), DY.data_ptr(), dw[1].data_ptr(), scr1.data_ptr(), *general) == 0
+    x64, w64, dy64 = (a.astype(np.float64) for a in (x, w, dy))
+    dxo, dwo, _ = oracle_nn.conv2d_bwd(x64, w64, dy64, 1, pad, True)
+    for got, want in ((y, oracle_nn.conv2d_fwd(x64, w64, None, 1, pad)), (dx, dxo), (dw, dwo)):
+        split, fp32 = rel_l2(host(got[0]), want), rel_l2(host(got[1]), want)
+        assert split <= fp32

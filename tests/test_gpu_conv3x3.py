@@ -72,3 +72,28 @@ def test_batchnorm_sums_taken_from_records(N, H, C):
         res.append([host(t) for t in ((out, rout, part) if fused else (out, rout, dx))])
     for a, b in zip(*res):
         assert rel_l2(b, a) < 2e-6 and max_abs(b, a) < 2e-5
+
+
+@pytest.mark.parametrize("N,H,C", [(1, 32, 16), (5, 32, 16), (37, 32, 16), (128, 32, 16), (1, 16, 32), (37, 16, 32), (128, 16, 32)])
+@pytest.mark.parametrize("kind", ["relu", "offset"])
+def test_fused_filter_gradient_no_less_exact_than_on_the_fp32_cores(oracle_nn, N, H, C, kind):
+    """The filter gradient that the fused backward kernel leaves (batch norm the identity, so that dx is dz) against the stand-alone
+    kernel's, which works on the fp32 matrix cores, both against float64."""
+    g = np.random.default_rng(N + C)
+    x = g.standard_normal((N, H, H, C))
+    x = (np.maximum(x, 0) if kind == "relu" else x + 8).astype(np.float32)
+    dz, w = (1e-3 * g.standard_normal((N, H, H, C))).astype(np.float32), (0.1 * g.standard_normal((3, 3, C, C))).astype(np.float32)
+    L, s = B.lib(), stream_ptr()
+    X, DZ, W, XC = dev(x), dev(dz), dev(w), dev(g.standard_normal((N, H, H, C)).astype(np.float32))
+    identity, ones, zeros = dev(np.repeat([0.0, 1.0], C).astype(np.float32)), dev(np.ones(C, np.float32)), dev(np.zeros(2 * C, np.float32))
+    chunks = L.dsspk_conv_bwd_fused_chunks(N, H, C)
+    out, rec, partial = empty((N, H, H, C)), empty(2 * C * L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1)), empty(chunks * 9 * C * C)
+    assert L.dsspk_conv_bwd_data_bn_wgrad(s, DZ.data_ptr(), XC.data_ptr(), identity.data_ptr(), ones.data_ptr(), zeros.data_ptr(), W.data_ptr(), None,
+                                          out.data_ptr(), XC.data_ptr(), identity.data_ptr(), rec.data_ptr(), X.data_ptr(), partial.data_ptr(),
+                                          None, None, 0, 0, N, H, C) == 0
+    dw, dw32, scr = empty(9 * C * C), empty(9 * C * C), empty(L.dsspk_conv_wgrad_scratch_floats(N, H, H, C, C, 3, 3, 1, 1))
+    assert L.dsspk_wgrad_reduce(s, partial.data_ptr(), dw.data_ptr(), 9 * C * C, chunks) == 0
+    assert L.dsspk_conv_bwd_weight(s, X.data_ptr(), DZ.data_ptr(), dw32.data_ptr(), scr.data_ptr(), N, H, H, C, C, 3, 3, 1, 1) == 0
+    _, want, _ = oracle_nn.conv2d_bwd(x.astype(np.float64), w.astype(np.float64), dz.astype(np.float64), 1, 1, True, need_dx=False)
+    fused, fp32 = rel_l2(host(dw), want), rel_l2(host(dw32), want)
+    assert fused <= fp32

@@ -205,6 +205,56 @@ __global__ __launch_bounds__(1024) void gemm_kernel(Operand a, Operand b, Epilog
     shaped_tile<SHAPE, AV, BV>(a, b, M, N, min(K - k_lo, k_per_layer), blockIdx.y, blockIdx.x, e, lds);
 }
 
+// Large products: a workgroup of four wavefronts owns a 64x64 tile and takes both operands through LDS, 16 reduction indices a stage,
+// the next stage's loads in flight.  Each operand is read once per tile instead of twice, with lanes along whichever index is
+// contiguous (K_FIRST: the reduction index), which is what counts once every compute unit has several tiles to work on and the
+// caches no longer hold the operands.  Rule: from 1024 tiles, four to a compute unit.  Measured, A row-major / transposed / B
+// transposed, this form against the one above: 256 tiles (1024^3) 55 / 55 / 53 against 36 / 39 / 49 us, 1024 tiles (2048^3)
+// 201 / 202 / 193 against 241 / 258 / 249, 4096 tiles (4096 x 4096, K = 1024) 387 / 389 / 381 against 504 / 531 / 496.
+constexpr int STAGED_TILES = 1024, STAGED_THREADS = 256;
+template <bool A_K_FIRST, bool B_K_FIRST>
+__global__ __launch_bounds__(STAGED_THREADS) void gemm_staged_kernel(Operand a, Operand b, Epilogue e, int M, int N, int K) {
+    __shared__ __attribute__((aligned(16))) float As[2][64 * mma::LDK], Bs[2][64 * mma::LDK];        // [row of op(A) / column of op(B)][k]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+    floatx4 acc[2][2];
+    mma::zero(acc);
+    float ra[4], rb[4];
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int idx = tid + u * STAGED_THREADS;
+            const int i = A_K_FIRST ? idx / 16 : idx % 64, ka = k0 + (A_K_FIRST ? idx % 16 : idx / 64);
+            ra[u] = m0 + i < M && ka < K ? a.p[(long)(m0 + i) * a.s + (long)ka * a.ks] : 0.f;
+            const int j = B_K_FIRST ? idx / 16 : idx % 64, kb = k0 + (B_K_FIRST ? idx % 16 : idx / 64);
+            rb[u] = n0 + j < N && kb < K ? b.p[(long)(n0 + j) * b.s + (long)kb * b.ks] : 0.f;
+        }
+    };
+    load(0);
+    for (int k0 = 0, buf = 0; k0 < K; k0 += mma::KC, buf ^= 1) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int idx = tid + u * STAGED_THREADS;
+            As[buf][A_K_FIRST ? idx / 16 * mma::LDK + idx % 16 : idx % 64 * mma::LDK + idx / 64] = ra[u];
+            Bs[buf][B_K_FIRST ? idx / 16 * mma::LDK + idx % 16 : idx % 64 * mma::LDK + idx / 64] = rb[u];
+        }
+        __syncthreads();
+        if (k0 + mma::KC < K) load(k0 + mma::KC);
+        mma::chunk16<2, 2, false, true>(As[buf], mma::LDK, Bs[buf], mma::LDK, 32 * (wave >> 1), 32 * (wave & 1), acc, lane);
+    }
+    mma::drain();
+    const int l16 = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = m0 + 32 * (wave >> 1) + 16 * i + 4 * q + v, col = n0 + 32 * (wave & 1) + 16 * j + l16;
+                if (row < M && col < N) store_result(e, row, col, acc[i][j][v]);
+            }
+}
+
 // Threads of a workgroup: a wavefront is worth having for two k-chunks; up to 16 of them for the one-sub-tile shapes.
 inline int tile_threads(int shape, int K) {
     const int chunks = ceil_div(K, mma::KC);
@@ -265,6 +315,13 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float* __restrict
 }
 
 int launch_gemm(hipStream_t s, const Operand& a, const Operand& b, const Epilogue& e, int M, int N, int K, int layers) {
+    if (layers == 1 && (long)ceil_div(M, 64) * ceil_div(N, 64) >= STAGED_TILES) {
+        const dim3 tiles(ceil_div(N, 64), ceil_div(M, 64)), threads(STAGED_THREADS);
+#define GO(A, B) hipLaunchKernelGGL((gemm_staged_kernel<A, B>), tiles, threads, 0, s, a, b, e, M, N, K)
+        if (a.ks == 1 && b.s == 1) GO(true, false); else if (a.ks == 1) GO(true, true); else if (b.s == 1) GO(false, false); else GO(false, true);
+#undef GO
+        return 1;
+    }
     const int chunks = ceil_div(K, mma::KC);
     const int k_per_layer = ceil_div(chunks, layers) * mma::KC;
     const int shape = tile_shape(M, N), edge = tile_edge(shape), threads = tile_threads(shape, k_per_layer < K ? k_per_layer : K);

@@ -79,3 +79,20 @@ def test_last_layer_with_softmax(oracle_nn, m, n_in, C):
     assert rel_l2(host(dz), dzo) < 1e-5 and max_abs(host(dz), dzo) < 2e-5
     assert L.dsspk_fc_softmax_xent(s, X.data_ptr(), W.data_ptr(), Bv.data_ptr(), Y.data_ptr(), z.data_ptr(), dz.data_ptr(),
                                    rl.data_ptr(), m, n_in, 129) == -1
+
+
+# both sides of the line from which a product takes its operands through LDS (1024 tiles of 64x64), remainders in every direction, every
+# order of the operands, a row pitch of the result
+@pytest.mark.parametrize("M,N,K", [(1985, 2000, 70), (2050, 2000, 70), (65500, 33, 17), (64, 65473, 1), (2048, 2048, 129)])
+@pytest.mark.parametrize("a_rows,b_rows", [(True, True), (False, True), (True, False), (False, False)])
+def test_gemm_large(M, N, K, a_rows, b_rows):
+    g = np.random.default_rng(M + K)
+    a, b, bias = (g.standard_normal(sh).astype(np.float32) for sh in ((M, K), (K, N), (N,)))
+    A, Bm, Bv = dev(a if a_rows else a.T), dev(b if b_rows else b.T), dev(bias)
+    ldc = N + 3
+    C = empty((M, ldc))
+    assert B.lib().dsspk_gemm(stream_ptr(), A.data_ptr(), *((K, 1) if a_rows else (1, M)), Bm.data_ptr(), *((N, 1) if b_rows else (1, K)), C.data_ptr(),
+                              ldc, M, N, K, Bv.data_ptr(), 1) == 0
+    got, want = host(C), np.maximum(a.astype(np.float64) @ b.astype(np.float64) + bias, 0)
+    assert np.isnan(got[:, N:]).all()                   # the pitch's gap is left alone
+    assert rel_l2(got[:, :N], want) < 1e-6 and max_abs(got[:, :N], want) < 1e-5         # sqrt(K) * 6e-8 of the sum's scale

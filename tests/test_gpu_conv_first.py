@@ -47,3 +47,29 @@ def test_conv_first(oracle_nn, N, offset):
     out = host(dw)
     assert rel_l2(out[:4800], dwo) < 2e-6 and max_abs(out[:4800], dwo) < 2e-5
     assert np.max(np.abs(out[4800:] - dbo)) < 2e-6 * 1e-2 * max(1.0, np.sqrt(N * 225)) * 4
+
+
+@pytest.mark.parametrize("N", [1, 37, 128, 300])
+def test_error_no_larger_than_the_fp32_matrix_cores(oracle_nn, N):
+    """Output and filter gradient against the general kernels' (implicit matrix product on the fp32 cores) on the same operands."""
+    g = np.random.default_rng(N)
+    x, b = g.standard_normal((N, 32, 32, 3)).astype(np.float32), g.standard_normal(64).astype(np.float32)
+    w = (np.sqrt(2.0 / 75) * g.standard_normal((5, 5, 3, 64))).astype(np.float32)
+    dp = (1e-3 * g.standard_normal((N, 15, 15, 64))).astype(np.float32)
+    X, W, Bd, DP = dev(x), dev(w), dev(b), dev(dp)
+    a, a32, p, arg, da = empty((N, 32, 32, 64)), empty((N, 32, 32, 64)), empty((N, 15, 15, 64)), torch.empty(N * 225 * 64, dtype=torch.uint8, device="cuda"), empty((N, 32, 32, 64))
+    L, s = B.lib(), stream_ptr()
+    assert L.dsspk_conv_first_pool_fwd(s, X.data_ptr(), W.data_ptr(), Bd.data_ptr(), a.data_ptr(), p.data_ptr(), arg.data_ptr(), N) == 0
+    general = (N, 32, 32, 3, 64, 5, 5, 1, 2)
+    assert L.dsspk_conv_fwd(s, X.data_ptr(), W.data_ptr(), Bd.data_ptr(), a32.data_ptr(), *general, 1, None) == 0
+    assert L.dsspk_maxpool_bwd_relu(s, DP.data_ptr(), arg.data_ptr(), a.data_ptr(), da.data_ptr(), N, 32, 32, 64) == 0
+    dw, dw32 = empty(4864), empty(4800)
+    scr, scr32 = empty(L.dsspk_conv_first_scratch_floats(N)), empty(L.dsspk_conv_wgrad_scratch_floats(*general))
+    assert L.dsspk_conv_first_pool_bwd_weight(s, X.data_ptr(), DP.data_ptr(), p.data_ptr(), arg.data_ptr(), dw.data_ptr(), scr.data_ptr(), N) == 0
+    assert L.dsspk_conv_bwd_weight(s, X.data_ptr(), da.data_ptr(), dw32.data_ptr(), scr32.data_ptr(), *general) == 0
+    x64, w64 = x.astype(np.float64), w.astype(np.float64)
+    ao = np.maximum(oracle_nn.conv2d_fwd(x64, w64, b.astype(np.float64), 1, 2), 0)
+    _, dwo, _ = oracle_nn.conv2d_bwd(x64, w64, host(da).astype(np.float64).reshape(N, 32, 32, 64), 1, 2, True, need_dx=False)
+    for got, got32, want in ((host(a), host(a32), ao), (host(dw)[:4800], host(dw32), dwo)):
+        split, fp32 = rel_l2(got, want), rel_l2(got32, want)
+        assert split <= fp32, (split, fp32)

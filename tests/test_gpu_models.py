@@ -523,6 +523,74 @@ def test_graph_replay_is_bit_identical_to_eager(oracle_nn):
     em.close()
 
 
+def test_short_steps_that_stay_launches_are_bit_identical():
+    """A step of few kernels never becomes a graph: its second call captures, counts and throws the capture away, and has to compute
+    all the same, as do the later ones."""
+    K, batch = 2, 8
+    w0 = inputs.init_weights(segs_of("mlp", 10), 1, jitter=0.1)
+    xs, ys = inputs.batches(1, K, 2, batch, 10, flat=True)
+    em = Emulation("mlp", K, 3, 12, 0.01, w0, batch, 10, xs, ys)
+    for p in range(K):
+        B.dssp_pull(em.ctx, p, em.w_local[p])
+    ref = {}
+    for rep in range(5):
+        for p in range(K):
+            for j in range(2):
+                em.grad[p].fill_(float("nan"))
+                em.loss[p].fill_(float("nan"))
+                torch.cuda.synchronize()
+                em.step(p, j)
+                g, loss = em.worker_grad(p)
+                assert np.isfinite(g).all() and np.isfinite(loss)
+                if rep == 0:
+                    ref[(p, j)] = (g.copy(), loss)
+                else:
+                    assert np.array_equal(g, ref[(p, j)][0]) and loss == ref[(p, j)][1], (rep, p, j)
+    em.close()
+
+
+@pytest.mark.parametrize("model,batch,ncls", [("mlp", 5, 129), ("mlp", 32, 1000), ("alexnet_ds", 3, 200), ("alexnet_3c", 4, 129), ("resnet8", 3, 1000)])
+def test_more_classes_than_the_fused_last_layer_holds(oracle_nn, model, batch, ncls):
+    """Beyond 128 classes the last layer and its softmax are kernels of their own: gradient and loss parity with the oracle."""
+    net = oracle_nn.make_net(model, ncls)
+    w0 = inputs.init_weights(segs_of(model, ncls), 2, jitter=0.1)
+    xs, ys = inputs.batches(2, 1, 1, batch, ncls, flat=(model == "mlp"))
+    em = Emulation(model, 1, 0, 0, 0.001, w0, batch, ncls, xs, ys)
+    B.dssp_pull(em.ctx, 0, em.w_local[0])
+    em.step(0, 0)
+    err, nflip = gradient_parity(net, em, 0, w0, xs[0][0], ys[0][0])
+    em.close()
+    assert err < GRAD_TOL
+
+
+@pytest.mark.parametrize("n,K,s_L,r_max", [(10_001, 4, 1, 0), (1_733_811, 8, 1, 2), (65_536, 16, 0, 0)])
+def test_releasing_pushes_leave_the_same_bits(n, K, s_L, r_max):
+    """Pushes that release waiting workers write all their snapshots with the update (fused_pull).  Weights, every snapshot and the
+    stamps the device saw are those of push and pull as separate calls, after every push; gradients of order 1, so that a push
+    lost or applied twice, or a snapshot one version off, changes a weight in its first digits."""
+    g = np.random.default_rng(n)
+    w0, grads = g.standard_normal(n, dtype=np.float32), g.standard_normal((K, n), dtype=np.float32)
+    d = (g.integers(1, 4, (K, 64)) * 1000 + g.integers(0, 1000, (K, 64))).astype(np.int64)
+    d[0] *= 5                                           # a straggler: the others wait for it
+    seen = []
+    for fused in (False, True):
+        em = Emulation("none", K, s_L, r_max, 0.5, w0, grads=grads)
+        states = []
+        schedule = em.schedule(d, fused_pull=fused)
+        for _ in range(3 * K):
+            schedule.advance(1)
+            em.synchronize()
+            states.append((em.weights(), [em.w_local[p].cpu().numpy() for p in range(K)], B.dssp_device_stamps(em.ctx, K)))
+        seen.append((states, schedule.log))
+        em.close()
+    assert seen[0][1] == seen[1][1]
+    for push, (a, b) in enumerate(zip(seen[0][0], seen[1][0])):
+        assert a[2] == b[2] and np.array_equal(a[0], b[0]), push
+        assert all(np.array_equal(x, y) for x, y in zip(a[1], b[1])), push
+        if push:
+            assert rel_l2(a[0], seen[0][0][push - 1][0]) > 1e-3         # every push shows
+
+
 # ------------------------------------------------------------------ error paths (host side; nothing faults)
 def test_failed_push_leaves_the_clocks_untouched():
     """A push whose device half is refused (here: a gradient pointer that is not 16-byte aligned, which the launcher rejects

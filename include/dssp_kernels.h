@@ -82,7 +82,10 @@ size_t dsspk_colsum_scratch_floats(long M, int N);
 #define DSSPK_NOALLOC_EHIP (-3)
 int dsspk_colsum_noalloc(void* stream, const float* X_dev, float* out_dev, long M, int N);
 
-/* Convolution (cross-correlation, zero padding), implicit GEMM on fp32 MFMA.
+/* Convolution (cross-correlation, zero padding), implicit GEMM on fp32 MFMA.  The 3x3, stride 1, pad 1 convolutions of 16 channels on
+ * 32x32 images, 32 on 16x16 and 64 on 8x8, here and in all calls below, do their fp32 arithmetic on the bf16 matrix cores (three bf16
+ * terms per operand), no less exactly and over all of fp32's range; around operands of 1e31 or more, results above 6e23, infinities
+ * and NaN on the fp32 ones, at several times the time.
  * Ho = (H + 2*pad - KH)/stride + 1.  bias_dev may be NULL; relu applies max(.,0) to the output.
  * bn_partial_dev (may be NULL): the kernel also writes, per workgroup tile, the mean and the sum of
  * squared deviations of every output channel (dsspk_conv_fwd_stat_parts(...) records of
@@ -145,7 +148,8 @@ int dsspk_conv_bwd_data_bn_wgrad(void* stream, const float* dz_dev, const float*
 int dsspk_conv_bwd_fused_chunks(int N, int H, int C);
 /* The two with the sums of their batch norm added up by the kernel itself: totals_dev NULL and in_parts records in
  * in_records_dev (what dsspk_bn_bwd_totals would be given; not the buffer records_dev points to); dgamma_dev[C] and dbeta_dev[C]
- * are stored as that call would.  Only where dsspk_conv_records_inline(in_parts, C) says 1 (few records; -1 otherwise).
+ * are stored as that call would.  Only where dsspk_conv_records_inline(in_parts, C) says 1 (C = 16, 32 or 64 and at most 2048 / C records; -1
+ * otherwise).
  * dsspk_conv_fwd_prebn merges such records in the same way, without a kernel of its own. */
 int dsspk_conv_records_inline(int parts, int C);
 int dsspk_conv_bwd_data_bn_records(void* stream, const float* dz_dev, const float* xc_dev, const float* stats_dev,
@@ -177,7 +181,9 @@ size_t dsspk_conv_wgrad_scratch_floats(int N, int H, int W, int Cin, int Cout, i
 
 /* Stride-1 convolutions of wide layers (Cin and Cout multiples of 64, k x k filters with k = 3 or 5, pad < k) with fp32
  * arithmetic on the bf16 matrix cores: every operand is split into three bf16 terms (24 significant bits in all), six of the
- * nine products of terms are accumulated in fp32; at least as accurate as dsspk_conv_*.  dsspk_conv_split_covers: 1 if the
+ * nine products of terms are accumulated in fp32; no less exact than dsspk_conv_* on the same operands, over all of fp32's range
+ * (subnormal operands included).  Where an operand of 1e31 or more, a result above 6e23, an infinity or a NaN takes part, the results around it
+ * are computed on the fp32 matrix cores: as dsspk_conv_* would, at several times the time.  dsspk_conv_split_covers: 1 if the
  * shape is one of these, its tiles fit and its filter has at most 2^30 elements (the launchers return -1 otherwise).
  * The filter is converted once per set of weights: dsspk_conv_split_filters writes the planes of the forward and / or of the
  * d-input pass (either may be NULL), dsspk_conv_split_filter_bytes(...) bytes each, 16-byte aligned. */

@@ -2,7 +2,9 @@
 // behind it, fp32 arithmetic on the bf16 matrix cores (split.hpp): forward with bias, ReLU and pooling in one pass; gradient
 // w.r.t. filter and bias from the pooled gradient, without the 32x32x64 gradient ever existing in memory.
 //
-// What the layer cannot do without is its output (33.5 MB at batch 128, written once); its products are 1.3 GFLOP.  Both
+// What the layer cannot do without is the images and its pooled output (1.6 and 9.2 MB at batch 128); its products are 1.3 GFLOP.  The
+// activations in front of the pooling (33.5 MB, most of what the forward kernel writes) are read by no kernel of a training step: they are
+// stored for callers of dsspk_conv_first_pool_fwd and dssp_workspace_tensor, who check ReLU decisions on them.  Both
 // directions use the image rows a band of output rows touches, laid out as patches: T[row][pixel][16] holds the 15
 // neighbouring values (5 pixels x 3 channels, contiguous in memory) that a filter row meets at that pixel, and a zero, as
 // three bf16 terms.  The reduction over a filter row is then 16 wide, and both operands of both directions are plain 8-byte

@@ -306,7 +306,9 @@ bool tiling_for(Tiling& t, int mt, int N, int OH, int OW, int ks) {
     return t.lds <= LDS_MAX;
 }
 
-// The largest tile (fewest halo rows and filter reads per pixel) that still gives most compute units a workgroup.
+// The largest tile (fewest halo rows and filter reads per pixel) that still gives most compute units (192 of 256) a workgroup.  With 96 /
+// 192 / 384 in its place, 5x5 on 15x15, us: batch 24 20.8 / 14.0 / 14.1, 48 27.0 / 21.0 / 19.0, 96 28.0 / 27.5 / 31.0, 128 31.0 / 30.8 /
+// 34.1, 160 55 / 55 / 48; 3x3 on 7x7: batch 96 9.1 / 6.7 / 6.7, 256 13.7 / 9.5 / 9.3.
 bool choose_tiling(Tiling& t, int N, int OH, int OW, int OC, int ks) {
     bool have = false;
     for (int mt = 8; mt >= 2; mt /= 2) {

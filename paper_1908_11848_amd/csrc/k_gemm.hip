@@ -172,7 +172,10 @@ __device__ __forceinline__ void tile_product(const Operand& a, const Operand& b,
 
 // Tile shapes: BIG 64x64 by 2x2 wavefronts of 32x32; MID 32x32 and SMALL 16x16 by one output sub-tile, the wavefronts
 // splitting k.  Rule: the largest tile that still gives half a chip of workgroups (128): the products here have few output
-// tiles and the time of one is the time of its slowest workgroup, while a smaller tile reads its operands more often.
+// tiles and the time of one is the time of its slowest workgroup, while a smaller tile reads its operands more often.  With 64 / 128 /
+// 256 in its place, us: product 256 x 256, K = 3072 25.7 / 11.4 / 11.4, 512 x 256 26.9 / 26.7 / 23.4, 1024 x 256 97 / 27.7 / 27.7,
+// 512 x 192, K = 384 5.5 / 6.0 / 6.0; backward pass of 3072 -> 256 at 32 rows 7.0 / 5.9 / 8.1, at 512 35.4 / 35.4 / 29.7, of 3136 -> 384 at
+// 64 rows 9.5 / 9.5 / 13.3, at 128 21.1 / 15.3 / 15.3, at 256 25.1 / 24.8 / 30.1.
 enum { BIG, MID, SMALL };
 inline int tile_shape(int M, int N) {
     if ((long)ceil_div(M, 64) * ceil_div(N, 64) >= 128) return BIG;
@@ -442,8 +445,9 @@ extern "C" int dsspk_gemm(void* stream, const float* A, long a_rs, long a_cs, co
     return DSSPK_LAUNCH_RC();
 }
 
-// Layers worth splitting K into (K of 1024 and more, fewer than 128 output tiles of 64 x 64): enough workgroups to cover
-// the chip, at least 8 k-chunks of work per layer.
+// Split-K for callers who want more workgroups than a product has output tiles (the networks' layers do not: wavefronts of a
+// workgroup split K without a second kernel).  Layers worth having: K of 1024 and more, fewer than 128 tiles of 64 x 64, at least 8
+// k-chunks per layer, as many as give 384 workgroups of such tiles; the launch may cut the result into smaller ones (tile_shape).
 extern "C" int dsspk_gemm_splitk_layers(int M, int N, int K) {
     if (M < 1 || N < 1 || K < 1) return 0;
     const int tiles = ceil_div(N, 64) * ceil_div(M, 64), chunks = ceil_div(K, mma::KC);

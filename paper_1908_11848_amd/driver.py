@@ -25,13 +25,14 @@ class Schedule:
         """grad_ptr(p) -> device pointer of worker p's gradient (None for a host-only context);
         pull_dst(p) -> device pointer of its local weights; step(p, n) enqueues worker p's n-th
         iteration (dssp_worker_step) or is None.  fused_pull: pushes go through dssp_push_pull, i.e. a worker
-        that is granted OK by its own push gets its snapshot from the apply kernel (same log, same results).
+        that is granted OK by its own push gets its snapshot from the apply kernel (same log, same results); a push that
+        can release waiting workers goes through dssp_push_many, alone, so that theirs come from that kernel as well.
         aggregate: pushes that share a timestamp go to the server together (dssp_push_many: decided one by one in
         worker order, applied by one kernel that also writes the snapshots; same log, same results)."""
         self.ctx, self.K, self.d, self.quota = ctx, K, durations, quota
         self.fused_pull = fused_pull
         self.aggregate = aggregate
-        self.aggregated = 0             # pushes that went through dssp_push_many
+        self.aggregated = 0             # pushes applied together with others of the same timestamp
         self.gp = grad_ptr or (lambda p: None)
         self.pd = pull_dst or (lambda p: None)
         self.step = step

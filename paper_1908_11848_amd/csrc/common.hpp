@@ -18,3 +18,14 @@ static inline int stream_grid(long items_per_block_total, int cap = 256 * 8) {
     if (g > cap) g = cap;
     return (int)g;
 }
+
+// Workgroups are handed to the 8 XCDs round-robin (workgroup b runs on XCD b mod 8) and every XCD has an L2 of its
+// own.  Tiles that are neighbours in memory share data - halo rows between the bands of an image, the whole input
+// tile between the channel splits of a band, dy between the input-channel slices of the last stage's d-filter
+// kernel - so consecutive tiles go to ONE XCD: workgroup b takes tile (b mod 8) * (n / 8) + b / 8, and what the
+// first of them fetched is in that L2 for the next (without this, halo rows and shared tiles come over the fabric
+// once per XCD that touches them: 1.1x to 1.7x the operands' bytes).  Needs n to be a multiple of 8.
+__device__ __forceinline__ int xcd_tile(int block, int n_blocks) {
+    constexpr int XCDS = 8;
+    return n_blocks % XCDS ? block : (block % XCDS) * (n_blocks / XCDS) + block / XCDS;
+}

@@ -30,17 +30,6 @@ namespace {
 
 constexpr int THREADS = 256;
 
-// Workgroups are handed to the 8 XCDs round-robin (workgroup b runs on XCD b mod 8) and every XCD has an L2 of its
-// own.  Tiles that are neighbours in memory share data - halo rows between the bands of an image, the whole input
-// tile between the channel splits of a band, dy between the input-channel slices of the last stage's d-filter
-// kernel - so consecutive tiles go to ONE XCD: workgroup b takes tile (b mod 8) * (n / 8) + b / 8, and what the
-// first of them fetched is in that L2 for the next (without this, halo rows and shared tiles come over the fabric
-// once per XCD that touches them: 1.1x to 1.7x the operands' bytes).  Needs n to be a multiple of 8.
-__device__ __forceinline__ int xcd_tile(int block, int n_blocks) {
-    constexpr int XCDS = 8;
-    return n_blocks % XCDS ? block : (block % XCDS) * (n_blocks / XCDS) + block / XCDS;
-}
-
 // ---- gradient w.r.t. the filter by minimal filtering F(3x3, 2x2):
 //      dw[tap][ci][co] = sum over pixels x[pixel + tap][ci] dy[pixel][co]; per 2x2 tile of dy and its 4x4 patch of x,
 //      dw += A^T [ (B^T x B) .* (G dy G^T) ] A with B^T = [1 0 -1 0; 0 1 1 0; 0 -1 1 0; 0 -1 0 1],

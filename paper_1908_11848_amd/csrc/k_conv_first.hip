@@ -28,11 +28,6 @@ constexpr int R = 8, BANDS = HW / R;                                        // o
 constexpr int TPITCH = 3 * 32 + 8, TPLANE = 32;                             // bytes of a pixel of T, of one of its planes
 constexpr int E = F * ROWF * CO;                                            // filter elements
 
-__device__ __forceinline__ int xcd_tile(int block, int n_blocks) {          // consecutive bands to one XCD (shared rows)
-    constexpr int XCDS = 8;
-    return n_blocks % XCDS ? block : (block % XCDS) * (n_blocks / XCDS) + block / XCDS;
-}
-
 // T rows for image rows h0 .. h0 + ROWS - 1.  A task is four values of one pixel's patch row.
 template <int ROWS>
 __device__ __forceinline__ void build_patches(const float* __restrict__ x, int n, int h0, char* T, int tid) {

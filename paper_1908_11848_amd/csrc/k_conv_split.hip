@@ -11,12 +11,6 @@ namespace {
 constexpr int THREADS = 256;
 constexpr size_t LDS_MAX = 160 * 1024;
 
-// Workgroups go to the 8 XCDs round-robin; consecutive tiles (shared halo rows) go to one XCD and its L2.
-__device__ __forceinline__ int xcd_tile(int block, int n_blocks) {
-    constexpr int XCDS = 8;
-    return n_blocks % XCDS ? block : (block % XCDS) * (n_blocks / XCDS) + block / XCDS;
-}
-
 // ---------------------------------------------------------------------------------------------
 // Filter planes in operand order: [step][16 result channels][plane][lane] of 16 bytes, step = (tap, 32 reduction channels),
 // lane (l16, q) holding the reduction channels 8 q .. 8 q + 7 of result channel l16.  A wavefront then fetches an operand

@@ -425,8 +425,14 @@ def test_device_clock_driven_schedule_on_an_unequal_cluster(oracle_nn):
         ratio.append(float(np.median(it)))
     say("device-clock schedule: pushes per worker %s, %d blocks, last push at %d us, median iteration %s us" % (n_it, blocks, st["T_end"], [int(r) for r in ratio]))
     # the emulated GPUs are as unequal as asked (how often a worker pushes is the controller's business: the run above
-    # may well grant the middle worker more extra iterations than the fastest ones)
-    assert ratio[3] > 1.3 * ratio[2] > 1.3 * 1.3 * max(ratio[0], ratio[1]) and min(n_it[0], n_it[1]) >= n_it[3] and blocks > 0
+    # may well grant the middle worker more extra iterations than the fastest ones): an iteration is held to the asked multiple of its
+    # real duration and no longer ...
+    for p in range(K):
+        stretch = np.median([(t[2] - t[0]) / (t[1] - t[0]) for t in st["times"][p][2:]])
+        assert slow[p] - 0.02 <= stretch <= 1.1 * slow[p], (p, stretch)
+    # ... and so medians stand in the asked proportion, up to what sharing the chip does to the real durations: 285 us alone, 450 us
+    # beside three others (ratio 1.6, over 100 runs), which leaves at least 3.5 / 2 / 1.6 = 1.09 and 2 / 1.6 = 1.25
+    assert ratio[3] > 1.05 * ratio[2] > 1.05 * 1.2 * max(ratio[0], ratio[1]) and min(n_it[0], n_it[1]) >= n_it[3] and blocks > 0
     out = ps.run(K, s_L, r_max, lr, w0, d, ps.model_grad_fn(net, xs, ys), total=total)
     assert log == out["log"]
     e = rel_l2(w_gpu, out["w"])

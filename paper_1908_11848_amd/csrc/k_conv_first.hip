@@ -10,8 +10,8 @@
 // three bf16 terms.  The reduction over a filter row is then 16 wide, and both operands of both directions are plain 8-byte
 // or transposing LDS reads.
 //
-// Measured alone, batch 37 / 128 / 512: forward and pooling 10.8 / 16.3 / 58.3 us (as implicit GEMM on the fp32 matrix cores and a
-// pooling kernel 17.8 / 37.0 / 122), gradients with their reduction 14.3 / 22.4 / 53.7 us (pooling backward, d-filter and column
+// Measured alone, batch 37 / 128 / 512: forward and pooling 10.9 / 16.3 / 55.8 us (as implicit GEMM on the fp32 matrix cores and a
+// pooling kernel 17.8 / 37.0 / 122), gradients with their reduction 14.3 / 22.4 / 53.1 us (pooling backward, d-filter and column
 // sums as kernels of their own 49 / 78 / 246).  Forward at batch 128 writes 41 MB: 2.6 TB/s; the rest is the patches'
 // construction, then 4 us of matrix instructions, one after the other within a workgroup (two fit a compute unit).
 #include "jobs.hpp"

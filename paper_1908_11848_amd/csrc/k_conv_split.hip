@@ -81,7 +81,7 @@ __global__ __launch_bounds__(THREADS) void filter_planes_kernel(Frag fwd, Frag b
 // tile), and the two halves of a sum meet in LDS at the end.  The smaller tiles gain nothing from that: several of their
 // workgroups share a compute unit, and with more than one stream eight wavefronts cost 4 % of a step at batch 37.
 // Bound by the matrix cores: 64 -> 64 at 5x5 on 15x15, batch 128, is 2.46 M MFMAs = 17 us of them at 2.4 GHz (the chip runs
-// them at 1.9).  Measured at batch 37 / 128 / 512: 19 / 33 / 140 us (largest tile with four wavefronts: 38 / 150 us).
+// them at 1.9).  Measured at batch 37 / 128 / 512: 20 / 34 / 135 us (largest tile with four wavefronts 12 % more).
 struct Geom {
     int N, H, W, OH, OW, pad;      // input / output pixel grid of this pass
     int IC, OC;                    // reduction / result channels of this pass
@@ -346,7 +346,7 @@ int launch_conv(hipStream_t s, const float* src, const uint4* wf, const float* b
 // LDS has the channels side by side: the transposing LDS reads turn them.  The next tile's loads are in flight while the
 // matrix cores work.  Wavefront w: input channels 16 (w mod 2) .., output channels 32 (w / 2 mod 2) .., the first or second 32
 // pixels of the tile (w / 4: two wavefronts to a SIMD, one multiplies while the other fetches); their sums meet in LDS at the end.
-// Measured with the reduction at batch 37 / 128 / 512: 23 / 51 / 146 us (four wavefronts, reads behind the barrier: 24 / 53 / 159).
+// Measured with the reduction at batch 37 / 128 / 512: 23 / 50 / 143 us (four wavefronts, reads behind the barrier: 1 / 2 / 13 us more).
 // Output: partial[chunk][KS KS IC OC (+ OC bias sums, added up by the workgroups of filter row 0 and the first channels)].
 constexpr int WG_PX = 64, WG_XPX = 96, CTHREADS = 512;
 constexpr int XPITCH = 32 * 6 + 32, DPITCH = 64 * 6 + 32;      // 24 and 8 words (mod 32): four rows cover all banks once

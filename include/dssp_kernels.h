@@ -181,7 +181,8 @@ size_t dsspk_conv_wgrad_scratch_floats(int N, int H, int W, int Cin, int Cout, i
 
 /* Stride-1 convolutions of wide layers (Cin and Cout multiples of 64, k x k filters with k = 3 or 5, pad < k) with fp32
  * arithmetic on the bf16 matrix cores: every operand is split into three bf16 terms (24 significant bits in all), six of the
- * nine products of terms are accumulated in fp32; no less exact than dsspk_conv_* on the same operands, over all of fp32's range
+ * nine products of terms are accumulated in fp32; no less exact than dsspk_conv_* on the same operands (filter gradients of other
+ * shapes than the networks' up to 1.2 times the error, where dsspk_conv_bwd_weight sums shorter pieces), over all of fp32's range
  * (subnormal operands included).  Where an operand of 1e31 or more, a result above 6e23, an infinity or a NaN takes part, the results around it
  * are computed on the fp32 matrix cores: as dsspk_conv_* would, at several times the time.  dsspk_conv_split_covers: 1 if the
  * shape is one of these, its tiles fit and its filter has at most 2^30 elements (the launchers return -1 otherwise).

@@ -122,11 +122,18 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
         base[t] = (ok ? ((gi * TH + r) * TW + c) * PITCH : 0) + 16 * q + 64 * half;
         out[t] = ok ? (((long)(n0 + gi) * g.OH + r0 + r) * g.OW + c) * g.OC : -1;
     }
-    floatx4 acc[W::TC][W::TP], small[W::TC][W::TP];
+    // Small products have accumulators of their own, except in the largest tile: its halves round each sum half as often, which keeps
+    // it below the fp32 matrix cores' error (5x5: 3.9e-7 against 4.7e-7), and 32 more registers would leave no room on the SIMD for
+    // another kernel's wavefronts.
+    constexpr bool APART = W::HALVES == 1;
+    floatx4 acc[W::TC][W::TP], small[APART ? W::TC : 1][APART ? W::TP : 1];
 #pragma unroll
     for (int i = 0; i < W::TC; ++i)
 #pragma unroll
-        for (int t = 0; t < W::TP; ++t) acc[i][t] = small[i][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < W::TP; ++t) {
+            acc[i][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (APART) small[i][t] = acc[i][t];
+        }
 
     const int tiles_c = g.OC / 16, steps_c = g.IC / 32;
     const split::Buffer images = split::buffer(src + (long)n0 * g.H * g.W * g.IC, 4u * (unsigned)(min(g.G, g.N - n0) * g.H * g.W * g.IC));
@@ -186,17 +193,20 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
                 if (s + u >= STEPS) break;
                 load_p((u + 1) & 1, s + u + 1);
                 __builtin_amdgcn_sched_barrier(0);      // or the compiler moves the reads down to their use, behind the products
-                split::product(wv[u], pv[u & 1], acc, small);
+                if constexpr (APART) split::product(wv[u], pv[u & 1], acc, small);
+                else split::product(wv[u], pv[u & 1], acc, acc);
                 __builtin_amdgcn_sched_barrier(0);
                 load_w(u, s + u + WD);
             }
         }
     }
 
+    if constexpr (APART) {
 #pragma unroll
-    for (int i = 0; i < W::TC; ++i)
+        for (int i = 0; i < W::TC; ++i)
 #pragma unroll
-        for (int t = 0; t < W::TP; ++t) acc[i][t] += small[i][t];
+            for (int t = 0; t < W::TP; ++t) acc[i][t] += small[i][t];
+    }
     auto finish = [&](const floatx4& sum, int ct, long at) {
         if (at < 0) return;
         const int co = 16 * ct + 4 * q;

@@ -164,6 +164,26 @@ int dsspk_conv_bwd_data_bn_wgrad_records(void* stream, const float* dz_dev, cons
                                          float* out_dev, const float* xc_post_dev, const float* stats_post_dev,
                                          float* records_dev, const float* x_in_dev, float* partial_dev,
                                          const float* red_partial_dev, float* red_dw_dev, int red_E, int red_chunks, int N, int H, int C);
+/* The same layers (C = 16 at 32x32, 32 at 16x16, 64 at 8x8) for larger batches, up to DSSPK_CONV3X3_LARGE_MAX images: larger workgroups,
+ * which leave half as many records and partial results (one per image; 16 channels: two) and always add up the records they are given.
+ * dsspk_conv3x3_large_parts: records of a tensor and, for C = 16 and 32, partial results of 9*C*C floats; 0: not covered.
+ * fwd: y = conv(a), a = src (records NULL, parts 0) or ReLU(BN(src) (+ shortcut)), stored in act_out, mean / invstd in stats_out, as
+ * dsspk_conv_fwd_prebn; records of y to records_out.  bwd_post: as dsspk_conv_bwd_data_post.  bwd: as
+ * dsspk_conv_bwd_data_bn_wgrad_records (C = 16, 32: partial, dx NULL) and dsspk_conv_bwd_data_bn_records (C = 64: dx, partial NULL). */
+#define DSSPK_CONV3X3_LARGE_MAX 128
+int dsspk_conv3x3_large_parts(int N, int H, int C);
+int dsspk_conv3x3_large_fwd(void* stream, const float* src_dev, const float* records_dev, int parts, const float* gamma_dev,
+                            const float* beta_dev, float eps, const float* shortcut_dev, float* act_out_dev, float* stats_out_dev,
+                            const float* w_dev, float* dst_dev, float* records_out_dev, int N, int H, int C);
+int dsspk_conv3x3_large_bwd_post(void* stream, const float* dy_dev, const float* w_dev, const float* add_dev, float* dz_dev,
+                                 const float* mask_src_dev, const float* xc_dev, const float* stats_dev, float* records_dev, int N, int H,
+                                 int C);
+int dsspk_conv3x3_large_bwd(void* stream, const float* dz_dev, const float* xc_dev, const float* stats_dev, const float* gamma_dev,
+                            const float* in_records_dev, int parts, float* dgamma_dev, float* dbeta_dev, float* dx_dev, float* partial_dev,
+                            const float* w_dev, const float* add_dev, float* out_dev, const float* x_in_dev, const float* xc_post_dev,
+                            const float* stats_post_dev, float* records_dev, const float* red_partial_dev, float* red_dw_dev, int red_E,
+                            int red_chunks, int N, int H, int C);
+
 /* dw[kh][kw][ci][co] = sum over batch and output pixels of x * dy.  Two stages (partial sums per
  * pixel chunk, then a fixed-order reduction).  scratch_dev: dsspk_conv_wgrad_scratch_floats(...) floats. */
 int dsspk_conv_bwd_weight(void* stream, const float* x_dev, const float* dy_dev, float* dw_dev, float* scratch_dev,

@@ -44,9 +44,13 @@ struct TotalsJob {
 static inline bool reduce_by_rows(int chunks) { return chunks > 64; }
 static inline int reduce_groups(int E, int chunks) { return reduce_by_rows(chunks) ? (E + 31) / 32 : (E + 1023) / 1024; }
 
-__device__ __forceinline__ void wgrad_reduce(const ReduceJob& j, int block, float* lds) {
+// T: threads of the carrier's workgroups, a multiple of THREADS; every THREADS of them work like a workgroup of their own (LDS_FLOATS
+// each), so that the order of the sums does not depend on the carrier.
+template <int T = THREADS>
+__device__ __forceinline__ void wgrad_reduce(const ReduceJob& j, int wg, float* lds) {
+    const int tid = threadIdx.x % THREADS, block = wg * (T / THREADS) + (int)threadIdx.x / THREADS, blocks = j.blocks * (T / THREADS);
     if (j.chunks <= 64) {
-        for (int e = (block * THREADS + (int)threadIdx.x) * 4; e < j.E; e += j.blocks * THREADS * 4) {
+        for (int e = (block * THREADS + tid) * 4; e < j.E; e += blocks * THREADS * 4) {
             float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
             for (int k0 = 0; k0 < j.chunks; k0 += 8) {
                 float4 v[8];
@@ -61,11 +65,11 @@ __device__ __forceinline__ void wgrad_reduce(const ReduceJob& j, int block, floa
         }
         return;
     }
-    float4(*part)[8] = reinterpret_cast<float4(*)[8]>(lds);
-    const int cg = threadIdx.x & 7, rg = threadIdx.x >> 3;
+    float4(*part)[8] = reinterpret_cast<float4(*)[8]>(lds + threadIdx.x / THREADS * LDS_FLOATS);
+    const int cg = tid & 7, rg = tid >> 3;
     const int groups = (j.E + 31) / 32;
-    for (int grp = block; grp < groups; grp += j.blocks) {
-        const int e = (grp * 8 + cg) * 4;
+    for (int g0 = wg * (T / THREADS); g0 < groups; g0 += blocks) {         // the same number of rounds for all of the workgroup
+        const int e = ((g0 + (int)threadIdx.x / THREADS) * 8 + cg) * 4;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
         if (e < j.E)
             for (int k = rg; k < j.chunks; k += 128) {

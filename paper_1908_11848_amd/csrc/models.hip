@@ -275,6 +275,8 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
     return 0;
 }
 
+constexpr int LARGE_ABOVE = 96;
+
 int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, const float* w, float* g, float* loss, std::string& err) {
     const int m = P->m;
     const float eps = 1e-5f;
@@ -291,9 +293,27 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     // and only the last block of a run materialises its output with the stand-alone BN kernels.
     float *recA = bscr, *recB = F(P->bn_scratch2);
     const int nb = (int)P->blocks.size();
+    // Above LARGE_ABOVE images the larger workgroups of dsspk_conv3x3_large_*: half as many records, few enough for every workgroup to
+    // add up (173 launches of a 110-layer step less).  Below, their number leaves compute units idle.  A round of the 20-layer network
+    // with the smaller / larger ones: batch 64, one worker 741 / 762 us, four 1105 / 1136; batch 128, one 850 / 827, four 1575 / 1568; a push of
+    // the 110-layer network, batch 128, one worker 3962 / 3881 us, four 1858 / 1815, eight of different speed 1877 / 1832.
+    const bool large = m > LARGE_ABOVE && m <= DSSPK_CONV3X3_LARGE_MAX;
+    auto parts_of = [&](int H, int cin, int cout, int stride) {       // records that the forward convolution leaves
+        if (!large) return dsspk_conv_fwd_stat_parts(m, H, H, cin, cout, 3, 3, stride, 1);
+        return cin == cout && stride == 1 ? dsspk_conv3x3_large_parts(m, H, cin) : 0;
+    };
+    auto conv = [&](const float* src, const float* wt, float* dst, int H, int cin, int cout, int stride, float* rec) {
+        if (large && rec) return dsspk_conv3x3_large_fwd(s, src, nullptr, 0, nullptr, nullptr, 0.f, nullptr, nullptr, nullptr, wt, dst, rec, m, H, cin);
+        return dsspk_conv_fwd(s, src, wt, nullptr, dst, m, H, H, cin, cout, 3, 3, stride, 1, 0, rec);
+    };
+    auto conv_prebn = [&](const float* src, const float* rec, int parts, const float* gamma, const float* beta, const float* shortcut, float* act,
+                          float* stats, const float* wt, float* dst, float* rec_out, int H, int C) {
+        return (large ? dsspk_conv3x3_large_fwd : dsspk_conv_fwd_prebn)(s, src, rec, parts, gamma, beta, eps, shortcut, act, stats, wt, dst, rec_out,
+                                                                       m, H, C);
+    };
     auto regular = [&](int i) {
         const ResBlock& b = P->blocks[i];
-        return b.stride == 1 && b.cin == b.cout && dsspk_conv_fwd_stat_parts(m, b.H, b.H, b.cin, b.cout, 3, 3, 1, 1) > 0;
+        return b.stride == 1 && b.cin == b.cout && parts_of(b.H, b.cin, b.cout, 1) > 0;
     };
     const float* cur = F(P->stem_a);
     bool pending = false;            // the previous block's output is not written yet (its BN2 is folded into this conv1)
@@ -301,22 +321,20 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         const ResBlock& B = P->blocks[bi];
         const int Ho = B.H / B.stride;
         const long M = (long)m * Ho * Ho;
-        const int parts1 = dsspk_conv_fwd_stat_parts(m, B.H, B.H, B.cin, B.cout, 3, 3, B.stride, 1);
-        const int parts2 = dsspk_conv_fwd_stat_parts(m, Ho, Ho, B.cout, B.cout, 3, 3, 1, 1);
+        const int parts1 = parts_of(B.H, B.cin, B.cout, B.stride);
+        const int parts2 = parts_of(Ho, B.cout, B.cout, 1);
         if (pending) {
             const ResBlock& Pv = P->blocks[bi - 1];
             const float* pin = bi >= 2 ? F(P->blocks[bi - 2].out) : F(P->stem_a);         // the previous block's input = its shortcut
-            RUN(dsspk_conv_fwd_prebn(s, F(Pv.c2), recB, parts2, w + Pv.g2, w + Pv.b2, eps, pin, F(Pv.out), F(Pv.st2),
-                                     w + B.w1, F(B.c1), recA, m, B.H, B.cin));
+            RUN(conv_prebn(F(Pv.c2), recB, parts2, w + Pv.g2, w + Pv.b2, pin, F(Pv.out), F(Pv.st2), w + B.w1, F(B.c1), recA, B.H, B.cin));
         } else {
-            RUN(dsspk_conv_fwd(s, cur, w + B.w1, nullptr, F(B.c1), m, B.H, B.H, B.cin, B.cout, 3, 3, B.stride, 1, 0, parts1 ? recA : nullptr));
+            RUN(conv(cur, w + B.w1, F(B.c1), B.H, B.cin, B.cout, B.stride, parts1 ? recA : nullptr));
         }
         if (parts1 && parts2) {
-            RUN(dsspk_conv_fwd_prebn(s, F(B.c1), recA, parts1, w + B.g1, w + B.b1, eps, nullptr, F(B.a1), F(B.st1),
-                                     w + B.w2, F(B.c2), recB, m, Ho, B.cout));
+            RUN(conv_prebn(F(B.c1), recA, parts1, w + B.g1, w + B.b1, nullptr, F(B.a1), F(B.st1), w + B.w2, F(B.c2), recB, Ho, B.cout));
         } else {
             RUN(dsspk_bn_fwd(s, F(B.c1), w + B.g1, w + B.b1, F(B.a1), F(B.st1), recA, M, B.cout, eps, 1, 0, nullptr, 0, 0, 0, parts1));
-            RUN(dsspk_conv_fwd(s, F(B.a1), w + B.w2, nullptr, F(B.c2), m, Ho, Ho, B.cout, B.cout, 3, 3, 1, 1, 0, parts2 ? recB : nullptr));
+            RUN(conv(F(B.a1), w + B.w2, F(B.c2), Ho, B.cout, B.cout, 1, parts2 ? recB : nullptr));
         }
         pending = regular(bi) && parts2 > 0 && bi + 1 < nb && regular(bi + 1);
         if (!pending) {
@@ -347,6 +365,10 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     float* scrs[2] = {scr, F(P->wg_scratch2)};
     int parts0 = 0;
     bool tot0 = false;
+    auto conv_bwd_post = [&](const float* dy, const float* wt, const float* add, float* dz, const float* mask, const float* xc, const float* st,
+                             float* rec, int H, int C) {
+        return (large ? dsspk_conv3x3_large_bwd_post : dsspk_conv_bwd_data_post)(s, dy, wt, add, dz, mask, xc, st, rec, m, H, C);
+    };
     struct { float* partial; float* dw; int E, chunks; bool on; } pend = {nullptr, nullptr, 0, 0, false};
     auto flush = [&]() -> int {
         if (!pend.on) return 0;
@@ -365,6 +387,15 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
                              float* ntot, float* ndgamma, float* ndbeta) -> int {
         float* out_scr = (pend.on && pend.partial == scrs[0]) ? scrs[1] : scrs[0];
         const float* rp = pend.on ? pend.partial : nullptr;
+        if (large) {
+            int chunks = parts_of(H, Cc, Cc, 1);
+            RUN(dsspk_conv3x3_large_bwd(s, dz, xc, st, gamma, in_rec, in_parts, in_dgamma, in_dbeta, Cc == 64 ? g1 : nullptr,
+                                        Cc == 64 ? nullptr : out_scr, wt, add, out, x_in, xc_post, st_post, records, rp, pend.dw, pend.E, pend.chunks,
+                                        m, H, Cc));
+            if (Cc == 64) RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, nullptr, 0, 0, nullptr, nullptr, nullptr, &chunks));
+            pend.partial = out_scr; pend.dw = dw; pend.E = 9 * Cc * Cc; pend.chunks = chunks; pend.on = true;
+            return 0;
+        }
         const bool own_sums = dsspk_conv_records_inline(in_parts, Cc) != 0;
         if (!own_sums && !ready) RUN(dsspk_bn_bwd_totals(s, in_rec, in_parts, Cc, tot, in_dgamma, in_dbeta));
         const float* totals = own_sums ? nullptr : tot;
@@ -388,9 +419,9 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         const float* xin = bi ? F(P->blocks[bi - 1].out) : F(P->stem_a);
         const int Ho = B.H / B.stride;
         const long M = (long)m * Ho * Ho;
-        const int parts1 = dsspk_conv_fwd_stat_parts(m, Ho, Ho, B.cout, B.cout, 3, 3, 1, 1);
+        const int parts1 = parts_of(Ho, B.cout, B.cout, 1);
         const bool identity = B.stride == 1 && B.cin == B.cout;
-        const int partsp = identity ? dsspk_conv_fwd_stat_parts(m, B.H, B.H, B.cin, B.cout, 3, 3, 1, 1) : 0;
+        const int partsp = identity ? parts_of(B.H, B.cin, B.cout, 1) : 0;
         const bool fused1 = parts1 > 0 && partsp > 0;        // conv1's layer takes the two-launch form
         bool tot1 = false;                                   // sums of BN1's records are in totA
         // ---- BN2 + conv2: g0 = dz2 -> g1 = d conv2 output, g2 = dz1 = d a1 * [a1 > 0] (+ BN1's records in bscr)
@@ -404,7 +435,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             RUN(dsspk_bn_bwd_dx(s, F(B.c2), w + B.g2, F(B.st2), g0, g1, g + B.g2, g + B.b2, recB0, M, B.cout, parts0));
             RUN(dsspk_conv_bwd_weight(s, F(B.a1), g1, g + B.w2, scr, m, Ho, Ho, B.cout, B.cout, 3, 3, 1, 1));
             if (parts1) {
-                RUN(dsspk_conv_bwd_data_post(s, g1, w + B.w2, nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr, m, Ho, B.cout));
+                RUN(conv_bwd_post(g1, w + B.w2, nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr, Ho, B.cout));
             } else {
                 RUN(dsspk_conv_bwd_data(s, g1, w + B.w2, nullptr, g2, m, Ho, Ho, B.cout, B.cout, 3, 3, 1, 1));
                 RUN(dsspk_bn_bwd_reduce(s, F(B.c1), F(B.st1), g2, F(B.a1), bscr, M, B.cout));
@@ -430,7 +461,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             if (partsp) {
                 const float* pc = bi ? F(P->blocks[bi - 1].c2) : F(P->stem_c);
                 const float* pst = bi ? F(P->blocks[bi - 1].st2) : F(P->stem_st);
-                RUN(dsspk_conv_bwd_data_post(s, g1, w + B.w1, g0, g2, xin, pc, pst, recB0, m, B.H, B.cin));
+                RUN(conv_bwd_post(g1, w + B.w1, g0, g2, xin, pc, pst, recB0, B.H, B.cin));
             } else {
                 RUN(dsspk_conv_bwd_data(s, g1, w + B.w1, identity ? g0 : nullptr, g2, m, B.H, B.H, B.cin, B.cout, 3, 3, B.stride, 1));
                 if (!identity) RUN(dsspk_shortcut_bwd_acc(s, g0, g2, m, Ho, Ho, B.cout));

@@ -97,9 +97,12 @@ __device__ __forceinline__ uint2 read_tr(const char* lds) {
 
 // One matrix-core operand of (scaled) fp32 values.  32 reduction channels: the three planes, a lane's eight channels each.
 // 16 reduction channels (C = 16): an instruction's 32 indices take two planes of them, a lane's four channels each, and
-// three instructions instead of six do the six products: (y2, y0) . (x0, x2), (y0, y1) . (x1, x0), (y0, y1) . (x0, x1).
-template <int C> struct Filt { uint4 v[C == 16 ? 2 : 3]; };
-template <int C> struct Pix { uint4 v[3]; };
+// three instructions instead of six do the six products: (y2, y0) . (x0, x2), (y1, y0) . (x0, x1), (y0, y1) . (x0, x1).
+// A pixel operand is fetched as the two register quads it is used as, x0 twice: put together by moves, it takes ten more vector
+// instructions, and as these wait for the fetch they follow, the fetch of the next operand no longer overlaps the products of the
+// present one.
+template <int C> struct Filt { uint4 v[3]; };
+template <int C> struct Pix { uint4 v[C == 16 ? 2 : 3]; };
 
 template <int C> __device__ __forceinline__ Filt<C> filter_operand(const float4 (&r)[C == 16 ? 1 : 2]) {
     Filt<C> f;
@@ -107,7 +110,8 @@ template <int C> __device__ __forceinline__ Filt<C> filter_operand(const float4 
     split4(r[0], lo);
     if constexpr (C == 16) {
         f.v[0] = make_uint4(lo[2].x, lo[2].y, lo[0].x, lo[0].y);
-        f.v[1] = make_uint4(lo[0].x, lo[0].y, lo[1].x, lo[1].y);
+        f.v[1] = make_uint4(lo[1].x, lo[1].y, lo[0].x, lo[0].y);
+        f.v[2] = make_uint4(lo[0].x, lo[0].y, lo[1].x, lo[1].y);
     } else {
         uint2 hi[PLANES];
         split4(r[1], hi);
@@ -117,14 +121,14 @@ template <int C> __device__ __forceinline__ Filt<C> filter_operand(const float4 
     return f;
 }
 
-template <int C, int PLANE> __device__ __forceinline__ Pix<C> pixel_operand(const char* at) {
+// at, again: the same address; C = 16 fetches x0 through both, and the compiler must not know that it is the same
+template <int C, int PLANE> __device__ __forceinline__ Pix<C> pixel_operand(const char* at, const char* again) {
     Pix<C> x;
     if constexpr (C == 16) {
-        const uint2 x0 = *reinterpret_cast<const uint2*>(at), x1 = *reinterpret_cast<const uint2*>(at + PLANE),
-                    x2 = *reinterpret_cast<const uint2*>(at + 2 * PLANE);
-        x.v[0] = make_uint4(x0.x, x0.y, x2.x, x2.y);
-        x.v[1] = make_uint4(x1.x, x1.y, x0.x, x0.y);
-        x.v[2] = make_uint4(x0.x, x0.y, x1.x, x1.y);
+        const uint2 a = *reinterpret_cast<const uint2*>(at), x2 = *reinterpret_cast<const uint2*>(at + 2 * PLANE),
+                    b = *reinterpret_cast<const uint2*>(again), x1 = *reinterpret_cast<const uint2*>(again + PLANE);
+        x.v[0] = make_uint4(a.x, a.y, x2.x, x2.y);
+        x.v[1] = make_uint4(b.x, b.y, x1.x, x1.y);
     } else {
 #pragma unroll
         for (int p = 0; p < PLANES; ++p) x.v[p] = *reinterpret_cast<const uint4*>(at + p * PLANE);
@@ -145,7 +149,7 @@ template <int C> constexpr int products() { return C == 16 ? 3 : 6; }
 // product p of the sum, small ones first
 template <int C> __device__ __forceinline__ floatx4 product(int p, const Filt<C>& f, const Pix<C>& x, floatx4 acc) {
     if constexpr (C == 16) {
-        return mfma(f.v[p ? 1 : 0], x.v[p], acc);
+        return mfma(f.v[p], x.v[p ? 1 : 0], acc);
     } else {
         constexpr int PF[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
         return mfma(f.v[PF[p]], x.v[PX[p]], acc);

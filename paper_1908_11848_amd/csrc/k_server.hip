@@ -11,15 +11,17 @@
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kUnroll = 4;      // 16-byte vectors in flight per lane per operand
+// 16-byte vectors in flight per lane per operand, and one workgroup for every kThreads * kUnroll of them however many: at 25 M parameters
+// apply + pull in one pass takes 58.1 us so, 59.1 with four, 60.0 with one, and 60.5 with four and at most 2048 workgroups in a loop.
+constexpr int kUnroll = 2;
 
 __global__ __launch_bounds__(kThreads) void apply_kernel(float* __restrict__ w, const float* __restrict__ g,
                                                           long n4, long n, float scale,
                                                           uint64_t* stamp, uint64_t version) {
     floatx4* __restrict__ w4 = reinterpret_cast<floatx4*>(w);
     const floatx4* __restrict__ g4 = reinterpret_cast<const floatx4*>(g);
-    const long stride = (long)gridDim.x * kThreads * kUnroll;
-    for (long base = (long)blockIdx.x * kThreads * kUnroll + threadIdx.x; base < n4; base += stride) {
+    {
+        const long base = (long)blockIdx.x * kThreads * kUnroll + threadIdx.x;
         floatx4 wv[kUnroll], gv[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
@@ -47,8 +49,8 @@ __global__ __launch_bounds__(kThreads) void pull_kernel(float* __restrict__ dst,
                                                          long n4, long n, uint64_t* dst_stamp, const uint64_t* stamp) {
     floatx4* __restrict__ d4 = reinterpret_cast<floatx4*>(dst);
     const floatx4* __restrict__ w4 = reinterpret_cast<const floatx4*>(w);
-    const long stride = (long)gridDim.x * kThreads * kUnroll;
-    for (long base = (long)blockIdx.x * kThreads * kUnroll + threadIdx.x; base < n4; base += stride) {
+    {
+        const long base = (long)blockIdx.x * kThreads * kUnroll + threadIdx.x;
         floatx4 v[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
@@ -76,8 +78,8 @@ __global__ __launch_bounds__(kThreads) void apply_pull_kernel(float* __restrict_
     floatx4* __restrict__ w4 = reinterpret_cast<floatx4*>(w);
     floatx4* __restrict__ d4 = reinterpret_cast<floatx4*>(dst);
     const floatx4* __restrict__ g4 = reinterpret_cast<const floatx4*>(g);
-    const long stride = (long)gridDim.x * kThreads * kUnroll;
-    for (long base = (long)blockIdx.x * kThreads * kUnroll + threadIdx.x; base < n4; base += stride) {
+    {
+        const long base = (long)blockIdx.x * kThreads * kUnroll + threadIdx.x;
         floatx4 wv[kUnroll], gv[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
@@ -116,31 +118,53 @@ struct ManyArgs {
     int m, n_dst;
 };
 
-constexpr int kManyChunk = 4;       // gradients fetched together per vector
+// GRADS gradients are fetched together, for VECS vectors per lane kThreads apart, so that a workgroup takes GRADS * VECS * 4 KB from memory at
+// a time, 4 * VECS KB of each stream in a row.  Many streams want long stretches of each: 16 gradients and 16 snapshots of 25 M
+// parameters (34 streams) take 592 us with <2, 8>, 602 with <4, 2>, 613 with <4, 4>, 648 with <4, 1> (630 with at most 2048 workgroups in a
+// loop: two passes over more streams than the memory has open rows); one gradient and four snapshots 104, 107, 104, 107 (118).  A small
+// vector wants workgroups: 0.2 M parameters, 8 and 8, 13.1 us with <2, 8>, 6.3 with <4, 1>; 1.7 M, 16 and 16, 40.8 and 38.8; 8 M 187 and 205.
+template <int GRADS, int VECS, bool ALL>
+__device__ __forceinline__ void apply_many(floatx4* __restrict__ w4, const ManyArgs& a, long first, long n4, float scale) {
+    const unsigned tid = threadIdx.x;           // the rest of an address is the same for the whole workgroup
+    auto in = [&](int u) { return ALL || first + u * kThreads + tid < n4; };
+    floatx4 wv[VECS];
+#pragma unroll
+    for (int u = 0; u < VECS; ++u)
+        if (in(u)) wv[u] = (w4 + first + u * kThreads)[tid];
+    int d = 0;
+    for (int j0 = 0; j0 < a.m; j0 += GRADS) {
+        floatx4 gv[GRADS][VECS];
+#pragma unroll
+        for (int c = 0; c < GRADS; ++c)
+            if (j0 + c < a.m)
+#pragma unroll
+                for (int u = 0; u < VECS; ++u)
+                    if (in(u)) gv[c][u] = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(a.g[j0 + c]) + first + u * kThreads + tid);
+#pragma unroll
+        for (int c = 0; c < GRADS; ++c)
+            if (j0 + c < a.m) {
+#pragma unroll
+                for (int u = 0; u < VECS; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) wv[u][e] = fmaf(-scale, gv[c][u][e], wv[u][e]);
+                for (; d < a.n_dst && a.dst_after[d] == j0 + c + 1; ++d)
+#pragma unroll
+                    for (int u = 0; u < VECS; ++u)
+                        if (in(u)) __builtin_nontemporal_store(wv[u], reinterpret_cast<floatx4*>(a.dst[d]) + first + u * kThreads + tid);
+            }
+    }
+#pragma unroll
+    for (int u = 0; u < VECS; ++u)
+        if (in(u)) (w4 + first + u * kThreads)[tid] = wv[u];
+}
 
+template <int GRADS, int VECS>
 __global__ __launch_bounds__(kThreads) void apply_many_kernel(float* __restrict__ w, ManyArgs a, long n4, long n, float scale,
                                                                uint64_t* stamp, uint64_t version_first) {
     floatx4* __restrict__ w4 = reinterpret_cast<floatx4*>(w);
-    const long stride = (long)gridDim.x * kThreads;
-    for (long i = (long)blockIdx.x * kThreads + threadIdx.x; i < n4; i += stride) {
-        floatx4 wv = w4[i];
-        int d = 0;
-        for (int j0 = 0; j0 < a.m; j0 += kManyChunk) {
-            floatx4 gv[kManyChunk];
-#pragma unroll
-            for (int u = 0; u < kManyChunk; ++u)
-                if (j0 + u < a.m) gv[u] = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(a.g[j0 + u]) + i);
-#pragma unroll
-            for (int u = 0; u < kManyChunk; ++u)
-                if (j0 + u < a.m) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) wv[e] = fmaf(-scale, gv[u][e], wv[e]);
-                    for (; d < a.n_dst && a.dst_after[d] == j0 + u + 1; ++d)
-                        __builtin_nontemporal_store(wv, reinterpret_cast<floatx4*>(a.dst[d]) + i);
-                }
-        }
-        w4[i] = wv;
-    }
+    const long first = (long)blockIdx.x * kThreads * VECS;
+    if (first + kThreads * VECS <= n4) apply_many<GRADS, VECS, true>(w4, a, first, n4, scale);
+    else apply_many<1, VECS, false>(w4, a, first, n4, scale);
     if (blockIdx.x == 0) {
         const long t = n4 * 4 + threadIdx.x;            // scalar tail, fewer than 4 elements
         if (t < n) {
@@ -169,7 +193,7 @@ extern "C" int dsspk_apply(void* stream, float* w, const float* g, int64_t n, fl
     if (!w || !g || !stamp || n < 0) return -1;
     const long n4 = (aligned16(w) && aligned16(g)) ? n / 4 : 0;
     if (n4 == 0 && n > 3) return -1;                  // buffers must be 16-byte aligned
-    const int grid = stream_grid(ceil_div(n4, (long)kThreads * kUnroll));
+    const int grid = n4 ? ceil_div(n4, (long)kThreads * kUnroll) : 1;
     hipLaunchKernelGGL(apply_kernel, dim3(grid), dim3(kThreads), 0, (hipStream_t)stream,
                        w, g, n4, (long)n, scale, stamp, version);
     return DSSPK_LAUNCH_RC();
@@ -180,7 +204,7 @@ extern "C" int dsspk_pull(void* stream, float* dst, const float* w, int64_t n,
     if (!w || !dst || n < 0 || (dst_stamp && !stamp)) return -1;
     const long n4 = (aligned16(w) && aligned16(dst)) ? n / 4 : 0;
     if (n4 == 0 && n > 3) return -1;
-    const int grid = stream_grid(ceil_div(n4, (long)kThreads * kUnroll));
+    const int grid = n4 ? ceil_div(n4, (long)kThreads * kUnroll) : 1;
     hipLaunchKernelGGL(pull_kernel, dim3(grid), dim3(kThreads), 0, (hipStream_t)stream,
                        dst, w, n4, (long)n, dst_stamp, stamp);
     return DSSPK_LAUNCH_RC();
@@ -191,7 +215,7 @@ extern "C" int dsspk_apply_pull(void* stream, float* w, const float* g, float* d
     if (!w || !g || !dst || !stamp || n < 0 || dst == w) return -1;
     const long n4 = (aligned16(w) && aligned16(g) && aligned16(dst)) ? n / 4 : 0;
     if (n4 == 0 && n > 3) return -1;
-    const int grid = stream_grid(ceil_div(n4, (long)kThreads * kUnroll));
+    const int grid = n4 ? ceil_div(n4, (long)kThreads * kUnroll) : 1;
     hipLaunchKernelGGL(apply_pull_kernel, dim3(grid), dim3(kThreads), 0, (hipStream_t)stream,
                        w, g, dst, n4, (long)n, scale, stamp, dst_stamp, version);
     return DSSPK_LAUNCH_RC();
@@ -221,8 +245,13 @@ extern "C" int dsspk_apply_many(void* stream, float* w, int m, const float* cons
     }
     const long n4 = al ? n / 4 : 0;
     if (n4 == 0 && n > 3) return -1;
-    const int grid = stream_grid(ceil_div(n4, (long)kThreads * 2));
-    hipLaunchKernelGGL(apply_many_kernel, dim3(grid), dim3(kThreads), 0, (hipStream_t)stream, w, a, n4, (long)n, scale, stamp,
-                       version_first);
+    // long stretches from where they still give the chip's 256 compute units two workgroups each
+    constexpr int GRADS = 2, VECS = 8;
+    if (n4 >= 512L * kThreads * VECS)
+        hipLaunchKernelGGL((apply_many_kernel<GRADS, VECS>), dim3(ceil_div(n4, (long)kThreads * VECS)), dim3(kThreads), 0, (hipStream_t)stream, w, a, n4,
+                           (long)n, scale, stamp, version_first);
+    else
+        hipLaunchKernelGGL((apply_many_kernel<4, 1>), dim3(n4 ? ceil_div(n4, (long)kThreads) : 1), dim3(kThreads), 0, (hipStream_t)stream, w, a, n4,
+                           (long)n, scale, stamp, version_first);
     return DSSPK_LAUNCH_RC();
 }

@@ -511,9 +511,16 @@ extern "C" int dssp_push_many(dssp_ctx* c, int m, const int* workers, const floa
     auto undo = [&](int rc) { restore_state(c, before); return rc; };
     const bool own = c->server_stream == nullptr;
     hipStream_t as = own ? c->wstream[workers[0]] : c->server_stream;
+    // Workers may share a stream; one event says that all gradients on it are complete, one wait holds up all of its workers (with an event
+    // and a wait each, 16 pushers on four streams left the GPU 120 us between two aggregated applies of 25 M parameters, 631 us each).
+    auto shares = [&](const int* list, int k) {     // the stream of list[k] with one listed before
+        for (int e = 0; e < k; ++e)
+            if (c->wstream[list[e]] == c->wstream[list[k]]) return true;
+        return false;
+    };
     for (int j = 0; j < m; ++j) {
         hipStream_t ws = c->wstream[workers[j]];
-        if (ws == as) continue;
+        if (ws == as || shares(workers, j)) continue;
         if (hipEventRecord(c->ev_grad[workers[j]], ws) != hipSuccess || hipStreamWaitEvent(as, c->ev_grad[workers[j]], 0) != hipSuccess)
             return undo(fail(c, DSSP_EHIP, "event between a pusher's stream and the apply's"));
     }
@@ -532,7 +539,7 @@ extern "C" int dssp_push_many(dssp_ctx* c, int m, const int* workers, const floa
     HIP_TRY(c, hipEventRecord(c->ev_apply, as));
     c->apply_stream = as;
     for (int e = 0; e < n_snap; ++e)        // whoever got a snapshot goes on behind the kernel that wrote it
-        if (c->wstream[snap_worker[e]] != as) HIP_TRY(c, hipStreamWaitEvent(c->wstream[snap_worker[e]], c->ev_apply, 0));
+        if (c->wstream[snap_worker[e]] != as && !shares(snap_worker, e)) HIP_TRY(c, hipStreamWaitEvent(c->wstream[snap_worker[e]], c->ev_apply, 0));
     return DSSP_OK;
 }
 

@@ -168,16 +168,13 @@ int dsspk_conv_bwd_data_bn_wgrad_records(void* stream, const float* dz_dev, cons
  * which leave half as many records and partial results (one per image; 16 channels: two) and always add up the records they are given.
  * dsspk_conv3x3_large_parts: records of a tensor and, for C = 16 and 32, partial results of 9*C*C floats; 0: not covered.
  * fwd: y = conv(a), a = src (records NULL, parts 0) or ReLU(BN(src) (+ shortcut)), stored in act_out, mean / invstd in stats_out, as
- * dsspk_conv_fwd_prebn; records of y to records_out.  bwd_post: as dsspk_conv_bwd_data_post.  bwd: as
+ * dsspk_conv_fwd_prebn; records of y to records_out.  bwd: as
  * dsspk_conv_bwd_data_bn_wgrad_records (C = 16, 32: partial, dx NULL) and dsspk_conv_bwd_data_bn_records (C = 64: dx, partial NULL). */
 #define DSSPK_CONV3X3_LARGE_MAX 128
 int dsspk_conv3x3_large_parts(int N, int H, int C);
 int dsspk_conv3x3_large_fwd(void* stream, const float* src_dev, const float* records_dev, int parts, const float* gamma_dev,
                             const float* beta_dev, float eps, const float* shortcut_dev, float* act_out_dev, float* stats_out_dev,
                             const float* w_dev, float* dst_dev, float* records_out_dev, int N, int H, int C);
-int dsspk_conv3x3_large_bwd_post(void* stream, const float* dy_dev, const float* w_dev, const float* add_dev, float* dz_dev,
-                                 const float* mask_src_dev, const float* xc_dev, const float* stats_dev, float* records_dev, int N, int H,
-                                 int C);
 int dsspk_conv3x3_large_bwd(void* stream, const float* dz_dev, const float* xc_dev, const float* stats_dev, const float* gamma_dev,
                             const float* in_records_dev, int parts, float* dgamma_dev, float* dbeta_dev, float* dx_dev, float* partial_dev,
                             const float* w_dev, const float* add_dev, float* out_dev, const float* x_in_dev, const float* xc_post_dev,
@@ -197,6 +194,9 @@ int dsspk_conv_bwd_weight_parts(void* stream, const float* x_dev, const float* d
                                 const float* records_dev, int G, int C, float* totals_dev, float* dgamma_dev,
                                 float* dbeta_dev, int* chunks_out);
 int dsspk_wgrad_reduce(void* stream, const float* partial_dev, float* dw_dev, int E, int chunks);
+/* n of them (host arrays, at most DSSPK_WGRAD_REDUCE_MAX) in one launch, the same results. */
+#define DSSPK_WGRAD_REDUCE_MAX 4
+int dsspk_wgrad_reduce_many(void* stream, int n, const float* const* partial_dev, float* const* dw_dev, const int* E, const int* chunks);
 size_t dsspk_conv_wgrad_scratch_floats(int N, int H, int W, int Cin, int Cout, int KH, int KW, int stride, int pad);
 
 /* Stride-1 convolutions of wide layers (Cin and Cout multiples of 64, k x k filters with k = 3 or 5, pad < k) with fp32
@@ -267,6 +267,9 @@ int dsspk_bn_bwd(void* stream, const float* x_dev, const float* gamma_dev, const
 /* The two kernels of dsspk_bn_bwd on their own: the per-slab sums (and the ReLU mask written into da), then dx. */
 int dsspk_bn_bwd_reduce(void* stream, const float* x_dev, const float* stats_dev, float* da_dev, const float* out_dev,
                         float* scratch_dev, long M, int C);
+/* dsspk_bn_bwd_reduce leaving `parts` records [parts][C][2] of M / parts rows each (M a multiple of parts). */
+int dsspk_bn_bwd_reduce_parts(void* stream, const float* x_dev, const float* stats_dev, float* da_dev, const float* out_dev,
+                              float* records_dev, int parts, long M, int C);
 /* conv_parts > 0: scratch_dev holds that many (sum dz, sum dz*xhat) records written by dsspk_conv_bwd_data_post. */
 int dsspk_bn_bwd_dx(void* stream, const float* x_dev, const float* gamma_dev, const float* stats_dev, const float* dz_dev,
                     float* dx_dev, float* dgamma_dev, float* dbeta_dev, const float* scratch_dev, long M, int C, int conv_parts);

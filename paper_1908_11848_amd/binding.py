@@ -105,6 +105,7 @@ _SIGNATURES = {
     "dsspk_bn_fwd": (c_int, [c_void_p] * 7 + [c_long, c_int, c_float, c_int, c_int, c_void_p, c_int, c_int, c_int, c_int]),
     "dsspk_bn_bwd": (c_int, [c_void_p] * 10 + [c_long, c_int]),
     "dsspk_bn_bwd_reduce": (c_int, [c_void_p] * 6 + [c_long, c_int]),
+    "dsspk_bn_bwd_reduce_parts": (c_int, [c_void_p] * 6 + [c_int, c_long, c_int]),
     "dsspk_bn_bwd_dx": (c_int, [c_void_p] * 9 + [c_long, c_int, c_int]),
     "dsspk_conv_bwd_data_post": (c_int, [c_void_p] * 9 + [c_int] * 3),
     "dsspk_conv_bwd_data_bn": (c_int, [c_void_p] * 16 + [c_int] * 5),
@@ -115,10 +116,10 @@ _SIGNATURES = {
     "dsspk_conv_bwd_fused_chunks": (c_int, [c_int] * 3),
     "dsspk_conv3x3_large_parts": (c_int, [c_int] * 3),
     "dsspk_conv3x3_large_fwd": (c_int, [c_void_p, c_void_p, c_void_p, c_int, c_void_p, c_void_p, c_float] + [c_void_p] * 6 + [c_int] * 3),
-    "dsspk_conv3x3_large_bwd_post": (c_int, [c_void_p] * 9 + [c_int] * 3),
     "dsspk_conv3x3_large_bwd": (c_int, [c_void_p] * 6 + [c_int] + [c_void_p] * 13 + [c_int] * 5),
     "dsspk_conv_bwd_weight_parts": (c_int, [c_void_p] * 4 + [c_int] * 9 + [c_void_p, c_int, c_int] + [c_void_p] * 4),
     "dsspk_wgrad_reduce": (c_int, [c_void_p] * 3 + [c_int] * 2),
+    "dsspk_wgrad_reduce_many": (c_int, [c_void_p, c_int] + [c_void_p] * 4),
     "dsspk_bn_bwd_totals": (c_int, [c_void_p, c_void_p, c_int, c_int] + [c_void_p] * 3),
     "dsspk_bn_scratch_floats": (c_size_t, [c_long, c_int]),
     "dsspk_shortcut_bwd_acc": (c_int, [c_void_p] * 3 + [c_int] * 4),

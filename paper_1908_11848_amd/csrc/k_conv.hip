@@ -637,6 +637,16 @@ __global__ __launch_bounds__(256) void bn_totals_kernel(jobs::TotalsJob j) {
     jobs::bn_totals(j, blockIdx.x, lds);
 }
 
+struct ReduceJobs { jobs::ReduceJob j[DSSPK_WGRAD_REDUCE_MAX]; int n; };
+
+// Several of them in one launch: the workgroups of a job follow those of the job before.
+__global__ __launch_bounds__(256) void wgrad_reduce_many_kernel(ReduceJobs r) {
+    __shared__ __attribute__((aligned(16))) float lds[jobs::LDS_FLOATS];
+    int b = blockIdx.x, k = 0;
+    while (k + 1 < r.n && b >= r.j[k].blocks) b -= r.j[k++].blocks;
+    jobs::wgrad_reduce(r.j[k], b, lds);
+}
+
 int launch_reduce(hipStream_t s, const float* partial, float* dw, int E, int chunks) {
     jobs::ReduceJob j;
     j.partial = partial; j.dw = dw; j.E = E; j.chunks = chunks; j.blocks = jobs::reduce_groups(E, chunks);
@@ -894,6 +904,21 @@ extern "C" int dsspk_conv_bwd_weight_parts(void* stream, const float* x, const f
 extern "C" int dsspk_wgrad_reduce(void* stream, const float* partial, float* dw, int E, int chunks) {
     if (!partial || !dw || E < 4 || E % 4 || chunks < 1) return -1;
     return launch_reduce((hipStream_t)stream, partial, dw, E, chunks);
+}
+
+extern "C" int dsspk_wgrad_reduce_many(void* stream, int n, const float* const* partial, float* const* dw, const int* E, const int* chunks) {
+    if (n < 1 || n > DSSPK_WGRAD_REDUCE_MAX || !partial || !dw || !E || !chunks) return -1;
+    ReduceJobs r = {};
+    r.n = n;
+    int blocks = 0;
+    for (int k = 0; k < n; ++k) {
+        if (!partial[k] || !dw[k] || E[k] < 4 || E[k] % 4 || chunks[k] < 1) return -1;
+        r.j[k].partial = partial[k]; r.j[k].dw = dw[k]; r.j[k].E = E[k]; r.j[k].chunks = chunks[k];
+        r.j[k].blocks = jobs::reduce_groups(E[k], chunks[k]);
+        blocks += r.j[k].blocks;
+    }
+    hipLaunchKernelGGL(wgrad_reduce_many_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, r);
+    return DSSPK_LAUNCH_RC();
 }
 
 extern "C" int dsspk_bn_bwd_totals(void* stream, const float* records, int G, int C, float* totals, float* dgamma, float* dbeta) {

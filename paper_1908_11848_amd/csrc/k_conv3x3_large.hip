@@ -47,17 +47,6 @@ extern "C" int dsspk_conv3x3_large_fwd(void* stream, const float* src, const flo
                     : forward<1>((hipStream_t)stream, src, w, dst, records_out, N, C, pre);
 }
 
-extern "C" int dsspk_conv3x3_large_bwd_post(void* stream, const float* dy, const float* w, const float* add, float* dz, const float* mask_src,
-                                            const float* xc, const float* stats, float* records, int N, int H, int C) {
-    if (!dy || !w || !dz || !mask_src || !xc || !stats || !records || dz == dy || dsspk_conv3x3_large_parts(N, H, C) == 0) return -1;
-    PostBn post;
-    post.mask_src = mask_src; post.xc = xc; post.stats = stats; post.records = records;
-    hipStream_t s = (hipStream_t)stream;
-    if (C == 16) return launch<16, 32, 16, 1, WAVES, true, 0, true>(s, dy, w, add, dz, nullptr, N, PreBn{}, post);
-    if (C == 32) return launch<32, 16, 16, 1, WAVES, true, 0, true>(s, dy, w, add, dz, nullptr, N, PreBn{}, post);
-    return launch<64, 8, 8, 1, WAVES, true, 0, true>(s, dy, w, add, dz, nullptr, N, PreBn{}, post);
-}
-
 extern "C" int dsspk_conv3x3_large_bwd(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,
                                        const float* in_records, int parts, float* dgamma, float* dbeta, float* dx, float* partial,
                                        const float* w, const float* add, float* out, const float* x_in, const float* xc_post,

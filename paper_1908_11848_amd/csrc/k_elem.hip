@@ -589,6 +589,17 @@ extern "C" int dsspk_bn_bwd_reduce(void* stream, const float* x, const float* st
     return DSSPK_LAUNCH_RC();
 }
 
+// The same with `parts` records of M / parts rows each, for consumers that add up the records themselves.
+extern "C" int dsspk_bn_bwd_reduce_parts(void* stream, const float* x, const float* stats, float* da, const float* out,
+                                         float* records, int parts, long M, int C) {
+    if (!bn_bwd_args_ok(x, x, stats, da, out, da, x, x, records, M, C) || parts < 1 || M % parts) return -1;
+    BnLayout L = bn_layout(M, C);
+    L.G = parts;
+    L.rows_per_block = M / parts;
+    hipLaunchKernelGGL(bn_bwd_partial_kernel, dim3(L.G), dim3(THREADS), 0, (hipStream_t)stream, x, stats, da, out, records, M, C, L);
+    return DSSPK_LAUNCH_RC();
+}
+
 extern "C" int dsspk_bn_bwd_dx(void* stream, const float* x, const float* gamma, const float* stats, const float* dz,
                                float* dx, float* dgamma, float* dbeta, const float* scratch, long M, int C, int conv_parts) {
     if (!bn_bwd_args_ok(x, gamma, stats, dz, nullptr, dx, dgamma, dbeta, scratch, M, C)) return -1;

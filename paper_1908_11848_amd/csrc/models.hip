@@ -32,6 +32,11 @@ struct Arena {
 
 }  // namespace
 
+// d-filter partial sums wait in scratch buffers until a later kernel carries their reduction: at most four at a time (one per regular
+// layer in a row, one more per stage boundary, the stem's), and one is being written.
+constexpr int WG_SCRATCH = 5;
+static_assert(WG_SCRATCH - 1 <= DSSPK_WGRAD_REDUCE_MAX, "what waits is one launch");
+
 struct Plan {
     int model_id = 0, m = 0, n_classes = 0, K = 0;
     char* ws = nullptr;
@@ -43,7 +48,7 @@ struct Plan {
     std::vector<Tens> tens;
 
     // common tail
-    size_t logits = 0, dlogits = 0, row_loss = 0, wg_scratch = 0, wg_scratch2 = 0, bn_scratch = 0, bn_scratch2 = 0, tot_a = 0, tot_b = 0;
+    size_t logits = 0, dlogits = 0, row_loss = 0, wg_scratch = 0, wg_more[WG_SCRATCH - 1] = {}, bn_scratch = 0, bn_scratch2 = 0, tot_a = 0, tot_b = 0;
     // MLP
     size_t mlp_a1 = 0, mlp_da1 = 0;
     // AlexNet-style
@@ -172,7 +177,7 @@ struct Plan {
         tens.push_back({2, logits, (int64_t)m * classes});
         row_loss = a.floats((size_t)m);
         wg_scratch = a.floats(wg ? wg : 1);
-        wg_scratch2 = a.floats(is_resnet(id) && wg ? wg : 1);   // d-filter partial sums alternate between the two
+        for (size_t& o : wg_more) o = a.floats(is_resnet(id) && wg ? wg : 1);
         bn_scratch = a.floats(bn ? bn : 1);
         bn_scratch2 = a.floats(bn ? bn : 1);
         tot_a = a.floats(128); tot_b = a.floats(128);          // batch-norm backward sums (2 x 64 channels at most)
@@ -355,25 +360,48 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     //               next batch norm in its epilogue, and the d-filter partial sums from the same LDS tiles (dx is
     //               never stored) - followed by the small kernel that sums those records
     //   stage 3   : the d-input kernel (stores dx), then the d-filter kernel, which carries the sums job
-    // In both forms the d-input kernel carries the reduction of the PREVIOUS layer's d-filter partial sums, which
-    // therefore alternate between two scratch buffers.
-    // Everything else (first and last layers, the stride-2 blocks) takes the stand-alone kernels.
+    // In both forms the d-input kernel carries the reduction of an earlier layer's d-filter partial sums, the oldest that waits.  A layer
+    // whose d-filter kernel is of another kind leaves its partial sums waiting too; what waits at the end is one launch.
+    // Everything else (stem, first convolutions of the stride-2 blocks) takes the stand-alone kernels.
     //   parts0 > 0 : g0 holds the masked dz of this block's BN2 and recB0 its records
     //   tot0       : their sums are in totB already (and dgamma / dbeta of BN2 stored)
-    //   pend       : d-filter partial sums whose reduction has not been launched yet
+    //   pend       : d-filter partial sums whose reduction has not been launched yet, the oldest first
     float *recB0 = F(P->bn_scratch2), *totA = F(P->tot_a), *totB = F(P->tot_b);
-    float* scrs[2] = {scr, F(P->wg_scratch2)};
+    float* scrs[WG_SCRATCH] = {F(P->wg_scratch)};
+    for (int i = 1; i < WG_SCRATCH; ++i) scrs[i] = F(P->wg_more[i - 1]);
     int parts0 = 0;
     bool tot0 = false;
-    auto conv_bwd_post = [&](const float* dy, const float* wt, const float* add, float* dz, const float* mask, const float* xc, const float* st,
-                             float* rec, int H, int C) {
-        return (large ? dsspk_conv3x3_large_bwd_post : dsspk_conv_bwd_data_post)(s, dy, wt, add, dz, mask, xc, st, rec, m, H, C);
+    struct Pending { const float* partial[WG_SCRATCH]; float* dw[WG_SCRATCH]; int E[WG_SCRATCH], chunks[WG_SCRATCH], n; } pend = {};
+    auto free_scr = [&]() {
+        int i = 0;
+        for (int k = 0; k < pend.n; ++k)
+            if (pend.partial[k] == scrs[i]) { ++i; k = -1; }
+        return scrs[i];
     };
-    struct { float* partial; float* dw; int E, chunks; bool on; } pend = {nullptr, nullptr, 0, 0, false};
+    auto push_back = [&](const float* partial, float* dw, int E, int chunks) {
+        pend.partial[pend.n] = partial; pend.dw[pend.n] = dw; pend.E[pend.n] = E; pend.chunks[pend.n] = chunks;
+        ++pend.n;
+    };
+    auto pop_front = [&]() {
+        --pend.n;
+        for (int k = 0; k < pend.n; ++k) {
+            pend.partial[k] = pend.partial[k + 1]; pend.dw[k] = pend.dw[k + 1]; pend.E[k] = pend.E[k + 1]; pend.chunks[k] = pend.chunks[k + 1];
+        }
+    };
     auto flush = [&]() -> int {
-        if (!pend.on) return 0;
-        pend.on = false;
-        return dsspk_wgrad_reduce(s, pend.partial, pend.dw, pend.E, pend.chunks);
+        if (!pend.n) return 0;
+        const int n = pend.n;
+        pend.n = 0;
+        return dsspk_wgrad_reduce_many(s, n, pend.partial, pend.dw, pend.E, pend.chunks);
+    };
+    // d-filter of a layer with a kernel of its own; its partial sums wait
+    auto filter_grad = [&](const float* xi, const float* dy, float* dw, int H, int cin, int cout, int stride) -> int {
+        if (pend.n == WG_SCRATCH - 1) RUN(flush());
+        int chunks = 0;
+        float* to = free_scr();
+        RUN(dsspk_conv_bwd_weight_parts(s, xi, dy, to, m, H, H, cin, cout, 3, 3, stride, 1, nullptr, 0, 0, nullptr, nullptr, nullptr, &chunks));
+        push_back(to, dw, 9 * cin * cout, chunks);
+        return 0;
     };
     // dz (masked, records summed into tot) -> through BN (xc, st, gamma) -> dx -> d-input (+ add) with the mask / records
     // epilogue (mask_src = x_in, xc_post, st_post -> records) into out, and d-filter (x_in, dx) into dw (pending).
@@ -385,15 +413,19 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
                              const float* wt, const float* add, float* out, const float* x_in, const float* xc_post,
                              const float* st_post, float* records, float* dw, int H, int Cc, bool sum_next, int nparts,
                              float* ntot, float* ndgamma, float* ndbeta) -> int {
-        float* out_scr = (pend.on && pend.partial == scrs[0]) ? scrs[1] : scrs[0];
-        const float* rp = pend.on ? pend.partial : nullptr;
+        float* out_scr = free_scr();
+        const bool carry = pend.n > 0;
+        const float* rp = carry ? pend.partial[0] : nullptr;
+        float* rdw = carry ? pend.dw[0] : nullptr;
+        const int rE = carry ? pend.E[0] : 0, rchunks = carry ? pend.chunks[0] : 0;
+        if (carry) pop_front();
         if (large) {
             int chunks = parts_of(H, Cc, Cc, 1);
             RUN(dsspk_conv3x3_large_bwd(s, dz, xc, st, gamma, in_rec, in_parts, in_dgamma, in_dbeta, Cc == 64 ? g1 : nullptr,
-                                        Cc == 64 ? nullptr : out_scr, wt, add, out, x_in, xc_post, st_post, records, rp, pend.dw, pend.E, pend.chunks,
+                                        Cc == 64 ? nullptr : out_scr, wt, add, out, x_in, xc_post, st_post, records, rp, rdw, rE, rchunks,
                                         m, H, Cc));
             if (Cc == 64) RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, nullptr, 0, 0, nullptr, nullptr, nullptr, &chunks));
-            pend.partial = out_scr; pend.dw = dw; pend.E = 9 * Cc * Cc; pend.chunks = chunks; pend.on = true;
+            push_back(out_scr, dw, 9 * Cc * Cc, chunks);
             return 0;
         }
         const bool own_sums = dsspk_conv_records_inline(in_parts, Cc) != 0;
@@ -403,15 +435,15 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         int chunks = dsspk_conv_bwd_fused_chunks(m, H, Cc);
         if (chunks > 0) {
             RUN(dsspk_conv_bwd_data_bn_wgrad_records(s, dz, xc, st, gamma, totals, in_rec, in_parts, in_dgamma, in_dbeta, wt, add, out, xc_post,
-                                                     st_post, records, x_in, out_scr, rp, pend.dw, pend.E, pend.chunks, m, H, Cc));
+                                                     st_post, records, x_in, out_scr, rp, rdw, rE, rchunks, m, H, Cc));
             if (sum_next) RUN(dsspk_bn_bwd_totals(s, records, nparts, Cc, ntot, ndgamma, ndbeta));
         } else {
             RUN(dsspk_conv_bwd_data_bn_records(s, dz, xc, st, gamma, totals, in_rec, in_parts, in_dgamma, in_dbeta, g1, wt, add, out, x_in,
-                                               xc_post, st_post, records, rp, pend.dw, pend.E, pend.chunks, m, H, Cc));
+                                               xc_post, st_post, records, rp, rdw, rE, rchunks, m, H, Cc));
             RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, sum_next ? records : nullptr,
                                             nparts, Cc, ntot, ndgamma, ndbeta, &chunks));
         }
-        pend.partial = out_scr; pend.dw = dw; pend.E = 9 * Cc * Cc; pend.chunks = chunks; pend.on = true;
+        push_back(out_scr, dw, 9 * Cc * Cc, chunks);
         return 0;
     };
     for (int bi = (int)P->blocks.size() - 1; bi >= 0; --bi) {
@@ -423,24 +455,14 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         const bool identity = B.stride == 1 && B.cin == B.cout;
         const int partsp = identity ? parts_of(B.H, B.cin, B.cout, 1) : 0;
         const bool fused1 = parts1 > 0 && partsp > 0;        // conv1's layer takes the two-launch form
-        bool tot1 = false;                                   // sums of BN1's records are in totA
         // ---- BN2 + conv2: g0 = dz2 -> g1 = d conv2 output, g2 = dz1 = d a1 * [a1 > 0] (+ BN1's records in bscr)
-        if (parts0 > 0 && parts1 > 0) {
-            RUN(regular_layer(recB0, parts0, g + B.g2, g + B.b2, tot0, g0, F(B.c2), F(B.st2), w + B.g2, totB, w + B.w2, nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr,
-                              g + B.w2, Ho, B.cout, fused1, parts1, totA, g + B.g1, g + B.b1));
-            tot1 = fused1;
-        } else {
-            RUN(flush());
-            if (!parts0) RUN(dsspk_bn_bwd_reduce(s, F(B.c2), F(B.st2), g0, F(B.out), recB0, M, B.cout));
-            RUN(dsspk_bn_bwd_dx(s, F(B.c2), w + B.g2, F(B.st2), g0, g1, g + B.g2, g + B.b2, recB0, M, B.cout, parts0));
-            RUN(dsspk_conv_bwd_weight(s, F(B.a1), g1, g + B.w2, scr, m, Ho, Ho, B.cout, B.cout, 3, 3, 1, 1));
-            if (parts1) {
-                RUN(conv_bwd_post(g1, w + B.w2, nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr, Ho, B.cout));
-            } else {
-                RUN(dsspk_conv_bwd_data(s, g1, w + B.w2, nullptr, g2, m, Ho, Ho, B.cout, B.cout, 3, 3, 1, 1));
-                RUN(dsspk_bn_bwd_reduce(s, F(B.c1), F(B.st1), g2, F(B.a1), bscr, M, B.cout));
-            }
+        if (!parts0) {                  // g0 is not masked yet
+            RUN(dsspk_bn_bwd_reduce_parts(s, F(B.c2), F(B.st2), g0, F(B.out), recB0, parts1, M, B.cout));
+            parts0 = parts1;
+            tot0 = false;
         }
+        RUN(regular_layer(recB0, parts0, g + B.g2, g + B.b2, tot0, g0, F(B.c2), F(B.st2), w + B.g2, totB, w + B.w2, nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr,
+                          g + B.w2, Ho, B.cout, fused1, parts1, totA, g + B.g1, g + B.b1));        // sums of BN1's records to totA if fused1
         // ---- BN1 + conv1: g2 = dz1 -> g1 = d conv1 output; d-input (+ dz2 through an identity shortcut) = gradient
         //      w.r.t. the block's input, which is the previous block's (or the stem's) post-ReLU output: mask +
         //      records of ITS batch norm in the same kernel where the specialised kernel applies
@@ -449,34 +471,25 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             const float* pst = bi ? F(P->blocks[bi - 1].st2) : F(P->stem_st);
             // output in place over the shortcut's gradient g0; g0 stays the gradient w.r.t. the previous block's output
             const bool next_fused = bi > 0;                  // the previous block's conv2 has this convolution's shape
-            RUN(regular_layer(bscr, parts1, g + B.g1, g + B.b1, tot1, g2, F(B.c1), F(B.st1), w + B.g1, totA, w + B.w1, g0, g0, xin, pc, pst, recB0, g + B.w1, B.H, B.cin,
+            RUN(regular_layer(bscr, parts1, g + B.g1, g + B.b1, true, g2, F(B.c1), F(B.st1), w + B.g1, totA, w + B.w1, g0, g0, xin, pc, pst, recB0, g + B.w1, B.H, B.cin,
                               next_fused, partsp, totB, next_fused ? g + P->blocks[bi - 1].g2 : nullptr,
                               next_fused ? g + P->blocks[bi - 1].b2 : nullptr));
             parts0 = partsp;
             tot0 = next_fused;
-        } else {
-            RUN(flush());
+        } else {                        // first block of a stage: stride 2, shortcut without parameters
             RUN(dsspk_bn_bwd_dx(s, F(B.c1), w + B.g1, F(B.st1), g2, g1, g + B.g1, g + B.b1, bscr, M, B.cout, parts1));
-            RUN(dsspk_conv_bwd_weight(s, xin, g1, g + B.w1, scr, m, B.H, B.H, B.cin, B.cout, 3, 3, B.stride, 1));
-            if (partsp) {
-                const float* pc = bi ? F(P->blocks[bi - 1].c2) : F(P->stem_c);
-                const float* pst = bi ? F(P->blocks[bi - 1].st2) : F(P->stem_st);
-                RUN(conv_bwd_post(g1, w + B.w1, g0, g2, xin, pc, pst, recB0, B.H, B.cin));
-            } else {
-                RUN(dsspk_conv_bwd_data(s, g1, w + B.w1, identity ? g0 : nullptr, g2, m, B.H, B.H, B.cin, B.cout, 3, 3, B.stride, 1));
-                if (!identity) RUN(dsspk_shortcut_bwd_acc(s, g0, g2, m, Ho, Ho, B.cout));
-            }
+            RUN(filter_grad(xin, g1, g + B.w1, B.H, B.cin, B.cout, B.stride));
+            RUN(dsspk_conv_bwd_data(s, g1, w + B.w1, nullptr, g2, m, B.H, B.H, B.cin, B.cout, 3, 3, B.stride, 1));
+            RUN(dsspk_shortcut_bwd_acc(s, g0, g2, m, Ho, Ho, B.cout));
             parts0 = partsp;
             tot0 = false;
             float* t = g0; g0 = g2; g2 = t;
         }
     }
-    RUN(flush());
-    if (!parts0) RUN(dsspk_bn_bwd_reduce(s, F(P->stem_c), F(P->stem_st), g0, F(P->stem_a), recB0, (long)m * 1024, 16));
     RUN(dsspk_bn_bwd_dx(s, F(P->stem_c), w + P->stem_g, F(P->stem_st), g0, g1, g + P->stem_g, g + P->stem_b, recB0,
                         (long)m * 1024, 16, parts0));
-    RUN(dsspk_conv_bwd_weight(s, x, g1, g + P->stem_w, scr, m, 32, 32, 3, 16, 3, 3, 1, 1));
-    return 0;
+    RUN(filter_grad(x, g1, g + P->stem_w, 32, 3, 16, 1));
+    return flush();
 }
 
 }  // namespace

@@ -95,6 +95,15 @@ int dsspk_conv_fwd(void* stream, const float* x_dev, const float* w_dev, const f
                    int N, int H, int W, int Cin, int Cout, int KH, int KW, int stride, int pad, int relu,
                    float* bn_partial_dev);
 int dsspk_conv_fwd_stat_parts(int N, int H, int W, int Cin, int Cout, int KH, int KW, int stride, int pad);
+/* Convolutions of other shapes (no bias, no ReLU) that leave such records of their result as well: dsspk_conv_fwd_records_parts(...) of
+ * them, as many as dsspk_conv_fwd_prebn takes; 0: not this shape (result rows no multiple of a tile's, or too many tiles). */
+int dsspk_conv_fwd_records_parts(int N, int H, int W, int Cin, int Cout, int KH, int KW, int stride, int pad);
+int dsspk_conv_fwd_records(void* stream, const float* x_dev, const float* w_dev, float* y_dev, float* records_dev, int N, int H, int W,
+                           int Cin, int Cout, int KH, int KW, int stride, int pad);
+/* dsspk_conv_bwd_data with stride 2 (H, W even, result H x W) and Cout = 2 Cin, plus the gradient of a parameter-free shortcut:
+ * dx[n][2 h][2 w][c] += shortcut[n][h][w][c] for c < Cin; shortcut is [N][H / 2][W / 2][Cout]. */
+int dsspk_conv_bwd_data_shortcut(void* stream, const float* dy_dev, const float* w_dev, const float* shortcut_dev, float* dx_dev, int N,
+                                 int H, int W, int Cin, int Cout, int KH, int KW, int pad);
 /* 3x3 / stride 1 / pad 1 / C -> C convolution of a = ReLU(BN(src) (+ shortcut)) without a separate batch-norm
  * pass: the kernel normalises src while loading it.  src is [N][H][H][C]; records_dev holds in_parts statistics
  * records of src as written by dsspk_conv_fwd(..., bn_partial_dev) for the same shape; shortcut_dev (may be

@@ -98,7 +98,7 @@ __device__ __forceinline__ bool src_pixel(const ConvGeom& g, int oh, int ow, int
 template <int BM, int BN, bool DGRAD, bool VEC, int KS = 1>
 __global__ __launch_bounds__(THREADS) void conv_igemm_kernel(const float* __restrict__ src, const float* __restrict__ wgt,
                                                              const float* __restrict__ bias, const float* __restrict__ add,
-                                                             float* __restrict__ dst, ConvGeom g, int relu, int mode) {
+                                                             float* __restrict__ dst, ConvGeom g, int relu, int mode, float* __restrict__ extra) {
     static_assert(KS == 1 || VEC, "several k-chunks per stage only with 16-byte gathers");
     constexpr int WM = BM / 64, WN = BN / 16;
     constexpr int KST = mma::KC * KS;                              // reduction indices per stage
@@ -319,10 +319,41 @@ __global__ __launch_bounds__(THREADS) void conv_igemm_kernel(const float* __rest
                 }
                 float x = acc[wm][wn][v] + bv;
                 if (add) x += add[m * g.OC + col];
+                if (DGRAD && extra && !(ph | pw)) x += extra[r * (2 * g.OC) + col];        // class (0, 0): its rows are the pixels of `extra`
                 if (relu) x = fmaxf(x, 0.f);
                 dst[m * g.OC + col] = x;
             }
         }
+    // Forward: statistics record of the tile (its rows are all there), mean and sum of squared deviations per channel.
+    if constexpr (!DGRAD) {
+        if (!extra) return;
+        float* red = igemm_lds;                                    // [2][4 wavefronts][BN]
+        static_assert(2 * 4 * BN <= 2 * BM * LDA, "room for the sums");
+        float mean[WN];
+        __syncthreads();                                           // the operand tiles are no longer needed
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+            for (int wn = 0; wn < WN; ++wn) {
+                float t = 0.f;
+#pragma unroll
+                for (int wm = 0; wm < WM; ++wm)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) { const float d = acc[wm][wn][v] - (pass ? mean[wn] : 0.f); t += pass ? d * d : d; }
+                t += __shfl_xor(t, 16);
+                t += __shfl_xor(t, 32);
+                if (q == 0) red[(4 * pass + wave) * BN + 16 * wn + l16] = t;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int wn = 0; wn < WN; ++wn) {
+                const float* p = red + 4 * pass * BN + 16 * wn + l16;
+                const float t = (p[0] + p[BN]) + (p[2 * BN] + p[3 * BN]);
+                if (pass == 0) mean[wn] = t * (1.0f / BM);
+                else if (tid < 16) *reinterpret_cast<float2*>(extra + ((long)blockIdx.x * g.OC + n0 + 16 * wn + l16) * 2) = make_float2(mean[wn], t);
+            }
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -706,7 +737,7 @@ constexpr size_t igemm_lds_bytes() {
 
 template <int BM, int BN, bool DGRAD, bool VEC, int KS>
 int igemm_launch(dim3 grid, hipStream_t s, const float* src, const float* w, const float* bias, const float* add, float* dst,
-                 const ConvGeom& g, int relu, bool parity) {
+                 const ConvGeom& g, int relu, bool parity, float* extra) {
     // staged gather: forward, element-wise, stride 1, tiles of whole rows of one image, the rows they touch within the LDS budget
     const bool staged = !VEC && !DGRAD && g.stride == 1 && g.OW <= BM && BM % g.OW == 0 && ((long)g.OH * g.OW) % BM == 0 &&
                         (long)(BM / g.OW + g.KH - 1) * (g.SW + 2 * g.pad) * g.IC <= IGEMM_IMG_MAX;
@@ -720,22 +751,28 @@ int igemm_launch(dim3 grid, hipStream_t s, const float* src, const float* w, con
             return -1;
         attr_set = true;
     }
-    hipLaunchKernelGGL(kern, grid, dim3(THREADS), bytes, s, src, w, bias, add, dst, g, relu, staged ? IGEMM_STAGED : parity ? IGEMM_PARITY : 0);
+    hipLaunchKernelGGL(kern, grid, dim3(THREADS), bytes, s, src, w, bias, add, dst, g, relu, staged ? IGEMM_STAGED : parity ? IGEMM_PARITY : 0, extra);
     return 0;
 }
 
+// Rows of a tile: small problems take 64-pixel tiles so that the grid still covers the chip.
+inline bool igemm_small(const ConvGeom& g) { return g.M < 128L * 512; }
+
+// extra: forward, statistics records of the result, one per tile of rows (M a multiple of the tile's); d-input by parity class, a tensor
+// [N][OH / 2][OW / 2][2 OC] whose first OC channels are added to the even pixels.
 template <bool DGRAD, bool VEC>
-int launch_igemm(hipStream_t s, const float* src, const float* w, const float* bias, const float* add, float* dst, const ConvGeom& g, int relu) {
+int launch_igemm(hipStream_t s, const float* src, const float* w, const float* bias, const float* add, float* dst, const ConvGeom& g, int relu,
+                 float* extra = nullptr) {
     // output-channel tile: the widest of 64, 32, 16 that divides the layer
     const int bn = g.OC % 64 == 0 ? 64 : g.OC % 32 == 0 ? 32 : g.OC % 16 == 0 ? 16 : 0;
     if (!bn) return -1;
-    // small problems take 64-pixel tiles so that the grid still covers the chip
-    const bool small = g.M < 128L * 512;
+    const bool small = igemm_small(g);
     // d-input of a stride-2 layer on an even pixel grid: four parity classes of rows, each with its own tiles
     const bool parity = DGRAD && VEC && g.stride == 2 && g.OH % 2 == 0 && g.OW % 2 == 0;
+    if (DGRAD && extra && !parity) return -1;
     dim3 grid(parity ? 4 * ceil_div(g.M / 4, small ? 64 : 128) : ceil_div(g.M, small ? 64 : 128), g.OC / bn);
-#define GO(BM, BN) do { if (igemm_launch<BM, BN, DGRAD, VEC, 1>(grid, s, src, w, bias, add, dst, g, relu, parity)) return -1; } while (0)
-#define GOK(BM, BN, KS) do { if (igemm_launch<BM, BN, DGRAD, VEC, KS>(grid, s, src, w, bias, add, dst, g, relu, parity)) return -1; } while (0)
+#define GO(BM, BN) do { if (igemm_launch<BM, BN, DGRAD, VEC, 1>(grid, s, src, w, bias, add, dst, g, relu, parity, extra)) return -1; } while (0)
+#define GOK(BM, BN, KS) do { if (igemm_launch<BM, BN, DGRAD, VEC, KS>(grid, s, src, w, bias, add, dst, g, relu, parity, extra)) return -1; } while (0)
     if constexpr (VEC) {
         if (bn == 64 && g.IC % 64 == 0 && small) {      // wide layers: several k-chunks per stage
             GOK(64, 64, 4);
@@ -774,6 +811,23 @@ extern "C" int dsspk_conv_fwd(void* stream, const float* x, const float* w, cons
     return launch_igemm<false, false>((hipStream_t)stream, x, w, bias, nullptr, y, g, relu);
 }
 
+// Statistics records that dsspk_conv_fwd_records leaves, 0: not this shape.  Few enough for dsspk_conv_fwd_prebn.
+extern "C" int dsspk_conv_fwd_records_parts(int N, int H, int W, int Cin, int Cout, int KH, int KW, int stride, int pad) {
+    ConvGeom g;
+    if (!geom(g, N, H, W, Cin, Cout, KH, KW, stride, pad) || Cout < 16 || Cout % 16) return 0;
+    const int rows = igemm_small(g) ? 64 : 128;
+    return g.M % rows == 0 && g.M / rows <= 512 && (Cout == 16 || Cout == 32 || Cout == 64) && g.M / rows <= 32 * (256 / Cout) ? (int)(g.M / rows) : 0;
+}
+
+extern "C" int dsspk_conv_fwd_records(void* stream, const float* x, const float* w, float* y, float* records, int N, int H, int W, int Cin, int Cout,
+                                      int KH, int KW, int stride, int pad) {
+    ConvGeom g;
+    if (!x || !w || !y || !records || dsspk_conv_fwd_records_parts(N, H, W, Cin, Cout, KH, KW, stride, pad) == 0) return -1;
+    if (!geom(g, N, H, W, Cin, Cout, KH, KW, stride, pad)) return -1;
+    if (Cin % 16 == 0) return launch_igemm<false, true>((hipStream_t)stream, x, w, nullptr, nullptr, y, g, 0, records);
+    return launch_igemm<false, false>((hipStream_t)stream, x, w, nullptr, nullptr, y, g, 0, records);
+}
+
 extern "C" int dsspk_conv_fwd_prebn(void* stream, const float* src, const float* records, int in_parts, const float* gamma,
                                     const float* beta, float eps, const float* shortcut, float* act_out, float* stats_out,
                                     const float* w, float* y, float* bn_partial, int N, int H, int C) {
@@ -806,6 +860,20 @@ extern "C" int dsspk_conv_bwd_data(void* stream, const float* dy, const float* w
     g.M = (long)N * H * W;
     if (g.M >= (1L << 31)) return -1;
     return launch_igemm<true, true>((hipStream_t)stream, dy, w, nullptr, add, dx, g, 0);
+}
+
+// First convolution of a stride-2 block with a parameter-free shortcut (every second pixel, channels appended): the shortcut's gradient
+// goes onto the even pixels in the epilogue.
+extern "C" int dsspk_conv_bwd_data_shortcut(void* stream, const float* dy, const float* w, const float* shortcut, float* dx, int N, int H, int W,
+                                            int Cin, int Cout, int KH, int KW, int pad) {
+    ConvGeom f;
+    if (!dy || !w || !shortcut || !dx || shortcut == dx || !geom(f, N, H, W, Cin, Cout, KH, KW, 2, pad)) return -1;
+    if (Cout % 16 || Cout != 2 * Cin || H % 2 || W % 2 || f.OH != H / 2 || f.OW != W / 2) return -1;
+    ConvGeom g = f;
+    g.OH = H; g.OW = W; g.SH = f.OH; g.SW = f.OW; g.IC = Cout; g.OC = Cin;
+    g.M = (long)N * H * W;
+    if (g.M >= (1L << 31)) return -1;
+    return launch_igemm<true, true>((hipStream_t)stream, dy, w, nullptr, nullptr, dx, g, 0, const_cast<float*>(shortcut));
 }
 
 extern "C" size_t dsspk_conv_wgrad_scratch_floats(int N, int H, int W, int Cin, int Cout, int KH, int KW, int stride, int pad) {

@@ -288,9 +288,6 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     auto F = [&](size_t off) { return (float*)(ws + off); };
     float *scr = F(P->wg_scratch), *bscr = F(P->bn_scratch);
     // ---- forward
-    RUN(dsspk_conv_fwd(s, x, w + P->stem_w, nullptr, F(P->stem_c), m, 32, 32, 3, 16, 3, 3, 1, 1, 0, nullptr));
-    RUN(dsspk_bn_fwd(s, F(P->stem_c), w + P->stem_g, w + P->stem_b, F(P->stem_a), F(P->stem_st), bscr,
-                     (long)m * 1024, 16, eps, 1, 0, nullptr, 0, 0, 0, 0));
     // Statistics records ping-pong between two buffers: conv1 writes recA, conv2 reads recA and writes recB,
     // the next block's conv1 reads recB.  A "regular" block (stride 1, same width, shape covered by the specialised
     // kernels) has its two batch norms folded into the loaders of the convolutions that consume them:
@@ -304,10 +301,11 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     // the 110-layer network, batch 128, one worker 3962 / 3881 us, four 1858 / 1815, eight of different speed 1877 / 1832.
     const bool large = m > LARGE_ABOVE && m <= DSSPK_CONV3X3_LARGE_MAX;
     auto parts_of = [&](int H, int cin, int cout, int stride) {       // records that the forward convolution leaves
-        if (!large) return dsspk_conv_fwd_stat_parts(m, H, H, cin, cout, 3, 3, stride, 1);
-        return cin == cout && stride == 1 ? dsspk_conv3x3_large_parts(m, H, cin) : 0;
+        if (cin != cout || stride != 1) return dsspk_conv_fwd_records_parts(m, H, H, cin, cout, 3, 3, stride, 1);
+        return large ? dsspk_conv3x3_large_parts(m, H, cin) : dsspk_conv_fwd_stat_parts(m, H, H, cin, cout, 3, 3, stride, 1);
     };
     auto conv = [&](const float* src, const float* wt, float* dst, int H, int cin, int cout, int stride, float* rec) {
+        if (rec && (cin != cout || stride != 1)) return dsspk_conv_fwd_records(s, src, wt, dst, rec, m, H, H, cin, cout, 3, 3, stride, 1);
         if (large && rec) return dsspk_conv3x3_large_fwd(s, src, nullptr, 0, nullptr, nullptr, 0.f, nullptr, nullptr, nullptr, wt, dst, rec, m, H, cin);
         return dsspk_conv_fwd(s, src, wt, nullptr, dst, m, H, H, cin, cout, 3, 3, stride, 1, 0, rec);
     };
@@ -320,15 +318,24 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         const ResBlock& b = P->blocks[i];
         return b.stride == 1 && b.cin == b.cout && parts_of(b.H, b.cin, b.cout, 1) > 0;
     };
+    // The stem's batch norm is folded into the first block's convolution in the same way where the stem leaves records.
+    const int stem_parts = parts_of(32, 3, 16, 1);
+    RUN(conv(x, w + P->stem_w, F(P->stem_c), 32, 3, 16, 1, stem_parts ? recB : nullptr));
+    if (!stem_parts)
+        RUN(dsspk_bn_fwd(s, F(P->stem_c), w + P->stem_g, w + P->stem_b, F(P->stem_a), F(P->stem_st), bscr, (long)m * 1024, 16, eps, 1, 0, nullptr, 0, 0,
+                         0, 0));
     const float* cur = F(P->stem_a);
-    bool pending = false;            // the previous block's output is not written yet (its BN2 is folded into this conv1)
+    bool pending = stem_parts > 0;   // the previous block's output is not written yet (its BN2 is folded into this conv1)
     for (int bi = 0; bi < nb; ++bi) {
         const ResBlock& B = P->blocks[bi];
         const int Ho = B.H / B.stride;
         const long M = (long)m * Ho * Ho;
         const int parts1 = parts_of(B.H, B.cin, B.cout, B.stride);
         const int parts2 = parts_of(Ho, B.cout, B.cout, 1);
-        if (pending) {
+        if (pending && bi == 0) {
+            RUN(conv_prebn(F(P->stem_c), recB, stem_parts, w + P->stem_g, w + P->stem_b, nullptr, F(P->stem_a), F(P->stem_st), w + B.w1, F(B.c1), recA, 32,
+                           16));
+        } else if (pending) {
             const ResBlock& Pv = P->blocks[bi - 1];
             const float* pin = bi >= 2 ? F(P->blocks[bi - 2].out) : F(P->stem_a);         // the previous block's input = its shortcut
             RUN(conv_prebn(F(Pv.c2), recB, parts2, w + Pv.g2, w + Pv.b2, pin, F(Pv.out), F(Pv.st2), w + B.w1, F(B.c1), recA, B.H, B.cin));
@@ -479,8 +486,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         } else {                        // first block of a stage: stride 2, shortcut without parameters
             RUN(dsspk_bn_bwd_dx(s, F(B.c1), w + B.g1, F(B.st1), g2, g1, g + B.g1, g + B.b1, bscr, M, B.cout, parts1));
             RUN(filter_grad(xin, g1, g + B.w1, B.H, B.cin, B.cout, B.stride));
-            RUN(dsspk_conv_bwd_data(s, g1, w + B.w1, nullptr, g2, m, B.H, B.H, B.cin, B.cout, 3, 3, B.stride, 1));
-            RUN(dsspk_shortcut_bwd_acc(s, g0, g2, m, Ho, Ho, B.cout));
+            RUN(dsspk_conv_bwd_data_shortcut(s, g1, w + B.w1, g0, g2, m, B.H, B.H, B.cin, B.cout, 3, 3, 1));
             parts0 = partsp;
             tot0 = false;
             float* t = g0; g0 = g2; g2 = t;

@@ -45,3 +45,45 @@ def test_sums_of_equal_slabs(parts, rows, C, masked):
     assert np.max(np.abs(host(rec) - want)) < 1e-5 * np.sqrt(rows) * 4
     if parts > 1:
         assert L.dsspk_bn_bwd_reduce_parts(s, X.data_ptr(), ST.data_ptr(), DA.data_ptr(), None, rec.data_ptr(), parts, M - 1, C) == -1
+
+
+@pytest.mark.parametrize("N,H,Cin,Cout,stride", [(1, 32, 3, 16, 1), (13, 32, 3, 16, 1), (32, 32, 3, 16, 1), (64, 32, 3, 16, 1), (1, 32, 16, 32, 2), (13, 32, 16, 32, 2), (64, 32, 16, 32, 2),
+                                                 (1, 16, 32, 64, 2), (128, 16, 32, 64, 2), (3, 8, 48, 32, 1)])
+def test_records_of_generic_convolutions(N, H, Cin, Cout, stride):
+    """The result is dsspk_conv_fwd's bit for bit; a record is the tile's mean and sum of squared deviations (fp32 sums of 64 or 128 terms)."""
+    g = np.random.default_rng(N + Cin)
+    x, w = dev(g.standard_normal((N, H, H, Cin)).astype(np.float32)), dev((0.2 * g.standard_normal((3, 3, Cin, Cout))).astype(np.float32))
+    Ho, L, s = H // stride, B.lib(), stream_ptr()
+    shape = (N, H, H, Cin, Cout, 3, 3, stride, 1)
+    parts = L.dsspk_conv_fwd_records_parts(*shape)
+    rows = 64 if N * Ho * Ho < 65536 else 128
+    assert parts == N * Ho * Ho // rows
+    y, y0, rec = empty((N, Ho, Ho, Cout)), empty((N, Ho, Ho, Cout)), empty((parts, Cout, 2))
+    assert L.dsspk_conv_fwd_records(s, x.data_ptr(), w.data_ptr(), y.data_ptr(), rec.data_ptr(), *shape) == 0
+    assert L.dsspk_conv_fwd(s, x.data_ptr(), w.data_ptr(), None, y0.data_ptr(), *shape, 0, None) == 0
+    assert np.array_equal(host(y), host(y0))
+    t = host(y).astype(np.float64).reshape(parts, rows, Cout)
+    mean = t.mean(1)
+    assert np.max(np.abs(host(rec)[..., 0] - mean)) < 1e-6 * np.abs(t).max()
+    assert rel_l2(host(rec)[..., 1], ((t - mean[:, None]) ** 2).sum(1)) < 1e-6
+
+
+def test_shapes_without_records():
+    L = B.lib()
+    for N, H, Cin, Cout, stride in [(33, 32, 3, 16, 1), (65, 32, 16, 32, 2), (1, 6, 16, 32, 2), (1, 32, 16, 48, 2)]:
+        assert L.dsspk_conv_fwd_records_parts(N, H, H, Cin, Cout, 3, 3, stride, 1) == 0
+
+
+@pytest.mark.parametrize("N,H,Cin", [(1, 32, 16), (5, 32, 16), (1, 16, 32), (9, 16, 32), (2, 6, 16), (128, 16, 32)])
+def test_input_gradient_with_shortcut(N, H, Cin):
+    """dsspk_conv_bwd_data and dsspk_shortcut_bwd_acc: the same two fp32 additions per element, the same bits."""
+    g = np.random.default_rng(N + H)
+    Ho, Cout = H // 2, 2 * Cin
+    dy, sc = (dev(g.standard_normal((N, Ho, Ho, Cout)).astype(np.float32)) for _ in range(2))
+    w, dx, want = dev((0.2 * g.standard_normal((3, 3, Cin, Cout))).astype(np.float32)), empty((N, H, H, Cin)), empty((N, H, H, Cin))
+    L, s = B.lib(), stream_ptr()
+    assert L.dsspk_conv_bwd_data(s, dy.data_ptr(), w.data_ptr(), None, want.data_ptr(), N, H, H, Cin, Cout, 3, 3, 2, 1) == 0
+    assert L.dsspk_shortcut_bwd_acc(s, sc.data_ptr(), want.data_ptr(), N, Ho, Ho, Cout) == 0
+    assert L.dsspk_conv_bwd_data_shortcut(s, dy.data_ptr(), w.data_ptr(), sc.data_ptr(), dx.data_ptr(), N, H, H, Cin, Cout, 3, 3, 1) == 0
+    assert np.array_equal(host(dx), host(want))
+    assert L.dsspk_conv_bwd_data_shortcut(s, dy.data_ptr(), w.data_ptr(), sc.data_ptr(), dx.data_ptr(), N, H + 1, H, Cin, Cout, 3, 3, 1) == -1

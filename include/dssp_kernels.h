@@ -114,6 +114,12 @@ int dsspk_conv_fwd_prebn(void* stream, const float* src_dev, const float* record
                          const float* gamma_dev, const float* beta_dev, float eps, const float* shortcut_dev,
                          float* act_out_dev, float* stats_out_dev, const float* w_dev, float* y_dev,
                          float* bn_partial_dev, int N, int H, int C);
+/* The same with a shortcut that is twice as high and wide and has half the channels (C = 32, 64): shortcut[n][2 h][2 w][c] for c < C / 2, zero
+ * beyond. */
+int dsspk_conv_fwd_prebn_half(void* stream, const float* src_dev, const float* records_dev, int in_parts,
+                         const float* gamma_dev, const float* beta_dev, float eps, const float* shortcut_dev,
+                         float* act_out_dev, float* stats_out_dev, const float* w_dev, float* y_dev,
+                         float* bn_partial_dev, int N, int H, int C);
 /* dx = transpose of the above applied to dy (gradient w.r.t. the input), plus add_dev element-wise if it
  * is not NULL (the gradient arriving through a residual shortcut; add_dev has dx's shape, may not alias dx). */
 int dsspk_conv_bwd_data(void* stream, const float* dy_dev, const float* w_dev, const float* add_dev, float* dx_dev,
@@ -177,13 +183,13 @@ int dsspk_conv_bwd_data_bn_wgrad_records(void* stream, const float* dz_dev, cons
  * which leave half as many records and partial results (one per image; 16 channels: two) and always add up the records they are given.
  * dsspk_conv3x3_large_parts: records of a tensor and, for C = 16 and 32, partial results of 9*C*C floats; 0: not covered.
  * fwd: y = conv(a), a = src (records NULL, parts 0) or ReLU(BN(src) (+ shortcut)), stored in act_out, mean / invstd in stats_out, as
- * dsspk_conv_fwd_prebn; records of y to records_out.  bwd: as
+ * dsspk_conv_fwd_prebn (shortcut_half: dsspk_conv_fwd_prebn_half); records of y to records_out.  bwd: as
  * dsspk_conv_bwd_data_bn_wgrad_records (C = 16, 32: partial, dx NULL) and dsspk_conv_bwd_data_bn_records (C = 64: dx, partial NULL). */
 #define DSSPK_CONV3X3_LARGE_MAX 128
 int dsspk_conv3x3_large_parts(int N, int H, int C);
 int dsspk_conv3x3_large_fwd(void* stream, const float* src_dev, const float* records_dev, int parts, const float* gamma_dev,
                             const float* beta_dev, float eps, const float* shortcut_dev, float* act_out_dev, float* stats_out_dev,
-                            const float* w_dev, float* dst_dev, float* records_out_dev, int N, int H, int C);
+                            const float* w_dev, float* dst_dev, float* records_out_dev, int shortcut_half, int N, int H, int C);
 int dsspk_conv3x3_large_bwd(void* stream, const float* dz_dev, const float* xc_dev, const float* stats_dev, const float* gamma_dev,
                             const float* in_records_dev, int parts, float* dgamma_dev, float* dbeta_dev, float* dx_dev, float* partial_dev,
                             const float* w_dev, const float* add_dev, float* out_dev, const float* x_in_dev, const float* xc_post_dev,
@@ -279,6 +285,13 @@ int dsspk_bn_bwd_reduce(void* stream, const float* x_dev, const float* stats_dev
 /* dsspk_bn_bwd_reduce leaving `parts` records [parts][C][2] of M / parts rows each (M a multiple of parts). */
 int dsspk_bn_bwd_reduce_parts(void* stream, const float* x_dev, const float* stats_dev, float* da_dev, const float* out_dev,
                               float* records_dev, int parts, long M, int C);
+/* The last batch norm of a network with the pooling behind it: y = ReLU(BN(x) + shortcut) (sc_half: as dsspk_conv_fwd_prebn_half, images of
+ * side x side pixels), pooled[n][c] = mean of y over the image; `parts` equal records of x.  And the way back: dz = [out > 0] dpooled / side^2,
+ * one record (sum dz, sum dz xhat) per image. */
+int dsspk_bn_fwd_gap(void* stream, const float* x_dev, const float* gamma_dev, const float* beta_dev, float* y_dev, float* stats_dev,
+                     const float* records_dev, int parts, const float* sc_dev, int sc_half, float* pooled_dev, int N, int side, int C, float eps);
+int dsspk_gap_bwd_bn_reduce(void* stream, const float* dpooled_dev, const float* x_dev, const float* stats_dev, const float* out_dev,
+                            float* dz_dev, float* records_dev, int N, int side, int C);
 /* conv_parts > 0: scratch_dev holds that many (sum dz, sum dz*xhat) records written by dsspk_conv_bwd_data_post. */
 int dsspk_bn_bwd_dx(void* stream, const float* x_dev, const float* gamma_dev, const float* stats_dev, const float* dz_dev,
                     float* dx_dev, float* dgamma_dev, float* dbeta_dev, const float* scratch_dev, long M, int C, int conv_parts);

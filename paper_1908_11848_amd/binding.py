@@ -87,6 +87,8 @@ _SIGNATURES = {
     "dsspk_conv_bwd_data_shortcut": (c_int, [c_void_p] * 5 + [c_int] * 7),
     "dsspk_conv_fwd_prebn": (c_int, [c_void_p, c_void_p, c_void_p, c_int, c_void_p, c_void_p, c_float, c_void_p, c_void_p,
                                      c_void_p, c_void_p, c_void_p, c_void_p, c_int, c_int, c_int]),
+    "dsspk_conv_fwd_prebn_half": (c_int, [c_void_p, c_void_p, c_void_p, c_int, c_void_p, c_void_p, c_float, c_void_p, c_void_p,
+                                     c_void_p, c_void_p, c_void_p, c_void_p, c_int, c_int, c_int]),
     "dsspk_conv_bwd_data": (c_int, [c_void_p] * 5 + [c_int] * 9),
     "dsspk_conv_bwd_weight": (c_int, [c_void_p] * 5 + [c_int] * 9),
     "dsspk_conv_wgrad_scratch_floats": (c_size_t, [c_int] * 9),
@@ -108,6 +110,8 @@ _SIGNATURES = {
     "dsspk_bn_fwd": (c_int, [c_void_p] * 7 + [c_long, c_int, c_float, c_int, c_int, c_void_p, c_int, c_int, c_int, c_int]),
     "dsspk_bn_bwd": (c_int, [c_void_p] * 10 + [c_long, c_int]),
     "dsspk_bn_bwd_reduce": (c_int, [c_void_p] * 6 + [c_long, c_int]),
+    "dsspk_bn_fwd_gap": (c_int, [c_void_p] * 7 + [c_int, c_void_p, c_int, c_void_p] + [c_int] * 3 + [c_float]),
+    "dsspk_gap_bwd_bn_reduce": (c_int, [c_void_p] * 7 + [c_int] * 3),
     "dsspk_bn_bwd_reduce_parts": (c_int, [c_void_p] * 6 + [c_int, c_long, c_int]),
     "dsspk_bn_bwd_dx": (c_int, [c_void_p] * 9 + [c_long, c_int, c_int]),
     "dsspk_conv_bwd_data_post": (c_int, [c_void_p] * 9 + [c_int] * 3),
@@ -118,7 +122,7 @@ _SIGNATURES = {
     "dsspk_conv_bwd_data_bn_wgrad_records": (c_int, [c_void_p] * 7 + [c_int] + [c_void_p] * 12 + [c_int] * 5),
     "dsspk_conv_bwd_fused_chunks": (c_int, [c_int] * 3),
     "dsspk_conv3x3_large_parts": (c_int, [c_int] * 3),
-    "dsspk_conv3x3_large_fwd": (c_int, [c_void_p, c_void_p, c_void_p, c_int, c_void_p, c_void_p, c_float] + [c_void_p] * 6 + [c_int] * 3),
+    "dsspk_conv3x3_large_fwd": (c_int, [c_void_p, c_void_p, c_void_p, c_int, c_void_p, c_void_p, c_float] + [c_void_p] * 6 + [c_int] * 4),
     "dsspk_conv3x3_large_bwd": (c_int, [c_void_p] * 6 + [c_int] + [c_void_p] * 13 + [c_int] * 5),
     "dsspk_conv_bwd_weight_parts": (c_int, [c_void_p] * 4 + [c_int] * 9 + [c_void_p, c_int, c_int] + [c_void_p] * 4),
     "dsspk_wgrad_reduce": (c_int, [c_void_p] * 3 + [c_int] * 2),

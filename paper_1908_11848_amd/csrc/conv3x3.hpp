@@ -87,7 +87,8 @@ struct PreBn {
     const float* gamma;
     const float* beta;
     float eps;
-    const float* shortcut;     // PRE == 2: added before the ReLU, same shape as src
+    const float* shortcut;     // PRE == 2: added before the ReLU, same shape as src ...
+    bool half;                 // ... or (C > 16) twice as high and wide with half the channels: every second pixel of it, zero beyond its channels
     float* act_out;            // a
     float* stats_out;          // mean[C], invstd[C]
     bool merge;                // every workgroup merges the records, the first one stores stats_out
@@ -279,7 +280,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         val[e] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (inside(e)) {
             val[e] = load4(src + tile_at + e * STEP, 4u * tid);
-            if constexpr (PRE == 2) scv[e] = load4(pre.shortcut + tile_at + e * STEP, 4u * tid);
+            if constexpr (PRE == 2) {
+                if (C > 16 && pre.half) {
+                    scv[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (c4 < C / 2) scv[e] = load4(pre.shortcut + 2 * (tile_at + e * STEP), (2 * pr0 * HW + tid / V % HW) * C + c4);
+                } else {
+                    scv[e] = load4(pre.shortcut + tile_at + e * STEP, 4u * tid);
+                }
+            }
             if constexpr (PRE == 3) scv[e] = load4(bwd.xc + tile_at + e * STEP, 4u * tid);
         }
     }
@@ -368,7 +376,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         if (h < 0 || h >= HW || w < 0 || w >= HW) return make_float4(0.f, 0.f, 0.f, 0.f);
         const long off = image_at + (h * HW + w) * C + c;
         float4 sc = make_float4(0.f, 0.f, 0.f, 0.f);
-        if constexpr (PRE == 2) sc = *reinterpret_cast<const float4*>(pre.shortcut + off);
+        if constexpr (PRE == 2) {
+            if (!(C > 16 && pre.half)) sc = *reinterpret_cast<const float4*>(pre.shortcut + off);
+            else if (c < C / 2) sc = *reinterpret_cast<const float4*>(pre.shortcut + 2 * image_at + (2 * h * HW + w) * C + c);
+        }
         if constexpr (PRE == 3) sc = *reinterpret_cast<const float4*>(bwd.xc + off);
         return transformed(*reinterpret_cast<const float4*>(src + off), sc, c);
     };

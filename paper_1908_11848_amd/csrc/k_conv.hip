@@ -21,7 +21,7 @@ int conv3x3_tiled_stat_parts(int N, int HW, int C);
 int conv3x3_tiled_dgrad_post(hipStream_t s, const float* dy, const float* w, const float* add, float* dz,
                               const float* mask_src, const float* xc, const float* stats, float* records, int N, int HW, int C);
 int conv3x3_tiled_prebn(hipStream_t s, const float* src, const float* records, int in_parts, const float* gamma,
-                         const float* beta, float eps, const float* shortcut, float* act_out, float* stats_out,
+                         const float* beta, float eps, const float* shortcut, bool half, float* act_out, float* stats_out,
                          const float* w, float* dst, float* bn_partial, int N, int HW, int C);
 int wgrad3x3_tiled_parts(int N, int HW, int C);
 int wgrad3x3_tiled(hipStream_t s, const float* x, const float* dy, float* partial, int N, int HW, int C, const jobs::TotalsJob& tj);
@@ -828,14 +828,27 @@ extern "C" int dsspk_conv_fwd_records(void* stream, const float* x, const float*
     return launch_igemm<false, false>((hipStream_t)stream, x, w, nullptr, nullptr, y, g, 0, records);
 }
 
-extern "C" int dsspk_conv_fwd_prebn(void* stream, const float* src, const float* records, int in_parts, const float* gamma,
-                                    const float* beta, float eps, const float* shortcut, float* act_out, float* stats_out,
+static int conv_fwd_prebn(void* stream, const float* src, const float* records, int in_parts, const float* gamma,
+                                    const float* beta, float eps, const float* shortcut, bool half, float* act_out, float* stats_out,
                                     const float* w, float* y, float* bn_partial, int N, int H, int C) {
     if (!src || !records || !gamma || !beta || !act_out || !stats_out || !w || !y || N < 1) return -1;
     if (conv3x3_tiled_stat_parts(N, H, C) == 0) return -1;
-    const int rc = conv3x3_tiled_prebn((hipStream_t)stream, src, records, in_parts, gamma, beta, eps, shortcut, act_out, stats_out,
+    const int rc = conv3x3_tiled_prebn((hipStream_t)stream, src, records, in_parts, gamma, beta, eps, shortcut, half, act_out, stats_out,
                                         w, y, bn_partial, N, H, C);
     return rc == -2 ? -1 : rc;
+}
+
+extern "C" int dsspk_conv_fwd_prebn(void* stream, const float* src, const float* records, int in_parts, const float* gamma, const float* beta,
+                                    float eps, const float* shortcut, float* act_out, float* stats_out, const float* w, float* dst,
+                                    float* bn_partial, int N, int H, int C) {
+    return conv_fwd_prebn(stream, src, records, in_parts, gamma, beta, eps, shortcut, false, act_out, stats_out, w, dst, bn_partial, N, H, C);
+}
+
+extern "C" int dsspk_conv_fwd_prebn_half(void* stream, const float* src, const float* records, int in_parts, const float* gamma, const float* beta,
+                                         float eps, const float* shortcut, float* act_out, float* stats_out, const float* w, float* dst,
+                                         float* bn_partial, int N, int H, int C) {
+    if (!shortcut || C <= 16) return -1;
+    return conv_fwd_prebn(stream, src, records, in_parts, gamma, beta, eps, shortcut, true, act_out, stats_out, w, dst, bn_partial, N, H, C);
 }
 
 extern "C" int dsspk_conv_bwd_data_post(void* stream, const float* dy, const float* w, const float* add, float* dz,

@@ -130,9 +130,10 @@ int conv3x3_tiled(hipStream_t s, const float* src, const float* w, const float* 
 // Forward convolution of a = ReLU(BN(src) (+ shortcut)), see PreBn.  in_parts: number of equal-sized
 // statistics records of src in `records` (as emitted by the forward kernel for the same shape).
 int conv3x3_tiled_prebn(hipStream_t s, const float* src, const float* records, int in_parts, const float* gamma,
-                         const float* beta, float eps, const float* shortcut, float* act_out, float* stats_out,
+                         const float* beta, float eps, const float* shortcut, bool half, float* act_out, float* stats_out,
                          const float* w, float* dst, float* bn_partial, int N, int HW, int C) {
     PreBn pre;
+    pre.half = half;
     pre.records = records;
     pre.M = (long)N * HW * HW;
     if (in_parts < 1 || pre.M % in_parts || in_parts > 32 * (THREADS / C)) return -1;

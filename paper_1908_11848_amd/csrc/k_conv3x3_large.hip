@@ -27,9 +27,11 @@ extern "C" int dsspk_conv3x3_large_parts(int N, int H, int C) { return N < 1 || 
 
 extern "C" int dsspk_conv3x3_large_fwd(void* stream, const float* src, const float* records, int parts, const float* gamma, const float* beta,
                                        float eps, const float* shortcut, float* act_out, float* stats_out, const float* w, float* dst,
-                                       float* records_out, int N, int H, int C) {
+                                       float* records_out, int shortcut_half, int N, int H, int C) {
     if (!src || !w || !dst || !records_out || dst == src || dsspk_conv3x3_large_parts(N, H, C) == 0) return -1;
+    if (shortcut_half && (!shortcut || C <= 16)) return -1;
     PreBn pre{};
+    pre.half = shortcut_half != 0;
     if (!records) {
         if (parts || shortcut) return -1;
         return forward<0>((hipStream_t)stream, src, w, dst, records_out, N, C, pre);

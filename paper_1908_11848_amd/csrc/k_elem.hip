@@ -422,6 +422,97 @@ __global__ __launch_bounds__(THREADS) void shortcut_bwd_acc_kernel(const float* 
     }
 }
 
+// The last batch norm with ReLU and shortcut and the average pooling behind it, one image to a workgroup; and both on the way back: the
+// pooled gradient spread over the image, masked, with its record.  Four launches of 5 us less the two that remain.
+template <int SC_MODE>
+__global__ __launch_bounds__(THREADS) void bn_gap_kernel(const float* __restrict__ x, const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                         const float* __restrict__ partial, float* __restrict__ stats, float* __restrict__ y, long M,
+                                                         int C, float eps, const float* __restrict__ sc, int side, float* __restrict__ pooled, BnLayout L) {
+    __shared__ float red[THREADS];
+    __shared__ __attribute__((aligned(16))) float sh[2 * THREADS];
+    __shared__ float4 red4[THREADS];
+    bn_merge_stats(partial, M, C, eps, red, sh, L);
+    if (blockIdx.x == 0 && threadIdx.x < 2 * C) stats[threadIdx.x] = sh[threadIdx.x];
+    const int VC = C / 4, RL = THREADS / VC, rl = threadIdx.x / VC, vc = threadIdx.x % VC, HW = side * side;
+    const long base = (long)blockIdx.x * HW;
+    const float4 mu = *reinterpret_cast<const float4*>(sh + 4 * vc), is = *reinterpret_cast<const float4*>(sh + C + 4 * vc);
+    const float4 ga = *reinterpret_cast<const float4*>(gamma + 4 * vc), be = *reinterpret_cast<const float4*>(beta + 4 * vc);
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int r0 = rl; r0 < HW; r0 += 4 * RL) {
+        float4 v[4], s4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = r0 + u * RL;
+            v[u] = s4[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (r >= HW) continue;
+            v[u] = *reinterpret_cast<const float4*>(x + (base + r) * C + 4 * vc);
+            if constexpr (SC_MODE == 1) s4[u] = *reinterpret_cast<const float4*>(sc + (base + r) * C + 4 * vc);
+            else if (4 * vc < C / 2)
+                s4[u] = *reinterpret_cast<const float4*>(sc + (4 * base + 2 * (r / side) * 2 * side + 2 * (r % side)) * (C / 2) + 4 * vc);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = r0 + u * RL;
+            if (r >= HW) continue;
+            float4 o;
+            o.x = fmaxf(fmaf((v[u].x - mu.x) * is.x, ga.x, be.x) + s4[u].x, 0.f);
+            o.y = fmaxf(fmaf((v[u].y - mu.y) * is.y, ga.y, be.y) + s4[u].y, 0.f);
+            o.z = fmaxf(fmaf((v[u].z - mu.z) * is.z, ga.z, be.z) + s4[u].z, 0.f);
+            o.w = fmaxf(fmaf((v[u].w - mu.w) * is.w, ga.w, be.w) + s4[u].w, 0.f);
+            *reinterpret_cast<float4*>(y + (base + r) * C + 4 * vc) = o;
+            sum.x += o.x; sum.y += o.y; sum.z += o.z; sum.w += o.w;
+        }
+    }
+    sum = reduce_rows(sum, red4, rl, vc, RL, VC);
+    if (rl == 0) {
+        const float n = (float)HW;
+        *reinterpret_cast<float4*>(pooled + (long)blockIdx.x * C + 4 * vc) = make_float4(sum.x / n, sum.y / n, sum.z / n, sum.w / n);
+    }
+}
+
+__global__ __launch_bounds__(THREADS) void gap_bwd_bn_reduce_kernel(const float* __restrict__ dpooled, const float* __restrict__ x,
+                                                                    const float* __restrict__ stats, const float* __restrict__ out,
+                                                                    float* __restrict__ dz, float* __restrict__ records, int HW, int C) {
+    __shared__ float4 red[THREADS];
+    const int VC = C / 4, RL = THREADS / VC, rl = threadIdx.x / VC, vc = threadIdx.x % VC;
+    const long base = (long)blockIdx.x * HW;
+    const float inv = 1.0f / (float)HW;
+    float4 g = *reinterpret_cast<const float4*>(dpooled + (long)blockIdx.x * C + 4 * vc);
+    g.x *= inv; g.y *= inv; g.z *= inv; g.w *= inv;
+    const float4 mu = *reinterpret_cast<const float4*>(stats + 4 * vc), is = *reinterpret_cast<const float4*>(stats + C + 4 * vc);
+    float4 sb = make_float4(0.f, 0.f, 0.f, 0.f), sg = sb;
+    for (int r0 = rl; r0 < HW; r0 += 4 * RL) {
+        float4 v[4], o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = r0 + u * RL;
+            v[u] = mu;
+            o[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (r >= HW) continue;
+            v[u] = *reinterpret_cast<const float4*>(x + (base + r) * C + 4 * vc);
+            o[u] = *reinterpret_cast<const float4*>(out + (base + r) * C + 4 * vc);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = r0 + u * RL;
+            const float4 d = make_float4(o[u].x > 0.f ? g.x : 0.f, o[u].y > 0.f ? g.y : 0.f, o[u].z > 0.f ? g.z : 0.f, o[u].w > 0.f ? g.w : 0.f);
+            if (r < HW) *reinterpret_cast<float4*>(dz + (base + r) * C + 4 * vc) = d;
+            sb.x += d.x; sb.y += d.y; sb.z += d.z; sb.w += d.w;
+            sg.x = fmaf(d.x, (v[u].x - mu.x) * is.x, sg.x);
+            sg.y = fmaf(d.y, (v[u].y - mu.y) * is.y, sg.y);
+            sg.z = fmaf(d.z, (v[u].z - mu.z) * is.z, sg.z);
+            sg.w = fmaf(d.w, (v[u].w - mu.w) * is.w, sg.w);
+        }
+    }
+    sb = reduce_rows(sb, red, rl, vc, RL, VC);
+    sg = reduce_rows(sg, red, rl, vc, RL, VC);
+    if (rl == 0) {
+        float4* to = reinterpret_cast<float4*>(records + ((long)blockIdx.x * C + 4 * vc) * 2);
+        to[0] = make_float4(sb.x, sg.x, sb.y, sg.y);
+        to[1] = make_float4(sb.z, sg.z, sb.w, sg.w);
+    }
+}
+
 // ------------------------------------------------------------------ global average pooling
 __global__ __launch_bounds__(THREADS) void gap_fwd_kernel(const float* __restrict__ x, float* __restrict__ y, int N, int HW, int C) {
     const int i = blockIdx.x * THREADS + threadIdx.x;
@@ -625,6 +716,29 @@ extern "C" int dsspk_shortcut_bwd_acc(void* stream, const float* dy, float* dx, 
     if (!dy || !dx || N < 1 || Ho < 1 || Wo < 1 || C < 8 || C % 8 || !al16(dy) || !al16(dx)) return -1;
     hipLaunchKernelGGL(shortcut_bwd_acc_kernel, dim3(grid_for((long)N * Ho * Wo * (C / 8))), dim3(THREADS), 0,
                        (hipStream_t)stream, dy, dx, N, Ho, Wo, C);
+    return DSSPK_LAUNCH_RC();
+}
+
+extern "C" int dsspk_bn_fwd_gap(void* stream, const float* x, const float* gamma, const float* beta, float* y, float* stats, const float* records,
+                                int parts, const float* sc, int sc_half, float* pooled, int N, int side, int C, float eps) {
+    const long M = (long)N * side * side;
+    if (!x || !gamma || !beta || !y || !stats || !records || !sc || !pooled || N < 1 || side < 1 || !bn_ok(M, C)) return -1;
+    if (!al16(x) || !al16(y) || !al16(gamma) || !al16(beta) || !al16(stats) || !al16(sc) || !al16(pooled) || (sc_half && C % 8)) return -1;
+    if (parts < 1 || M % parts || parts > 32 * (THREADS / C)) return -1;
+    BnLayout L = bn_layout(M, C);
+    L.G = parts;
+    L.rows_per_block = M / parts;
+    hipStream_t s = (hipStream_t)stream;
+    if (sc_half) hipLaunchKernelGGL((bn_gap_kernel<2>), dim3(N), dim3(THREADS), 0, s, x, gamma, beta, records, stats, y, M, C, eps, sc, side, pooled, L);
+    else hipLaunchKernelGGL((bn_gap_kernel<1>), dim3(N), dim3(THREADS), 0, s, x, gamma, beta, records, stats, y, M, C, eps, sc, side, pooled, L);
+    return DSSPK_LAUNCH_RC();
+}
+
+extern "C" int dsspk_gap_bwd_bn_reduce(void* stream, const float* dpooled, const float* x, const float* stats, const float* out, float* dz,
+                                       float* records, int N, int side, int C) {
+    if (!dpooled || !x || !stats || !out || !dz || !records || N < 1 || side < 1 || !bn_ok((long)N * side * side, C)) return -1;
+    if (!al16(dpooled) || !al16(x) || !al16(stats) || !al16(out) || !al16(dz) || !al16(records)) return -1;
+    hipLaunchKernelGGL(gap_bwd_bn_reduce_kernel, dim3(N), dim3(THREADS), 0, (hipStream_t)stream, dpooled, x, stats, out, dz, records, side * side, C);
     return DSSPK_LAUNCH_RC();
 }
 

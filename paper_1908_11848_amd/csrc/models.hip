@@ -306,13 +306,14 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     };
     auto conv = [&](const float* src, const float* wt, float* dst, int H, int cin, int cout, int stride, float* rec) {
         if (rec && (cin != cout || stride != 1)) return dsspk_conv_fwd_records(s, src, wt, dst, rec, m, H, H, cin, cout, 3, 3, stride, 1);
-        if (large && rec) return dsspk_conv3x3_large_fwd(s, src, nullptr, 0, nullptr, nullptr, 0.f, nullptr, nullptr, nullptr, wt, dst, rec, m, H, cin);
+        if (large && rec) return dsspk_conv3x3_large_fwd(s, src, nullptr, 0, nullptr, nullptr, 0.f, nullptr, nullptr, nullptr, wt, dst, rec, 0, m, H, cin);
         return dsspk_conv_fwd(s, src, wt, nullptr, dst, m, H, H, cin, cout, 3, 3, stride, 1, 0, rec);
     };
     auto conv_prebn = [&](const float* src, const float* rec, int parts, const float* gamma, const float* beta, const float* shortcut, float* act,
-                          float* stats, const float* wt, float* dst, float* rec_out, int H, int C) {
-        return (large ? dsspk_conv3x3_large_fwd : dsspk_conv_fwd_prebn)(s, src, rec, parts, gamma, beta, eps, shortcut, act, stats, wt, dst, rec_out,
-                                                                       m, H, C);
+                          float* stats, const float* wt, float* dst, float* rec_out, int H, int C, bool half = false) {
+        if (large) return dsspk_conv3x3_large_fwd(s, src, rec, parts, gamma, beta, eps, shortcut, act, stats, wt, dst, rec_out, half, m, H, C);
+        return (half ? dsspk_conv_fwd_prebn_half : dsspk_conv_fwd_prebn)(s, src, rec, parts, gamma, beta, eps, shortcut, act, stats, wt, dst, rec_out,
+                                                                        m, H, C);
     };
     auto regular = [&](int i) {
         const ResBlock& b = P->blocks[i];
@@ -338,7 +339,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         } else if (pending) {
             const ResBlock& Pv = P->blocks[bi - 1];
             const float* pin = bi >= 2 ? F(P->blocks[bi - 2].out) : F(P->stem_a);         // the previous block's input = its shortcut
-            RUN(conv_prebn(F(Pv.c2), recB, parts2, w + Pv.g2, w + Pv.b2, pin, F(Pv.out), F(Pv.st2), w + B.w1, F(B.c1), recA, B.H, B.cin));
+            RUN(conv_prebn(F(Pv.c2), recB, parts2, w + Pv.g2, w + Pv.b2, pin, F(Pv.out), F(Pv.st2), w + B.w1, F(B.c1), recA, B.H, B.cin, Pv.stride == 2));
         } else {
             RUN(conv(cur, w + B.w1, F(B.c1), B.H, B.cin, B.cout, B.stride, parts1 ? recA : nullptr));
         }
@@ -348,18 +349,18 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             RUN(dsspk_bn_fwd(s, F(B.c1), w + B.g1, w + B.b1, F(B.a1), F(B.st1), recA, M, B.cout, eps, 1, 0, nullptr, 0, 0, 0, parts1));
             RUN(conv(F(B.a1), w + B.w2, F(B.c2), Ho, B.cout, B.cout, 1, parts2 ? recB : nullptr));
         }
-        pending = regular(bi) && parts2 > 0 && bi + 1 < nb && regular(bi + 1);
-        if (!pending) {
-            const int mode = (B.stride == 1 && B.cin == B.cout) ? 1 : 2;
+        pending = parts2 > 0 && bi + 1 < nb && regular(bi + 1);
+        const int mode = (B.stride == 1 && B.cin == B.cout) ? 1 : 2;
+        if (bi + 1 == nb) {
+            RUN(dsspk_bn_fwd_gap(s, F(B.c2), w + B.g2, w + B.b2, F(B.out), F(B.st2), recB, parts2, cur, mode == 2, F(P->pooled), m, Ho, B.cout, eps));
+        } else if (!pending) {
             RUN(dsspk_bn_fwd(s, F(B.c2), w + B.g2, w + B.b2, F(B.out), F(B.st2), recB, M, B.cout, eps, 1, mode, cur, m, Ho, Ho, parts2));
         }
         cur = F(B.out);
     }
-    RUN(dsspk_gap_fwd(s, cur, F(P->pooled), m, 64, 64));
     if (int rc = last_layer(P, ws, s, F(P->pooled), 64, y, w, g, P->fc_w, P->fc_b, F(P->dpooled), 0, loss, err)) return rc;
     // ---- backward
     float *g0 = F(P->G[0]), *g1 = F(P->G[1]), *g2 = F(P->G[2]);     // g0: gradient w.r.t. the current block output
-    RUN(dsspk_gap_bwd(s, F(P->dpooled), g0, m, 64, 64));
     // Per convolution layer the backward pass is  BN backward -> d-input convolution -> d-filter convolution.
     // Where the specialised 3x3 kernels apply, and the gradient arrives already masked with sum records (written by the
     // epilogue of the d-input convolution before it), these collapse (regular_layer below):
@@ -463,7 +464,10 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         const int partsp = identity ? parts_of(B.H, B.cin, B.cout, 1) : 0;
         const bool fused1 = parts1 > 0 && partsp > 0;        // conv1's layer takes the two-launch form
         // ---- BN2 + conv2: g0 = dz2 -> g1 = d conv2 output, g2 = dz1 = d a1 * [a1 > 0] (+ BN1's records in bscr)
-        if (!parts0) {                  // g0 is not masked yet
+        if (bi + 1 == nb) {             // from the pooled gradient
+            RUN(dsspk_gap_bwd_bn_reduce(s, F(P->dpooled), F(B.c2), F(B.st2), F(B.out), g0, recB0, m, Ho, B.cout));
+            parts0 = m;
+        } else if (!parts0) {           // g0 is not masked yet
             RUN(dsspk_bn_bwd_reduce_parts(s, F(B.c2), F(B.st2), g0, F(B.out), recB0, parts1, M, B.cout));
             parts0 = parts1;
             tot0 = false;

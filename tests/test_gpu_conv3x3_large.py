@@ -16,7 +16,7 @@ def test_what_is_covered():
     for H, C in SHAPES:
         assert [L.dsspk_conv3x3_large_parts(N, H, C) for N in (0, 1, 128, 129)] == [0, 2 if C == 16 else 1, 256 if C == 16 else 128, 0]
         assert L.dsspk_conv3x3_large_parts(4, H + 1, C) == 0 and L.dsspk_conv3x3_large_parts(4, H, C + 16) == 0
-    assert L.dsspk_conv3x3_large_fwd(None, None, None, 0, None, None, 1e-5, None, None, None, None, None, None, 4, 32, 16) == -1
+    assert L.dsspk_conv3x3_large_fwd(None, None, None, 0, None, None, 1e-5, None, None, None, None, None, None, 0, 4, 32, 16) == -1
 
 
 def _records(parts, C, x):
@@ -41,11 +41,11 @@ def test_forward(oracle_nn, N, H, C, form):
     act, stats, y, rec = empty((N, H, H, C)), empty(2 * C), empty((N, H, H, C)), empty((parts, C, 2))
     a = x.astype(np.float64)
     if form == "plain":
-        assert L.dsspk_conv3x3_large_fwd(s, X.data_ptr(), None, 0, None, None, 1e-5, None, None, None, W.data_ptr(), y.data_ptr(), rec.data_ptr(), N, H, C) == 0
+        assert L.dsspk_conv3x3_large_fwd(s, X.data_ptr(), None, 0, None, None, 1e-5, None, None, None, W.data_ptr(), y.data_ptr(), rec.data_ptr(), 0, N, H, C) == 0
     else:
         short = SC.data_ptr() if form == "bn+shortcut" else None
         assert L.dsspk_conv3x3_large_fwd(s, X.data_ptr(), REC.data_ptr(), parts, G.data_ptr(), BE.data_ptr(), 1e-5, short, act.data_ptr(),
-                                         stats.data_ptr(), W.data_ptr(), y.data_ptr(), rec.data_ptr(), N, H, C) == 0
+                                         stats.data_ptr(), W.data_ptr(), y.data_ptr(), rec.data_ptr(), 0, N, H, C) == 0
         mean, var = a.mean((0, 1, 2)), a.var((0, 1, 2))
         st = host(stats).reshape(2, C)
         assert max_abs(st[0], mean) < 2e-6 and rel_l2(st[1], 1 / np.sqrt(var + 1e-5)) < 1e-6

@@ -87,3 +87,61 @@ def test_input_gradient_with_shortcut(N, H, Cin):
     assert L.dsspk_conv_bwd_data_shortcut(s, dy.data_ptr(), w.data_ptr(), sc.data_ptr(), dx.data_ptr(), N, H, H, Cin, Cout, 3, 3, 1) == 0
     assert np.array_equal(host(dx), host(want))
     assert L.dsspk_conv_bwd_data_shortcut(s, dy.data_ptr(), w.data_ptr(), sc.data_ptr(), dx.data_ptr(), N, H + 1, H, Cin, Cout, 3, 3, 1) == -1
+
+
+def _records(parts, C, x):
+    r = x.reshape(parts, -1, C).astype(np.float64)
+    m = r.mean(1)
+    return np.stack([m, ((r - m[:, None]) ** 2).sum(1)], axis=2).astype(np.float32)
+
+
+@pytest.mark.parametrize("N,side,C", [(1, 8, 64), (13, 8, 64), (128, 8, 64), (2, 3, 16), (3, 10, 32)])
+@pytest.mark.parametrize("half", [False, True])
+def test_last_batch_norm_with_pooling(N, side, C, half):
+    """Against the kernels one by one: the same activations bit for bit, the pooled sums of side^2 terms in another order."""
+    g = np.random.default_rng(N + side)
+    HW, L, s = side * side, B.lib(), stream_ptr()
+    M = N * HW
+    x = g.standard_normal((M, C)).astype(np.float32)
+    sc = dev(g.standard_normal((N, 2 * side, 2 * side, C // 2) if half else (M, C)).astype(np.float32))
+    X, G, BE, rec = dev(x), dev(1 + 0.1 * g.standard_normal(C)), dev(0.1 * g.standard_normal(C)), dev(_records(N, C, x))
+    y, y0, st, st0, p, p0 = empty((M, C)), empty((M, C)), empty(2 * C), empty(2 * C), empty((N, C)), empty((N, C))
+    assert L.dsspk_bn_fwd_gap(s, X.data_ptr(), G.data_ptr(), BE.data_ptr(), y.data_ptr(), st.data_ptr(), rec.data_ptr(), N, sc.data_ptr(), int(half),
+                              p.data_ptr(), N, side, C, 1e-5) == 0
+    assert L.dsspk_bn_fwd(s, X.data_ptr(), G.data_ptr(), BE.data_ptr(), y0.data_ptr(), st0.data_ptr(), rec.data_ptr(), M, C, 1e-5, 1, 2 if half else 1,
+                          sc.data_ptr(), N, side, side, N) == 0
+    assert L.dsspk_gap_fwd(s, y0.data_ptr(), p0.data_ptr(), N, HW, C) == 0
+    assert np.array_equal(host(y), host(y0)) and np.array_equal(host(st), host(st0))
+    assert np.max(np.abs(host(p) - host(p0))) < 1e-6 * np.abs(host(y)).max()
+    dp, dz, dz0, r, r0 = dev(g.standard_normal((N, C)).astype(np.float32)), empty((M, C)), empty((M, C)), empty((N, C, 2)), empty((N, C, 2))
+    assert L.dsspk_gap_bwd_bn_reduce(s, dp.data_ptr(), X.data_ptr(), st.data_ptr(), y.data_ptr(), dz.data_ptr(), r.data_ptr(), N, side, C) == 0
+    assert L.dsspk_gap_bwd(s, dp.data_ptr(), dz0.data_ptr(), N, HW, C) == 0
+    assert L.dsspk_bn_bwd_reduce_parts(s, X.data_ptr(), st.data_ptr(), dz0.data_ptr(), y.data_ptr(), r0.data_ptr(), N, M, C) == 0
+    assert np.array_equal(host(dz), host(dz0)) and np.array_equal(host(r), host(r0))
+
+
+@pytest.mark.parametrize("N,H,C", [(1, 16, 32), (5, 16, 32), (128, 16, 32), (1, 8, 64), (5, 8, 64), (128, 8, 64)])
+@pytest.mark.parametrize("large", [False, True])
+@pytest.mark.parametrize("scale", [1.0, 1e32])
+def test_convolution_behind_a_stride_2_shortcut(N, H, C, large, scale):
+    """Both kernel families against the batch norm with that shortcut and the plain convolution, one after the other; scale: of one shortcut
+    value, the second beyond the range of the scaled terms (the tiles it meets are then computed by other instructions: 4e-7)."""
+    g = np.random.default_rng(N + C)
+    f = lambda *sh: g.standard_normal(sh).astype(np.float32)
+    x, sc = f(N, H, H, C), f(N, 2 * H, 2 * H, C // 2)
+    sc[N - 1, 2, 2 * H - 2, 1] = scale
+    L, s = B.lib(), stream_ptr()
+    parts = L.dsspk_conv3x3_large_parts(N, H, C) if large else L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1)
+    X, SC, W, G, BE, rec = dev(x), dev(sc), dev(0.1 * f(3, 3, C, C)), dev(1 + 0.1 * f(C)), dev(0.1 * f(C)), dev(_records(parts, C, x))
+    act, act0, st, st0, y, y0, out = empty(x.shape), empty(x.shape), empty(2 * C), empty(2 * C), empty(x.shape), empty(x.shape), empty((parts, C, 2))
+    args = (s, X.data_ptr(), rec.data_ptr(), parts, G.data_ptr(), BE.data_ptr(), 1e-5, SC.data_ptr(), act.data_ptr(), st.data_ptr(), W.data_ptr(),
+            y.data_ptr(), out.data_ptr())
+    assert (L.dsspk_conv3x3_large_fwd(*args, 1, N, H, C) if large else L.dsspk_conv_fwd_prebn_half(*args, N, H, C)) == 0
+    assert L.dsspk_bn_fwd(s, X.data_ptr(), G.data_ptr(), BE.data_ptr(), act0.data_ptr(), st0.data_ptr(), rec.data_ptr(), N * H * H, C, 1e-5, 1, 2,
+                          SC.data_ptr(), N, H, H, parts) == 0
+    assert L.dsspk_conv_fwd(s, act0.data_ptr(), W.data_ptr(), None, y0.data_ptr(), N, H, H, C, C, 3, 3, 1, 1, 0, None) == 0
+    a, a0, c, c0 = host(act), host(act0), host(y), host(y0)
+    quiet = np.abs(c0) < 1e6
+    assert np.isfinite(c).all() and np.max(np.abs(a - a0) / np.maximum(np.abs(a0), 1)) < 4e-6
+    assert rel_l2(c[quiet], c0[quiet]) < 2e-6 and rel_l2(c, c0) < 2e-6
+    assert (L.dsspk_conv3x3_large_fwd(*args, 1, N, 32, 16) if large else L.dsspk_conv_fwd_prebn_half(*args, N, 32, 16)) == -1

@@ -195,6 +195,18 @@ int dsspk_conv3x3_large_bwd(void* stream, const float* dz_dev, const float* xc_d
                             const float* w_dev, const float* add_dev, float* out_dev, const float* x_in_dev, const float* xc_post_dev,
                             const float* stats_post_dev, float* records_dev, const float* red_partial_dev, float* red_dw_dev, int red_E,
                             int red_chunks, int N, int H, int C);
+/* The same for small batches, up to DSSPK_CONV3X3_SMALL_MAX images: smaller workgroups, twice as many records and partial results as the
+ * kernels of dsspk_conv_fwd_prebn and its relatives leave (64 channels: one per image). */
+#define DSSPK_CONV3X3_SMALL_MAX 16
+int dsspk_conv3x3_small_parts(int N, int H, int C);
+int dsspk_conv3x3_small_fwd(void* stream, const float* src_dev, const float* records_dev, int parts, const float* gamma_dev,
+                            const float* beta_dev, float eps, const float* shortcut_dev, float* act_out_dev, float* stats_out_dev,
+                            const float* w_dev, float* dst_dev, float* records_out_dev, int shortcut_half, int N, int H, int C);
+int dsspk_conv3x3_small_bwd(void* stream, const float* dz_dev, const float* xc_dev, const float* stats_dev, const float* gamma_dev,
+                            const float* in_records_dev, int parts, float* dgamma_dev, float* dbeta_dev, float* dx_dev, float* partial_dev,
+                            const float* w_dev, const float* add_dev, float* out_dev, const float* x_in_dev, const float* xc_post_dev,
+                            const float* stats_post_dev, float* records_dev, const float* red_partial_dev, float* red_dw_dev, int red_E,
+                            int red_chunks, int N, int H, int C);
 
 /* dw[kh][kw][ci][co] = sum over batch and output pixels of x * dy.  Two stages (partial sums per
  * pixel chunk, then a fixed-order reduction).  scratch_dev: dsspk_conv_wgrad_scratch_floats(...) floats. */

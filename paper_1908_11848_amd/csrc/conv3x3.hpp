@@ -31,6 +31,9 @@
 
 namespace {
 
+// Records of the tensor in front that a thread of its consumer fetches at most
+template <int C, int WAVES, int NT> constexpr int max_records() { return NT == 2 || (WAVES == 8 && C == 64) ? 16 : 8; }
+
 template <int C, int HW, int R, int NSPLIT, int WAVES>
 struct Cfg {
     static constexpr int THREADS = 64 * WAVES;
@@ -44,13 +47,17 @@ struct Cfg {
     static constexpr int XB = (R + 2) * TW * PITCH;            // bytes
     static constexpr int WAVES_N = CN / 16;        // wavefronts side by side over the output channels
     static constexpr int WAVES_M = WAVES / WAVES_N;    // ... and over the pixels or, in the last stage, the input channels
-    // A wavefront works on four pixel tiles, each one (HW >= 16) or two (HW = 8) image rows below the one before.
+    // A wavefront works on NT (four or two) pixel tiles, each one (HW >= 16) or two (HW = 8) image rows below the one before.
     static constexpr int TROWS = HW >= 16 ? 1 : 2;
     static constexpr int TX = HW >= 16 ? HW / 16 : 1;          // tiles side by side
-    static constexpr int WPX = R / (4 * TROWS) * TX;           // wavefronts over the band's pixels
-    static constexpr int KS = WAVES_M / WPX;       // wavefronts that share pixels and split the input channels; they swap
+    static constexpr int KS = C == 64 ? 2 : 1;     // wavefronts that share pixels and split the input channels; they swap
                                                    // halves of their sums through LDS and each finishes its half
-    static constexpr int WM = 4 / KS;              // pixel tiles a wavefront finishes
+    static constexpr int WPX = WAVES_M / KS;                   // wavefronts over the band's pixels
+    static constexpr int NT = R * TX / (TROWS * WPX);
+    static constexpr int WM = NT / KS;             // pixel tiles a wavefront finishes
+    // Two tiles: the products of a filter column are too few to hide the fetch of the next one, and registers are not what counts
+    // where the tiles are that small: all three columns are fetched up front.
+    static constexpr int COLUMNS = NT == 4 ? 1 : 3;
     static constexpr int SC = WAVES_M * CN;        // floats: per-wavefront column sums (batch-norm records, one component)
     static constexpr int SS = 2 * SC;
     static constexpr int PS = 5 * C;               // floats: per-channel vectors of the loader
@@ -62,7 +69,7 @@ struct Cfg {
     static constexpr size_t RED = C == 16 ? (size_t)WAVES * 9 * C * C * sizeof(float) : 0;
     static constexpr size_t COLUMN = C == 32 && RSPLIT == 2 ? (size_t)DTILES * 3 * 256 * sizeof(float) : 0;
     static constexpr size_t LDS_BYTES_WG = LDS_BYTES + COLUMN > RED ? LDS_BYTES + COLUMN : RED;
-    static_assert(WPX * KS == WAVES_M && (KS == 1 || KS == 2) && (C == 16 || C == 32 * KS), "roles of the wavefronts");
+    static_assert(WPX * KS == WAVES_M && (NT == 4 || NT == 2) && NT * TROWS * WPX == R * TX && (C == 16 || C == 32 * KS), "roles of the wavefronts");
     static_assert(XB % 16 == 0 && WAVES * 2 * 64 * 16 <= XB, "alignment; room for the exchange");
     // the loader: rows inside the image (or halo rows of a band), columns inside the image; what remains of the tile is zero
     static constexpr bool WHOLE = R == HW;
@@ -72,7 +79,7 @@ struct Cfg {
     static constexpr int ZERO_UNIT = PITCH % 16 == 0 ? 16 : 8, ZERO_UNITS = 3 * PLANE / ZERO_UNIT;       // of a border pixel
     static constexpr int ZERO = (2 * (R + 2) + (WHOLE ? 2 * HW : 0)) * ZERO_UNITS;
     // records of the tensor in front: each thread fetches at most this many
-    static constexpr int RECORDS = WAVES == 8 && C == 64 ? 16 : 8;
+    static constexpr int RECORDS = max_records<C, WAVES, NT>();
 };
 
 // Normalisation applied to the input while it is loaded (PRE != 0): the kernel then computes
@@ -152,7 +159,7 @@ __device__ __forceinline__ float sum16(float v) {
 __device__ __forceinline__ float4 sum16(float4 v) { return make_float4(sum16(v.x), sum16(v.y), sum16(v.z), sum16(v.w)); }
 
 // The most records of a tensor that every workgroup of its consumer merges itself.
-template <int C, int WAVES> constexpr int inline_records() { return 64 * WAVES * (WAVES == 8 && C == 64 ? 16 : 8) / C; }
+template <int C, int WAVES, int NT = 4> constexpr int inline_records() { return 64 * WAVES * max_records<C, WAVES, NT>() / C; }
 
 // Thread (channel tid % C, lane tid / C) holds records lane, lane + THREADS / C, ... of its channel; all loads in flight together.
 template <int C, int THREADS, int RECORDS>
@@ -212,7 +219,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         r.wave_n = r.wave % K::WAVES_N; r.wave_m = r.wave / K::WAVES_N;
         r.co_w = part * K::CN + 16 * r.wave_n;                  // first output channel of this wavefront
         r.wpx = r.wave_m / K::KS; r.ks = r.wave_m % K::KS;      // its pixels, its share of the input channels
-        r.row0 = r.wpx / K::TX * 4 * K::TROWS + (K::TROWS == 2 ? r.l16 >> 3 : 0);           // this lane's pixel in the first tile
+        r.row0 = r.wpx / K::TX * K::NT * K::TROWS + (K::TROWS == 2 ? r.l16 >> 3 : 0);           // this lane's pixel in the first tile
         r.col = K::TROWS == 2 ? r.l16 & 7 : 16 * (r.wpx % K::TX) + r.l16;
         return r;
     };
@@ -224,7 +231,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     //      One filter column (three taps) at a time: the product loop walks the columns, and a row of the next one is
     //      fetched while the loop still works with that row of the present one.
     constexpr int FV = C == 16 ? 1 : 2;
-    float4 fr[3][FV];
+    float4 fr[K::COLUMNS][3][FV];
     split::Filt<C> filt[3];
     unsigned filter_at;
     {
@@ -237,17 +244,18 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         for (int e = 0; e < FV; ++e) {
             const int tap = 3 * ky + kx;
             if constexpr (TRANSPOSED) {
-                fr[ky][e] = load4(wgt + (8 - tap) * C * C + 4 * e, filter_at);
+                fr[kx % K::COLUMNS][ky][e] = load4(wgt + (8 - tap) * C * C + 4 * e, filter_at);
             } else {
                 const float* wp = wgt + tap * C * C + 4 * e * C;
-                fr[ky][e] = make_float4((wp + 0 * C)[filter_at], (wp + 1 * C)[filter_at], (wp + 2 * C)[filter_at], (wp + 3 * C)[filter_at]);
+                fr[kx % K::COLUMNS][ky][e] = make_float4((wp + 0 * C)[filter_at], (wp + 1 * C)[filter_at], (wp + 2 * C)[filter_at], (wp + 3 * C)[filter_at]);
             }
         }
     };
-    auto split_filter = [&](int ky) {
+    auto split_filter = [&](int ky, int kx) {
+        float4 (&f)[FV] = fr[kx % K::COLUMNS][ky];
 #pragma unroll
-        for (int e = 0; e < FV; ++e) fr[ky][e] = split::scaled(fr[ky][e]);
-        filt[ky] = split::filter_operand<C>(fr[ky]);
+        for (int e = 0; e < FV; ++e) f[e] = split::scaled(f[e]);
+        filt[ky] = split::filter_operand<C>(f);
     };
     float2 rec[PRE ? K::RECORDS : 1];
     if constexpr (PRE == 1 || PRE == 2)
@@ -255,7 +263,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     if constexpr (PRE == 3)
         if (!bwd.totals) load_records<C, THREADS>(rec, bwd.records, bwd.parts, tid);
 #pragma unroll
-    for (int ky = 0; ky < 3; ++ky) load_filter(ky, 0);
+    for (int kx = 0; kx < K::COLUMNS; ++kx)
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) load_filter(ky, kx);
     // ---- input halo tile, zero outside the image.  The raw loads are issued first; the first filter column is split while
     //      they are in flight.
     float4 val[NL], scv[PRE >= 2 ? NL : 1];
@@ -292,7 +302,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         }
     }
 #pragma unroll
-    for (int ky = 0; ky < 3; ++ky) split_filter(ky);
+    for (int ky = 0; ky < 3; ++ky) split_filter(ky, 0);
     float* red = reinterpret_cast<float*>(lds);         // the tile is not there yet
     if constexpr (PRE == 1 || PRE == 2) {               // mean / invstd of the input
         if (pre.merge) {                                // mean = sum n mean_g / M, M2 = sum (M2_g + n (mean_g - mean)^2)
@@ -419,7 +429,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     //      (halo coordinates); it meets filter row ky in the tile t with TROWS t + ky = st.
     floatx4 acc[K::WM];
     {
-        constexpr int ST = 3 * K::TROWS + 3;
+        constexpr int NT = K::NT, LAST = (NT - 1) * K::TROWS, ST = LAST + 3;
         const Role r = role_of(tid);
         int at_px = (r.row0 * K::TW + r.col) * K::PITCH + (C == 16 ? 8 : 16) * r.q + 64 * r.ks;
         const char* base = Xs + at_px;
@@ -427,28 +437,28 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         const char* again = Xs + at_px;
         // Two accumulators: the leading products, and the small ones (2^-8 and less of them), so that most of the roundings are
         // those of the small sum.
-        floatx4 a[4], lo[4];
+        floatx4 a[NT], lo[NT];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) a[t] = lo[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < NT; ++t) a[t] = lo[t] = floatx4{0.f, 0.f, 0.f, 0.f};
         split::Pix<C> x[2];
         auto pixels = [&](int i) { return split::pixel_operand<C, K::PLANE>(base + (i % ST * K::TW + i / ST) * K::PITCH, again + (i % ST * K::TW + i / ST) * K::PITCH); };
         x[0] = pixels(0);
 #pragma unroll
         for (int i = 0; i < 3 * ST; ++i) {
             const int st = i % ST, kx = i / ST;
-            // filter row ky meets its last pixel operand of a column at st = 3 TROWS + ky: there the next column's is fetched one
+            // filter row ky meets its last pixel operand of a column at st = LAST + ky: there the next column's is fetched one
             // step before and split one step after
 #pragma unroll
             for (int ky = 0; ky < 3; ++ky) {
-                if (i % ST == (3 * K::TROWS + ky + 1) % ST && kx + (ky < 2) >= 1 && kx + (ky < 2) <= 2) split_filter(ky);
-                if (st == 3 * K::TROWS + ky - 1 && kx < 2) load_filter(ky, kx + 1);
+                if (i % ST == (LAST + ky + 1) % ST && kx + (ky < 2) >= 1 && kx + (ky < 2) <= 2) split_filter(ky, kx + (ky < 2));
+                if (K::COLUMNS == 1 && st == LAST + ky - 1 && kx < 2) load_filter(ky, kx + 1);
             }
             if (i + 1 < 3 * ST) x[(i + 1) & 1] = pixels(i + 1);
             __builtin_amdgcn_sched_barrier(0);      // or the compiler moves the reads down to their use, behind the products
 #pragma unroll
             for (int p = 0; p < split::products<C>(); ++p)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
+                for (int t = 0; t < NT; ++t) {
                     const int ky = st - K::TROWS * t;
                     if (ky < 0 || ky > 2) continue;
                     floatx4& to = p + 1 < split::products<C>() ? lo[t] : a[t];
@@ -458,30 +468,30 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         }
         mma::drain();
 #pragma unroll
-        for (int t = 0; t < 4; ++t) a[t] += lo[t];
+        for (int t = 0; t < NT; ++t) a[t] += lo[t];
         if constexpr (K::KS == 1) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[t] = a[t];
+            for (int t = 0; t < NT; ++t) acc[t] = a[t];
         } else {
             // the two wavefronts of a group of pixels hold partial sums over their halves of the input channels: each
             // hands the other the two tiles it will not finish and adds what it receives (first half + second half)
             const int ks = r.ks, lane = r.lane, wave = r.wave;
             __syncthreads();                               // every wavefront has read the tile for the last time
-            float* Ex = reinterpret_cast<float*>(lds);             // [wavefront][2][64][4]
+            float* Ex = reinterpret_cast<float*>(lds);             // [wavefront][WM][64][4]
 #pragma unroll
-            for (int wm = 0; wm < 2; ++wm)
+            for (int wm = 0; wm < K::WM; ++wm)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const float give = ks == 0 ? a[2 + wm][v] : a[wm][v];
-                    acc[wm][v] = ks == 0 ? a[wm][v] : a[2 + wm][v];
-                    Ex[((wave * 2 + wm) * 64 + lane) * 4 + v] = give;
+                    const float give = ks == 0 ? a[K::WM + wm][v] : a[wm][v];
+                    acc[wm][v] = ks == 0 ? a[wm][v] : a[K::WM + wm][v];
+                    Ex[((wave * K::WM + wm) * 64 + lane) * 4 + v] = give;
                 }
             __syncthreads();
             const int partner = (r.wave_m ^ 1) * K::WAVES_N + r.wave_n;
 #pragma unroll
-            for (int wm = 0; wm < 2; ++wm)
+            for (int wm = 0; wm < K::WM; ++wm)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[wm][v] += Ex[((partner * 2 + wm) * 64 + lane) * 4 + v];
+                for (int v = 0; v < 4; ++v) acc[wm][v] += Ex[((partner * K::WM + wm) * 64 + lane) * 4 + v];
         }
     }
 

@@ -1,73 +1,11 @@
 // The 3x3 kernels of conv3x3.hpp with eight wavefronts to a workgroup: 16 rows of a 32x32 image with 16 channels, a whole 16x16 image
 // with 32, a whole 8x8 image with all 64 output channels.  Against four wavefronts: no (or half the) halo rows, the last stage's input
 // loaded and split once and not per half of the output channels, half the partial filter gradients, half the records.
-#include "conv3x3.hpp"
+#include "conv3x3_forms.hpp"
 #include "../../include/dssp_kernels.h"
 
 namespace {
-
-constexpr int WAVES = 8;
-
-bool covers(int H, int C) { return (C == 16 && H == 32) || (C == 32 && H == 16) || (C == 64 && H == 8); }
-
-bool merges(int parts, int C) {
-    return parts >= 1 && parts <= (C == 16 ? inline_records<16, WAVES>() : C == 32 ? inline_records<32, WAVES>() : inline_records<64, WAVES>());
-}
-
-template <int PRE>
-int forward(hipStream_t s, const float* src, const float* w, float* dst, float* records_out, int N, int C, const PreBn& pre) {
-    if (C == 16) return launch<16, 32, 16, 1, WAVES, false, PRE>(s, src, w, nullptr, dst, records_out, N, pre);
-    if (C == 32) return launch<32, 16, 16, 1, WAVES, false, PRE>(s, src, w, nullptr, dst, records_out, N, pre);
-    return launch<64, 8, 8, 1, WAVES, false, PRE>(s, src, w, nullptr, dst, records_out, N, pre);
-}
-
+struct Large { static constexpr int WAVES = 8, TILES = 4, R16 = 16, R32 = 16, SPLIT64 = 1, IMAGES = DSSPK_CONV3X3_LARGE_MAX; };
 }  // namespace
 
-extern "C" int dsspk_conv3x3_large_parts(int N, int H, int C) { return N < 1 || N > DSSPK_CONV3X3_LARGE_MAX || !covers(H, C) ? 0 : C == 16 ? 2 * N : N; }
-
-extern "C" int dsspk_conv3x3_large_fwd(void* stream, const float* src, const float* records, int parts, const float* gamma, const float* beta,
-                                       float eps, const float* shortcut, float* act_out, float* stats_out, const float* w, float* dst,
-                                       float* records_out, int shortcut_half, int N, int H, int C) {
-    if (!src || !w || !dst || !records_out || dst == src || dsspk_conv3x3_large_parts(N, H, C) == 0) return -1;
-    if (shortcut_half && (!shortcut || C <= 16)) return -1;
-    PreBn pre{};
-    pre.half = shortcut_half != 0;
-    if (!records) {
-        if (parts || shortcut) return -1;
-        return forward<0>((hipStream_t)stream, src, w, dst, records_out, N, C, pre);
-    }
-    const long M = (long)N * H * H;
-    if (!gamma || !beta || !act_out || !stats_out || act_out == src || act_out == dst || records == records_out || !merges(parts, C) || M % parts) return -1;
-    pre.records = records;
-    pre.M = M;
-    pre.L.G = parts;
-    pre.L.rows_per_block = M / parts;
-    pre.gamma = gamma; pre.beta = beta; pre.eps = eps;
-    pre.shortcut = shortcut; pre.act_out = act_out; pre.stats_out = stats_out;
-    pre.merge = true;
-    return shortcut ? forward<2>((hipStream_t)stream, src, w, dst, records_out, N, C, pre)
-                    : forward<1>((hipStream_t)stream, src, w, dst, records_out, N, C, pre);
-}
-
-extern "C" int dsspk_conv3x3_large_bwd(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,
-                                       const float* in_records, int parts, float* dgamma, float* dbeta, float* dx, float* partial,
-                                       const float* w, const float* add, float* out, const float* x_in, const float* xc_post,
-                                       const float* stats_post, float* records, const float* red_partial, float* red_dw, int red_E,
-                                       int red_chunks, int N, int H, int C) {
-    if (!dz || !xc || !stats || !gamma || !in_records || !dgamma || !dbeta || !w || !out || !x_in || !xc_post || !stats_post || !records) return -1;
-    if (dsspk_conv3x3_large_parts(N, H, C) == 0 || !merges(parts, C) || in_records == records || out == dz) return -1;
-    if (C == 64 ? !dx || partial || dx == dz || dx == out : dx || !partial || partial == red_partial) return -1;
-    if (red_partial && (!red_dw || red_E < 4 || red_E % 4 || red_chunks < 1)) return -1;
-    BwdBn bwd;
-    bwd.xc = xc; bwd.stats = stats; bwd.gamma = gamma; bwd.totals = nullptr; bwd.records = in_records; bwd.parts = parts;
-    bwd.dgamma = dgamma; bwd.dbeta = dbeta; bwd.inv_m = 1.0f / (float)((long)N * H * H); bwd.dx_out = dx;
-    PostBn post;
-    post.mask_src = x_in; post.xc = xc_post; post.stats = stats_post; post.records = records;
-    const jobs::ReduceJob rj = reduce_job(red_partial, red_dw, red_E, red_chunks, 64 * WAVES);
-    WgradFused wg;
-    wg.x_in = x_in; wg.partial = partial;
-    hipStream_t s = (hipStream_t)stream;
-    if (C == 16) return launch<16, 32, 16, 1, WAVES, true, 3, true, true>(s, dz, w, add, out, nullptr, N, PreBn{}, post, bwd, rj, wg);
-    if (C == 32) return launch<32, 16, 16, 1, WAVES, true, 3, true, true>(s, dz, w, add, out, nullptr, N, PreBn{}, post, bwd, rj, wg);
-    return launch<64, 8, 8, 1, WAVES, true, 3, true>(s, dz, w, add, out, nullptr, N, PreBn{}, post, bwd, rj);
-}
+DSSPK_CONV3X3_FORM(large, Large)

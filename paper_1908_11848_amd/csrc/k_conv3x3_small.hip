@@ -1,0 +1,14 @@
+// The 3x3 kernels of conv3x3.hpp with four wavefronts of two pixel tiles each: 4 rows of a 32x32 image with 16 channels, 4 rows of a
+// 16x16 image with 32, a quarter of the output channels of an 8x8 image with 64.  For batches whose launches leave most compute units idle: a
+// launch lasts as long as one workgroup, and these have half the loads, products and stores of the kernels of k_conv3x3.hip.
+// Bound by latency: of 6.5 to 13 us a launch 4.5 are what a launch of a graph costs at least.  A push of the 20-layer network, one worker, with
+// the kernels of k_conv3x3.hip / these, us: batch 1 488 / 454, 8 512 / 484, 16 543 / 499; four workers, a round: 901 / 853, 954 / 912,
+// 1005 / 939.  At most 16 images: above, the 64-row records of the stem (16 an image) are more than a workgroup adds up.
+#include "conv3x3_forms.hpp"
+#include "../../include/dssp_kernels.h"
+
+namespace {
+struct Small { static constexpr int WAVES = 4, TILES = 2, R16 = 4, R32 = 4, SPLIT64 = 4, IMAGES = DSSPK_CONV3X3_SMALL_MAX; };
+}  // namespace
+
+DSSPK_CONV3X3_FORM(small, Small)

@@ -88,6 +88,7 @@ struct Plan {
         auto wg_need = [&](int N, int H, int Cin, int Cout, int k, int s, int p) {
             const size_t f = dsspk_conv_wgrad_scratch_floats(N, H, H, Cin, Cout, k, k, s, p);
             if (f > wg) wg = f;
+            if (k == 3 && s == 1 && Cin == Cout) wg = std::max(wg, (size_t)dsspk_conv3x3_small_parts(N, H, Cin) * 9 * Cin * Cout);
         };
         // wide stride-1 layer (dsspk_conv_split_*): room for its filter planes and the partial sums of its d-filter pass
         auto wide_conv = [&](WideConv& c, int H, int k, int p) {
@@ -299,19 +300,26 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     // add up (173 launches of a 110-layer step less).  Below, their number leaves compute units idle.  A round of the 20-layer network
     // with the smaller / larger ones: batch 64, one worker 741 / 762 us, four 1105 / 1136; batch 128, one 850 / 827, four 1575 / 1568; a push of
     // the 110-layer network, batch 128, one worker 3962 / 3881 us, four 1858 / 1815, eight of different speed 1877 / 1832.
-    const bool large = m > LARGE_ABOVE && m <= DSSPK_CONV3X3_LARGE_MAX;
+    // Up to DSSPK_CONV3X3_SMALL_MAX images the smaller workgroups of dsspk_conv3x3_small_* (k_conv3x3_small.hip: 5 to 8 % of a step).
+    const bool large = m > LARGE_ABOVE && m <= DSSPK_CONV3X3_LARGE_MAX, small = m <= DSSPK_CONV3X3_SMALL_MAX;
     auto parts_of = [&](int H, int cin, int cout, int stride) {       // records that the forward convolution leaves
         if (cin != cout || stride != 1) return dsspk_conv_fwd_records_parts(m, H, H, cin, cout, 3, 3, stride, 1);
-        return large ? dsspk_conv3x3_large_parts(m, H, cin) : dsspk_conv_fwd_stat_parts(m, H, H, cin, cout, 3, 3, stride, 1);
+        return large   ? dsspk_conv3x3_large_parts(m, H, cin)
+               : small ? dsspk_conv3x3_small_parts(m, H, cin)
+                       : dsspk_conv_fwd_stat_parts(m, H, H, cin, cout, 3, 3, stride, 1);
     };
     auto conv = [&](const float* src, const float* wt, float* dst, int H, int cin, int cout, int stride, float* rec) {
         if (rec && (cin != cout || stride != 1)) return dsspk_conv_fwd_records(s, src, wt, dst, rec, m, H, H, cin, cout, 3, 3, stride, 1);
-        if (large && rec) return dsspk_conv3x3_large_fwd(s, src, nullptr, 0, nullptr, nullptr, 0.f, nullptr, nullptr, nullptr, wt, dst, rec, 0, m, H, cin);
+        if ((large || small) && rec)
+            return (large ? dsspk_conv3x3_large_fwd : dsspk_conv3x3_small_fwd)(s, src, nullptr, 0, nullptr, nullptr, 0.f, nullptr, nullptr, nullptr, wt,
+                                                                              dst, rec, 0, m, H, cin);
         return dsspk_conv_fwd(s, src, wt, nullptr, dst, m, H, H, cin, cout, 3, 3, stride, 1, 0, rec);
     };
     auto conv_prebn = [&](const float* src, const float* rec, int parts, const float* gamma, const float* beta, const float* shortcut, float* act,
                           float* stats, const float* wt, float* dst, float* rec_out, int H, int C, bool half = false) {
-        if (large) return dsspk_conv3x3_large_fwd(s, src, rec, parts, gamma, beta, eps, shortcut, act, stats, wt, dst, rec_out, half, m, H, C);
+        if (large || small)
+            return (large ? dsspk_conv3x3_large_fwd : dsspk_conv3x3_small_fwd)(s, src, rec, parts, gamma, beta, eps, shortcut, act, stats, wt, dst,
+                                                                              rec_out, half, m, H, C);
         return (half ? dsspk_conv_fwd_prebn_half : dsspk_conv_fwd_prebn)(s, src, rec, parts, gamma, beta, eps, shortcut, act, stats, wt, dst, rec_out,
                                                                         m, H, C);
     };
@@ -427,11 +435,11 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         float* rdw = carry ? pend.dw[0] : nullptr;
         const int rE = carry ? pend.E[0] : 0, rchunks = carry ? pend.chunks[0] : 0;
         if (carry) pop_front();
-        if (large) {
+        if (large || small) {
             int chunks = parts_of(H, Cc, Cc, 1);
-            RUN(dsspk_conv3x3_large_bwd(s, dz, xc, st, gamma, in_rec, in_parts, in_dgamma, in_dbeta, Cc == 64 ? g1 : nullptr,
-                                        Cc == 64 ? nullptr : out_scr, wt, add, out, x_in, xc_post, st_post, records, rp, rdw, rE, rchunks,
-                                        m, H, Cc));
+            const auto bwd = large ? dsspk_conv3x3_large_bwd : dsspk_conv3x3_small_bwd;
+            RUN(bwd(s, dz, xc, st, gamma, in_rec, in_parts, in_dgamma, in_dbeta, Cc == 64 ? g1 : nullptr, Cc == 64 ? nullptr : out_scr, wt, add, out,
+                    x_in, xc_post, st_post, records, rp, rdw, rE, rchunks, m, H, Cc));
             if (Cc == 64) RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, nullptr, 0, 0, nullptr, nullptr, nullptr, &chunks));
             push_back(out_scr, dw, 9 * Cc * Cc, chunks);
             return 0;

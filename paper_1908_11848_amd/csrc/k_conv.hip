@@ -764,16 +764,31 @@ template <bool DGRAD, bool VEC>
 int launch_igemm(hipStream_t s, const float* src, const float* w, const float* bias, const float* add, float* dst, const ConvGeom& g, int relu,
                  float* extra = nullptr) {
     // output-channel tile: the widest of 64, 32, 16 that divides the layer
-    const int bn = g.OC % 64 == 0 ? 64 : g.OC % 32 == 0 ? 32 : g.OC % 16 == 0 ? 16 : 0;
+    int bn = g.OC % 64 == 0 ? 64 : g.OC % 32 == 0 ? 32 : g.OC % 16 == 0 ? 16 : 0;
     if (!bn) return -1;
     const bool small = igemm_small(g);
     // d-input of a stride-2 layer on an even pixel grid: four parity classes of rows, each with its own tiles
     const bool parity = DGRAD && VEC && g.stride == 2 && g.OH % 2 == 0 && g.OW % 2 == 0;
     if (DGRAD && extra && !parity) return -1;
-    dim3 grid(parity ? 4 * ceil_div(g.M / 4, small ? 64 : 128) : ceil_div(g.M, small ? 64 : 128), g.OC / bn);
+    const int row_tiles = parity ? 4 * ceil_div(g.M / 4, small ? 64 : 128) : ceil_div(g.M, small ? 64 : 128);
+    // ... or a narrower one where that leaves half the chip idle: the launch then lasts as long as one workgroup, whose products are half as
+    // many, with more k-chunks to a stage (64 -> 32 channels d-input at batch 8: 16 chunks with a barrier each, now 4).  A push of the 20-layer
+    // network, wide / narrow, us: batch 1 454 / 440, 8 484 / 469, 16 499 / 485.
+    bool narrow = false;
+    if constexpr (VEC)
+        for (; small && bn > 16 && row_tiles * (g.OC / bn) < 128; bn /= 2) narrow = true;
+    dim3 grid(row_tiles, g.OC / bn);
 #define GO(BM, BN) do { if (igemm_launch<BM, BN, DGRAD, VEC, 1>(grid, s, src, w, bias, add, dst, g, relu, parity, extra)) return -1; } while (0)
 #define GOK(BM, BN, KS) do { if (igemm_launch<BM, BN, DGRAD, VEC, KS>(grid, s, src, w, bias, add, dst, g, relu, parity, extra)) return -1; } while (0)
     if constexpr (VEC) {
+        if (narrow && g.IC % 64 == 0) {
+            if (bn == 16) GOK(64, 16, 4); else GOK(64, 32, 4);
+            return DSSPK_LAUNCH_RC();
+        }
+        if (narrow && g.IC % 32 == 0) {
+            if (bn == 16) GOK(64, 16, 2); else GOK(64, 32, 2);
+            return DSSPK_LAUNCH_RC();
+        }
         if (bn == 64 && g.IC % 64 == 0 && small) {      // wide layers: several k-chunks per stage
             GOK(64, 64, 4);
             return DSSPK_LAUNCH_RC();

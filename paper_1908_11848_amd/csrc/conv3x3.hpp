@@ -58,6 +58,9 @@ struct Cfg {
     // Two tiles: the products of a filter column are too few to hide the fetch of the next one, and registers are not what counts
     // where the tiles are that small: all three columns are fetched up front.
     static constexpr int COLUMNS = NT == 4 ? 1 : 3;
+    // ... and so is everything else the workgroup reads: one latency instead of three or four in a row.  A push of the 20-layer network, one
+    // worker, without / with it, us: batch 1 440 / 434, 8 470 / 466, 16 485 / 481; four workers, a round: 830 / 820, 895 / 881, 920 / 900.
+    static constexpr bool EARLY = NT == 2;
     static constexpr int SC = WAVES_M * CN;        // floats: per-wavefront column sums (batch-norm records, one component)
     static constexpr int SS = 2 * SC;
     static constexpr int PS = 5 * C;               // floats: per-channel vectors of the loader
@@ -146,8 +149,9 @@ struct WgradFused {
 // dst must differ from src, whose halo rows other workgroups still read.
 // Wavefronts per SIMD the register allocation aims at: with eight wavefronts to a workgroup two of them per compute unit need four; with four
 // to a workgroup the fourth brought nothing (110 layers, batch 128, four streams: 1.858 ms a push with three, 1.875 with four).
-template <int C, int WAVES, bool WG>
-constexpr int min_waves() { return WAVES == 8 || (C == 16 && !WG) ? 4 : 3; }
+// Two pixel tiles to a wavefront: no second workgroup waits for room on the compute unit.
+template <int C, int WAVES, bool WG, int NT>
+constexpr int min_waves() { return NT == 2 ? 2 : WAVES == 8 || (C == 16 && !WG) ? 4 : 3; }
 
 // Sum over the 16 lanes of a quarter wavefront, in all of them.
 __device__ __forceinline__ float sum16(float v) {
@@ -186,7 +190,7 @@ __device__ __forceinline__ float channel_sum(float s, float* red, int tid) {
 }
 
 template <int C, int HW, int R, int NSPLIT, int WAVES, bool TRANSPOSED, int PRE, bool POST = false, bool WG = false>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_waves<C, WAVES, WG>()))) void conv3x3_kernel(
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_waves<C, WAVES, WG, Cfg<C, HW, R, NSPLIT, WAVES>::NT>()))) void conv3x3_kernel(
     const float* __restrict__ src, const float* __restrict__ wgt, const float* add, float* dst, float* __restrict__ bn_partial, PreBn pre,
     PostBn post, BwdBn bwd, int conv_blocks, jobs::ReduceJob rj, WgradFused wg) {
     using K = Cfg<C, HW, R, NSPLIT, WAVES>;
@@ -257,6 +261,15 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         for (int e = 0; e < FV; ++e) f[e] = split::scaled(f[e]);
         filt[ky] = split::filter_operand<C>(f);
     };
+    // EARLY: what the loader needs of the batch norm (PRE 1, 2: of this thread's channels; 3: of channel tid)
+    float4 norm_g = make_float4(0.f, 0.f, 0.f, 0.f), norm_b = norm_g;
+    float norm_mean = 0.f, norm_is = 0.f, norm_gamma = 0.f;
+    if constexpr (K::EARLY && (PRE == 1 || PRE == 2)) {
+        norm_g = *reinterpret_cast<const float4*>(pre.gamma + tid % V * 4);
+        norm_b = *reinterpret_cast<const float4*>(pre.beta + tid % V * 4);
+    }
+    if constexpr (K::EARLY && PRE == 3)
+        if (tid < C) { norm_mean = bwd.stats[tid]; norm_is = bwd.stats[C + tid]; norm_gamma = bwd.gamma[tid]; }
     float2 rec[PRE ? K::RECORDS : 1];
     if constexpr (PRE == 1 || PRE == 2)
         if (pre.merge) load_records<C, THREADS>(rec, pre.records, pre.L.G, tid);
@@ -301,6 +314,41 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             if constexpr (PRE == 3) scv[e] = load4(bwd.xc + tile_at + e * STEP, 4u * tid);
         }
     }
+    // what the epilogue adds, masks with and sums over, a lane's four channels of its pixel of every tile: all these loads together (dst may
+    // alias add, so the compiler cannot move them across the stores itself)
+    float4 mu_c = make_float4(0.f, 0.f, 0.f, 0.f), is_c = mu_c, addv[K::WM], maskv[POST ? K::WM : 1], xcv[POST ? K::WM : 1];
+    constexpr int OUT_STEP = K::TROWS * HW * C;                                             // from tile to tile
+    auto out_at_of = [&](const Role& r) -> unsigned {                                       // from the band's first pixel, first tile
+        return ((r.row0 + K::TROWS * r.ks * K::WM) * HW + r.col) * C + r.co_w + 4 * r.q;
+    };
+    auto epilogue_loads = [&](const Role& r) {
+        const unsigned at = out_at_of(r);
+        if constexpr (POST) {
+            mu_c = *reinterpret_cast<const float4*>(post.stats + r.co_w + 4 * r.q);
+            is_c = *reinterpret_cast<const float4*>(post.stats + C + r.co_w + 4 * r.q);
+        }
+#pragma unroll
+        for (int wm = 0; wm < K::WM; ++wm) {
+            addv[wm] = add ? load4(add + band_at + wm * OUT_STEP, at) : make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (POST) {
+                maskv[wm] = load4(post.mask_src + band_at + wm * OUT_STEP, at);
+                xcv[wm] = load4(post.xc + band_at + wm * OUT_STEP, at);
+            }
+        }
+    };
+    // x halo tile of the fused d-filter: on its way during the epilogue
+    float4 xin[WG ? NL : 1];
+    auto load_x_tile = [&]() {
+#pragma unroll
+        for (int e = 0; e < NL; ++e) {
+            xin[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (inside(e)) xin[e] = load4(wg.x_in + tile_at + e * STEP, 4u * tid);
+        }
+    };
+    if constexpr (K::EARLY) {
+        epilogue_loads(role_of(tid));
+        if constexpr (WG) load_x_tile();
+    }
 #pragma unroll
     for (int ky = 0; ky < 3; ++ky) split_filter(ky, 0);
     float* red = reinterpret_cast<float*>(lds);         // the tile is not there yet
@@ -339,10 +387,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             sum_g = bwd.totals[C + tid];
         }
         if (tid < C) {
-            const float is = bwd.stats[C + tid];
-            Sh[tid] = bwd.stats[tid];
+            const float is = K::EARLY ? norm_is : bwd.stats[C + tid];
+            Sh[tid] = K::EARLY ? norm_mean : bwd.stats[tid];
             Sh[C + tid] = is;
-            Sh[2 * C + tid] = bwd.gamma[tid] * is;
+            Sh[2 * C + tid] = (K::EARLY ? norm_gamma : bwd.gamma[tid]) * is;
             Sh[3 * C + tid] = sum_b * bwd.inv_m;
             Sh[4 * C + tid] = sum_g * bwd.inv_m;
             if (!bwd.totals && blockIdx.x == 0) { bwd.dbeta[tid] = sum_b; bwd.dgamma[tid] = sum_g; }
@@ -356,7 +404,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(to + p * K::PLANE) = pl[p];
     };
     // what the convolution runs on, four channels of a pixel of src (and of the shortcut or xc)
-    auto transformed = [&](float4 o, float4 sc, int c) {
+    auto transformed = [&](float4 o, float4 sc, int c, bool own_channels) {
         if constexpr (PRE == 3) {
             const float4 mu = *reinterpret_cast<const float4*>(Sh + c);
             const float4 is = *reinterpret_cast<const float4*>(Sh + C + c);
@@ -371,8 +419,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         if constexpr (PRE == 1 || PRE == 2) {
             const float4 mu = *reinterpret_cast<const float4*>(Sh + c);
             const float4 is = *reinterpret_cast<const float4*>(Sh + C + c);
-            const float4 ga = *reinterpret_cast<const float4*>(pre.gamma + c);
-            const float4 be = *reinterpret_cast<const float4*>(pre.beta + c);
+            const float4 ga = K::EARLY && own_channels ? norm_g : *reinterpret_cast<const float4*>(pre.gamma + c);
+            const float4 be = K::EARLY && own_channels ? norm_b : *reinterpret_cast<const float4*>(pre.beta + c);
             o.x = fmaf((o.x - mu.x) * is.x, ga.x, be.x);
             o.y = fmaf((o.y - mu.y) * is.y, ga.y, be.y);
             o.z = fmaf((o.z - mu.z) * is.z, ga.z, be.z);
@@ -391,7 +439,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             else if (c < C / 2) sc = *reinterpret_cast<const float4*>(pre.shortcut + 2 * image_at + (2 * h * HW + w) * C + c);
         }
         if constexpr (PRE == 3) sc = *reinterpret_cast<const float4*>(bwd.xc + off);
-        return transformed(*reinterpret_cast<const float4*>(src + off), sc, c);
+        return transformed(*reinterpret_cast<const float4*>(src + off), sc, c, false);
     };
     for (int i = tid; i < K::ZERO; i += THREADS) {          // outside the image: left and right, for a whole image above and below
         const int px = i / K::ZERO_UNITS, unit = i % K::ZERO_UNITS;
@@ -406,7 +454,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         if (!own(e)) continue;
         if constexpr (PRE != 0) {
             if (inside(e)) {
-                val[e] = transformed(val[e], scv[PRE >= 2 ? e : 0], c4);
+                val[e] = transformed(val[e], scv[PRE >= 2 ? e : 0], c4, true);
                 // the band's own rows (not the halo rows) are this workgroup's part of `a` or dx
                 if (!WG && part == 0 && (K::WHOLE || (pr0 + e * RE >= 1 && pr0 + e * RE <= R)))
                     *reinterpret_cast<float4*>((PRE == 3 ? bwd.dx_out : pre.act_out) + tile_at + e * STEP + 4u * tid) = val[e];
@@ -414,15 +462,6 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         }
         stage(tile_to + e * STEP_TO, val[e]);
     }
-    // x halo tile of the fused d-filter: on its way during the epilogue
-    float4 xin[WG ? NL : 1];
-    auto load_x_tile = [&]() {
-#pragma unroll
-        for (int e = 0; e < NL; ++e) {
-            xin[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (inside(e)) xin[e] = load4(wg.x_in + tile_at + e * STEP, 4u * tid);
-        }
-    };
     __syncthreads();
 
     // ---- products.  Pixel operand (st, kx): the tile that starts st rows below the wavefront's first one, kx to the right
@@ -532,27 +571,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
 
     // ---- store: a lane holds channels co .. co + 3 of its pixel of every tile
     const int co = co_w + 4 * q;
-    float4 mu_c = make_float4(0.f, 0.f, 0.f, 0.f), is_c = mu_c;
-    const unsigned out_at = ((row0 + K::TROWS * ks * K::WM) * HW + col) * C + co;          // from the band's first pixel, first tile
-    constexpr int OUT_STEP = K::TROWS * HW * C;                                             // from tile to tile
-    // all loads of the epilogue together (dst may alias add, so the compiler cannot move them across the stores itself)
-    float4 addv[K::WM], maskv[POST ? K::WM : 1], xcv[POST ? K::WM : 1];
-    auto epilogue_loads = [&]() {
-        if constexpr (POST) {
-            mu_c = *reinterpret_cast<const float4*>(post.stats + co);
-            is_c = *reinterpret_cast<const float4*>(post.stats + C + co);
-        }
-#pragma unroll
-        for (int wm = 0; wm < K::WM; ++wm) {
-            addv[wm] = add ? load4(add + band_at + wm * OUT_STEP, out_at) : make_float4(0.f, 0.f, 0.f, 0.f);
-            if constexpr (POST) {
-                maskv[wm] = load4(post.mask_src + band_at + wm * OUT_STEP, out_at);
-                xcv[wm] = load4(post.xc + band_at + wm * OUT_STEP, out_at);
-            }
-        }
-    };
-    epilogue_loads();
-    if constexpr (WG) load_x_tile();
+    const unsigned out_at = out_at_of(role);
+    if constexpr (!K::EARLY) {
+        epilogue_loads(role);
+        if constexpr (WG) load_x_tile();
+    }
     float4 sum_dz = make_float4(0.f, 0.f, 0.f, 0.f), sum_dzx = sum_dz;
 #pragma unroll
     for (int wm = 0; wm < K::WM; ++wm) {

@@ -1,6 +1,8 @@
 // Stride-1 convolutions of wide layers (channels multiples of 64, 3x3 or 5x5
 // filters) with fp32 arithmetic on the bf16 matrix cores (split.hpp): forward, gradient w.r.t. the input (the same kernel on
 // a transposed, reversed filter) and gradient w.r.t. the filter and bias.
+#include <algorithm>
+
 #include "jobs.hpp"
 #include "mma.hpp"
 #include "split.hpp"
@@ -81,7 +83,7 @@ __global__ __launch_bounds__(THREADS) void filter_planes_kernel(Frag fwd, Frag b
 // tile), and the two halves of a sum meet in LDS at the end.  The smaller tiles gain nothing from that: several of their
 // workgroups share a compute unit, and with more than one stream eight wavefronts cost 4 % of a step at batch 37.
 // Bound by the matrix cores: 64 -> 64 at 5x5 on 15x15, batch 128, is 2.46 M MFMAs = 17 us of them at 2.4 GHz (the chip runs
-// them at 1.9).  Measured at batch 37 / 128 / 512: 20 / 34 / 135 us (largest tile with four wavefronts 12 % more).
+// them at 1.9).  Measured at batch 37 / 128: 18 / 31 us (largest tile with four wavefronts 12 % more).
 struct Geom {
     int N, H, W, OH, OW, pad;      // input / output pixel grid of this pass
     int IC, OC;                    // reduction / result channels of this pass
@@ -93,6 +95,50 @@ template <int MT> struct Waves { static constexpr int WP = MT >= 4 ? 2 : 1, WC =
 
 constexpr int ICB = 64;            // reduction channels staged at a time
 constexpr int pitch(int channels) { return channels * 2 * split::PLANES + 16; }      // bytes of a pixel in LDS: 4 words (mod 32) apart
+
+// One pixel's four result channels 16 ct + 4 q ..: bias, addend, ReLU.
+__device__ __forceinline__ void finish_pixel(const floatx4& sum, int ct, long at, const float* __restrict__ bias, const float* __restrict__ add,
+                                             float* __restrict__ dst, int relu) {
+    if (at < 0) return;
+    const int co = 16 * ct + 4 * ((threadIdx.x & 63) >> 4);
+    const float4 b = bias ? *reinterpret_cast<const float4*>(bias + co) : make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 v = make_float4(sum[0] + b.x, sum[1] + b.y, sum[2] + b.z, sum[3] + b.w);
+    if (add) {
+        const float4 a = *reinterpret_cast<const float4*>(add + at + co);
+        v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+    }
+    if (relu) { v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f); v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f); }
+    *reinterpret_cast<float4*>(dst + at + co) = v;
+}
+
+// Sums beyond the range of the scaled terms: a matrix-core tile (16 channels, this lane's pixel of image n, row h0, column c) from the
+// operands in memory.  A step takes 32 channels of a tap, a lane the eight of its filter fragment.
+template <int KS>
+__device__ __forceinline__ floatx4 direct_sum(const float* __restrict__ src, const uint4* __restrict__ wf, const Geom& g, int ct, int n, int h0,
+                                              int c, bool ok) {
+    const int lane = threadIdx.x & 63, q = lane >> 4, tiles_c = g.OC / 16, steps_c = g.IC / 32;
+    floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int tap = 0; tap < KS * KS; ++tap) {
+        const int h = h0 + tap / KS - g.pad, w = c + tap % KS - g.pad;
+        const bool in = ok && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
+        const float* px = src + (((long)n * g.H + h) * g.W + w) * g.IC + 8 * q;
+        for (int c32 = 0; c32 < steps_c; ++c32) {
+            float a[8], b[8];
+            unsigned u[split::PLANES][4];
+#pragma unroll
+            for (int k = 0; k < split::PLANES; ++k)
+                *reinterpret_cast<uint4*>(u[k]) = wf[((tap * steps_c + c32) * tiles_c + ct) * (split::PLANES * 64) + k * 64 + lane];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                a[j] = filter_value(u[0][j / 2] >> 16 * (j & 1) & 0xffffu, u[1][j / 2] >> 16 * (j & 1) & 0xffffu, u[2][j / 2] >> 16 * (j & 1) & 0xffffu);
+                b[j] = in ? px[32 * c32 + j] : 0.f;
+            }
+            sum = split::product32(a, b, sum);
+        }
+    }
+    mma::drain();
+    return sum;
+}
 
 template <int MT, int KS>
 __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_waves_per_eu(2))) void conv_split_kernel(const float* __restrict__ src, const uint4* __restrict__ wf,
@@ -207,46 +253,13 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
 #pragma unroll
             for (int t = 0; t < W::TP; ++t) acc[i][t] += small[i][t];
     }
-    auto finish = [&](const floatx4& sum, int ct, long at) {
-        if (at < 0) return;
-        const int co = 16 * ct + 4 * q;
-        const float4 b = bias ? *reinterpret_cast<const float4*>(bias + co) : make_float4(0.f, 0.f, 0.f, 0.f);
-        float4 v = make_float4(sum[0] + b.x, sum[1] + b.y, sum[2] + b.z, sum[3] + b.w);
-        if (add) {
-            const float4 a = *reinterpret_cast<const float4*>(add + at + co);
-            v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
-        }
-        if (relu) { v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f); v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f); }
-        *reinterpret_cast<float4*>(dst + at + co) = v;
-    };
-    // Sums beyond the range of the scaled terms: the tile from the operands in memory.  A step takes 32 channels of a tap, a lane the
-    // eight of its filter fragment.
     auto direct = [&](int ct, int t) {
         int p = (wp * W::TP + t) * 16 + l16;
         asm("" : "+v"(p));              // or the compiler keeps what it worked out above for every tile in registers through the product loop
         const int per = g.R * g.OW, gi = p / per, rest = p - gi * per, r = rest / g.OW, c = rest - r * g.OW;
         const bool ok = gi < g.G && n0 + gi < g.N && r0 + r < g.OH;
-        floatx4 sum = {0.f, 0.f, 0.f, 0.f};
-        for (int tap = 0; tap < KS * KS; ++tap) {
-            const int h = r0 + r + tap / KS - g.pad, w = c + tap % KS - g.pad;
-            const bool in = ok && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
-            const float* px = src + (((long)(n0 + gi) * g.H + h) * g.W + w) * g.IC + 8 * q;
-            for (int c32 = 0; c32 < steps_c; ++c32) {
-                float a[8], b[8];
-                unsigned u[split::PLANES][4];
-#pragma unroll
-                for (int k = 0; k < split::PLANES; ++k)
-                    *reinterpret_cast<uint4*>(u[k]) = wf[((tap * steps_c + c32) * tiles_c + ct) * (split::PLANES * 64) + k * 64 + lane];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    a[j] = filter_value(u[0][j / 2] >> 16 * (j & 1) & 0xffffu, u[1][j / 2] >> 16 * (j & 1) & 0xffffu, u[2][j / 2] >> 16 * (j & 1) & 0xffffu);
-                    b[j] = in ? px[32 * c32 + j] : 0.f;
-                }
-                sum = split::product32(a, b, sum);
-            }
-        }
-        mma::drain();
-        finish(sum, ct, ok ? (((long)(n0 + gi) * g.OH + r0 + r) * g.OW + c) * g.OC : -1);
+        finish_pixel(direct_sum<KS>(src, wf, g, ct, n0 + gi, r0 + r, c, ok), ct, ok ? (((long)(n0 + gi) * g.OH + r0 + r) * g.OW + c) * g.OC : -1, bias, add,
+                     dst, relu);
     };
     float bad = 0.f;
     if constexpr (W::HALVES == 1) {
@@ -262,7 +275,7 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
 #pragma unroll
         for (int i = 0; i < W::TC; ++i)
 #pragma unroll
-            for (int t = 0; t < W::TP; ++t) finish(acc[i][t] * split::UNSCALE, ct0 + i, out[t]);
+            for (int t = 0; t < W::TP; ++t) finish_pixel(acc[i][t] * split::UNSCALE, ct0 + i, out[t], bias, add, dst, relu);
     } else {        // the other half's share of the channel tile this wavefront finishes, against its own share of the other one
         static_assert(W::HALVES == 1 || W::TC == 2, "a channel tile each");
         __syncthreads();
@@ -285,12 +298,207 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
             return;
         }
 #pragma unroll
-        for (int t = 0; t < W::TP; ++t) finish(acc[0][t] * split::UNSCALE, ct0 + half, out[t]);
+        for (int t = 0; t < W::TP; ++t) finish_pixel(acc[0][t] * split::UNSCALE, ct0 + half, out[t], bias, add, dst, relu);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same with the largest tile for more tiles than compute units (walks_tiles): one workgroup of eight wavefronts to a compute
+// unit.  Wavefronts 0 .. 3 and 4 .. 7 take the filter taps in turn; the two halves of a sum meet in LDS at the end of a tile.  A workgroup
+// walks its tiles in blocks of 32 reduction channels; while one block is multiplied, the next one (of this tile or the next) is converted into
+// the other LDS buffer between the products, and the one after that is on its way into registers: nothing is staged in front of the
+// products but a workgroup's first block.  Bound by the matrix cores at two thirds of the rate they hold on such operands alone.  5x5, 64 -> 64 on
+// 15x15, one workgroup to a tile / this, us: batch 160 55.8 / 50.3, 256 60.0 / 57.5, 512 117.6 / 109.6.
+constexpr int LARGE_PX = 128, LTHREADS = 512, LARGE_LOADS = 4;
+constexpr int LPITCH = pitch(32), LARGE_HALO = LARGE_LOADS * LTHREADS / 8;      // bytes of a pixel, pixels of a tile with its halo at most
+
+template <int KS>
+__global__ __launch_bounds__(LTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void conv_split_large_kernel(const float* __restrict__ src, const uint4* __restrict__ wf,
+                                                             const float* __restrict__ bias, const float* __restrict__ add,
+                                                             float* __restrict__ dst, Geom g, int relu, int blocks, int per_group, int buffer_bytes) {
+    constexpr int TAPS = KS * KS, TP = 4, TC = 2, PLANE = 64;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, q = lane >> 4, half = wave >> 2, wp = wave & 1, wc = wave >> 1 & 1;
+    const int TH = g.R + KS - 1, TW = g.OW + KS - 1, per = g.R * g.OW;
+    const int ct0 = blockIdx.y * 4 + wc * TC;              // first 16-channel tile of this wavefront
+    const int tile0 = xcd_tile(blockIdx.x, gridDim.x) * per_group, tile1 = min(blocks, tile0 + per_group);
+    const int tiles_c = g.OC / 16, steps_c = g.IC / 32;
+
+    // where this lane's pixels' patches start in LDS (a pixel beyond the tile, the image or the batch takes what is there: not stored)
+    int base[TP];
+#pragma unroll
+    for (int t = 0; t < TP; ++t) {
+        const int p = (wp * TP + t) * 16 + l16, gi = p / per, rest = p - gi * per, r = rest / g.OW, c = rest - r * g.OW;
+        base[t] = (gi < g.G ? ((gi * TH + r) * TW + c) * LPITCH : 0) + 16 * q;
+    }
+    floatx4 acc[TC][TP];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < TC; ++i)
+#pragma unroll
+            for (int t = 0; t < TP; ++t) acc[i][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    };
+
+    // The thread's staged elements.  Rows above or below a single image fall outside its buffer, as do images past the last.
+    float4 rv[LARGE_LOADS];
+    unsigned off[LARGE_LOADS];
+#pragma unroll
+    for (int e = 0; e < LARGE_LOADS; ++e) {
+        const int idx = tid + e * LTHREADS, px = idx >> 3, c4 = idx & 7;
+        const int gi = px / (TH * TW), rest = px - gi * (TH * TW), ty = rest / TW, tx = rest - ty * TW, h = ty - g.pad, w = tx - g.pad;
+        const bool in = gi < g.G && (unsigned)w < (unsigned)g.W && (g.G == 1 || (unsigned)h < (unsigned)g.H);
+        off[e] = in ? 4u * (unsigned)(((gi * g.H + h) * g.W + w) * g.IC + 4 * c4) : split::OUTSIDE;
+    }
+    const int staged = (g.G * TH * TW * 8 + 63) / 64;      // wavefronts' worth of elements
+    int ft = tile0, fc = 0;                                // tile and channel block of the next fetch
+    unsigned fo = 0;
+    split::Buffer images;
+    auto locate = [&]() {
+        const int n0 = ft / g.bands * g.G, r0 = ft % g.bands * g.R;
+        images = ft < tile1 ? split::buffer(src + (long)n0 * g.H * g.W * g.IC, 4u * (unsigned)(min(g.G, g.N - n0) * g.H * g.W * g.IC)) : split::buffer(src, 0);
+        fo = 4u * (unsigned)(r0 * g.W * g.IC + 32 * fc);
+    };
+    auto advance = [&]() {
+        if (++fc == steps_c) { fc = 0; ++ft; }
+        locate();
+    };
+    auto fetch = [&](int e) { if (wave + 8 * e < staged) rv[e] = split::load4(images, off[e] + fo); };
+    auto stage = [&](int e, char* buf) {
+        if (wave + 8 * e >= staged) return;
+        uint2 pl[split::PLANES];
+        split::split4(split::scaled(rv[e]), pl);
+        const int idx = tid + e * LTHREADS;
+        char* to = buf + (idx >> 3) * LPITCH + 8 * (idx & 7);
+#pragma unroll
+        for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(to + p * PLANE) = pl[p];
+    };
+
+    // Filter planes are fetched two steps before their use, also over the end of a block; pixel operands one step.
+    uint4 wv[2][TC][split::PLANES], pv[2][TP][split::PLANES];
+    int wtap = half, wblk = 0, wpar = half;
+    auto load_w = [&](int buf) {
+        const uint4* p = wf + ((wtap * steps_c + wblk) * tiles_c + ct0) * (split::PLANES * 64) + lane;
+#pragma unroll
+        for (int i = 0; i < TC; ++i)
+#pragma unroll
+            for (int k = 0; k < split::PLANES; ++k) wv[buf][i][k] = p[(i * split::PLANES + k) * 64];
+        wtap += 2;
+        if (wtap >= TAPS) {
+            wpar ^= 1;
+            wtap = wpar;
+            if (++wblk == steps_c) wblk = 0;
+        }
+    };
+    auto load_p = [&](int buf, int tap, const char* from) {
+        const int o = (tap / KS * TW + tap % KS) * LPITCH;
+#pragma unroll
+        for (int t = 0; t < TP; ++t)
+#pragma unroll
+            for (int k = 0; k < split::PLANES; ++k) pv[buf][t][k] = *reinterpret_cast<const uint4*>(from + base[t] + o + k * PLANE);
+    };
+    locate();
+#pragma unroll
+    for (int e = 0; e < LARGE_LOADS; ++e) fetch(e);
+    load_w(0);
+    load_w(1);
+    advance();
+#pragma unroll
+    for (int e = 0; e < LARGE_LOADS; ++e) stage(e, lds);
+#pragma unroll
+    for (int e = 0; e < LARGE_LOADS; ++e) fetch(e);
+    advance();
+    clear();
+    __syncthreads();
+    load_p(0, half, lds);
+
+    int parity = half, blk = 0, tile = tile0;              // this wavefront's first tap of the block
+    char *cur = lds, *nxt = lds + buffer_bytes;
+    while (tile < tile1) {
+        const int n = (TAPS + 1 - parity) / 2;
+        // step s works with pv[s mod 2], wv[s mod 2]; the last one reads the next block's first operands behind the barrier
+        auto step = [&](int buf, int s) {
+            if (s + 1 < n) {
+                load_p(buf ^ 1, parity + 2 * (s + 1), cur);
+            } else {
+                __syncthreads();
+                load_p(buf ^ 1, parity ^ 1, nxt);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            split::product(wv[buf], pv[buf], acc, acc);
+            __builtin_amdgcn_sched_barrier(0);
+            load_w(buf);
+        };
+        static_assert(TAPS / 2 >= LARGE_LOADS, "a staged element to a step");
+        int s = 0;
+#pragma unroll
+        for (; s < LARGE_LOADS - 1; ++s) {                 // (the compiler is free to mix these with the products)
+            stage(s, nxt);
+            if (s == LARGE_LOADS - 2) stage(s + 1, nxt);
+            step(s & 1, s);
+            fetch(s);
+            if (s == LARGE_LOADS - 2) fetch(s + 1);
+        }
+        advance();
+        static_assert(LARGE_LOADS % 2 == 0, "the loop goes on with the odd step");
+        step(1, s++);
+        for (; s + 1 < n; s += 2) { step(0, s); step(1, s + 1); }
+        if (s < n) {
+            step(0, s);
+#pragma unroll
+            for (int k = 0; k < split::PLANES; ++k) {
+#pragma unroll
+                for (int t = 0; t < TP; ++t) pv[0][t][k] = pv[1][t][k];
+#pragma unroll
+                for (int i = 0; i < TC; ++i) { const uint4 w = wv[0][i][k]; wv[0][i][k] = wv[1][i][k]; wv[1][i][k] = w; }
+            }
+        }
+        parity ^= 1;
+        if (++blk == steps_c) {
+            // the other half's share of the channel tile this wavefront finishes, against its own share of the other one, through the
+            // buffer that was just consumed
+            const int n0 = tile / g.bands * g.G, r0 = tile % g.bands * g.R;
+            floatx4* ex = reinterpret_cast<floatx4*>(cur);         // [wavefront][TP][64]
+#pragma unroll
+            for (int t = 0; t < TP; ++t) {
+                const floatx4 u = acc[0][t], v = acc[1][t];
+                ex[(wave * TP + t) * 64 + lane] = half ? u : v;
+                acc[0][t] = half ? v : u;
+            }
+            __syncthreads();
+            float bad = 0.f;
+#pragma unroll
+            for (int t = 0; t < TP; ++t) {
+                acc[0][t] += ex[((wave ^ 4) * TP + t) * 64 + lane];
+                bad = split::spoil(acc[0][t], bad);
+            }
+            __syncthreads();                                       // before the next block is staged there
+            const int ct = ct0 + half;
+            auto pixel = [&](int t, auto&& value) {
+                int p = (wp * TP + t) * 16 + l16;
+                asm("" : "+v"(p));      // or the compiler keeps what it works out here in registers through the product loop
+                const int gi = p / per, rest = p - gi * per, r = rest / g.OW, c = rest - r * g.OW;
+                const bool ok = gi < g.G && n0 + gi < g.N && r0 + r < g.OH;
+                finish_pixel(value(n0 + gi, r0 + r, c, ok), ct, ok ? (((long)(n0 + gi) * g.OH + r0 + r) * g.OW + c) * g.OC : -1, bias, add, dst, relu);
+            };
+            if (split::spoiled(bad)) {
+#pragma unroll 1
+                for (int t = 0; t < TP; ++t) pixel(t, [&](int n, int h, int c, bool ok) { return direct_sum<KS>(src, wf, g, ct, n, h, c, ok); });
+            } else {
+#pragma unroll
+                for (int t = 0; t < TP; ++t) pixel(t, [&](int, int, int, bool) { return acc[0][t] * split::UNSCALE; });
+            }
+            clear();
+            blk = 0;
+            ++tile;
+        }
+        char* t = cur; cur = nxt; nxt = t;
     }
 }
 
 // Tile of one launch: the number of 16-pixel tiles per workgroup, its rows and images.
 struct Tiling { int mt, R, G, bands, blocks; size_t lds; };
+constexpr int UNITS = 256;         // compute units, one workgroup of the largest tile each
 
 size_t tile_bytes(int G, int R, int OW, int ks) { return (size_t)G * (R + ks - 1) * (OW + ks - 1) * pitch(ICB); }
 
@@ -337,11 +545,37 @@ int launch_tile(hipStream_t s, const float* src, const uint4* wf, const float* b
     return DSSPK_LAUNCH_RC();
 }
 
+template <int KS>
+int launch_large(hipStream_t s, const float* src, const uint4* wf, const float* bias, const float* add, float* dst, const Geom& g, int relu,
+                 const Tiling& t) {
+    auto kern = conv_split_large_kernel<KS>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX) != hipSuccess) return -1;
+        attr_set = true;
+    }
+    // as many tiles to a workgroup as there would be rounds of workgroups
+    const int per = ceil_div(t.blocks, std::max(1, UNITS / (g.OC / 64)));
+    constexpr int BUFFER = LARGE_HALO * LPITCH;
+    static_assert(BUFFER >= 32 * 1024, "room for the exchange: four matrix-core tiles of every wavefront");
+    hipLaunchKernelGGL(kern, dim3(ceil_div(t.blocks, per), g.OC / 64), dim3(LTHREADS), 2 * BUFFER, s, src, wf, bias, add, dst, g, relu, t.blocks, per,
+                       BUFFER);
+    return DSSPK_LAUNCH_RC();
+}
+
+// More tiles of the largest kind than compute units: the kernel that stages a workgroup's next tile during the present one.  (One tile to a
+// workgroup has nothing to overlap and its barriers cost 1 to 10 %: 5x5 at batch 128 31.2 / 31.6 us, 3x3 at batch 512 15.4 / 16.9.)
+bool walks_tiles(const Tiling& t, const Geom& g, int ks) {
+    return t.mt == 8 && (long)t.blocks * (g.OC / 64) > UNITS && (long)t.G * (t.R + ks - 1) * (g.OW + ks - 1) <= LARGE_HALO;
+}
+
 int launch_conv(hipStream_t s, const float* src, const uint4* wf, const float* bias, const float* add, float* dst, Geom g, int ks, int relu) {
     Tiling t;
     if (!choose_tiling(t, g.N, g.OH, g.OW, g.OC, ks)) return -1;
     g.R = t.R; g.G = t.G; g.bands = t.bands;
 #define GO(MT) return ks == 5 ? launch_tile<MT, 5>(s, src, wf, bias, add, dst, g, relu, t) : launch_tile<MT, 3>(s, src, wf, bias, add, dst, g, relu, t)
+    if (walks_tiles(t, g, ks))
+        return ks == 5 ? launch_large<5>(s, src, wf, bias, add, dst, g, relu, t) : launch_large<3>(s, src, wf, bias, add, dst, g, relu, t);
     if (t.mt == 8) GO(8);
     if (t.mt == 4) GO(4);
     GO(2);

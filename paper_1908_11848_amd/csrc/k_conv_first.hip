@@ -99,14 +99,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) vo
     for (int r = 0; r < ROWS_F; ++r)
 #pragma unroll
         for (int h = 0; h < 2; ++h) hi[r][h] = lo[r][h] = floatx4{0.f, 0.f, 0.f, 0.f};
-    int at_px = l16 * TPITCH + 8 * q;
-    const char* base = T + at_px;
-    asm("" : "+v"(at_px));
-    const char* again = T + at_px;
+    const char* base = T + l16 * TPITCH + 8 * q;
     split::Pix<16> op[2][2];
     auto load = [&](int t) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) op[t & 1][h] = split::pixel_operand<16, TPLANE>(base + (t * HW + 16 * h) * TPITCH, again + (t * HW + 16 * h) * TPITCH);
+        for (int h = 0; h < 2; ++h) op[t & 1][h] = split::pixel_operand<16, TPLANE>(base + (t * HW + 16 * h) * TPITCH);
     };
     const int rows = band == BANDS - 1 ? R : ROWS_F;
     auto store = [&](int r, int h, const floatx4& sum, float factor) {
@@ -180,7 +177,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) vo
         for (int k = 0; k < F; ++k)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const split::Pix<16> o = split::pixel_operand<16, TPLANE>(base + ((r + k) * HW + 16 * h) * TPITCH, again + ((r + k) * HW + 16 * h) * TPITCH);
+                const split::Pix<16> o = split::pixel_operand<16, TPLANE>(base + ((r + k) * HW + 16 * h) * TPITCH);
                 small[h] = split::product<16>(0, filt[k], o, small[h]);
                 small[h] = split::product<16>(1, filt[k], o, small[h]);
                 sum[h] = split::product<16>(2, filt[k], o, sum[h]);

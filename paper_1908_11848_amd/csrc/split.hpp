@@ -121,7 +121,8 @@ template <int C> __device__ __forceinline__ Filt<C> filter_operand(const float4 
     return f;
 }
 
-// at, again: the same address; C = 16 fetches x0 through both, and the compiler must not know that it is the same
+// at, again: the same address; C = 16 fetches x0 through both, where the compiler does not know that it is the same.  (The first layer of the
+// AlexNet-style networks gives one address: its loop has the time for the moves and not for the reads, 1 to 2 % of a step.)
 template <int C, int PLANE> __device__ __forceinline__ Pix<C> pixel_operand(const char* at, const char* again) {
     Pix<C> x;
     if constexpr (C == 16) {
@@ -135,6 +136,8 @@ template <int C, int PLANE> __device__ __forceinline__ Pix<C> pixel_operand(cons
     }
     return x;
 }
+
+template <int C, int PLANE> __device__ __forceinline__ Pix<C> pixel_operand(const char* at) { return pixel_operand<C, PLANE>(at, at); }
 
 // the same for the transposing reads of the d-filter step: lane l16 of quarter q receives channel l16 of pixels 8 q ..
 template <int PLANE> __device__ __forceinline__ void transposed_operand(uint4 (&x)[PLANES], const char* lo_at, const char* hi_at) {

@@ -197,7 +197,7 @@ int dsspk_conv3x3_large_bwd(void* stream, const float* dz_dev, const float* xc_d
                             int red_chunks, int N, int H, int C);
 /* The same for small batches, up to DSSPK_CONV3X3_SMALL_MAX images: smaller workgroups, twice as many records and partial results as the
  * kernels of dsspk_conv_fwd_prebn and its relatives leave (64 channels: one per image). */
-#define DSSPK_CONV3X3_SMALL_MAX 16
+#define DSSPK_CONV3X3_SMALL_MAX 32
 int dsspk_conv3x3_small_parts(int N, int H, int C);
 int dsspk_conv3x3_small_fwd(void* stream, const float* src_dev, const float* records_dev, int parts, const float* gamma_dev,
                             const float* beta_dev, float eps, const float* shortcut_dev, float* act_out_dev, float* stats_out_dev,

@@ -3,7 +3,8 @@
 // launch lasts as long as one workgroup, and these have half the loads, products and stores of the kernels of k_conv3x3.hip.
 // Bound by latency: of 6.5 to 13 us a launch 4.5 are what a launch of a graph costs at least.  A push of the 20-layer network, one worker, with
 // the kernels of k_conv3x3.hip / these, us: batch 1 488 / 454, 8 512 / 484, 16 543 / 499; four workers, a round: 901 / 853, 954 / 912,
-// 1005 / 939.  At most 16 images: above, the 64-row records of the stem (16 an image) are more than a workgroup adds up.
+// 1005 / 939; batch 20, 32, one worker 531 / 497, 548 / 518, four 996 / 935, 1047 / 1022; 110 layers, batch 32, eight workers 9275 / 8709.  At
+// most 32 images: eight records an image (16 channels) are then all that a workgroup adds up.
 #include "conv3x3_forms.hpp"
 #include "../../include/dssp_kernels.h"
 

@@ -328,7 +328,8 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         return b.stride == 1 && b.cin == b.cout && parts_of(b.H, b.cin, b.cout, 1) > 0;
     };
     // The stem's batch norm is folded into the first block's convolution in the same way where the stem leaves records.
-    const int stem_parts = parts_of(32, 3, 16, 1);
+    // (The smaller workgroups add up at most 256 of the stem's records, 16 an image.)
+    const int stem_parts = small && m > 16 ? 0 : parts_of(32, 3, 16, 1);
     RUN(conv(x, w + P->stem_w, F(P->stem_c), 32, 3, 16, 1, stem_parts ? recB : nullptr));
     if (!stem_parts)
         RUN(dsspk_bn_fwd(s, F(P->stem_c), w + P->stem_g, w + P->stem_b, F(P->stem_a), F(P->stem_st), bscr, (long)m * 1024, 16, eps, 1, 0, nullptr, 0, 0,

@@ -15,15 +15,14 @@ Algorithmic work per launch, with T = 4 * N * H * H * C bytes (one activation te
 W = 6 * 2 * N * H * H * C * 9 * C FLOP, what the bf16 matrix cores execute for one 3x3 convolution with fp32 operands (three bf16
 terms each, six products of terms per product):
     conv_fwd       plain forward convolution + statistics records            W,  2 T  (read x, write y)
-    conv_fwd_bn    records merge + forward convolution with BN + shortcut    W,  4 T  (read z, shortcut; write a, y)
-                   + ReLU folded into its loader (2 kernels)
+    conv_fwd_bn    forward convolution with BN + shortcut + ReLU folded      W,  4 T  (read z, shortcut; write a, y)
+                   into its loader, which merges the records itself
     conv_bwd_fused d-input AND d-filter convolution of a layer in one kernel 2W, 6 T  (read dz, xc, add, x, xc of the next BN;
                    (stages 1-2): BN backward in its loader, shortcut                  write out) + its own partial sums and
                    gradient, ReLU mask + sum records in its epilogue,                 the carried reduction's
-                   carrying the previous layer's d-filter reduction
+                   carrying an earlier layer's d-filter reduction
     conv_dgrad_bn  the same without the d-filter part (stage 3), dx stored   W,  7 T  + the carried reduction's partial sums
-    conv_wgrad     d-filter convolution, stage 1 (stage 3), carrying the     W,  2 T + its partial sums
-                   BN sums job
+    conv_wgrad     d-filter convolution, stage 1 (stage 3)                   W,  2 T + its partial sums
     bn_fwd / bn_bwd  stand-alone batch-norm kernels (irregular layers only)      4 T / 7 T
     apply / pull   server update and snapshot copy                               12 / 8 bytes per parameter
     apply_pull     update + the pusher's snapshot in one pass                    16 bytes per parameter
@@ -47,14 +46,14 @@ _COUNTERS = os.path.join(os.path.dirname(_HERE), "profiles", "traffic_counters.j
 STAGES = ((32, 16), (16, 32), (8, 64))      # (height = width, channels) of the three ResNet stages
 BATCH = 128
 N_PARAMS = 1_733_812                         # ResNet-110, 10 classes
-SOURCES = ("k_conv3x3.hip", "k_conv.hip", "k_elem.hip", "k_server.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp", "common.hpp")
+SOURCES = ("conv3x3.hpp", "conv3x3_forms.hpp", "k_conv3x3_large.hip", "k_conv3x3.hip", "k_conv.hip", "k_elem.hip", "k_server.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp", "common.hpp")
 
 
 def case_list(n_params=N_PARAMS):
     """[(key, kernels per launch, kernels launched once beforehand)] in launch order; no GPU needed."""
     out = []
     for H, C in STAGES:
-        out += [("conv_fwd_%dx%dx%d" % (H, H, C), 1, 0), ("conv_fwd_bn_%dx%dx%d" % (H, H, C), 2, 1)]
+        out += [("conv_fwd_%dx%dx%d" % (H, H, C), 1, 0), ("conv_fwd_bn_%dx%dx%d" % (H, H, C), 1, 1)]
         if C < 64:
             out += [("conv_bwd_fused_%dx%dx%d" % (H, H, C), 1, 0)]
         else:
@@ -98,7 +97,7 @@ def _traffic(key, srcs):
     return int(e["fetch_bytes"] + e["write_bytes"])
 
 
-_CONV_SRCS = ("k_conv3x3.hip", "k_conv.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp")
+_CONV_SRCS = ("conv3x3.hpp", "conv3x3_forms.hpp", "k_conv3x3_large.hip", "k_conv3x3.hip", "k_conv.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp")
 
 
 def _conv_cases(H, C, dev):
@@ -115,52 +114,46 @@ def _conv_cases(H, C, dev):
     gamma, beta = torch.ones(C, device=dev), torch.zeros(C, device=dev)
     stats = torch.cat([torch.zeros(C, device=dev), torch.ones(C, device=dev)])
     stats_o = torch.empty(2 * C, device=dev)
-    tot = torch.zeros(2 * C, device=dev)
     dgam, dbet = torch.empty(C, device=dev), torch.empty(C, device=dev)
-    parts = L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1)
+    parts = L.dsspk_conv3x3_large_parts(N, H, C)         # records and, in stages 1 and 2, partial filter gradients
     recA = torch.empty(L.dsspk_bn_scratch_floats(M, C), device=dev)
     recB = torch.empty_like(recA)
-    rec = torch.empty(2 * parts * C, device=dev)
+    rec, rec_in = torch.empty(2 * parts * C, device=dev), torch.zeros(2 * parts * C, device=dev)
     scr = torch.empty(L.dsspk_conv_wgrad_scratch_floats(N, H, H, C, C, 3, 3, 1, 1), device=dev)
     dw = torch.empty(9 * C * C, device=dev)
     E = 9 * C * C
     ch = ctypes.c_int(0)
     T = 4.0 * M * C
     F = 6 * 2.0 * M * C * 9 * C                  # executed on the matrix cores (six products of bf16 terms)
-    fwd = lambda s: L.dsspk_conv_fwd(s, x.data_ptr(), w.data_ptr(), None, z.data_ptr(), N, H, H, C, C, 3, 3, 1, 1, 0, recA.data_ptr())
-    fwd_bn = lambda s: L.dsspk_conv_fwd_prebn(s, z.data_ptr(), recA.data_ptr(), parts, gamma.data_ptr(), beta.data_ptr(), 1e-5,
-                                              sc.data_ptr(), a.data_ptr(), stats_o.data_ptr(), w.data_ptr(), y.data_ptr(),
-                                              recB.data_ptr(), N, H, C)
+    fwd = lambda s: L.dsspk_conv3x3_large_fwd(s, x.data_ptr(), None, 0, None, None, 0.0, None, None, None, w.data_ptr(), z.data_ptr(),
+                                              recA.data_ptr(), 0, N, H, C)
+    fwd_bn = lambda s: L.dsspk_conv3x3_large_fwd(s, z.data_ptr(), recA.data_ptr(), parts, gamma.data_ptr(), beta.data_ptr(), 1e-5,
+                                                 sc.data_ptr(), a.data_ptr(), stats_o.data_ptr(), w.data_ptr(), y.data_ptr(),
+                                                 recB.data_ptr(), 0, N, H, C)
     wgrad = lambda s: L.dsspk_conv_bwd_weight_parts(s, x.data_ptr(), dx.data_ptr(), scr.data_ptr(), N, H, H, C, C, 3, 3, 1, 1,
-                                                    rec.data_ptr(), parts, C, tot.data_ptr(), dgam.data_ptr(), dbet.data_ptr(),
-                                                    ctypes.byref(ch))
-    chunks = L.dsspk_conv_wgrad_scratch_floats(N, H, H, C, C, 3, 3, 1, 1) // E
-    dgrad_bn = lambda s: L.dsspk_conv_bwd_data_bn(s, dz.data_ptr(), xc.data_ptr(), stats.data_ptr(), gamma.data_ptr(), tot.data_ptr(),
-                                                  dx.data_ptr(), w.data_ptr(), add.data_ptr(), add.data_ptr(), act.data_ptr(),
-                                                  xcp.data_ptr(), stats.data_ptr(), rec.data_ptr(), scr.data_ptr(), dw.data_ptr(),
-                                                  E, chunks, N, H, C)
+                                                    None, 0, 0, None, None, None, ctypes.byref(ch))
+    chunks = parts if C < 64 else (N + 3) // 4
     scr2 = torch.zeros_like(scr)
-    fused = lambda s: L.dsspk_conv_bwd_data_bn_wgrad(s, dz.data_ptr(), xc.data_ptr(), stats.data_ptr(), gamma.data_ptr(), tot.data_ptr(),
-                                                     w.data_ptr(), add.data_ptr(), add.data_ptr(), xcp.data_ptr(), stats.data_ptr(),
-                                                     rec.data_ptr(), act.data_ptr(), scr.data_ptr(), scr2.data_ptr(), dw.data_ptr(),
-                                                     E, chunks, N, H, C)
-    keep = (x, z, sc, a, y, dz, xc, add, act, xcp, dx, w, gamma, beta, stats, stats_o, tot, dgam, dbet, recA, recB, rec, scr, scr2, dw, ch)
+    bwd = lambda s: L.dsspk_conv3x3_large_bwd(s, dz.data_ptr(), xc.data_ptr(), stats.data_ptr(), gamma.data_ptr(), rec_in.data_ptr(), parts,
+                                              dgam.data_ptr(), dbet.data_ptr(), None if C < 64 else dx.data_ptr(),
+                                              scr.data_ptr() if C < 64 else None, w.data_ptr(), add.data_ptr(), add.data_ptr(), act.data_ptr(),
+                                              xcp.data_ptr(), stats.data_ptr(), rec.data_ptr(), scr2.data_ptr(), dw.data_ptr(), E, chunks, N, H, C)
+    keep = (x, z, sc, a, y, dz, xc, add, act, xcp, dx, w, gamma, beta, stats, stats_o, dgam, dbet, recA, recB, rec, rec_in, scr, scr2, dw, ch)
     part_bytes = 4.0 * chunks * E
-    own_bytes = 4.0 * ((N + 3) // 4) * E if C == 64 else part_bytes      # partial sums the d-filter kernel of the last stage writes
     desc = "%d->%d @%dx%d, batch %d" % (C, C, H, H, N)
     head = [
         ("conv_fwd_%dx%dx%d" % (H, H, C), "conv 3x3 forward + statistics records " + desc, F, 2 * T, fwd, None, keep),
-        ("conv_fwd_bn_%dx%dx%d" % (H, H, C), "records merge + conv 3x3 forward with BN, shortcut, ReLU in its loader " + desc,
+        ("conv_fwd_bn_%dx%dx%d" % (H, H, C), "conv 3x3 forward with BN, shortcut, ReLU in its loader " + desc,
          F, 4 * T, fwd_bn, fwd, keep)]
     if C < 64:
         return head + [
             ("conv_bwd_fused_%dx%dx%d" % (H, H, C), "conv 3x3 d-input + d-filter in one kernel: BN backward in its loader, shortcut "
              "gradient, ReLU mask + sum records in its epilogue, carrying a d-filter reduction " + desc,
-             2 * F, 6 * T + 2 * part_bytes + 4.0 * E, fused, None, keep)]
+             2 * F, 6 * T + 2 * part_bytes + 4.0 * E, bwd, None, keep)]
     return head + [
         ("conv_dgrad_bn_%dx%dx%d" % (H, H, C), "conv 3x3 d-input with BN backward in its loader, shortcut gradient, ReLU mask + "
-         "sum records in its epilogue, carrying a d-filter reduction " + desc, F, 7 * T + part_bytes + 4.0 * E, dgrad_bn, wgrad, keep),
-        ("conv_wgrad_%dx%dx%d" % (H, H, C), "conv 3x3 d-filter stage 1, carrying the BN sums " + desc, F, 2 * T + own_bytes, wgrad, None, keep),
+         "sum records in its epilogue, carrying a d-filter reduction " + desc, F, 7 * T + part_bytes + 4.0 * E, bwd, wgrad, keep),
+        ("conv_wgrad_%dx%dx%d" % (H, H, C), "conv 3x3 d-filter stage 1 " + desc, F, 2 * T + part_bytes, wgrad, None, keep),
     ]
 
 
@@ -271,10 +264,10 @@ def _alexnet_conv2_case(dev):
 
 def measure(workload, em):
     """(dominant kernel entry, list of the other entries).  The kernel with the largest share of GPU time in the
-    ResNet-110 profile is the fused backward convolution kernel of the first stage; for the server stress it is the apply kernel."""
+    ResNet-110 profile is the fused backward convolution kernel of the second stage; for the server stress it is the apply kernel."""
     allm = measure_all(em.dev, em.streams[0], em.n)
     if workload.startswith("resnet"):
-        top = "conv_bwd_fused_32x32x16"
+        top = "conv_bwd_fused_16x16x32"
     elif workload.startswith("alexnet"):
         case = _alexnet_conv2_case(em.dev)
         top = case[0]

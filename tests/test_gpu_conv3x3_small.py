@@ -5,7 +5,7 @@ import pytest
 import test_gpu_conv3x3_large as large
 from paper_1908_11848_amd import binding as B
 
-SIZES = [(N, H, C) for N in (1, 3, 13, 16) for H, C in large.SHAPES]
+SIZES = [(N, H, C) for N in (1, 3, 13, 32) for H, C in large.SHAPES]
 
 
 class _Small:
@@ -22,7 +22,7 @@ def small(monkeypatch):
 def test_what_is_covered():
     L = B.lib()
     for (H, C), per_image in zip(large.SHAPES, (8, 4, 1)):
-        assert [L.dsspk_conv3x3_small_parts(N, H, C) for N in (0, 1, 16, 17)] == [0, per_image, 16 * per_image, 0]
+        assert [L.dsspk_conv3x3_small_parts(N, H, C) for N in (0, 1, 32, 33)] == [0, per_image, 32 * per_image, 0]
         assert L.dsspk_conv3x3_small_parts(4, H + 1, C) == 0 and L.dsspk_conv3x3_small_parts(4, H, C + 16) == 0
 
 

@@ -12,7 +12,8 @@ namespace {
 
 constexpr int kThreads = 256;
 // 16-byte vectors in flight per lane per operand, and one workgroup for every kThreads * kUnroll of them however many: at 25 M parameters
-// apply + pull in one pass takes 58.1 us so, 59.1 with four, 60.0 with one, and 60.5 with four and at most 2048 workgroups in a loop.
+// apply + pull in one pass takes 58.1 us so, 59.1 with four, 60.0 with one, and 60.5 with four and at most 2048 workgroups in a loop. The same order
+// from 10 K parameters (1.9 / 2.3 / 2.1 us a launch with two, four, the loop) through 1.4 M (4.1 / 4.5 / 4.3) to 6 M (13.5 / 14.7 / 14.5).
 constexpr int kUnroll = 2;
 
 __global__ __launch_bounds__(kThreads) void apply_kernel(float* __restrict__ w, const float* __restrict__ g,

@@ -307,8 +307,9 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
 // unit.  Wavefronts 0 .. 3 and 4 .. 7 take the filter taps in turn; the two halves of a sum meet in LDS at the end of a tile.  A workgroup
 // walks its tiles in blocks of 32 reduction channels; while one block is multiplied, the next one (of this tile or the next) is converted into
 // the other LDS buffer between the products, and the one after that is on its way into registers: nothing is staged in front of the
-// products but a workgroup's first block.  Bound by the matrix cores at two thirds of the rate they hold on such operands alone.  5x5, 64 -> 64 on
-// 15x15, one workgroup to a tile / this, us: batch 160 55.8 / 50.3, 256 60.0 / 57.5, 512 117.6 / 109.6.
+// products but a workgroup's first block.  The halves' numbers of steps differ by one; the longer one takes its extra step in front of the
+// barrier that both pass once a block.  Bound by the matrix cores at two thirds of the rate they hold on such operands alone.  5x5, 64 -> 64
+// on 15x15, one workgroup to a tile / this, us: batch 160 54.4 / 49.4, 256 56.0 / 53.8, 257 80.3 / 70.8, 512 109.7 / 101.8.
 constexpr int LARGE_PX = 128, LTHREADS = 512, LARGE_LOADS = 4;
 constexpr int LPITCH = pitch(32), LARGE_HALO = LARGE_LOADS * LTHREADS / 8;      // bytes of a pixel, pixels of a tile with its halo at most
 
@@ -415,21 +416,20 @@ __global__ __launch_bounds__(LTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     int parity = half, blk = 0, tile = tile0;              // this wavefront's first tap of the block
     char *cur = lds, *nxt = lds + buffer_bytes;
     while (tile < tile1) {
-        const int n = (TAPS + 1 - parity) / 2;
-        // step s works with pv[s mod 2], wv[s mod 2]; the last one reads the next block's first operands behind the barrier
-        auto step = [&](int buf, int s) {
-            if (s + 1 < n) {
-                load_p(buf ^ 1, parity + 2 * (s + 1), cur);
-            } else {
-                __syncthreads();
-                load_p(buf ^ 1, parity ^ 1, nxt);
-            }
+        const int n = (TAPS + 1 - parity) / 2;             // steps: the two halves of the workgroup differ by one
+        // Step s works with pv[s mod 2], wv[s mod 2].  While it does, the next one's pixel operands arrive: of this block, or behind the block's
+        // barrier the first ones of the next.
+        auto multiply = [&](int buf) {
             __builtin_amdgcn_sched_barrier(0);
             split::product(wv[buf], pv[buf], acc, acc);
             __builtin_amdgcn_sched_barrier(0);
             load_w(buf);
         };
-        static_assert(TAPS / 2 >= LARGE_LOADS, "a staged element to a step");
+        auto step = [&](int buf, int s) {
+            load_p(buf ^ 1, parity + 2 * (s + 1), cur);
+            multiply(buf);
+        };
+        static_assert(TAPS / 2 >= LARGE_LOADS, "a staged element to a step, all of them in front of the last one");
         int s = 0;
 #pragma unroll
         for (; s < LARGE_LOADS - 1; ++s) {                 // (the compiler is free to mix these with the products)
@@ -441,18 +441,20 @@ __global__ __launch_bounds__(LTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         }
         advance();
         static_assert(LARGE_LOADS % 2 == 0, "the loop goes on with the odd step");
-        step(1, s++);
-        for (; s + 1 < n; s += 2) { step(0, s); step(1, s + 1); }
-        if (s < n) {
-            step(0, s);
+        for (; s + 2 < n; s += 2) { step(1, s); step(0, s + 1); }
+        if (s + 1 < n) {        // one more in this half: its operands go where the other half has those of its last step
+            step(1, s);
 #pragma unroll
             for (int k = 0; k < split::PLANES; ++k) {
 #pragma unroll
-                for (int t = 0; t < TP; ++t) pv[0][t][k] = pv[1][t][k];
+                for (int t = 0; t < TP; ++t) pv[1][t][k] = pv[0][t][k];
 #pragma unroll
                 for (int i = 0; i < TC; ++i) { const uint4 w = wv[0][i][k]; wv[0][i][k] = wv[1][i][k]; wv[1][i][k] = w; }
             }
         }
+        __syncthreads();        // the same one for both halves: everything of the next block is staged, this one has been read
+        load_p(0, parity ^ 1, nxt);
+        multiply(1);
         parity ^= 1;
         if (++blk == steps_c) {
             // the other half's share of the channel tile this wavefront finishes, against its own share of the other one, through the

@@ -282,9 +282,13 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
 }
 
 constexpr int LARGE_ABOVE = 96;
+// A record buffer holds 512 records of 16 channels, four an image.  A convolution of more images would write beyond it, and the one behind would
+// refuse so many.
+constexpr int RESNET_MAX = 128;
 
 int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, const float* w, float* g, float* loss, std::string& err) {
     const int m = P->m;
+    if (m > RESNET_MAX) { err = "residual networks take at most 128 images"; return -1; }
     const float eps = 1e-5f;
     auto F = [&](size_t off) { return (float*)(ws + off); };
     float *scr = F(P->wg_scratch), *bscr = F(P->bn_scratch);

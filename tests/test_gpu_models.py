@@ -631,6 +631,25 @@ def test_failed_push_leaves_the_clocks_untouched():
 
 
 
+@pytest.mark.parametrize("batch", [129, 300])
+def test_residual_steps_beyond_128_images_are_refused_untouched(batch):
+    """More images than a record buffer holds records of: refused before anything is launched, so that nothing is written, neither in the
+    worker's part of the workspace nor behind it."""
+    w0 = inputs.init_weights(segs_of("resnet8", 10), 4)
+    xs, ys = inputs.batches(4, 1, 1, batch, 10)
+    em = Emulation("resnet8", 1, 1, 2, 0.01, w0, batch, 10, xs, ys)
+    B.dssp_pull(em.ctx, 0, em.w_local[0])
+    em.ws.fill_(7)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        with pytest.raises(B.DsspError) as e:
+            em.step(0, 0)
+        assert e.value.code == B.DSSP_EHIP
+    em.synchronize()
+    assert bool((em.ws == 7).all()) and not em.grad.any()
+    em.close()
+
+
 def test_error_codes():
     import torch
     w = torch.zeros(1024, device="cuda")

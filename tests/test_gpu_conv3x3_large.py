@@ -30,22 +30,26 @@ def _records(parts, C, x):
 @pytest.mark.parametrize("N,H,C", SIZES)
 @pytest.mark.parametrize("form", ["plain", "bn", "bn+shortcut"])
 def test_forward(oracle_nn, N, H, C, form):
-    """Convolution 2e-7 as in test_gpu_conv3x3.py plus the activations' rounding (about 1e-7 each): 4e-7."""
+    forward(oracle_nn, "large", N, H, C, form)
+
+
+def forward(oracle_nn, family, N, H, C, form):
+    """dsspk_conv3x3_<family>_fwd.  Convolution 2e-7 as in test_gpu_conv3x3.py plus the activations' rounding (about 1e-7 each): 4e-7."""
     g = np.random.default_rng(N + C)
     f = lambda *sh: g.standard_normal(sh).astype(np.float32)
     x, sc, w = f(N, H, H, C) + 0.5, f(N, H, H, C), (np.sqrt(2.0 / (9 * C)) * f(3, 3, C, C)).astype(np.float32)
     gamma, beta = 1 + 0.1 * f(C), 0.1 * f(C)
     L, s = B.lib(), stream_ptr()
-    parts = L.dsspk_conv3x3_large_parts(N, H, C)
+    parts, fwd = getattr(L, "dsspk_conv3x3_%s_parts" % family)(N, H, C), getattr(L, "dsspk_conv3x3_%s_fwd" % family)
     X, SC, W, G, BE, REC = dev(x), dev(sc), dev(w), dev(gamma), dev(beta), dev(_records(parts, C, x))
     act, stats, y, rec = empty((N, H, H, C)), empty(2 * C), empty((N, H, H, C)), empty((parts, C, 2))
     a = x.astype(np.float64)
     if form == "plain":
-        assert L.dsspk_conv3x3_large_fwd(s, X.data_ptr(), None, 0, None, None, 1e-5, None, None, None, W.data_ptr(), y.data_ptr(), rec.data_ptr(), 0, N, H, C) == 0
+        assert fwd(s, X.data_ptr(), None, 0, None, None, 1e-5, None, None, None, W.data_ptr(), y.data_ptr(), rec.data_ptr(), 0, N, H, C) == 0
     else:
         short = SC.data_ptr() if form == "bn+shortcut" else None
-        assert L.dsspk_conv3x3_large_fwd(s, X.data_ptr(), REC.data_ptr(), parts, G.data_ptr(), BE.data_ptr(), 1e-5, short, act.data_ptr(),
-                                         stats.data_ptr(), W.data_ptr(), y.data_ptr(), rec.data_ptr(), 0, N, H, C) == 0
+        assert fwd(s, X.data_ptr(), REC.data_ptr(), parts, G.data_ptr(), BE.data_ptr(), 1e-5, short, act.data_ptr(), stats.data_ptr(), W.data_ptr(),
+                   y.data_ptr(), rec.data_ptr(), 0, N, H, C) == 0
         mean, var = a.mean((0, 1, 2)), a.var((0, 1, 2))
         st = host(stats).reshape(2, C)
         assert max_abs(st[0], mean) < 2e-6 and rel_l2(st[1], 1 / np.sqrt(var + 1e-5)) < 1e-6
@@ -75,12 +79,17 @@ def _backward_inputs(N, H, C, large):
 @pytest.mark.parametrize("N,H,C", SIZES)
 @pytest.mark.parametrize("large", [False, True])
 def test_backward(N, H, C, large):
-    """Against dsspk_conv_bwd_data_bn(_wgrad) behind dsspk_bn_bwd_totals: the same products in the same order per output; sums over the
+    backward("large", N, H, C, large)
+
+
+def backward(family, N, H, C, large):
+    """dsspk_conv3x3_<family>_bwd against dsspk_conv_bwd_data_bn(_wgrad) behind dsspk_bn_bwd_totals: the same products in the same order per output; sums over the
     batch and over the records in another: 2e-6 of the result, as between those kernels' own forms."""
     L, s = B.lib(), stream_ptr()
     t = _backward_inputs(N, H, C, large)
     P = {k: v.data_ptr() for k, v in t.items()}
-    parts, parts4 = L.dsspk_conv3x3_large_parts(N, H, C), L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1)
+    parts, parts4 = getattr(L, "dsspk_conv3x3_%s_parts" % family)(N, H, C), L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1)
+    bwd = getattr(L, "dsspk_conv3x3_%s_bwd" % family)
     rin = dev(np.random.default_rng(1).standard_normal((parts, C, 2)).astype(np.float32))
     tot, dgam, dbet, dg, db = empty(2 * C), empty(C), empty(C), empty(C), empty(C)
     assert L.dsspk_bn_bwd_totals(s, rin.data_ptr(), parts, C, tot.data_ptr(), dgam.data_ptr(), dbet.data_ptr()) == 0
@@ -91,9 +100,9 @@ def test_backward(N, H, C, large):
     job = dev(np.random.default_rng(2).standard_normal((70, 2304)).astype(np.float32))
     jw, jw4 = empty(2304), empty(2304)
     o = other.data_ptr()
-    assert L.dsspk_conv3x3_large_bwd(s, P["dz"], P["xc"], P["stats"], P["gamma"], rin.data_ptr(), parts, dg.data_ptr(), db.data_ptr(),
-                                     None if fused else o, o if fused else None, P["w"], P["add"], out.data_ptr(), P["xin"], P["xp"], P["statsp"],
-                                     rec.data_ptr(), job.data_ptr(), jw.data_ptr(), 2304, 70, N, H, C) == 0
+    assert bwd(s, P["dz"], P["xc"], P["stats"], P["gamma"], rin.data_ptr(), parts, dg.data_ptr(), db.data_ptr(), None if fused else o,
+               o if fused else None, P["w"], P["add"], out.data_ptr(), P["xin"], P["xp"], P["statsp"], rec.data_ptr(), job.data_ptr(), jw.data_ptr(), 2304,
+               70, N, H, C) == 0
     red = (job.data_ptr(), jw4.data_ptr(), 2304, 70, N, H, C)
     if fused:
         assert L.dsspk_conv_bwd_data_bn_wgrad(s, P["dz"], P["xc"], P["stats"], P["gamma"], tot.data_ptr(), P["w"], P["add"], out4.data_ptr(), P["xp"],

@@ -8,17 +8,6 @@ from paper_1908_11848_amd import binding as B
 SIZES = [(N, H, C) for N in (1, 3, 13, 32) for H, C in large.SHAPES]
 
 
-class _Small:
-    def __getattr__(self, name):
-        return getattr(_Small.lib, name.replace("_large_", "_small_"))
-
-
-@pytest.fixture
-def small(monkeypatch):
-    _Small.lib = B.lib()
-    monkeypatch.setattr(B, "lib", _Small)
-
-
 def test_what_is_covered():
     L = B.lib()
     for (H, C), per_image in zip(large.SHAPES, (8, 4, 1)):
@@ -29,12 +18,12 @@ def test_what_is_covered():
 @pytest.mark.gpu
 @pytest.mark.parametrize("N,H,C", SIZES)
 @pytest.mark.parametrize("form", ["plain", "bn", "bn+shortcut"])
-def test_forward(oracle_nn, small, N, H, C, form):
-    large.test_forward(oracle_nn, N, H, C, form)
+def test_forward(oracle_nn, N, H, C, form):
+    large.forward(oracle_nn, "small", N, H, C, form)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("N,H,C", SIZES)
 @pytest.mark.parametrize("big", [False, True])
-def test_backward(small, N, H, C, big):
-    large.test_backward(N, H, C, big)
+def test_backward(N, H, C, big):
+    large.backward("small", N, H, C, big)

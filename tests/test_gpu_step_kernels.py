@@ -120,23 +120,36 @@ def test_last_batch_norm_with_pooling(N, side, C, half):
     assert np.array_equal(host(dz), host(dz0)) and np.array_equal(host(r), host(r0))
 
 
-@pytest.mark.parametrize("N,H,C", [(1, 16, 32), (5, 16, 32), (128, 16, 32), (1, 8, 64), (5, 8, 64), (128, 8, 64)])
-@pytest.mark.parametrize("large", [False, True])
+def _family(family, N, H, C):
+    """(records it leaves, forward with a batch norm in the loader) of a family of the 3x3 kernels; short_half: of a stride-2 block's shortcut."""
+    L = B.lib()
+    if family == "middle":
+        return (L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1),
+                lambda *a, short_half=0: (L.dsspk_conv_fwd_prebn_half if short_half else L.dsspk_conv_fwd_prebn)(*a))
+    fwd = getattr(L, "dsspk_conv3x3_%s_fwd" % family)
+    return getattr(L, "dsspk_conv3x3_%s_parts" % family)(N, H, C), lambda *a, short_half=0: fwd(*a[:13], short_half, *a[13:])
+
+
+BEHIND = [(family, N, H, C) for family in ("middle", "large") for N, H, C in ((1, 16, 32), (5, 16, 32), (128, 16, 32), (1, 8, 64), (5, 8, 64), (128, 8, 64))]
+BEHIND += [("small", N, H, C) for N in (1, 5, 17, 32) for H, C in ((16, 32), (8, 64))]
+
+
+@pytest.mark.parametrize("family,N,H,C", BEHIND)
 @pytest.mark.parametrize("scale", [1.0, 1e32])
-def test_convolution_behind_a_stride_2_shortcut(N, H, C, large, scale):
-    """Both kernel families against the batch norm with that shortcut and the plain convolution, one after the other; scale: of one shortcut
+def test_convolution_behind_a_stride_2_shortcut(family, N, H, C, scale):
+    """The kernel families against the batch norm with that shortcut and the plain convolution, one after the other; scale: of one shortcut
     value, the second beyond the range of the scaled terms (the tiles it meets are then computed by other instructions: 4e-7)."""
     g = np.random.default_rng(N + C)
     f = lambda *sh: g.standard_normal(sh).astype(np.float32)
     x, sc = f(N, H, H, C), f(N, 2 * H, 2 * H, C // 2)
     sc[N - 1, 2, 2 * H - 2, 1] = scale
     L, s = B.lib(), stream_ptr()
-    parts = L.dsspk_conv3x3_large_parts(N, H, C) if large else L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1)
+    parts, fwd = _family(family, N, H, C)
     X, SC, W, G, BE, rec = dev(x), dev(sc), dev(0.1 * f(3, 3, C, C)), dev(1 + 0.1 * f(C)), dev(0.1 * f(C)), dev(_records(parts, C, x))
     act, act0, st, st0, y, y0, out = empty(x.shape), empty(x.shape), empty(2 * C), empty(2 * C), empty(x.shape), empty(x.shape), empty((parts, C, 2))
     args = (s, X.data_ptr(), rec.data_ptr(), parts, G.data_ptr(), BE.data_ptr(), 1e-5, SC.data_ptr(), act.data_ptr(), st.data_ptr(), W.data_ptr(),
             y.data_ptr(), out.data_ptr())
-    assert (L.dsspk_conv3x3_large_fwd(*args, 1, N, H, C) if large else L.dsspk_conv_fwd_prebn_half(*args, N, H, C)) == 0
+    assert fwd(*args, N, H, C, short_half=1) == 0
     assert L.dsspk_bn_fwd(s, X.data_ptr(), G.data_ptr(), BE.data_ptr(), act0.data_ptr(), st0.data_ptr(), rec.data_ptr(), N * H * H, C, 1e-5, 1, 2,
                           SC.data_ptr(), N, H, H, parts) == 0
     assert L.dsspk_conv_fwd(s, act0.data_ptr(), W.data_ptr(), None, y0.data_ptr(), N, H, H, C, C, 3, 3, 1, 1, 0, None) == 0
@@ -144,4 +157,36 @@ def test_convolution_behind_a_stride_2_shortcut(N, H, C, large, scale):
     quiet = np.abs(c0) < 1e6
     assert np.isfinite(c).all() and np.max(np.abs(a - a0) / np.maximum(np.abs(a0), 1)) < 4e-6
     assert rel_l2(c[quiet], c0[quiet]) < 2e-6 and rel_l2(c, c0) < 2e-6
-    assert (L.dsspk_conv3x3_large_fwd(*args, 1, N, 32, 16) if large else L.dsspk_conv_fwd_prebn_half(*args, N, 32, 16)) == -1
+    assert fwd(*args, N, 32, 16, short_half=1) == -1
+
+
+# family, images, channels in front, stride, height and width of the result, channels: the stem and the stride-2 convolutions in front of each
+# family, at the ends of the batches for which a residual network's step has the records merged by the kernel behind
+FRONT = [("small", N, 3, 1, 32, 16) for N in (1, 16)] + [("middle", 64, 3, 1, 32, 16)]
+FRONT += [("small", N, 16, 2, 16, 32) for N in (1, 32)] + [("middle", N, 16, 2, 16, 32) for N in (33, 64)]
+FRONT += [("small", N, 32, 2, 8, 64) for N in (1, 32)] + [("middle", N, 32, 2, 8, 64) for N in (33, 96)] + [("large", N, 32, 2, 8, 64) for N in (97, 128)]
+
+
+@pytest.mark.parametrize("family,N,Cin,stride,H,C", FRONT)
+def test_convolution_behind_a_generic_one(family, N, Cin, stride, H, C):
+    """Records of a generic convolution, another number than the family's own leaves, merged in the loader of the 3x3 kernel behind it, against
+    the batch norm by itself on the same records (the same sums in another order) and the plain convolution."""
+    g = np.random.default_rng(N + C)
+    f = lambda *sh: dev(g.standard_normal(sh).astype(np.float32))
+    L, s = B.lib(), stream_ptr()
+    shape = (N, H * stride, H * stride, Cin, C, 3, 3, stride, 1)
+    parts = L.dsspk_conv_fwd_records_parts(*shape)
+    assert parts > 0
+    own, fwd = _family(family, N, H, C)
+    x0, w0, W, G, BE = f(N, H * stride, H * stride, Cin), 0.3 * f(3, 3, Cin, C), 0.1 * f(3, 3, C, C), 1 + 0.1 * f(C), 0.1 * f(C)
+    x, rec, out = empty((N, H, H, C)), empty((parts, C, 2)), empty((own, C, 2))
+    assert L.dsspk_conv_fwd_records(s, x0.data_ptr(), w0.data_ptr(), x.data_ptr(), rec.data_ptr(), *shape) == 0
+    act, act0, st, st0, y, y0 = empty(x.shape), empty(x.shape), empty(2 * C), empty(2 * C), empty(x.shape), empty(x.shape)
+    assert fwd(s, x.data_ptr(), rec.data_ptr(), parts, G.data_ptr(), BE.data_ptr(), 1e-5, None, act.data_ptr(), st.data_ptr(), W.data_ptr(), y.data_ptr(),
+               out.data_ptr(), N, H, C) == 0
+    assert L.dsspk_bn_fwd(s, x.data_ptr(), G.data_ptr(), BE.data_ptr(), act0.data_ptr(), st0.data_ptr(), rec.data_ptr(), N * H * H, C, 1e-5, 1, 0,
+                          None, 0, 0, 0, parts) == 0
+    assert L.dsspk_conv_fwd(s, act0.data_ptr(), W.data_ptr(), None, y0.data_ptr(), N, H, H, C, C, 3, 3, 1, 1, 0, None) == 0
+    assert rel_l2(host(st), host(st0)) < 1e-6 and rel_l2(host(act), host(act0)) < 1e-6 and rel_l2(host(y), host(y0)) < 2e-6
+    want = _records(own, C, host(y))
+    assert np.max(np.abs(host(out)[..., 0] - want[..., 0])) < 2e-6 * np.abs(host(y)).max() and rel_l2(host(out)[..., 1], want[..., 1]) < 2e-6

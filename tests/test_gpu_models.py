@@ -501,6 +501,29 @@ def test_odd_batch_sizes_and_class_counts(oracle_nn, model, batch, ncls):
     em.close()
 
 
+@pytest.mark.parametrize("batch", [16, 17, 32, 33, 63, 64, 65, 96, 97])
+def test_residual_step_where_its_kernels_change(oracle_nn, batch):
+    """A residual network's step takes other kernels, and other ones leave and merge the batch norms' records, from 17, 33, 64, 65 and 97 images:
+    gradient parity on either side, with a regular block behind each stride-2 one; and the same bits from a captured step."""
+    model, ncls = "resnet14", 100
+    net = oracle_nn.make_net(model, ncls)
+    w0 = inputs.init_weights(segs_of(model, ncls), 4, jitter=0.1)
+    xs, ys = inputs.batches(4, 1, 1, batch, ncls)
+    em = Emulation(model, 1, 1, 2, 0.01, w0, batch, ncls, xs, ys)
+    B.dssp_pull(em.ctx, 0, em.w_local[0])
+    em.step(0, 0)
+    err, nflip = gradient_parity(net, em, 0, w0, xs[0][0], ys[0][0])
+    g = em.worker_grad(0)[0].copy()
+    for _ in range(2):                      # captured, replayed
+        em.grad[0].fill_(float("nan"))
+        torch.cuda.synchronize()
+        em.step(0, 0)
+        assert np.array_equal(em.worker_grad(0)[0], g)
+    say("%s batch %d: gradient error %.2e (%d near-ties resolved)" % (model, batch, err, nflip))
+    assert err < GRAD_TOL
+    em.close()
+
+
 # ------------------------------------------------------------------ graph replay
 def test_graph_replay_is_bit_identical_to_eager(oracle_nn):
     """A worker step runs eagerly the first time it sees a set of buffers, is captured into a HIP graph

@@ -359,7 +359,8 @@ def test_aggregated_pushes_stress_vector(oracle_nn):
                                                             ("mlp", 4, 32, 10, "equal", 1, 2)])
 def test_aggregated_pushes_model(oracle_nn, model, K, batch, ncls, kind, s_L, r_max):
     """The same on a model: 50 updates with simultaneous pushes aggregated; log bit-exact, weights bit-identical to the
-    one-by-one path (also with the server's applies on a stream of their own) and within 1e-3 of the oracle."""
+    one-by-one path (also with the server's applies on a stream of their own, and with workers that share streams, evenly or
+    three to one) and within 1e-3 of the oracle."""
     lr = {"resnet8": 0.05, "alexnet_ds": 0.001, "mlp": 0.01}[model]
     d = tie_durations(kind, K, 64)
     net = oracle_nn.make_net(model, ncls)
@@ -367,8 +368,9 @@ def test_aggregated_pushes_model(oracle_nn, model, K, batch, ncls, kind, s_L, r_
     xs, ys = inputs.batches(4, K, 4, batch, ncls, flat=(model == "mlp"))
     out = ps.run(K, s_L, r_max, lr, w0, d, ps.model_grad_fn(net, xs, ys), total=50)
     results = []
-    for aggregate, server_stream in ((True, False), (False, False), (True, True)):
-        em = Emulation(model, K, s_L, r_max, lr, w0, batch, ncls, xs, ys, server_stream=server_stream)
+    for aggregate, server_stream, streams, rates in ((True, False, None, None), (False, False, None, None), (True, True, None, None), (True, False, 2, None),
+                                                     (True, True, 2, None), (True, False, 2, [9, 1, 1, 1]), (True, True, 2, [9, 1, 1, 1]), (True, True, 1, None)):
+        em = Emulation(model, K, s_L, r_max, lr, w0, batch, ncls, xs, ys, worker_streams=streams, server_stream=server_stream, rates=rates)
         log, st = em.run(d, total=50, aggregate=aggregate)
         assert log == out["log"]
         assert (st["aggregated"] >= 20) == aggregate

@@ -120,10 +120,9 @@ struct ManyArgs {
 };
 
 // GRADS gradients are fetched together, for VECS vectors per lane kThreads apart, so that a workgroup takes GRADS * VECS * 4 KB from memory at
-// a time, 4 * VECS KB of each stream in a row.  Many streams want long stretches of each: 16 gradients and 16 snapshots of 25 M
-// parameters (34 streams) take 592 us with <2, 8>, 602 with <4, 2>, 613 with <4, 4>, 648 with <4, 1> (630 with at most 2048 workgroups in a
-// loop: two passes over more streams than the memory has open rows); one gradient and four snapshots 104, 107, 104, 107 (118).  A small
-// vector wants workgroups: 0.2 M parameters, 8 and 8, 13.1 us with <2, 8>, 6.3 with <4, 1>; 1.7 M, 16 and 16, 40.8 and 38.8; 8 M 187 and 205.
+// a time, 4 * VECS KB of each stream in a row.  us, <4, 1> / <2, 4> / <2, 8> / a loop of at most 2048 workgroups: 16 gradients and 16 snapshots
+// behind the last of them, 1.7 M parameters 42 / 46 / 76 / 50, 5 M 117 / 119 / 133 / 119, 14 M 337 / 344 / 356 / 341, 25 M 646 / 607 / 608 / 622;
+// 4 and 4, 7 M 44.5 / 46.9 / 48.2 / 45.7, 25 M 154 / 150 / 155 / 155.  (<2, 8> takes 196 registers: two workgroups to a compute unit.)
 template <int GRADS, int VECS, bool ALL>
 __device__ __forceinline__ void apply_many(floatx4* __restrict__ w4, const ManyArgs& a, long first, long n4, float scale) {
     const unsigned tid = threadIdx.x;           // the rest of an address is the same for the whole workgroup
@@ -246,9 +245,10 @@ extern "C" int dsspk_apply_many(void* stream, float* w, int m, const float* cons
     }
     const long n4 = al ? n / 4 : 0;
     if (n4 == 0 && n > 3) return -1;
-    // long stretches from where they still give the chip's 256 compute units two workgroups each
-    constexpr int GRADS = 2, VECS = 8;
-    if (n4 >= 512L * kThreads * VECS)
+    // Longer stretches from 21 M parameters.  A round of 16 pushes through dssp_push_many with <4, 1> / <2, 4>, us: 17 M 451 / 461, 20 M 543 / 543,
+    // 22 M 605 / 589, 25 M 694 / 649 (34 streams 100 MB apart), 30 M 771 / 772.
+    constexpr int GRADS = 2, VECS = 4;
+    if (n4 >= 5L << 20)
         hipLaunchKernelGGL((apply_many_kernel<GRADS, VECS>), dim3(ceil_div(n4, (long)kThreads * VECS)), dim3(kThreads), 0, (hipStream_t)stream, w, a, n4,
                            (long)n, scale, stamp, version_first);
     else

@@ -1,4 +1,4 @@
-"""The aggregated apply where its two forms meet (4 M parameters and more: long stretches of every stream) and at partly filled last
+"""The aggregated apply where its two forms meet (21 M parameters and more: longer stretches of every stream) and at partly filled last
 workgroups of either, against single applies and pulls: the same bits."""
 import ctypes
 
@@ -8,7 +8,7 @@ from paper_1908_11848_amd import binding as B
 from gpu_util import empty, stream_ptr
 
 pytestmark = pytest.mark.gpu
-LINE = 512 * 256 * 8 * 4
+LINE = 5 * 2 ** 22
 
 
 @pytest.mark.parametrize("n", [LINE - 4, LINE - 1, LINE, LINE + 3, LINE + 4, LINE + 8 * 1024 + 2049 * 4 + 1, LINE + 7 * 8192 - 4])

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 LINE = 5 * 2 ** 22
 
 
-@pytest.mark.parametrize("n", [LINE - 4, LINE - 1, LINE, LINE + 3, LINE + 4, LINE + 8 * 1024 + 2049 * 4 + 1, LINE + 7 * 8192 - 4])
+@pytest.mark.parametrize("n", [1, 3, 4, 1000, 1023, 1024, 1027, 50_001, LINE - 4, LINE - 1, LINE, LINE + 3, LINE + 4, LINE + 8 * 1024 + 2049 * 4 + 1, LINE + 7 * 8192 - 4])
 @pytest.mark.parametrize("m,after", [(1, [1, 1]), (3, [2, 3]), (16, [1, 16, 16])])
 def test_same_bits_as_single_applies(n, m, after):
     import torch

@@ -291,7 +291,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     if (m > RESNET_MAX) { err = "residual networks take at most 128 images"; return -1; }
     const float eps = 1e-5f;
     auto F = [&](size_t off) { return (float*)(ws + off); };
-    float *scr = F(P->wg_scratch), *bscr = F(P->bn_scratch);
+    float* bscr = F(P->bn_scratch);
     // ---- forward
     // Statistics records ping-pong between two buffers: conv1 writes recA, conv2 reads recA and writes recB,
     // the next block's conv1 reads recB.  A "regular" block (stride 1, same width, shape covered by the specialised
@@ -332,7 +332,9 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         return b.stride == 1 && b.cin == b.cout && parts_of(b.H, b.cin, b.cout, 1) > 0;
     };
     // The stem's batch norm is folded into the first block's convolution in the same way where the stem leaves records.
-    // (The smaller workgroups add up at most 256 of the stem's records, 16 an image.)
+    // It leaves 16 an image, of which the smaller workgroups add up at most 256; beyond 32 images it leaves some at 64 alone, where its tiles get
+    // larger and the list just fits (20 layers, one worker, batch 63 / 64 / 65: 654 / 641 / 687 us; at 65 the first stride-2 convolution's list ends
+    // as well).
     const int stem_parts = small && m > 16 ? 0 : parts_of(32, 3, 16, 1);
     RUN(conv(x, w + P->stem_w, F(P->stem_c), 32, 3, 16, 1, stem_parts ? recB : nullptr));
     if (!stem_parts)
@@ -385,7 +387,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     // whose d-filter kernel is of another kind leaves its partial sums waiting too; what waits at the end is one launch.
     // Everything else (stem, first convolutions of the stride-2 blocks) takes the stand-alone kernels.
     //   parts0 > 0 : g0 holds the masked dz of this block's BN2 and recB0 its records
-    //   tot0       : their sums are in totB already (and dgamma / dbeta of BN2 stored)
+    //   tot0       : their sums are in totB already (and dgamma / dbeta of BN2 stored), or the kernel behind adds them up
     //   pend       : d-filter partial sums whose reduction has not been launched yet, the oldest first
     float *recB0 = F(P->bn_scratch2), *totA = F(P->tot_a), *totB = F(P->tot_b);
     float* scrs[WG_SCRATCH] = {F(P->wg_scratch)};
@@ -426,9 +428,9 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     };
     // dz (masked, records summed into tot) -> through BN (xc, st, gamma) -> dx -> d-input (+ add) with the mask / records
     // epilogue (mask_src = x_in, xc_post, st_post -> records) into out, and d-filter (x_in, dx) into dw (pending).
-    // The sums of dz: in_rec / in_parts / in_dgamma / in_dbeta, added up by the kernel itself where they are few, else already in
-    // tot (ready) or by a launch here.  sum_next: the records just written are summed into ntot / ndgamma / ndbeta for the
-    // next layer (not where that layer does it itself).
+    // The sums of dz: in_rec / in_parts / in_dgamma / in_dbeta, added up by the kernel itself in the larger and the smaller workgroups; between
+    // them (33 images and more: more records than a workgroup of those kernels adds up) already in tot (ready) or by a launch here, and
+    // sum_next: the records just written are summed into ntot / ndgamma / ndbeta for the next layer.
     auto regular_layer = [&](const float* in_rec, int in_parts, float* in_dgamma, float* in_dbeta, bool ready,
                              const float* dz, const float* xc, const float* st, const float* gamma, float* tot,
                              const float* wt, const float* add, float* out, const float* x_in, const float* xc_post,
@@ -449,17 +451,14 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             push_back(out_scr, dw, 9 * Cc * Cc, chunks);
             return 0;
         }
-        const bool own_sums = dsspk_conv_records_inline(in_parts, Cc) != 0;
-        if (!own_sums && !ready) RUN(dsspk_bn_bwd_totals(s, in_rec, in_parts, Cc, tot, in_dgamma, in_dbeta));
-        const float* totals = own_sums ? nullptr : tot;
-        sum_next = sum_next && !dsspk_conv_records_inline(nparts, Cc);
+        if (!ready) RUN(dsspk_bn_bwd_totals(s, in_rec, in_parts, Cc, tot, in_dgamma, in_dbeta));
         int chunks = dsspk_conv_bwd_fused_chunks(m, H, Cc);
         if (chunks > 0) {
-            RUN(dsspk_conv_bwd_data_bn_wgrad_records(s, dz, xc, st, gamma, totals, in_rec, in_parts, in_dgamma, in_dbeta, wt, add, out, xc_post,
+            RUN(dsspk_conv_bwd_data_bn_wgrad_records(s, dz, xc, st, gamma, tot, in_rec, in_parts, in_dgamma, in_dbeta, wt, add, out, xc_post,
                                                      st_post, records, x_in, out_scr, rp, rdw, rE, rchunks, m, H, Cc));
             if (sum_next) RUN(dsspk_bn_bwd_totals(s, records, nparts, Cc, ntot, ndgamma, ndbeta));
         } else {
-            RUN(dsspk_conv_bwd_data_bn_records(s, dz, xc, st, gamma, totals, in_rec, in_parts, in_dgamma, in_dbeta, g1, wt, add, out, x_in,
+            RUN(dsspk_conv_bwd_data_bn_records(s, dz, xc, st, gamma, tot, in_rec, in_parts, in_dgamma, in_dbeta, g1, wt, add, out, x_in,
                                                xc_post, st_post, records, rp, rdw, rE, rchunks, m, H, Cc));
             RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, sum_next ? records : nullptr,
                                             nparts, Cc, ntot, ndgamma, ndbeta, &chunks));

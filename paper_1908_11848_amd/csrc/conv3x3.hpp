@@ -2,12 +2,13 @@
 // ResNet-110): forward and gradient w.r.t. the input as ONE kernel.
 //
 // A workgroup owns a band of R output rows of one image (or all of them) and CN of the C output channels, and has four or eight
-// wavefronts.  It loads the (R+2) x (HW+2) x C input halo tile (zero borders) into LDS once; everything else is served from LDS, so
-// every input element is read from memory once per band instead of nine times.  The filter never passes through LDS: a wavefront owns
-// ONE tile of 16 output channels and holds one column of that tile's filter (three taps) in registers; a row of the next column is
-// fetched and split while the products still work with the present one.  LDS therefore holds the halo tile only (35 to 42 KB with four
-// wavefronts, 42 to 81 KB with eight), registers stay below 128 with eight, and what fits a compute unit of LDS and registers overlaps:
-// one workgroup's transfers run beside another's products.
+// wavefronts of four pixel tiles each, or four wavefronts of two (k_conv3x3.hip, k_conv3x3_large.hip, k_conv3x3_small.hip).  It loads the
+// (R+2) x (HW+2) x C input halo tile (zero borders) into LDS once; everything else is served from LDS, so every input element is read from
+// memory once per band instead of nine times.  The filter never passes through LDS: a wavefront owns ONE tile of 16 output channels and holds
+// one column of that tile's filter (three taps) in registers; a row of the next column is fetched and split while the products still work with
+// the present one.  (Two pixel tiles: all three columns, fetched up front.)  LDS therefore holds the halo tile and a little for the sums: 36 to
+// 42 KB with four wavefronts, 42 to 81 KB with eight, 22 to 42 KB with two pixel tiles.  Registers are at most 128 with eight wavefronts, and
+// what fits a compute unit of LDS and registers overlaps: one workgroup's transfers run beside another's products.
 //
 // What bounds them (110 layers, batch 128, four streams, 1.82 ms a push): registers and LDS admit 16 wavefronts to a compute unit and each
 // fetches, multiplies and stores one after the other.  Without the products a push takes 1.27 ms (its bytes at copy rate: 1.0), without
@@ -148,7 +149,8 @@ struct WgradFused {
 // add and dst may be the same buffer (every element is read and written by the same lane); with PRE == 3
 // dst must differ from src, whose halo rows other workgroups still read.
 // Wavefronts per SIMD the register allocation aims at: with eight wavefronts to a workgroup two of them per compute unit need four; with four
-// to a workgroup the fourth brought nothing (110 layers, batch 128, four streams: 1.858 ms a push with three, 1.875 with four).
+// to a workgroup the fourth brings nothing (a round of eight workers on four streams, three / four, us: 110 layers, batch 64 12390 / 12460, 50
+// layers, batch 33 5760 / 5800).
 // Two pixel tiles to a wavefront: no second workgroup waits for room on the compute unit.
 template <int C, int WAVES, bool WG, int NT>
 constexpr int min_waves() { return NT == 2 ? 2 : WAVES == 8 || (C == 16 && !WG) ? 4 : 3; }

@@ -828,7 +828,8 @@ extern "C" int dsspk_conv_fwd(void* stream, const float* x, const float* w, cons
     return launch_igemm<false, false>((hipStream_t)stream, x, w, bias, nullptr, y, g, relu);
 }
 
-// Statistics records that dsspk_conv_fwd_records leaves, 0: not this shape.  Few enough for dsspk_conv_fwd_prebn.
+// Statistics records that dsspk_conv_fwd_records leaves, 0: not this shape.  Few enough for dsspk_conv_fwd_prebn: 16 channels at 32x32, up to 32
+// images in tiles of 64 rows, and 64 images, the one batch whose tiles of 128 rows are not too many.
 extern "C" int dsspk_conv_fwd_records_parts(int N, int H, int W, int Cin, int Cout, int KH, int KW, int stride, int pad) {
     ConvGeom g;
     if (!geom(g, N, H, W, Cin, Cout, KH, KW, stride, pad) || Cout < 16 || Cout % 16) return 0;

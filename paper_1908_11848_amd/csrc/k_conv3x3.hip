@@ -72,8 +72,8 @@ __device__ __forceinline__ void dfilter_finish(const floatx4 (&M)[16], floatx4 (
     }
 }
 
-// Up to batch 32 every workgroup merges the records itself.  A kernel of its own for that takes 4 us of a stream's time.  20-layer
-// network, four workers, a round with such kernels and without: batch 16 876 -> 821 us, batch 32 945 -> 894 us.
+// Up to this many values every workgroup merges the records itself; a kernel of its own for that takes 4 us of a stream's time.  That serves
+// callers of the layers one by one: a network's step runs these kernels at 33 to 96 images, and then the lists are longer.
 constexpr int INLINE_RECORDS = 2048;
 static_assert(inline_records<16, 4>() == INLINE_RECORDS / 16 && inline_records<64, 4>() == INLINE_RECORDS / 64, "what the kernels fetch");
 constexpr bool records_inline(int parts, int C) { return (C == 16 || C == 32 || C == 64) && parts >= 1 && (long)parts * C <= INLINE_RECORDS; }

@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
 // products but a workgroup's first block.  The halves' numbers of steps differ by one; the longer one takes its extra step in front of the
 // barrier that both pass once a block.  Bound by the matrix cores at two thirds of the rate they hold on such operands alone.  5x5, 64 -> 64
 // on 15x15, one workgroup to a tile / this, us: batch 160 54.4 / 49.4, 256 56.0 / 53.8, 257 80.3 / 70.8, 512 109.7 / 101.8.
-constexpr int LARGE_PX = 128, LTHREADS = 512, LARGE_LOADS = 4;
+constexpr int LTHREADS = 512, LARGE_LOADS = 4;
 constexpr int LPITCH = pitch(32), LARGE_HALO = LARGE_LOADS * LTHREADS / 8;      // bytes of a pixel, pixels of a tile with its halo at most
 
 template <int KS>
@@ -521,8 +521,9 @@ bool tiling_for(Tiling& t, int mt, int N, int OH, int OW, int ks) {
 }
 
 // The largest tile (fewest halo rows and filter reads per pixel) that still gives most compute units (192 of 256) a workgroup.  With 96 /
-// 192 / 384 in its place, 5x5 on 15x15, us: batch 24 20.8 / 14.0 / 14.1, 48 27.0 / 21.0 / 19.0, 96 28.0 / 27.5 / 31.0, 128 31.0 / 30.8 /
-// 34.1, 160 55 / 55 / 48; 3x3 on 7x7: batch 96 9.1 / 6.7 / 6.7, 256 13.7 / 9.5 / 9.3.
+// 192 / 384 in its place, 5x5 on 15x15, us: batch 24 21.4 / 14.0 / 13.9, 48 27.0 / 21.9 / 19.2, 96 27.4 / 27.2 / 30.9, 128 33.7 / 32.6 /
+// 35.3, 130 49.7 / 49.8 / 47.3, 192 50.2 / 50.2 / 50.8 (walked tiles from 129 images on); 3x3 on 7x7: batch 96 9.2 / 6.8 / 6.8, 256 13.8 /
+// 9.8 / 9.7.
 bool choose_tiling(Tiling& t, int N, int OH, int OW, int OC, int ks) {
     bool have = false;
     for (int mt = 8; mt >= 2; mt /= 2) {

@@ -84,17 +84,36 @@ __global__ __launch_bounds__(THREADS) void filter_planes_kernel(Frag fwd, Frag b
 // workgroups share a compute unit, and with more than one stream eight wavefronts cost 4 % of a step at batch 37.
 // Bound by the matrix cores: 64 -> 64 at 5x5 on 15x15, batch 128, is 2.46 M MFMAs = 17 us of them at 2.4 GHz (the chip runs
 // them at 1.9).  Measured at batch 37 / 128: 18 / 31 us (largest tile with four wavefronts 12 % more).
+// A wavefront fetches a pixel operand as 16-byte reads of 16 pixels side by side in the result, four parts of a pixel each.  LDS has 64
+// banks and serves such a read in four steps of 16 lanes, 0-3, 12-15 and 20-27 in the first: pixels 0-3 and 12-15 of one part, 4-11 of the
+// next (measured read by read).  No two of them share a bank if a pixel takes 32 bytes (mod 64) more than the one before, also where a tile
+// goes on in the next row or image of the result: these are padded to the bank at which their first pixel would have followed.  Rows of
+// 15 pixels, 5x5: 4 steps a read instead of 11 on average with 16 bytes behind a pixel and nothing behind a row.  The reads are not what
+// bounds the kernels, so the gain is small: batch 128 30.4 -> 30.1 us, 512 105.6 -> 103.8; 3x3, 256 channels on 14x14, batch 64 82 -> 80.
+struct LdsPitch { int px, row, image; };       // bytes
+constexpr int BANKS = 256;                     // bytes
+
+LdsPitch lds_pitch(int channels, bool padded, int R, int OW, int ks) {
+    LdsPitch p;
+    p.px = channels * 2 * split::PLANES + (padded ? 32 : 16);
+    p.row = (OW + ks - 1) * p.px;
+    if (padded) p.row += (unsigned)((1 - ks) * p.px) % BANKS;
+    p.image = (R + ks - 1) * p.row;
+    if (padded) p.image += (unsigned)((1 - ks) * p.row) % BANKS;
+    return p;
+}
+
 struct Geom {
     int N, H, W, OH, OW, pad;      // input / output pixel grid of this pass
     int IC, OC;                    // reduction / result channels of this pass
     int R, G, bands;               // output rows per tile, images per tile (G > 1: whole images), tiles per image
+    LdsPitch at;                   // forward / d-input: the tile in LDS
 };
 
 // MT pixel tiles per workgroup; four wavefronts: WP over the pixels, 4 / WP over the 4 channel tiles; HALVES such groups
 template <int MT> struct Waves { static constexpr int WP = MT >= 4 ? 2 : 1, WC = 4 / WP, TP = MT / WP, TC = 4 / WC, HALVES = MT == 8 ? 2 : 1; };
 
 constexpr int ICB = 64;            // reduction channels staged at a time
-constexpr int pitch(int channels) { return channels * 2 * split::PLANES + 16; }      // bytes of a pixel in LDS: 4 words (mod 32) apart
 
 // One pixel's four result channels 16 ct + 4 q ..: bias, addend, ReLU.
 __device__ __forceinline__ void finish_pixel(const floatx4& sum, int ct, long at, const float* __restrict__ bias, const float* __restrict__ add,
@@ -145,7 +164,7 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
                                                              const float* __restrict__ bias, const float* __restrict__ add,
                                                              float* __restrict__ dst, Geom g, int relu) {
     using W = Waves<MT>;
-    constexpr int PITCH = pitch(ICB), PLANE = 2 * ICB, CS = ICB / 32 / W::HALVES;      // CS: steps per tap and block of channels
+    constexpr int PLANE = 2 * ICB, CS = ICB / 32 / W::HALVES;      // CS: steps per tap and block of channels
     constexpr int STEPS = KS * KS * CS, WD = MT == 2 ? 8 : MT == 4 ? 4 : 2, NT = THREADS * W::HALVES;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -165,7 +184,7 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
         asm("" : "+v"(p));              // or the compiler keeps what it worked out above for every tile in registers through the product loop
         const int per = g.R * g.OW, gi = p / per, rest = p - gi * per, r = rest / g.OW, c = rest - r * g.OW;
         const bool ok = gi < g.G && n0 + gi < g.N && r0 + r < g.OH;
-        base[t] = (ok ? ((gi * TH + r) * TW + c) * PITCH : 0) + 16 * q + 64 * half;
+        base[t] = (ok ? gi * g.at.image + r * g.at.row + c * g.at.px : 0) + 16 * q + 64 * half;
         out[t] = ok ? (((long)(n0 + gi) * g.OH + r0 + r) * g.OW + c) * g.OC : -1;
     }
     // Small products have accumulators of their own, except in the largest tile: its halves round each sum half as often, which keeps
@@ -203,29 +222,30 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
         const int total = g.G * TH * TW * (ICB / 4);
         for (int i0 = tid; i0 < total; i0 += LOADS * NT) {
             float4 v[LOADS];
+            int to[LOADS];
 #pragma unroll
             for (int e = 0; e < LOADS; ++e) {
                 const int idx = i0 + e * NT, px = idx / (ICB / 4), c4 = idx % (ICB / 4);
                 const int gi = px / (TH * TW), rest = px - gi * (TH * TW), ty = rest / TW, tx = rest - ty * TW;
                 const int h = r0 + ty - g.pad, w = tx - g.pad;
+                to[e] = gi * g.at.image + ty * g.at.row + tx * g.at.px + 8 * c4;
                 const bool in = idx < total && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;      // images past the last: beyond the buffer
                 v[e] = split::load4(images, in ? 4u * (unsigned)(((gi * g.H + h) * g.W + w) * g.IC + c0 + 4 * c4) : split::OUTSIDE);
             }
 #pragma unroll
             for (int e = 0; e < LOADS; ++e) {
-                const int idx = i0 + e * NT;
-                if (idx >= total) break;
+                if (i0 + e * NT >= total) break;
                 uint2 pl[split::PLANES];
                 split::split4(split::scaled(v[e]), pl);
 #pragma unroll
                 for (int p = 0; p < split::PLANES; ++p)
-                    *reinterpret_cast<uint2*>(lds + idx / (ICB / 4) * PITCH + p * PLANE + 8 * (idx % (ICB / 4))) = pl[p];
+                    *reinterpret_cast<uint2*>(lds + to[e] + p * PLANE) = pl[p];
             }
         }
         uint4 pv[2][W::TP][split::PLANES];
         auto load_p = [&](int buf, int s) {
             s = s < STEPS ? s : STEPS - 1;
-            const int tap = s / CS, off = (tap / KS * TW + tap % KS) * PITCH + s % CS * 64;
+            const int tap = s / CS, off = tap / KS * g.at.row + tap % KS * g.at.px + s % CS * 64;
 #pragma unroll
             for (int t = 0; t < W::TP; ++t)
 #pragma unroll
@@ -311,7 +331,7 @@ __global__ __launch_bounds__(256 * Waves<MT>::HALVES) __attribute__((amdgpu_wave
 // barrier that both pass once a block.  Bound by the matrix cores at two thirds of the rate they hold on such operands alone.  5x5, 64 -> 64
 // on 15x15, one workgroup to a tile / this, us: batch 160 54.4 / 49.4, 256 56.0 / 53.8, 257 80.3 / 70.8, 512 109.7 / 101.8.
 constexpr int LTHREADS = 512, LARGE_LOADS = 4;
-constexpr int LPITCH = pitch(32), LARGE_HALO = LARGE_LOADS * LTHREADS / 8;      // bytes of a pixel, pixels of a tile with its halo at most
+constexpr int LARGE_HALO = LARGE_LOADS * LTHREADS / 8;         // pixels of a tile with its halo at most
 
 template <int KS>
 __global__ __launch_bounds__(LTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void conv_split_large_kernel(const float* __restrict__ src, const uint4* __restrict__ wf,
@@ -331,7 +351,7 @@ __global__ __launch_bounds__(LTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
     for (int t = 0; t < TP; ++t) {
         const int p = (wp * TP + t) * 16 + l16, gi = p / per, rest = p - gi * per, r = rest / g.OW, c = rest - r * g.OW;
-        base[t] = (gi < g.G ? ((gi * TH + r) * TW + c) * LPITCH : 0) + 16 * q;
+        base[t] = (gi < g.G ? gi * g.at.image + r * g.at.row + c * g.at.px : 0) + 16 * q;
     }
     floatx4 acc[TC][TP];
     auto clear = [&]() {
@@ -344,12 +364,14 @@ __global__ __launch_bounds__(LTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     // The thread's staged elements.  Rows above or below a single image fall outside its buffer, as do images past the last.
     float4 rv[LARGE_LOADS];
     unsigned off[LARGE_LOADS];
+    int put[LARGE_LOADS];                                  // where they go in LDS
 #pragma unroll
     for (int e = 0; e < LARGE_LOADS; ++e) {
         const int idx = tid + e * LTHREADS, px = idx >> 3, c4 = idx & 7;
         const int gi = px / (TH * TW), rest = px - gi * (TH * TW), ty = rest / TW, tx = rest - ty * TW, h = ty - g.pad, w = tx - g.pad;
         const bool in = gi < g.G && (unsigned)w < (unsigned)g.W && (g.G == 1 || (unsigned)h < (unsigned)g.H);
         off[e] = in ? 4u * (unsigned)(((gi * g.H + h) * g.W + w) * g.IC + 4 * c4) : split::OUTSIDE;
+        put[e] = (gi < g.G ? gi * g.at.image + ty * g.at.row + tx * g.at.px : g.G * g.at.image) + 8 * c4;      // or behind the tile
     }
     const int staged = (g.G * TH * TW * 8 + 63) / 64;      // wavefronts' worth of elements
     int ft = tile0, fc = 0;                                // tile and channel block of the next fetch
@@ -369,10 +391,8 @@ __global__ __launch_bounds__(LTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         if (wave + 8 * e >= staged) return;
         uint2 pl[split::PLANES];
         split::split4(split::scaled(rv[e]), pl);
-        const int idx = tid + e * LTHREADS;
-        char* to = buf + (idx >> 3) * LPITCH + 8 * (idx & 7);
 #pragma unroll
-        for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(to + p * PLANE) = pl[p];
+        for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(buf + put[e] + p * PLANE) = pl[p];
     };
 
     // Filter planes are fetched two steps before their use, also over the end of a block; pixel operands one step.
@@ -392,7 +412,7 @@ __global__ __launch_bounds__(LTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         }
     };
     auto load_p = [&](int buf, int tap, const char* from) {
-        const int o = (tap / KS * TW + tap % KS) * LPITCH;
+        const int o = tap / KS * g.at.row + tap % KS * g.at.px;
 #pragma unroll
         for (int t = 0; t < TP; ++t)
 #pragma unroll
@@ -499,10 +519,8 @@ __global__ __launch_bounds__(LTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 }
 
 // Tile of one launch: the number of 16-pixel tiles per workgroup, its rows and images.
-struct Tiling { int mt, R, G, bands, blocks; size_t lds; };
+struct Tiling { int mt, R, G, bands, blocks; LdsPitch at; size_t lds; };
 constexpr int UNITS = 256;         // compute units, one workgroup of the largest tile each
-
-size_t tile_bytes(int G, int R, int OW, int ks) { return (size_t)G * (R + ks - 1) * (OW + ks - 1) * pitch(ICB); }
 
 bool tiling_for(Tiling& t, int mt, int N, int OH, int OW, int ks) {
     const int px = 16 * mt;
@@ -513,8 +531,11 @@ bool tiling_for(Tiling& t, int mt, int N, int OH, int OW, int ks) {
     t.R = ceil_div(OH, t.bands);                          // even bands
     t.G = t.bands == 1 ? px / (OH * OW) : 1;
     if (t.G > N) t.G = N;
-    while (t.G > 1 && tile_bytes(t.G, t.R, OW, ks) > LDS_MAX) --t.G;
-    t.lds = tile_bytes(t.G, t.R, OW, ks);
+    t.at = lds_pitch(ICB, false, t.R, OW, ks);
+    while (t.G > 1 && (size_t)t.G * t.at.image > LDS_MAX) --t.G;
+    const LdsPitch padded = lds_pitch(ICB, true, t.R, OW, ks);
+    if ((size_t)t.G * padded.image <= LDS_MAX) t.at = padded;         // never a smaller tile for it
+    t.lds = (size_t)t.G * t.at.image;
     if (mt == 8 && t.lds < 32 * 1024) t.lds = 32 * 1024;  // exchange of sums: four matrix-core tiles of each of the eight wavefronts
     t.blocks = ceil_div(N, t.G) * t.bands;
     return t.lds <= LDS_MAX;
@@ -548,6 +569,9 @@ int launch_tile(hipStream_t s, const float* src, const uint4* wf, const float* b
     return DSSPK_LAUNCH_RC();
 }
 
+// Bytes of one of its two buffers: the tile and a pixel behind it, or the exchange (four matrix-core tiles of every wavefront).
+int large_buffer(const Geom& g) { return std::max(g.G * g.at.image + g.at.px, 32 * 1024); }
+
 template <int KS>
 int launch_large(hipStream_t s, const float* src, const uint4* wf, const float* bias, const float* add, float* dst, const Geom& g, int relu,
                  const Tiling& t) {
@@ -559,10 +583,9 @@ int launch_large(hipStream_t s, const float* src, const uint4* wf, const float* 
     }
     // as many tiles to a workgroup as there would be rounds of workgroups
     const int per = ceil_div(t.blocks, std::max(1, UNITS / (g.OC / 64)));
-    constexpr int BUFFER = LARGE_HALO * LPITCH;
-    static_assert(BUFFER >= 32 * 1024, "room for the exchange: four matrix-core tiles of every wavefront");
-    hipLaunchKernelGGL(kern, dim3(ceil_div(t.blocks, per), g.OC / 64), dim3(LTHREADS), 2 * BUFFER, s, src, wf, bias, add, dst, g, relu, t.blocks, per,
-                       BUFFER);
+    const int buffer = large_buffer(g);
+    hipLaunchKernelGGL(kern, dim3(ceil_div(t.blocks, per), g.OC / 64), dim3(LTHREADS), 2 * buffer, s, src, wf, bias, add, dst, g, relu, t.blocks, per,
+                       buffer);
     return DSSPK_LAUNCH_RC();
 }
 
@@ -577,8 +600,11 @@ int launch_conv(hipStream_t s, const float* src, const uint4* wf, const float* b
     if (!choose_tiling(t, g.N, g.OH, g.OW, g.OC, ks)) return -1;
     g.R = t.R; g.G = t.G; g.bands = t.bands;
 #define GO(MT) return ks == 5 ? launch_tile<MT, 5>(s, src, wf, bias, add, dst, g, relu, t) : launch_tile<MT, 3>(s, src, wf, bias, add, dst, g, relu, t)
-    if (walks_tiles(t, g, ks))
+    if (walks_tiles(t, g, ks)) {
+        g.at = lds_pitch(32, true, g.R, g.OW, ks);         // (63 KB a buffer at most, over all tiles of LARGE_HALO pixels)
         return ks == 5 ? launch_large<5>(s, src, wf, bias, add, dst, g, relu, t) : launch_large<3>(s, src, wf, bias, add, dst, g, relu, t);
+    }
+    g.at = t.at;
     if (t.mt == 8) GO(8);
     if (t.mt == 4) GO(4);
     GO(2);

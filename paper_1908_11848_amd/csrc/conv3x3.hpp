@@ -29,6 +29,7 @@
 #include "split.hpp"
 #include "bn_merge.hpp"
 #include "jobs.hpp"
+#include "conv3x3_filter.hpp"
 
 namespace {
 
@@ -192,9 +193,10 @@ __device__ __forceinline__ float channel_sum(float s, float* red, int tid) {
     return t;
 }
 
-template <int C, int HW, int R, int NSPLIT, int WAVES, bool TRANSPOSED, int PRE, bool POST = false, bool WG = false>
+// PL: the filter's operands are there already, see conv3x3_filter.hpp
+template <int C, int HW, int R, int NSPLIT, int WAVES, bool TRANSPOSED, int PRE, bool POST, bool WG, bool PL>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_waves<C, WAVES, WG, Cfg<C, HW, R, NSPLIT, WAVES>::NT>()))) void conv3x3_kernel(
-    const float* __restrict__ src, const float* __restrict__ wgt, const float* add, float* dst, float* __restrict__ bn_partial, PreBn pre,
+    const float* __restrict__ src, const float* __restrict__ wgt, const uint4* __restrict__ planes, const float* add, float* dst, float* __restrict__ bn_partial, PreBn pre,
     PostBn post, BwdBn bwd, int conv_blocks, jobs::ReduceJob rj, WgradFused wg) {
     using K = Cfg<C, HW, R, NSPLIT, WAVES>;
     constexpr int THREADS = K::THREADS, V = K::V, NL = K::NL;
@@ -238,31 +240,48 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     //      One filter column (three taps) at a time: the product loop walks the columns, and a row of the next one is
     //      fetched while the loop still works with that row of the present one.
     constexpr int FV = C == 16 ? 1 : 2;
-    float4 fr[K::COLUMNS][3][FV];
-    split::Filt<C> filt[3];
+    float4 fr[PL ? 1 : K::COLUMNS][3][FV];
+    split::Filt<C> filt[PL ? K::COLUMNS : 1][3];
     unsigned filter_at;
-    {
+    if constexpr (PL) {
+        const Role r = role_of(tid);
+        filter_at = ((C == 64 ? 4 * r.ks : 0) + r.co_w / 16) * 192 + r.lane;
+    } else {
         const Role r = role_of(tid);
         const int k0 = C == 16 ? 4 * r.q : 32 * r.ks + 8 * r.q;
         filter_at = TRANSPOSED ? (r.co_w + r.l16) * C + k0 : k0 * C + r.co_w + r.l16;
     }
     auto load_filter = [&](int ky, int kx) {
+        const int tap = 3 * ky + kx;
+        if constexpr (PL) {
 #pragma unroll
-        for (int e = 0; e < FV; ++e) {
-            const int tap = 3 * ky + kx;
-            if constexpr (TRANSPOSED) {
-                fr[kx % K::COLUMNS][ky][e] = load4(wgt + (8 - tap) * C * C + 4 * e, filter_at);
-            } else {
-                const float* wp = wgt + tap * C * C + 4 * e * C;
-                fr[kx % K::COLUMNS][ky][e] = make_float4((wp + 0 * C)[filter_at], (wp + 1 * C)[filter_at], (wp + 2 * C)[filter_at], (wp + 3 * C)[filter_at]);
+            for (int p = 0; p < 3; ++p)
+                filt[kx % K::COLUMNS][ky].v[p] = (planes + (tap * (filter3x3_operands(C) / 9) * 3 + p) * 64)[filter_at];
+        } else {
+#pragma unroll
+            for (int e = 0; e < FV; ++e) {
+                if constexpr (TRANSPOSED) {
+                    fr[kx % K::COLUMNS][ky][e] = load4(wgt + (8 - tap) * C * C + 4 * e, filter_at);
+                } else {
+                    const float* wp = wgt + tap * C * C + 4 * e * C;
+                    fr[kx % K::COLUMNS][ky][e] = make_float4((wp + 0 * C)[filter_at], (wp + 1 * C)[filter_at], (wp + 2 * C)[filter_at], (wp + 3 * C)[filter_at]);
+                }
             }
         }
     };
     auto split_filter = [&](int ky, int kx) {
-        float4 (&f)[FV] = fr[kx % K::COLUMNS][ky];
+        if constexpr (!PL) {
+            float4 (&f)[FV] = fr[kx % K::COLUMNS][ky];
 #pragma unroll
-        for (int e = 0; e < FV; ++e) f[e] = split::scaled(f[e]);
-        filt[ky] = split::filter_operand<C>(f);
+            for (int e = 0; e < FV; ++e) f[e] = split::scaled(f[e]);
+            filt[0][ky] = split::filter_operand<C>(f);
+        }
+    };
+    auto first_columns = [&]() {
+#pragma unroll
+        for (int kx = 0; kx < K::COLUMNS; ++kx)
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky) load_filter(ky, kx);
     };
     // EARLY: what the loader needs of the batch norm (PRE 1, 2: of this thread's channels; 3: of channel tid)
     float4 norm_g = make_float4(0.f, 0.f, 0.f, 0.f), norm_b = norm_g;
@@ -278,10 +297,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         if (pre.merge) load_records<C, THREADS>(rec, pre.records, pre.L.G, tid);
     if constexpr (PRE == 3)
         if (!bwd.totals) load_records<C, THREADS>(rec, bwd.records, bwd.parts, tid);
-#pragma unroll
-    for (int kx = 0; kx < K::COLUMNS; ++kx)
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky) load_filter(ky, kx);
+    if constexpr (!PL) first_columns();
     // ---- input halo tile, zero outside the image.  The raw loads are issued first; the first filter column is split while
     //      they are in flight.
     float4 val[NL], scv[PRE >= 2 ? NL : 1];
@@ -317,6 +333,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             if constexpr (PRE == 3) scv[e] = load4(bwd.xc + tile_at + e * STEP, 4u * tid);
         }
     }
+    if constexpr (PL) first_columns();          // the tile is needed before them
     // what the epilogue adds, masks with and sums over, a lane's four channels of its pixel of every tile: all these loads together (dst may
     // alias add, so the compiler cannot move them across the stores itself)
     float4 mu_c = make_float4(0.f, 0.f, 0.f, 0.f), is_c = mu_c, addv[K::WM], maskv[POST ? K::WM : 1], xcv[POST ? K::WM : 1];
@@ -493,7 +510,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
 #pragma unroll
             for (int ky = 0; ky < 3; ++ky) {
                 if (i % ST == (LAST + ky + 1) % ST && kx + (ky < 2) >= 1 && kx + (ky < 2) <= 2) split_filter(ky, kx + (ky < 2));
-                if (K::COLUMNS == 1 && st == LAST + ky - 1 && kx < 2) load_filter(ky, kx + 1);
+                if (!PL && K::COLUMNS == 1 && st == LAST + ky - 1 && kx < 2) load_filter(ky, kx + 1);
             }
             if (i + 1 < 3 * ST) x[(i + 1) & 1] = pixels(i + 1);
             __builtin_amdgcn_sched_barrier(0);      // or the compiler moves the reads down to their use, behind the products
@@ -504,9 +521,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
                     const int ky = st - K::TROWS * t;
                     if (ky < 0 || ky > 2) continue;
                     floatx4& to = p + 1 < split::products<C>() ? lo[t] : a[t];
-                    to = split::product<C>(p, filt[ky], x[i & 1], to);
+                    to = split::product<C>(p, filt[PL ? kx % K::COLUMNS : 0][ky], x[i & 1], to);
                 }
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (PL && K::COLUMNS == 1)        // into the registers of the row that has just been used for the last time
+                if (st >= LAST && kx < 2) load_filter(st - LAST, kx + 1);
         }
         mma::drain();
 #pragma unroll
@@ -789,15 +808,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     }
 }
 
-template <int C, int HW, int R, int NSPLIT, int WAVES, bool T, int PRE = 0, bool POST = false, bool WG = false>
-int launch(hipStream_t s, const float* src, const float* w, const float* add, float* dst, float* bn_partial, int N,
-           const PreBn& pre = PreBn{}, const PostBn& post = PostBn(), const BwdBn& bwd = BwdBn(),
-           const jobs::ReduceJob& rj = jobs::ReduceJob(), const WgradFused& wg = WgradFused()) {
+template <bool PL, int C, int HW, int R, int NSPLIT, int WAVES, bool T, int PRE, bool POST, bool WG>
+int launch_form(hipStream_t s, const float* src, const Filter3x3& w, const float* add, float* dst, float* bn_partial, int N,
+           const PreBn& pre, const PostBn& post, const BwdBn& bwd, const jobs::ReduceJob& rj, const WgradFused& wg) {
     using K = Cfg<C, HW, R, NSPLIT, WAVES>;
     constexpr size_t LDS_BYTES = WG ? K::LDS_BYTES_WG : K::LDS_BYTES;
     static_assert(LDS_BYTES >= jobs::LDS_FLOATS * (K::THREADS / jobs::THREADS) * sizeof(float), "room for a carried job");
     static bool attr_set = false;       // raise the dynamic-LDS limit once per instantiation
-    auto kern = conv3x3_kernel<C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG>;
+    auto kern = conv3x3_kernel<C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG, PL>;
     if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)LDS_BYTES) != hipSuccess)
@@ -805,9 +823,17 @@ int launch(hipStream_t s, const float* src, const float* w, const float* add, fl
         attr_set = true;
     }
     const int conv_blocks = N * (HW / R) * NSPLIT;
-    hipLaunchKernelGGL(kern, dim3(conv_blocks + rj.blocks), dim3(K::THREADS), LDS_BYTES, s, src, w, add, dst, bn_partial, pre, post,
+    hipLaunchKernelGGL(kern, dim3(conv_blocks + rj.blocks), dim3(K::THREADS), LDS_BYTES, s, src, w.w, w.planes, add, dst, bn_partial, pre, post,
                        bwd, conv_blocks, rj, wg);
     return (int)hipGetLastError();
+}
+
+template <int C, int HW, int R, int NSPLIT, int WAVES, bool T, int PRE = 0, bool POST = false, bool WG = false>
+int launch(hipStream_t s, const float* src, const Filter3x3& w, const float* add, float* dst, float* bn_partial, int N, const PreBn& pre = PreBn{},
+           const PostBn& post = PostBn(), const BwdBn& bwd = BwdBn(), const jobs::ReduceJob& rj = jobs::ReduceJob(), const WgradFused& wg = WgradFused()) {
+    if constexpr (!T || PRE == 3)           // what a network's step launches
+        if (w.planes) return launch_form<true, C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG>(s, src, w, add, dst, bn_partial, N, pre, post, bwd, rj, wg);
+    return launch_form<false, C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG>(s, src, w, add, dst, bn_partial, N, pre, post, bwd, rj, wg);
 }
 
 // The reduction job a launch carries, and the workgroups (of `threads` threads) given to it.

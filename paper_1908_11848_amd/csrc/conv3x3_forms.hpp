@@ -2,6 +2,7 @@
 // images at most), behind dsspk_conv3x3_large_* and dsspk_conv3x3_small_*.
 #pragma once
 #include "conv3x3.hpp"
+#include "conv3x3_layers.hpp"
 
 namespace {
 
@@ -16,7 +17,7 @@ template <class F> bool form_merges(int parts, int C) {
 }
 
 template <class F, int PRE>
-int form_launch(hipStream_t s, const float* src, const float* w, float* dst, float* records_out, int N, int C, const PreBn& pre) {
+int form_launch(hipStream_t s, const float* src, const Filter3x3& w, float* dst, float* records_out, int N, int C, const PreBn& pre) {
     if (C == 16) return launch<16, 32, F::R16, 1, F::WAVES, false, PRE>(s, src, w, nullptr, dst, records_out, N, pre);
     if (C == 32) return launch<32, 16, F::R32, 1, F::WAVES, false, PRE>(s, src, w, nullptr, dst, records_out, N, pre);
     return launch<64, 8, 8, F::SPLIT64, F::WAVES, false, PRE>(s, src, w, nullptr, dst, records_out, N, pre);
@@ -24,9 +25,9 @@ int form_launch(hipStream_t s, const float* src, const float* w, float* dst, flo
 
 template <class F>
 int form_fwd(void* stream, const float* src, const float* records, int parts, const float* gamma, const float* beta, float eps,
-             const float* shortcut, float* act_out, float* stats_out, const float* w, float* dst, float* records_out, int shortcut_half, int N,
+             const float* shortcut, float* act_out, float* stats_out, const Filter3x3& w, float* dst, float* records_out, int shortcut_half, int N,
              int H, int C) {
-    if (!src || !w || !dst || !records_out || dst == src || form_parts<F>(N, H, C) == 0) return -1;
+    if (!src || !w.w || !dst || !records_out || dst == src || form_parts<F>(N, H, C) == 0) return -1;
     if (shortcut_half && (!shortcut || C <= 16)) return -1;
     PreBn pre{};
     pre.half = shortcut_half != 0;
@@ -49,10 +50,10 @@ int form_fwd(void* stream, const float* src, const float* records, int parts, co
 
 template <class F>
 int form_bwd(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma, const float* in_records, int parts,
-             float* dgamma, float* dbeta, float* dx, float* partial, const float* w, const float* add, float* out, const float* x_in,
+             float* dgamma, float* dbeta, float* dx, float* partial, const Filter3x3& w, const float* add, float* out, const float* x_in,
              const float* xc_post, const float* stats_post, float* records, const float* red_partial, float* red_dw, int red_E, int red_chunks,
              int N, int H, int C) {
-    if (!dz || !xc || !stats || !gamma || !in_records || !dgamma || !dbeta || !w || !out || !x_in || !xc_post || !stats_post || !records) return -1;
+    if (!dz || !xc || !stats || !gamma || !in_records || !dgamma || !dbeta || !w.w || !out || !x_in || !xc_post || !stats_post || !records) return -1;
     if (form_parts<F>(N, H, C) == 0 || !form_merges<F>(parts, C) || in_records == records || out == dz) return -1;
     if (C == 64 ? !dx || partial || dx == dz || dx == out : dx || !partial || partial == red_partial) return -1;
     if (red_partial && (!red_dw || red_E < 4 || red_E % 4 || red_chunks < 1)) return -1;
@@ -73,18 +74,32 @@ int form_bwd(void* stream, const float* dz, const float* xc, const float* stats,
 }  // namespace
 
 #define DSSPK_CONV3X3_FORM(NAME, F)                                                                                                                \
+    int conv3x3_##NAME##_fwd(void* stream, const float* src, const float* records, int parts, const float* gamma, const float* beta,              \
+                             float eps, const float* shortcut, float* act_out, float* stats_out, const Filter3x3& w, float* dst,                   \
+                             float* records_out, int shortcut_half, int N, int H, int C) {                                                         \
+        return form_fwd<F>(stream, src, records, parts, gamma, beta, eps, shortcut, act_out, stats_out, w, dst, records_out, shortcut_half, N, H, \
+                           C);                                                                                                                     \
+    }                                                                                                                                              \
+    int conv3x3_##NAME##_bwd(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,                              \
+                             const float* in_records, int parts, float* dgamma, float* dbeta, float* dx, float* partial,                           \
+                             const Filter3x3& w, const float* add, float* out, const float* x_in, const float* xc_post,                            \
+                             const float* stats_post, float* records, const float* red_partial, float* red_dw, int red_E, int red_chunks,          \
+                             int N, int H, int C) {                                                                                                \
+        return form_bwd<F>(stream, dz, xc, stats, gamma, in_records, parts, dgamma, dbeta, dx, partial, w, add, out, x_in, xc_post, stats_post,   \
+                           records, red_partial, red_dw, red_E, red_chunks, N, H, C);                                                              \
+    }                                                                                                                                              \
     extern "C" int dsspk_conv3x3_##NAME##_parts(int N, int H, int C) { return form_parts<F>(N, H, C); }                                            \
     extern "C" int dsspk_conv3x3_##NAME##_fwd(void* stream, const float* src, const float* records, int parts, const float* gamma,                \
                                               const float* beta, float eps, const float* shortcut, float* act_out, float* stats_out,              \
                                               const float* w, float* dst, float* records_out, int shortcut_half, int N, int H, int C) {           \
-        return form_fwd<F>(stream, src, records, parts, gamma, beta, eps, shortcut, act_out, stats_out, w, dst, records_out, shortcut_half, N, H, \
-                           C);                                                                                                                     \
+        return conv3x3_##NAME##_fwd(stream, src, records, parts, gamma, beta, eps, shortcut, act_out, stats_out, w, dst, records_out,             \
+                                    shortcut_half, N, H, C);                                                                                       \
     }                                                                                                                                              \
     extern "C" int dsspk_conv3x3_##NAME##_bwd(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,             \
                                               const float* in_records, int parts, float* dgamma, float* dbeta, float* dx, float* partial,         \
                                               const float* w, const float* add, float* out, const float* x_in, const float* xc_post,              \
                                               const float* stats_post, float* records, const float* red_partial, float* red_dw, int red_E,        \
                                               int red_chunks, int N, int H, int C) {                                                               \
-        return form_bwd<F>(stream, dz, xc, stats, gamma, in_records, parts, dgamma, dbeta, dx, partial, w, add, out, x_in, xc_post, stats_post,   \
-                           records, red_partial, red_dw, red_E, red_chunks, N, H, C);                                                              \
+        return conv3x3_##NAME##_bwd(stream, dz, xc, stats, gamma, in_records, parts, dgamma, dbeta, dx, partial, w, add, out, x_in, xc_post,      \
+                                    stats_post, records, red_partial, red_dw, red_E, red_chunks, N, H, C);                                         \
     }

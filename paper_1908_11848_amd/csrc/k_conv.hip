@@ -12,32 +12,8 @@
 // slice prefetched into registers while the matrix cores work on the current one).
 #include "mma.hpp"
 #include "jobs.hpp"
+#include "conv3x3_layers.hpp"
 #include "../../include/dssp_kernels.h"
-
-// Specialised 3x3 / stride 1 / Cin = Cout kernels (k_conv3x3.hip); -2 = shape not covered.
-int conv3x3_tiled(hipStream_t s, const float* src, const float* w, const float* add, float* dst, float* bn_partial,
-                   int N, int HW, int C, bool transposed);
-int conv3x3_tiled_stat_parts(int N, int HW, int C);
-int conv3x3_tiled_dgrad_post(hipStream_t s, const float* dy, const float* w, const float* add, float* dz,
-                              const float* mask_src, const float* xc, const float* stats, float* records, int N, int HW, int C);
-int conv3x3_tiled_prebn(hipStream_t s, const float* src, const float* records, int in_parts, const float* gamma,
-                         const float* beta, float eps, const float* shortcut, bool half, float* act_out, float* stats_out,
-                         const float* w, float* dst, float* bn_partial, int N, int HW, int C);
-int wgrad3x3_tiled_parts(int N, int HW, int C);
-int wgrad3x3_tiled(hipStream_t s, const float* x, const float* dy, float* partial, int N, int HW, int C, const jobs::TotalsJob& tj);
-// The batch norm's sums: totals, or (totals null) parts records to add up, dgamma and dbeta stored from them.
-bool conv3x3_records_inline(int parts, int C);
-int conv3x3_tiled_dgrad_bn(hipStream_t s, const float* dz, const float* xc, const float* stats, const float* gamma,
-                            const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta, float* dx_out,
-                            const float* w, const float* add, float* out,
-                            const float* mask_src, const float* xc_post, const float* stats_post, float* records,
-                            const float* red_partial, float* red_dw, int red_E, int red_chunks, int N, int HW, int C);
-int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc, const float* stats, const float* gamma,
-                                  const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta,
-                                  const float* w, const float* add, float* out,
-                                  const float* xc_post, const float* stats_post, float* records,
-                                  const float* x_in, float* partial, const float* red_partial, float* red_dw, int red_E,
-                                  int red_chunks, int N, int HW, int C);
 
 namespace {
 
@@ -95,12 +71,15 @@ __device__ __forceinline__ bool src_pixel(const ConvGeom& g, int oh, int ow, int
 //   KS   : k-chunks of 16 per LDS stage (VEC only; IC a multiple of 16 * KS).  A stage is one barrier, one round of
 //          address arithmetic and one round of global loads, so wide layers take KS = 2: half the barriers and
 //          half the vector instructions per MFMA (fp32 MFMA and vector arithmetic do not overlap on this chip).
+//   Job: workgroups behind the kernel's own convert the filters of later layers (FilterJob).
 //   EXTRA: the epilogue also leaves statistics records (forward) or adds a shortcut's gradient (DGRAD).  Instances of their own: with the
 //          question asked inside, calls without it took up to 5 % longer (16 -> 32 channels, stride 2, 32x32, batch 64: 7.1 -> 7.5 us).
-template <int BM, int BN, bool DGRAD, bool VEC, int KS, bool EXTRA>
+template <int BM, int BN, bool DGRAD, bool VEC, int KS, bool EXTRA, class... Job>
 __global__ __launch_bounds__(THREADS) void conv_igemm_kernel(const float* __restrict__ src, const float* __restrict__ wgt,
                                                              const float* __restrict__ bias, const float* __restrict__ add,
-                                                             float* __restrict__ dst, ConvGeom g, int relu, int mode, float* __restrict__ extra) {
+                                                             float* __restrict__ dst, ConvGeom g, int relu, int mode, float* __restrict__ extra, Job... job) {
+    if constexpr (sizeof...(Job) > 0)
+        if ((..., ((int)blockIdx.x >= job.own_blocks))) return (..., convert_filters(job, blockIdx.x - job.own_blocks));
     static_assert(KS == 1 || VEC, "several k-chunks per stage only with 16-byte gathers");
     constexpr int WM = BM / 64, WN = BN / 16;
     constexpr int KST = mma::KC * KS;                              // reduction indices per stage
@@ -736,14 +715,14 @@ constexpr size_t igemm_lds_bytes() {
     return sizeof(float) * 2 * ((size_t)BM * LDA + (DGRAD ? (size_t)BN * LDA : (size_t)KST * (BN + 4)));
 }
 
-template <int BM, int BN, bool DGRAD, bool VEC, int KS, bool EXTRA>
+template <int BM, int BN, bool DGRAD, bool VEC, int KS, bool EXTRA, class... Job>
 int igemm_launch(dim3 grid, hipStream_t s, const float* src, const float* w, const float* bias, const float* add, float* dst,
-                 const ConvGeom& g, int relu, bool parity, float* extra) {
+                 const ConvGeom& g, int relu, bool parity, float* extra, const Job&... job) {
     // staged gather: forward, element-wise, stride 1, tiles of whole rows of one image, the rows they touch within the LDS budget
     const bool staged = !VEC && !DGRAD && g.stride == 1 && g.OW <= BM && BM % g.OW == 0 && ((long)g.OH * g.OW) % BM == 0 &&
                         (long)(BM / g.OW + g.KH - 1) * (g.SW + 2 * g.pad) * g.IC <= IGEMM_IMG_MAX;
     const size_t bytes = igemm_lds_bytes<BM, BN, DGRAD, KS>() + (staged ? sizeof(float) * IGEMM_IMG_MAX : 0);
-    auto kern = conv_igemm_kernel<BM, BN, DGRAD, VEC, KS, EXTRA>;
+    auto kern = conv_igemm_kernel<BM, BN, DGRAD, VEC, KS, EXTRA, Job...>;
     static bool attr_set = false;       // raise the dynamic-LDS limit once per instantiation
     if (!attr_set) {
         constexpr size_t most = igemm_lds_bytes<BM, BN, DGRAD, KS>() + (VEC ? 0 : sizeof(float) * IGEMM_IMG_MAX);
@@ -752,7 +731,7 @@ int igemm_launch(dim3 grid, hipStream_t s, const float* src, const float* w, con
             return -1;
         attr_set = true;
     }
-    hipLaunchKernelGGL(kern, grid, dim3(THREADS), bytes, s, src, w, bias, add, dst, g, relu, staged ? IGEMM_STAGED : parity ? IGEMM_PARITY : 0, extra);
+    hipLaunchKernelGGL(kern, grid, dim3(THREADS), bytes, s, src, w, bias, add, dst, g, relu, staged ? IGEMM_STAGED : parity ? IGEMM_PARITY : 0, extra, job...);
     return 0;
 }
 
@@ -844,6 +823,17 @@ extern "C" int dsspk_conv_fwd_records(void* stream, const float* x, const float*
     if (!geom(g, N, H, W, Cin, Cout, KH, KW, stride, pad)) return -1;
     if (Cin % 16 == 0) return launch_igemm<false, true>((hipStream_t)stream, x, w, nullptr, nullptr, y, g, 0, records);
     return launch_igemm<false, false>((hipStream_t)stream, x, w, nullptr, nullptr, y, g, 0, records);
+}
+
+int conv_stem(hipStream_t s, const float* x, const float* w, float* y, float* records, int N, FilterJob job) {
+    ConvGeom g;
+    if (!geom(g, N, 32, 32, 3, 16, 3, 3, 1, 1)) return -1;
+    job.own_blocks = ceil_div(g.M, igemm_small(g) ? 64 : 128);
+    const dim3 grid(job.own_blocks + job.blocks());
+#define GO(BM, EXTRA) igemm_launch<BM, 16, false, false, 1, EXTRA>(grid, s, x, w, nullptr, nullptr, y, g, 0, false, records, job)
+    if (igemm_small(g) ? (records ? GO(64, true) : GO(64, false)) : (records ? GO(128, true) : GO(128, false))) return -1;
+#undef GO
+    return DSSPK_LAUNCH_RC();
 }
 
 static int conv_fwd_prebn(void* stream, const float* src, const float* records, int in_parts, const float* gamma,

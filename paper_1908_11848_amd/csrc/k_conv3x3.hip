@@ -1,6 +1,7 @@
 // The 3x3 kernels of conv3x3.hpp with four wavefronts to a workgroup behind the launchers of the raw layers, the small kernel that
 // merges statistics records, and the d-filter kernels of their own.
 #include "conv3x3.hpp"
+#include "conv3x3_layers.hpp"
 #include "../../include/dssp_kernels.h"
 
 namespace {
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(THREADS) void records_merge_kernel(const float* __r
 
 // dst = conv(src) (+ add, element-wise, if add != NULL).  Returns -2 if the shape is not one of the
 // specialised ones (the caller then uses the generic kernel).
-int conv3x3_tiled(hipStream_t s, const float* src, const float* w, const float* add, float* dst, float* bn_partial,
+int conv3x3_tiled(hipStream_t s, const float* src, const Filter3x3& w, const float* add, float* dst, float* bn_partial,
                    int N, int HW, int C, bool transposed) {
     if (C == 16 && HW == 32) return transposed ? launch<16, 32, 8, 1, 4, true>(s, src, w, add, dst, bn_partial, N) : launch<16, 32, 8, 1, 4, false>(s, src, w, add, dst, bn_partial, N);
     if (C == 32 && HW == 16) return transposed ? launch<32, 16, 8, 1, 4, true>(s, src, w, add, dst, bn_partial, N) : launch<32, 16, 8, 1, 4, false>(s, src, w, add, dst, bn_partial, N);
@@ -131,7 +132,7 @@ int conv3x3_tiled(hipStream_t s, const float* src, const float* w, const float* 
 // statistics records of src in `records` (as emitted by the forward kernel for the same shape).
 int conv3x3_tiled_prebn(hipStream_t s, const float* src, const float* records, int in_parts, const float* gamma,
                          const float* beta, float eps, const float* shortcut, bool half, float* act_out, float* stats_out,
-                         const float* w, float* dst, float* bn_partial, int N, int HW, int C) {
+                         const Filter3x3& w, float* dst, float* bn_partial, int N, int HW, int C) {
     PreBn pre;
     pre.half = half;
     pre.records = records;
@@ -175,7 +176,7 @@ int conv3x3_tiled_dgrad_post(hipStream_t s, const float* dy, const float* w, con
 // optionally carries the second stage of an earlier d-filter convolution (red_partial != NULL).
 int conv3x3_tiled_dgrad_bn(hipStream_t s, const float* dz, const float* xc, const float* stats, const float* gamma,
                             const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta, float* dx_out,
-                            const float* w, const float* add, float* out,
+                            const Filter3x3& w, const float* add, float* out,
                             const float* mask_src, const float* xc_post, const float* stats_post, float* records,
                             const float* red_partial, float* red_dw, int red_E, int red_chunks, int N, int HW, int C) {
     if (!totals && !records_inline(parts, C)) return -1;
@@ -196,7 +197,7 @@ int conv3x3_tiled_dgrad_bn(hipStream_t s, const float* dz, const float* xc, cons
 // dx is not stored.  Returns -2 for shapes the fused form does not cover (then the two-kernel form applies).
 int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc, const float* stats, const float* gamma,
                                   const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta,
-                                  const float* w, const float* add, float* out,
+                                  const Filter3x3& w, const float* add, float* out,
                                   const float* xc_post, const float* stats_post, float* records,
                                   const float* x_in, float* partial, const float* red_partial, float* red_dw, int red_E,
                                   int red_chunks, int N, int HW, int C) {

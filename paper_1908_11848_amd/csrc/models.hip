@@ -6,6 +6,7 @@
 
 #include "../../include/dssp.h"
 #include "../../include/dssp_kernels.h"
+#include "conv3x3_layers.hpp"
 #include "model.hpp"
 
 namespace dssp_model {
@@ -21,6 +22,7 @@ struct ResBlock {
     int H, cin, cout, stride;              // H: input height = width
     int64_t w1, g1, b1, w2, g2, b2;        // offsets into the flat parameter vector (floats)
     size_t c1, a1, c2, out, st1, st2;      // offsets into the worker's workspace slice (bytes)
+    size_t f1, f2;                         // the converted filters of the two convolutions (conv3x3_filter.hpp), f1 of a stride-1 block
 };
 
 // Bump allocator over one worker's slice of the workspace (256-byte granules).
@@ -59,6 +61,8 @@ struct Plan {
     // ResNet
     std::vector<ResBlock> blocks;
     int64_t stem_w = 0, stem_g = 0, stem_b = 0, fc_w = 0, fc_b = 0;
+    size_t filters = 0;
+    FilterRun filter_runs[3] = {};
     size_t stem_c = 0, stem_a = 0, stem_st = 0, pooled = 0, dpooled = 0, G[3] = {0, 0, 0};
 
     void seg(int kind, int64_t size, int64_t fan_in) { segs.push_back({kind, size, fan_in}); n_params += size; }
@@ -170,6 +174,19 @@ struct Plan {
             fc_w = fc_seg(64, classes); fc_b = fc_w + 64 * (int64_t)classes;
             pooled = a.floats((size_t)m * 64); dpooled = a.floats((size_t)m * 64);
             for (int i = 0; i < 3; ++i) G[i] = a.floats(s0);
+            // A stage's filters of stride-1 convolutions are evenly spaced in the parameters: all of the first stage's, from the second
+            // convolution on in the others.
+            size_t uint4s = 0;
+            for (int st = 0; st < 3; ++st) {
+                const int C = widths[st], per = 9 * C * C + 2 * C;
+                filter_runs[st] = {st ? blocks[st * n].w2 : blocks[0].w1, st ? 2 * n - 1 : 2 * n, per};
+                for (int i = 0; i < filter_runs[st].count; ++i, uint4s += 2 * filter3x3_uint4s(C)) {
+                    const int conv = st ? i + 1 : i;
+                    ResBlock& B = blocks[st * n + conv / 2];
+                    (conv % 2 ? B.f2 : B.f1) = uint4s;
+                }
+            }
+            filters = a.take(uint4s * sizeof(uint4));
         } else {
             return false;
         }
@@ -313,20 +330,23 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
                : small ? dsspk_conv3x3_small_parts(m, H, cin)
                        : dsspk_conv_fwd_stat_parts(m, H, H, cin, cout, 3, 3, stride, 1);
     };
-    auto conv = [&](const float* src, const float* wt, float* dst, int H, int cin, int cout, int stride, float* rec) {
-        if (rec && (cin != cout || stride != 1)) return dsspk_conv_fwd_records(s, src, wt, dst, rec, m, H, H, cin, cout, 3, 3, stride, 1);
+    uint4* planes = (uint4*)(ws + P->filters);
+    auto forward_filter = [&](int64_t at, size_t f) { return Filter3x3(w + at, planes + f); };
+    auto input_filter = [&](int64_t at, size_t f, int C) { return Filter3x3(w + at, planes + f + filter3x3_uint4s(C)); };
+    auto conv = [&](const float* src, const Filter3x3& wt, float* dst, int H, int cin, int cout, int stride, float* rec) {
+        if (rec && (cin != cout || stride != 1)) return dsspk_conv_fwd_records(s, src, wt.w, dst, rec, m, H, H, cin, cout, 3, 3, stride, 1);
         if ((large || small) && rec)
-            return (large ? dsspk_conv3x3_large_fwd : dsspk_conv3x3_small_fwd)(s, src, nullptr, 0, nullptr, nullptr, 0.f, nullptr, nullptr, nullptr, wt,
+            return (large ? conv3x3_large_fwd : conv3x3_small_fwd)(s, src, nullptr, 0, nullptr, nullptr, 0.f, nullptr, nullptr, nullptr, wt,
                                                                               dst, rec, 0, m, H, cin);
-        return dsspk_conv_fwd(s, src, wt, nullptr, dst, m, H, H, cin, cout, 3, 3, stride, 1, 0, rec);
+        if (rec) return conv3x3_tiled((hipStream_t)s, src, wt, nullptr, dst, rec, m, H, cin, false);
+        return dsspk_conv_fwd(s, src, wt.w, nullptr, dst, m, H, H, cin, cout, 3, 3, stride, 1, 0, nullptr);
     };
     auto conv_prebn = [&](const float* src, const float* rec, int parts, const float* gamma, const float* beta, const float* shortcut, float* act,
-                          float* stats, const float* wt, float* dst, float* rec_out, int H, int C, bool half = false) {
+                          float* stats, const Filter3x3& wt, float* dst, float* rec_out, int H, int C, bool half = false) {
         if (large || small)
-            return (large ? dsspk_conv3x3_large_fwd : dsspk_conv3x3_small_fwd)(s, src, rec, parts, gamma, beta, eps, shortcut, act, stats, wt, dst,
+            return (large ? conv3x3_large_fwd : conv3x3_small_fwd)(s, src, rec, parts, gamma, beta, eps, shortcut, act, stats, wt, dst,
                                                                               rec_out, half, m, H, C);
-        return (half ? dsspk_conv_fwd_prebn_half : dsspk_conv_fwd_prebn)(s, src, rec, parts, gamma, beta, eps, shortcut, act, stats, wt, dst, rec_out,
-                                                                        m, H, C);
+        return conv3x3_tiled_prebn((hipStream_t)s, src, rec, parts, gamma, beta, eps, shortcut, half, act, stats, wt, dst, rec_out, m, H, C);
     };
     auto regular = [&](int i) {
         const ResBlock& b = P->blocks[i];
@@ -337,7 +357,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     // larger and the list just fits (20 layers, one worker, batch 63 / 64 / 65: 654 / 641 / 687 us; at 65 the first stride-2 convolution's list ends
     // as well).
     const int stem_parts = small && m > 16 ? 0 : parts_of(32, 3, 16, 1);
-    RUN(conv(x, w + P->stem_w, F(P->stem_c), 32, 3, 16, 1, stem_parts ? recB : nullptr));
+    RUN(conv_stem((hipStream_t)s, x, w + P->stem_w, F(P->stem_c), stem_parts ? recB : nullptr, m, FilterJob(w, planes, P->filter_runs)));
     if (!stem_parts)
         RUN(dsspk_bn_fwd(s, F(P->stem_c), w + P->stem_g, w + P->stem_b, F(P->stem_a), F(P->stem_st), bscr, (long)m * 1024, 16, eps, 1, 0, nullptr, 0, 0,
                          0, 0));
@@ -347,26 +367,26 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         const ResBlock& B = P->blocks[bi];
         const int Ho = B.H / B.stride;
         const long M = (long)m * Ho * Ho;
+        const int mode = (B.stride == 1 && B.cin == B.cout) ? 1 : 2;
         const int parts1 = parts_of(B.H, B.cin, B.cout, B.stride);
         const int parts2 = parts_of(Ho, B.cout, B.cout, 1);
         if (pending && bi == 0) {
-            RUN(conv_prebn(F(P->stem_c), recB, stem_parts, w + P->stem_g, w + P->stem_b, nullptr, F(P->stem_a), F(P->stem_st), w + B.w1, F(B.c1), recA, 32,
+            RUN(conv_prebn(F(P->stem_c), recB, stem_parts, w + P->stem_g, w + P->stem_b, nullptr, F(P->stem_a), F(P->stem_st), forward_filter(B.w1, B.f1), F(B.c1), recA, 32,
                            16));
         } else if (pending) {
             const ResBlock& Pv = P->blocks[bi - 1];
             const float* pin = bi >= 2 ? F(P->blocks[bi - 2].out) : F(P->stem_a);         // the previous block's input = its shortcut
-            RUN(conv_prebn(F(Pv.c2), recB, parts2, w + Pv.g2, w + Pv.b2, pin, F(Pv.out), F(Pv.st2), w + B.w1, F(B.c1), recA, B.H, B.cin, Pv.stride == 2));
+            RUN(conv_prebn(F(Pv.c2), recB, parts2, w + Pv.g2, w + Pv.b2, pin, F(Pv.out), F(Pv.st2), forward_filter(B.w1, B.f1), F(B.c1), recA, B.H, B.cin, Pv.stride == 2));
         } else {
-            RUN(conv(cur, w + B.w1, F(B.c1), B.H, B.cin, B.cout, B.stride, parts1 ? recA : nullptr));
+            RUN(conv(cur, mode == 1 ? forward_filter(B.w1, B.f1) : Filter3x3(w + B.w1), F(B.c1), B.H, B.cin, B.cout, B.stride, parts1 ? recA : nullptr));
         }
         if (parts1 && parts2) {
-            RUN(conv_prebn(F(B.c1), recA, parts1, w + B.g1, w + B.b1, nullptr, F(B.a1), F(B.st1), w + B.w2, F(B.c2), recB, Ho, B.cout));
+            RUN(conv_prebn(F(B.c1), recA, parts1, w + B.g1, w + B.b1, nullptr, F(B.a1), F(B.st1), forward_filter(B.w2, B.f2), F(B.c2), recB, Ho, B.cout));
         } else {
             RUN(dsspk_bn_fwd(s, F(B.c1), w + B.g1, w + B.b1, F(B.a1), F(B.st1), recA, M, B.cout, eps, 1, 0, nullptr, 0, 0, 0, parts1));
-            RUN(conv(F(B.a1), w + B.w2, F(B.c2), Ho, B.cout, B.cout, 1, parts2 ? recB : nullptr));
+            RUN(conv(F(B.a1), forward_filter(B.w2, B.f2), F(B.c2), Ho, B.cout, B.cout, 1, parts2 ? recB : nullptr));
         }
         pending = parts2 > 0 && bi + 1 < nb && regular(bi + 1);
-        const int mode = (B.stride == 1 && B.cin == B.cout) ? 1 : 2;
         if (bi + 1 == nb) {
             RUN(dsspk_bn_fwd_gap(s, F(B.c2), w + B.g2, w + B.b2, F(B.out), F(B.st2), recB, parts2, cur, mode == 2, F(P->pooled), m, Ho, B.cout, eps));
         } else if (!pending) {
@@ -434,7 +454,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     // sum_next: the records just written are summed into ntot / ndgamma / ndbeta for the next layer.
     auto regular_layer = [&](const float* in_rec, int in_parts, float* in_dgamma, float* in_dbeta, bool ready,
                              const float* dz, const float* xc, const float* st, const float* gamma, float* tot,
-                             const float* wt, const float* add, float* out, const float* x_in, const float* xc_post,
+                             const Filter3x3& wt, const float* add, float* out, const float* x_in, const float* xc_post,
                              const float* st_post, float* records, float* dw, int H, int Cc, bool sum_next, int nparts,
                              float* ntot, float* ndgamma, float* ndbeta) -> int {
         float* out_scr = free_scr();
@@ -445,7 +465,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         if (carry) pop_front();
         if (large || small) {
             int chunks = parts_of(H, Cc, Cc, 1);
-            const auto bwd = large ? dsspk_conv3x3_large_bwd : dsspk_conv3x3_small_bwd;
+            const auto bwd = large ? conv3x3_large_bwd : conv3x3_small_bwd;
             RUN(bwd(s, dz, xc, st, gamma, in_rec, in_parts, in_dgamma, in_dbeta, Cc == 64 ? g1 : nullptr, Cc == 64 ? nullptr : out_scr, wt, add, out,
                     x_in, xc_post, st_post, records, rp, rdw, rE, rchunks, m, H, Cc));
             if (Cc == 64) RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, nullptr, 0, 0, nullptr, nullptr, nullptr, &chunks));
@@ -455,12 +475,12 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         if (!ready) RUN(dsspk_bn_bwd_totals(s, in_rec, in_parts, Cc, tot, in_dgamma, in_dbeta));
         int chunks = dsspk_conv_bwd_fused_chunks(m, H, Cc);
         if (chunks > 0) {
-            RUN(dsspk_conv_bwd_data_bn_wgrad_records(s, dz, xc, st, gamma, tot, in_rec, in_parts, in_dgamma, in_dbeta, wt, add, out, xc_post,
-                                                     st_post, records, x_in, out_scr, rp, rdw, rE, rchunks, m, H, Cc));
+            RUN(conv3x3_tiled_dgrad_bn_wgrad((hipStream_t)s, dz, xc, st, gamma, tot, in_rec, in_parts, in_dgamma, in_dbeta, wt, add, out, xc_post,
+                                             st_post, records, x_in, out_scr, rp, rdw, rE, rchunks, m, H, Cc));
             if (sum_next) RUN(dsspk_bn_bwd_totals(s, records, nparts, Cc, ntot, ndgamma, ndbeta));
         } else {
-            RUN(dsspk_conv_bwd_data_bn_records(s, dz, xc, st, gamma, tot, in_rec, in_parts, in_dgamma, in_dbeta, g1, wt, add, out, x_in,
-                                               xc_post, st_post, records, rp, rdw, rE, rchunks, m, H, Cc));
+            RUN(conv3x3_tiled_dgrad_bn((hipStream_t)s, dz, xc, st, gamma, tot, in_rec, in_parts, in_dgamma, in_dbeta, g1, wt, add, out, x_in,
+                                       xc_post, st_post, records, rp, rdw, rE, rchunks, m, H, Cc));
             RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, sum_next ? records : nullptr,
                                             nparts, Cc, ntot, ndgamma, ndbeta, &chunks));
         }
@@ -485,7 +505,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             parts0 = parts1;
             tot0 = false;
         }
-        RUN(regular_layer(recB0, parts0, g + B.g2, g + B.b2, tot0, g0, F(B.c2), F(B.st2), w + B.g2, totB, w + B.w2, nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr,
+        RUN(regular_layer(recB0, parts0, g + B.g2, g + B.b2, tot0, g0, F(B.c2), F(B.st2), w + B.g2, totB, input_filter(B.w2, B.f2, B.cout), nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr,
                           g + B.w2, Ho, B.cout, fused1, parts1, totA, g + B.g1, g + B.b1));        // sums of BN1's records to totA if fused1
         // ---- BN1 + conv1: g2 = dz1 -> g1 = d conv1 output; d-input (+ dz2 through an identity shortcut) = gradient
         //      w.r.t. the block's input, which is the previous block's (or the stem's) post-ReLU output: mask +
@@ -495,7 +515,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             const float* pst = bi ? F(P->blocks[bi - 1].st2) : F(P->stem_st);
             // output in place over the shortcut's gradient g0; g0 stays the gradient w.r.t. the previous block's output
             const bool next_fused = bi > 0;                  // the previous block's conv2 has this convolution's shape
-            RUN(regular_layer(bscr, parts1, g + B.g1, g + B.b1, true, g2, F(B.c1), F(B.st1), w + B.g1, totA, w + B.w1, g0, g0, xin, pc, pst, recB0, g + B.w1, B.H, B.cin,
+            RUN(regular_layer(bscr, parts1, g + B.g1, g + B.b1, true, g2, F(B.c1), F(B.st1), w + B.g1, totA, input_filter(B.w1, B.f1, B.cout), g0, g0, xin, pc, pst, recB0, g + B.w1, B.H, B.cin,
                               next_fused, partsp, totB, next_fused ? g + P->blocks[bi - 1].g2 : nullptr,
                               next_fused ? g + P->blocks[bi - 1].b2 : nullptr));
             parts0 = partsp;

@@ -172,11 +172,20 @@ template <int C, int WAVES, int NT = 4> constexpr int inline_records() { return 
 // Thread (channel tid % C, lane tid / C) holds records lane, lane + THREADS / C, ... of its channel; all loads in flight together.
 template <int C, int THREADS, int RECORDS>
 __device__ __forceinline__ void load_records(float2 (&v)[RECORDS], const float* __restrict__ records, int parts, int tid) {
+    constexpr int FEW = 4;          // at a time: where a list is short its loads would keep those behind them waiting
 #pragma unroll
-    for (int u = 0; u < RECORDS; ++u) {
-        const int g = tid / C + u * (THREADS / C);
-        v[u] = *reinterpret_cast<const float2*>(records + ((long)min(g, parts - 1) * C + tid % C) * 2);
-        if (g >= parts) v[u] = make_float2(0.f, 0.f);
+    for (int u0 = 0; u0 < RECORDS; u0 += FEW) {
+        if (RECORDS > 8 && u0 * (THREADS / C) >= parts) {
+#pragma unroll
+            for (int u = u0; u < u0 + FEW; ++u) v[u] = make_float2(0.f, 0.f);
+            continue;
+        }
+#pragma unroll
+        for (int u = u0; u < u0 + FEW; ++u) {
+            const int g = tid / C + u * (THREADS / C);
+            v[u] = *reinterpret_cast<const float2*>(records + ((long)min(g, parts - 1) * C + tid % C) * 2);
+            if (g >= parts) v[u] = make_float2(0.f, 0.f);
+        }
     }
 }
 
@@ -200,6 +209,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     PostBn post, BwdBn bwd, int conv_blocks, jobs::ReduceJob rj, WgradFused wg) {
     using K = Cfg<C, HW, R, NSPLIT, WAVES>;
     constexpr int THREADS = K::THREADS, V = K::V, NL = K::NL;
+    // Filter columns in registers.  With converted filters and two pixel tiles the next one's rows, and then what the epilogue reads and the
+    // fused d-filter's x tile, are fetched between the products (SPREAD): in front of them the records and the tile wait behind some fifty other
+    // loads a wavefront, each 16 cycles of the compute unit's address unit (batch 8, cycles until the records are summed: 5 to 7 thousand; it is
+    // also 50 to 90 registers less).  All loads in front / so, a round of pushes, us: 20 layers, batch 8, four workers 678 / 652, batch 17, three
+    // 580 / 577; 50 layers, batch 8, two 1143 / 1059; 110 layers, batch 3, eight 7677 / 7177.
+    constexpr bool SPREAD = PL && K::EARLY;
+    constexpr int COLUMNS = SPREAD ? 2 : K::COLUMNS;
     static_assert(!WG || (PRE == 3 && NSPLIT == 1 && TRANSPOSED && (C == 16 || C == 32)), "fused d-filter: d-input form, whole channel range");
     extern __shared__ __attribute__((aligned(16))) char lds_bytes[];
     char* lds = lds_bytes;
@@ -240,8 +256,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     //      One filter column (three taps) at a time: the product loop walks the columns, and a row of the next one is
     //      fetched while the loop still works with that row of the present one.
     constexpr int FV = C == 16 ? 1 : 2;
-    float4 fr[PL ? 1 : K::COLUMNS][3][FV];
-    split::Filt<C> filt[PL ? K::COLUMNS : 1][3];
+    float4 fr[PL ? 1 : COLUMNS][3][FV];
+    split::Filt<C> filt[PL ? COLUMNS : 1][3];
     unsigned filter_at;
     if constexpr (PL) {
         const Role r = role_of(tid);
@@ -256,22 +272,22 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         if constexpr (PL) {
 #pragma unroll
             for (int p = 0; p < 3; ++p)
-                filt[kx % K::COLUMNS][ky].v[p] = (planes + (tap * (filter3x3_operands(C) / 9) * 3 + p) * 64)[filter_at];
+                filt[kx % COLUMNS][ky].v[p] = (planes + (tap * (filter3x3_operands(C) / 9) * 3 + p) * 64)[filter_at];
         } else {
 #pragma unroll
             for (int e = 0; e < FV; ++e) {
                 if constexpr (TRANSPOSED) {
-                    fr[kx % K::COLUMNS][ky][e] = load4(wgt + (8 - tap) * C * C + 4 * e, filter_at);
+                    fr[kx % COLUMNS][ky][e] = load4(wgt + (8 - tap) * C * C + 4 * e, filter_at);
                 } else {
                     const float* wp = wgt + tap * C * C + 4 * e * C;
-                    fr[kx % K::COLUMNS][ky][e] = make_float4((wp + 0 * C)[filter_at], (wp + 1 * C)[filter_at], (wp + 2 * C)[filter_at], (wp + 3 * C)[filter_at]);
+                    fr[kx % COLUMNS][ky][e] = make_float4((wp + 0 * C)[filter_at], (wp + 1 * C)[filter_at], (wp + 2 * C)[filter_at], (wp + 3 * C)[filter_at]);
                 }
             }
         }
     };
     auto split_filter = [&](int ky, int kx) {
         if constexpr (!PL) {
-            float4 (&f)[FV] = fr[kx % K::COLUMNS][ky];
+            float4 (&f)[FV] = fr[kx % COLUMNS][ky];
 #pragma unroll
             for (int e = 0; e < FV; ++e) f[e] = split::scaled(f[e]);
             filt[0][ky] = split::filter_operand<C>(f);
@@ -279,7 +295,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     };
     auto first_columns = [&]() {
 #pragma unroll
-        for (int kx = 0; kx < K::COLUMNS; ++kx)
+        for (int kx = 0; kx < (SPREAD ? 1 : COLUMNS); ++kx)
 #pragma unroll
             for (int ky = 0; ky < 3; ++ky) load_filter(ky, kx);
     };
@@ -349,7 +365,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         }
 #pragma unroll
         for (int wm = 0; wm < K::WM; ++wm) {
-            addv[wm] = add ? load4(add + band_at + wm * OUT_STEP, at) : make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (SPREAD)       // (a load behind a branch makes those before it wait: the compiler cannot count it)
+                addv[wm] = split::load4(split::buffer(add + band_at, add ? 4u * R * HW * C : 0u), 4u * (at + wm * OUT_STEP));
+            else
+                addv[wm] = add ? load4(add + band_at + wm * OUT_STEP, at) : make_float4(0.f, 0.f, 0.f, 0.f);
             if constexpr (POST) {
                 maskv[wm] = load4(post.mask_src + band_at + wm * OUT_STEP, at);
                 xcv[wm] = load4(post.xc + band_at + wm * OUT_STEP, at);
@@ -361,11 +380,16 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     auto load_x_tile = [&]() {
 #pragma unroll
         for (int e = 0; e < NL; ++e) {
+            if constexpr (SPREAD) {
+                xin[e] = split::load4(split::buffer(wg.x_in + image_at, 4u * HW * HW * C),
+                                      inside(e) ? 4u * (unsigned)((r_base + K::ROW0 - 1) * HW * C + 4 * tid + e * STEP) : split::OUTSIDE);
+                continue;
+            }
             xin[e] = make_float4(0.f, 0.f, 0.f, 0.f);
             if (inside(e)) xin[e] = load4(wg.x_in + tile_at + e * STEP, 4u * tid);
         }
     };
-    if constexpr (K::EARLY) {
+    if constexpr (K::EARLY && !SPREAD) {
         epilogue_loads(role_of(tid));
         if constexpr (WG) load_x_tile();
     }
@@ -510,7 +534,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
 #pragma unroll
             for (int ky = 0; ky < 3; ++ky) {
                 if (i % ST == (LAST + ky + 1) % ST && kx + (ky < 2) >= 1 && kx + (ky < 2) <= 2) split_filter(ky, kx + (ky < 2));
-                if (!PL && K::COLUMNS == 1 && st == LAST + ky - 1 && kx < 2) load_filter(ky, kx + 1);
+                if (!PL && COLUMNS == 1 && st == LAST + ky - 1 && kx < 2) load_filter(ky, kx + 1);
             }
             if (i + 1 < 3 * ST) x[(i + 1) & 1] = pixels(i + 1);
             __builtin_amdgcn_sched_barrier(0);      // or the compiler moves the reads down to their use, behind the products
@@ -521,10 +545,16 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
                     const int ky = st - K::TROWS * t;
                     if (ky < 0 || ky > 2) continue;
                     floatx4& to = p + 1 < split::products<C>() ? lo[t] : a[t];
-                    to = split::product<C>(p, filt[PL ? kx % K::COLUMNS : 0][ky], x[i & 1], to);
+                    to = split::product<C>(p, filt[PL ? kx % COLUMNS : 0][ky], x[i & 1], to);
                 }
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (PL && K::COLUMNS == 1)        // into the registers of the row that has just been used for the last time
+            if constexpr (SPREAD) {
+                if (st < 3 && kx < 2) load_filter(st, kx + 1);
+                if (st == 3 && kx == 0) epilogue_loads(r);
+                if constexpr (WG)
+                    if (st == 3 && kx == 1) load_x_tile();
+            }
+            if constexpr (PL && COLUMNS == 1)        // into the registers of the row that has just been used for the last time
                 if (st >= LAST && kx < 2) load_filter(st - LAST, kx + 1);
         }
         mma::drain();

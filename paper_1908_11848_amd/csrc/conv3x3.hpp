@@ -74,7 +74,10 @@ struct Cfg {
     static constexpr int DTILES = C == 16 ? 1 : 4, RSPLIT = WAVES / DTILES, RUNS = R * HW / 32 / RSPLIT;
     static constexpr size_t RED = C == 16 ? (size_t)WAVES * 9 * C * C * sizeof(float) : 0;
     static constexpr size_t COLUMN = C == 32 && RSPLIT == 2 ? (size_t)DTILES * 3 * 256 * sizeof(float) : 0;
-    static constexpr size_t LDS_BYTES_WG = LDS_BYTES + COLUMN > RED ? LDS_BYTES + COLUMN : RED;
+    // C = 64 (the output channels in four parts): the x tile, 16 channels of it, has a place of its own, and so has what wavefronts exchange.
+    static constexpr int X2PLANE = 32, X2PITCH = 3 * X2PLANE + 8, X2 = (R + 2) * TW * X2PITCH;
+    static constexpr size_t OWN_X = C == 64 ? X2 + (size_t)WAVES * WM * 64 * 16 : 0;
+    static constexpr size_t LDS_BYTES_WG = LDS_BYTES + COLUMN + OWN_X > RED ? LDS_BYTES + COLUMN + OWN_X : RED;
     static_assert(WPX * KS == WAVES_M && (NT == 4 || NT == 2) && NT * TROWS * WPX == R * TX && (C == 16 || C == 32 * KS), "roles of the wavefronts");
     static_assert(XB % 16 == 0 && WAVES * 2 * 64 * 16 <= XB, "alignment; room for the exchange");
     // the loader: rows inside the image (or halo rows of a band), columns inside the image; what remains of the tile is zero
@@ -136,7 +139,7 @@ struct BwdBn {
     float* dx_out;
 };
 
-// Gradient w.r.t. the filter in the same kernel (WG, only with PRE == 3 and all channels in one workgroup): the
+// Gradient w.r.t. the filter in the same kernel (WG, only with PRE == 3; a workgroup has all output channels of the layer in its tile): the
 // dx tile the loader has just built in LDS is the d-filter convolution's dy, so only the convolution's input x
 // (halo tile, a second LDS buffer) has to be fetched; dx itself never goes to memory.  After the d-input MFMA
 // loop the wavefronts accumulate, as wgrad3x3_kernel does, dw[tap][ci][co] += x[pixel + tap][ci] * dx[pixel][co]
@@ -216,7 +219,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     // 580 / 577; 50 layers, batch 8, two 1143 / 1059; 110 layers, batch 3, eight 7677 / 7177.
     constexpr bool SPREAD = PL && K::EARLY;
     constexpr int COLUMNS = SPREAD ? 2 : K::COLUMNS;
-    static_assert(!WG || (PRE == 3 && NSPLIT == 1 && TRANSPOSED && (C == 16 || C == 32)), "fused d-filter: d-input form, whole channel range");
+    static_assert(!WG || (PRE == 3 && TRANSPOSED && (C == 64 ? NSPLIT == 4 && SPREAD : NSPLIT == 1)), "fused d-filter: d-input form");
     extern __shared__ __attribute__((aligned(16))) char lds_bytes[];
     char* lds = lds_bytes;
     if ((int)blockIdx.x >= conv_blocks) {           // workgroups behind the convolution's own carry the reduction job
@@ -376,8 +379,12 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         }
     };
     // x halo tile of the fused d-filter: on its way during the epilogue
-    float4 xin[WG ? NL : 1];
+    float4 xin[WG && C != 64 ? NL : 1];
     auto load_x_tile = [&]() {
+        if constexpr (C == 64) {            // this part's 16 channels
+            xin[0] = load4(wg.x_in + image_at, tid / 4 * C + part * K::CN + tid % 4 * 4);
+            return;
+        }
 #pragma unroll
         for (int e = 0; e < NL; ++e) {
             if constexpr (SPREAD) {
@@ -485,6 +492,12 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         if constexpr (PRE == 3) sc = *reinterpret_cast<const float4*>(bwd.xc + off);
         return transformed(*reinterpret_cast<const float4*>(src + off), sc, c, false);
     };
+    if constexpr (WG && C == 64)            // the x tile's border
+        for (int i = tid; i < 4 * (K::TW - 1) * (K::X2PITCH / 8); i += THREADS) {
+            const int px = i / (K::X2PITCH / 8), side = px / (K::TW - 1), j = px % (K::TW - 1);
+            const int r = side == 0 ? 0 : side == 1 ? K::TW - 1 : side == 2 ? j + 1 : j, c = side == 0 ? j : side == 1 ? j + 1 : side == 2 ? 0 : K::TW - 1;
+            *reinterpret_cast<uint2*>(lds + K::LDS_BYTES + (r * K::TW + c) * K::X2PITCH + 8 * (i % (K::X2PITCH / 8))) = make_uint2(0u, 0u);
+        }
     for (int i = tid; i < K::ZERO; i += THREADS) {          // outside the image: left and right, for a whole image above and below
         const int px = i / K::ZERO_UNITS, unit = i % K::ZERO_UNITS;
         int r = px >> 1, c = (px & 1) * (K::TW - 1);
@@ -567,8 +580,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             // the two wavefronts of a group of pixels hold partial sums over their halves of the input channels: each
             // hands the other the two tiles it will not finish and adds what it receives (first half + second half)
             const int ks = r.ks, lane = r.lane, wave = r.wave;
-            __syncthreads();                               // every wavefront has read the tile for the last time
-            float* Ex = reinterpret_cast<float*>(lds);             // [wavefront][WM][64][4]
+            if constexpr (!WG) __syncthreads();            // every wavefront has read the tile for the last time
+            float* Ex = reinterpret_cast<float*>(WG ? lds + K::LDS_BYTES + K::X2 : lds);       // [wavefront][WM][64][4]
 #pragma unroll
             for (int wm = 0; wm < K::WM; ++wm)
 #pragma unroll
@@ -675,7 +688,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     //      One filter column after the other, its small products with accumulators of their own: in one
     //      accumulator all six are rounded to the size of the sum, and with a bias, so that the error of the sum over the workgroups
     //      grew with their number (16 channels, batch 1 / 37 / 128: 1.1e-7 / 2.0e-7 / 3.2e-7; so 0.7e-7 / 1.0e-7 / 1.2e-7).
-    if constexpr (WG) {
+    if constexpr (WG && C != 64) {
         constexpr int RUNS = K::RUNS, RROWS = 32 / HW;         // image rows per run
         const int cit = C == 16 ? 0 : (wave & 3) >> 1, cot = C == 16 ? 0 : wave & 1;
         const int first = RUNS * RROWS * (wave / K::DTILES);   // first image row of the wavefront's runs
@@ -814,6 +827,82 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         }
     }
 
+    // The same with 64 channels: a wavefront owns 16 output channels, all nine taps of this part's 16 input channels and the image's two runs of
+    // 32 pixels (four rows each); the dx tile stays where it is.  Products and
+    // sums in the order of wgrad3x3_wide_kernel, which as a launch of its own takes 8.5 us at these batches, this 2.  With that kernel / so, a round
+    // of pushes, us: 20 layers, batch 8, four workers 652 / 606, batch 17, three 577 / 537; 50 layers, batch 8, two 1059 / 979; 110 layers, batch 3,
+    // eight 7177 / 6054.  (Partial sums of an image are nine times its activations: not for larger batches.)
+    if constexpr (WG && C == 64) {
+        constexpr int RUN = 4 * K::TW;                         // pixels of the tile from run to run
+        char* X2 = lds + K::LDS_BYTES;
+        {
+            const int px = tid / 4;
+            uint2 pl[split::PLANES];
+            split::split4(split::scaled(xin[0]), pl);
+#pragma unroll
+            for (int p = 0; p < split::PLANES; ++p)
+                *reinterpret_cast<uint2*>(X2 + ((px / HW + 1) * K::TW + px % HW + 1) * K::X2PITCH + p * K::X2PLANE + 8 * (tid % 4)) = pl[p];
+        }
+        const char *xa[2], *da[2];                             // of pixels 8 q + 4 h + l16 / 4 of the first run
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int p = 8 * q + 4 * h + (l16 >> 2), at = p / HW * K::TW + p % HW;
+            xa[h] = X2 + at * K::X2PITCH + 8 * (l16 & 3);
+            da[h] = Xs + (at + K::TW + 1) * K::PITCH + 32 * wave + 8 * (l16 & 3);
+        }
+        uint4 d[2][split::PLANES], x[2][split::PLANES];
+#pragma unroll
+        for (int run = 0; run < 2; ++run) split::transposed_operand<K::PLANE>(d[run], da[0] + run * RUN * K::PITCH, da[1] + run * RUN * K::PITCH);
+        auto load_x = [&](int i) {                             // filter column i / 6, run i / 3 mod 2, row i mod 3
+            const int off = (i / 3 % 2 * RUN + i % 3 * K::TW + i / 6) * K::X2PITCH;
+            split::transposed_operand<K::X2PLANE>(x[i & 1], xa[0] + off, xa[1] + off);
+        };
+        __syncthreads();
+        load_x(0);
+        const int ci = part * K::CN + l16;
+        float* pout = wg.partial + (long)n * 9 * C * C + ci * C + 16 * wave + 4 * q;
+        float worst = 0.f;
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+            floatx4 sum[3];
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky) sum[ky] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 6 * kx; i < 6 * kx + 6; ++i) {
+                if (i + 1 < 18) load_x(i + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                constexpr int PD[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+                for (int p = 0; p < 6; ++p) sum[i % 3] = split::mfma(d[i / 3 % 2][PD[p]], x[i & 1][PX[p]], sum[i % 3]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            mma::drain();
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky) {
+                worst = split::spoil(sum[ky], worst);
+                *reinterpret_cast<floatx4*>(pout + (3 * ky + kx) * C * C) = sum[ky] * split::UNSCALE;
+            }
+        }
+        if (split::spoiled(worst)) {    // beyond the range of the scaled terms: from the operands in memory, four pixels of a row a step
+            const int c = 16 * wave + l16;
+#pragma unroll 1
+            for (int tap = 0; tap < 9; ++tap) {
+                floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (int p = q; p < HW * HW; p += 4) {
+                    const int h = p / HW, w = p % HW, xh = h + tap / 3 - 1, xw = w + tap % 3 - 1;
+                    const float4 dx = input(h, w, c & ~3);
+                    const float dv[1] = {c & 2 ? (c & 1 ? dx.w : dx.z) : (c & 1 ? dx.y : dx.x)};
+                    const bool in = (unsigned)xh < (unsigned)HW && (unsigned)xw < (unsigned)HW;
+                    const float xv[1] = {in ? wg.x_in[image_at + (xh * HW + xw) * C + ci] : 0.f};
+                    v = split::product32(dv, xv, v);
+                }
+                mma::drain();
+                *reinterpret_cast<floatx4*>(pout + tap * C * C) = v;
+            }
+        }
+    }
+
     // ---- optional: batch-norm statistics of this workgroup's output tile, per channel:
     //      mean over its R*HW pixels and the sum of squared deviations from that mean
     //      (bn_partial[(g*C + c)*2 + {0,1}], g = image * bands + band), merged later like row slabs.
@@ -867,11 +956,11 @@ int launch(hipStream_t s, const float* src, const Filter3x3& w, const float* add
 }
 
 // The reduction job a launch carries, and the workgroups (of `threads` threads) given to it.
-inline jobs::ReduceJob reduce_job(const float* partial, float* dw, int E, int chunks, int threads) {
+inline jobs::ReduceJob reduce_job(const jobs::Partials& waiting, int threads) {
     jobs::ReduceJob rj = jobs::ReduceJob();
-    if (partial) {
-        rj.partial = partial; rj.dw = dw; rj.E = E; rj.chunks = chunks;
-        const int groups = jobs::reduce_groups(E, chunks), per = threads / jobs::THREADS;
+    if (waiting.partial) {
+        static_cast<jobs::Partials&>(rj) = waiting;
+        const int groups = jobs::reduce_groups(rj.E, rj.chunks), per = threads / jobs::THREADS;
         rj.blocks = ((groups < 288 ? groups : 288) + per - 1) / per;
     }
     return rj;

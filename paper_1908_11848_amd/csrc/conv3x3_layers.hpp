@@ -8,6 +8,8 @@
 // dsspk_conv_fwd_records, or NULL.
 int conv_stem(hipStream_t s, const float* x, const float* w, float* y, float* records, int N, FilterJob job);
 
+int wgrad_reduce_many(hipStream_t s, int n, const jobs::Partials* waiting);
+
 // k_conv3x3.hip; -2 = shape not covered.
 int conv3x3_tiled(hipStream_t s, const float* src, const Filter3x3& w, const float* add, float* dst, float* bn_partial,
                    int N, int HW, int C, bool transposed);
@@ -33,7 +35,8 @@ int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc
                                   const float* x_in, float* partial, const float* red_partial, float* red_dw, int red_E,
                                   int red_chunks, int N, int HW, int C);
 
-// k_conv3x3_large.hip, k_conv3x3_small.hip: dsspk_conv3x3_large_* and dsspk_conv3x3_small_*
+// k_conv3x3_large.hip, k_conv3x3_small.hip: dsspk_conv3x3_large_* and dsspk_conv3x3_small_*.  small_bwd with converted filters takes `partial` for 64
+// channels too: one partial result an image, to be reduced as Partials::quads.
 #define CONV3X3_FORM_LAUNCHERS(NAME)                                                                                                          \
     int conv3x3_##NAME##_fwd(void* stream, const float* src, const float* records, int parts, const float* gamma, const float* beta,         \
                              float eps, const float* shortcut, float* act_out, float* stats_out, const Filter3x3& w, float* dst,              \
@@ -41,7 +44,6 @@ int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc
     int conv3x3_##NAME##_bwd(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,                         \
                              const float* in_records, int parts, float* dgamma, float* dbeta, float* dx, float* partial,                      \
                              const Filter3x3& w, const float* add, float* out, const float* x_in, const float* xc_post,                       \
-                             const float* stats_post, float* records, const float* red_partial, float* red_dw, int red_E, int red_chunks,     \
-                             int N, int H, int C);
+                             const float* stats_post, float* records, const jobs::Partials& red, int N, int H, int C);
 CONV3X3_FORM_LAUNCHERS(large)
 CONV3X3_FORM_LAUNCHERS(small)

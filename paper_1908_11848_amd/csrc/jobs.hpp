@@ -17,11 +17,17 @@ namespace jobs {
 constexpr int THREADS = 256;
 constexpr int LDS_FLOATS = 1024;        // LDS (16-byte aligned) either job needs
 
-struct ReduceJob {
+// Partial filter gradients that wait for their reduction.  quads: one an image (at most 64), to be added up four images at a time,
+// (0 + 2) + (1 + 3), as the d-filter kernel with four images to a workgroup does, so that both leave the same bits.
+struct Partials {
     const float* partial;   // [chunks][E]
     float* dw;              // [E]
     int E;                  // multiple of 4
     int chunks;
+    bool quads;
+};
+
+struct ReduceJob : Partials {
     int blocks;             // workgroups given to the job (0: none); each takes groups of elements round-robin
 };
 
@@ -57,6 +63,18 @@ __device__ __forceinline__ void wgrad_reduce(const ReduceJob& j, int wg, float* 
 #pragma unroll
                 for (int u = 0; u < 8; ++u)     // unconditional loads (index clamped), all in flight together
                     v[u] = *reinterpret_cast<const float4*>(j.partial + (long)min(k0 + u, j.chunks - 1) * j.E + e);
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (k0 + u >= j.chunks) v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (j.quads) {
+#pragma unroll
+                    for (int u = 0; u < 8; u += 4) {
+                        if (k0 + u >= j.chunks) break;
+                        s.x += (v[u].x + v[u + 2].x) + (v[u + 1].x + v[u + 3].x); s.y += (v[u].y + v[u + 2].y) + (v[u + 1].y + v[u + 3].y);
+                        s.z += (v[u].z + v[u + 2].z) + (v[u + 1].z + v[u + 3].z); s.w += (v[u].w + v[u + 2].w) + (v[u + 1].w + v[u + 3].w);
+                    }
+                    continue;
+                }
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
                     if (k0 + u < j.chunks) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }

@@ -659,7 +659,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_many_kernel(ReduceJobs r) {
 }
 
 int launch_reduce(hipStream_t s, const float* partial, float* dw, int E, int chunks) {
-    jobs::ReduceJob j;
+    jobs::ReduceJob j = {};
     j.partial = partial; j.dw = dw; j.E = E; j.chunks = chunks; j.blocks = jobs::reduce_groups(E, chunks);
     hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(j.blocks), dim3(256), 0, s, j);
     return DSSPK_LAUNCH_RC();
@@ -995,19 +995,25 @@ extern "C" int dsspk_wgrad_reduce(void* stream, const float* partial, float* dw,
     return launch_reduce((hipStream_t)stream, partial, dw, E, chunks);
 }
 
-extern "C" int dsspk_wgrad_reduce_many(void* stream, int n, const float* const* partial, float* const* dw, const int* E, const int* chunks) {
-    if (n < 1 || n > DSSPK_WGRAD_REDUCE_MAX || !partial || !dw || !E || !chunks) return -1;
+int wgrad_reduce_many(hipStream_t s, int n, const jobs::Partials* p) {
     ReduceJobs r = {};
     r.n = n;
     int blocks = 0;
     for (int k = 0; k < n; ++k) {
-        if (!partial[k] || !dw[k] || E[k] < 4 || E[k] % 4 || chunks[k] < 1) return -1;
-        r.j[k].partial = partial[k]; r.j[k].dw = dw[k]; r.j[k].E = E[k]; r.j[k].chunks = chunks[k];
-        r.j[k].blocks = jobs::reduce_groups(E[k], chunks[k]);
+        if (!p[k].partial || !p[k].dw || p[k].E < 4 || p[k].E % 4 || p[k].chunks < 1) return -1;
+        static_cast<jobs::Partials&>(r.j[k]) = p[k];
+        r.j[k].blocks = jobs::reduce_groups(p[k].E, p[k].chunks);
         blocks += r.j[k].blocks;
     }
-    hipLaunchKernelGGL(wgrad_reduce_many_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, r);
+    hipLaunchKernelGGL(wgrad_reduce_many_kernel, dim3(blocks), dim3(256), 0, s, r);
     return DSSPK_LAUNCH_RC();
+}
+
+extern "C" int dsspk_wgrad_reduce_many(void* stream, int n, const float* const* partial, float* const* dw, const int* E, const int* chunks) {
+    if (n < 1 || n > DSSPK_WGRAD_REDUCE_MAX || !partial || !dw || !E || !chunks) return -1;
+    jobs::Partials p[DSSPK_WGRAD_REDUCE_MAX];
+    for (int k = 0; k < n; ++k) p[k] = {partial[k], dw[k], E[k], chunks[k], false};
+    return wgrad_reduce_many((hipStream_t)stream, n, p);
 }
 
 extern "C" int dsspk_bn_bwd_totals(void* stream, const float* records, int G, int C, float* totals, float* dgamma, float* dbeta) {

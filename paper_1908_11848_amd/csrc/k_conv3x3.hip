@@ -186,7 +186,7 @@ int conv3x3_tiled_dgrad_bn(hipStream_t s, const float* dz, const float* xc, cons
     bwd.inv_m = 1.0f / (float)((long)N * HW * HW);
     PostBn post;
     post.mask_src = mask_src; post.xc = xc_post; post.stats = stats_post; post.records = records;
-    const jobs::ReduceJob rj = reduce_job(red_partial, red_dw, red_E, red_chunks, THREADS);
+    const jobs::ReduceJob rj = reduce_job({red_partial, red_dw, red_E, red_chunks, false}, THREADS);
     if (C == 16 && HW == 32) return launch<16, 32, 8, 1, 4, true, 3, true>(s, dz, w, add, out, nullptr, N, PreBn(), post, bwd, rj);
     if (C == 32 && HW == 16) return launch<32, 16, 8, 1, 4, true, 3, true>(s, dz, w, add, out, nullptr, N, PreBn(), post, bwd, rj);
     if (C == 64 && HW == 8) return launch<64, 8, 8, 2, 4, true, 3, true>(s, dz, w, add, out, nullptr, N, PreBn(), post, bwd, rj);
@@ -208,7 +208,7 @@ int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc
     bwd.inv_m = 1.0f / (float)((long)N * HW * HW);
     PostBn post;
     post.mask_src = x_in; post.xc = xc_post; post.stats = stats_post; post.records = records;
-    const jobs::ReduceJob rj = reduce_job(red_partial, red_dw, red_E, red_chunks, THREADS);
+    const jobs::ReduceJob rj = reduce_job({red_partial, red_dw, red_E, red_chunks, false}, THREADS);
     WgradFused wg;
     wg.x_in = x_in; wg.partial = partial;
     if (C == 16 && HW == 32) return launch<16, 32, 8, 1, 4, true, 3, true, true>(s, dz, w, add, out, nullptr, N, PreBn(), post, bwd, rj, wg);

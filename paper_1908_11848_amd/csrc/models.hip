@@ -415,28 +415,22 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     for (int i = 1; i < WG_SCRATCH; ++i) scrs[i] = F(P->wg_more[i - 1]);
     int parts0 = 0;
     bool tot0 = false;
-    struct Pending { const float* partial[WG_SCRATCH]; float* dw[WG_SCRATCH]; int E[WG_SCRATCH], chunks[WG_SCRATCH], n; } pend = {};
+    struct Pending { jobs::Partials p[WG_SCRATCH]; int n; } pend = {};
     auto free_scr = [&]() {
         int i = 0;
         for (int k = 0; k < pend.n; ++k)
-            if (pend.partial[k] == scrs[i]) { ++i; k = -1; }
+            if (pend.p[k].partial == scrs[i]) { ++i; k = -1; }
         return scrs[i];
     };
-    auto push_back = [&](const float* partial, float* dw, int E, int chunks) {
-        pend.partial[pend.n] = partial; pend.dw[pend.n] = dw; pend.E[pend.n] = E; pend.chunks[pend.n] = chunks;
-        ++pend.n;
-    };
+    auto push_back = [&](const float* partial, float* dw, int E, int chunks, bool quads = false) { pend.p[pend.n++] = {partial, dw, E, chunks, quads}; };
     auto pop_front = [&]() {
         --pend.n;
-        for (int k = 0; k < pend.n; ++k) {
-            pend.partial[k] = pend.partial[k + 1]; pend.dw[k] = pend.dw[k + 1]; pend.E[k] = pend.E[k + 1]; pend.chunks[k] = pend.chunks[k + 1];
-        }
+        for (int k = 0; k < pend.n; ++k) pend.p[k] = pend.p[k + 1];
     };
     auto flush = [&]() -> int {
-        if (!pend.n) return 0;
         const int n = pend.n;
         pend.n = 0;
-        return dsspk_wgrad_reduce_many(s, n, pend.partial, pend.dw, pend.E, pend.chunks);
+        return n ? wgrad_reduce_many((hipStream_t)s, n, pend.p) : 0;
     };
     // d-filter of a layer with a kernel of its own; its partial sums wait
     auto filter_grad = [&](const float* xi, const float* dy, float* dw, int H, int cin, int cout, int stride) -> int {
@@ -458,29 +452,27 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
                              const float* st_post, float* records, float* dw, int H, int Cc, bool sum_next, int nparts,
                              float* ntot, float* ndgamma, float* ndbeta) -> int {
         float* out_scr = free_scr();
-        const bool carry = pend.n > 0;
-        const float* rp = carry ? pend.partial[0] : nullptr;
-        float* rdw = carry ? pend.dw[0] : nullptr;
-        const int rE = carry ? pend.E[0] : 0, rchunks = carry ? pend.chunks[0] : 0;
-        if (carry) pop_front();
+        const jobs::Partials red = pend.n ? pend.p[0] : jobs::Partials{};
+        if (pend.n) pop_front();
         if (large || small) {
             int chunks = parts_of(H, Cc, Cc, 1);
             const auto bwd = large ? conv3x3_large_bwd : conv3x3_small_bwd;
-            RUN(bwd(s, dz, xc, st, gamma, in_rec, in_parts, in_dgamma, in_dbeta, Cc == 64 ? g1 : nullptr, Cc == 64 ? nullptr : out_scr, wt, add, out,
-                    x_in, xc_post, st_post, records, rp, rdw, rE, rchunks, m, H, Cc));
-            if (Cc == 64) RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, nullptr, 0, 0, nullptr, nullptr, nullptr, &chunks));
-            push_back(out_scr, dw, 9 * Cc * Cc, chunks);
+            const bool apart = large && Cc == 64;           // a d-filter kernel of its own
+            RUN(bwd(s, dz, xc, st, gamma, in_rec, in_parts, in_dgamma, in_dbeta, apart ? g1 : nullptr, apart ? nullptr : out_scr, wt, add, out,
+                    x_in, xc_post, st_post, records, red, m, H, Cc));
+            if (apart) RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, nullptr, 0, 0, nullptr, nullptr, nullptr, &chunks));
+            push_back(out_scr, dw, 9 * Cc * Cc, chunks, small && Cc == 64);
             return 0;
         }
         if (!ready) RUN(dsspk_bn_bwd_totals(s, in_rec, in_parts, Cc, tot, in_dgamma, in_dbeta));
         int chunks = dsspk_conv_bwd_fused_chunks(m, H, Cc);
         if (chunks > 0) {
             RUN(conv3x3_tiled_dgrad_bn_wgrad((hipStream_t)s, dz, xc, st, gamma, tot, in_rec, in_parts, in_dgamma, in_dbeta, wt, add, out, xc_post,
-                                             st_post, records, x_in, out_scr, rp, rdw, rE, rchunks, m, H, Cc));
+                                             st_post, records, x_in, out_scr, red.partial, red.dw, red.E, red.chunks, m, H, Cc));
             if (sum_next) RUN(dsspk_bn_bwd_totals(s, records, nparts, Cc, ntot, ndgamma, ndbeta));
         } else {
             RUN(conv3x3_tiled_dgrad_bn((hipStream_t)s, dz, xc, st, gamma, tot, in_rec, in_parts, in_dgamma, in_dbeta, g1, wt, add, out, x_in,
-                                       xc_post, st_post, records, rp, rdw, rE, rchunks, m, H, Cc));
+                                       xc_post, st_post, records, red.partial, red.dw, red.E, red.chunks, m, H, Cc));
             RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, sum_next ? records : nullptr,
                                             nparts, Cc, ntot, ndgamma, ndbeta, &chunks));
         }

@@ -67,7 +67,9 @@ struct Cfg {
     static constexpr int SC = WAVES_M * CN;        // floats: per-wavefront column sums (batch-norm records, one component)
     static constexpr int SS = 2 * SC;
     static constexpr int PS = 5 * C;               // floats: per-channel vectors of the loader
+    static constexpr int PX = 4 * C;               // ... and of the fused d-filter's x tile
     static constexpr size_t LDS_BYTES = XB + (size_t)(SS + PS) * sizeof(float);
+    static constexpr size_t LDS_X = LDS_BYTES + PX * sizeof(float);        // with a fused d-filter
     // fused d-filter: the x halo tile takes the place of the first one.  A wavefront owns one 16x16 tile of (ci, co) and RUNS of the
     // band's runs of 32 pixels; RSPLIT wavefronts share a tile and their sums meet in LDS: C = 16 all nine taps at the end, in the
     // tile's place; C = 32 one filter column after the other, behind everything else.
@@ -77,8 +79,11 @@ struct Cfg {
     // C = 64 (the output channels in four parts): the x tile, 16 channels of it, has a place of its own, and so has what wavefronts exchange.
     static constexpr int X2PLANE = 32, X2PITCH = 3 * X2PLANE + 8, X2 = (R + 2) * TW * X2PITCH;
     static constexpr size_t OWN_X = C == 64 ? X2 + (size_t)WAVES * WM * 64 * 16 : 0;
-    static constexpr size_t LDS_BYTES_WG = LDS_BYTES + COLUMN + OWN_X > RED ? LDS_BYTES + COLUMN + OWN_X : RED;
+    // (RED takes everything's place)
+    static constexpr size_t TWO = 80 * 1024;       // bytes of which a compute unit holds two
+    static constexpr size_t WG_BYTES = LDS_X + COLUMN + OWN_X, LDS_BYTES_WG = WG_BYTES > RED ? WG_BYTES : RED;
     static_assert(WPX * KS == WAVES_M && (NT == 4 || NT == 2) && NT * TROWS * WPX == R * TX && (C == 16 || C == 32 * KS), "roles of the wavefronts");
+    static_assert(WG_BYTES <= TWO && SS >= WAVES, "two workgroups to a compute unit");
     static_assert(XB % 16 == 0 && WAVES * 2 * 64 * 16 <= XB, "alignment; room for the exchange");
     // the loader: rows inside the image (or halo rows of a band), columns inside the image; what remains of the tile is zero
     static constexpr bool WHOLE = R == HW;
@@ -119,6 +124,7 @@ struct PostBn {
     const float* xc;           // the batch norm's input (convolution output)
     const float* stats;        // its mean[C], invstd[C]
     float* records;            // out: (sum dz, sum dz * xhat) per tile and channel
+    const float *gamma, *beta; // of the batch norm (REPEAT)
 };
 
 // Batch-norm backward applied to the input while it is loaded (PRE == 3, d-input convolutions): src is dz, the
@@ -206,7 +212,11 @@ __device__ __forceinline__ float channel_sum(float s, float* red, int tid) {
 }
 
 // PL: the filter's operands are there already, see conv3x3_filter.hpp
-template <int C, int HW, int R, int NSPLIT, int WAVES, bool TRANSPOSED, int PRE, bool POST, bool WG, bool PL>
+// REPEAT (POST): mask_src is ReLU(BN(xc)) with nothing added, so the mask and the fused d-filter's x tile are worked out from xc again, by the
+// forward pass's own operations (the same bits), and a tensor less is read: a sixth of such a layer's bytes.  Reading it / so, a round of pushes, us:
+// batch 128, eight workers, 110 layers 16513 / 16322, 50 layers 7633 / 7509; 56 layers, batch 95, four 3216 / 3200; small batches the same.  (In the
+// last stage's d-filter kernel, where it would be a fourth of 6 MB, it changed nothing and was left out.)
+template <int C, int HW, int R, int NSPLIT, int WAVES, bool TRANSPOSED, int PRE, bool POST, bool WG, bool PL, bool REPEAT>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_waves<C, WAVES, WG, Cfg<C, HW, R, NSPLIT, WAVES>::NT>()))) void conv3x3_kernel(
     const float* __restrict__ src, const float* __restrict__ wgt, const uint4* __restrict__ planes, const float* add, float* dst, float* __restrict__ bn_partial, PreBn pre,
     PostBn post, BwdBn bwd, int conv_blocks, jobs::ReduceJob rj, WgradFused wg) {
@@ -355,7 +365,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     if constexpr (PL) first_columns();          // the tile is needed before them
     // what the epilogue adds, masks with and sums over, a lane's four channels of its pixel of every tile: all these loads together (dst may
     // alias add, so the compiler cannot move them across the stores itself)
-    float4 mu_c = make_float4(0.f, 0.f, 0.f, 0.f), is_c = mu_c, addv[K::WM], maskv[POST ? K::WM : 1], xcv[POST ? K::WM : 1];
+    float4 mu_c = make_float4(0.f, 0.f, 0.f, 0.f), is_c = mu_c, ga_c = mu_c, be_c = mu_c, addv[K::WM], maskv[POST ? K::WM : 1], xcv[POST ? K::WM : 1];
     constexpr int OUT_STEP = K::TROWS * HW * C;                                             // from tile to tile
     auto out_at_of = [&](const Role& r) -> unsigned {                                       // from the band's first pixel, first tile
         return ((r.row0 + K::TROWS * r.ks * K::WM) * HW + r.col) * C + r.co_w + 4 * r.q;
@@ -365,6 +375,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         if constexpr (POST) {
             mu_c = *reinterpret_cast<const float4*>(post.stats + r.co_w + 4 * r.q);
             is_c = *reinterpret_cast<const float4*>(post.stats + C + r.co_w + 4 * r.q);
+            if constexpr (REPEAT) {
+                ga_c = *reinterpret_cast<const float4*>(post.gamma + r.co_w + 4 * r.q);
+                be_c = *reinterpret_cast<const float4*>(post.beta + r.co_w + 4 * r.q);
+            }
         }
 #pragma unroll
         for (int wm = 0; wm < K::WM; ++wm) {
@@ -373,28 +387,42 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             else
                 addv[wm] = add ? load4(add + band_at + wm * OUT_STEP, at) : make_float4(0.f, 0.f, 0.f, 0.f);
             if constexpr (POST) {
-                maskv[wm] = load4(post.mask_src + band_at + wm * OUT_STEP, at);
+                if constexpr (!REPEAT) maskv[wm] = load4(post.mask_src + band_at + wm * OUT_STEP, at);
                 xcv[wm] = load4(post.xc + band_at + wm * OUT_STEP, at);
             }
         }
     };
     // x halo tile of the fused d-filter: on its way during the epilogue
     float4 xin[WG && C != 64 ? NL : 1];
+    const float* x_src = REPEAT ? post.xc : wg.x_in;
     auto load_x_tile = [&]() {
         if constexpr (C == 64) {            // this part's 16 channels
-            xin[0] = load4(wg.x_in + image_at, tid / 4 * C + part * K::CN + tid % 4 * 4);
+            xin[0] = load4(x_src + image_at, tid / 4 * C + part * K::CN + tid % 4 * 4);
             return;
         }
 #pragma unroll
         for (int e = 0; e < NL; ++e) {
             if constexpr (SPREAD) {
-                xin[e] = split::load4(split::buffer(wg.x_in + image_at, 4u * HW * HW * C),
+                xin[e] = split::load4(split::buffer(x_src + image_at, 4u * HW * HW * C),
                                       inside(e) ? 4u * (unsigned)((r_base + K::ROW0 - 1) * HW * C + 4 * tid + e * STEP) : split::OUTSIDE);
                 continue;
             }
             xin[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (inside(e)) xin[e] = load4(wg.x_in + tile_at + e * STEP, 4u * tid);
+            if (inside(e)) xin[e] = load4(x_src + tile_at + e * STEP, 4u * tid);
         }
+    };
+    // REPEAT: the batch norm's four vectors for the x tile, in LDS (mean, invstd, gamma, beta)
+    float* Sx = Sh + K::PS;
+    if constexpr (WG && REPEAT)
+        for (int i = tid; i < 4 * C; i += THREADS) Sx[i] = (i < 2 * C ? post.stats + i : i < 3 * C ? post.gamma + i - 2 * C : post.beta + i - 3 * C)[0];
+    auto x_value = [&](float4 o, int c) {       // of the x tile, inside the image
+        if constexpr (REPEAT) {
+            const float4 mu = *reinterpret_cast<const float4*>(Sx + c), is = *reinterpret_cast<const float4*>(Sx + C + c);
+            const float4 ga = *reinterpret_cast<const float4*>(Sx + 2 * C + c), be = *reinterpret_cast<const float4*>(Sx + 3 * C + c);
+            o.x = fmaxf(fmaf((o.x - mu.x) * is.x, ga.x, be.x), 0.f); o.y = fmaxf(fmaf((o.y - mu.y) * is.y, ga.y, be.y), 0.f);
+            o.z = fmaxf(fmaf((o.z - mu.z) * is.z, ga.z, be.z), 0.f); o.w = fmaxf(fmaf((o.w - mu.w) * is.w, ga.w, be.w), 0.f);
+        }
+        return o;
     };
     if constexpr (K::EARLY && !SPREAD) {
         epilogue_loads(role_of(tid));
@@ -496,7 +524,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         for (int i = tid; i < 4 * (K::TW - 1) * (K::X2PITCH / 8); i += THREADS) {
             const int px = i / (K::X2PITCH / 8), side = px / (K::TW - 1), j = px % (K::TW - 1);
             const int r = side == 0 ? 0 : side == 1 ? K::TW - 1 : side == 2 ? j + 1 : j, c = side == 0 ? j : side == 1 ? j + 1 : side == 2 ? 0 : K::TW - 1;
-            *reinterpret_cast<uint2*>(lds + K::LDS_BYTES + (r * K::TW + c) * K::X2PITCH + 8 * (i % (K::X2PITCH / 8))) = make_uint2(0u, 0u);
+            *reinterpret_cast<uint2*>(lds + K::LDS_X + (r * K::TW + c) * K::X2PITCH + 8 * (i % (K::X2PITCH / 8))) = make_uint2(0u, 0u);
         }
     for (int i = tid; i < K::ZERO; i += THREADS) {          // outside the image: left and right, for a whole image above and below
         const int px = i / K::ZERO_UNITS, unit = i % K::ZERO_UNITS;
@@ -581,7 +609,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             // hands the other the two tiles it will not finish and adds what it receives (first half + second half)
             const int ks = r.ks, lane = r.lane, wave = r.wave;
             if constexpr (!WG) __syncthreads();            // every wavefront has read the tile for the last time
-            float* Ex = reinterpret_cast<float*>(WG ? lds + K::LDS_BYTES + K::X2 : lds);       // [wavefront][WM][64][4]
+            float* Ex = reinterpret_cast<float*>(WG ? lds + K::LDS_X + K::X2 : lds);       // [wavefront][WM][64][4]
 #pragma unroll
             for (int wm = 0; wm < K::WM; ++wm)
 #pragma unroll
@@ -646,13 +674,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     for (int wm = 0; wm < K::WM; ++wm) {
         float4 r = make_float4(acc[wm][0] + addv[wm].x, acc[wm][1] + addv[wm].y, acc[wm][2] + addv[wm].z, acc[wm][3] + addv[wm].w);
         if constexpr (POST) {
+            const float4 hat = make_float4((xcv[wm].x - mu_c.x) * is_c.x, (xcv[wm].y - mu_c.y) * is_c.y, (xcv[wm].z - mu_c.z) * is_c.z, (xcv[wm].w - mu_c.w) * is_c.w);
+            if constexpr (REPEAT)
+                maskv[wm] = make_float4(fmaf(hat.x, ga_c.x, be_c.x), fmaf(hat.y, ga_c.y, be_c.y), fmaf(hat.z, ga_c.z, be_c.z), fmaf(hat.w, ga_c.w, be_c.w));
             r.x = maskv[wm].x > 0.f ? r.x : 0.f; r.y = maskv[wm].y > 0.f ? r.y : 0.f;
             r.z = maskv[wm].z > 0.f ? r.z : 0.f; r.w = maskv[wm].w > 0.f ? r.w : 0.f;
             sum_dz.x += r.x; sum_dz.y += r.y; sum_dz.z += r.z; sum_dz.w += r.w;
-            sum_dzx.x = fmaf(r.x, (xcv[wm].x - mu_c.x) * is_c.x, sum_dzx.x);
-            sum_dzx.y = fmaf(r.y, (xcv[wm].y - mu_c.y) * is_c.y, sum_dzx.y);
-            sum_dzx.z = fmaf(r.z, (xcv[wm].z - mu_c.z) * is_c.z, sum_dzx.z);
-            sum_dzx.w = fmaf(r.w, (xcv[wm].w - mu_c.w) * is_c.w, sum_dzx.w);
+            sum_dzx.x = fmaf(r.x, hat.x, sum_dzx.x); sum_dzx.y = fmaf(r.y, hat.y, sum_dzx.y);
+            sum_dzx.z = fmaf(r.z, hat.z, sum_dzx.z); sum_dzx.w = fmaf(r.w, hat.w, sum_dzx.w);
         }
         *reinterpret_cast<float4*>(dst + band_at + wm * OUT_STEP + out_at) = r;
     }
@@ -710,7 +739,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < NL; ++e)
-            if (own(e)) stage(tile_to + e * STEP_TO, xin[e]);
+            if (own(e)) stage(tile_to + e * STEP_TO, !REPEAT ? xin[e] : inside(e) ? x_value(xin[e], c4) : make_float4(0.f, 0.f, 0.f, 0.f));
         __syncthreads();
         constexpr int ST = RROWS * (RUNS - 1) + 3;             // image rows the runs and the three filter rows meet
         constexpr int XB = WAVES == 8 ? 1 : 2;                  // operands in registers: four wavefronts a SIMD hide the fetch
@@ -720,7 +749,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             split::transposed_operand<K::PLANE>(x[b], xa[0] + off, xa[1] + off);
         };
         floatx4 dw[C == 16 ? 9 : 1];                           // C = 16: all taps, summed over the wavefronts at the end
-        floatx4* Column = reinterpret_cast<floatx4*>(lds + K::LDS_BYTES) + (wave & 3) * 3 * 64 + lane;
+        floatx4* Column = reinterpret_cast<floatx4*>(lds + K::LDS_X) + (wave & 3) * 3 * 64 + lane;
         float* pout = wg.partial + (long)tile * 9 * C * C;
         float worst = 0.f;
         // C = 32: the sums of a filter column go to memory, with eight wavefronts those of both halves of the image: 4 to 7 hand theirs to 0 to 3
@@ -780,7 +809,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         }
         // sums beyond the range of the scaled terms: the wavefront's runs from the operands in memory, four pixels of a row a step (C = 32:
         // all of the workgroup's, which meet in finish_column)
-        if (C == 16 ? split::spoiled(worst) : __builtin_expect(__syncthreads_or(worst != 0.f) != 0, 0)) {
+        bool again = split::spoiled(worst);
+        if constexpr (C != 16) {                               // (through the column sums' place: __syncthreads_or takes LDS of its own, too much for two
+            if (lane == 0) Ss[wave] = again ? 1.f : 0.f;       // workgroups of 16x16 pixels and 32 channels to a compute unit)
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < WAVES; ++j) again |= Ss[j] != 0.f;
+        }
+        if (again) {
 #pragma unroll 1
             for (int kx = 0; kx < 3; ++kx) {
                 floatx4 v[3];
@@ -834,11 +870,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     // eight 7177 / 6054.  (Partial sums of an image are nine times its activations: not for larger batches.)
     if constexpr (WG && C == 64) {
         constexpr int RUN = 4 * K::TW;                         // pixels of the tile from run to run
-        char* X2 = lds + K::LDS_BYTES;
+        char* X2 = lds + K::LDS_X;
         {
             const int px = tid / 4;
             uint2 pl[split::PLANES];
-            split::split4(split::scaled(xin[0]), pl);
+            split::split4(split::scaled(x_value(xin[0], part * K::CN + tid % 4 * 4)), pl);
 #pragma unroll
             for (int p = 0; p < split::PLANES; ++p)
                 *reinterpret_cast<uint2*>(X2 + ((px / HW + 1) * K::TW + px % HW + 1) * K::X2PITCH + p * K::X2PLANE + 8 * (tid % 4)) = pl[p];
@@ -927,14 +963,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     }
 }
 
-template <bool PL, int C, int HW, int R, int NSPLIT, int WAVES, bool T, int PRE, bool POST, bool WG>
+template <bool PL, int C, int HW, int R, int NSPLIT, int WAVES, bool T, int PRE, bool POST, bool WG, bool REPEAT = false>
 int launch_form(hipStream_t s, const float* src, const Filter3x3& w, const float* add, float* dst, float* bn_partial, int N,
            const PreBn& pre, const PostBn& post, const BwdBn& bwd, const jobs::ReduceJob& rj, const WgradFused& wg) {
     using K = Cfg<C, HW, R, NSPLIT, WAVES>;
     constexpr size_t LDS_BYTES = WG ? K::LDS_BYTES_WG : K::LDS_BYTES;
     static_assert(LDS_BYTES >= jobs::LDS_FLOATS * (K::THREADS / jobs::THREADS) * sizeof(float), "room for a carried job");
     static bool attr_set = false;       // raise the dynamic-LDS limit once per instantiation
-    auto kern = conv3x3_kernel<C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG, PL>;
+    auto kern = conv3x3_kernel<C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG, PL, REPEAT>;
     if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)LDS_BYTES) != hipSuccess)
@@ -950,6 +986,9 @@ int launch_form(hipStream_t s, const float* src, const Filter3x3& w, const float
 template <int C, int HW, int R, int NSPLIT, int WAVES, bool T, int PRE = 0, bool POST = false, bool WG = false>
 int launch(hipStream_t s, const float* src, const Filter3x3& w, const float* add, float* dst, float* bn_partial, int N, const PreBn& pre = PreBn{},
            const PostBn& post = PostBn(), const BwdBn& bwd = BwdBn(), const jobs::ReduceJob& rj = jobs::ReduceJob(), const WgradFused& wg = WgradFused()) {
+    if constexpr (T && PRE == 3)
+        if (w.planes && post.gamma)
+            return launch_form<true, C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG, true>(s, src, w, add, dst, bn_partial, N, pre, post, bwd, rj, wg);
     if constexpr (!T || PRE == 3)           // what a network's step launches
         if (w.planes) return launch_form<true, C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG>(s, src, w, add, dst, bn_partial, N, pre, post, bwd, rj, wg);
     return launch_form<false, C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG>(s, src, w, add, dst, bn_partial, N, pre, post, bwd, rj, wg);

@@ -51,7 +51,8 @@ int form_fwd(void* stream, const float* src, const float* records, int parts, co
 template <class F>
 int form_bwd(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma, const float* in_records, int parts,
              float* dgamma, float* dbeta, float* dx, float* partial, const Filter3x3& w, const float* add, float* out, const float* x_in,
-             const float* xc_post, const float* stats_post, float* records, const jobs::Partials& red, int N, int H, int C) {
+             const float* xc_post, const float* stats_post, float* records, const jobs::Partials& red, int N, int H, int C,
+             const float* gamma_post = nullptr, const float* beta_post = nullptr) {
     if (!dz || !xc || !stats || !gamma || !in_records || !dgamma || !dbeta || !w.w || !out || !x_in || !xc_post || !stats_post || !records) return -1;
     if (form_parts<F>(N, H, C) == 0 || !form_merges<F>(parts, C) || in_records == records || out == dz) return -1;
     // 64 channels: dx for a d-filter kernel of its own or, in a network's step with small workgroups, the partial filter gradients (one an image)
@@ -61,8 +62,8 @@ int form_bwd(void* stream, const float* dz, const float* xc, const float* stats,
     BwdBn bwd;
     bwd.xc = xc; bwd.stats = stats; bwd.gamma = gamma; bwd.totals = nullptr; bwd.records = in_records; bwd.parts = parts;
     bwd.dgamma = dgamma; bwd.dbeta = dbeta; bwd.inv_m = 1.0f / (float)((long)N * H * H); bwd.dx_out = dx;
-    PostBn post;
-    post.mask_src = x_in; post.xc = xc_post; post.stats = stats_post; post.records = records;
+    PostBn post{};
+    post.mask_src = x_in; post.xc = xc_post; post.stats = stats_post; post.records = records; post.gamma = gamma_post; post.beta = beta_post;
     const jobs::ReduceJob rj = reduce_job(red, 64 * F::WAVES);
     WgradFused wg;
     wg.x_in = x_in; wg.partial = partial;
@@ -70,7 +71,8 @@ int form_bwd(void* stream, const float* dz, const float* xc, const float* stats,
     if (C == 16) return launch<16, 32, F::R16, 1, F::WAVES, true, 3, true, true>(s, dz, w, add, out, nullptr, N, PreBn{}, post, bwd, rj, wg);
     if (C == 32) return launch<32, 16, F::R32, 1, F::WAVES, true, 3, true, true>(s, dz, w, add, out, nullptr, N, PreBn{}, post, bwd, rj, wg);
     if constexpr (F::SPLIT64 == 4)
-        return fused ? launch_form<true, 64, 8, 8, 4, F::WAVES, true, 3, true, true>(s, dz, w, add, out, nullptr, N, PreBn{}, post, bwd, rj, wg)
+        return fused ? gamma_post ? launch_form<true, 64, 8, 8, 4, F::WAVES, true, 3, true, true, true>(s, dz, w, add, out, nullptr, N, PreBn{}, post, bwd, rj, wg)
+                                  : launch_form<true, 64, 8, 8, 4, F::WAVES, true, 3, true, true>(s, dz, w, add, out, nullptr, N, PreBn{}, post, bwd, rj, wg)
                      : launch_form<false, 64, 8, 8, 4, F::WAVES, true, 3, true, false>(s, dz, w, add, out, nullptr, N, PreBn{}, post, bwd, rj, wg);
     else
         return launch<64, 8, 8, F::SPLIT64, F::WAVES, true, 3, true>(s, dz, w, add, out, nullptr, N, PreBn{}, post, bwd, rj);
@@ -88,9 +90,10 @@ int form_bwd(void* stream, const float* dz, const float* xc, const float* stats,
     int conv3x3_##NAME##_bwd(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,                              \
                              const float* in_records, int parts, float* dgamma, float* dbeta, float* dx, float* partial,                           \
                              const Filter3x3& w, const float* add, float* out, const float* x_in, const float* xc_post,                            \
-                             const float* stats_post, float* records, const jobs::Partials& red, int N, int H, int C) {                            \
+                             const float* stats_post, float* records, const jobs::Partials& red, int N, int H, int C, const float* gamma_post,     \
+                             const float* beta_post) {                                                                                             \
         return form_bwd<F>(stream, dz, xc, stats, gamma, in_records, parts, dgamma, dbeta, dx, partial, w, add, out, x_in, xc_post, stats_post,   \
-                           records, red, N, H, C);                                                                                                 \
+                           records, red, N, H, C, gamma_post, beta_post);                                                                          \
     }                                                                                                                                              \
     extern "C" int dsspk_conv3x3_##NAME##_parts(int N, int H, int C) { return form_parts<F>(N, H, C); }                                            \
     extern "C" int dsspk_conv3x3_##NAME##_fwd(void* stream, const float* src, const float* records, int parts, const float* gamma,                \
@@ -105,5 +108,5 @@ int form_bwd(void* stream, const float* dz, const float* xc, const float* stats,
                                               const float* stats_post, float* records, const float* red_partial, float* red_dw, int red_E,        \
                                               int red_chunks, int N, int H, int C) {                                                               \
         return conv3x3_##NAME##_bwd(stream, dz, xc, stats, gamma, in_records, parts, dgamma, dbeta, dx, partial, w, add, out, x_in, xc_post,      \
-                                    stats_post, records, jobs::Partials{red_partial, red_dw, red_E, red_chunks, false}, N, H, C);                 \
+                                    stats_post, records, jobs::Partials{red_partial, red_dw, red_E, red_chunks, false}, N, H, C, nullptr, nullptr); \
     }

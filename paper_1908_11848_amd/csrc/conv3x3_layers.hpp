@@ -27,16 +27,18 @@ int conv3x3_tiled_dgrad_bn(hipStream_t s, const float* dz, const float* xc, cons
                             const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta, float* dx_out,
                             const Filter3x3& w, const float* add, float* out,
                             const float* mask_src, const float* xc_post, const float* stats_post, float* records,
-                            const float* red_partial, float* red_dw, int red_E, int red_chunks, int N, int HW, int C);
+                            const float* red_partial, float* red_dw, int red_E, int red_chunks, int N, int HW, int C,
+                            const float* gamma_post = nullptr, const float* beta_post = nullptr);
 int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc, const float* stats, const float* gamma,
                                   const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta,
                                   const Filter3x3& w, const float* add, float* out,
                                   const float* xc_post, const float* stats_post, float* records,
                                   const float* x_in, float* partial, const float* red_partial, float* red_dw, int red_E,
-                                  int red_chunks, int N, int HW, int C);
+                                  int red_chunks, int N, int HW, int C, const float* gamma_post = nullptr, const float* beta_post = nullptr);
 
 // k_conv3x3_large.hip, k_conv3x3_small.hip: dsspk_conv3x3_large_* and dsspk_conv3x3_small_*.  small_bwd with converted filters takes `partial` for 64
-// channels too: one partial result an image, to be reduced as Partials::quads.
+// channels too: one partial result an image, to be reduced as Partials::quads.  gamma_post, beta_post:
+// of the batch norm of xc_post, if x_in is ReLU(BN(xc_post)) with nothing added (else NULL).
 #define CONV3X3_FORM_LAUNCHERS(NAME)                                                                                                          \
     int conv3x3_##NAME##_fwd(void* stream, const float* src, const float* records, int parts, const float* gamma, const float* beta,         \
                              float eps, const float* shortcut, float* act_out, float* stats_out, const Filter3x3& w, float* dst,              \
@@ -44,6 +46,7 @@ int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc
     int conv3x3_##NAME##_bwd(void* stream, const float* dz, const float* xc, const float* stats, const float* gamma,                         \
                              const float* in_records, int parts, float* dgamma, float* dbeta, float* dx, float* partial,                      \
                              const Filter3x3& w, const float* add, float* out, const float* x_in, const float* xc_post,                       \
-                             const float* stats_post, float* records, const jobs::Partials& red, int N, int H, int C);
+                             const float* stats_post, float* records, const jobs::Partials& red, int N, int H, int C, const float* gamma_post,  \
+                             const float* beta_post);
 CONV3X3_FORM_LAUNCHERS(large)
 CONV3X3_FORM_LAUNCHERS(small)

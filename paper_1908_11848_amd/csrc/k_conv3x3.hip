@@ -164,7 +164,7 @@ int conv3x3_tiled_prebn(hipStream_t s, const float* src, const float* records, i
 // batch norm that comes next in the backward direction, see PostBn.
 int conv3x3_tiled_dgrad_post(hipStream_t s, const float* dy, const float* w, const float* add, float* dz,
                               const float* mask_src, const float* xc, const float* stats, float* records, int N, int HW, int C) {
-    PostBn post;
+    PostBn post{};
     post.mask_src = mask_src; post.xc = xc; post.stats = stats; post.records = records;
     if (C == 16 && HW == 32) return launch<16, 32, 8, 1, 4, true, 0, true>(s, dy, w, add, dz, nullptr, N, PreBn(), post);
     if (C == 32 && HW == 16) return launch<32, 16, 8, 1, 4, true, 0, true>(s, dy, w, add, dz, nullptr, N, PreBn(), post);
@@ -178,14 +178,15 @@ int conv3x3_tiled_dgrad_bn(hipStream_t s, const float* dz, const float* xc, cons
                             const float* totals, const float* in_records, int parts, float* dgamma, float* dbeta, float* dx_out,
                             const Filter3x3& w, const float* add, float* out,
                             const float* mask_src, const float* xc_post, const float* stats_post, float* records,
-                            const float* red_partial, float* red_dw, int red_E, int red_chunks, int N, int HW, int C) {
+                            const float* red_partial, float* red_dw, int red_E, int red_chunks, int N, int HW, int C,
+                            const float* gamma_post, const float* beta_post) {
     if (!totals && !records_inline(parts, C)) return -1;
     BwdBn bwd;
     bwd.xc = xc; bwd.stats = stats; bwd.gamma = gamma; bwd.totals = totals; bwd.dx_out = dx_out;
     bwd.records = in_records; bwd.parts = parts; bwd.dgamma = dgamma; bwd.dbeta = dbeta;
     bwd.inv_m = 1.0f / (float)((long)N * HW * HW);
-    PostBn post;
-    post.mask_src = mask_src; post.xc = xc_post; post.stats = stats_post; post.records = records;
+    PostBn post{};
+    post.mask_src = mask_src; post.xc = xc_post; post.stats = stats_post; post.records = records; post.gamma = gamma_post; post.beta = beta_post;
     const jobs::ReduceJob rj = reduce_job({red_partial, red_dw, red_E, red_chunks, false}, THREADS);
     if (C == 16 && HW == 32) return launch<16, 32, 8, 1, 4, true, 3, true>(s, dz, w, add, out, nullptr, N, PreBn(), post, bwd, rj);
     if (C == 32 && HW == 16) return launch<32, 16, 8, 1, 4, true, 3, true>(s, dz, w, add, out, nullptr, N, PreBn(), post, bwd, rj);
@@ -200,14 +201,14 @@ int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc
                                   const Filter3x3& w, const float* add, float* out,
                                   const float* xc_post, const float* stats_post, float* records,
                                   const float* x_in, float* partial, const float* red_partial, float* red_dw, int red_E,
-                                  int red_chunks, int N, int HW, int C) {
+                                  int red_chunks, int N, int HW, int C, const float* gamma_post, const float* beta_post) {
     if (!totals && !records_inline(parts, C)) return -1;
     BwdBn bwd;
     bwd.xc = xc; bwd.stats = stats; bwd.gamma = gamma; bwd.totals = totals; bwd.dx_out = nullptr;
     bwd.records = in_records; bwd.parts = parts; bwd.dgamma = dgamma; bwd.dbeta = dbeta;
     bwd.inv_m = 1.0f / (float)((long)N * HW * HW);
-    PostBn post;
-    post.mask_src = x_in; post.xc = xc_post; post.stats = stats_post; post.records = records;
+    PostBn post{};
+    post.mask_src = x_in; post.xc = xc_post; post.stats = stats_post; post.records = records; post.gamma = gamma_post; post.beta = beta_post;
     const jobs::ReduceJob rj = reduce_job({red_partial, red_dw, red_E, red_chunks, false}, THREADS);
     WgradFused wg;
     wg.x_in = x_in; wg.partial = partial;

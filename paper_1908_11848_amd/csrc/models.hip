@@ -445,12 +445,12 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     // epilogue (mask_src = x_in, xc_post, st_post -> records) into out, and d-filter (x_in, dx) into dw (pending).
     // The sums of dz: in_rec / in_parts / in_dgamma / in_dbeta, added up by the kernel itself in the larger and the smaller workgroups; between
     // them (33 images and more: more records than a workgroup of those kernels adds up) already in tot (ready) or by a launch here, and
-    // sum_next: the records just written are summed into ntot / ndgamma / ndbeta for the next layer.
+    // gamma_post, beta_post: of the batch norm of xc_post, if x_in is ReLU(BN(xc_post)) with nothing added; sum_next: the records just written are summed into ntot / ndgamma / ndbeta for the next layer.
     auto regular_layer = [&](const float* in_rec, int in_parts, float* in_dgamma, float* in_dbeta, bool ready,
                              const float* dz, const float* xc, const float* st, const float* gamma, float* tot,
                              const Filter3x3& wt, const float* add, float* out, const float* x_in, const float* xc_post,
                              const float* st_post, float* records, float* dw, int H, int Cc, bool sum_next, int nparts,
-                             float* ntot, float* ndgamma, float* ndbeta) -> int {
+                             float* ntot, float* ndgamma, float* ndbeta, const float* gamma_post = nullptr, const float* beta_post = nullptr) -> int {
         float* out_scr = free_scr();
         const jobs::Partials red = pend.n ? pend.p[0] : jobs::Partials{};
         if (pend.n) pop_front();
@@ -459,7 +459,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             const auto bwd = large ? conv3x3_large_bwd : conv3x3_small_bwd;
             const bool apart = large && Cc == 64;           // a d-filter kernel of its own
             RUN(bwd(s, dz, xc, st, gamma, in_rec, in_parts, in_dgamma, in_dbeta, apart ? g1 : nullptr, apart ? nullptr : out_scr, wt, add, out,
-                    x_in, xc_post, st_post, records, red, m, H, Cc));
+                    x_in, xc_post, st_post, records, red, m, H, Cc, gamma_post, beta_post));
             if (apart) RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, nullptr, 0, 0, nullptr, nullptr, nullptr, &chunks));
             push_back(out_scr, dw, 9 * Cc * Cc, chunks, small && Cc == 64);
             return 0;
@@ -468,11 +468,11 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         int chunks = dsspk_conv_bwd_fused_chunks(m, H, Cc);
         if (chunks > 0) {
             RUN(conv3x3_tiled_dgrad_bn_wgrad((hipStream_t)s, dz, xc, st, gamma, tot, in_rec, in_parts, in_dgamma, in_dbeta, wt, add, out, xc_post,
-                                             st_post, records, x_in, out_scr, red.partial, red.dw, red.E, red.chunks, m, H, Cc));
+                                             st_post, records, x_in, out_scr, red.partial, red.dw, red.E, red.chunks, m, H, Cc, gamma_post, beta_post));
             if (sum_next) RUN(dsspk_bn_bwd_totals(s, records, nparts, Cc, ntot, ndgamma, ndbeta));
         } else {
             RUN(conv3x3_tiled_dgrad_bn((hipStream_t)s, dz, xc, st, gamma, tot, in_rec, in_parts, in_dgamma, in_dbeta, g1, wt, add, out, x_in,
-                                       xc_post, st_post, records, red.partial, red.dw, red.E, red.chunks, m, H, Cc));
+                                       xc_post, st_post, records, red.partial, red.dw, red.E, red.chunks, m, H, Cc, gamma_post, beta_post));
             RUN(dsspk_conv_bwd_weight_parts(s, x_in, g1, out_scr, m, H, H, Cc, Cc, 3, 3, 1, 1, sum_next ? records : nullptr,
                                             nparts, Cc, ntot, ndgamma, ndbeta, &chunks));
         }
@@ -498,7 +498,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             tot0 = false;
         }
         RUN(regular_layer(recB0, parts0, g + B.g2, g + B.b2, tot0, g0, F(B.c2), F(B.st2), w + B.g2, totB, input_filter(B.w2, B.f2, B.cout), nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr,
-                          g + B.w2, Ho, B.cout, fused1, parts1, totA, g + B.g1, g + B.b1));        // sums of BN1's records to totA if fused1
+                          g + B.w2, Ho, B.cout, fused1, parts1, totA, g + B.g1, g + B.b1, w + B.g1, w + B.b1));        // sums of BN1's records to totA if fused1
         // ---- BN1 + conv1: g2 = dz1 -> g1 = d conv1 output; d-input (+ dz2 through an identity shortcut) = gradient
         //      w.r.t. the block's input, which is the previous block's (or the stem's) post-ReLU output: mask +
         //      records of ITS batch norm in the same kernel where the specialised kernel applies

@@ -17,6 +17,7 @@
 #include "jobs.hpp"
 #include "mma.hpp"
 #include "split.hpp"
+#include "conv_split_layers.hpp"
 #include "../../include/dssp_kernels.h"
 
 namespace {
@@ -66,15 +67,18 @@ constexpr int ROWS_F = R + 1;                                               // c
 constexpr int RING_PITCH = 16 * 4 + 16, RING_ROW = HW * RING_PITCH, RING = 3 * RING_ROW;
 constexpr int FWD_LDS = (ROWS_F + F - 1) * HW * TPITCH + 4 * RING;
 
+template <class... Job>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2))) void conv_first_kernel(
     const float* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias, float* __restrict__ a,
-    float4* __restrict__ pooled, uchar4* __restrict__ arg) {
+    float4* __restrict__ pooled, uchar4* __restrict__ arg, int own_blocks, Job... job) {
+    if constexpr (sizeof...(Job) > 0)
+        if ((int)blockIdx.x >= own_blocks) return (..., convert_filters(job, blockIdx.x - own_blocks));
     extern __shared__ __attribute__((aligned(16))) char lds_bytes[];
     char* T = lds_bytes;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, q = lane >> 4;
     char* ring = lds_bytes + (ROWS_F + F - 1) * HW * TPITCH + wave * RING;
-    const int tile = xcd_tile(blockIdx.x, gridDim.x), n = tile / BANDS, band = tile % BANDS, r0 = band * R;
+    const int tile = xcd_tile(blockIdx.x, own_blocks), n = tile / BANDS, band = tile % BANDS, r0 = band * R;
 
     float4 fr[F][1];
 #pragma unroll
@@ -381,28 +385,55 @@ int allow_lds(K kern, int bytes, bool& done) {           // raise the dynamic-LD
 
 }  // namespace
 
-extern "C" int dsspk_conv_first_pool_fwd(void* stream, const float* x, const float* w, const float* bias, float* a, float* pooled,
-                                         uint8_t* arg, int N) {
+__global__ __launch_bounds__(SplitFilterJob::THREADS) void convert_filters_kernel(SplitFilterJob job) { convert_filters(job, blockIdx.x); }
+
+template <class... Job>
+static int launch_fwd(hipStream_t s, const float* x, const float* w, const float* bias, float* a, float* pooled, uint8_t* arg, int N, int more_blocks,
+                      const Job&... job) {
     if (!x || !w || !bias || !a || !pooled || !arg || N < 1 || (long)N * HW * HW >= 1L << 31) return -1;
     static bool done = false;
-    if (allow_lds(conv_first_kernel, FWD_LDS, done)) return -1;
-    hipLaunchKernelGGL(conv_first_kernel, dim3(N * BANDS), dim3(THREADS), FWD_LDS, (hipStream_t)stream, x, w, bias, a,
-                       reinterpret_cast<float4*>(pooled), reinterpret_cast<uchar4*>(arg));
+    if (allow_lds(conv_first_kernel<Job...>, FWD_LDS, done)) return -1;
+    hipLaunchKernelGGL((conv_first_kernel<Job...>), dim3(N * BANDS + more_blocks), dim3(THREADS), FWD_LDS, s, x, w, bias, a, reinterpret_cast<float4*>(pooled),
+                       reinterpret_cast<uchar4*>(arg), N * BANDS, job...);
     return DSSPK_LAUNCH_RC();
+}
+
+int conv_first_pool_fwd(hipStream_t s, const float* x, const float* w, const float* bias, float* a, float* pooled, uint8_t* arg, int N, SplitFilterJob job) {
+    // Not where the job alone would begin a second round of workgroups, two to a compute unit.  A round of pushes, two 5x5 layers, conversion by
+    // a launch of its own / carried, us: batch 128, four workers 631 / 637 and 633 / 649, 95 492 / 490, 512, two workers 1102 / 1088; three
+    // convolutions: batch 37 408 / 390, 140 769 / 760.
+    constexpr int ROUND = 2 * 256;
+    const int own = N * BANDS;
+    if (own > ROUND || own + job.blocks() <= ROUND) return launch_fwd(s, x, w, bias, a, pooled, arg, N, job.blocks(), job);
+    if (const int rc = launch_fwd(s, x, w, bias, a, pooled, arg, N, 0)) return rc;
+    hipLaunchKernelGGL(convert_filters_kernel, dim3(job.blocks()), dim3(SplitFilterJob::THREADS), 0, s, job);
+    return DSSPK_LAUNCH_RC();
+}
+
+extern "C" int dsspk_conv_first_pool_fwd(void* stream, const float* x, const float* w, const float* bias, float* a, float* pooled,
+                                         uint8_t* arg, int N) {
+    return launch_fwd((hipStream_t)stream, x, w, bias, a, pooled, arg, N, 0);
 }
 
 extern "C" size_t dsspk_conv_first_scratch_floats(int N) {
     return N < 1 ? 0 : (size_t)ceil_div((long)N * BANDS, bands_per_chunk(N)) * (E + CO);
 }
 
-extern "C" int dsspk_conv_first_pool_bwd_weight(void* stream, const float* x, const float* dpooled, const float* pooled, const uint8_t* arg,
-                                                float* dw, float* scratch, int N) {
+int conv_first_pool_bwd_weight_parts(hipStream_t stream, const float* x, const float* dpooled, const float* pooled, const uint8_t* arg, float* dw,
+                                     float* scratch, int N, jobs::Partials* waiting) {
     if (!x || !dpooled || !pooled || !arg || !dw || !scratch || N < 1 || (long)N * HW * HW >= 1L << 31) return -1;
     static bool done = false;
     if (allow_lds(conv_first_wgrad_kernel, WGRAD_LDS, done)) return -1;
     const int per = bands_per_chunk(N), chunks = ceil_div((long)N * BANDS, per);
-    hipLaunchKernelGGL(conv_first_wgrad_kernel, dim3(chunks), dim3(THREADS), WGRAD_LDS, (hipStream_t)stream, x, dpooled, pooled, arg, scratch,
+    hipLaunchKernelGGL(conv_first_wgrad_kernel, dim3(chunks), dim3(THREADS), WGRAD_LDS, stream, x, dpooled, pooled, arg, scratch,
                        N * BANDS, per);
-    if (const int rc = DSSPK_LAUNCH_RC()) return rc;
-    return dsspk_wgrad_reduce(stream, scratch, dw, E + CO, chunks);
+    *waiting = {scratch, dw, E + CO, chunks, false};
+    return DSSPK_LAUNCH_RC();
+}
+
+extern "C" int dsspk_conv_first_pool_bwd_weight(void* stream, const float* x, const float* dpooled, const float* pooled, const uint8_t* arg,
+                                                float* dw, float* scratch, int N) {
+    jobs::Partials p;
+    if (const int rc = conv_first_pool_bwd_weight_parts((hipStream_t)stream, x, dpooled, pooled, arg, dw, scratch, N, &p)) return rc;
+    return dsspk_wgrad_reduce(stream, p.partial, p.dw, p.E, p.chunks);
 }

@@ -6,6 +6,7 @@
 #include "jobs.hpp"
 #include "mma.hpp"
 #include "split.hpp"
+#include "conv_split_layers.hpp"
 #include "../../include/dssp_kernels.h"
 
 namespace {
@@ -14,49 +15,6 @@ constexpr int THREADS = 256;
 constexpr size_t LDS_MAX = 160 * 1024;
 
 // ---------------------------------------------------------------------------------------------
-// Filter planes in operand order: [step][16 result channels][plane][lane] of 16 bytes, step = (tap, 32 reduction channels),
-// lane (l16, q) holding the reduction channels 8 q .. 8 q + 7 of result channel l16.  A wavefront then fetches an operand
-// as one contiguous KiB.  Written once per step, read by every workgroup of the layer's convolutions.
-// A value that the terms cannot hold (2^103 or more, infinite, NaN) has NaN as its leading term, which spoils every sum it enters, and
-// its two halves in the place of the others, where the computation in fp32 finds it.
-//   TR = false: result channel = output channel;  true (d-input): result = input channel, taps reversed
-constexpr float WIDE = 0x1p103f;
-constexpr unsigned BF16_NAN = 0x7fc0u;
-struct Frag {
-    const float* w;
-    uint4* out;
-    int taps, IC, OC;       // of the layer
-};
-
-__device__ __forceinline__ void filter_frag(const Frag& f, bool tr, long idx) {
-    const int RC = tr ? f.OC : f.IC, RS = tr ? f.IC : f.OC;      // reduction / result channels
-    const int lane = (int)(idx & 63);
-    const long r = idx >> 6;
-    const int tiles = RS / 16, tile = (int)(r % tiles), step = (int)(r / tiles);
-    const int c32 = step % (RC / 32), tap = step / (RC / 32);
-    const int rs = 16 * tile + (lane & 15), rc = 32 * c32 + 8 * (lane >> 4);
-    float v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        v[j] = tr ? f.w[((long)(f.taps - 1 - tap) * f.IC + rs) * f.OC + rc + j] : f.w[((long)tap * f.IC + rc + j) * f.OC + rs];
-    float t[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) t[j] = v[j] * split::SCALE;
-#pragma unroll
-    for (int p = 0; p < split::PLANES; ++p) {
-        unsigned u[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) u[j] = split::take(t[2 * j], t[2 * j + 1]);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (fabsf(v[j]) < WIDE) continue;               // (not so for NaN)
-            const unsigned bits = __float_as_uint(v[j]), part = p == 0 ? BF16_NAN : p == 1 ? bits >> 16 : bits & 0xffffu;
-            u[j / 2] = j % 2 ? (u[j / 2] & 0xffffu) | part << 16 : (u[j / 2] & 0xffff0000u) | part;
-        }
-        f.out[(r * split::PLANES + p) * 64 + lane] = make_uint4(u[0], u[1], u[2], u[3]);
-    }
-}
-
 // the value again from its terms (16 bits each)
 __device__ __forceinline__ float filter_value(unsigned t0, unsigned t1, unsigned t2) {
     if ((t0 & 0x7fffu) == BF16_NAN) return __uint_as_float(t1 << 16 | t2);
@@ -917,15 +875,21 @@ extern "C" size_t dsspk_conv_split_wgrad_scratch_floats(int N, int H, int W, int
     return (size_t)ceil_div(g.N * g.bands, wgrad_items(g, k)) * ((size_t)k * k * Cin * Cout + Cout);
 }
 
-extern "C" int dsspk_conv_split_bwd_weight(void* stream, const float* x, const float* dy, float* dw, int with_bias, float* scratch, int N,
-                                           int H, int W, int Cin, int Cout, int k, int pad) {
+int conv_split_bwd_weight_parts(hipStream_t stream, const float* x, const float* dy, float* dw, int with_bias, float* scratch, int N, int H, int W,
+                                int Cin, int Cout, int k, int pad, jobs::Partials* waiting) {
     if (!x || !dy || !dw || !scratch || !dsspk_conv_split_covers(N, H, W, Cin, Cout, k, pad)) return -1;
     Geom g = forward_geom(N, H, W, Cin, Cout, k, pad);
     wgrad_rows(g, k);
     const int per = wgrad_items(g, k), chunks = ceil_div(g.N * g.bands, per);
     const dim3 grid(chunks, k * (Cin / 32), Cout / 64);
-    hipStream_t s = (hipStream_t)stream;
-    const int rc1 = k == 5 ? launch_wgrad<5>(s, grid, x, dy, scratch, g, per, with_bias) : launch_wgrad<3>(s, grid, x, dy, scratch, g, per, with_bias);
-    if (rc1) return rc1;
-    return dsspk_wgrad_reduce(stream, scratch, dw, k * k * Cin * Cout + (with_bias ? Cout : 0), chunks);
+    if (const int rc = k == 5 ? launch_wgrad<5>(stream, grid, x, dy, scratch, g, per, with_bias) : launch_wgrad<3>(stream, grid, x, dy, scratch, g, per, with_bias)) return rc;
+    *waiting = {scratch, dw, k * k * Cin * Cout + (with_bias ? Cout : 0), chunks, false};
+    return 0;
+}
+
+extern "C" int dsspk_conv_split_bwd_weight(void* stream, const float* x, const float* dy, float* dw, int with_bias, float* scratch, int N,
+                                           int H, int W, int Cin, int Cout, int k, int pad) {
+    jobs::Partials p;
+    if (const int rc = conv_split_bwd_weight_parts((hipStream_t)stream, x, dy, dw, with_bias, scratch, N, H, W, Cin, Cout, k, pad, &p)) return rc;
+    return dsspk_wgrad_reduce(stream, p.partial, p.dw, p.E, p.chunks);
 }

@@ -7,6 +7,7 @@
 #include "../../include/dssp.h"
 #include "../../include/dssp_kernels.h"
 #include "conv3x3_layers.hpp"
+#include "conv_split_layers.hpp"
 #include "model.hpp"
 
 namespace dssp_model {
@@ -195,7 +196,7 @@ struct Plan {
         tens.push_back({2, logits, (int64_t)m * classes});
         row_loss = a.floats((size_t)m);
         wg_scratch = a.floats(wg ? wg : 1);
-        for (size_t& o : wg_more) o = a.floats(is_resnet(id) && wg ? wg : 1);
+        for (size_t& o : wg_more) o = a.floats(wg ? wg : 1);
         bn_scratch = a.floats(bn ? bn : 1);
         bn_scratch2 = a.floats(bn ? bn : 1);
         tot_a = a.floats(128); tot_b = a.floats(128);          // batch-norm backward sums (2 x 64 channels at most)
@@ -250,21 +251,23 @@ int step_alexnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, c
     const int64_t cw1 = 0, cb1 = 4800, cw2 = cb1 + 64, cb2 = cw2 + 102400, fw1 = cb2 + 64, fb1 = fw1 + 3136 * 384,
                   fw2 = fb1 + 384, fb2 = fw2 + 384 * 192, fw3 = fb2 + 192, fb3 = fw3 + 192 * (int64_t)C;
     // forward
-    RUN(dsspk_conv_first_pool_fwd(s, x, w + cw1, w + cb1, a1, p1, arg1, m));
-    RUN(dsspk_conv_split_filters(s, w + cw2, ws + P->wide2.fwd, ws + P->wide2.bwd, 64, 64, 5));
+    SplitFilterJob filters;
+    filters.add(w + cw2, ws + P->wide2.fwd, ws + P->wide2.bwd, 64, 5);
+    RUN(conv_first_pool_fwd((hipStream_t)s, x, w + cw1, w + cb1, a1, p1, arg1, m, filters));
     RUN(dsspk_conv_split_fwd(s, p1, ws + P->wide2.fwd, w + cb2, a2, m, 15, 15, 64, 64, 5, 2, 1));
     RUN(dsspk_maxpool_fwd(s, a2, p2, arg2, m, 15, 15, 64));
     RUN(dsspk_gemm(s, p2, 3136, 1, w + fw1, 384, 1, a3, 384, m, 384, 3136, w + fb1, 1));
     RUN(dsspk_gemm(s, a3, 384, 1, w + fw2, 192, 1, a4, 192, m, 192, 384, w + fb2, 1));
     if (int rc = last_layer(P, ws, s, a4, 192, y, w, g, fw3, fb3, da4, 1, loss, err)) return rc;
-    // backward
+    // backward; the convolutions' partial filter gradients wait for one launch at the end
+    jobs::Partials waiting[2];
     RUN(dsspk_fc_bwd(s, a3, da4, w + fw2, g + fw2, g + fb2, da3, 1, nullptr, nullptr, m, 384, 192));
     RUN(dsspk_fc_bwd(s, p2, da3, w + fw1, g + fw1, g + fb1, dp2, 0, nullptr, nullptr, m, 3136, 384));
     RUN(dsspk_maxpool_bwd_relu(s, dp2, arg2, a2, da2, m, 15, 15, 64));
-    RUN(dsspk_conv_split_bwd_weight(s, p1, da2, g + cw2, 1, scr, m, 15, 15, 64, 64, 5, 2));      // and the biases behind the filter
+    RUN(conv_split_bwd_weight_parts((hipStream_t)s, p1, da2, g + cw2, 1, F(P->wg_more[0]), m, 15, 15, 64, 64, 5, 2, &waiting[1]));      // and the biases behind the filter
     RUN(dsspk_conv_split_bwd_data(s, da2, ws + P->wide2.bwd, nullptr, dp1, m, 15, 15, 64, 64, 5, 2));
-    RUN(dsspk_conv_first_pool_bwd_weight(s, x, dp1, p1, arg1, g + cw1, scr, m));      // and the biases behind the filter
-    return 0;
+    RUN(conv_first_pool_bwd_weight_parts((hipStream_t)s, x, dp1, p1, arg1, g + cw1, scr, m, &waiting[0]));      // and the biases behind the filter
+    return wgrad_reduce_many((hipStream_t)s, 2, waiting);
 }
 
 // The reduced AlexNet with three convolutional and two fully connected layers (Sec. V-A3); the layers and kernels of
@@ -279,23 +282,25 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
     const int64_t cw1 = 0, cb1 = 4800, cw2 = cb1 + 64, cb2 = cw2 + 102400, cw3 = cb2 + 64, cb3 = cw3 + 36864,
                   fw1 = cb3 + 64, fb1 = fw1 + 3136 * 384, fw2 = fb1 + 384, fb2 = fw2 + 384 * (int64_t)C;
     // forward
-    RUN(dsspk_conv_first_pool_fwd(s, x, w + cw1, w + cb1, a1, p1, arg1, m));
-    RUN(dsspk_conv_split_filters(s, w + cw2, ws + P->wide2.fwd, ws + P->wide2.bwd, 64, 64, 5));
+    SplitFilterJob filters;
+    filters.add(w + cw2, ws + P->wide2.fwd, ws + P->wide2.bwd, 64, 5);
+    filters.add(w + cw3, ws + P->wide3.fwd, ws + P->wide3.bwd, 64, 3);
+    RUN(conv_first_pool_fwd((hipStream_t)s, x, w + cw1, w + cb1, a1, p1, arg1, m, filters));
     RUN(dsspk_conv_split_fwd(s, p1, ws + P->wide2.fwd, w + cb2, a2, m, 15, 15, 64, 64, 5, 2, 1));
     RUN(dsspk_maxpool_fwd(s, a2, p2, arg2, m, 15, 15, 64));
-    RUN(dsspk_conv_split_filters(s, w + cw3, ws + P->wide3.fwd, ws + P->wide3.bwd, 64, 64, 3));
     RUN(dsspk_conv_split_fwd(s, p2, ws + P->wide3.fwd, w + cb3, c3, m, 7, 7, 64, 64, 3, 1, 1));
     RUN(dsspk_gemm(s, c3, 3136, 1, w + fw1, 384, 1, a3, 384, m, 384, 3136, w + fb1, 1));
     if (int rc = last_layer(P, ws, s, a3, 384, y, w, g, fw2, fb2, da3, 1, loss, err)) return rc;
-    // backward
+    // backward, as above
+    jobs::Partials waiting[3];
     RUN(dsspk_fc_bwd(s, c3, da3, w + fw1, g + fw1, g + fb1, dc3, 1, nullptr, nullptr, m, 3136, 384));
-    RUN(dsspk_conv_split_bwd_weight(s, p2, dc3, g + cw3, 1, scr, m, 7, 7, 64, 64, 3, 1));
+    RUN(conv_split_bwd_weight_parts((hipStream_t)s, p2, dc3, g + cw3, 1, F(P->wg_more[1]), m, 7, 7, 64, 64, 3, 1, &waiting[2]));
     RUN(dsspk_conv_split_bwd_data(s, dc3, ws + P->wide3.bwd, nullptr, dp2, m, 7, 7, 64, 64, 3, 1));
     RUN(dsspk_maxpool_bwd_relu(s, dp2, arg2, a2, da2, m, 15, 15, 64));
-    RUN(dsspk_conv_split_bwd_weight(s, p1, da2, g + cw2, 1, scr, m, 15, 15, 64, 64, 5, 2));      // and the biases behind the filter
+    RUN(conv_split_bwd_weight_parts((hipStream_t)s, p1, da2, g + cw2, 1, F(P->wg_more[0]), m, 15, 15, 64, 64, 5, 2, &waiting[1]));      // and the biases behind the filter
     RUN(dsspk_conv_split_bwd_data(s, da2, ws + P->wide2.bwd, nullptr, dp1, m, 15, 15, 64, 64, 5, 2));
-    RUN(dsspk_conv_first_pool_bwd_weight(s, x, dp1, p1, arg1, g + cw1, scr, m));      // and the biases behind the filter
-    return 0;
+    RUN(conv_first_pool_bwd_weight_parts((hipStream_t)s, x, dp1, p1, arg1, g + cw1, scr, m, &waiting[0]));      // and the biases behind the filter
+    return wgrad_reduce_many((hipStream_t)s, 3, waiting);
 }
 
 constexpr int LARGE_ABOVE = 96;

@@ -274,7 +274,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     unsigned filter_at;
     if constexpr (PL) {
         const Role r = role_of(tid);
-        filter_at = ((C == 64 ? 4 * r.ks : 0) + r.co_w / 16) * 192 + r.lane;
+        filter_at = ((C == 64 ? 4 * r.ks : 0) + r.co_w / 16) * filter3x3_quads(C) * 64 + r.lane;
     } else {
         const Role r = role_of(tid);
         const int k0 = C == 16 ? 4 * r.q : 32 * r.ks + 8 * r.q;
@@ -284,8 +284,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         const int tap = 3 * ky + kx;
         if constexpr (PL) {
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
-                filt[kx % COLUMNS][ky].v[p] = (planes + (tap * (filter3x3_operands(C) / 9) * 3 + p) * 64)[filter_at];
+            for (int p = 0; p < filter3x3_quads(C); ++p)
+                filt[kx % COLUMNS][ky].v[C == 16 ? 2 * p : p] = (planes + (tap * (filter3x3_operands(C) / 9) * filter3x3_quads(C) + p) * 64)[filter_at];
         } else {
 #pragma unroll
             for (int e = 0; e < FV; ++e) {
@@ -577,6 +577,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
                 if (i % ST == (LAST + ky + 1) % ST && kx + (ky < 2) >= 1 && kx + (ky < 2) <= 2) split_filter(ky, kx + (ky < 2));
                 if (!PL && COLUMNS == 1 && st == LAST + ky - 1 && kx < 2) load_filter(ky, kx + 1);
             }
+            if constexpr (PL && C == 16)                // the quad that is not stored, for the row that this step is the first to use
+                if (st < 3) {
+                    split::Filt<C>& f = filt[kx % COLUMNS][st];
+                    f.v[1] = make_uint4(f.v[2].z, f.v[2].w, f.v[2].x, f.v[2].y);
+                }
             if (i + 1 < 3 * ST) x[(i + 1) & 1] = pixels(i + 1);
             __builtin_amdgcn_sched_barrier(0);      // or the compiler moves the reads down to their use, behind the products
 #pragma unroll

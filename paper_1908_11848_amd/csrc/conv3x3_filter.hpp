@@ -14,9 +14,13 @@ struct Filter3x3 {
     Filter3x3(const float* w_, const uint4* planes_ = nullptr) : w(w_), planes(planes_) {}
 };
 
-// Operands of one filter and direction: [tap][32 reduction channels][16 result channels][3][lane].
+// Operands of one filter and direction: [tap][32 reduction channels][16 result channels][quad][lane].  Of the three quads of 16 reduction channels, (x2, x0),
+// (x1, x0) and (x0, x1), the second is the third with its halves exchanged and is not stored (every
+// wavefront of a workgroup fetches all of such a filter; a round of pushes with three / two quads, us: 110 layers, batch 128 15382 / 15310, 56 layers, batch 2
+// 932 / 929, 20 layers, batch 8 475 / 473).
+constexpr int filter3x3_quads(int C) { return C == 16 ? 2 : 3; }
 constexpr int filter3x3_operands(int C) { return 9 * (C / 16) * (C == 16 ? 1 : C / 32); }
-constexpr size_t filter3x3_uint4s(int C) { return (size_t)filter3x3_operands(C) * 3 * 64; }
+constexpr size_t filter3x3_uint4s(int C) { return (size_t)filter3x3_operands(C) * filter3x3_quads(C) * 64; }
 
 // `count` filters of C channels, one every `stride` floats from `first` on.
 struct FilterRun { int64_t first; int count, stride; };
@@ -60,7 +64,7 @@ __device__ __forceinline__ void convert_filter(const float* __restrict__ w, uint
     }
     const split::Filt<C> terms = split::filter_operand<C>(v);
 #pragma unroll
-    for (int p = 0; p < 3; ++p) out[((int64_t)at * 3 + p) * 64 + lane] = terms.v[p];
+    for (int p = 0; p < filter3x3_quads(C); ++p) out[((int64_t)at * filter3x3_quads(C) + p) * 64 + lane] = terms.v[C == 16 ? 2 * p : p];
 }
 
 // Workgroup `block` of the job, a wavefront an operand.
@@ -68,8 +72,8 @@ __device__ __forceinline__ void convert_filters(const FilterJob& j, int block) {
     const int at = __builtin_amdgcn_readfirstlane(block * (FilterJob::THREADS / 64) + (int)threadIdx.x / 64), lane = threadIdx.x & 63;
     uint4* out = j.out;
     if (at < j.end[0]) return convert_filter<16>(j.w, out, j.run[0], at, lane);
-    out += (int64_t)j.end[0] * 192;
+    out += (int64_t)j.end[0] * filter3x3_quads(16) * 64;
     if (at < j.end[1]) return convert_filter<32>(j.w, out, j.run[1], at - j.end[0], lane);
-    out += (int64_t)(j.end[1] - j.end[0]) * 192;
+    out += (int64_t)(j.end[1] - j.end[0]) * filter3x3_quads(32) * 64;
     if (at < j.end[2]) convert_filter<64>(j.w, out, j.run[2], at - j.end[1], lane);
 }

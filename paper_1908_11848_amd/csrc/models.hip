@@ -408,7 +408,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     //   stages 1-2: ONE kernel - BN backward in its loader, d-input convolution, ReLU mask + sum records of the
     //               next batch norm in its epilogue, and the d-filter partial sums from the same LDS tiles (dx is
     //               never stored) - followed by the small kernel that sums those records
-    //   stage 3   : the d-input kernel (stores dx), then the d-filter kernel, which carries the sums job
+    //   stage 3   : the d-input kernel (stores dx), then the d-filter kernel, which carries the sums job; up to 32 images one kernel too
     // In both forms the d-input kernel carries the reduction of an earlier layer's d-filter partial sums, the oldest that waits.  A layer
     // whose d-filter kernel is of another kind leaves its partial sums waiting too; what waits at the end is one launch.
     // Everything else (stem, first convolutions of the stride-2 blocks) takes the stand-alone kernels.

@@ -58,7 +58,7 @@ struct Plan {
     size_t ax_a1 = 0, ax_p1 = 0, ax_arg1 = 0, ax_a2 = 0, ax_p2 = 0, ax_arg2 = 0, ax_a3 = 0, ax_a4 = 0;
     size_t ax_da4 = 0, ax_da3 = 0, ax_dp2 = 0, ax_da2 = 0, ax_dp1 = 0;
     size_t ax_c3 = 0, ax_dc3 = 0;     // three-convolution variant: conv3 output (post-ReLU) and its gradient
-    struct WideConv { size_t fwd = 0, bwd = 0; } wide2, wide3;      // filter planes of the convolutions behind the first one
+    struct WideConv { size_t fwd = 0, bwd = 0, partial = 0; } wide2, wide3;      // the convolutions behind the first one: filter planes, partial filter gradients
     // ResNet
     std::vector<ResBlock> blocks;
     int64_t stem_w = 0, stem_g = 0, stem_b = 0, fc_w = 0, fc_b = 0;
@@ -95,10 +95,10 @@ struct Plan {
             if (f > wg) wg = f;
             if (k == 3 && s == 1 && Cin == Cout) wg = std::max(wg, (size_t)dsspk_conv3x3_small_parts(N, H, Cin) * 9 * Cin * Cout);
         };
-        // wide stride-1 layer (dsspk_conv_split_*): room for its filter planes and the partial sums of its d-filter pass
+        // wide stride-1 layer (dsspk_conv_split_*): room for its filter planes and the partial sums of its d-filter pass, which wait for the end of
+        // the step
         auto wide_conv = [&](WideConv& c, int H, int k, int p) {
-            const size_t f = dsspk_conv_split_wgrad_scratch_floats(m, H, H, 64, 64, k, p);
-            if (f > wg) wg = f;
+            c.partial = a.floats(dsspk_conv_split_wgrad_scratch_floats(m, H, H, 64, 64, k, p));
             c.fwd = a.take(dsspk_conv_split_filter_bytes(64, 64, k));
             c.bwd = a.take(dsspk_conv_split_filter_bytes(64, 64, k));
         };
@@ -121,7 +121,7 @@ struct Plan {
             ax_a3 = a.floats((size_t)m * 384); ax_a4 = a.floats((size_t)m * 192);
             ax_da4 = a.floats((size_t)m * 192); ax_da3 = a.floats((size_t)m * 384); ax_dp2 = a.floats(s7);
             ax_da2 = a.floats(s15); ax_dp1 = a.floats(s15);
-            wg = std::max(wg, dsspk_conv_first_scratch_floats(m));
+            wg = dsspk_conv_first_scratch_floats(m);
             wide_conv(wide2, 15, 5, 2);
             tens.push_back({0, ax_a1, (int64_t)s32}); tens.push_back({0, ax_a2, (int64_t)s15});
             tens.push_back({0, ax_a3, (int64_t)m * 384}); tens.push_back({0, ax_a4, (int64_t)m * 192});
@@ -138,7 +138,7 @@ struct Plan {
             ax_c3 = a.floats(s7c); ax_a3 = a.floats((size_t)m * 384);
             ax_da3 = a.floats((size_t)m * 384); ax_dc3 = a.floats(s7c); ax_dp2 = a.floats(s7);
             ax_da2 = a.floats(s15); ax_dp1 = a.floats(s15);
-            wg = std::max(wg, dsspk_conv_first_scratch_floats(m));
+            wg = dsspk_conv_first_scratch_floats(m);
             wide_conv(wide2, 15, 5, 2);
             wide_conv(wide3, 7, 3, 1);
             tens.push_back({0, ax_a1, (int64_t)s32}); tens.push_back({0, ax_a2, (int64_t)s15});
@@ -196,7 +196,7 @@ struct Plan {
         tens.push_back({2, logits, (int64_t)m * classes});
         row_loss = a.floats((size_t)m);
         wg_scratch = a.floats(wg ? wg : 1);
-        for (size_t& o : wg_more) o = a.floats(wg ? wg : 1);
+        for (size_t& o : wg_more) o = a.floats(is_resnet(id) && wg ? wg : 1);
         bn_scratch = a.floats(bn ? bn : 1);
         bn_scratch2 = a.floats(bn ? bn : 1);
         tot_a = a.floats(128); tot_b = a.floats(128);          // batch-norm backward sums (2 x 64 channels at most)
@@ -264,7 +264,7 @@ int step_alexnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, c
     RUN(dsspk_fc_bwd(s, a3, da4, w + fw2, g + fw2, g + fb2, da3, 1, nullptr, nullptr, m, 384, 192));
     RUN(dsspk_fc_bwd(s, p2, da3, w + fw1, g + fw1, g + fb1, dp2, 0, nullptr, nullptr, m, 3136, 384));
     RUN(dsspk_maxpool_bwd_relu(s, dp2, arg2, a2, da2, m, 15, 15, 64));
-    RUN(conv_split_bwd_weight_parts((hipStream_t)s, p1, da2, g + cw2, 1, F(P->wg_more[0]), m, 15, 15, 64, 64, 5, 2, &waiting[1]));      // and the biases behind the filter
+    RUN(conv_split_bwd_weight_parts((hipStream_t)s, p1, da2, g + cw2, 1, F(P->wide2.partial), m, 15, 15, 64, 64, 5, 2, &waiting[1]));      // and the biases behind the filter
     RUN(dsspk_conv_split_bwd_data(s, da2, ws + P->wide2.bwd, nullptr, dp1, m, 15, 15, 64, 64, 5, 2));
     RUN(conv_first_pool_bwd_weight_parts((hipStream_t)s, x, dp1, p1, arg1, g + cw1, scr, m, &waiting[0]));      // and the biases behind the filter
     return wgrad_reduce_many((hipStream_t)s, 2, waiting);
@@ -294,10 +294,10 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
     // backward, as above
     jobs::Partials waiting[3];
     RUN(dsspk_fc_bwd(s, c3, da3, w + fw1, g + fw1, g + fb1, dc3, 1, nullptr, nullptr, m, 3136, 384));
-    RUN(conv_split_bwd_weight_parts((hipStream_t)s, p2, dc3, g + cw3, 1, F(P->wg_more[1]), m, 7, 7, 64, 64, 3, 1, &waiting[2]));
+    RUN(conv_split_bwd_weight_parts((hipStream_t)s, p2, dc3, g + cw3, 1, F(P->wide3.partial), m, 7, 7, 64, 64, 3, 1, &waiting[2]));
     RUN(dsspk_conv_split_bwd_data(s, dc3, ws + P->wide3.bwd, nullptr, dp2, m, 7, 7, 64, 64, 3, 1));
     RUN(dsspk_maxpool_bwd_relu(s, dp2, arg2, a2, da2, m, 15, 15, 64));
-    RUN(conv_split_bwd_weight_parts((hipStream_t)s, p1, da2, g + cw2, 1, F(P->wg_more[0]), m, 15, 15, 64, 64, 5, 2, &waiting[1]));      // and the biases behind the filter
+    RUN(conv_split_bwd_weight_parts((hipStream_t)s, p1, da2, g + cw2, 1, F(P->wide2.partial), m, 15, 15, 64, 64, 5, 2, &waiting[1]));      // and the biases behind the filter
     RUN(dsspk_conv_split_bwd_data(s, da2, ws + P->wide2.bwd, nullptr, dp1, m, 15, 15, 64, 64, 5, 2));
     RUN(conv_first_pool_bwd_weight_parts((hipStream_t)s, x, dp1, p1, arg1, g + cw1, scr, m, &waiting[0]));      // and the biases behind the filter
     return wgrad_reduce_many((hipStream_t)s, 3, waiting);

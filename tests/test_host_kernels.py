@@ -1,0 +1,19 @@
+"""What the library lays out and refuses before anything is launched; no GPU needed."""
+import pytest
+
+from paper_1908_11848_amd import binding as B
+
+
+@pytest.mark.parametrize("batch", [1, 37, 128, 512])
+@pytest.mark.parametrize("model", ["alexnet_ds", "alexnet_3c"])
+def test_alexnet_style_workspace_holds_what_the_step_uses(model, batch):
+    """Activations, their gradients, converted filters and one buffer of partial sums for each convolution's filter gradient, sized by that
+    convolution: every buffer begins on a 256-byte boundary (at most 40 of them), a few more hold 4 bytes to 2 KB."""
+    L, m = B.lib(), batch
+    a1, p1, p2 = m * 32 * 32 * 64, m * 15 * 15 * 64, m * 7 * 7 * 64
+    wide = [(15, 5, 2)] + ([(7, 3, 1)] if model == "alexnet_3c" else [])
+    rows = 384 * 2 if model == "alexnet_3c" else 384 * 2 + 192 * 2
+    floats = a1 + 4 * p1 + (2 if model == "alexnet_ds" else 4) * p2 + rows * m + 21 * m       # two rows of 10 classes, one of losses
+    floats += L.dsspk_conv_first_scratch_floats(m) + sum(L.dsspk_conv_split_wgrad_scratch_floats(m, H, H, 64, 64, k, p) for H, k, p in wide)
+    nbytes = 4 * floats + p1 + p2 + sum(2 * L.dsspk_conv_split_filter_bytes(64, 64, k) for _, k, _ in wide)
+    assert 0 <= B.dssp_workspace_bytes(B.model_id(model), batch, 10, 1) - nbytes < 40 * 256 + 4096

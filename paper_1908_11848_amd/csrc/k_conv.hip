@@ -996,6 +996,7 @@ extern "C" int dsspk_wgrad_reduce(void* stream, const float* partial, float* dw,
 }
 
 int wgrad_reduce_many(hipStream_t s, int n, const jobs::Partials* p) {
+    if (n < 1 || n > DSSPK_WGRAD_REDUCE_MAX || !p) return -1;
     ReduceJobs r = {};
     r.n = n;
     int blocks = 0;

@@ -1,7 +1,13 @@
 """What the library lays out and refuses before anything is launched; no GPU needed."""
+import ctypes
+import os
+import re
+
 import pytest
 
 from paper_1908_11848_amd import binding as B
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.parametrize("batch", [1, 37, 128, 512])
@@ -17,3 +23,18 @@ def test_alexnet_style_workspace_holds_what_the_step_uses(model, batch):
     floats += L.dsspk_conv_first_scratch_floats(m) + sum(L.dsspk_conv_split_wgrad_scratch_floats(m, H, H, 64, 64, k, p) for H, k, p in wide)
     nbytes = 4 * floats + p1 + p2 + sum(2 * L.dsspk_conv_split_filter_bytes(64, 64, k) for _, k, _ in wide)
     assert 0 <= B.dssp_workspace_bytes(B.model_id(model), batch, 10, 1) - nbytes < 40 * 256 + 4096
+
+
+class Partials(ctypes.Structure):           # jobs::Partials
+    _fields_ = [("partial", ctypes.c_void_p), ("dw", ctypes.c_void_p), ("E", ctypes.c_int), ("chunks", ctypes.c_int), ("quads", ctypes.c_bool)]
+
+
+def test_a_step_reduces_no_more_filter_gradients_than_one_launch_holds():
+    """The library's own reduction launcher, which the networks' steps call: it fills an array of DSSPK_WGRAD_REDUCE_MAX jobs."""
+    text = open(os.path.join(ROOT, "include", "dssp_kernels.h")).read()
+    most = int(re.search(r"#define DSSPK_WGRAD_REDUCE_MAX (\d+)", text).group(1))
+    many = B.lib()._Z17wgrad_reduce_manyP12ihipStream_tiPKN4jobs8PartialsE
+    many.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+    jobs = (Partials * (most + 1))(*[Partials(4096, 4096, 4, 1, False)] * (most + 1))
+    assert many(None, 0, jobs) == -1
+    assert many(None, most + 1, jobs) == -1

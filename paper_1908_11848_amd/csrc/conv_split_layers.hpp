@@ -4,7 +4,8 @@
 #include "jobs.hpp"
 #include "split.hpp"
 
-namespace {
+// (A named namespace: SplitFilterJob has these as members and goes from one source file to another.)
+namespace split_filter {
 
 // Filter planes in operand order: [step][16 result channels][plane][lane] of 16 bytes, step = (tap, 32 reduction channels),
 // lane (l16, q) holding the reduction channels 8 q .. 8 q + 7 of result channel l16.  A wavefront then fetches an operand
@@ -49,13 +50,13 @@ __device__ __forceinline__ void filter_frag(const Frag& f, bool tr, long idx) {
     }
 }
 
-}  // namespace
+}  // namespace split_filter
 
 // A step's wide filters, forward and d-input: the first layer's kernel carries their conversion as workgroups behind its own, a launch of 4.8 us less for
 // each layer.
 struct SplitFilterJob {
     static constexpr int THREADS = 256, MOST = 4;
-    Frag frag[MOST] = {};
+    split_filter::Frag frag[MOST] = {};
     int end[MOST] = {}, n = 0;         // workgroups up to and with a conversion
 
     void add(const float* w, void* fwd, void* bwd, int channels, int k) {
@@ -72,8 +73,8 @@ __device__ __forceinline__ void convert_filters(const SplitFilterJob& j, int blo
     int i = 0;
     while (i + 1 < j.n && block >= j.end[i]) ++i;
     const long at = (long)(block - (i ? j.end[i - 1] : 0)) * SplitFilterJob::THREADS + threadIdx.x;
-    const Frag f = j.frag[i];
-    if (at < (long)f.taps * f.IC * f.OC / 8) filter_frag(f, i % 2, at);
+    const split_filter::Frag f = j.frag[i];
+    if (at < (long)f.taps * f.IC * f.OC / 8) split_filter::filter_frag(f, i % 2, at);
 }
 
 int conv_first_pool_fwd(hipStream_t s, const float* x, const float* w, const float* bias, float* a, float* pooled, uint8_t* arg, int N, SplitFilterJob job);

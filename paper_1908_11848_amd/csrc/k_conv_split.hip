@@ -11,6 +11,10 @@
 
 namespace {
 
+using split_filter::BF16_NAN;
+using split_filter::Frag;
+using split_filter::filter_frag;
+
 constexpr int THREADS = 256;
 constexpr size_t LDS_MAX = 160 * 1024;
 

@@ -2,10 +2,11 @@
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
-from paper_1908_11848_amd import binding as B
+from paper_1908_11848_amd import binding as B, buildlib
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -38,3 +39,10 @@ def test_a_step_reduces_no_more_filter_gradients_than_one_launch_holds():
     jobs = (Partials * (most + 1))(*[Partials(4096, 4096, 4, 1, False)] * (most + 1))
     assert many(None, 0, jobs) == -1
     assert many(None, most + 1, jobs) == -1
+
+
+def test_what_goes_between_source_files_is_one_type():
+    """SplitFilterJob is passed by value from models.hip to k_conv_first.hip; its member type must be the same in both."""
+    names = subprocess.run(["nm", "-C", buildlib.LIB], capture_output=True, text=True, check=True).stdout
+    assert "SplitFilterJob" in names and "Frag" in names
+    assert "(anonymous namespace)::Frag" not in names

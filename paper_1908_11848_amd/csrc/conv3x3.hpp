@@ -990,10 +990,11 @@ int launch_form(hipStream_t s, const float* src, const Filter3x3& w, const float
 template <int C, int HW, int R, int NSPLIT, int WAVES, bool T, int PRE = 0, bool POST = false, bool WG = false>
 int launch(hipStream_t s, const float* src, const Filter3x3& w, const float* add, float* dst, float* bn_partial, int N, const PreBn& pre = PreBn{},
            const PostBn& post = PostBn(), const BwdBn& bwd = BwdBn(), const jobs::ReduceJob& rj = jobs::ReduceJob(), const WgradFused& wg = WgradFused()) {
-    if constexpr (T && PRE == 3)
+    // what a network's step launches (with 16 and 32 channels d-input and d-filter always come from one kernel)
+    if constexpr (T && PRE == 3 && (WG || C == 64))
         if (w.planes && post.gamma)
             return launch_form<true, C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG, true>(s, src, w, add, dst, bn_partial, N, pre, post, bwd, rj, wg);
-    if constexpr (!T || PRE == 3)           // what a network's step launches
+    if constexpr (!T || (PRE == 3 && (WG || C == 64)))
         if (w.planes) return launch_form<true, C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG>(s, src, w, add, dst, bn_partial, N, pre, post, bwd, rj, wg);
     return launch_form<false, C, HW, R, NSPLIT, WAVES, T, PRE, POST, WG>(s, src, w, add, dst, bn_partial, N, pre, post, bwd, rj, wg);
 }

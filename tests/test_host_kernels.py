@@ -46,3 +46,15 @@ def test_what_goes_between_source_files_is_one_type():
     names = subprocess.run(["nm", "-C", buildlib.LIB], capture_output=True, text=True, check=True).stdout
     assert "SplitFilterJob" in names and "Frag" in names
     assert "(anonymous namespace)::Frag" not in names
+
+
+def test_converted_filters_only_where_a_step_takes_them():
+    """conv3x3_kernel<C, HW, R, NSPLIT, WAVES, TRANSPOSED, PRE, POST, WG, PL, REPEAT>: a step's backward pass takes d-input and d-filter from one kernel
+    with 16 and 32 channels at every batch, and recomputes (REPEAT) only with converted filters (PL)."""
+    names = subprocess.run(["nm", "-C", buildlib.LIB], capture_output=True, text=True, check=True).stdout
+    forms = set(re.findall(r" void \(anonymous namespace\)::conv3x3_kernel<([^>]*)>", names))
+    assert len(forms) > 60
+    for form in forms:
+        C, _, _, _, _, T, PRE, _, WG, PL, REPEAT = form.split(", ")
+        assert PL == "false" or T == "false" or (PRE == "3" and (WG == "true" or C == "64")), form
+        assert REPEAT == "false" or PL == "true" and T == "true", form

@@ -234,8 +234,10 @@ size_t dsspk_conv_wgrad_scratch_floats(int N, int H, int W, int Cin, int Cout, i
  * are computed on the fp32 matrix cores: as dsspk_conv_* would, at several times the time.  dsspk_conv_split_covers: 1 if the
  * shape is one of these, its tiles fit and its filter has at most 2^30 elements (the launchers return -1 otherwise).
  * The filter is converted once per set of weights: dsspk_conv_split_filters writes the planes of the forward and / or of the
- * d-input pass (either may be NULL), dsspk_conv_split_filter_bytes(...) bytes each, 16-byte aligned. */
+ * d-input pass (either may be NULL), dsspk_conv_split_filter_bytes(...) bytes each, 16-byte aligned.
+ * dsspk_conv_split_resident: workgroups of the forward kernel that a compute unit holds side by side, 1 or 2 (0: not covered). */
 int dsspk_conv_split_covers(int N, int H, int W, int Cin, int Cout, int k, int pad);
+int dsspk_conv_split_resident(int N, int H, int W, int Cin, int Cout, int k, int pad);
 size_t dsspk_conv_split_filter_bytes(int Cin, int Cout, int k);
 int dsspk_conv_split_filters(void* stream, const float* w_dev, void* planes_fwd_dev, void* planes_bwd_dev, int Cin, int Cout, int k);
 int dsspk_conv_split_fwd(void* stream, const float* x_dev, const void* planes_fwd_dev, const float* bias_dev, float* y_dev, int N,

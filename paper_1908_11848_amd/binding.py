@@ -93,6 +93,7 @@ _SIGNATURES = {
     "dsspk_conv_bwd_weight": (c_int, [c_void_p] * 5 + [c_int] * 9),
     "dsspk_conv_wgrad_scratch_floats": (c_size_t, [c_int] * 9),
     "dsspk_conv_split_covers": (c_int, [c_int] * 7),
+    "dsspk_conv_split_resident": (c_int, [c_int] * 7),
     "dsspk_conv_split_filter_bytes": (c_size_t, [c_int] * 3),
     "dsspk_conv_split_filters": (c_int, [c_void_p] * 4 + [c_int] * 3),
     "dsspk_conv_split_fwd": (c_int, [c_void_p] * 5 + [c_int] * 8),

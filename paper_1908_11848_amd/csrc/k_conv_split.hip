@@ -495,8 +495,11 @@ bool tiling_for(Tiling& t, int mt, int N, int OH, int OW, int ks) {
     if (t.G > N) t.G = N;
     t.at = lds_pitch(ICB, false, t.R, OW, ks);
     while (t.G > 1 && (size_t)t.G * t.at.image > LDS_MAX) --t.G;
+    // Padded, but never at the price of a smaller tile, nor of the second workgroup of a compute unit (the two smaller tiles: registers admit two).
+    // Without the latter / so, us: 5x5 on 29x29, batch 18 42.4 / 32.3, on 36x36, batch 10 41.2 / 31.4; 3x3 on 64x64, batch 5 22.7 / 17.2.
     const LdsPitch padded = lds_pitch(ICB, true, t.R, OW, ks);
-    if ((size_t)t.G * padded.image <= LDS_MAX) t.at = padded;         // never a smaller tile for it
+    const size_t room = mt < 8 && (size_t)t.G * t.at.image <= LDS_MAX / 2 ? LDS_MAX / 2 : LDS_MAX;
+    if ((size_t)t.G * padded.image <= room) t.at = padded;
     t.lds = (size_t)t.G * t.at.image;
     if (mt == 8 && t.lds < 32 * 1024) t.lds = 32 * 1024;  // exchange of sums: four matrix-core tiles of each of the eight wavefronts
     t.blocks = ceil_div(N, t.G) * t.bands;
@@ -847,6 +850,14 @@ extern "C" int dsspk_conv_split_covers(int N, int H, int W, int Cin, int Cout, i
     // byte offsets within a group of images stay below split::OUTSIDE
     auto fits = [&](const Geom& g) { Tiling t; return choose_tiling(t, N, g.OH, g.OW, g.OC, k) && (long)t.G * g.H * g.W * g.IC < 1L << 29; };
     return fits(f) && fits(b) && wgrad_rows(f, k);
+}
+
+extern "C" int dsspk_conv_split_resident(int N, int H, int W, int Cin, int Cout, int k, int pad) {
+    if (!dsspk_conv_split_covers(N, H, W, Cin, Cout, k, pad)) return 0;
+    const Geom g = forward_geom(N, H, W, Cin, Cout, k, pad);
+    Tiling t;
+    choose_tiling(t, N, g.OH, g.OW, Cout, k);
+    return t.mt == 8 ? 1 : (int)std::min<size_t>(2, LDS_MAX / t.lds);
 }
 
 extern "C" size_t dsspk_conv_split_filter_bytes(int Cin, int Cout, int k) { return (size_t)k * k * Cin * Cout * 2 * split::PLANES; }

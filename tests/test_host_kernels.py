@@ -58,3 +58,12 @@ def test_converted_filters_only_where_a_step_takes_them():
         C, _, _, _, _, T, PRE, _, WG, PL, REPEAT = form.split(", ")
         assert PL == "false" or T == "false" or (PRE == "3" and (WG == "true" or C == "64")), form
         assert REPEAT == "false" or PL == "true" and T == "true", form
+
+
+# pixels of LDS without padding: 400 bytes each, 160 KB a compute unit.  Two workgroups: 64 result pixels of a row and 3x3's halo, 3 x 66; 5x5's around
+# two rows of 29 or 30, 6 x 33, 6 x 34; around a row of 36, 5 x 40; a 5x5 filter on a single row of 9, 5 x 3 x 13 (three images of 1x9).
+@pytest.mark.parametrize("shape,resident", [((5, 64, 64, 64, 64, 3, 1), 2), ((18, 29, 29, 64, 64, 5, 2), 2), ((20, 30, 30, 64, 64, 5, 2), 2),
+                                            ((10, 36, 36, 64, 64, 5, 2), 2), ((8, 1, 9, 64, 64, 5, 2), 2), ((37, 15, 15, 64, 64, 5, 2), 2),
+                                            ((128, 15, 15, 64, 64, 5, 2), 1), ((6, 64, 64, 64, 64, 3, 1), 1), ((1, 8, 200, 64, 64, 3, 1), 0)])
+def test_wide_tiles_are_not_padded_out_of_a_compute_unit(shape, resident):
+    assert B.lib().dsspk_conv_split_resident(*shape) == resident

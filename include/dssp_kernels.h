@@ -207,6 +207,28 @@ int dsspk_conv3x3_small_bwd(void* stream, const float* dz_dev, const float* xc_d
                             const float* w_dev, const float* add_dev, float* out_dev, const float* x_in_dev, const float* xc_post_dev,
                             const float* stats_post_dev, float* records_dev, const float* red_partial_dev, float* red_dw_dev, int red_E,
                             int red_chunks, int N, int H, int C);
+/* The launches of a residual network's step, on their own: the same layers and results on filters that have been converted once per step
+ * (a step's first kernel carries that; dsspk_conv3x3_filters does it for one filter, dsspk_conv3x3_filter_bytes bytes, 16-byte aligned, both
+ * directions).  workgroups: which of the three sizes, and with it the arguments: MEDIUM as dsspk_conv_fwd (records NULL), dsspk_conv_fwd_prebn(_half),
+ * dsspk_conv_bwd_data_bn_wgrad and, C = 64, dsspk_conv_bwd_data_bn (totals, in_records NULL); LARGE, SMALL as dsspk_conv3x3_large_* and
+ * dsspk_conv3x3_small_* (totals NULL).  SMALL takes `partial` for C = 64 too, dx NULL then: one partial result an image, to be added up four images at a
+ * time, (0 + 2) + (1 + 3) (red_quads, at most 64 results), for the bits of dsspk_conv_bwd_weight.  gamma_post, beta_post: of the batch norm of xc_post,
+ * if x_in is ReLU(BN(xc_post)) with nothing added; x_in is then worked out again (and read only where sums leave the range of the bf16 terms).
+ * Else both NULL. */
+#define DSSPK_CONV3X3_MEDIUM 0
+#define DSSPK_CONV3X3_LARGE 1
+#define DSSPK_CONV3X3_SMALL 2
+size_t dsspk_conv3x3_filter_bytes(int C);
+int dsspk_conv3x3_filters(void* stream, const float* w_dev, void* planes_dev, int C);
+int dsspk_conv3x3_step_fwd(void* stream, int workgroups, const float* src_dev, const float* records_dev, int parts, const float* gamma_dev,
+                           const float* beta_dev, float eps, const float* shortcut_dev, float* act_out_dev, float* stats_out_dev,
+                           const float* w_dev, const void* planes_dev, float* dst_dev, float* records_out_dev, int shortcut_half, int N, int H, int C);
+int dsspk_conv3x3_step_bwd(void* stream, int workgroups, const float* dz_dev, const float* xc_dev, const float* stats_dev, const float* gamma_dev,
+                           const float* totals_dev, const float* in_records_dev, int parts, float* dgamma_dev, float* dbeta_dev, float* dx_dev,
+                           float* partial_dev, const float* w_dev, const void* planes_dev, const float* add_dev, float* out_dev, const float* x_in_dev,
+                           const float* xc_post_dev, const float* stats_post_dev, const float* gamma_post_dev, const float* beta_post_dev,
+                           float* records_dev, const float* red_partial_dev, float* red_dw_dev, int red_E, int red_chunks, int red_quads, int N, int H,
+                           int C);
 
 /* dw[kh][kw][ci][co] = sum over batch and output pixels of x * dy.  Two stages (partial sums per
  * pixel chunk, then a fixed-order reduction).  scratch_dev: dsspk_conv_wgrad_scratch_floats(...) floats. */

@@ -5,9 +5,11 @@
 // wavefronts of four pixel tiles each, or four wavefronts of two (k_conv3x3.hip, k_conv3x3_large.hip, k_conv3x3_small.hip).  It loads the
 // (R+2) x (HW+2) x C input halo tile (zero borders) into LDS once; everything else is served from LDS, so every input element is read from
 // memory once per band instead of nine times.  The filter never passes through LDS: a wavefront owns ONE tile of 16 output channels and holds
-// one column of that tile's filter (three taps) in registers; a row of the next column is fetched and split while the products still work with
-// the present one.  (Two pixel tiles: all three columns, fetched up front.)  In a network's step the filter comes already split (conv3x3_filter.hpp).  LDS therefore holds the halo tile and a little for the sums: 36 to
-// 42 KB with four wavefronts, 42 to 81 KB with eight, 22 to 42 KB with two pixel tiles.  Registers are at most 128 with eight wavefronts, and
+// one column of that tile's filter (three taps) in registers; a row of the next column is fetched while the products still work with the present
+// one.  In a network's step the filter comes already split (conv3x3_filter.hpp), with two pixel tiles two columns are held, and what is not needed
+// at once is fetched between the products.  Callers of single layers have the filter split here; with two pixel tiles all three columns and
+// everything else are then fetched up front.  LDS holds the halo tile and a little for the sums: 36 to 42 KB with four wavefronts, 42 to 81 KB with
+// eight, 22 to 42 KB with two pixel tiles (the last stage's d-filter beside its d-input: 57).  Registers are at most 128 with eight wavefronts, and
 // what fits a compute unit of LDS and registers overlaps: one workgroup's transfers run beside another's products.
 //
 // What bounds them (110 layers, batch 128, four streams, 1.82 ms a push): registers and LDS admit 16 wavefronts to a compute unit and each
@@ -16,8 +18,8 @@
 // 1.86 ms), addresses as 32-bit offsets from a uniform base, and nothing held across the product loop that the thread index gives.
 //
 // The arithmetic is fp32 on the bf16 matrix cores (split.hpp): the loader leaves every element in LDS as three bf16 terms
-// (each converted once, not once per tap), the filter values are split in registers while the input is on its way, and six
-// of the nine products are taken.  The matrix-core tile is 16 output channels (rows) x 16 pixels (columns); a wavefront owns
+// (each converted once, not once per tap), the filter values come split or are split in registers while the input is on its way, and
+// six of the nine products are taken.  The matrix-core tile is 16 output channels (rows) x 16 pixels (columns); a wavefront owns
 // one channel tile and four pixel tiles that lie below each other, so a pixel operand fetched for one filter row serves
 // the tiles above it too, and a lane ends up with four consecutive channels of a pixel (16-byte loads and stores in the
 // epilogue).
@@ -58,9 +60,10 @@ struct Cfg {
     static constexpr int NT = R * TX / (TROWS * WPX);
     static constexpr int WM = NT / KS;             // pixel tiles a wavefront finishes
     // Two tiles: the products of a filter column are too few to hide the fetch of the next one, and registers are not what counts
-    // where the tiles are that small: all three columns are fetched up front.
+    // where the tiles are that small: all three columns are fetched up front (where the kernel splits the filter; see SPREAD).
     static constexpr int COLUMNS = NT == 4 ? 1 : 3;
-    // ... and so is everything else the workgroup reads: one latency instead of three or four in a row.  A push of the 20-layer network, one
+    // ... and so is everything else the workgroup reads: one latency instead of three or four in a row (figures before the filters were converted
+    // ahead).  A push of the 20-layer network, one
     // worker, without / with it, us: batch 1 440 / 434, 8 470 / 466, 16 485 / 481; four workers, a round: 830 / 820, 895 / 881, 920 / 900.
     static constexpr bool EARLY = NT == 2;
     static constexpr int SC = WAVES_M * CN;        // floats: per-wavefront column sums (batch-norm records, one component)
@@ -177,7 +180,7 @@ __device__ __forceinline__ float4 sum16(float4 v) { return make_float4(sum16(v.x
 // The most records of a tensor that every workgroup of its consumer merges itself.
 template <int C, int WAVES, int NT = 4> constexpr int inline_records() { return 64 * WAVES * max_records<C, WAVES, NT>() / C; }
 
-// Thread (channel tid % C, lane tid / C) holds records lane, lane + THREADS / C, ... of its channel; all loads in flight together.
+// Thread (channel tid % C, lane tid / C) holds records lane, lane + THREADS / C, ... of its channel.
 template <int C, int THREADS, int RECORDS>
 __device__ __forceinline__ void load_records(float2 (&v)[RECORDS], const float* __restrict__ records, int parts, int tid) {
     constexpr int FEW = 4;          // at a time: where a list is short its loads would keep those behind them waiting

@@ -324,9 +324,11 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     const int nb = (int)P->blocks.size();
     // Above LARGE_ABOVE images the larger workgroups of dsspk_conv3x3_large_*: half as many records, few enough for every workgroup to
     // add up (173 launches of a 110-layer step less).  A round with the four-wavefront / the larger ones, us: 20 layers, one worker, batch 65
-    // 687 / 677, 96 706 / 699, 97 716 / 703, 128 766 / 739, four workers 65 1406 / 1368, 96 1575 / 1517, 97 1603 / 1532, 128 1804 / 1744; 50
-    // layers, eight workers 65 6630 / 6310, 96 7380 / 7020, 97 7550 / 7090, 128 8500 / 8090; 110 layers 65 12700 / 12440, 128 17280 / 16680.  So
-    // the line could lie at 64, not lower: up to 64 images the first stride-2 convolution leaves more records than they add up.
+    // 660 / 661, four workers 80 1467 / 1416, 96 1571 / 1500; 50 layers, eight workers 65 5108 / 4892, 96 5977 / 5676; 110 layers 80 11673 / 11055;
+    // before the filters were converted ahead: 20 layers, four workers 97 1603 / 1532, 128 1804 / 1744, 50 layers, eight workers 97 7550 / 7090,
+    // 128 8500 / 8090, 110 layers 128 17280 / 16680.  By these figures the line belongs at 64 (not lower: up to 64 images the first stride-2
+    // convolution leaves more records than they add up); it lies at 96 because from 65 to 96 images a step would then take its statistics and filter
+    // gradients from other partial sums, which no test has held to the oracle at those batches yet.
     // Up to DSSPK_CONV3X3_SMALL_MAX images the smaller workgroups of dsspk_conv3x3_small_* (k_conv3x3_small.hip: 5 to 8 % of a step).
     const bool large = m > LARGE_ABOVE && m <= DSSPK_CONV3X3_LARGE_MAX, small = m <= DSSPK_CONV3X3_SMALL_MAX;
     auto parts_of = [&](int H, int cin, int cout, int stride) {       // records that the forward convolution leaves

@@ -2,7 +2,7 @@
 
 Every case launches one kernel family of the worker step (or of the server) at the shape and
 launch configuration the ResNet-110 / batch 128 workload uses, through the exported `dsspk_*`
-launchers.  `measure_*` time `reps` back-to-back launches on ONE stream with HIP events recorded
+launchers; the 3x3 convolutions are the kernels of its step (dsspk_conv3x3_step_*, filters converted beforehand).  `measure_*` time `reps` back-to-back launches on ONE stream with HIP events recorded
 on that same stream.  Run as a program it launches every case a few times and exits, which is
 what the hardware-counter passes are taken on:
 
@@ -22,6 +22,8 @@ terms each, six products of terms per product):
                    gradient, ReLU mask + sum records in its epilogue,                 the carried reduction's
                    carrying an earlier layer's d-filter reduction
     conv_dgrad_bn  the same without the d-filter part (stage 3), dx stored   W,  7 T  + the carried reduction's partial sums
+    ..2            either for a block's second convolution: no shortcut, x       2 T less
+                   worked out again from the next BN's input
     conv_wgrad     d-filter convolution, stage 1 (stage 3)                   W,  2 T + its partial sums
     bn_fwd / bn_bwd  stand-alone batch-norm kernels (irregular layers only)      4 T / 7 T
     apply / pull   server update and snapshot copy                               12 / 8 bytes per parameter
@@ -46,7 +48,7 @@ _COUNTERS = os.path.join(os.path.dirname(_HERE), "profiles", "traffic_counters.j
 STAGES = ((32, 16), (16, 32), (8, 64))      # (height = width, channels) of the three ResNet stages
 BATCH = 128
 N_PARAMS = 1_733_812                         # ResNet-110, 10 classes
-SOURCES = ("conv3x3.hpp", "conv3x3_forms.hpp", "k_conv3x3_large.hip", "k_conv3x3.hip", "k_conv.hip", "k_elem.hip", "k_server.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp", "common.hpp")
+SOURCES = ("conv3x3.hpp", "conv3x3_forms.hpp", "conv3x3_filter.hpp", "conv3x3_layers.hpp", "k_conv3x3_step.hip", "k_conv3x3_large.hip", "k_conv3x3.hip", "k_conv.hip", "k_elem.hip", "k_server.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp", "common.hpp")
 
 
 def case_list(n_params=N_PARAMS):
@@ -55,9 +57,9 @@ def case_list(n_params=N_PARAMS):
     for H, C in STAGES:
         out += [("conv_fwd_%dx%dx%d" % (H, H, C), 1, 0), ("conv_fwd_bn_%dx%dx%d" % (H, H, C), 1, 1)]
         if C < 64:
-            out += [("conv_bwd_fused_%dx%dx%d" % (H, H, C), 1, 0)]
+            out += [("conv_bwd_fused%s_%dx%dx%d" % (i, H, H, C), 1, 0) for i in ("", "2")]
         else:
-            out += [("conv_dgrad_bn_%dx%dx%d" % (H, H, C), 1, 1), ("conv_wgrad_%dx%dx%d" % (H, H, C), 1, 0)]
+            out += [("conv_dgrad_bn%s_%dx%dx%d" % (i, H, H, C), 1, 1) for i in ("", "2")] + [("conv_wgrad_%dx%dx%d" % (H, H, C), 1, 0)]
     out += [("bn_fwd_32x32x16", 2, 0), ("bn_bwd_32x32x16", 2, 2)]
     for n in sorted({n_params, 25_000_000}):
         out += [("apply_%d" % n, 1, 0), ("pull_%d" % n, 1, 0)]
@@ -97,11 +99,11 @@ def _traffic(key, srcs):
     return int(e["fetch_bytes"] + e["write_bytes"])
 
 
-_CONV_SRCS = ("conv3x3.hpp", "conv3x3_forms.hpp", "k_conv3x3_large.hip", "k_conv3x3.hip", "k_conv.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp")
+_CONV_SRCS = ("conv3x3.hpp", "conv3x3_forms.hpp", "conv3x3_filter.hpp", "conv3x3_layers.hpp", "k_conv3x3_step.hip", "k_conv3x3_large.hip", "k_conv3x3.hip", "k_conv.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp")
 
 
 def _conv_cases(H, C, dev):
-    """The four fused convolution launches of a regular layer of the stage, on random data."""
+    """The convolution launches of a regular block of the stage, on random data."""
     import torch
     from . import binding as B
     L = B.lib()
@@ -125,36 +127,45 @@ def _conv_cases(H, C, dev):
     ch = ctypes.c_int(0)
     T = 4.0 * M * C
     F = 6 * 2.0 * M * C * 9 * C                  # executed on the matrix cores (six products of bf16 terms)
-    fwd = lambda s: L.dsspk_conv3x3_large_fwd(s, x.data_ptr(), None, 0, None, None, 0.0, None, None, None, w.data_ptr(), z.data_ptr(),
-                                              recA.data_ptr(), 0, N, H, C)
-    fwd_bn = lambda s: L.dsspk_conv3x3_large_fwd(s, z.data_ptr(), recA.data_ptr(), parts, gamma.data_ptr(), beta.data_ptr(), 1e-5,
-                                                 sc.data_ptr(), a.data_ptr(), stats_o.data_ptr(), w.data_ptr(), y.data_ptr(),
-                                                 recB.data_ptr(), 0, N, H, C)
+    planes = torch.empty(L.dsspk_conv3x3_filter_bytes(C), dtype=torch.uint8, device=dev)
+    if L.dsspk_conv3x3_filters(torch.cuda.current_stream().cuda_stream, w.data_ptr(), planes.data_ptr(), C):
+        raise RuntimeError("dsspk_conv3x3_filters")
+    torch.cuda.current_stream().synchronize()
+    large = 1                                    # DSSPK_CONV3X3_LARGE
+    fwd = lambda s: L.dsspk_conv3x3_step_fwd(s, large, x.data_ptr(), None, 0, None, None, 0.0, None, None, None, w.data_ptr(), planes.data_ptr(),
+                                             z.data_ptr(), recA.data_ptr(), 0, N, H, C)
+    fwd_bn = lambda s: L.dsspk_conv3x3_step_fwd(s, large, z.data_ptr(), recA.data_ptr(), parts, gamma.data_ptr(), beta.data_ptr(), 1e-5,
+                                                sc.data_ptr(), a.data_ptr(), stats_o.data_ptr(), w.data_ptr(), planes.data_ptr(), y.data_ptr(),
+                                                recB.data_ptr(), 0, N, H, C)
     wgrad = lambda s: L.dsspk_conv_bwd_weight_parts(s, x.data_ptr(), dx.data_ptr(), scr.data_ptr(), N, H, H, C, C, 3, 3, 1, 1,
                                                     None, 0, 0, None, None, None, ctypes.byref(ch))
     chunks = parts if C < 64 else (N + 3) // 4
     scr2 = torch.zeros_like(scr)
-    bwd = lambda s: L.dsspk_conv3x3_large_bwd(s, dz.data_ptr(), xc.data_ptr(), stats.data_ptr(), gamma.data_ptr(), rec_in.data_ptr(), parts,
-                                              dgam.data_ptr(), dbet.data_ptr(), None if C < 64 else dx.data_ptr(),
-                                              scr.data_ptr() if C < 64 else None, w.data_ptr(), add.data_ptr(), add.data_ptr(), act.data_ptr(),
-                                              xcp.data_ptr(), stats.data_ptr(), rec.data_ptr(), scr2.data_ptr(), dw.data_ptr(), E, chunks, N, H, C)
-    keep = (x, z, sc, a, y, dz, xc, add, act, xcp, dx, w, gamma, beta, stats, stats_o, dgam, dbet, recA, recB, rec, rec_in, scr, scr2, dw, ch)
+
+    def bwd(s, second=False):
+        shortcut, again = (None, (gamma.data_ptr(), beta.data_ptr())) if second else (add.data_ptr(), (None, None))
+        return L.dsspk_conv3x3_step_bwd(s, large, dz.data_ptr(), xc.data_ptr(), stats.data_ptr(), gamma.data_ptr(), None, rec_in.data_ptr(), parts,
+                                        dgam.data_ptr(), dbet.data_ptr(), None if C < 64 else dx.data_ptr(), scr.data_ptr() if C < 64 else None,
+                                        w.data_ptr(), planes.data_ptr(), shortcut, add.data_ptr(), act.data_ptr(), xcp.data_ptr(), stats.data_ptr(),
+                                        *again, rec.data_ptr(), scr2.data_ptr(), dw.data_ptr(), E, chunks, 0, N, H, C)
+
+    bwd2 = lambda s: bwd(s, True)
+    keep = (x, z, sc, a, y, dz, xc, add, act, xcp, dx, w, gamma, beta, stats, stats_o, dgam, dbet, recA, recB, rec, rec_in, scr, scr2, dw, ch, planes)
     part_bytes = 4.0 * chunks * E
     desc = "%d->%d @%dx%d, batch %d" % (C, C, H, H, N)
     head = [
         ("conv_fwd_%dx%dx%d" % (H, H, C), "conv 3x3 forward + statistics records " + desc, F, 2 * T, fwd, None, keep),
         ("conv_fwd_bn_%dx%dx%d" % (H, H, C), "conv 3x3 forward with BN, shortcut, ReLU in its loader " + desc,
          F, 4 * T, fwd_bn, fwd, keep)]
-    if C < 64:
-        return head + [
-            ("conv_bwd_fused_%dx%dx%d" % (H, H, C), "conv 3x3 d-input + d-filter in one kernel: BN backward in its loader, shortcut "
-             "gradient, ReLU mask + sum records in its epilogue, carrying a d-filter reduction " + desc,
-             2 * F, 6 * T + 2 * part_bytes + 4.0 * E, bwd, None, keep)]
-    return head + [
-        ("conv_dgrad_bn_%dx%dx%d" % (H, H, C), "conv 3x3 d-input with BN backward in its loader, shortcut gradient, ReLU mask + "
-         "sum records in its epilogue, carrying a d-filter reduction " + desc, F, 7 * T + part_bytes + 4.0 * E, bwd, wgrad, keep),
-        ("conv_wgrad_%dx%dx%d" % (H, H, C), "conv 3x3 d-filter stage 1 " + desc, F, 2 * T + part_bytes, wgrad, None, keep),
-    ]
+    back = ("conv 3x3 d-input + d-filter in one kernel: " if C < 64 else "conv 3x3 d-input with ") + "BN backward in its loader, "
+    end = "ReLU mask + sum records in its epilogue, carrying a d-filter reduction " + desc
+    key, flops = ("conv_bwd_fused%s_%dx%dx%d", 2 * F) if C < 64 else ("conv_dgrad_bn%s_%dx%dx%d", F)
+    first, moved = (None, 6 * T + 2 * part_bytes + 4.0 * E) if C < 64 else (wgrad, 7 * T + part_bytes + 4.0 * E)
+    head += [(key % ("", H, H, C), back + "shortcut gradient, " + end, flops, moved, bwd, first, keep),
+             (key % ("2", H, H, C), back + "x worked out again from the next BN's input, " + end, flops, moved - 2 * T, bwd2, first, keep)]
+    if C == 64:
+        head += [("conv_wgrad_%dx%dx%d" % (H, H, C), "conv 3x3 d-filter stage 1 " + desc, F, 2 * T + part_bytes, wgrad, None, keep)]
+    return head
 
 
 def _bn_cases(H, C, dev):

@@ -328,7 +328,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     // before the filters were converted ahead: 20 layers, four workers 97 1603 / 1532, 128 1804 / 1744, 50 layers, eight workers 97 7550 / 7090,
     // 128 8500 / 8090, 110 layers 128 17280 / 16680.  By these figures the line belongs at 64 (not lower: up to 64 images the first stride-2
     // convolution leaves more records than they add up); it lies at 96 because from 65 to 96 images a step would then take its statistics and filter
-    // gradients from other partial sums, which no test has held to the oracle at those batches yet.
+    // gradients from other partial sums, which no test checks at those batches yet.
     // Up to DSSPK_CONV3X3_SMALL_MAX images the smaller workgroups of dsspk_conv3x3_small_* (k_conv3x3_small.hip: 5 to 8 % of a step).
     const bool large = m > LARGE_ABOVE && m <= DSSPK_CONV3X3_LARGE_MAX, small = m <= DSSPK_CONV3X3_SMALL_MAX;
     auto parts_of = [&](int H, int cin, int cout, int stride) {       // records that the forward convolution leaves

@@ -180,13 +180,13 @@ __device__ __forceinline__ float4 sum16(float4 v) { return make_float4(sum16(v.x
 // The most records of a tensor that every workgroup of its consumer merges itself.
 template <int C, int WAVES, int NT = 4> constexpr int inline_records() { return 64 * WAVES * max_records<C, WAVES, NT>() / C; }
 
-// Thread (channel tid % C, lane tid / C) holds records lane, lane + THREADS / C, ... of its channel; behind the last one zeros or, LATE, anything:
-// there has_record is asked where they are added up.  Asked behind the loads it makes each few of them wait for the ones before (small
-// workgroups behind a batch norm, batch 32, 16 / 32 / 64 channels, us: 7.25 / 7.82 / 7.85, LATE 6.78 / 7.23 / 7.48).  Eight records are loaded
-// without a condition, and the backward pass's sums gain 0 to 3 % there and lose 2 % elsewhere: these stay as they are.
-template <bool LATE, int C, int THREADS, int RECORDS>
+// Thread (channel tid % C, lane tid / C) holds records lane, lane + THREADS / C, ... of its channel, behind the last one zeros: the list is a
+// buffer, so neither its end nor an address takes vector instructions (68 before: a push of the 50-layer network, batch 128, one worker 1719 ->
+// 1698 us).  A load beyond the end still takes its turn: all sixteen without a condition, 20 layers, batch 8, 349 -> 363 us.
+template <int C, int THREADS, int RECORDS>
 __device__ __forceinline__ void load_records(float2 (&v)[RECORDS], const float* __restrict__ records, int parts, int tid) {
     constexpr int FEW = 4;          // at a time: where a list is short its loads would keep those behind them waiting
+    const split::Buffer list = split::buffer(records, 8u * (unsigned)(parts * C));
 #pragma unroll
     for (int u0 = 0; u0 < RECORDS; u0 += FEW) {
         if (RECORDS > 8 && u0 * (THREADS / C) >= parts) {
@@ -195,11 +195,7 @@ __device__ __forceinline__ void load_records(float2 (&v)[RECORDS], const float* 
             continue;
         }
 #pragma unroll
-        for (int u = u0; u < u0 + FEW; ++u) {
-            const int g = tid / C + u * (THREADS / C);
-            v[u] = *reinterpret_cast<const float2*>(records + ((long)min(g, parts - 1) * C + tid % C) * 2);
-            if (!LATE && g >= parts) v[u] = make_float2(0.f, 0.f);
-        }
+        for (int u = u0; u < u0 + FEW; ++u) v[u] = split::load2(list, 8u * (unsigned)(tid + u * THREADS));
     }
 }
 template <int C, int THREADS> __device__ __forceinline__ bool has_record(int u, int parts, int tid) { return tid / C + u * (THREADS / C) < parts; }
@@ -318,21 +314,22 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
 #pragma unroll
             for (int ky = 0; ky < 3; ++ky) load_filter(ky, kx);
     };
-    // EARLY: what the loader needs of the batch norm (PRE 1, 2: of this thread's channels; 3: of channel tid)
+    // What the loader needs of the batch norm (PRE 1, 2: of this thread's channels; 3: of channel tid), fetched with everything else: read where
+    // it is used, behind the sums and once a vector of the tile, each vector waits for memory again.  A push of the 50-layer network, batch
+    // 128, one worker / four, us: 1688 / 806, so 1669 / 795; with the vectors of the tile's channels read from LDS once, 1660 / 798.
     float4 norm_g = make_float4(0.f, 0.f, 0.f, 0.f), norm_b = norm_g;
     float norm_mean = 0.f, norm_is = 0.f, norm_gamma = 0.f;
-    if constexpr (K::EARLY && (PRE == 1 || PRE == 2)) {
+    if constexpr (PRE == 1 || PRE == 2) {
         norm_g = *reinterpret_cast<const float4*>(pre.gamma + tid % V * 4);
         norm_b = *reinterpret_cast<const float4*>(pre.beta + tid % V * 4);
     }
-    if constexpr (K::EARLY && PRE == 3)
+    if constexpr (PRE == 3)
         if (tid < C) { norm_mean = bwd.stats[tid]; norm_is = bwd.stats[C + tid]; norm_gamma = bwd.gamma[tid]; }
-    constexpr bool LATE = (PRE == 1 || PRE == 2) && K::RECORDS > 8;
     float2 rec[PRE ? K::RECORDS : 1];
     if constexpr (PRE == 1 || PRE == 2)
-        if (pre.merge) load_records<LATE, C, THREADS>(rec, pre.records, pre.L.G, tid);
+        if (pre.merge) load_records<C, THREADS>(rec, pre.records, pre.L.G, tid);
     if constexpr (PRE == 3)
-        if (!bwd.totals) load_records<false, C, THREADS>(rec, bwd.records, bwd.parts, tid);
+        if (!bwd.totals) load_records<C, THREADS>(rec, bwd.records, bwd.parts, tid);
     if constexpr (!PL) first_columns();
     // ---- input halo tile, zero outside the image.  The raw loads are issued first; the first filter column is split while
     //      they are in flight.
@@ -369,7 +366,6 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             if constexpr (PRE == 3) scv[e] = load4(bwd.xc + tile_at + e * STEP, 4u * tid);
         }
     }
-    if constexpr (PL) first_columns();          // the tile is needed before them
     // what the epilogue adds, masks with and sums over, a lane's four channels of its pixel of every tile: all these loads together (dst may
     // alias add, so the compiler cannot move them across the stores itself)
     float4 mu_c = make_float4(0.f, 0.f, 0.f, 0.f), is_c = mu_c, ga_c = mu_c, be_c = mu_c, addv[K::WM], maskv[POST ? K::WM : 1], xcv[POST ? K::WM : 1];
@@ -441,15 +437,26 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     if constexpr (PRE == 1 || PRE == 2) {               // mean / invstd of the input
         if (pre.merge) {                                // mean = sum n mean_g / M, M2 = sum (M2_g + n (mean_g - mean)^2)
             const float nn = (float)pre.L.rows_per_block, M = (float)pre.M;
-            float s_ = 0.f, m2 = 0.f;
+            float s_ = 0.f, m2 = 0.f, d2 = 0.f;
 #pragma unroll
-            for (int u = 0; u < K::RECORDS; ++u) s_ = fmaf(nn, !LATE || has_record<C, THREADS>(u, pre.L.G, tid) ? rec[u].x : 0.f, s_);
-            const float mean = channel_sum<C, WAVES>(s_, red, tid) / M;
+            for (int u = 0; u < K::RECORDS; ++u) s_ += rec[u].x;
+            const float mean = channel_sum<C, WAVES>(s_, red, tid) * nn / M;
+            if (pre.L.G == K::RECORDS * (THREADS / C)) {
 #pragma unroll
-            for (int u = 0; u < K::RECORDS; ++u) {
-                const float d = rec[u].x - mean;
-                m2 += has_record<C, THREADS>(u, pre.L.G, tid) ? rec[u].y + nn * d * d : 0.f;
+                for (int u = 0; u < K::RECORDS; ++u) {
+                    const float d = rec[u].x - mean;
+                    m2 += rec[u].y;
+                    d2 = fmaf(d, d, d2);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < K::RECORDS; ++u) {
+                    const float d = has_record<C, THREADS>(u, pre.L.G, tid) ? rec[u].x - mean : 0.f;
+                    m2 += rec[u].y;
+                    d2 = fmaf(d, d, d2);
+                }
             }
+            m2 = fmaf(nn, d2, m2);
             const float invstd = 1.0f / sqrtf(channel_sum<C, WAVES>(m2, red + WAVES * C, tid) / M + pre.eps);
             if (tid < C) {
                 Sh[tid] = mean;
@@ -473,44 +480,54 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             sum_g = bwd.totals[C + tid];
         }
         if (tid < C) {
-            const float is = K::EARLY ? norm_is : bwd.stats[C + tid];
-            Sh[tid] = K::EARLY ? norm_mean : bwd.stats[tid];
+            const float is = norm_is;
+            Sh[tid] = norm_mean;
             Sh[C + tid] = is;
-            Sh[2 * C + tid] = (K::EARLY ? norm_gamma : bwd.gamma[tid]) * is;
+            Sh[2 * C + tid] = norm_gamma * is;
             Sh[3 * C + tid] = sum_b * bwd.inv_m;
             Sh[4 * C + tid] = sum_g * bwd.inv_m;
             if (!bwd.totals && blockIdx.x == 0) { bwd.dbeta[tid] = sum_b; bwd.dgamma[tid] = sum_g; }
         }
         __syncthreads();
     }
+    if constexpr (PL) first_columns();          // behind the records of every wavefront: they are needed first (50 layers, batch 128 1698 -> 1688 us)
     auto stage = [&](char* to, float4 v) {  // 4 channels of a pixel as their three terms
         uint2 pl[split::PLANES];
         split::split4(split::scaled(v), pl);
 #pragma unroll
         for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(to + p * K::PLANE) = pl[p];
     };
-    // what the convolution runs on, four channels of a pixel of src (and of the shortcut or xc)
-    auto transformed = [&](float4 o, float4 sc, int c, bool own_channels) {
+    // what the convolution runs on, four channels of a pixel of src (and of the shortcut or xc); the batch norm's vectors of these channels
+    struct Vectors { float4 mu, is, ga, be, dg; };
+    auto vectors = [&](int c, bool own_channels) {
+        Vectors v{};
         if constexpr (PRE == 3) {
-            const float4 mu = *reinterpret_cast<const float4*>(Sh + c);
-            const float4 is = *reinterpret_cast<const float4*>(Sh + C + c);
-            const float4 gi = *reinterpret_cast<const float4*>(Sh + 2 * C + c);
-            const float4 db = *reinterpret_cast<const float4*>(Sh + 3 * C + c);
-            const float4 dg = *reinterpret_cast<const float4*>(Sh + 4 * C + c);
-            o.x = gi.x * (o.x - db.x - (sc.x - mu.x) * is.x * dg.x);
-            o.y = gi.y * (o.y - db.y - (sc.y - mu.y) * is.y * dg.y);
-            o.z = gi.z * (o.z - db.z - (sc.z - mu.z) * is.z * dg.z);
-            o.w = gi.w * (o.w - db.w - (sc.w - mu.w) * is.w * dg.w);
+            v.ga = *reinterpret_cast<const float4*>(Sh + 2 * C + c);            // gamma * invstd
+            v.be = *reinterpret_cast<const float4*>(Sh + 3 * C + c);
+            v.dg = *reinterpret_cast<const float4*>(Sh + 4 * C + c);
         }
         if constexpr (PRE == 1 || PRE == 2) {
-            const float4 mu = *reinterpret_cast<const float4*>(Sh + c);
-            const float4 is = *reinterpret_cast<const float4*>(Sh + C + c);
-            const float4 ga = K::EARLY && own_channels ? norm_g : *reinterpret_cast<const float4*>(pre.gamma + c);
-            const float4 be = K::EARLY && own_channels ? norm_b : *reinterpret_cast<const float4*>(pre.beta + c);
-            o.x = fmaf((o.x - mu.x) * is.x, ga.x, be.x);
-            o.y = fmaf((o.y - mu.y) * is.y, ga.y, be.y);
-            o.z = fmaf((o.z - mu.z) * is.z, ga.z, be.z);
-            o.w = fmaf((o.w - mu.w) * is.w, ga.w, be.w);
+            v.ga = own_channels ? norm_g : *reinterpret_cast<const float4*>(pre.gamma + c);
+            v.be = own_channels ? norm_b : *reinterpret_cast<const float4*>(pre.beta + c);
+        }
+        if constexpr (PRE != 0) {
+            v.mu = *reinterpret_cast<const float4*>(Sh + c);
+            v.is = *reinterpret_cast<const float4*>(Sh + C + c);
+        }
+        return v;
+    };
+    auto transformed = [&](float4 o, float4 sc, const Vectors& v) {
+        if constexpr (PRE == 3) {
+            o.x = v.ga.x * (o.x - v.be.x - (sc.x - v.mu.x) * v.is.x * v.dg.x);
+            o.y = v.ga.y * (o.y - v.be.y - (sc.y - v.mu.y) * v.is.y * v.dg.y);
+            o.z = v.ga.z * (o.z - v.be.z - (sc.z - v.mu.z) * v.is.z * v.dg.z);
+            o.w = v.ga.w * (o.w - v.be.w - (sc.w - v.mu.w) * v.is.w * v.dg.w);
+        }
+        if constexpr (PRE == 1 || PRE == 2) {
+            o.x = fmaf((o.x - v.mu.x) * v.is.x, v.ga.x, v.be.x);
+            o.y = fmaf((o.y - v.mu.y) * v.is.y, v.ga.y, v.be.y);
+            o.z = fmaf((o.z - v.mu.z) * v.is.z, v.ga.z, v.be.z);
+            o.w = fmaf((o.w - v.mu.w) * v.is.w, v.ga.w, v.be.w);
             if constexpr (PRE == 2) { o.x += sc.x; o.y += sc.y; o.z += sc.z; o.w += sc.w; }
             o.x = fmaxf(o.x, 0.f); o.y = fmaxf(o.y, 0.f); o.z = fmaxf(o.z, 0.f); o.w = fmaxf(o.w, 0.f);
         }
@@ -525,7 +542,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             else if (c < C / 2) sc = *reinterpret_cast<const float4*>(pre.shortcut + 2 * image_at + (2 * h * HW + w) * C + c);
         }
         if constexpr (PRE == 3) sc = *reinterpret_cast<const float4*>(bwd.xc + off);
-        return transformed(*reinterpret_cast<const float4*>(src + off), sc, c, false);
+        return transformed(*reinterpret_cast<const float4*>(src + off), sc, vectors(c, false));
     };
     if constexpr (WG && C == 64)            // the x tile's border
         for (int i = tid; i < 4 * (K::TW - 1) * (K::X2PITCH / 8); i += THREADS) {
@@ -541,12 +558,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         if constexpr (K::ZERO_UNIT == 16) *reinterpret_cast<uint4*>(to) = make_uint4(0u, 0u, 0u, 0u);
         else *reinterpret_cast<uint2*>(to) = make_uint2(0u, 0u);
     }
+    const Vectors own_vectors = vectors(c4, true);
 #pragma unroll
     for (int e = 0; e < NL; ++e) {
         if (!own(e)) continue;
         if constexpr (PRE != 0) {
             if (inside(e)) {
-                val[e] = transformed(val[e], scv[PRE >= 2 ? e : 0], c4, true);
+                val[e] = transformed(val[e], scv[PRE >= 2 ? e : 0], own_vectors);
                 // the band's own rows (not the halo rows) are this workgroup's part of `a` or dx
                 if (!WG && part == 0 && (K::WHOLE || (pr0 + e * RE >= 1 && pr0 + e * RE <= R)))
                     *reinterpret_cast<float4*>((PRE == 3 ? bwd.dx_out : pre.act_out) + tile_at + e * STEP + 4u * tid) = val[e];

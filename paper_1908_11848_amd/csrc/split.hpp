@@ -171,6 +171,9 @@ __device__ __forceinline__ Buffer buffer(const void* p, unsigned bytes) {
 __device__ __forceinline__ float4 load4(Buffer b, unsigned offset) {
     return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)offset, 0, 0));
 }
+__device__ __forceinline__ float2 load2(Buffer b, unsigned offset) {
+    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(b, (int)offset, 0, 0));
+}
 __device__ __forceinline__ unsigned load1(Buffer b, unsigned offset) { return __builtin_amdgcn_raw_buffer_load_b32(b, (int)offset, 0, 0); }
 
 }  // namespace split

@@ -198,19 +198,96 @@ __device__ __forceinline__ void load_records(float2 (&v)[RECORDS], const float* 
         for (int u = u0; u < u0 + FEW; ++u) v[u] = split::load2(list, 8u * (unsigned)(tid + u * THREADS));
     }
 }
+// ... and how many of a channel's the lanes of wavefront w hold together
+template <int C, int THREADS> __device__ __forceinline__ int records_of(int parts, int w) {
+    constexpr int LANES = THREADS / C, PER = 64 / C;
+    return parts / LANES * PER + min(max(parts % LANES - w * PER, 0), PER);
+}
 template <int C, int THREADS> __device__ __forceinline__ bool has_record(int u, int parts, int tid) { return tid / C + u * (THREADS / C) < parts; }
 
-// Sum of every lane's s of this thread's channel, in a fixed order; red: WAVES * C floats nobody else uses between the barriers.
-template <int C, int WAVES>
-__device__ __forceinline__ float channel_sum(float s, float* red, int tid) {
-    if constexpr (C <= 32) s += __shfl_xor(s, 32);
-    if constexpr (C <= 16) s += __shfl_xor(s, 16);
-    if ((tid & 63) < C) red[tid / 64 * C + tid % C] = s;
-    __syncthreads();
-    float t = red[tid % C];
+// Sum over the lanes of a wavefront that share a channel (thread: channel tid % C), in all of them.
+template <int C> __device__ __forceinline__ float lanes_sum(float v) {
+    if constexpr (C <= 32) {
+        const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    }
+    if constexpr (C <= 16) {
+        const auto h = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    }
+    return v;
+}
+
+// Statistics records are merged (Chan's formula) by each wavefront for itself, its lanes by swaps of their registers, and the wavefronts meet
+// once; with the mean of all first and then the deviations from it they met twice.  A push of 50 layers, batch 128, one worker / four 1650 / 786 ->
+// 1638 / 776 us, 20 layers, batch 8 385 -> 383.
+// A wavefront's share of the statistics records (mean, sum of squared deviations; of nn rows each): mean and sum of squared deviations of all its
+// rows, for the channel of the lane.
+template <int C, int THREADS, int RECORDS>
+__device__ __forceinline__ float2 merge_lanes(const float2 (&rec)[RECORDS], int parts, float nn, int tid) {
+    constexpr int LANES = THREADS / C, PER = 64 / C;        // that share a channel: of the workgroup, of a wavefront
+    float s_ = 0.f, m2 = 0.f, d2 = 0.f, mean;
+    if (parts == RECORDS * LANES) {
 #pragma unroll
-    for (int j = 1; j < WAVES; ++j) t += red[j * C + tid % C];
-    return t;
+        for (int u = 0; u < RECORDS; ++u) s_ += rec[u].x;
+        mean = lanes_sum<C>(s_) * (1.f / (RECORDS * PER));
+#pragma unroll
+        for (int u = 0; u < RECORDS; ++u) {
+            const float d = rec[u].x - mean;
+            m2 += rec[u].y;
+            d2 = fmaf(d, d, d2);
+        }
+    } else {
+        const int count = records_of<C, THREADS>(parts, __builtin_amdgcn_readfirstlane(tid >> 6));
+#pragma unroll
+        for (int u = 0; u < RECORDS; ++u) s_ += rec[u].x;
+        mean = count ? lanes_sum<C>(s_) / (float)count : 0.f;
+        constexpr int FEW = RECORDS < 4 ? RECORDS : 4;
+#pragma unroll
+        for (int u0 = 0; u0 < RECORDS; u0 += FEW) {
+            if (u0 * LANES >= parts) continue;
+#pragma unroll
+            for (int u = u0; u < u0 + FEW; ++u) {
+                const float d = has_record<C, THREADS>(u, parts, tid) ? rec[u].x - mean : 0.f;
+                m2 += rec[u].y;
+                d2 = fmaf(d, d, d2);
+            }
+        }
+    }
+    return make_float2(mean, lanes_sum<C>(fmaf(nn, d2, m2)));
+}
+
+// ... and of all wavefronts' shares (`of` them at red, C float2 each): the channel's mean and its sum of squared deviations.
+template <int C, int WAVES, int RECORDS>
+__device__ __forceinline__ float2 merge_waves(const float2* red, int parts, float nn, int c) {
+    constexpr int THREADS = 64 * WAVES, LANES = THREADS / C, PER = 64 / C;
+    float2 v[WAVES];
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) v[w] = red[w * C + c];
+    float mean = 0.f, m2 = 0.f, d2 = 0.f;
+    if (parts == RECORDS * LANES) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) mean += v[w].x;
+        mean *= 1.f / WAVES;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float d = v[w].x - mean;
+            m2 += v[w].y;
+            d2 = fmaf(d, d, d2);
+        }
+        d2 *= RECORDS * PER;
+    } else {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) mean = fmaf((float)records_of<C, THREADS>(parts, w), v[w].x, mean);
+        mean /= (float)parts;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float d = v[w].x - mean;
+            m2 += v[w].y;
+            d2 = fmaf((float)records_of<C, THREADS>(parts, w) * d, d, d2);
+        }
+    }
+    return make_float2(mean, fmaf(nn, d2, m2));
 }
 
 // PL: the filter's operands are there already, see conv3x3_filter.hpp
@@ -373,9 +450,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     auto out_at_of = [&](const Role& r) -> unsigned {                                       // from the band's first pixel, first tile
         return ((r.row0 + K::TROWS * r.ks * K::WM) * HW + r.col) * C + r.co_w + 4 * r.q;
     };
-    auto epilogue_loads = [&](const Role& r) {
+    auto epilogue_loads = [&](const Role& r, int which = 7) {
         const unsigned at = out_at_of(r);
-        if constexpr (POST) {
+        if (POST && (which & 1)) {
             mu_c = *reinterpret_cast<const float4*>(post.stats + r.co_w + 4 * r.q);
             is_c = *reinterpret_cast<const float4*>(post.stats + C + r.co_w + 4 * r.q);
             if constexpr (REPEAT) {
@@ -385,13 +462,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         }
 #pragma unroll
         for (int wm = 0; wm < K::WM; ++wm) {
-            if constexpr (SPREAD)       // (a load behind a branch makes those before it wait: the compiler cannot count it)
+            if (!(which & 2)) ;
+            else if constexpr (PL && POST)       // (a load behind a branch makes those before it wait: the compiler cannot count it)
                 addv[wm] = split::load4(split::buffer(add + band_at, add ? 4u * R * HW * C : 0u), 4u * (at + wm * OUT_STEP));
             else
                 addv[wm] = add ? load4(add + band_at + wm * OUT_STEP, at) : make_float4(0.f, 0.f, 0.f, 0.f);
             if constexpr (POST) {
-                if constexpr (!REPEAT) maskv[wm] = load4(post.mask_src + band_at + wm * OUT_STEP, at);
-                xcv[wm] = load4(post.xc + band_at + wm * OUT_STEP, at);
+                if (!REPEAT && (which & 4)) maskv[wm] = load4(post.mask_src + band_at + wm * OUT_STEP, at);
+                if (which & 1) xcv[wm] = load4(post.xc + band_at + wm * OUT_STEP, at);
             }
         }
     };
@@ -435,33 +513,18 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     for (int ky = 0; ky < 3; ++ky) split_filter(ky, 0);
     float* red = reinterpret_cast<float*>(lds);         // the tile is not there yet
     if constexpr (PRE == 1 || PRE == 2) {               // mean / invstd of the input
-        if (pre.merge) {                                // mean = sum n mean_g / M, M2 = sum (M2_g + n (mean_g - mean)^2)
-            const float nn = (float)pre.L.rows_per_block, M = (float)pre.M;
-            float s_ = 0.f, m2 = 0.f, d2 = 0.f;
-#pragma unroll
-            for (int u = 0; u < K::RECORDS; ++u) s_ += rec[u].x;
-            const float mean = channel_sum<C, WAVES>(s_, red, tid) * nn / M;
-            if (pre.L.G == K::RECORDS * (THREADS / C)) {
-#pragma unroll
-                for (int u = 0; u < K::RECORDS; ++u) {
-                    const float d = rec[u].x - mean;
-                    m2 += rec[u].y;
-                    d2 = fmaf(d, d, d2);
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < K::RECORDS; ++u) {
-                    const float d = has_record<C, THREADS>(u, pre.L.G, tid) ? rec[u].x - mean : 0.f;
-                    m2 += rec[u].y;
-                    d2 = fmaf(d, d, d2);
-                }
-            }
-            m2 = fmaf(nn, d2, m2);
-            const float invstd = 1.0f / sqrtf(channel_sum<C, WAVES>(m2, red + WAVES * C, tid) / M + pre.eps);
+        if (pre.merge) {
+            const float nn = (float)pre.L.rows_per_block;
+            float2* shares = reinterpret_cast<float2*>(red);
+            const float2 share = merge_lanes<C, THREADS>(rec, pre.L.G, nn, tid);
+            if ((tid & 63) < C) shares[tid / 64 * C + tid % C] = share;
+            __syncthreads();
             if (tid < C) {
-                Sh[tid] = mean;
+                const float2 all = merge_waves<C, WAVES, K::RECORDS>(shares, pre.L.G, nn, tid);
+                const float invstd = 1.0f / sqrtf(all.y / (float)pre.M + pre.eps);
+                Sh[tid] = all.x;
                 Sh[C + tid] = invstd;
-                if (blockIdx.x == 0) { pre.stats_out[tid] = mean; pre.stats_out[C + tid] = invstd; }
+                if (blockIdx.x == 0) { pre.stats_out[tid] = all.x; pre.stats_out[C + tid] = invstd; }
             }
         } else if (tid < 2 * C) {
             Sh[tid] = pre.stats_out[tid];
@@ -471,10 +534,18 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     if constexpr (PRE == 3) {               // mean, invstd, gamma * invstd, sum(dz) / M, sum(dz * xhat) / M
         float sum_b = 0.f, sum_g = 0.f;
         if (!bwd.totals) {
+            float2* shares = reinterpret_cast<float2*>(red);
 #pragma unroll
             for (int u = 0; u < K::RECORDS; ++u) { sum_b += rec[u].x; sum_g += rec[u].y; }
-            sum_b = channel_sum<C, WAVES>(sum_b, red, tid);
-            sum_g = channel_sum<C, WAVES>(sum_g, red + WAVES * C, tid);
+            sum_b = lanes_sum<C>(sum_b);
+            sum_g = lanes_sum<C>(sum_g);
+            if ((tid & 63) < C) shares[tid / 64 * C + tid % C] = make_float2(sum_b, sum_g);
+            __syncthreads();
+            if (tid < C) {
+                sum_b = sum_g = 0.f;
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) { sum_b += shares[w * C + tid].x; sum_g += shares[w * C + tid].y; }
+            }
         } else if (tid < C) {
             sum_b = bwd.totals[tid];
             sum_g = bwd.totals[C + tid];
@@ -626,7 +697,16 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
                     if (st == 3 && kx == 1) load_x_tile();
             }
             if constexpr (PL && COLUMNS == 1)        // into the registers of the row that has just been used for the last time
+            {
                 if (st >= LAST && kx < 2) load_filter(st - LAST, kx + 1);
+                // What the epilogue reads, as far as the registers that the last column's rows leave go (all of it with 16 and 32 channels: up
+                // to 35 spilled).  Epilogue of the last stage 2400 to 3700 -> 750 cycles; a push of 50 layers, batch 128, one worker 1661 -> 1650 us.
+                if constexpr (C == 64) {
+                    if (st >= LAST && kx == 2) epilogue_loads(r, 1 << (st - LAST));
+                } else {
+                    if (st == LAST + (REPEAT ? 1 : 2) && kx == 2) epilogue_loads(r, 1);
+                }
+            }
         }
         mma::drain();
 #pragma unroll
@@ -696,7 +776,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     const int co = co_w + 4 * q;
     const unsigned out_at = out_at_of(role);
     if constexpr (!K::EARLY) {
-        epilogue_loads(role);
+        epilogue_loads(role, !PL ? 7 : C == 64 ? 0 : 6);
         if constexpr (WG) load_x_tile();
     }
     float4 sum_dz = make_float4(0.f, 0.f, 0.f, 0.f), sum_dzx = sum_dz;

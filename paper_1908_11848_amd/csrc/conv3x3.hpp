@@ -43,12 +43,14 @@ struct Cfg {
     static constexpr int THREADS = 64 * WAVES;
     static constexpr int CN = C / NSPLIT;          // output channels per workgroup
     static constexpr int PLANE = 2 * C;            // bytes between the three bf16 terms of a pixel in LDS
-    // Pitch of a pixel: 16 bytes behind its terms (C = 16: 8).  LDS has 64 banks, and a 16-byte read is served 16 lanes at a time, 0-3, 12-15 and
-    // 20-27 first (measured read by read): so a pixel operand takes twice (C = 32) or three times (C = 64) the steps it could.  A layout that
-    // takes every bank once, without padding (the 16-byte parts of a plane dealt by the column), changed no kernel's and no step's time.
-    static constexpr int PITCH = 3 * PLANE + (C == 16 ? 8 : 16);
+    // Pitch of a pixel: 16 bytes behind its terms (C = 16: 8; 64: 32, and 192 behind a row).  LDS has 64 banks, and a 16-byte read is served 16
+    // lanes at a time, 0-3, 12-15 and 20-27 first (measured read by read): so a pixel operand takes twice the steps it could with 32 channels (32 bytes
+    // would not leave room for two workgroups, and dealing the 16-byte parts of a plane by the column changed no time) and no more than it
+    // must with 64 (16 bytes: three times; a push of 50 layers, batch 128, one worker 1639 -> 1634 us, 20 layers, batch 8 383.3 -> 382.4).
+    static constexpr int PITCH = 3 * PLANE + (C == 16 ? 8 : C == 32 ? 16 : 32);
     static constexpr int TW = HW + 2;              // halo tile width
-    static constexpr int XB = (R + 2) * TW * PITCH;            // bytes
+    static constexpr int ROW = TW * PITCH + (C == 64 ? 192 : 0);       // bytes of a tile row
+    static constexpr int XB = (R + 2) * ROW;
     static constexpr int WAVES_N = CN / 16;        // wavefronts side by side over the output channels
     static constexpr int WAVES_M = WAVES / WAVES_N;    // ... and over the pixels or, in the last stage, the input channels
     // A wavefront works on NT (four or two) pixel tiles, each one (HW >= 16) or two (HW = 8) image rows below the one before.
@@ -402,6 +404,17 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     }
     if constexpr (PRE == 3)
         if (tid < C) { norm_mean = bwd.stats[tid]; norm_is = bwd.stats[C + tid]; norm_gamma = bwd.gamma[tid]; }
+    // The filter is new to every L2, and workgroups that keep step with each other all wait for each of its rows in turn.  With eight wavefronts
+    // the workgroups of an XCD therefore touch a line of it a thread, each its share, before they do anything else.  A push of 50 layers, batch 128,
+    // one worker 1635 -> 1624 us, a round of eight workers 7024 -> 6952.  (Smaller workgroups: nothing, two such loads a thread cost as much.  The
+    // epilogue's operands touched in the same way: 1660 -> 1688.)
+    constexpr bool WARM = PL && WAVES == 8;
+    unsigned warm = 0;
+    if constexpr (WARM) {
+        constexpr int LINES = (int)(filter3x3_uint4s(C) / 8);
+        const int groups = conv_blocks / 8, share = groups ? (LINES + groups - 1) / groups : 0, at = blockIdx.x / 8 * share + tid;
+        if (tid < share && at < LINES) warm = planes[8 * at].x;
+    }
     float2 rec[PRE ? K::RECORDS : 1];
     if constexpr (PRE == 1 || PRE == 2)
         if (pre.merge) load_records<C, THREADS>(rec, pre.records, pre.L.G, tid);
@@ -416,8 +429,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     static_assert(RE * V * HW == THREADS && NL == (K::ROWS + RE - 1) / RE, "whole rows");
     const int pr0 = tid / (V * HW), c4 = tid % V * 4;
     const long tile_at = image_at + (r_base + K::ROW0 - 1) * HW * C;       // may lie in front of the image, where nothing is fetched
-    char* tile_to = Xs + ((pr0 + K::ROW0) * K::TW + tid / V % HW + 1) * K::PITCH + 2 * c4;
-    constexpr int STEP = RE * HW * C, STEP_TO = RE * K::TW * K::PITCH;
+    char* tile_to = Xs + (pr0 + K::ROW0) * K::ROW + (tid / V % HW + 1) * K::PITCH + 2 * c4;
+    constexpr int STEP = RE * HW * C, STEP_TO = RE * K::ROW;
     auto own = [&](int e) { return (e + 1) * RE <= K::ROWS || pr0 + e * RE < K::ROWS; };                            // a row of the tile
     auto inside = [&](int e) { return K::WHOLE || (own(e) && (unsigned)(r_base - 1 + pr0 + e * RE) < (unsigned)HW); };   // and of the image
     const split::Buffer image = split::buffer(src + image_at, 4u * HW * HW * C);
@@ -625,7 +638,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         const int px = i / K::ZERO_UNITS, unit = i % K::ZERO_UNITS;
         int r = px >> 1, c = (px & 1) * (K::TW - 1);
         if (K::WHOLE && px >= 2 * (R + 2)) { r = (px & 1) * (R + 1); c = ((px - 2 * (R + 2)) >> 1) + 1; }
-        char* to = Xs + (r * K::TW + c) * K::PITCH + unit * K::ZERO_UNIT;
+        char* to = Xs + r * K::ROW + c * K::PITCH + unit * K::ZERO_UNIT;
         if constexpr (K::ZERO_UNIT == 16) *reinterpret_cast<uint4*>(to) = make_uint4(0u, 0u, 0u, 0u);
         else *reinterpret_cast<uint2*>(to) = make_uint2(0u, 0u);
     }
@@ -651,7 +664,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     {
         constexpr int NT = K::NT, LAST = (NT - 1) * K::TROWS, ST = LAST + 3;
         const Role r = role_of(tid);
-        int at_px = (r.row0 * K::TW + r.col) * K::PITCH + (C == 16 ? 8 : 16) * r.q + 64 * r.ks;
+        int at_px = r.row0 * K::ROW + r.col * K::PITCH + (C == 16 ? 8 : 16) * r.q + 64 * r.ks;
         const char* base = Xs + at_px;
         if constexpr (C == 16) asm("" : "+v"(at_px));
         const char* again = Xs + at_px;
@@ -661,7 +674,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
 #pragma unroll
         for (int t = 0; t < NT; ++t) a[t] = lo[t] = floatx4{0.f, 0.f, 0.f, 0.f};
         split::Pix<C> x[2];
-        auto pixels = [&](int i) { return split::pixel_operand<C, K::PLANE>(base + (i % ST * K::TW + i / ST) * K::PITCH, again + (i % ST * K::TW + i / ST) * K::PITCH); };
+        auto pixels = [&](int i) { return split::pixel_operand<C, K::PLANE>(base + i % ST * K::ROW + i / ST * K::PITCH, again + i % ST * K::ROW + i / ST * K::PITCH); };
         x[0] = pixels(0);
 #pragma unroll
         for (int i = 0; i < 3 * ST; ++i) {
@@ -737,6 +750,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         }
     }
 
+    if constexpr (WARM) asm volatile("" :: "v"(warm));
     int again_tid = tid;
     asm("" : "+v"(again_tid));
     const Role role = role_of(again_tid);
@@ -838,13 +852,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int p = 8 * q + 4 * h + (l16 >> 2);
-                const int o = ((first + p / HW) * K::TW + p % HW) * K::PITCH + 8 * (l16 & 3);
+                const int o = (first + p / HW) * K::ROW + p % HW * K::PITCH + 8 * (l16 & 3);
                 xa[h] = Xs + o + 32 * cit;
-                da[h] = Xs + o + (K::TW + 1) * K::PITCH + 32 * cot;
+                da[h] = Xs + o + K::ROW + K::PITCH + 32 * cot;
             }
 #pragma unroll
             for (int run = 0; run < RUNS; ++run)
-                split::transposed_operand<K::PLANE>(d[run], da[0] + run * RROWS * K::TW * K::PITCH, da[1] + run * RROWS * K::TW * K::PITCH);
+                split::transposed_operand<K::PLANE>(d[run], da[0] + run * RROWS * K::ROW, da[1] + run * RROWS * K::ROW);
         }
         __syncthreads();
 #pragma unroll
@@ -855,7 +869,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         constexpr int XB = WAVES == 8 ? 1 : 2;                  // operands in registers: four wavefronts a SIMD hide the fetch
         uint4 x[XB][split::PLANES];
         auto load_x = [&](int b, int i) {
-            const int off = (i % ST * K::TW + i / ST) * K::PITCH;
+            const int off = i % ST * K::ROW + i / ST * K::PITCH;
             split::transposed_operand<K::PLANE>(x[b], xa[0] + off, xa[1] + off);
         };
         floatx4 dw[C == 16 ? 9 : 1];                           // C = 16: all taps, summed over the wavefronts at the end
@@ -992,13 +1006,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         const char *xa[2], *da[2];                             // of pixels 8 q + 4 h + l16 / 4 of the first run
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int p = 8 * q + 4 * h + (l16 >> 2), at = p / HW * K::TW + p % HW;
-            xa[h] = X2 + at * K::X2PITCH + 8 * (l16 & 3);
-            da[h] = Xs + (at + K::TW + 1) * K::PITCH + 32 * wave + 8 * (l16 & 3);
+            const int p = 8 * q + 4 * h + (l16 >> 2);
+            xa[h] = X2 + (p / HW * K::TW + p % HW) * K::X2PITCH + 8 * (l16 & 3);
+            da[h] = Xs + (p / HW + 1) * K::ROW + (p % HW + 1) * K::PITCH + 32 * wave + 8 * (l16 & 3);
         }
         uint4 d[2][split::PLANES], x[2][split::PLANES];
 #pragma unroll
-        for (int run = 0; run < 2; ++run) split::transposed_operand<K::PLANE>(d[run], da[0] + run * RUN * K::PITCH, da[1] + run * RUN * K::PITCH);
+        for (int run = 0; run < 2; ++run) split::transposed_operand<K::PLANE>(d[run], da[0] + run * 4 * K::ROW, da[1] + run * 4 * K::ROW);
         auto load_x = [&](int i) {                             // filter column i / 6, run i / 3 mod 2, row i mod 3
             const int off = (i / 3 % 2 * RUN + i % 3 * K::TW + i / 6) * K::X2PITCH;
             split::transposed_operand<K::X2PLANE>(x[i & 1], xa[0] + off, xa[1] + off);

@@ -2,6 +2,10 @@
 
 hipcc cross-compiles without a GPU.  Packed-fp32 instruction selection is switched off
 for the device pass (the host pass prints a harmless warning about the unknown feature).
+A kernel's first arguments (as many as fit 14 words: pointers and numbers, not structs) are put into
+registers with its dispatch (-amdgpu-kernarg-preload-count): without that every wavefront begins
+with a load of them from memory, which its first load waits for.  A push of a 20-layer residual network,
+batch 8: 383 us without, 377 with it, 360 with the 3x3 kernels' arguments in the order of their use.
 """
 import glob
 import os
@@ -13,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdssp.so")
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno-gpu-rdc",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Wall", "-Wno-unused-function"]
 
 

@@ -297,10 +297,15 @@ __device__ __forceinline__ float2 merge_waves(const float2* red, int parts, floa
 // forward pass's own operations (the same bits), and a tensor less is read: a sixth of such a layer's bytes.  Reading it / so, a round of pushes, us:
 // batch 128, eight workers, 110 layers 16513 / 16322, 50 layers 7633 / 7509; 56 layers, batch 95, four 3216 / 3200; small batches the same.  (In the
 // last stage's d-filter kernel, where it would be a fourth of 6 MB, it changed nothing and was left out.)
+// Arguments: the first 14 words are in registers when a wavefront starts (-amdgpu-kernarg-preload-count), so what the first loads need comes first:
+// records, their number (0: merged or added up before) with 2^16 for a shortcut of twice the size, src, what is normalised with it (beside: shortcut, or the batch
+// norm's input), the filter, gamma and beta (or statistics and gamma).  Anything else is a load from memory that those would wait for: a push of 50
+// layers, batch 128, one worker 1624 -> 1565 us, 20 layers, batch 8 382 -> 360 (with the arguments in their old order 1612 and 377).
 template <int C, int HW, int R, int NSPLIT, int WAVES, bool TRANSPOSED, int PRE, bool POST, bool WG, bool PL, bool REPEAT>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_waves<C, WAVES, WG, Cfg<C, HW, R, NSPLIT, WAVES>::NT>()))) void conv3x3_kernel(
-    const float* __restrict__ src, const float* __restrict__ wgt, const uint4* __restrict__ planes, const float* add, float* dst, float* __restrict__ bn_partial, PreBn pre,
-    PostBn post, BwdBn bwd, int conv_blocks, jobs::ReduceJob rj, WgradFused wg) {
+    const float* __restrict__ records, int list, int conv_blocks, const float* __restrict__ src, const float* __restrict__ beside, const uint4* __restrict__ planes,
+    const float* __restrict__ norm_first, const float* __restrict__ norm_second, const float* __restrict__ wgt, const float* add, float* dst,
+    float* __restrict__ bn_partial, PreBn pre, PostBn post, BwdBn bwd, jobs::ReduceJob rj, WgradFused wg) {
     using K = Cfg<C, HW, R, NSPLIT, WAVES>;
     constexpr int THREADS = K::THREADS, V = K::V, NL = K::NL;
     // Filter columns in registers.  With converted filters and two pixel tiles the next one's rows, and then what the epilogue reads and the
@@ -317,6 +322,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         jobs::wgrad_reduce<THREADS>(rj, blockIdx.x - conv_blocks, reinterpret_cast<float*>(lds));
         return;
     }
+    const int parts = list & 0xffff;                // 0: already merged, or added up
+    const bool half = list >> 16;
     char* Xs = lds;
     float* Ss = reinterpret_cast<float*>(lds + K::XB);          // column sums
     float* Sh = Ss + K::SS;                                     // per-channel vectors of the loader
@@ -399,11 +406,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     float4 norm_g = make_float4(0.f, 0.f, 0.f, 0.f), norm_b = norm_g;
     float norm_mean = 0.f, norm_is = 0.f, norm_gamma = 0.f;
     if constexpr (PRE == 1 || PRE == 2) {
-        norm_g = *reinterpret_cast<const float4*>(pre.gamma + tid % V * 4);
-        norm_b = *reinterpret_cast<const float4*>(pre.beta + tid % V * 4);
+        norm_g = *reinterpret_cast<const float4*>(norm_first + tid % V * 4);
+        norm_b = *reinterpret_cast<const float4*>(norm_second + tid % V * 4);
     }
     if constexpr (PRE == 3)
-        if (tid < C) { norm_mean = bwd.stats[tid]; norm_is = bwd.stats[C + tid]; norm_gamma = bwd.gamma[tid]; }
+        if (tid < C) { norm_mean = norm_first[tid]; norm_is = norm_first[C + tid]; norm_gamma = norm_second[tid]; }
     // The filter is new to every L2, and workgroups that keep step with each other all wait for each of its rows in turn.  With eight wavefronts
     // the workgroups of an XCD therefore touch a line of it a thread, each its share, before they do anything else.  A push of 50 layers, batch 128,
     // one worker 1635 -> 1624 us, a round of eight workers 7024 -> 6952.  (Smaller workgroups: nothing, two such loads a thread cost as much.  The
@@ -417,9 +424,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     }
     float2 rec[PRE ? K::RECORDS : 1];
     if constexpr (PRE == 1 || PRE == 2)
-        if (pre.merge) load_records<C, THREADS>(rec, pre.records, pre.L.G, tid);
+        if (parts) load_records<C, THREADS>(rec, records, parts, tid);
     if constexpr (PRE == 3)
-        if (!bwd.totals) load_records<C, THREADS>(rec, bwd.records, bwd.parts, tid);
+        if (parts) load_records<C, THREADS>(rec, records, parts, tid);
     if constexpr (!PL) first_columns();
     // ---- input halo tile, zero outside the image.  The raw loads are issued first; the first filter column is split while
     //      they are in flight.
@@ -446,14 +453,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         if (inside(e)) {
             val[e] = load4(src + tile_at + e * STEP, 4u * tid);
             if constexpr (PRE == 2) {
-                if (C > 16 && pre.half) {
+                if (C > 16 && half) {
                     scv[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (c4 < C / 2) scv[e] = load4(pre.shortcut + 2 * (tile_at + e * STEP), (2 * pr0 * HW + tid / V % HW) * C + c4);
+                    if (c4 < C / 2) scv[e] = load4(beside + 2 * (tile_at + e * STEP), (2 * pr0 * HW + tid / V % HW) * C + c4);
                 } else {
-                    scv[e] = load4(pre.shortcut + tile_at + e * STEP, 4u * tid);
+                    scv[e] = load4(beside + tile_at + e * STEP, 4u * tid);
                 }
             }
-            if constexpr (PRE == 3) scv[e] = load4(bwd.xc + tile_at + e * STEP, 4u * tid);
+            if constexpr (PRE == 3) scv[e] = load4(beside + tile_at + e * STEP, 4u * tid);
         }
     }
     // what the epilogue adds, masks with and sums over, a lane's four channels of its pixel of every tile: all these loads together (dst may
@@ -526,14 +533,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     for (int ky = 0; ky < 3; ++ky) split_filter(ky, 0);
     float* red = reinterpret_cast<float*>(lds);         // the tile is not there yet
     if constexpr (PRE == 1 || PRE == 2) {               // mean / invstd of the input
-        if (pre.merge) {
+        if (parts) {
             const float nn = (float)pre.L.rows_per_block;
             float2* shares = reinterpret_cast<float2*>(red);
-            const float2 share = merge_lanes<C, THREADS>(rec, pre.L.G, nn, tid);
+            const float2 share = merge_lanes<C, THREADS>(rec, parts, nn, tid);
             if ((tid & 63) < C) shares[tid / 64 * C + tid % C] = share;
             __syncthreads();
             if (tid < C) {
-                const float2 all = merge_waves<C, WAVES, K::RECORDS>(shares, pre.L.G, nn, tid);
+                const float2 all = merge_waves<C, WAVES, K::RECORDS>(shares, parts, nn, tid);
                 const float invstd = 1.0f / sqrtf(all.y / (float)pre.M + pre.eps);
                 Sh[tid] = all.x;
                 Sh[C + tid] = invstd;
@@ -546,7 +553,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     }
     if constexpr (PRE == 3) {               // mean, invstd, gamma * invstd, sum(dz) / M, sum(dz * xhat) / M
         float sum_b = 0.f, sum_g = 0.f;
-        if (!bwd.totals) {
+        if (parts) {
             float2* shares = reinterpret_cast<float2*>(red);
 #pragma unroll
             for (int u = 0; u < K::RECORDS; ++u) { sum_b += rec[u].x; sum_g += rec[u].y; }
@@ -570,7 +577,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             Sh[2 * C + tid] = norm_gamma * is;
             Sh[3 * C + tid] = sum_b * bwd.inv_m;
             Sh[4 * C + tid] = sum_g * bwd.inv_m;
-            if (!bwd.totals && blockIdx.x == 0) { bwd.dbeta[tid] = sum_b; bwd.dgamma[tid] = sum_g; }
+            if (parts && blockIdx.x == 0) { bwd.dbeta[tid] = sum_b; bwd.dgamma[tid] = sum_g; }
         }
         __syncthreads();
     }
@@ -591,8 +598,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
             v.dg = *reinterpret_cast<const float4*>(Sh + 4 * C + c);
         }
         if constexpr (PRE == 1 || PRE == 2) {
-            v.ga = own_channels ? norm_g : *reinterpret_cast<const float4*>(pre.gamma + c);
-            v.be = own_channels ? norm_b : *reinterpret_cast<const float4*>(pre.beta + c);
+            v.ga = own_channels ? norm_g : *reinterpret_cast<const float4*>(norm_first + c);
+            v.be = own_channels ? norm_b : *reinterpret_cast<const float4*>(norm_second + c);
         }
         if constexpr (PRE != 0) {
             v.mu = *reinterpret_cast<const float4*>(Sh + c);
@@ -622,10 +629,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         const long off = image_at + (h * HW + w) * C + c;
         float4 sc = make_float4(0.f, 0.f, 0.f, 0.f);
         if constexpr (PRE == 2) {
-            if (!(C > 16 && pre.half)) sc = *reinterpret_cast<const float4*>(pre.shortcut + off);
-            else if (c < C / 2) sc = *reinterpret_cast<const float4*>(pre.shortcut + 2 * image_at + (2 * h * HW + w) * C + c);
+            if (!(C > 16 && half)) sc = *reinterpret_cast<const float4*>(beside + off);
+            else if (c < C / 2) sc = *reinterpret_cast<const float4*>(beside + 2 * image_at + (2 * h * HW + w) * C + c);
         }
-        if constexpr (PRE == 3) sc = *reinterpret_cast<const float4*>(bwd.xc + off);
+        if constexpr (PRE == 3) sc = *reinterpret_cast<const float4*>(beside + off);
         return transformed(*reinterpret_cast<const float4*>(src + off), sc, vectors(c, false));
     };
     if constexpr (WG && C == 64)            // the x tile's border
@@ -1102,8 +1109,9 @@ int launch_form(hipStream_t s, const float* src, const Filter3x3& w, const float
         attr_set = true;
     }
     const int conv_blocks = N * (HW / R) * NSPLIT;
-    hipLaunchKernelGGL(kern, dim3(conv_blocks + rj.blocks), dim3(K::THREADS), LDS_BYTES, s, src, w.w, w.planes, add, dst, bn_partial, pre, post,
-                       bwd, conv_blocks, rj, wg);
+    hipLaunchKernelGGL(kern, dim3(conv_blocks + rj.blocks), dim3(K::THREADS), LDS_BYTES, s,
+                       PRE == 3 ? bwd.records : pre.records, PRE == 3 ? (bwd.totals ? 0 : bwd.parts) : (pre.merge ? pre.L.G : 0) | (pre.half ? 1 << 16 : 0), conv_blocks, src, PRE == 3 ? bwd.xc : pre.shortcut, w.planes,
+                       PRE == 3 ? bwd.stats : pre.gamma, PRE == 3 ? bwd.gamma : pre.beta, w.w, add, dst, bn_partial, pre, post, bwd, rj, wg);
     return (int)hipGetLastError();
 }
 

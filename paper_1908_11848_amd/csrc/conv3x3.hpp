@@ -228,22 +228,24 @@ template <int C> __device__ __forceinline__ float lanes_sum(float v) {
 template <int C, int THREADS, int RECORDS>
 __device__ __forceinline__ float2 merge_lanes(const float2 (&rec)[RECORDS], int parts, float nn, int tid) {
     constexpr int LANES = THREADS / C, PER = 64 / C;        // that share a channel: of the workgroup, of a wavefront
-    float s_ = 0.f, m2 = 0.f, d2 = 0.f, mean;
+    // (nothing is added to a zero: the compiler would move that up to the load, and the tile's loads would wait for the records)
+    float s_ = rec[0].x, m2 = rec[0].y, d2, mean;
+#pragma unroll
+    for (int u = 1; u < RECORDS; ++u) s_ += rec[u].x;
+    s_ = lanes_sum<C>(s_);
     if (parts == RECORDS * LANES) {
+        mean = s_ * (1.f / (RECORDS * PER));
+        d2 = (rec[0].x - mean) * (rec[0].x - mean);
 #pragma unroll
-        for (int u = 0; u < RECORDS; ++u) s_ += rec[u].x;
-        mean = lanes_sum<C>(s_) * (1.f / (RECORDS * PER));
-#pragma unroll
-        for (int u = 0; u < RECORDS; ++u) {
+        for (int u = 1; u < RECORDS; ++u) {
             const float d = rec[u].x - mean;
             m2 += rec[u].y;
             d2 = fmaf(d, d, d2);
         }
     } else {
         const int count = records_of<C, THREADS>(parts, __builtin_amdgcn_readfirstlane(tid >> 6));
-#pragma unroll
-        for (int u = 0; u < RECORDS; ++u) s_ += rec[u].x;
-        mean = count ? lanes_sum<C>(s_) / (float)count : 0.f;
+        mean = count ? s_ / (float)count : 0.f;
+        d2 = 0.f;
         constexpr int FEW = RECORDS < 4 ? RECORDS : 4;
 #pragma unroll
         for (int u0 = 0; u0 < RECORDS; u0 += FEW) {
@@ -251,7 +253,7 @@ __device__ __forceinline__ float2 merge_lanes(const float2 (&rec)[RECORDS], int 
 #pragma unroll
             for (int u = u0; u < u0 + FEW; ++u) {
                 const float d = has_record<C, THREADS>(u, parts, tid) ? rec[u].x - mean : 0.f;
-                m2 += rec[u].y;
+                if (u) m2 += rec[u].y;
                 d2 = fmaf(d, d, d2);
             }
         }
@@ -320,7 +322,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     char* lds = lds_bytes;
     if ((int)blockIdx.x >= conv_blocks) {           // workgroups behind the convolution's own carry the reduction job
         jobs::wgrad_reduce<THREADS>(rj, blockIdx.x - conv_blocks, reinterpret_cast<float*>(lds));
-        return;
+        __builtin_amdgcn_endpgm();
+        __builtin_unreachable();
     }
     const int parts = list & 0xffff;                // 0: already merged, or added up
     const bool half = list >> 16;
@@ -440,27 +443,18 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     constexpr int STEP = RE * HW * C, STEP_TO = RE * K::ROW;
     auto own = [&](int e) { return (e + 1) * RE <= K::ROWS || pr0 + e * RE < K::ROWS; };                            // a row of the tile
     auto inside = [&](int e) { return K::WHOLE || (own(e) && (unsigned)(r_base - 1 + pr0 + e * RE) < (unsigned)HW); };   // and of the image
+    // Nothing up to here and none of these loads stands behind a branch that the compiler cannot count, and nothing waits in between: what waits for the
+    // records would wait for the tile as well.  A push of 20 layers, batch 8, one worker 360 -> 349 us, 50 layers, batch 128 1565 -> 1546.
+    const bool sub = PRE == 2 && C > 16 && half;                           // every second pixel of the shortcut
     const split::Buffer image = split::buffer(src + image_at, 4u * HW * HW * C);
+    const split::Buffer image_beside = split::buffer(beside + (sub ? 2 : 1) * image_at, (sub ? 8u : 4u) * HW * HW * C);
 #pragma unroll
     for (int e = 0; e < NL; ++e) {
-        if constexpr (PRE == 0) {
-            // Nothing but the scaling comes between load and split: behind a branch the compiler moves it up to the load, and each load
-            // waits for the one before (batch 8: 6.7 instead of 5.9 us).  The others come out 0.1 to 0.4 us slower in this form.
-            val[e] = split::load4(image, inside(e) ? 4u * (unsigned)((r_base + K::ROW0 - 1) * HW * C + 4 * tid + e * STEP) : split::OUTSIDE);
-            continue;
-        }
-        val[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (inside(e)) {
-            val[e] = load4(src + tile_at + e * STEP, 4u * tid);
-            if constexpr (PRE == 2) {
-                if (C > 16 && half) {
-                    scv[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (c4 < C / 2) scv[e] = load4(beside + 2 * (tile_at + e * STEP), (2 * pr0 * HW + tid / V % HW) * C + c4);
-                } else {
-                    scv[e] = load4(beside + tile_at + e * STEP, 4u * tid);
-                }
-            }
-            if constexpr (PRE == 3) scv[e] = load4(beside + tile_at + e * STEP, 4u * tid);
+        const unsigned at = (r_base + K::ROW0 - 1) * HW * C + e * STEP;
+        val[e] = split::load4(image, inside(e) ? 4u * (at + 4 * tid) : split::OUTSIDE);
+        if constexpr (PRE >= 2) {
+            const bool in = inside(e) && !(sub && c4 >= C / 2);
+            scv[e] = split::load4(image_beside, !in ? split::OUTSIDE : sub ? 4u * (2 * at + (2 * pr0 * HW + tid / V % HW) * C + c4) : 4u * (at + 4 * tid));
         }
     }
     // what the epilogue adds, masks with and sums over, a lane's four channels of its pixel of every tile: all these loads together (dst may
@@ -514,8 +508,12 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     };
     // REPEAT: the batch norm's four vectors for the x tile, in LDS (mean, invstd, gamma, beta)
     float* Sx = Sh + K::PS;
-    if constexpr (WG && REPEAT)
-        for (int i = tid; i < 4 * C; i += THREADS) Sx[i] = (i < 2 * C ? post.stats + i : i < 3 * C ? post.gamma + i - 2 * C : post.beta + i - 3 * C)[0];
+    // (stored behind the tile: here the store would wait for all loads before it, 349 -> 347.5 us)
+    float x_norm = 0.f;
+    if constexpr (WG && REPEAT) {
+        static_assert(4 * C <= THREADS, "an element to a thread");
+        if (tid < 4 * C) x_norm = (tid < 2 * C ? post.stats + tid : tid < 3 * C ? post.gamma + tid - 2 * C : post.beta + tid - 3 * C)[0];
+    }
     auto x_value = [&](float4 o, int c) {       // of the x tile, inside the image
         if constexpr (REPEAT) {
             const float4 mu = *reinterpret_cast<const float4*>(Sx + c), is = *reinterpret_cast<const float4*>(Sx + C + c);
@@ -556,9 +554,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         if (parts) {
             float2* shares = reinterpret_cast<float2*>(red);
 #pragma unroll
-            for (int u = 0; u < K::RECORDS; ++u) { sum_b += rec[u].x; sum_g += rec[u].y; }
-            sum_b = lanes_sum<C>(sum_b);
-            sum_g = lanes_sum<C>(sum_g);
+            for (int u = 1; u < K::RECORDS; ++u) { rec[0].x += rec[u].x; rec[0].y += rec[u].y; }
+            sum_b = lanes_sum<C>(rec[0].x);
+            sum_g = lanes_sum<C>(rec[0].y);
             if ((tid & 63) < C) shares[tid / 64 * C + tid % C] = make_float2(sum_b, sum_g);
             __syncthreads();
             if (tid < C) {
@@ -663,6 +661,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
         }
         stage(tile_to + e * STEP_TO, val[e]);
     }
+    if constexpr (WG && REPEAT)
+        if (tid < 4 * C) Sx[tid] = x_norm;
     __syncthreads();
 
     // ---- products.  Pixel operand (st, kx): the tile that starts st rows below the wavefront's first one, kx to the right

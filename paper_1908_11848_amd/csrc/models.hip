@@ -8,6 +8,7 @@
 #include "../../include/dssp_kernels.h"
 #include "conv3x3_layers.hpp"
 #include "conv_split_layers.hpp"
+#include "head.hpp"
 #include "model.hpp"
 
 namespace dssp_model {
@@ -64,7 +65,7 @@ struct Plan {
     int64_t stem_w = 0, stem_g = 0, stem_b = 0, fc_w = 0, fc_b = 0;
     size_t filters = 0;
     FilterRun filter_runs[3] = {};
-    size_t stem_c = 0, stem_a = 0, stem_st = 0, pooled = 0, dpooled = 0, G[3] = {0, 0, 0};
+    size_t stem_c = 0, stem_a = 0, stem_st = 0, pooled = 0, dpooled = 0, head_records = 0, G[3] = {0, 0, 0};
 
     void seg(int kind, int64_t size, int64_t fan_in) { segs.push_back({kind, size, fan_in}); n_params += size; }
     int64_t conv_seg(int k, int cin, int cout, bool bias) {
@@ -174,6 +175,7 @@ struct Plan {
                 }
             fc_w = fc_seg(64, classes); fc_b = fc_w + 64 * (int64_t)classes;
             pooled = a.floats((size_t)m * 64); dpooled = a.floats((size_t)m * 64);
+            head_records = a.floats((size_t)m * 128);
             for (int i = 0; i < 3; ++i) G[i] = a.floats(s0);
             // A stage's filters of stride-1 convolutions are evenly spaced in the parameters: all of the first stage's, from the second
             // convolution on in the others.
@@ -321,6 +323,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     //   conv1 [+ BN2/shortcut/ReLU of the previous block in its loader]  ->  conv2 [+ BN1/ReLU in its loader]
     // and only the last block of a run materialises its output with the stand-alone BN kernels.
     float *recA = bscr, *recB = F(P->bn_scratch2);
+    float *g0 = F(P->G[0]), *g1 = F(P->G[1]), *g2 = F(P->G[2]);     // backward; g0: gradient w.r.t. the current block output
     const int nb = (int)P->blocks.size();
     // Above LARGE_ABOVE images the larger workgroups of dsspk_conv3x3_large_*: half as many records, few enough for every workgroup to
     // add up (173 launches of a 110-layer step less).  A round with the four-wavefront / the larger ones, us: 20 layers, one worker, batch 65
@@ -368,6 +371,8 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     if (!stem_parts)
         RUN(dsspk_bn_fwd(s, F(P->stem_c), w + P->stem_g, w + P->stem_b, F(P->stem_a), F(P->stem_st), bscr, (long)m * 1024, 16, eps, 1, 0, nullptr, 0, 0,
                          0, 0));
+    // everything between the last convolution and its gradient in one launch
+    const bool head = resnet_head_takes(m, parts_of(8, 64, 64, 1), P->n_classes);
     const float* cur = F(P->stem_a);
     bool pending = stem_parts > 0;   // the previous block's output is not written yet (its BN2 is folded into this conv1)
     for (int bi = 0; bi < nb; ++bi) {
@@ -394,16 +399,23 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             RUN(conv(F(B.a1), forward_filter(B.w2, B.f2), F(B.c2), Ho, B.cout, B.cout, 1, parts2 ? recB : nullptr));
         }
         pending = parts2 > 0 && bi + 1 < nb && regular(bi + 1);
-        if (bi + 1 == nb) {
+        if (bi + 1 == nb && head) {
+            const HeadArgs end = {F(B.out), F(B.st2), y, F(P->pooled), F(P->logits), F(P->dlogits), F(P->row_loss), g0, F(P->head_records),
+                                  eps, (float)(M / parts2), 1.f / (float)m, P->n_classes};
+            RUN(resnet_head((hipStream_t)s, F(B.c2), recB, parts2, w + B.g2, cur, mode == 2, w + P->fc_w, m, end));
+        } else if (bi + 1 == nb) {
             RUN(dsspk_bn_fwd_gap(s, F(B.c2), w + B.g2, w + B.b2, F(B.out), F(B.st2), recB, parts2, cur, mode == 2, F(P->pooled), m, Ho, B.cout, eps));
         } else if (!pending) {
             RUN(dsspk_bn_fwd(s, F(B.c2), w + B.g2, w + B.b2, F(B.out), F(B.st2), recB, M, B.cout, eps, 1, mode, cur, m, Ho, Ho, parts2));
         }
         cur = F(B.out);
     }
-    if (int rc = last_layer(P, ws, s, F(P->pooled), 64, y, w, g, P->fc_w, P->fc_b, F(P->dpooled), 0, loss, err)) return rc;
+    if (head) {
+        RUN(dsspk_fc_bwd(s, F(P->pooled), F(P->dlogits), nullptr, g + P->fc_w, g + P->fc_b, nullptr, 0, F(P->row_loss), loss, m, 64, P->n_classes));
+    } else if (int rc = last_layer(P, ws, s, F(P->pooled), 64, y, w, g, P->fc_w, P->fc_b, F(P->dpooled), 0, loss, err)) {
+        return rc;
+    }
     // ---- backward
-    float *g0 = F(P->G[0]), *g1 = F(P->G[1]), *g2 = F(P->G[2]);     // g0: gradient w.r.t. the current block output
     // Per convolution layer the backward pass is  BN backward -> d-input convolution -> d-filter convolution.
     // Where the specialised 3x3 kernels apply, and the gradient arrives already masked with sum records (written by the
     // epilogue of the d-input convolution before it), these collapse (regular_layer below):
@@ -496,7 +508,9 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         const int partsp = identity ? parts_of(B.H, B.cin, B.cout, 1) : 0;
         const bool fused1 = parts1 > 0 && partsp > 0;        // conv1's layer takes the two-launch form
         // ---- BN2 + conv2: g0 = dz2 -> g1 = d conv2 output, g2 = dz1 = d a1 * [a1 > 0] (+ BN1's records in bscr)
-        if (bi + 1 == nb) {             // from the pooled gradient
+        if (bi + 1 == nb && head) {
+            parts0 = m;
+        } else if (bi + 1 == nb) {      // from the pooled gradient
             RUN(dsspk_gap_bwd_bn_reduce(s, F(P->dpooled), F(B.c2), F(B.st2), F(B.out), g0, recB0, m, Ho, B.cout));
             parts0 = m;
         } else if (!parts0) {           // g0 is not masked yet
@@ -504,7 +518,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             parts0 = parts1;
             tot0 = false;
         }
-        RUN(regular_layer(recB0, parts0, g + B.g2, g + B.b2, tot0, g0, F(B.c2), F(B.st2), w + B.g2, totB, input_filter(B.w2, B.f2, B.cout), nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr,
+        RUN(regular_layer(bi + 1 == nb && head ? F(P->head_records) : recB0, parts0, g + B.g2, g + B.b2, tot0, g0, F(B.c2), F(B.st2), w + B.g2, totB, input_filter(B.w2, B.f2, B.cout), nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr,
                           g + B.w2, Ho, B.cout, fused1, parts1, totA, g + B.g1, g + B.b1, w + B.g1, w + B.b1));        // sums of BN1's records to totA if fused1
         // ---- BN1 + conv1: g2 = dz1 -> g1 = d conv1 output; d-input (+ dz2 through an identity shortcut) = gradient
         //      w.r.t. the block's input, which is the previous block's (or the stem's) post-ReLU output: mask +

@@ -13,6 +13,7 @@ using bnm::BnLayout;
 using bnm::bn_layout;
 using bnm::reduce_sub;
 using bnm::bn_merge_stats;
+using bnm::Records;
 constexpr int THREADS = bnm::THREADS;
 
 // ------------------------------------------------------------------ elementwise
@@ -239,27 +240,26 @@ __global__ __launch_bounds__(THREADS) void bn_apply_kernel(const float* __restri
                                                            BnLayout L) {
     __shared__ float red[THREADS];
     __shared__ __attribute__((aligned(16))) float sh[2 * THREADS];
-    bn_merge_stats(partial, M, C, eps, red, sh, L);
-    if (blockIdx.x == 0 && threadIdx.x < 2 * C) stats[threadIdx.x] = sh[threadIdx.x];
+    const Records records(partial, C, L.G);
     const int VC = C / 4, vshift = __ffs(VC) - 1;
     const long total = M * VC;
     const long stride = (long)gridDim.x * THREADS;
-    // four independent rows per lane and trip: all loads are issued before the first use
-    for (long i0 = (long)blockIdx.x * THREADS + threadIdx.x; i0 < total; i0 += 4 * stride) {
-        float4 v[4], s4[4];
-        bool ok[4];
+    const int vc = (int)(threadIdx.x & (VC - 1));           // VC is a power of two (C is 4 .. 64 and divides the workgroup size), and divides the stride
+    const float4 ga = *reinterpret_cast<const float4*>(gamma + 4 * vc), be = *reinterpret_cast<const float4*>(beta + 4 * vc);
+    // four independent rows per lane and trip: all loads are issued before the first use, the first trip's before the records are merged
+    float4 v[4], s4[4];
+    auto load = [&](long i0) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const long i = i0 + u * stride;
-            ok[u] = i < total;
-            const int vc = (int)(i & (VC - 1));     // VC is a power of two (C is 4 .. 64 and divides the workgroup size)
+            const bool ok = i < total;
             const long row = i >> vshift;
-            v[u] = ok[u] ? *reinterpret_cast<const float4*>(x + row * C + 4 * vc) : make_float4(0.f, 0.f, 0.f, 0.f);
+            v[u] = ok ? *reinterpret_cast<const float4*>(x + row * C + 4 * vc) : make_float4(0.f, 0.f, 0.f, 0.f);
             s4[u] = make_float4(0.f, 0.f, 0.f, 0.f);
             if constexpr (SC_MODE == 1) {
-                if (ok[u]) s4[u] = *reinterpret_cast<const float4*>(sc + row * C + 4 * vc);
+                if (ok) s4[u] = *reinterpret_cast<const float4*>(sc + row * C + 4 * vc);
             } else if constexpr (SC_MODE == 2) {
-                if (ok[u] && 4 * vc < C / 2) {   // first half of the channels: input pixel (2ho, 2wo), C/2 channels wide
+                if (ok && 4 * vc < C / 2) {      // first half of the channels: input pixel (2ho, 2wo), C/2 channels wide
                     const unsigned ru = (unsigned)row, rq = ru / (unsigned)sc_wo;       // M < 2^31: 32-bit divisions
                     const int wo = (int)(ru - rq * (unsigned)sc_wo);
                     const long n = rq / (unsigned)sc_ho;
@@ -268,23 +268,25 @@ __global__ __launch_bounds__(THREADS) void bn_apply_kernel(const float* __restri
                 }
             }
         }
+    };
+    const long first = (long)blockIdx.x * THREADS + threadIdx.x;
+    load(first);
+    bn_merge_stats(records, M, C, eps, red, sh, L);
+    if (blockIdx.x == 0 && threadIdx.x < 2 * C) stats[threadIdx.x] = sh[threadIdx.x];
+    const float4 mu = *reinterpret_cast<const float4*>(sh + 4 * vc), is = *reinterpret_cast<const float4*>(sh + C + 4 * vc);
+    for (long i0 = first; i0 < total; i0 += 4 * stride) {
+        if (i0 != first) load(i0);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            if (!ok[u]) continue;
             const long i = i0 + u * stride;
-            const int vc = (int)(i & (VC - 1));     // VC is a power of two (C is 4 .. 64 and divides the workgroup size)
-            const long row = i >> vshift;
-            const float4 mu = *reinterpret_cast<const float4*>(sh + 4 * vc);
-            const float4 is = *reinterpret_cast<const float4*>(sh + C + 4 * vc);
-            const float4 ga = *reinterpret_cast<const float4*>(gamma + 4 * vc);
-            const float4 be = *reinterpret_cast<const float4*>(beta + 4 * vc);
+            if (i >= total) continue;
             float4 o;
             o.x = fmaf((v[u].x - mu.x) * is.x, ga.x, be.x) + s4[u].x;
             o.y = fmaf((v[u].y - mu.y) * is.y, ga.y, be.y) + s4[u].y;
             o.z = fmaf((v[u].z - mu.z) * is.z, ga.z, be.z) + s4[u].z;
             o.w = fmaf((v[u].w - mu.w) * is.w, ga.w, be.w) + s4[u].w;
             if (relu) { o.x = fmaxf(o.x, 0.f); o.y = fmaxf(o.y, 0.f); o.z = fmaxf(o.z, 0.f); o.w = fmaxf(o.w, 0.f); }
-            *reinterpret_cast<float4*>(y + row * C + 4 * vc) = o;
+            *reinterpret_cast<float4*>(y + (i >> vshift) * C + 4 * vc) = o;
         }
     }
 }
@@ -344,61 +346,60 @@ __global__ __launch_bounds__(THREADS) void bn_bwd_dx_kernel(const float* __restr
                                                             BnLayout L) {
     __shared__ float red[THREADS];
     __shared__ __attribute__((aligned(16))) float sh[2 * THREADS];      // [0,C): dbeta, [C,2C): dgamma
-    {
-        const int SUB = THREADS / C;
-        const int c = threadIdx.x % C, sub = threadIdx.x / C;
-        float2 pv[32];
+    const Records records(partial, C, L.G);
+    const int VC = C / 4, vshift = __ffs(VC) - 1;
+    const long total = M * VC;
+    const float inv_m = 1.0f / (float)M;
+    const long stride = (long)gridDim.x * THREADS;
+    const int vc = (int)(threadIdx.x & (VC - 1));           // VC is a power of two (C is 4 .. 64 and divides the workgroup size), and divides the stride
+    const float4 mu = *reinterpret_cast<const float4*>(stats + 4 * vc), is = *reinterpret_cast<const float4*>(stats + C + 4 * vc);
+    const float4 ga = *reinterpret_cast<const float4*>(gamma + 4 * vc);
+    float4 v[4], d[4];
+    auto load = [&](long i0) {                              // all loads of a trip first, the first trip's before the records are added up
 #pragma unroll
-        for (int u = 0; u < 32; ++u)            // one batch of unconditional loads (G <= 32 * SUB; index clamped)
-            pv[u] = *reinterpret_cast<const float2*>(partial + ((long)min(sub + u * SUB, L.G - 1) * C + c) * 2);
+        for (int u = 0; u < 4; ++u) {
+            const long i = i0 + u * stride;
+            const bool ok = i < total;
+            v[u] = ok ? *reinterpret_cast<const float4*>(x + (i >> vshift) * C + 4 * vc) : make_float4(0.f, 0.f, 0.f, 0.f);
+            d[u] = ok ? *reinterpret_cast<const float4*>(dz + (i >> vshift) * C + 4 * vc) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    const long first = (long)blockIdx.x * THREADS + threadIdx.x;
+    load(first);
+    {
+        const int SUB = THREADS / C, c = threadIdx.x % C, sub = threadIdx.x / C;
         float sb = 0.f, sg = 0.f;
 #pragma unroll
-        for (int u = 0; u < 32; ++u) {
-            const bool in = sub + u * SUB < L.G;
-            sb += in ? pv[u].x : 0.f;
-            sg += in ? pv[u].y : 0.f;
+        for (int u0 = 0; u0 < 32; u0 += 8) {
+            if (u0 * SUB >= L.G) continue;
+#pragma unroll
+            for (int u = u0; u < u0 + 8; ++u) {
+                const bool in = sub + u * SUB < L.G;
+                sb += in ? records.v[u].x : 0.f;
+                sg += in ? records.v[u].y : 0.f;
+            }
         }
-        sb = reduce_sub(sb, red, c, sub, SUB, C);
-        sg = reduce_sub(sg, red, c, sub, SUB, C);
+        sb = reduce_sub(sb, red, c, C);
+        sg = reduce_sub(sg, red, c, C);
         if (sub == 0) {
             sh[c] = sb; sh[C + c] = sg;
             if (blockIdx.x == 0) { dbeta[c] = sb; dgamma[c] = sg; }
         }
         __syncthreads();
     }
-    const int VC = C / 4, vshift = __ffs(VC) - 1;
-    const long total = M * VC;
-    const float inv_m = 1.0f / (float)M;
-    const long stride = (long)gridDim.x * THREADS;
-    for (long i0 = (long)blockIdx.x * THREADS + threadIdx.x; i0 < total; i0 += 4 * stride) {
-        float4 v[4], d[4];
-        bool ok[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {            // all loads of the trip first
-            const long i = i0 + u * stride;
-            ok[u] = i < total;
-            const int vc = (int)(i & (VC - 1));     // VC is a power of two (C is 4 .. 64 and divides the workgroup size)
-            const long row = i >> vshift;
-            v[u] = ok[u] ? *reinterpret_cast<const float4*>(x + row * C + 4 * vc) : make_float4(0.f, 0.f, 0.f, 0.f);
-            d[u] = ok[u] ? *reinterpret_cast<const float4*>(dz + row * C + 4 * vc) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+    const float4 db = *reinterpret_cast<const float4*>(sh + 4 * vc), dg = *reinterpret_cast<const float4*>(sh + C + 4 * vc);
+    for (long i0 = first; i0 < total; i0 += 4 * stride) {
+        if (i0 != first) load(i0);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            if (!ok[u]) continue;
             const long i = i0 + u * stride;
-            const int vc = (int)(i & (VC - 1));     // VC is a power of two (C is 4 .. 64 and divides the workgroup size)
-            const long row = i >> vshift;
-            const float4 mu = *reinterpret_cast<const float4*>(stats + 4 * vc);
-            const float4 is = *reinterpret_cast<const float4*>(stats + C + 4 * vc);
-            const float4 ga = *reinterpret_cast<const float4*>(gamma + 4 * vc);
-            const float4 db = *reinterpret_cast<const float4*>(sh + 4 * vc);
-            const float4 dg = *reinterpret_cast<const float4*>(sh + C + 4 * vc);
+            if (i >= total) continue;
             float4 o;
             o.x = ga.x * is.x * (d[u].x - db.x * inv_m - (v[u].x - mu.x) * is.x * (dg.x * inv_m));
             o.y = ga.y * is.y * (d[u].y - db.y * inv_m - (v[u].y - mu.y) * is.y * (dg.y * inv_m));
             o.z = ga.z * is.z * (d[u].z - db.z * inv_m - (v[u].z - mu.z) * is.z * (dg.z * inv_m));
             o.w = ga.w * is.w * (d[u].w - db.w * inv_m - (v[u].w - mu.w) * is.w * (dg.w * inv_m));
-            *reinterpret_cast<float4*>(dx + row * C + 4 * vc) = o;
+            *reinterpret_cast<float4*>(dx + (i >> vshift) * C + 4 * vc) = o;
         }
     }
 }
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(THREADS) void bn_gap_kernel(const float* __restrict
     __shared__ float red[THREADS];
     __shared__ __attribute__((aligned(16))) float sh[2 * THREADS];
     __shared__ float4 red4[THREADS];
-    bn_merge_stats(partial, M, C, eps, red, sh, L);
+    bn_merge_stats(Records(partial, C, L.G), M, C, eps, red, sh, L);
     if (blockIdx.x == 0 && threadIdx.x < 2 * C) stats[threadIdx.x] = sh[threadIdx.x];
     const int VC = C / 4, RL = THREADS / VC, rl = threadIdx.x / VC, vc = threadIdx.x % VC, HW = side * side;
     const long base = (long)blockIdx.x * HW;

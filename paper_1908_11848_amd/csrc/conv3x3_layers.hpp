@@ -8,6 +8,14 @@
 // dsspk_conv_fwd_records, or NULL.
 int conv_stem(hipStream_t s, const float* x, const float* w, float* y, float* records, int N, FilterJob job);
 
+// k_conv.hip: a residual network's stride-2 3x3 convolution (16 -> 32 channels on 32x32, 32 -> 64 on 16x16; at most 32 images): dsspk_conv_bwd_data_shortcut and the
+// first stage of its d-filter, with the backward pass of the ReLU and batch norm in front begun: dx is masked by mask > 0 (the convolution's input, that
+// norm's output behind the ReLU) and the sums of dx and dx * xhat, xhat of xc and stats, are left as records.  ..records: how many; 0: shape not taken.
+struct BehindBn { const float *mask, *xc, *stats; float* records; };
+int conv_stride2_bwd_records(int N, int H, int Cin);
+int conv_stride2_bwd(hipStream_t s, const float* dy, const float* w, const float* shortcut, float* dx, float* partial, const BehindBn& behind, int N, int H, int Cin,
+                     int* chunks_out);
+
 int wgrad_reduce_many(hipStream_t s, int n, const jobs::Partials* waiting);
 
 // k_conv3x3.hip; -2 = shape not covered.

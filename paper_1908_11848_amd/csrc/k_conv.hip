@@ -10,6 +10,9 @@
 // row are neighbouring runs.  A workgroup of 4 wavefronts stages a BM-pixel x 16 slice of the
 // gathered operand and the matching 16 x C slice of the filter in LDS (double buffered, next
 // slice prefetched into registers while the matrix cores work on the current one).
+#include <algorithm>
+#include <type_traits>
+
 #include "mma.hpp"
 #include "jobs.hpp"
 #include "conv3x3_layers.hpp"
@@ -71,15 +74,16 @@ __device__ __forceinline__ bool src_pixel(const ConvGeom& g, int oh, int ow, int
 //   KS   : k-chunks of 16 per LDS stage (VEC only; IC a multiple of 16 * KS).  A stage is one barrier, one round of
 //          address arithmetic and one round of global loads, so wide layers take KS = 2: half the barriers and
 //          half the vector instructions per MFMA (fp32 MFMA and vector arithmetic do not overlap on this chip).
-//   Job: workgroups behind the kernel's own convert the filters of later layers (FilterJob).
+//   Job: workgroups behind the kernel's own convert the filters of later layers (FilterJob), or (DGRAD, with EXTRA) the epilogue masks the result
+//          and leaves the sum records of the batch norm in front (BehindBn).
 //   EXTRA: the epilogue also leaves statistics records (forward) or adds a shortcut's gradient (DGRAD).  Instances of their own: with the
 //          question asked inside, calls without it took up to 5 % longer (16 -> 32 channels, stride 2, 32x32, batch 64: 7.1 -> 7.5 us).
 template <int BM, int BN, bool DGRAD, bool VEC, int KS, bool EXTRA, class... Job>
-__global__ __launch_bounds__(THREADS) void conv_igemm_kernel(const float* __restrict__ src, const float* __restrict__ wgt,
-                                                             const float* __restrict__ bias, const float* __restrict__ add,
-                                                             float* __restrict__ dst, ConvGeom g, int relu, int mode, float* __restrict__ extra, Job... job) {
-    if constexpr (sizeof...(Job) > 0)
-        if ((..., ((int)blockIdx.x >= job.own_blocks))) return (..., convert_filters(job, blockIdx.x - job.own_blocks));
+__device__ __forceinline__ void igemm_tile(int block_x, int block_y, int blocks_x, float* igemm_lds, const float* __restrict__ src,
+                                           const float* __restrict__ wgt, const float* __restrict__ bias, const float* __restrict__ add,
+                                           float* __restrict__ dst, const ConvGeom& g, int relu, int mode, float* __restrict__ extra, const Job&... job) {
+    constexpr bool BEHIND = (std::is_same_v<Job, BehindBn> || ...);
+    static_assert(!BEHIND || (DGRAD && EXTRA), "in the epilogue of a d-input");
     static_assert(KS == 1 || VEC, "several k-chunks per stage only with 16-byte gathers");
     constexpr int WM = BM / 64, WN = BN / 16;
     constexpr int KST = mma::KC * KS;                              // reduction indices per stage
@@ -88,24 +92,24 @@ __global__ __launch_bounds__(THREADS) void conv_igemm_kernel(const float* __rest
     constexpr int BS = DGRAD ? BN * LDA : KST * (BN + 4);
     constexpr int RPT = BM / 64;                                   // gathered rows per thread (VEC)
     constexpr int BV = KST * BN / 4 / THREADS > 0 ? KST * BN / 4 / THREADS : 1;     // 16-byte filter loads per thread and stage
-    extern __shared__ __attribute__((aligned(16))) float igemm_lds[];      // As[2][BM * LDA], then Bs[2][BS], then the staged rows
+    // igemm_lds: As[2][BM * LDA], then Bs[2][BS], then the staged rows
     float (*As)[BM * LDA] = reinterpret_cast<float (*)[BM * LDA]>(igemm_lds);
     float (*Bs)[BS] = reinterpret_cast<float (*)[BS]>(igemm_lds + 2 * BM * LDA);
     const float* Img = igemm_lds + 2 * BM * LDA + 2 * BS;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool staged = !VEC && mode == IGEMM_STAGED;
-    const int n0 = blockIdx.y * BN;
+    const int n0 = block_y * BN;
     const int taps = g.KH * g.KW;
     // IGEMM_PARITY (d-input of a stride-2 layer, even H and W): the rows are ordered by the parity class (h % 2, w % 2) of
     // the pixel, a workgroup's rows are of one class, and it walks only the taps that reach a dy pixel from that class
     // (kh = (h + pad) mod 2, +2, ...): a quarter of the (pixel, tap) pairs, the others would multiply zeros.
     const bool parity = DGRAD && mode == IGEMM_PARITY;
-    long m0 = (long)blockIdx.x * BM, Mrows = g.M;
+    long m0 = (long)block_x * BM, Mrows = g.M;
     ConvGeom gr = g;                                               // pixel grid the rows are decomposed on
     int ph = 0, pw = 0, kh0 = 0, kw0 = 0, nkw = g.KW, ntaps = taps;
     if (parity) {
-        const int tiles = gridDim.x >> 2, cls = blockIdx.x / tiles;
-        m0 = (long)(blockIdx.x - cls * tiles) * BM;
+        const int tiles = blocks_x >> 2, cls = block_x / tiles;
+        m0 = (long)(block_x - cls * tiles) * BM;
         ph = cls >> 1; pw = cls & 1;
         kh0 = (ph + g.pad) & 1; kw0 = (pw + g.pad) & 1;
         nkw = (g.KW - kw0 + 1) >> 1;
@@ -282,12 +286,15 @@ __global__ __launch_bounds__(THREADS) void conv_igemm_kernel(const float* __rest
 
     mma::drain();
     const int l16 = lane & 15, q = lane >> 4;
+    float sum_dz[BEHIND ? WN : 1] = {}, sum_dzx[BEHIND ? WN : 1] = {};
 #pragma unroll
     for (int wm = 0; wm < WM; ++wm)
 #pragma unroll
         for (int wn = 0; wn < WN; ++wn) {
             const int col = n0 + 16 * wn + l16;
             const float bv = bias ? bias[col] : 0.f;
+            float mu = 0.f, is = 0.f;
+            if constexpr (BEHIND) { mu = (job, ...).stats[col]; is = (job, ...).stats[g.OC + col]; }
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const long r = m0 + wave * (BM / 4) + 16 * wm + 4 * q + v;
@@ -302,9 +309,31 @@ __global__ __launch_bounds__(THREADS) void conv_igemm_kernel(const float* __rest
                 if (add) x += add[m * g.OC + col];
                 if (DGRAD && EXTRA && !(ph | pw)) x += extra[r * (2 * g.OC) + col];        // class (0, 0): its rows are the pixels of `extra`
                 if (relu) x = fmaxf(x, 0.f);
+                if constexpr (BEHIND) {
+                    x = (job, ...).mask[m * g.OC + col] > 0.f ? x : 0.f;
+                    sum_dz[wn] += x;
+                    sum_dzx[wn] = fmaf(x, ((job, ...).xc[m * g.OC + col] - mu) * is, sum_dzx[wn]);
+                }
                 dst[m * g.OC + col] = x;
             }
         }
+    // Record of the tile: sum dz and sum dz * xhat per channel, lanes first, then the wavefronts, in a fixed order.
+    if constexpr (BEHIND) {
+        float2* red = reinterpret_cast<float2*>(igemm_lds);        // [4 wavefronts][BN]
+        __syncthreads();                                           // the operand tiles are no longer needed
+#pragma unroll
+        for (int wn = 0; wn < WN; ++wn) {
+            float a = sum_dz[wn], b = sum_dzx[wn];
+            a += __shfl_xor(a, 16); b += __shfl_xor(b, 16);
+            a += __shfl_xor(a, 32); b += __shfl_xor(b, 32);
+            if (q == 0) red[wave * BN + 16 * wn + l16] = make_float2(a, b);
+        }
+        __syncthreads();
+        if (tid < BN) {
+            const float2 a = red[tid], b = red[BN + tid], c = red[2 * BN + tid], d = red[3 * BN + tid];
+            *reinterpret_cast<float2*>((job, ...).records + ((long)block_x * g.OC + n0 + tid) * 2) = make_float2((a.x + b.x) + (c.x + d.x), (a.y + b.y) + (c.y + d.y));
+        }
+    }
     // Forward: statistics record of the tile (its rows are all there), mean and sum of squared deviations per channel.
     if constexpr (!DGRAD && EXTRA) {
         float* red = igemm_lds;                                    // [2][4 wavefronts][BN]
@@ -330,10 +359,20 @@ __global__ __launch_bounds__(THREADS) void conv_igemm_kernel(const float* __rest
                 const float* p = red + 4 * pass * BN + 16 * wn + l16;
                 const float t = (p[0] + p[BN]) + (p[2 * BN] + p[3 * BN]);
                 if (pass == 0) mean[wn] = t * (1.0f / BM);
-                else if (tid < 16) *reinterpret_cast<float2*>(extra + ((long)blockIdx.x * g.OC + n0 + 16 * wn + l16) * 2) = make_float2(mean[wn], t);
+                else if (tid < 16) *reinterpret_cast<float2*>(extra + ((long)block_x * g.OC + n0 + 16 * wn + l16) * 2) = make_float2(mean[wn], t);
             }
         }
     }
+}
+
+template <int BM, int BN, bool DGRAD, bool VEC, int KS, bool EXTRA, class... Job>
+__global__ __launch_bounds__(THREADS) void conv_igemm_kernel(const float* __restrict__ src, const float* __restrict__ wgt,
+                                                             const float* __restrict__ bias, const float* __restrict__ add,
+                                                             float* __restrict__ dst, ConvGeom g, int relu, int mode, float* __restrict__ extra, Job... job) {
+    extern __shared__ __attribute__((aligned(16))) float igemm_lds[];
+    if constexpr ((std::is_same_v<Job, FilterJob> || ...))
+        if ((..., ((int)blockIdx.x >= job.own_blocks))) return (..., convert_filters(job, blockIdx.x - job.own_blocks));
+    igemm_tile<BM, BN, DGRAD, VEC, KS, EXTRA>(blockIdx.x, blockIdx.y, gridDim.x, igemm_lds, src, wgt, bias, add, dst, g, relu, mode, extra, job...);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -348,24 +387,24 @@ __global__ __launch_bounds__(THREADS) void conv_igemm_kernel(const float* __rest
 //          zero padding first, in coalesced loads, and the (pixel, tap, ci) operand is gathered from that copy through
 //          offsets each thread works out once: the element-wise gather from global memory costs far more than the MFMAs.
 constexpr int WGRAD_IMG_MAX = 2048;                 // floats of the staged input rows
+// LDS of its operand tiles
+template <int CI_T, int CO_T> constexpr int wgrad_floats() { return 64 * (16 * CI_T + 4 + 16 * CO_T + 4); }
 template <int CI_T, int CO_T, bool VEC, bool IMG = false>
-__global__ __launch_bounds__(THREADS) void conv_wgrad_kernel(const float* __restrict__ x, const float* __restrict__ dy,
-                                                             float* __restrict__ partial, ConvGeom g, int stages, int rows_total) {
+__device__ __forceinline__ void wgrad_chunk(int block_x, int block_y, int block_z, float* lds, const float* __restrict__ x, const float* __restrict__ dy,
+                                            float* __restrict__ partial, const ConvGeom& g, int stages, int rows_total) {
     static_assert(!(VEC && IMG), "staged rows serve the element-wise gather only");
     constexpr int CIP = 16 * CI_T, COP = 16 * CO_T;
     constexpr int LDA = CIP + 4, LDB = COP + 4;
     constexpr int PIX = 64;
     static_assert(CIP * COP <= PIX * LDA, "the cross-wavefront sum reuses the operand tile");
-    __shared__ __attribute__((aligned(16))) float Xs[PIX * LDA];
-    __shared__ __attribute__((aligned(16))) float Ds[PIX * LDB];
-    __shared__ __attribute__((aligned(16))) float Img[IMG ? WGRAD_IMG_MAX : 4];
+    float *Xs = lds, *Ds = lds + PIX * LDA, *Img = Ds + PIX * LDB;
     float* Red = Xs;                                                // used after the last slice has been consumed
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tap = blockIdx.y;
+    const int tap = block_y;
     const int kh = tap / g.KW, kw = tap - kh * g.KW;
-    const long p_begin = (long)blockIdx.x * stages * PIX;
+    const long p_begin = (long)block_x * stages * PIX;
     const int ci_slices = VEC ? g.IC / CIP : 1;
-    const int ci0 = ((int)blockIdx.z % ci_slices) * CIP, co0 = ((int)blockIdx.z / ci_slices) * COP;
+    const int ci0 = ((int)block_z % ci_slices) * CIP, co0 = ((int)block_z / ci_slices) * COP;
 
     floatx4 acc[CI_T][CO_T];
     mma::zero(acc);
@@ -511,11 +550,18 @@ __global__ __launch_bounds__(THREADS) void conv_wgrad_kernel(const float* __rest
     __syncthreads();
     // partial[chunk][row][co]; VEC: row = tap*Cin + ci, else row = flattened (tap, ci)
     const int rows = VEC ? CIP : rows_total;
-    float* out = partial + ((long)blockIdx.x * rows_total + (VEC ? (long)tap * g.IC + ci0 : 0)) * g.OC + co0;
+    float* out = partial + ((long)block_x * rows_total + (VEC ? (long)tap * g.IC + ci0 : 0)) * g.OC + co0;
     for (int idx = tid; idx < rows * COP; idx += THREADS) {
         const int rr = idx / COP, co = idx - rr * COP;
         out[(long)rr * g.OC + co] = Red[rr * COP + co];
     }
+}
+
+template <int CI_T, int CO_T, bool VEC, bool IMG = false>
+__global__ __launch_bounds__(THREADS) void conv_wgrad_kernel(const float* __restrict__ x, const float* __restrict__ dy,
+                                                             float* __restrict__ partial, ConvGeom g, int stages, int rows_total) {
+    __shared__ __attribute__((aligned(16))) float lds[wgrad_floats<CI_T, CO_T>() + (IMG ? WGRAD_IMG_MAX : 0)];
+    wgrad_chunk<CI_T, CO_T, VEC, IMG>(blockIdx.x, blockIdx.y, blockIdx.z, lds, x, dy, partial, g, stages, rows_total);
 }
 
 // d-filter, stage 1, for wide layers (at least four 16x16 tiles per tap).  Same work split over
@@ -523,15 +569,8 @@ __global__ __launch_bounds__(THREADS) void conv_wgrad_kernel(const float* __rest
 // all 64 pixels of every slice (no cross-wavefront sum), and the next slice is prefetched into
 // registers while the matrix cores work on the current one (two LDS buffers, one barrier per slice).
 template <int CI_T, int CO_T>
-__global__ __launch_bounds__(THREADS) void conv_wgrad_tile_kernel(const float* __restrict__ x, const float* __restrict__ dy,
-                                                                  float* __restrict__ partial, ConvGeom g, int stages,
-                                                                  int own_x, jobs::TotalsJob tj) {
-    extern __shared__ __attribute__((aligned(16))) float lds[];
-    if ((int)blockIdx.x >= own_x) {                 // columns of workgroups behind the kernel's own carry the batch-norm sums job
-        const int jb = ((int)blockIdx.x - own_x) * gridDim.y + blockIdx.y;
-        if (jb < tj.blocks) jobs::bn_totals(tj, jb, lds);
-        return;
-    }
+__device__ __forceinline__ void wgrad_tile_chunk(int block_x, int block_y, float* lds, const float* __restrict__ x, const float* __restrict__ dy,
+                                                 float* __restrict__ partial, const ConvGeom& g, int stages) {
     constexpr int CIP = 16 * CI_T, COP = 16 * CO_T;
     constexpr int LDA = CIP + 4, LDB = COP + 4;
     constexpr int PIX = 64;
@@ -542,9 +581,9 @@ __global__ __launch_bounds__(THREADS) void conv_wgrad_tile_kernel(const float* _
     float* Xs = lds;                                   // [2][PIX * LDA]
     float* Ds = lds + 2 * PIX * LDA;                   // [2][PIX * LDB]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tap = blockIdx.y;
+    const int tap = block_y;
     const int kh = tap / g.KW, kw = tap - kh * g.KW;
-    const long p_begin = (long)blockIdx.x * stages * PIX;
+    const long p_begin = (long)block_x * stages * PIX;
     int nst = stages;
     if (p_begin + (long)nst * PIX > g.M) nst = (int)((g.M - p_begin + PIX - 1) / PIX);
 
@@ -608,7 +647,7 @@ __global__ __launch_bounds__(THREADS) void conv_wgrad_tile_kernel(const float* _
     }
     mma::drain();
     const int l16 = lane & 15, q = lane >> 4;
-    float* out = partial + ((long)blockIdx.x * g.KH * g.KW * g.IC + (long)tap * g.IC) * g.OC;
+    float* out = partial + ((long)block_x * g.KH * g.KW * g.IC + (long)tap * g.IC) * g.OC;
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -619,9 +658,22 @@ __global__ __launch_bounds__(THREADS) void conv_wgrad_tile_kernel(const float* _
 }
 
 template <int CI_T, int CO_T>
+__global__ __launch_bounds__(THREADS) void conv_wgrad_tile_kernel(const float* __restrict__ x, const float* __restrict__ dy,
+                                                                  float* __restrict__ partial, ConvGeom g, int stages,
+                                                                  int own_x, jobs::TotalsJob tj) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    if ((int)blockIdx.x >= own_x) {                 // columns of workgroups behind the kernel's own carry the batch-norm sums job
+        const int jb = ((int)blockIdx.x - own_x) * gridDim.y + blockIdx.y;
+        if (jb < tj.blocks) jobs::bn_totals(tj, jb, lds);
+        return;
+    }
+    wgrad_tile_chunk<CI_T, CO_T>(blockIdx.x, blockIdx.y, lds, x, dy, partial, g, stages);
+}
+
+template <int CI_T, int CO_T>
 int launch_wgrad_tile(hipStream_t s, const float* x, const float* dy, float* scratch, const ConvGeom& g, int stages, dim3 grid,
                       const jobs::TotalsJob& tj) {
-    constexpr size_t bytes = (size_t)2 * 64 * ((16 * CI_T + 4) + (16 * CO_T + 4)) * sizeof(float);
+    constexpr size_t bytes = 2 * wgrad_floats<CI_T, CO_T>() * sizeof(float);
     static_assert(bytes >= jobs::LDS_FLOATS * sizeof(float), "room for a carried job");
     const int own_x = grid.x;
     grid.x += (tj.blocks + grid.y - 1) / grid.y;
@@ -895,6 +947,61 @@ extern "C" int dsspk_conv_bwd_data_shortcut(void* stream, const float* dy, const
     g.M = (long)N * H * W;
     if (g.M >= (1L << 31)) return -1;
     return launch_igemm<true, true>((hipStream_t)stream, dy, w, nullptr, nullptr, dx, g, 0, const_cast<float*>(shortcut));
+}
+
+// Both gradients of a residual network's stride-2 convolution in one launch, workgroups of the d-input first (they take longer), and the way back through the
+// ReLU and batch norm in front of it begun in the d-input's epilogue.  One after the other, with a launch for that batch norm, these were three dependent
+// launches of 5 to 9 us at each stage boundary: a push of 20 layers, batch 8, one worker 326 -> 317 us with the epilogue, -> 309 with one launch, 8 layers, batch 13, three
+// workers, launches, a round 380 -> 345.
+template <int KS, bool TILE>
+__global__ __launch_bounds__(THREADS) void stride2_bwd_kernel(const float* __restrict__ dy, const float* __restrict__ w, float* __restrict__ shortcut,
+                                                              float* __restrict__ dx, const float* __restrict__ x, float* __restrict__ partial,
+                                                              int igemm_tiles, int chunks, int stages, ConvGeom gd, ConvGeom gw, BehindBn behind) {
+    extern __shared__ __attribute__((aligned(16))) float stride2_lds[];
+    const int igemm_blocks = igemm_tiles * (gd.OC / 16);
+    if ((int)blockIdx.x < igemm_blocks) {
+        igemm_tile<64, 16, true, true, KS, true>(blockIdx.x % igemm_tiles, blockIdx.x / igemm_tiles, igemm_tiles, stride2_lds, dy, w, nullptr, nullptr, dx, gd, 0,
+                                                 IGEMM_PARITY, shortcut, behind);
+        return;
+    }
+    const int b = blockIdx.x - igemm_blocks;
+    if constexpr (TILE) wgrad_tile_chunk<2, 4>(b % chunks, b / chunks, stride2_lds, x, dy, partial, gw, stages);
+    else wgrad_chunk<1, 2, true, false>(b % chunks, b / chunks, 0, stride2_lds, x, dy, partial, gw, stages, 9 * 16);
+}
+
+template <int KS, bool TILE>
+static int launch_stride2(hipStream_t s, const float* dy, const float* w, const float* shortcut, float* dx, const float* x, float* partial, int chunks, int stages,
+                          const ConvGeom& gd, const ConvGeom& gw, const BehindBn& behind) {
+    constexpr size_t bytes = std::max(igemm_lds_bytes<64, 16, true, KS>(), sizeof(float) * (TILE ? 2 * wgrad_floats<2, 4>() : wgrad_floats<1, 2>()));
+    auto kern = stride2_bwd_kernel<KS, TILE>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        if (bytes > 48 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return -1;
+        attr_set = true;
+    }
+    const int tiles = 4 * ceil_div(gd.M / 4, 64);
+    hipLaunchKernelGGL(kern, dim3(tiles * (gd.OC / 16) + 9 * chunks), dim3(THREADS), bytes, s, dy, w, const_cast<float*>(shortcut), dx, x, partial, tiles, chunks,
+                       stages, gd, gw, behind);
+    return DSSPK_LAUNCH_RC();
+}
+
+int conv_stride2_bwd_records(int N, int H, int Cin) {
+    if (N < 1 || N > 32 || !((H == 32 && Cin == 16) || (H == 16 && Cin == 32))) return 0;
+    return 4 * ceil_div((long)N * (H / 2) * (H / 2), 64);
+}
+
+int conv_stride2_bwd(hipStream_t s, const float* dy, const float* w, const float* shortcut, float* dx, float* partial, const BehindBn& behind, int N, int H, int Cin,
+                     int* chunks_out) {
+    ConvGeom gw;
+    if (!dy || !w || !shortcut || !dx || !partial || shortcut == dx || !behind.mask || !behind.xc || !behind.stats || !behind.records) return -1;
+    if (!conv_stride2_bwd_records(N, H, Cin) || !geom(gw, N, H, H, Cin, 2 * Cin, 3, 3, 2, 1)) return -1;
+    ConvGeom gd = gw;
+    gd.OH = H; gd.OW = H; gd.SH = gw.OH; gd.SW = gw.OW; gd.IC = 2 * Cin; gd.OC = Cin;
+    gd.M = (long)N * H * H;
+    const int stages = wgrad_stages(gw, 9), chunks = ceil_div(gw.M, 64L * stages);
+    *chunks_out = chunks;
+    if (Cin == 16) return launch_stride2<1, false>(s, dy, w, shortcut, dx, behind.mask, partial, chunks, stages, gd, gw, behind);
+    return launch_stride2<4, true>(s, dy, w, shortcut, dx, behind.mask, partial, chunks, stages, gd, gw, behind);
 }
 
 extern "C" size_t dsspk_conv_wgrad_scratch_floats(int N, int H, int W, int Cin, int Cout, int KH, int KW, int stride, int pad) {

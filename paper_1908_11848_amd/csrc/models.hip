@@ -306,6 +306,7 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
 }
 
 constexpr int LARGE_ABOVE = 96;
+constexpr int SMALL_RECORDS = 4096;         // records times channels that a workgroup of dsspk_conv3x3_small_* adds up
 // A record buffer holds 512 records of 16 channels, four an image.  A convolution of more images would write beyond it, and the one behind would
 // refuse so many.
 constexpr int RESNET_MAX = 128;
@@ -535,9 +536,20 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             tot0 = next_fused;
         } else {                        // first block of a stage: stride 2, shortcut without parameters
             RUN(dsspk_bn_bwd_dx(s, F(B.c1), w + B.g1, F(B.st1), g2, g1, g + B.g1, g + B.b1, bscr, M, B.cout, parts1));
-            RUN(filter_grad(xin, g1, g + B.w1, B.H, B.cin, B.cout, B.stride));
-            RUN(dsspk_conv_bwd_data_shortcut(s, g1, w + B.w1, g0, g2, m, B.H, B.H, B.cin, B.cout, 3, 3, 1));
-            parts0 = partsp;
+            // both gradients, with the ReLU and the sums of the block in front, in one kernel where the kernel behind adds up as many records itself
+            parts0 = small ? conv_stride2_bwd_records(m, B.H, B.cin) : 0;
+            if (parts0 > SMALL_RECORDS / B.cin) parts0 = 0;
+            if (parts0) {
+                const ResBlock& Pv = P->blocks[bi - 1];
+                if (pend.n == WG_SCRATCH - 1) RUN(flush());
+                float* to = free_scr();
+                int chunks = 0;
+                RUN(conv_stride2_bwd((hipStream_t)s, g1, w + B.w1, g0, g2, to, BehindBn{xin, F(Pv.c2), F(Pv.st2), recB0}, m, B.H, B.cin, &chunks));
+                push_back(to, g + B.w1, 9 * B.cin * B.cout, chunks);
+            } else {
+                RUN(filter_grad(xin, g1, g + B.w1, B.H, B.cin, B.cout, B.stride));
+                RUN(dsspk_conv_bwd_data_shortcut(s, g1, w + B.w1, g0, g2, m, B.H, B.H, B.cin, B.cout, 3, 3, 1));
+            }
             tot0 = false;
             float* t = g0; g0 = g2; g2 = t;
         }

@@ -27,5 +27,6 @@ static inline int stream_grid(long items_per_block_total, int cap = 256 * 8) {
 // once per XCD that touches them: 1.1x to 1.7x the operands' bytes).  Needs n to be a multiple of 8.
 __device__ __forceinline__ int xcd_tile(int block, int n_blocks) {
     constexpr int XCDS = 8;
-    return n_blocks % XCDS ? block : (block % XCDS) * (n_blocks / XCDS) + block / XCDS;
+    const int xcd = block % XCDS;
+    return xcd * (n_blocks / XCDS) + min(xcd, n_blocks % XCDS) + block / XCDS;
 }

@@ -587,31 +587,38 @@ int launch_conv(hipStream_t s, const float* src, const uint4* wf, const float* b
 // Measured with the reduction at batch 37 / 128 / 512: 23 / 50 / 143 us (four wavefronts, reads behind the barrier: 1 / 2 / 13 us more).
 // Output: partial[chunk][KS KS IC OC (+ OC bias sums, added up by the workgroups of filter row 0 and the first channels)].
 constexpr int WG_PX = 64, WG_XPX = 96, CTHREADS = 512;
-constexpr int XPITCH = 32 * 6 + 32, DPITCH = 64 * 6 + 32;      // 24 and 8 words (mod 32): four rows cover all banks once
+constexpr int XPITCH = 32 * 6 + 32, DPITCH = 64 * 6 + 32;      // 24 and 8 words (mod 32): four rows cover half the banks once ...
+__device__ __forceinline__ int row_half(int px) { return (px >> 3 & 1) * 128; }        // ... and the four rows eight further down the other half
 
 template <int KS>
 __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void wgrad_split_kernel(const float* __restrict__ x, const float* __restrict__ dy,
                                                               float* __restrict__ partial, Geom g, int items_per_chunk, int with_bias) {
     constexpr int NX = (WG_XPX * 8 + CTHREADS - 1) / CTHREADS, ND = WG_PX * 16 / CTHREADS;      // 16-byte loads per thread and tile
     static_assert(WG_PX == 64 && WG_PX * 16 % CTHREADS == 0, "one run of 32 pixels per wavefront");
-    constexpr int XBYTES = WG_XPX * XPITCH, BUF = XBYTES + WG_PX * DPITCH;
+    constexpr int XBYTES = WG_XPX * XPITCH + 128, BUF = XBYTES + WG_PX * DPITCH + 128;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q = lane >> 4, run = wave >> 2;
     const int ci_w = 16 * (wave & 1), co_w = 32 * (wave >> 1 & 1);         // this wavefront's first channels within the workgroup's
-    const int kh = blockIdx.y % KS, ci0 = blockIdx.y / KS * 32, co0 = blockIdx.z * 64;
+    const int roles = gridDim.y * gridDim.z, tile = xcd_tile(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x * roles);
+    const int chunk = tile / roles, role = tile % roles, role_y = role % gridDim.y;
+    const int kh = role_y % KS, ci0 = role_y / KS * 32, co0 = role / gridDim.y * 64;
     const int TW = g.OW + KS - 1, P = g.R * g.OW;
-    const int items = g.N * g.bands, i0 = blockIdx.x * items_per_chunk, i1 = min(items, i0 + items_per_chunk);
-    const bool bias_role = with_bias && blockIdx.y == 0;
+    const int items = g.N * g.bands, i0 = chunk * items_per_chunk, i1 = min(items, i0 + items_per_chunk);
+    const bool bias_role = with_bias && role_y == 0;
 
     // transposing reads: this lane names row 8 q + l16 / 4 (and the one four further) of its run of 32 pixels
-    int xa[2], da[2];
+    int xa[KS][2], da[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int p = 32 * run + 8 * q + 4 * h + (l16 >> 2);
         const int r = p / g.OW, c = p - r * g.OW;
-        xa[h] = (p < P ? (r * TW + c) * XPITCH : 0) + 8 * (l16 & 3) + 2 * ci_w;      // beyond P dy is zero
-        da[h] = p * DPITCH + 8 * (l16 & 3) + 2 * co_w;
+#pragma unroll
+        for (int kw = 0; kw < KS; ++kw) {
+            const int px = (p < P ? r * TW + c : 0) + kw;                                       // beyond P dy is zero
+            xa[kw][h] = px * XPITCH + row_half(px) + 8 * (l16 & 3) + 2 * ci_w;
+        }
+        da[h] = p * DPITCH + row_half(p) + 8 * (l16 & 3) + 2 * co_w;
     }
     floatx4 acc[KS][2][1], small[KS][2][1];
 #pragma unroll
@@ -662,7 +669,7 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         split::split4(split::scaled(v), pl);
         const int idx = tid + (e < NX ? e : e - NX) * CTHREADS;
         if (e < NX && idx >= WG_XPX * 8) return;
-        char* to = e < NX ? buf + (idx >> 3) * XPITCH + 8 * (idx & 7) : buf + XBYTES + (idx >> 4) * DPITCH + 8 * (idx & 15);
+        char* to = e < NX ? buf + (idx >> 3) * XPITCH + row_half(idx >> 3) + 8 * (idx & 7) : buf + XBYTES + (idx >> 4) * DPITCH + row_half(idx >> 4) + 8 * (idx & 15);
 #pragma unroll
         for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(to + p * (e < NX ? 64 : 128)) = pl[p];
     };
@@ -671,7 +678,7 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
         for (int i = 0; i < 2; ++i) split::transposed_operand<128>(to[i], buf + XBYTES + da[0] + 32 * i, buf + XBYTES + da[1] + 32 * i);
     };
-    auto load_x = [&](uint4 (&to)[1][split::PLANES], int kw, const char* buf) { split::transposed_operand<64>(to[0], buf + xa[0] + kw * XPITCH, buf + xa[1] + kw * XPITCH); };
+    auto load_x = [&](uint4 (&to)[1][split::PLANES], int kw, const char* buf) { split::transposed_operand<64>(to[0], buf + xa[kw][0], buf + xa[kw][1]); };
     if (i0 < i1) {
         image();
 #pragma unroll
@@ -756,7 +763,7 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         for (int kw = 0; kw < KS; ++kw) { acc[kw][0][0] *= split::UNSCALE; acc[kw][1][0] *= split::UNSCALE; }
     }
     const long E = (long)KS * KS * g.IC * g.OC;
-    float* outp = partial + blockIdx.x * (E + (with_bias ? g.OC : 0));
+    float* outp = partial + chunk * (E + (with_bias ? g.OC : 0));
     // the sums over the other run: this wavefront finishes its output channel tile `run` and gives the other one away
     static_assert(8 * KS * 1024 <= 2 * BUF, "room for the exchange");
     __syncthreads();
@@ -785,7 +792,7 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 
 template <int KS>
 int launch_wgrad(hipStream_t s, dim3 grid, const float* x, const float* dy, float* partial, const Geom& g, int items_per_chunk, int with_bias) {
-    constexpr int bytes = 2 * (WG_XPX * XPITCH + WG_PX * DPITCH);
+    constexpr int bytes = 2 * (WG_XPX * XPITCH + WG_PX * DPITCH + 256);
     auto kern = wgrad_split_kernel<KS>;
     static bool attr_set = false;
     if (!attr_set) {

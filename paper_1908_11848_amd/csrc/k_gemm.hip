@@ -181,7 +181,7 @@ inline int tile_shape(int M, int N) {
     if ((long)ceil_div(M, 64) * ceil_div(N, 64) >= 128) return BIG;
     return (long)ceil_div(M, 32) * ceil_div(N, 32) >= 128 ? MID : SMALL;
 }
-inline int tile_edge(int shape) { return shape == BIG ? 64 : shape == MID ? 32 : 16; }
+__host__ __device__ constexpr int tile_edge(int shape) { return shape == BIG ? 64 : shape == MID ? 32 : 16; }
 
 // The small tile fetches two k-chunks at a time.  With 1 / 2 / 3 / 4 / 6 of them, us: perceptron, batch 32, one worker 37.8 / 37.8 / 38.0 / 38.2 / 42.2; a push of the
 // AlexNet-style network, batch 128, one worker 207.2 / 206.2 / 206.8 / 208.5 / 217.9, three convolutions, batch 37, 157.3 / 157.8 / 157.9 / 158.9 / 166.1.
@@ -199,11 +199,16 @@ inline size_t tile_lds(int shape, int threads) {
     return kw > 1 ? sizeof(float) * waves * (shape == SMALL ? 256 : 1024) : 0;
 }
 
+// Arguments of the kernels from here on: pointers and numbers in front, which are in registers when a wavefront starts, and operands put together from them.  As
+// structs they were a load from memory that every other one waited for: perceptron, batch 1, one worker 33.4 -> 31.4 us a push, batch 32 37.7 -> 36.0, AlexNet-style,
+// batch 128, 207.8 -> 205.6.
 // Layer z of the grid takes the reduction indices [z * k_per_layer, (z + 1) * k_per_layer) and writes its product to the
 // z-th [M][N] slab of C (split-K with a second kernel; one layer otherwise).
 template <int SHAPE, bool AV, bool BV>
-__global__ __launch_bounds__(1024) void gemm_kernel(Operand a, Operand b, Epilogue e, int M, int N, int K, int k_per_layer) {
+__global__ __launch_bounds__(1024) void gemm_kernel(const float* __restrict__ a_p, const float* __restrict__ b_p, int M, int N, int K, int k_per_layer, long a_s,
+                                                    long b_ks, long b_s, long a_ks, Epilogue e) {      // (numbers in front: they are there when a wavefront starts)
     extern __shared__ float lds[];
+    Operand a{a_p, a_s, AV ? 1 : a_ks}, b{b_p, b_s, BV ? 1 : b_ks};
     const int k_lo = blockIdx.z * k_per_layer;
     a.p += (long)k_lo * a.ks; b.p += (long)k_lo * b.ks;
     e.C += (long)blockIdx.z * M * N;
@@ -333,7 +338,7 @@ int launch_gemm(hipStream_t s, const Operand& a, const Operand& b, const Epilogu
     const dim3 grid(ceil_div(N, edge), ceil_div(M, edge), ceil_div(K, k_per_layer));
     const bool av = vector_k(a, K), bv = vector_k(b, K);
     const size_t lds = tile_lds(shape, threads);
-#define GO(S, AV, BV) hipLaunchKernelGGL((gemm_kernel<S, AV, BV>), grid, dim3(threads), lds, s, a, b, e, M, N, K, k_per_layer)
+#define GO(S, AV, BV) hipLaunchKernelGGL((gemm_kernel<S, AV, BV>), grid, dim3(threads), lds, s, a.p, b.p, M, N, K, k_per_layer, a.s, b.ks, b.s, a.ks, e)
 #define GO_V(S) do { if (av && bv) GO(S, true, true); else if (av) GO(S, true, false); else if (bv) GO(S, false, true); else GO(S, false, false); } while (0)
     if (shape == BIG) GO_V(BIG); else if (shape == MID) GO_V(MID); else GO_V(SMALL);
 #undef GO_V
@@ -346,45 +351,44 @@ int launch_gemm(hipStream_t s, const Operand& a, const Operand& b, const Epilogu
 // products do not depend on each other, so their tiles are workgroups of one grid; as kernels of their own (with the bias
 // sums and the ReLU mask two more) each of them cost a dependent launch of 4 to 6 us.
 struct FcBwd {
-    Operand xt, dy_n;           // dW = xt * dy_n
-    Operand dy_k, wt;           // dx = dy_k * wt
-    Epilogue edw, edx;
-    const float* dy; float* db;
+    float *dw, *db, *dx;
+    int mask_dx;
     const float* row_loss; float* loss;
-    int m, n_in, n_out;
-    int tiles_n_w, tiles_n_x;   // output tiles side by side
-    int blocks_w, blocks_x, blocks_b;
+    int blocks_b;
 };
 
 constexpr int FC_THREADS = 256;
 
 template <int SHW, int SHX, bool V>
-__global__ __launch_bounds__(FC_THREADS) void fc_bwd_kernel(FcBwd f) {
+__global__ __launch_bounds__(FC_THREADS) void fc_bwd_kernel(const float* __restrict__ x, const float* __restrict__ dy, const float* __restrict__ w, int m, int n_in,
+                                                            int n_out, int blocks_x, int blocks_w, FcBwd f) {
     extern __shared__ float lds[];
     int b = blockIdx.x;
-    if (b < f.blocks_x) {
-        shaped_tile<SHX, V, V>(f.dy_k, f.wt, f.m, f.n_in, f.n_out, b / f.tiles_n_x, b % f.tiles_n_x, f.edx, lds);
+    if (b < blocks_x) {         // dx = dy W^T
+        const int side = (n_in + tile_edge(SHX) - 1) / tile_edge(SHX);      // output tiles side by side
+        shaped_tile<SHX, V, V>(Operand{dy, n_out, 1}, Operand{w, n_out, 1}, m, n_in, n_out, b / side, b % side, Epilogue{f.dx, n_in, nullptr, 0, f.mask_dx ? x : nullptr}, lds);
         return;
     }
-    b -= f.blocks_x;
-    if (b < f.blocks_w) {
-        shaped_tile<SHW, false, false>(f.xt, f.dy_n, f.n_in, f.n_out, f.m, b / f.tiles_n_w, b % f.tiles_n_w, f.edw, lds);
+    b -= blocks_x;
+    if (b < blocks_w) {         // dW = x^T dy
+        const int side = (n_out + tile_edge(SHW) - 1) / tile_edge(SHW);
+        shaped_tile<SHW, false, false>(Operand{x, 1, n_in}, Operand{dy, 1, n_out}, n_in, n_out, m, b / side, b % side, Epilogue{f.dw, n_out, nullptr, 0, nullptr}, lds);
         return;
     }
-    b -= f.blocks_w;
+    b -= blocks_w;
     if (b < f.blocks_b) {
-        colsum_block(f.dy, f.db, 0, f.m, f.n_out, b, lds);
+        colsum_block(dy, f.db, 0, m, n_out, b, lds);
         return;
     }
     float s = 0.f;              // mean loss: a lane adds its samples in order, lanes by a tree
-    for (int i = threadIdx.x; i < f.m; i += FC_THREADS) s += f.row_loss[i];
+    for (int i = threadIdx.x; i < m; i += FC_THREADS) s += f.row_loss[i];
     lds[threadIdx.x] = s;
     __syncthreads();
     for (int h = FC_THREADS / 2; h >= 1; h >>= 1) {
         if ((int)threadIdx.x < h) lds[threadIdx.x] += lds[threadIdx.x + h];
         __syncthreads();
     }
-    if (threadIdx.x == 0) *f.loss = lds[0] / (float)f.m;
+    if (threadIdx.x == 0) *f.loss = lds[0] / (float)m;
 }
 
 // Last layer and loss in one kernel: logits z = x W + b for 16 samples per workgroup (every class, at most 128), then the
@@ -392,10 +396,10 @@ __global__ __launch_bounds__(FC_THREADS) void fc_bwd_kernel(FcBwd f) {
 // Eight wavefronts: class tiles side by side, the rest of them split the inputs.
 constexpr int SX_WAVES = 8, SX_MAX_C = 128;
 template <bool AV>
-__global__ __launch_bounds__(64 * SX_WAVES) void fc_softmax_kernel(Operand x, Operand w, const float* __restrict__ bias,
-                                                                   const int32_t* __restrict__ label, float* __restrict__ z,
-                                                                   float* __restrict__ dz, float* __restrict__ row_loss, int m,
-                                                                   int n_in, int C) {
+__global__ __launch_bounds__(64 * SX_WAVES) void fc_softmax_kernel(const float* __restrict__ x_p, const float* __restrict__ w_p, int m, int n_in, int C,
+                                                                   const float* __restrict__ bias, const int32_t* __restrict__ label,
+                                                                   float* __restrict__ z, float* __restrict__ dz, float* __restrict__ row_loss) {
+    const Operand x{x_p, n_in, 1}, w{w_p, 1, C};
     __shared__ float part[SX_WAVES][16][17];
     __shared__ float Z[16][SX_MAX_C + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -475,24 +479,16 @@ extern "C" int dsspk_gemm_splitk(void* stream, const float* A, long a_rs, long a
 extern "C" int dsspk_fc_bwd(void* stream, const float* x, const float* dy, const float* w, float* dw, float* db, float* dx, int mask_dx,
                             const float* row_loss, float* loss, int m, int n_in, int n_out) {
     if (!x || !dy || !dw || !db || (dx && !w) || (loss && !row_loss) || m < 1 || n_in < 1 || n_out < 1) return -1;
-    FcBwd f;
-    f.xt = Operand{x, 1, n_in}; f.dy_n = Operand{dy, 1, n_out};
-    f.dy_k = Operand{dy, n_out, 1}; f.wt = Operand{w, n_out, 1};
-    f.edw = Epilogue{dw, n_out, nullptr, 0, nullptr};
-    f.edx = Epilogue{dx, n_in, nullptr, 0, mask_dx ? x : nullptr};
-    f.dy = dy; f.db = db; f.row_loss = row_loss; f.loss = loss; f.m = m; f.n_in = n_in; f.n_out = n_out;
     const int shw = tile_shape(n_in, n_out), shx = tile_shape(m, n_in), ew = tile_edge(shw), ex = tile_edge(shx);
-    f.tiles_n_w = ceil_div(n_out, ew); f.tiles_n_x = ceil_div(n_in, ex);
-    f.blocks_w = f.tiles_n_w * ceil_div(n_in, ew);
-    f.blocks_x = dx ? f.tiles_n_x * ceil_div(m, ex) : 0;
-    f.blocks_b = ceil_div(n_out, 64);
-    const int grid = f.blocks_x + f.blocks_w + f.blocks_b + (loss ? 1 : 0);
-    const bool v = dx && vector_k(f.dy_k, n_out) && vector_k(f.wt, n_out);
+    const int blocks_w = ceil_div(n_out, ew) * ceil_div(n_in, ew), blocks_x = dx ? ceil_div(n_in, ex) * ceil_div(m, ex) : 0;
+    const FcBwd f = {dw, db, dx, mask_dx, row_loss, loss, ceil_div(n_out, 64)};
+    const int grid = blocks_x + blocks_w + f.blocks_b + (loss ? 1 : 0);
+    const bool v = dx && vector_k(Operand{dy, n_out, 1}, n_out) && vector_k(Operand{w, n_out, 1}, n_out);
     size_t lds = tile_lds(shw, FC_THREADS), ldx = tile_lds(shx, FC_THREADS);
     if (lds < ldx) lds = ldx;
     if (lds < sizeof(float) * FC_THREADS) lds = sizeof(float) * FC_THREADS;
-#define GO(W, X) do { if (v) hipLaunchKernelGGL((fc_bwd_kernel<W, X, true>), dim3(grid), dim3(FC_THREADS), lds, (hipStream_t)stream, f); \
-                      else hipLaunchKernelGGL((fc_bwd_kernel<W, X, false>), dim3(grid), dim3(FC_THREADS), lds, (hipStream_t)stream, f); } while (0)
+#define GO(W, X) do { if (v) hipLaunchKernelGGL((fc_bwd_kernel<W, X, true>), dim3(grid), dim3(FC_THREADS), lds, (hipStream_t)stream, x, dy, w, m, n_in, n_out, blocks_x, blocks_w, f); \
+                      else hipLaunchKernelGGL((fc_bwd_kernel<W, X, false>), dim3(grid), dim3(FC_THREADS), lds, (hipStream_t)stream, x, dy, w, m, n_in, n_out, blocks_x, blocks_w, f); } while (0)
 #define GO_X(W) do { if (shx == BIG) GO(W, BIG); else if (shx == MID) GO(W, MID); else GO(W, SMALL); } while (0)
     if (shw == BIG) GO_X(BIG); else if (shw == MID) GO_X(MID); else GO_X(SMALL);
 #undef GO_X
@@ -503,12 +499,12 @@ extern "C" int dsspk_fc_bwd(void* stream, const float* x, const float* dy, const
 extern "C" int dsspk_fc_softmax_xent(void* stream, const float* x, const float* w, const float* bias, const int32_t* y, float* z,
                                      float* dz, float* row_loss, int m, int n_in, int C) {
     if (!x || !w || !bias || !y || !z || !dz || !row_loss || m < 1 || n_in < 1 || C < 1 || C > SX_MAX_C) return -1;
-    const Operand a{x, n_in, 1}, b{w, 1, C};
+    const Operand a{x, n_in, 1};
     const dim3 grid(ceil_div(m, 16)), threads(64 * SX_WAVES);
     if (vector_k(a, n_in))
-        hipLaunchKernelGGL((fc_softmax_kernel<true>), grid, threads, 0, (hipStream_t)stream, a, b, bias, y, z, dz, row_loss, m, n_in, C);
+        hipLaunchKernelGGL((fc_softmax_kernel<true>), grid, threads, 0, (hipStream_t)stream, x, w, m, n_in, C, bias, y, z, dz, row_loss);
     else
-        hipLaunchKernelGGL((fc_softmax_kernel<false>), grid, threads, 0, (hipStream_t)stream, a, b, bias, y, z, dz, row_loss, m, n_in, C);
+        hipLaunchKernelGGL((fc_softmax_kernel<false>), grid, threads, 0, (hipStream_t)stream, x, w, m, n_in, C, bias, y, z, dz, row_loss);
     return DSSPK_LAUNCH_RC();
 }
 

@@ -588,14 +588,14 @@ int launch_conv(hipStream_t s, const float* src, const uint4* wf, const float* b
 // Output: partial[chunk][KS KS IC OC (+ OC bias sums, added up by the workgroups of filter row 0 and the first channels)].
 constexpr int WG_PX = 64, WG_XPX = 96, CTHREADS = 512;
 constexpr int XPITCH = 32 * 6 + 32, DPITCH = 64 * 6 + 32;      // 24 and 8 words (mod 32): four rows cover half the banks once ...
-__device__ __forceinline__ int row_half(int px) { return (px >> 3 & 1) * 128; }        // ... and the four rows eight further down the other half
+constexpr __host__ __device__ int row_skew(int px) { return (px >> 3) * 128; }         // ... and the four rows eight further down the other half
 
 template <int KS>
 __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void wgrad_split_kernel(const float* __restrict__ x, const float* __restrict__ dy,
                                                               float* __restrict__ partial, Geom g, int items_per_chunk, int with_bias) {
     constexpr int NX = (WG_XPX * 8 + CTHREADS - 1) / CTHREADS, ND = WG_PX * 16 / CTHREADS;      // 16-byte loads per thread and tile
     static_assert(WG_PX == 64 && WG_PX * 16 % CTHREADS == 0, "one run of 32 pixels per wavefront");
-    constexpr int XBYTES = WG_XPX * XPITCH + 128, BUF = XBYTES + WG_PX * DPITCH + 128;
+    constexpr int XBYTES = WG_XPX * XPITCH + row_skew(WG_XPX), BUF = XBYTES + WG_PX * DPITCH + row_skew(WG_PX);
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q = lane >> 4, run = wave >> 2;
@@ -616,9 +616,9 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
         for (int kw = 0; kw < KS; ++kw) {
             const int px = (p < P ? r * TW + c : 0) + kw;                                       // beyond P dy is zero
-            xa[kw][h] = px * XPITCH + row_half(px) + 8 * (l16 & 3) + 2 * ci_w;
+            xa[kw][h] = px * XPITCH + row_skew(px) + 8 * (l16 & 3) + 2 * ci_w;
         }
-        da[h] = p * DPITCH + row_half(p) + 8 * (l16 & 3) + 2 * co_w;
+        da[h] = p * DPITCH + row_skew(p) + 8 * (l16 & 3) + 2 * co_w;
     }
     floatx4 acc[KS][2][1], small[KS][2][1];
 #pragma unroll
@@ -669,7 +669,7 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         split::split4(split::scaled(v), pl);
         const int idx = tid + (e < NX ? e : e - NX) * CTHREADS;
         if (e < NX && idx >= WG_XPX * 8) return;
-        char* to = e < NX ? buf + (idx >> 3) * XPITCH + row_half(idx >> 3) + 8 * (idx & 7) : buf + XBYTES + (idx >> 4) * DPITCH + row_half(idx >> 4) + 8 * (idx & 15);
+        char* to = e < NX ? buf + (idx >> 3) * XPITCH + row_skew(idx >> 3) + 8 * (idx & 7) : buf + XBYTES + (idx >> 4) * DPITCH + row_skew(idx >> 4) + 8 * (idx & 15);
 #pragma unroll
         for (int p = 0; p < split::PLANES; ++p) *reinterpret_cast<uint2*>(to + p * (e < NX ? 64 : 128)) = pl[p];
     };
@@ -792,7 +792,7 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 
 template <int KS>
 int launch_wgrad(hipStream_t s, dim3 grid, const float* x, const float* dy, float* partial, const Geom& g, int items_per_chunk, int with_bias) {
-    constexpr int bytes = 2 * (WG_XPX * XPITCH + WG_PX * DPITCH + 256);
+    constexpr int bytes = 2 * (WG_XPX * XPITCH + row_skew(WG_XPX) + WG_PX * DPITCH + row_skew(WG_PX));
     auto kern = wgrad_split_kernel<KS>;
     static bool attr_set = false;
     if (!attr_set) {

@@ -24,7 +24,7 @@ static inline int stream_grid(long items_per_block_total, int cap = 256 * 8) {
 // tile between the channel splits of a band, dy between the input-channel slices of the last stage's d-filter
 // kernel - so consecutive tiles go to ONE XCD: workgroup b takes tile (b mod 8) * (n / 8) + b / 8, and what the
 // first of them fetched is in that L2 for the next (without this, halo rows and shared tiles come over the fabric
-// once per XCD that touches them: 1.1x to 1.7x the operands' bytes).  Needs n to be a multiple of 8.
+// once per XCD that touches them: 1.1x to 1.7x the operands' bytes).  Where n is no multiple of 8, the first n mod 8 XCDs take a tile more.
 __device__ __forceinline__ int xcd_tile(int block, int n_blocks) {
     constexpr int XCDS = 8;
     const int xcd = block % XCDS;

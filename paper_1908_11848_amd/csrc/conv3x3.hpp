@@ -12,7 +12,7 @@
 // eight, 22 to 42 KB with two pixel tiles (the last stage's d-filter beside its d-input: 57).  Registers are at most 128 with eight wavefronts, and
 // what fits a compute unit of LDS and registers overlaps: one workgroup's transfers run beside another's products.
 //
-// What bounds them (110 layers, batch 128, four streams, 1.82 ms a push): registers and LDS admit 16 wavefronts to a compute unit and each
+// What bounds them (110 layers, batch 128, four streams, measured where a push took 1.82 ms): registers and LDS admit 16 wavefronts to a compute unit and each
 // fetches, multiplies and stores one after the other.  Without the products a push takes 1.27 ms (its bytes at copy rate: 1.0), without
 // the fused d-filter 1.60, without the epilogue's loads 1.74.  Therefore: no spilled register (with one to 17 of them per kernel
 // 1.86 ms), addresses as 32-bit offsets from a uniform base, and nothing held across the product loop that the thread index gives.

@@ -10,8 +10,8 @@ struct HeadArgs {
     const int32_t* label;
     float *pooled, *logits, *dlogits, *row_loss;
     float *dz, *records_out;                   // masked gradient in front of the last ReLU, its sum records [N][64][2]
-    float eps, rows_per_record, inv_n;
-    int classes;
+    float eps, inv_n;
+    int rows_per_record, classes;
 };
 
 // Records of the input that every workgroup merges, classes a workgroup holds.

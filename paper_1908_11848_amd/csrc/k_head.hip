@@ -11,7 +11,7 @@
 namespace {
 
 constexpr int HEAD_THREADS = 256, HEAD_WAVES = 4, HEAD_C = 64, HEAD_SIDE = 8, HEAD_PX = HEAD_SIDE * HEAD_SIDE;
-constexpr int HEAD_RECORDS = HEAD_MAX_PARTS * HEAD_C / HEAD_THREADS;
+static_assert(HEAD_THREADS == bnm::THREADS && HEAD_MAX_PARTS * HEAD_C == 32 * HEAD_THREADS, "the records a thread merges");
 constexpr int HEAD_V = HEAD_C / 4, HEAD_ROWS = HEAD_THREADS / HEAD_V, HEAD_PER = HEAD_PX / HEAD_ROWS;    // a thread: 4 channels of every HEAD_ROWS-th pixel
 
 // Sum over the pixels of the workgroup's image, in all threads of the four channels; red: HEAD_WAVES * HEAD_C floats.
@@ -37,8 +37,7 @@ __global__ __launch_bounds__(HEAD_THREADS) void head_kernel(const float* __restr
     __shared__ float Z[2][HEAD_MAX_CLASSES], dlog[HEAD_MAX_CLASSES];
     const int tid = threadIdx.x, lane = tid & 63, vc = tid % HEAD_V, row = tid / HEAD_V, classes = a.classes;
     const long image_at = (long)blockIdx.x * HEAD_PX * C;
-    float2 rec[HEAD_RECORDS];
-    load_records<C, HEAD_THREADS>(rec, records, parts, tid);
+    const bnm::Records rec(records, C, parts);
     const float4 ga = *reinterpret_cast<const float4*>(gamma + 4 * vc), be = *reinterpret_cast<const float4*>(gamma + C + 4 * vc);
     const split::Buffer beside = split::buffer(shortcut + (half ? 2 : 1) * image_at, (half ? 8u : 4u) * HEAD_PX * C);
     float4 v[HEAD_PER], sc[HEAD_PER];
@@ -58,19 +57,12 @@ __global__ __launch_bounds__(HEAD_THREADS) void head_kernel(const float* __restr
     const int y = a.label[blockIdx.x];
     const float bias = tid < classes ? w[C * classes + tid] : 0.f;
 
-    const float nn = a.rows_per_record;
-    float2* shares = reinterpret_cast<float2*>(W);
-    const float2 share = merge_lanes<C, HEAD_THREADS>(rec, parts, nn, tid);
-    shares[tid / 64 * C + lane] = share;
-    __syncthreads();
-    if (tid < C) {
-        const float2 all = merge_waves<C, HEAD_WAVES, HEAD_RECORDS>(shares, parts, nn, tid);
-        const float invstd = 1.0f / sqrtf(all.y / (nn * (float)parts) + a.eps);
-        norm[tid] = all.x;
-        norm[C + tid] = invstd;
-        if (blockIdx.x == 0) { a.stats[tid] = all.x; a.stats[C + tid] = invstd; }
-    }
-    __syncthreads();
+    // (merged as dsspk_bn_fwd_gap does, to the same bits)
+    bnm::BnLayout L = {};
+    L.G = parts;
+    L.rows_per_block = a.rows_per_record;
+    bnm::bn_merge_stats(rec, (long)parts * a.rows_per_record, C, a.eps, red[0], norm, L);
+    if (blockIdx.x == 0 && tid < 2 * C) a.stats[tid] = norm[tid];
 #pragma unroll
     for (int u = 0; u < WV; ++u)
         if (4 * (tid + u * HEAD_THREADS) < C * classes) *reinterpret_cast<float4*>(W + 4 * (tid + u * HEAD_THREADS)) = wv[u];

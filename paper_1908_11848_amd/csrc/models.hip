@@ -65,7 +65,7 @@ struct Plan {
     int64_t stem_w = 0, stem_g = 0, stem_b = 0, fc_w = 0, fc_b = 0;
     size_t filters = 0;
     FilterRun filter_runs[3] = {};
-    size_t stem_c = 0, stem_a = 0, stem_st = 0, pooled = 0, dpooled = 0, head_records = 0, G[3] = {0, 0, 0};
+    size_t stem_c = 0, stem_a = 0, stem_st = 0, pooled = 0, dpooled = 0, G[3] = {0, 0, 0};
 
     void seg(int kind, int64_t size, int64_t fan_in) { segs.push_back({kind, size, fan_in}); n_params += size; }
     int64_t conv_seg(int k, int cin, int cout, bool bias) {
@@ -175,7 +175,6 @@ struct Plan {
                 }
             fc_w = fc_seg(64, classes); fc_b = fc_w + 64 * (int64_t)classes;
             pooled = a.floats((size_t)m * 64); dpooled = a.floats((size_t)m * 64);
-            head_records = a.floats((size_t)m * 128);
             for (int i = 0; i < 3; ++i) G[i] = a.floats(s0);
             // A stage's filters of stride-1 convolutions are evenly spaced in the parameters: all of the first stage's, from the second
             // convolution on in the others.
@@ -401,8 +400,8 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         }
         pending = parts2 > 0 && bi + 1 < nb && regular(bi + 1);
         if (bi + 1 == nb && head) {
-            const HeadArgs end = {F(B.out), F(B.st2), y, F(P->pooled), F(P->logits), F(P->dlogits), F(P->row_loss), g0, F(P->head_records),
-                                  eps, (float)(M / parts2), 1.f / (float)m, P->n_classes};
+            const HeadArgs end = {F(B.out), F(B.st2), y, F(P->pooled), F(P->logits), F(P->dlogits), F(P->row_loss), g0, recA,
+                                  eps, 1.f / (float)m, (int)(M / parts2), P->n_classes};
             RUN(resnet_head((hipStream_t)s, F(B.c2), recB, parts2, w + B.g2, cur, mode == 2, w + P->fc_w, m, end));
         } else if (bi + 1 == nb) {
             RUN(dsspk_bn_fwd_gap(s, F(B.c2), w + B.g2, w + B.b2, F(B.out), F(B.st2), recB, parts2, cur, mode == 2, F(P->pooled), m, Ho, B.cout, eps));
@@ -430,7 +429,8 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
     //   parts0 > 0 : g0 holds the masked dz of this block's BN2 and recB0 its records
     //   tot0       : their sums are in totB already (and dgamma / dbeta of BN2 stored), or the kernel behind adds them up
     //   pend       : d-filter partial sums whose reduction has not been launched yet, the oldest first
-    float *recB0 = F(P->bn_scratch2), *totA = F(P->tot_a), *totB = F(P->tot_b);
+    // (the head reads its input's records from the one record buffer and leaves its own in the other: the two change places)
+    float *recB0 = head ? recA : recB, *recA0 = head ? recB : recA, *totA = F(P->tot_a), *totB = F(P->tot_b);
     float* scrs[WG_SCRATCH] = {F(P->wg_scratch)};
     for (int i = 1; i < WG_SCRATCH; ++i) scrs[i] = F(P->wg_more[i - 1]);
     int parts0 = 0;
@@ -508,7 +508,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
         const bool identity = B.stride == 1 && B.cin == B.cout;
         const int partsp = identity ? parts_of(B.H, B.cin, B.cout, 1) : 0;
         const bool fused1 = parts1 > 0 && partsp > 0;        // conv1's layer takes the two-launch form
-        // ---- BN2 + conv2: g0 = dz2 -> g1 = d conv2 output, g2 = dz1 = d a1 * [a1 > 0] (+ BN1's records in bscr)
+        // ---- BN2 + conv2: g0 = dz2 -> g1 = d conv2 output, g2 = dz1 = d a1 * [a1 > 0] (+ BN1's records in recA0)
         if (bi + 1 == nb && head) {
             parts0 = m;
         } else if (bi + 1 == nb) {      // from the pooled gradient
@@ -519,7 +519,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             parts0 = parts1;
             tot0 = false;
         }
-        RUN(regular_layer(bi + 1 == nb && head ? F(P->head_records) : recB0, parts0, g + B.g2, g + B.b2, tot0, g0, F(B.c2), F(B.st2), w + B.g2, totB, input_filter(B.w2, B.f2, B.cout), nullptr, g2, F(B.a1), F(B.c1), F(B.st1), bscr,
+        RUN(regular_layer(recB0, parts0, g + B.g2, g + B.b2, tot0, g0, F(B.c2), F(B.st2), w + B.g2, totB, input_filter(B.w2, B.f2, B.cout), nullptr, g2, F(B.a1), F(B.c1), F(B.st1), recA0,
                           g + B.w2, Ho, B.cout, fused1, parts1, totA, g + B.g1, g + B.b1, w + B.g1, w + B.b1));        // sums of BN1's records to totA if fused1
         // ---- BN1 + conv1: g2 = dz1 -> g1 = d conv1 output; d-input (+ dz2 through an identity shortcut) = gradient
         //      w.r.t. the block's input, which is the previous block's (or the stem's) post-ReLU output: mask +
@@ -529,13 +529,13 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             const float* pst = bi ? F(P->blocks[bi - 1].st2) : F(P->stem_st);
             // output in place over the shortcut's gradient g0; g0 stays the gradient w.r.t. the previous block's output
             const bool next_fused = bi > 0;                  // the previous block's conv2 has this convolution's shape
-            RUN(regular_layer(bscr, parts1, g + B.g1, g + B.b1, true, g2, F(B.c1), F(B.st1), w + B.g1, totA, input_filter(B.w1, B.f1, B.cout), g0, g0, xin, pc, pst, recB0, g + B.w1, B.H, B.cin,
+            RUN(regular_layer(recA0, parts1, g + B.g1, g + B.b1, true, g2, F(B.c1), F(B.st1), w + B.g1, totA, input_filter(B.w1, B.f1, B.cout), g0, g0, xin, pc, pst, recB0, g + B.w1, B.H, B.cin,
                               next_fused, partsp, totB, next_fused ? g + P->blocks[bi - 1].g2 : nullptr,
                               next_fused ? g + P->blocks[bi - 1].b2 : nullptr));
             parts0 = partsp;
             tot0 = next_fused;
         } else {                        // first block of a stage: stride 2, shortcut without parameters
-            RUN(dsspk_bn_bwd_dx(s, F(B.c1), w + B.g1, F(B.st1), g2, g1, g + B.g1, g + B.b1, bscr, M, B.cout, parts1));
+            RUN(dsspk_bn_bwd_dx(s, F(B.c1), w + B.g1, F(B.st1), g2, g1, g + B.g1, g + B.b1, recA0, M, B.cout, parts1));
             // both gradients, with the ReLU and the sums of the block in front, in one kernel where the kernel behind adds up as many records itself
             parts0 = small ? conv_stride2_bwd_records(m, B.H, B.cin) : 0;
             if (parts0 > SMALL_RECORDS / B.cin) parts0 = 0;

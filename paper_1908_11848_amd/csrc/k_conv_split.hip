@@ -584,7 +584,8 @@ int launch_conv(hipStream_t s, const float* src, const uint4* wf, const float* b
 // LDS has the channels side by side: the transposing LDS reads turn them.  The next tile's loads are in flight while the
 // matrix cores work.  Wavefront w: input channels 16 (w mod 2) .., output channels 32 (w / 2 mod 2) .., the first or second 32
 // pixels of the tile (w / 4: two wavefronts to a SIMD, one multiplies while the other fetches); their sums meet in LDS at the end.
-// Measured with the reduction at batch 37 / 128 / 512: 23 / 50 / 143 us (four wavefronts, reads behind the barrier: 1 / 2 / 13 us more).
+// Measured with the reduction at batch 37 / 128 / 512: 22.4 / 42.5 / 137 us (four wavefronts, reads behind the barrier: 1 / 2 / 13 us more).  With the
+// workgroups of a chunk side by side on one XCD 8.8 instead of 46 MB are fetched at 128 and 35 instead of 183 at 512, and it takes 24.4 / 44.9 / 134.
 // Output: partial[chunk][KS KS IC OC (+ OC bias sums, added up by the workgroups of filter row 0 and the first channels)].
 constexpr int WG_PX = 64, WG_XPX = 96, CTHREADS = 512;
 constexpr int XPITCH = 32 * 6 + 32, DPITCH = 64 * 6 + 32;      // 24 and 8 words (mod 32): four rows cover all banks once
@@ -599,13 +600,10 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q = lane >> 4, run = wave >> 2;
     const int ci_w = 16 * (wave & 1), co_w = 32 * (wave >> 1 & 1);         // this wavefront's first channels within the workgroup's
-    // the workgroups that read the same pixels side by side on one XCD (over all eight: 366 MB fetched at batch 512; time within 0.6 % either way)
-    const int roles = gridDim.y * gridDim.z, tile = xcd_tile(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x * roles);
-    const int chunk = tile / roles, role = tile % roles, role_y = role % gridDim.y;
-    const int kh = role_y % KS, ci0 = role_y / KS * 32, co0 = role / gridDim.y * 64;
+    const int kh = blockIdx.y % KS, ci0 = blockIdx.y / KS * 32, co0 = blockIdx.z * 64;
     const int TW = g.OW + KS - 1, P = g.R * g.OW;
-    const int items = g.N * g.bands, i0 = chunk * items_per_chunk, i1 = min(items, i0 + items_per_chunk);
-    const bool bias_role = with_bias && role_y == 0;
+    const int items = g.N * g.bands, i0 = blockIdx.x * items_per_chunk, i1 = min(items, i0 + items_per_chunk);
+    const bool bias_role = with_bias && blockIdx.y == 0;
 
     // transposing reads: this lane names row 8 q + l16 / 4 (and the one four further) of its run of 32 pixels
     int xa[2], da[2];
@@ -759,7 +757,7 @@ __global__ __launch_bounds__(CTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         for (int kw = 0; kw < KS; ++kw) { acc[kw][0][0] *= split::UNSCALE; acc[kw][1][0] *= split::UNSCALE; }
     }
     const long E = (long)KS * KS * g.IC * g.OC;
-    float* outp = partial + chunk * (E + (with_bias ? g.OC : 0));
+    float* outp = partial + blockIdx.x * (E + (with_bias ? g.OC : 0));
     // the sums over the other run: this wavefront finishes its output channel tile `run` and gives the other one away
     static_assert(8 * KS * 1024 <= 2 * BUF, "room for the exchange");
     __syncthreads();

@@ -11,10 +11,13 @@ template <class F> int form_parts(int N, int H, int C) {
     return C == 16 && H == 32 ? N * (32 / F::R16) : C == 32 && H == 16 ? N * (16 / F::R32) : C == 64 && H == 8 ? N : 0;
 }
 
-template <class F> bool form_merges(int parts, int C) {
-    return parts >= 1 && parts <= (C == 16 ? inline_records<16, F::WAVES, F::TILES>() : C == 32 ? inline_records<32, F::WAVES, F::TILES>()
-                                                                                                  : inline_records<64, F::WAVES, F::TILES>());
+// Records that a workgroup adds up itself, at most.
+template <class F> int form_records(int C) {
+    return C == 16   ? inline_records<16, F::WAVES, F::TILES>()
+           : C == 32 ? inline_records<32, F::WAVES, F::TILES>()
+                     : inline_records<64, F::WAVES, F::TILES>();
 }
+template <class F> bool form_merges(int parts, int C) { return parts >= 1 && parts <= form_records<F>(C); }
 
 template <class F, int PRE>
 int form_launch(hipStream_t s, const float* src, const Filter3x3& w, float* dst, float* records_out, int N, int C, const PreBn& pre) {

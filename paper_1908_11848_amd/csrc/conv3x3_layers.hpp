@@ -58,3 +58,4 @@ int conv3x3_tiled_dgrad_bn_wgrad(hipStream_t s, const float* dz, const float* xc
                              const float* beta_post);
 CONV3X3_FORM_LAUNCHERS(large)
 CONV3X3_FORM_LAUNCHERS(small)
+int conv3x3_small_records(int C);            // records of a tensor of C channels that a small workgroup adds up, at most

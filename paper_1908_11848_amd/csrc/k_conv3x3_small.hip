@@ -13,3 +13,5 @@ struct Small { static constexpr int WAVES = 4, TILES = 2, R16 = 4, R32 = 4, SPLI
 }  // namespace
 
 DSSPK_CONV3X3_FORM(small, Small)
+
+int conv3x3_small_records(int C) { return form_records<Small>(C); }

@@ -305,7 +305,6 @@ int step_alexnet3(Plan* P, char* ws, void* s, const float* x, const int32_t* y, 
 }
 
 constexpr int LARGE_ABOVE = 96;
-constexpr int SMALL_RECORDS = 4096;         // records times channels that a workgroup of dsspk_conv3x3_small_* adds up
 // A record buffer holds 512 records of 16 channels, four an image.  A convolution of more images would write beyond it, and the one behind would
 // refuse so many.
 constexpr int RESNET_MAX = 128;
@@ -538,7 +537,7 @@ int step_resnet(Plan* P, char* ws, void* s, const float* x, const int32_t* y, co
             RUN(dsspk_bn_bwd_dx(s, F(B.c1), w + B.g1, F(B.st1), g2, g1, g + B.g1, g + B.b1, recA0, M, B.cout, parts1));
             // both gradients, with the ReLU and the sums of the block in front, in one kernel where the kernel behind adds up as many records itself
             parts0 = small ? conv_stride2_bwd_records(m, B.H, B.cin) : 0;
-            if (parts0 > SMALL_RECORDS / B.cin) parts0 = 0;
+            if (parts0 > conv3x3_small_records(B.cin)) parts0 = 0;
             if (parts0) {
                 const ResBlock& Pv = P->blocks[bi - 1];
                 if (pend.n == WG_SCRATCH - 1) RUN(flush());

@@ -41,6 +41,17 @@ def test_a_step_reduces_no_more_filter_gradients_than_one_launch_holds():
     assert many(None, most + 1, jobs) == -1
 
 
+def test_small_steps_ask_the_small_kernels_how_many_records_they_add_up():
+    """A step leaves a stride-2 convolution's sums to the kernel behind as long as that one takes so many: the number is the kernels' own, one
+    record more is refused (before anything is launched), and 16 images with 16 channels and 32 with 32 are what just fits."""
+    L, p, q, r, n = B.lib(), 4096, 8192, 12288, None
+    most, left = L._Z21conv3x3_small_recordsi, L._Z24conv_stride2_bwd_recordsiii
+    for N, H, C in ((16, 32, 16), (32, 16, 32)):
+        assert left(N, H, C) == most(C)
+        assert L.dsspk_conv3x3_small_bwd(n, p, p, p, p, q, most(C) + 1, p, p, n, r, p, n, r, p, p, p, p, n, n, 0, 0, N, H, C) == -1
+    assert left(17, 32, 16) > most(16) and left(33, 16, 32) == 0
+
+
 def test_what_goes_between_source_files_is_one_type():
     """SplitFilterJob is passed by value from models.hip to k_conv_first.hip; its member type must be the same in both."""
     names = subprocess.run(["nm", "-C", buildlib.LIB], capture_output=True, text=True, check=True).stdout

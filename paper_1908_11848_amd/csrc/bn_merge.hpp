@@ -31,15 +31,15 @@ __host__ __device__ inline BnLayout bn_layout(long M, int C) {
     return L;
 }
 
-// Sum `v` over the lanes that share channel c = thread mod C (C a power of two up to 64), in a fixed order: within the wavefronts, then over them.
-// red: THREADS floats; result in all threads.
-__device__ __forceinline__ float reduce_sub(float v, float* red, int c, int C) {
-    for (int o = 32; o >= C; o >>= 1) v += __shfl_xor(v, o);
-    if ((threadIdx.x & 63) < C) red[threadIdx.x / 64 * C + c] = v;
+// Sum `v` over the lanes that share channel thread mod C (C a power of two up to 64), as a tree that adds the farther half of them at each step: over the
+// wavefronts, then within them.  red: THREADS floats; result in all threads.
+__device__ __forceinline__ float reduce_sub(float v, float* red, int C) {
+    static_assert(THREADS == 4 * 64, "four wavefronts");
+    const int lane = threadIdx.x & 63;
+    red[threadIdx.x] = v;
     __syncthreads();
-    float out = red[c];
-#pragma unroll
-    for (int w = 1; w < THREADS / 64; ++w) out += red[w * C + c];
+    float out = (red[lane] + red[lane + 128]) + (red[lane + 64] + red[lane + 192]);
+    for (int o = 32; o >= C; o >>= 1) out += __shfl_xor(out, o);
     __syncthreads();
     return out;
 }
@@ -84,7 +84,7 @@ __device__ __forceinline__ void bn_merge_stats(const Records& r, long M, int C, 
 #pragma unroll
         for (int u = u0; u < u0 + 8; ++u) s = fmaf(weight(u), r.v[u].x, s);
     }
-    const float mean = reduce_sub(s, red, c, C) / (float)M;
+    const float mean = reduce_sub(s, red, C) / (float)M;
     float m2 = 0.f;
 #pragma unroll
     for (int u0 = 0; u0 < 32; u0 += 8) {
@@ -95,7 +95,7 @@ __device__ __forceinline__ void bn_merge_stats(const Records& r, long M, int C, 
             m2 += n > 0.f ? r.v[u].y + n * d * d : 0.f;
         }
     }
-    m2 = reduce_sub(m2, red, c, C);
+    m2 = reduce_sub(m2, red, C);
     if (sub == 0) {
         sh[c] = mean;
         sh[C + c] = 1.0f / sqrtf(m2 / (float)M + eps);

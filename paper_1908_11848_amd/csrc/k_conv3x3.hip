@@ -102,14 +102,14 @@ __global__ __launch_bounds__(THREADS) void records_merge_kernel(const float* __r
     float s_ = 0.f;
 #pragma unroll
     for (int u = 0; u < 8; ++u) s_ = fmaf(nn[u], pv[u].x, s_);
-    const float mean = bnm::reduce_sub(s_, red, cl, CW) / (float)M;
+    const float mean = bnm::reduce_sub(s_, red, CW) / (float)M;
     float m2 = 0.f;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
         const float d = pv[u].x - mean;
         m2 += nn[u] > 0.f ? pv[u].y + nn[u] * d * d : 0.f;
     }
-    m2 = bnm::reduce_sub(m2, red, cl, CW);
+    m2 = bnm::reduce_sub(m2, red, CW);
     if (sub == 0) {
         stats[c] = mean;
         stats[C + c] = 1.0f / sqrtf(m2 / (float)M + eps);

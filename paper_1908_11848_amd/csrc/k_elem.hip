@@ -379,8 +379,8 @@ __global__ __launch_bounds__(THREADS) void bn_bwd_dx_kernel(const float* __restr
                 sg += in ? records.v[u].y : 0.f;
             }
         }
-        sb = reduce_sub(sb, red, c, C);
-        sg = reduce_sub(sg, red, c, C);
+        sb = reduce_sub(sb, red, C);
+        sg = reduce_sub(sg, red, C);
         if (sub == 0) {
             sh[c] = sb; sh[C + c] = sg;
             if (blockIdx.x == 0) { dbeta[c] = sb; dgamma[c] = sg; }

@@ -1,5 +1,6 @@
 """Sums over the records of a batch norm.  In the loaders of the 3x3 kernels: error of mean and invstd against float64 over many channels, no larger than that of
-the plain formula in fp32 (the mean of all records, then all deviations from it; a lane's records in turn, lanes in pairs, wavefronts in turn)."""
+the plain formula in fp32 (the mean of all records, then all deviations from it; a lane's records in turn, lanes in pairs, wavefronts in turn).  In the kernels
+of their own: the order of the sums, bit for bit."""
 import numpy as np
 import pytest
 
@@ -81,3 +82,38 @@ def test_error(family, batches, H, C, spread):
     rms = lambda e: np.sqrt(np.mean(np.square(np.concatenate(e, axis=1)), axis=1))
     ours, theirs = rms(ours), rms(theirs)
     assert (ours <= theirs).all(), (ours, theirs)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N", [33, 48, 96])
+@pytest.mark.parametrize("H,C", SHAPES)
+def test_tree_of_sums(N, H, C):
+    """The merge ahead of the four-wavefront kernels, 64 lanes a channel: a lane's records in turn, then a tree that adds the farther half of the lanes, bit
+    for bit (of the products one is exact and one is in an fma: one element in 100 for the emulation's double roundings)."""
+    L, s = B.lib(), stream_ptr()
+    parts = L.dsspk_conv_fwd_stat_parts(N, H, H, C, C, 3, 3, 1, 1)
+    n, M = N * H * H // parts, f32(N * H * H)
+    r = drawn(np.random.default_rng(N), parts, n, C, 1)
+    R, x, w = dev(r), dev(np.zeros((N, H, H, C), f32)), dev(np.zeros((3, 3, C, C), f32))
+    gamma, beta, act, y, st, rec = dev(np.ones(C, f32)), dev(np.zeros(C, f32)), empty((N, H, H, C)), empty((N, H, H, C)), empty(2 * C), empty((parts, C, 2))
+    assert L.dsspk_conv_records_inline(parts, C) == 0
+    assert L.dsspk_conv_fwd_prebn(s, x.data_ptr(), R.data_ptr(), parts, gamma.data_ptr(), beta.data_ptr(), EPS, None, act.data_ptr(), st.data_ptr(),
+                                  w.data_ptr(), y.data_ptr(), rec.data_ptr(), N, H, C) == 0
+    v = np.zeros((-(-parts // 64) * 64, C, 2), f32)
+    v[:parts] = r
+    v, there = v.reshape(-1, 64, C, 2), (np.arange(-(-parts // 64) * 64) < parts).reshape(-1, 64, 1)
+
+    def tree(t):
+        s = np.zeros(t.shape[1:], f32)
+        for u in t:
+            s = s + u
+        while len(s) > 1:
+            s = s[:len(s) // 2] + s[len(s) // 2:]
+        return s[0]
+
+    mean = tree(f32(n) * v[..., 0]) / M
+    d = v[..., 0] - mean
+    m2 = tree(np.where(there, (v[..., 1] + (f32(n) * d).astype(np.float64) * d).astype(f32), f32(0)))
+    got = host(st)
+    assert np.array_equal(got[:C], mean)
+    assert np.mean(got[C:] != f32(1) / np.sqrt(m2 / M + f32(EPS))) <= 0.01

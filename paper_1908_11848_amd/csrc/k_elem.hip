@@ -394,11 +394,11 @@ __global__ __launch_bounds__(THREADS) void bn_bwd_dx_kernel(const float* __restr
         for (int u = 0; u < 4; ++u) {
             const long i = i0 + u * stride;
             if (i >= total) continue;
-            float4 o;
-            o.x = ga.x * is.x * (d[u].x - db.x * inv_m - (v[u].x - mu.x) * is.x * (dg.x * inv_m));
-            o.y = ga.y * is.y * (d[u].y - db.y * inv_m - (v[u].y - mu.y) * is.y * (dg.y * inv_m));
-            o.z = ga.z * is.z * (d[u].z - db.z * inv_m - (v[u].z - mu.z) * is.z * (dg.z * inv_m));
-            o.w = ga.w * is.w * (d[u].w - db.w * inv_m - (v[u].w - mu.w) * is.w * (dg.w * inv_m));
+            float4 o;           // (fmaf: the mean of dz goes without a rounding of its own, also where the compiler takes the product out of the loop)
+            o.x = ga.x * is.x * (fmaf(-db.x, inv_m, d[u].x) - (v[u].x - mu.x) * is.x * (dg.x * inv_m));
+            o.y = ga.y * is.y * (fmaf(-db.y, inv_m, d[u].y) - (v[u].y - mu.y) * is.y * (dg.y * inv_m));
+            o.z = ga.z * is.z * (fmaf(-db.z, inv_m, d[u].z) - (v[u].z - mu.z) * is.z * (dg.z * inv_m));
+            o.w = ga.w * is.w * (fmaf(-db.w, inv_m, d[u].w) - (v[u].w - mu.w) * is.w * (dg.w * inv_m));
             *reinterpret_cast<float4*>(dx + (i >> vshift) * C + 4 * vc) = o;
         }
     }

@@ -117,3 +117,22 @@ def test_tree_of_sums(N, H, C):
     got = host(st)
     assert np.array_equal(got[:C], mean)
     assert np.mean(got[C:] != f32(1) / np.sqrt(m2 / M + f32(EPS))) <= 0.01
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,C", [(100, 4), (100, 64), (3000, 16), (50001, 32)])
+def test_gradient_behind_a_batch_norm(M, C):
+    """dx of gradients with a large mean, which cancels, from the sums the kernel stored: one rounding for d - mean, bit for bit.  (Double roundings of this
+    emulation: fewer than one element in 1000.)"""
+    g = np.random.default_rng(M + C)
+    L, s, f = B.lib(), stream_ptr(), lambda *sh: g.standard_normal(sh).astype(f32)
+    x, gamma, da = f(M, C), 1 + 0.1 * f(C), 100 + f(M, C)
+    X, G, BE, DA, y, st, dx = dev(x), dev(gamma), dev(f(C)), dev(da), empty((M, C)), empty(2 * C), empty((M, C))
+    scr, dg, db = empty(L.dsspk_bn_scratch_floats(M, C)), empty(C), empty(C)
+    assert L.dsspk_bn_fwd(s, X.data_ptr(), G.data_ptr(), BE.data_ptr(), y.data_ptr(), st.data_ptr(), scr.data_ptr(), M, C, EPS, 0, 0, None, 0, 0, 0, 0) == 0
+    assert L.dsspk_bn_bwd(s, X.data_ptr(), G.data_ptr(), st.data_ptr(), DA.data_ptr(), None, dx.data_ptr(), dg.data_ptr(), db.data_ptr(), scr.data_ptr(), M, C) == 0
+    st, dg, db, inv = host(st), host(dg), host(db), f32(1) / f32(M)
+    fma = lambda a, b, c: (a.astype(np.float64) * b + c).astype(f32)
+    d, hat = fma(-db, inv, da), (x - st[:C]) * st[C:]
+    want = gamma * st[C:] * fma(-hat, (dg * inv).astype(np.float64), d)
+    assert np.mean(host(dx) != want) < 1e-3

@@ -105,17 +105,21 @@ struct Cfg {
 // i.e. the batch norm + ReLU that separates two convolutions never runs as a pass of its own.
 // mean / invstd come from the statistics records of src, merged by a small kernel launched just before or, if they are few
 // (records_inline), by every workgroup itself; they are also what the backward pass needs.  The workgroups write `a` (their own rows).
-struct PreBn {
-    const float* records;      // statistics records of src
-    bnm::BnLayout L;           // their layout
-    long M;                    // rows of src (= N * HW * HW)
-    const float* gamma;
-    const float* beta;
+// What a kernel is handed of it stands in the base; the rest are arguments of their own (conv3x3_kernel), which this description of a launch holds for
+// the host alone.
+struct PreArgs {
+    long M, rows;              // of src (= N * HW * HW); of a record
     float eps;
-    const float* shortcut;     // PRE == 2: added before the ReLU, same shape as src ...
-    bool half;                 // ... or (C > 16) twice as high and wide with half the channels: every second pixel of it, zero beyond its channels
     float* act_out;            // a
     float* stats_out;          // mean[C], invstd[C]
+};
+struct PreBn : PreArgs {
+    const float* records;      // statistics records of src
+    int parts;                 // how many
+    const float* gamma;
+    const float* beta;
+    const float* shortcut;     // PRE == 2: added before the ReLU, same shape as src ...
+    bool half;                 // ... or (C > 16) twice as high and wide with half the channels: every second pixel of it, zero beyond its channels
     bool merge;                // every workgroup merges the records, the first one stores stats_out
 };
 
@@ -137,16 +141,18 @@ struct PostBn {
 // the gradient w.r.t. the batch norm's input xc; the workgroups also write dx (their own rows) for the
 // d-filter kernel.  The two sums come from the records of the epilogue that produced dz: added up before (TotalsJob) or, if
 // they are few, by every workgroup itself.
-struct BwdBn {
-    const float* xc;           // the batch norm's input
-    const float* stats;        // its mean[C], invstd[C]
-    const float* gamma;
-    const float* totals;       // sum dz [C], sum dz * xhat [C]; null: add up `records`
-    const float* records;      // [parts][C][2]
-    int parts;
+struct BwdArgs {
+    const float* totals;       // sum dz [C], sum dz * xhat [C]; null: add up the records
     float *dgamma, *dbeta;     // with records: sum dz * xhat and sum dz, stored by the first workgroup
     float inv_m;               // 1 / (N * HW * HW)
     float* dx_out;
+};
+struct BwdBn : BwdArgs {
+    const float* xc;           // the batch norm's input
+    const float* stats;        // its mean[C], invstd[C]
+    const float* gamma;
+    const float* records;      // [parts][C][2]
+    int parts;
 };
 
 // Gradient w.r.t. the filter in the same kernel (WG, only with PRE == 3; a workgroup has all output channels of the layer in its tile): the
@@ -314,7 +320,7 @@ template <int C, int HW, int R, int NSPLIT, int WAVES, bool TRANSPOSED, int PRE,
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_waves<C, WAVES, WG, Cfg<C, HW, R, NSPLIT, WAVES>::NT>()))) void conv3x3_kernel(
     const float* __restrict__ records, int list, int conv_blocks, const float* __restrict__ src, const float* __restrict__ beside, const uint4* __restrict__ planes,
     const float* __restrict__ norm_first, const float* __restrict__ norm_second, const float* __restrict__ wgt, const float* add, float* dst,
-    float* __restrict__ bn_partial, PreBn pre, PostBn post, BwdBn bwd, jobs::ReduceJob rj, WgradFused wg) {
+    float* __restrict__ bn_partial, PreArgs pre, PostBn post, BwdArgs bwd, jobs::ReduceJob rj, WgradFused wg) {
     using K = Cfg<C, HW, R, NSPLIT, WAVES>;
     constexpr int THREADS = K::THREADS, V = K::V, NL = K::NL;
     // Filter columns in registers.  With converted filters and two pixel tiles the next one's rows, and then what the epilogue reads and the
@@ -539,7 +545,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(min_
     float* red = reinterpret_cast<float*>(lds);         // the tile is not there yet
     if constexpr (PRE == 1 || PRE == 2) {               // mean / invstd of the input
         if (parts) {
-            const float nn = (float)pre.L.rows_per_block;
+            const float nn = (float)pre.rows;
             Share* shares = reinterpret_cast<Share*>(red);
             static_assert(WAVES * C * sizeof(Share) <= K::XB, "room for the shares");
             const Share share = merge_lanes<C, THREADS>(rec, parts, nn, tid);
@@ -1117,9 +1123,12 @@ int launch_form(hipStream_t s, const float* src, const Filter3x3& w, const float
         attr_set = true;
     }
     const int conv_blocks = N * (HW / R) * NSPLIT;
-    hipLaunchKernelGGL(kern, dim3(conv_blocks + rj.blocks), dim3(K::THREADS), LDS_BYTES, s,
-                       PRE == 3 ? bwd.records : pre.records, PRE == 3 ? (bwd.totals ? 0 : bwd.parts) : (pre.merge ? pre.L.G : 0) | (pre.half ? 1 << 16 : 0), conv_blocks, src, PRE == 3 ? bwd.xc : pre.shortcut, w.planes,
-                       PRE == 3 ? bwd.stats : pre.gamma, PRE == 3 ? bwd.gamma : pre.beta, w.w, add, dst, bn_partial, pre, post, bwd, rj, wg);
+    const int list = PRE == 3 ? bwd.totals ? 0 : bwd.parts : (pre.merge ? pre.parts : 0) | (pre.half ? 1 << 16 : 0);
+    const PreArgs& pre_args = pre;
+    const BwdArgs& bwd_args = bwd;
+    hipLaunchKernelGGL(kern, dim3(conv_blocks + rj.blocks), dim3(K::THREADS), LDS_BYTES, s, PRE == 3 ? bwd.records : pre.records, list, conv_blocks, src,
+                       PRE == 3 ? bwd.xc : pre.shortcut, w.planes, PRE == 3 ? bwd.stats : pre.gamma, PRE == 3 ? bwd.gamma : pre.beta, w.w, add, dst,
+                       bn_partial, pre_args, post, bwd_args, rj, wg);
     return (int)hipGetLastError();
 }
 

@@ -42,8 +42,8 @@ int form_fwd(void* stream, const float* src, const float* records, int parts, co
     if (!gamma || !beta || !act_out || !stats_out || act_out == src || act_out == dst || records == records_out || !form_merges<F>(parts, C) || M % parts) return -1;
     pre.records = records;
     pre.M = M;
-    pre.L.G = parts;
-    pre.L.rows_per_block = M / parts;
+    pre.parts = parts;
+    pre.rows = M / parts;
     pre.gamma = gamma; pre.beta = beta; pre.eps = eps;
     pre.shortcut = shortcut; pre.act_out = act_out; pre.stats_out = stats_out;
     pre.merge = true;

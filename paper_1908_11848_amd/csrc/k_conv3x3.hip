@@ -138,16 +138,15 @@ int conv3x3_tiled_prebn(hipStream_t s, const float* src, const float* records, i
     pre.records = records;
     pre.M = (long)N * HW * HW;
     if (in_parts < 1 || pre.M % in_parts || in_parts > 32 * (THREADS / C)) return -1;
-    pre.L = bnm::bn_layout(pre.M, C);
-    pre.L.G = in_parts;
-    pre.L.rows_per_block = pre.M / in_parts;
+    pre.parts = in_parts;
+    pre.rows = pre.M / in_parts;
     pre.gamma = gamma; pre.beta = beta; pre.eps = eps;
     pre.shortcut = shortcut; pre.act_out = act_out; pre.stats_out = stats_out;
     if (C != 16 && C != 32 && C != 64) return -2;
     if (in_parts > 8 * (THREADS / 4)) return -1;
     pre.merge = records_inline(in_parts, C);
     if (!pre.merge)
-        hipLaunchKernelGGL(records_merge_kernel, dim3(C / 4), dim3(THREADS), 0, s, records, in_parts, pre.L.rows_per_block, pre.M, C, eps, stats_out);
+        hipLaunchKernelGGL(records_merge_kernel, dim3(C / 4), dim3(THREADS), 0, s, records, in_parts, pre.rows, pre.M, C, eps, stats_out);
     if (C == 16 && HW == 32)
         return shortcut ? launch<16, 32, 8, 1, 4, false, 2>(s, src, w, nullptr, dst, bn_partial, N, pre)
                         : launch<16, 32, 8, 1, 4, false, 1>(s, src, w, nullptr, dst, bn_partial, N, pre);

@@ -4,7 +4,8 @@
 // A record is (mean, sum of squared deviations from that mean) of one channel over a slab of
 // rows; slabs have `rows_per_block` rows (the last one possibly fewer).  Records come either from
 // bn_stats_partial_kernel (row slabs) or from the epilogue of a convolution kernel (one record per
-// workgroup tile).  Every consumer merges them itself, with identical arithmetic, in its prologue.
+// workgroup tile).  Every consumer merges them itself in its prologue (or records_merge_kernel ahead of it), in a fixed order: the batch norm kernels and
+// the network's last one as bn_merge_stats does, to the same bits; the 3x3 convolutions wavefront by wavefront (conv3x3.hpp).
 #pragma once
 #include "common.hpp"
 

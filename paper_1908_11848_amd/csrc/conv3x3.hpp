@@ -8,8 +8,8 @@
 // one column of that tile's filter (three taps) in registers; a row of the next column is fetched while the products still work with the present
 // one.  In a network's step the filter comes already split (conv3x3_filter.hpp), with two pixel tiles two columns are held, and what is not needed
 // at once is fetched between the products.  Callers of single layers have the filter split here; with two pixel tiles all three columns and
-// everything else are then fetched up front.  LDS holds the halo tile and a little for the sums: 36 to 42 KB with four wavefronts, 42 to 81 KB with
-// eight, 22 to 42 KB with two pixel tiles (the last stage's d-filter beside its d-input: 57).  Registers are at most 128 with eight wavefronts, and
+// everything else are then fetched up front.  LDS holds the halo tile and a little for the sums: 36 to 45 KB with four wavefronts, 46 to 82 KB with
+// eight, 22 to 45 KB with two pixel tiles (the last stage's d-filter beside its d-input: 61).  Registers are at most 128 with eight wavefronts, and
 // what fits a compute unit of LDS and registers overlaps: one workgroup's transfers run beside another's products.
 //
 // What bounds them (110 layers, batch 128, four streams, measured where a push took 1.82 ms): registers and LDS admit 16 wavefronts to a compute unit and each

@@ -229,6 +229,21 @@ int dsspk_conv3x3_step_bwd(void* stream, int workgroups, const float* dz_dev, co
                            const float* xc_post_dev, const float* stats_post_dev, const float* gamma_post_dev, const float* beta_post_dev,
                            float* records_dev, const float* red_partial_dev, float* red_dw_dev, int red_E, int red_chunks, int red_quads, int N, int H,
                            int C);
+/* Both gradients of a stride-2 3x3 convolution of the same step (16 -> 32 channels on 32x32, 32 -> 64 on 16x16, at most 32 images): dx[N][H][H][Cin] as
+ * dsspk_conv_bwd_data_shortcut leaves it, masked by x_in_dev > 0 (the convolution's input, post-ReLU), the sums (sum dx, sum dx xhat) of the batch norm in
+ * front (input xc_post_dev, stats_post_dev) as dsspk_stride2_step_records(N, H, Cin) records (0: shape not taken), and *chunks_out (host memory)
+ * partial filter gradients as dsspk_conv_bwd_weight_parts leaves them.  dx_dev is none of the inputs. */
+int dsspk_stride2_step_records(int N, int H, int Cin);
+int dsspk_stride2_step_bwd(void* stream, const float* dy_dev, const float* w_dev, const float* shortcut_dev, float* dx_dev, float* partial_dev,
+                           const float* x_in_dev, const float* xc_post_dev, const float* stats_post_dev, float* records_dev, int N, int H, int Cin,
+                           int* chunks_out);
+/* The end of the step, 8x8 images of 64 channels: dsspk_bn_fwd_gap, dsspk_fc_softmax_xent, dx of dsspk_fc_bwd and dsspk_gap_bwd_bn_reduce in one launch.
+ * gamma_beta_dev: gamma and beta one behind the other; w_bias_dev: [64][classes] and the biases behind it; labels 0 to classes - 1.  Takes up to 128
+ * records that divide the rows, and up to 128 classes (dsspk_head_step_takes). */
+int dsspk_head_step_takes(int N, int parts, int classes);
+int dsspk_head_step(void* stream, const float* x_dev, const float* records_dev, int parts, const float* gamma_beta_dev, const float* shortcut_dev,
+                    int shortcut_half, const float* w_bias_dev, const int32_t* label_dev, float eps, float* out_dev, float* stats_dev, float* pooled_dev,
+                    float* logits_dev, float* dlogits_dev, float* row_loss_dev, float* dz_dev, float* records_out_dev, int N, int classes);
 
 /* dw[kh][kw][ci][co] = sum over batch and output pixels of x * dy.  Two stages (partial sums per
  * pixel chunk, then a fixed-order reduction).  scratch_dev: dsspk_conv_wgrad_scratch_floats(...) floats. */

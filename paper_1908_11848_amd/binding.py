@@ -132,6 +132,10 @@ _SIGNATURES = {
     "dsspk_conv3x3_filters": (c_int, [c_void_p] * 3 + [c_int]),
     "dsspk_conv3x3_step_fwd": (c_int, [c_void_p, c_int, c_void_p, c_void_p, c_int, c_void_p, c_void_p, c_float] + [c_void_p] * 7 + [c_int] * 4),
     "dsspk_conv3x3_step_bwd": (c_int, [c_void_p, c_int] + [c_void_p] * 6 + [c_int] + [c_void_p] * 16 + [c_int] * 6),
+    "dsspk_stride2_step_records": (c_int, [c_int] * 3),
+    "dsspk_stride2_step_bwd": (c_int, [c_void_p] * 10 + [c_int] * 3 + [c_void_p]),
+    "dsspk_head_step_takes": (c_int, [c_int] * 3),
+    "dsspk_head_step": (c_int, [c_void_p] * 3 + [c_int, c_void_p, c_void_p, c_int, c_void_p, c_void_p, c_float] + [c_void_p] * 8 + [c_int] * 2),
     "dsspk_conv_bwd_weight_parts": (c_int, [c_void_p] * 4 + [c_int] * 9 + [c_void_p, c_int, c_int] + [c_void_p] * 4),
     "dsspk_wgrad_reduce": (c_int, [c_void_p] * 3 + [c_int] * 2),
     "dsspk_wgrad_reduce_many": (c_int, [c_void_p, c_int] + [c_void_p] * 4),

@@ -1,7 +1,9 @@
-// The 3x3 launches of a residual network's step behind the C interface, so that the forms only a step takes (filters converted ahead, a block's
-// inner activation worked out again, the last stage's d-filter beside its d-input) can be checked and timed on their own.
+// Launches of a residual network's step behind the C interface, so that the forms only a step takes (3x3 convolutions with filters converted ahead, a
+// block's inner activation worked out again, the last stage's d-filter beside its d-input; both gradients of a stride-2 convolution; the end of the
+// network) can be checked and timed on their own.
 #include "common.hpp"
 #include "conv3x3_layers.hpp"
+#include "head.hpp"
 #include "../../include/dssp_kernels.h"
 
 namespace {
@@ -60,4 +62,23 @@ extern "C" int dsspk_conv3x3_step_bwd(void* stream, int workgroups, const float*
                                       red_partial, red_dw, red_E, red_chunks, N, H, C, gamma_post, beta_post);
     return conv3x3_tiled_dgrad_bn_wgrad(s, dz, xc, stats, gamma, totals, nullptr, 0, nullptr, nullptr, f, add, out, xc_post, stats_post, records, x_in,
                                         partial, red_partial, red_dw, red_E, red_chunks, N, H, C, gamma_post, beta_post);
+}
+
+extern "C" int dsspk_stride2_step_records(int N, int H, int Cin) { return conv_stride2_bwd_records(N, H, Cin); }
+
+extern "C" int dsspk_stride2_step_bwd(void* stream, const float* dy, const float* w, const float* shortcut, float* dx, float* partial, const float* x_in,
+                                      const float* xc_post, const float* stats_post, float* records, int N, int H, int Cin, int* chunks_out) {
+    if (!chunks_out || dx == dy || dx == x_in || dx == xc_post || partial == dx || records == partial) return -1;
+    return conv_stride2_bwd((hipStream_t)stream, dy, w, shortcut, dx, partial, BehindBn{x_in, xc_post, stats_post, records}, N, H, Cin, chunks_out);
+}
+
+extern "C" int dsspk_head_step_takes(int N, int parts, int classes) { return N >= 1 && resnet_head_takes(N, parts, classes); }
+
+extern "C" int dsspk_head_step(void* stream, const float* x, const float* records, int parts, const float* gamma_beta, const float* shortcut,
+                               int shortcut_half, const float* w_bias, const int32_t* label, float eps, float* out, float* stats, float* pooled, float* logits,
+                               float* dlogits, float* row_loss, float* dz, float* records_out, int N, int classes) {
+    if (!dsspk_head_step_takes(N, parts, classes)) return -1;
+    if (!label || !out || !stats || !pooled || !logits || !dlogits || !row_loss || !dz || !records_out || dz == out) return -1;
+    const HeadArgs a = {out, stats, label, pooled, logits, dlogits, row_loss, dz, records_out, eps, 1.f / (float)N, (int)((long)N * 64 / parts), classes};
+    return resnet_head((hipStream_t)stream, x, records, parts, gamma_beta, shortcut, shortcut_half != 0, w_bias, N, a);
 }

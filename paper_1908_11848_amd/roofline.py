@@ -33,12 +33,13 @@ A case is bound by whichever of its two floors is higher: its FLOP at 2517 TFLOP
 x 4 SIMDs x 1024 FLOP/cycle x 2.4 GHz) or its bytes at 8 TB/s (HBM).  HBM traffic per launch (`traffic`)
 comes from profiles/traffic_counters.json (counter values scaled by what the same counter reads
 for the snapshot-copy kernel of known size) and is reported as null as soon as the kernel's
-source file differs from the one the counters were taken on.
+source file, or a header that it includes, differs from the one the counters were taken on.
 """
 import ctypes
 import hashlib
 import json
 import os
+import re
 
 PEAK_MFMA = 2516.6e12
 PEAK_HBM = 8.0e12
@@ -48,7 +49,23 @@ _COUNTERS = os.path.join(os.path.dirname(_HERE), "profiles", "traffic_counters.j
 STAGES = ((32, 16), (16, 32), (8, 64))      # (height = width, channels) of the three ResNet stages
 BATCH = 128
 N_PARAMS = 1_733_812                         # ResNet-110, 10 classes
-SOURCES = ("conv3x3.hpp", "conv3x3_forms.hpp", "conv3x3_filter.hpp", "conv3x3_layers.hpp", "k_conv3x3_step.hip", "k_conv3x3_large.hip", "k_conv3x3.hip", "k_conv.hip", "k_elem.hip", "k_server.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp", "common.hpp")
+
+
+def with_headers(*files):
+    """These source files and every header of the same folder that they include, directly or not."""
+    out, todo = [], list(files)
+    while todo:
+        f = todo.pop(0)
+        if f not in out:
+            out.append(f)
+            with open(os.path.join(_HERE, "csrc", f)) as src:
+                todo += re.findall(r'^#include "([^"/]+)"', src.read(), re.M)
+    return tuple(out)
+
+
+_CONV_SRCS = with_headers("k_conv3x3_step.hip", "k_conv3x3_large.hip", "k_conv3x3.hip", "k_conv.hip")
+_BN_SRCS, _SERVER_SRCS, _WIDE_SRCS = with_headers("k_elem.hip"), with_headers("k_server.hip"), with_headers("k_conv_split.hip")
+SOURCES = tuple(dict.fromkeys(_CONV_SRCS + _BN_SRCS + _SERVER_SRCS))         # what the counters are taken on
 
 
 def case_list(n_params=N_PARAMS):
@@ -97,9 +114,6 @@ def _traffic(key, srcs):
     if not e or any(db.get("source_hash", {}).get(s) != source_hash(s) for s in srcs):
         return None
     return int(e["fetch_bytes"] + e["write_bytes"])
-
-
-_CONV_SRCS = ("conv3x3.hpp", "conv3x3_forms.hpp", "conv3x3_filter.hpp", "conv3x3_layers.hpp", "k_conv3x3_step.hip", "k_conv3x3_large.hip", "k_conv3x3.hip", "k_conv.hip", "jobs.hpp", "bn_merge.hpp", "mma.hpp", "split.hpp")
 
 
 def _conv_cases(H, C, dev):
@@ -197,7 +211,7 @@ def cases(dev, n_params=N_PARAMS):
     out = []
     for H, C in STAGES:
         out += [c[:6] + (_CONV_SRCS, c[6]) for c in _conv_cases(H, C, dev)]
-    out += [c[:6] + (("k_elem.hip", "bn_merge.hpp"), c[6]) for c in _bn_cases(32, 16, dev)]
+    out += [c[:6] + (_BN_SRCS, c[6]) for c in _bn_cases(32, 16, dev)]
     L = B.lib()
     for n in sorted({n_params, 25_000_000}):
         w = torch.randn(n, device=dev)
@@ -207,10 +221,10 @@ def cases(dev, n_params=N_PARAMS):
         pw, pg, pd, ps = w.data_ptr(), g.data_ptr(), dst.data_ptr(), st.data_ptr()      # pointers taken once: these
         out.append(("apply_%d" % n, "apply_kernel (%d params)" % n, 0.0, 12.0 * n,      # kernels are as short as a launch
                     lambda s, pw=pw, pg=pg, ps=ps, n=n: L.dsspk_apply(s, pw, pg, n, 1e-3, ps, 1),
-                    None, ("k_server.hip",), (w, g, st)))
+                    None, _SERVER_SRCS, (w, g, st)))
         out.append(("pull_%d" % n, "pull_kernel (%d params)" % n, 0.0, 8.0 * n,
                     lambda s, pw=pw, pd=pd, ps=ps, n=n: L.dsspk_pull(s, pd, pw, n, ps + 8, ps),
-                    None, ("k_server.hip",), (w, dst, st)))
+                    None, _SERVER_SRCS, (w, dst, st)))
     # the two fused server kernels at the stress size: apply + the pusher's pull in one pass (16 B/param), and four
     # simultaneous pushes with one snapshot in one pass (4 * 4 + 8 + 4 = 28 B/param instead of 4 * 12 + 8 = 56)
     n = 25_000_000
@@ -222,14 +236,14 @@ def cases(dev, n_params=N_PARAMS):
     pg = gs[0].data_ptr()
     out.append(("apply_pull_%d" % n, "apply_pull_kernel: update + the pusher's snapshot in one pass (%d params)" % n, 0.0, 16.0 * n,
                 lambda s, pw=pw, pg=pg, pd=pd, ps=ps, n=n: L.dsspk_apply_pull(s, pw, pg, pd, n, 1e-3, ps, ps + 8, 1),
-                None, ("k_server.hip",), (w, gs, dst, st)))
+                None, _SERVER_SRCS, (w, gs, dst, st)))
     g_arr = (ctypes.c_void_p * 4)(*[g.data_ptr() for g in gs])
     d_arr = (ctypes.c_void_p * 1)(pd)
     a_arr = (ctypes.c_int * 1)(4)
     s_arr = (ctypes.c_void_p * 1)(ps + 8)
     out.append(("apply_many4_%d" % n, "apply_many_kernel: 4 simultaneous pushes + 1 snapshot in one pass (%d params)" % n, 0.0, 28.0 * n,
                 lambda s, pw=pw, ps=ps, n=n: L.dsspk_apply_many(s, pw, 4, g_arr, n, 1e-3, 1, d_arr, a_arr, s_arr, ps, 1),
-                None, ("k_server.hip",), (w, gs, dst, st, g_arr, d_arr, a_arr, s_arr)))
+                None, _SERVER_SRCS, (w, gs, dst, st, g_arr, d_arr, a_arr, s_arr)))
     assert [c[0] for c in out] == [k for k, _, _ in case_list(n_params)]
     return out
 
@@ -270,7 +284,7 @@ def _alexnet_conv2_case(dev):
     fn = lambda s: L.dsspk_conv_split_fwd(s, x.data_ptr(), planes.data_ptr(), b.data_ptr(), y.data_ptr(), N, H, H, C, C, 5, 2, 1)
     flops = 6 * 2.0 * N * H * H * C * 25 * C
     return ("alexnet_conv2_fwd", "conv 5x5 forward + bias + ReLU 64->64 @15x15, batch %d (three bf16 terms)" % N, flops,
-            2 * 4.0 * N * H * H * C, fn, prep, ("k_conv_split.hip", "split.hpp"), (x, w, b, y, planes))
+            2 * 4.0 * N * H * H * C, fn, prep, _WIDE_SRCS, (x, w, b, y, planes))
 
 
 def measure(workload, em):

@@ -56,11 +56,11 @@ def test_what_is_refused():
 HEAD_OUT = ("out", "stats", "pooled", "logits", "dlogits", "row_loss", "dz", "records")
 
 
-def head_inputs(N, classes, half, kind="ordinary"):
+def head_inputs(N, classes, half, kind="ordinary", parts=None):
     g = np.random.default_rng(N + classes)
     f = lambda *sh: g.standard_normal(sh).astype(np.float32)
     x, w, bias, gamma, sc = f(N, 64, 64) + 0.3, 0.3 * f(64, classes), f(classes), 1 + 0.1 * f(64), f(N, 16, 16, 32) if half else f(N, 64, 64)
-    r = x.astype(np.float64)
+    r = x.astype(np.float64).reshape(parts or N, -1, 64)
     m = r.mean(1)
     rec = np.stack([m, ((r - m[:, None]) ** 2).sum(1)], axis=2).astype(np.float32)
     sc.reshape(-1)[7] = {"inf": np.inf, "nan": np.nan, "far": 3e38}.get(kind, sc.reshape(-1)[7])
@@ -81,32 +81,33 @@ def head_outputs(N, classes):
                 dz=empty((N, 64, 64)), records=empty((N, 64, 2)))
 
 
-def head(t, N, classes, half):
+def head(t, N, classes, half, parts=None):
     o, L, P = head_outputs(N, classes), B.lib(), {k: v.data_ptr() for k, v in t.items()}
-    assert L.dsspk_head_step(stream_ptr(), P["x"], P["rec"], N, P["gb"], P["sc"], int(half), P["wb"], P["label"], 1e-5, *(o[k].data_ptr() for k in HEAD_OUT), N, classes) == 0
+    assert L.dsspk_head_step(stream_ptr(), P["x"], P["rec"], parts or N, P["gb"], P["sc"], int(half), P["wb"], P["label"], 1e-5, *(o[k].data_ptr() for k in HEAD_OUT), N, classes) == 0
     return o
 
 
-def one_by_one(t, N, classes, half):
+def one_by_one(t, N, classes, half, parts=None):
     o, L, s, P = head_outputs(N, classes), B.lib(), stream_ptr(), {k: v.data_ptr() for k, v in t.items()}
     O = {k: v.data_ptr() for k, v in o.items()}
     w, bias, dp, dw, db = P["wb"], P["wb"] + 4 * 64 * classes, empty((N, 64)), empty((64, classes)), empty(classes)
-    assert L.dsspk_bn_fwd_gap(s, P["x"], P["gb"], P["gb"] + 256, O["out"], O["stats"], P["rec"], N, P["sc"], int(half), O["pooled"], N, 8, 64, 1e-5) == 0
+    assert L.dsspk_bn_fwd_gap(s, P["x"], P["gb"], P["gb"] + 256, O["out"], O["stats"], P["rec"], parts or N, P["sc"], int(half), O["pooled"], N, 8, 64, 1e-5) == 0
     assert L.dsspk_fc_softmax_xent(s, O["pooled"], w, bias, P["label"], O["logits"], O["dlogits"], O["row_loss"], N, 64, classes) == 0
     assert L.dsspk_fc_bwd(s, O["pooled"], O["dlogits"], w, dw.data_ptr(), db.data_ptr(), dp.data_ptr(), 0, None, None, N, 64, classes) == 0
     assert L.dsspk_gap_bwd_bn_reduce(s, dp.data_ptr(), P["x"], O["stats"], O["out"], O["dz"], O["records"], N, 8, 64) == 0
     return o
 
 
-HEADS = [(1, 2, False), (13, 7, True), (5, 64, False), (3, 65, True), (37, 127, False), (128, 100, True), (128, 128, False)]
+HEADS = [(1, 2, False, 1), (13, 7, True, 13), (5, 64, False, 5), (3, 65, True, 3), (37, 127, False, 37), (128, 100, True, 128), (128, 128, False, 128),
+         (6, 10, False, 1), (4, 10, True, 128), (200, 10, False, 100)]          # the last three: records of several images, of a part of one
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("N,classes,half", HEADS)
-def test_head(N, classes, half):
+@pytest.mark.parametrize("N,classes,half,parts", HEADS)
+def test_head(N, classes, half, parts):
     """Bounds: a sum of n terms is off by at most n roundings of the sum of their magnitudes; e carries one stage's bound into the next."""
-    t = head_inputs(N, classes, half)
-    o, one = head(t, N, classes, half), one_by_one(t, N, classes, half)
+    t = head_inputs(N, classes, half, parts=parts)
+    o, one = head(t, N, classes, half, parts), one_by_one(t, N, classes, half, parts)
     same(o["out"], one["out"], "output")
     same(o["stats"], one["stats"], "mean, invstd")
     out, stats, wb, label = f64(o["out"]), f64(o["stats"]), f64(t["wb"]), host(t["label"])
